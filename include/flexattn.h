@@ -377,9 +377,9 @@ int flexattn_paged_forward(const flexattn_dims* dims, const flexattn_tensor* Q,
  * Device-side values are not trusted: a context length outside [0, max_pages * page_size] is clamped to
  * that range and a page id outside [0, n_pool_pages) to the nearest valid page, so that wrong tables
  * give wrong rows and never an access outside the table, the pools or the workspace.
- * The KV range is cut into splits of 128 ... 1024 keys, one wave each; the split length is chosen
+ * The KV range is cut into splits of 128 ... 2048 keys, one workgroup each; the split length is chosen
  * from nseq * Hkv * max_pages * page_size so that the launch still fills the chip when the batch is
- * small (flexattn_paged_decode_workspace_bytes accounts for it).  mask_id: FLEXATTN_MASK_CTX_LEN (which, with the query at
+ * small (flexattn_paged_decode_workspace_bytes covers it).  mask_id: FLEXATTN_MASK_CTX_LEN (which, with the query at
  * q_idx = ctx_len - 1, is also the causal mask of a decode step: the offset conversion of section 5.2) or
  * FLEXATTN_MASK_CTX_LEN_WINDOW (additionally q_idx - kv_idx <= params->window; splits wholly below the
  * window are skipped).

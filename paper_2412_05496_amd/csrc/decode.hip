@@ -1,17 +1,22 @@
 // Paged split-KV decode (decoding template of paper section 4.1; page-table indirection fused
 // into the KV-block walk as in section 5.1) and the partial-softmax combine.
 //
-// The path is bound by reading K and V once from HBM.  One WAVE owns one (sequence, KV head,
-// KV split) and never synchronises with another: it walks its logical pages 32 keys at a time,
-// looks each key's page up in the page table and pulls the K and V rows straight from the pool into
-// its private, XOR-swizzled LDS tiles (global_load_lds_dwordx4: every wave instruction moves 1 KiB
-// of whole 256-byte rows, so the page gather is fully coalesced; non-temporal, since a decode step
-// reads every K / V row exactly once); the gather of the next tile is
-// started as soon as the current tile's operand fragments sit in registers.  S^T = K Q^T takes K rows from
-// LDS as the A operand with the G query heads of the group as (zero-padded) columns of the B
-// operand, so K and V are read once per KV head, never once per query head; V^T comes out of the
-// row-major V tile through the transposing LDS read.  Each wave leaves (m, l, O) of its split in
-// the workspace; the combine kernel merges the splits of a (sequence, head) with log-sum-exp weights.
+// The path is bound by reading K and V once from HBM; a small batch is bound by latency: launches, the
+// chain context length -> page id -> K / V rows, and the per-tile arithmetic that nothing else hides.  One
+// WORKGROUP of four waves owns one (sequence, KV head, KV split); the waves take its 32-key tiles in turn
+// and do not synchronise until the end: each walks the logical pages of its keys, looks every key's page
+// up in the page table and pulls the K and V rows straight from the pool into its private, XOR-swizzled
+// LDS tiles (global_load_lds_dwordx4: every wave instruction moves 1 KiB of whole 256-byte rows, so the
+// page gather is fully coalesced; non-temporal, since a decode step reads every K / V row exactly once);
+// the gather of its next tile is started as soon as the current tile's operand fragments sit in registers.
+// S^T = K Q^T takes K rows from LDS as the A operand with the G <= 16 query heads of the group as the
+// columns of the B operand (16x16x32 MFMAs), so K and V are read once per KV head, never once per query
+// head; V^T comes out of the row-major V tile through the transposing LDS read.  The waves' (m, l, O) are
+// merged in LDS into one result of the split; the combine kernel merges the splits of a (sequence, head)
+// with log-sum-exp weights, and is not needed where a sequence has a single split.
+// Measured on MI355X, 32 query / 8 KV heads, D = 128, 16-token pages (before: one wave per split, 32-column
+// MFMAs, one wave per head walking the splits in the combine): one sequence of 8k tokens 33 -> 14 us, of 32k
+// 69 -> 27, four of 8k 40 -> 26, sixteen of 8k 102 -> 86 (6.2 TB/s), 64 of 1k to 32k 783 -> 718 (6.8 TB/s).
 #include <mutex>
 
 #include "flex_common.h"
@@ -25,11 +30,10 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace flexattn {
 
-constexpr int kDecWaves = 4;       // waves per workgroup (the mapping below assumes 4)
+constexpr int kDecWaves = 4;       // waves per workgroup, all on one split
 constexpr int kDecTile = 32;       // keys per inner tile
-constexpr int kDecSplitMax = 1024; // keys per split: a power of two in [kDecSplitMin, kDecSplitMax],
+constexpr int kDecSplitMax = 2048; // keys per split: a power of two in [kDecSplitMin, kDecSplitMax],
 constexpr int kDecSplitMin = 128;  // chosen by the host so that the launch fills the chip (split_len_of)
-constexpr int kDecTargetWaves = 256 * 4;   // one wave per SIMD: finer cuts cost more per-wave start-up than they gain
 
 struct DecodeArgs {
     const bf16* Q;
@@ -52,70 +56,85 @@ struct DecodeArgs {
     float* LSE;
 };
 
+// The values of the two lanes l, l ^ 16 (SWAP16) or l, l ^ 32 in one order or the other, so that a
+// commutative operation on the pair is a reduction over it.  (Inline assembly: the compiler at hand
+// hands the first result of the swap builtins out for both.  The s_nop covers the wait states between
+// the vector instruction that wrote v and the swap.)
+struct LanePair {
+    float a, b;
+};
+template <bool SWAP16>
+__device__ __forceinline__ LanePair lane_pair(float v) {
+    LanePair p = {v, v};
+    if constexpr (SWAP16) asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(p.a), "+v"(p.b));
+    else asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(p.a), "+v"(p.b));
+    return p;
+}
+// reductions over the four lanes that hold the same query column (lanes l, l ^ 16, l ^ 32, l ^ 48)
+__device__ __forceinline__ float column_max(float v) {
+    const LanePair p = lane_pair<true>(v);
+    const LanePair q = lane_pair<false>(fmaxf(p.a, p.b));
+    return fmaxf(q.a, q.b);
+}
+__device__ __forceinline__ float column_sum(float v) {
+    const LanePair p = lane_pair<true>(v);
+    const LanePair q = lane_pair<false>(p.a + p.b);
+    return q.a + q.b;
+}
+
+// D[16x16] += A[16x32] * B[32x16]: lane l supplies A[row = l % 16][k-slots of group l / 16] and
+// B[k-slots of group l / 16][col = l % 16]; register i of lane l holds D[row = 4 * (l / 16) + i][col = l % 16].
+// The G <= 16 query heads of a KV head are the columns: half the multiplications, softmax
+// instructions and accumulators of a 32-column tile whose upper columns no head would use.
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
 template <int D, uint32_t SCORE>
-__global__ __launch_bounds__(kDecWaves * 64, 2) void decode_split_kernel(const DecodeArgs a) {
+__global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_split_kernel(const DecodeArgs a) {
     constexpr int DC = D / 8;                  // 16-byte chunks per row
     constexpr int RPI = 64 / DC;               // rows per wave instruction
     constexpr int NI = kDecTile / RPI;         // instructions per tile and tensor
     constexpr int TILE = kDecTile * D;         // elements
+    constexpr int NKC = D / 32, NDB = D / 16;  // 32-dim slices of the score product, 16-dim blocks of O
+    constexpr int OROW = D + 4;                // floats per query row of a wave's O in LDS (padded: 16 rows, no conflicts)
     __shared__ __attribute__((aligned(1024))) bf16 smem[kDecWaves * 2 * TILE];   // per wave: K tile, V tile
+    __shared__ float s_ml[kDecWaves][2][16];   // per wave: running max, sum of the 16 query columns
+    static_assert(16 * OROW * 4 <= 2 * TILE * 2, "a wave's O must fit its own K and V tiles");
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
-    // workgroup -> consecutive splits of one (sequence, KV head): blockIdx.x walks the (sequence, KV
-    // head) units, blockIdx.y the groups of splits, so the splits of a long sequence are spread over the
-    // launch.  When a sequence has fewer splits than a workgroup has waves, the spare waves take the
-    // following units instead of idling.
-    const int spw = a.max_splits >= 4 ? 4 : (a.max_splits >= 2 ? 2 : 1);   // splits per workgroup
-    const int upw = kDecWaves / spw;                     // units per workgroup
-    const int split = blockIdx.y * spw + wave % spw;
-    const int unit = blockIdx.x * upw + wave / spw;
-    if (unit >= a.nseq * a.Hkv || split >= a.max_splits) return;
+    const int tid = threadIdx.x, lane = tid & 63, grp = lane >> 4, l16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int unit = blockIdx.x, split = blockIdx.y + gridDim.y * blockIdx.z;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     // A context length beyond what the page table addresses (or a negative one) is clamped, and so is
     // every page id below: wrong device-side tables give wrong rows, never an access outside the
     // table, the pools or the workspace.
-    const int ctx = min(max(a.ctx_lens[b], 0), a.max_ctx);
+    const int ctx = min(max(ldc(a.ctx_lens + b), 0), a.max_ctx);
     // The query sits at q_idx = ctx - 1 (the offset of the decode step), so "causal" is kv < ctx and a
     // sliding window adds the lower bound kv >= q_idx - window.
     const int kv_lo = a.window >= 0 ? max(ctx - 1 - a.window, 0) : 0;
     const int tok_begin = split * a.split_len;
-    if (tok_begin >= ctx || tok_begin + a.split_len <= kv_lo) return;   // wave-uniform; the kernel has no barriers
+    if (tok_begin >= ctx || tok_begin + a.split_len <= kv_lo) {         // (uniform over the workgroup)
+        if (ctx == 0 && split == 0) {
+            for (int i = tid; i < a.G * D / 8; i += kDecWaves * 64)
+                *(u32x4*)(a.O + ((int64_t)b * a.Hq + hkv * a.G) * D + i * 8) = u32x4{0, 0, 0, 0};
+            if (a.LSE && tid < a.G) a.LSE[(int64_t)b * a.Hq + hkv * a.G + tid] = -INFINITY;
+        }
+        return;
+    }
     const int tok_end = min(ctx, tok_begin + a.split_len);
-    const int tok_first = max(tok_begin, kv_lo & ~(kDecTile - 1));    // first tile that holds a visible key
+    // the four waves take the 32-key tiles of the split in turn, from the first tile that holds a visible key
+    const int tok_first = max(tok_begin, kv_lo & ~(kDecTile - 1)) + wave * kDecTile;
+    constexpr int kStep = kDecWaves * kDecTile;
     bf16* k_tile = smem + wave * 2 * TILE;
     bf16* v_tile = k_tile + TILE;
 
-    const int g_lane = l32;                             // query head of the group held by this lane
-    const bool g_ok = g_lane < a.G;
-    const int hq = hkv * a.G + (g_ok ? g_lane : 0);
-    bf16x8 qf[D / 16];
-    {
-        const bf16* qp = a.Q + (int64_t)b * a.q_stride_seq + (int64_t)hq * D + half * 8;
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-            u32x4 v = *(const u32x4*)(qp + ks * 16);
-            if (!g_ok) v = u32x4{0, 0, 0, 0};
-            qf[ks] = __builtin_bit_cast(bf16x8, v);
-        }
-    }
-    const ScoreMod<SCORE> smod(a.p, hq, a.scale);
-    const int q_idx = ctx - 1;
     const int32_t* pt = a.page_table + (int64_t)b * a.pt_stride;
     const int page_mask = a.page_size - 1;
     const int64_t slab = (int64_t)a.page_size * D;      // elements per (page, head)
-    const RowReader<D> k_reader(l32, half, lds_addr(k_tile));
-    const TrReader<D> v_reader(lane, lds_addr(v_tile));
-
-    f32x16 oacc[D / 32];
-#pragma unroll
-    for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[db][r] = 0.0f;
-    float m_run = -INFINITY, l_run = 0.0f;
-
     // Page ids of the rows this lane fetches for one tile (NI wave instructions, RPI rows each; rows
     // past the context re-read the last key).
     auto lookup = [&](int tok0, int (&pg)[NI]) __attribute__((always_inline)) {
@@ -139,158 +158,236 @@ __global__ __launch_bounds__(kDecWaves * 64, 2) void decode_split_kernel(const D
             dma_global_nt(lds_addr(v_tile + i * 512), a.V_pool + off);
         }
     };
-
     int pg_next[NI];
-    lookup(tok_first, pg_next);
-    gather(tok_first, pg_next);
-    if (tok_first + kDecTile < tok_end) lookup(tok_first + kDecTile, pg_next);
+    if (tok_first < tok_end) {
+        lookup(tok_first, pg_next);
+        gather(tok_first, pg_next);
+        if (tok_first + kStep < tok_end) lookup(tok_first + kStep, pg_next);
+    }
 
-    for (int tok0 = tok_first; tok0 < tok_end; tok0 += kDecTile) {
+    const bool g_ok = l16 < a.G;                        // query head of the group held by this lane: l16
+    const int hq = hkv * a.G + (g_ok ? l16 : 0);
+    bf16x8 qf[NKC];                                     // column l16, dims 32 kc + 8 grp ..
+    {
+        const bf16* qp = a.Q + (int64_t)b * a.q_stride_seq + (int64_t)hq * D + grp * 8;
+#pragma unroll
+        for (int kc = 0; kc < NKC; ++kc) {
+            u32x4 v = *(const u32x4*)(qp + kc * 32);
+            if (!g_ok) v = u32x4{0, 0, 0, 0};
+            qf[kc] = __builtin_bit_cast(bf16x8, v);
+        }
+    }
+    const ScoreMod<SCORE> smod(a.p, hq, a.scale);
+    const int q_idx = ctx - 1;
+
+    // LDS byte addresses of the operand reads for the first 16 keys (rows r + 16 have the swizzle of r).
+    // K: row l16, 16-byte chunk 4 kc + grp.  V^T: transposing reads; group grp covers rows 4 grp .. +3 and
+    // 16 + 4 grp .. +3 -- the keys whose scores the lanes of the group hold.
+    uint32_t k_off[NKC], v_off[NDB];
+#pragma unroll
+    for (int kc = 0; kc < NKC; ++kc) k_off[kc] = lds_addr(k_tile) + 2u * (uint32_t)tile_off<D>(l16, 4 * kc + grp);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) {
+        const int row = 4 * grp + (l16 >> 2), col = 16 * db + 4 * (l16 & 3);
+        v_off[db] = lds_addr(v_tile) + 2u * (uint32_t)(tile_off<D>(row, col >> 3) + (col & 7));
+    }
+
+    f32x4 oacc[NDB];                                    // O^T: dims 16 db + 4 grp + i of query l16
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) oacc[db] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    float m_run = -INFINITY, l_run = 0.0f;
+
+    for (int tok0 = tok_first; tok0 < tok_end; tok0 += kStep) {
         // ---- tile tok0 has landed; take every operand fragment out of LDS, then start the gather of
         // the next tile into the same (wave-private) buffers so that it runs beside this tile's compute
         wait_vmem();
-        bf16x8 kfr[D / 16], vfr[D / 32][2];
+        bf16x8 kfr[2][NKC], vfr[NDB];
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) kfr[ks] = k_reader.read(0, 0, ks);
+        for (int kc = 0; kc < NKC; ++kc)
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db)
+            for (int kb = 0; kb < 2; ++kb)
+                kfr[kb][kc] = *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)(k_off[kc] + kb * 16 * D * 2);
 #pragma unroll
-            for (int c = 0; c < 2; ++c) vfr[db][c] = v_reader.read(0, 16 * c, db);
-        if (tok0 + kDecTile < tok_end) {
+        for (int db = 0; db < NDB; ++db) {
+            const u32x2 lo = lds_read_tr4(v_off[db]), hi = lds_read_tr4(v_off[db] + 16 * D * 2);
+            vfr[db] = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+        }
+        if (tok0 + kStep < tok_end) {
             __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): the fragments are in registers
-            gather(tok0 + kDecTile, pg_next);
-            if (tok0 + 2 * kDecTile < tok_end) lookup(tok0 + 2 * kDecTile, pg_next);
+            gather(tok0 + kStep, pg_next);
+            if (tok0 + 2 * kStep < tok_end) lookup(tok0 + 2 * kStep, pg_next);
         }
 
-        // ---- S^T = K Q^T
-        f32x16 sacc;
+        // ---- S^T = K Q^T for the two 16-key blocks
+        f32x4 sacc[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[r] = 0.0f;
+        for (int kc = 0; kc < NKC; ++kc)
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) sacc = mfma32(kfr[ks], qf[ks], sacc);
+            for (int kb = 0; kb < 2; ++kb) sacc[kb] = mfma16(kfr[kb][kc], qf[kc], sacc[kb]);
 
         // ---- score_mod, mask kv_lo <= kv < ctx_len (only the first and the last tile can hold masked
         // keys), softmax
         const bool ragged = tok0 + kDecTile > tok_end || tok0 < kv_lo;
-        float mx = -INFINITY;
+        float x[8], mx = -INFINITY;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int kv = tok0 + crow(r, half);
-            float x = smod.apply(sacc[r], q_idx - kv);
-            if (ragged && (kv >= tok_end || kv < kv_lo)) x = -INFINITY;
-            sacc[r] = x;
-            mx = fmaxf(mx, x);
+        for (int e = 0; e < 8; ++e) {
+            const int kv = tok0 + 16 * (e >> 2) + 4 * grp + (e & 3);
+            x[e] = smod.apply(sacc[e >> 2][e & 3], q_idx - kv);
+            if (ragged && (kv >= tok_end || kv < kv_lo)) x[e] = -INFINITY;
+            mx = fmaxf(mx, x[e]);
         }
-        mx = fmaxf(mx, swap_halves(mx));
+        mx = column_max(mx);
         const float m_new = fmaxf(m_run, mx);          // finite: every tile holds at least one key
         const float alpha = fast_exp2(m_run - m_new);
         m_run = m_new;
         float psum = 0.0f;
-        bf16x8 pf[2];
+        u32x4 pk;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            u32x4 pk;
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const float p0 = fast_exp2(sacc[8 * c + 2 * jj] - m_new);
-                const float p1 = fast_exp2(sacc[8 * c + 2 * jj + 1] - m_new);
-                psum += p0 + p1;
-                pk[jj] = pack_bf16(p0, p1);
-            }
-            pf[c] = __builtin_bit_cast(bf16x8, pk);
+        for (int jj = 0; jj < 4; ++jj) {
+            const float p0 = fast_exp2(x[2 * jj] - m_new), p1 = fast_exp2(x[2 * jj + 1] - m_new);
+            psum += p0 + p1;
+            pk[jj] = pack_bf16(p0, p1);
         }
+        const bf16x8 pf = __builtin_bit_cast(bf16x8, pk);
         l_run = l_run * alpha + psum;
         if (__any(alpha != 1.0f)) {
 #pragma unroll
-            for (int db = 0; db < D / 32; ++db)
+            for (int db = 0; db < NDB; ++db)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+                for (int i = 0; i < 4; ++i) oacc[db][i] *= alpha;
         }
 
         // ---- O^T += V^T P^T
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) oacc[db] = mfma32(vfr[db][c], pf[c], oacc[db]);
+        for (int db = 0; db < NDB; ++db) oacc[db] = mfma16(vfr[db], pf, oacc[db]);
     }
 
-    const float l_tot = l_run + swap_halves(l_run);
+    // ---- the four waves' (m, l, O) become one result of the split.  Every wave leaves its part in its own
+    // tiles (all of whose reads and loads are done); a wave without a tile contributes weight 0.
+    const float l_tot = column_sum(l_run);
+    float* o_wave = (float*)k_tile;
     if (g_ok) {
-        const int64_t out_item = ((int64_t)b * a.Hq + hq) * a.max_splits + split;
-        float* po = a.part_O + out_item * D;
 #pragma unroll
-        for (int db = 0; db < D / 32; ++db)
+        for (int db = 0; db < NDB; ++db) *(f32x4*)(o_wave + l16 * OROW + 16 * db + 4 * grp) = oacc[db];
+        if (grp == 0) {
+            s_ml[wave][0][l16] = m_run;
+            s_ml[wave][1][l16] = l_tot;
+        }
+    }
+    __syncthreads();
+    // The only non-empty split of a sequence writes the final O and LSE; the combine kernel leaves such
+    // sequences alone.
+    const bool only = (ctx - 1) / a.split_len == kv_lo / a.split_len;
+    for (int it = tid; it < a.G * (D / 4); it += kDecWaves * 64) {
+        const int g = it / (D / 4), d = (it % (D / 4)) * 4;
+        float m = s_ml[0][0][g];
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                f32x4 v = {oacc[db][4 * rg], oacc[db][4 * rg + 1], oacc[db][4 * rg + 2], oacc[db][4 * rg + 3]};
-                *(f32x4*)(po + db * 32 + 8 * rg + 4 * half) = v;
-            }
-        if (half == 0) {
-            a.part_ml[out_item * 2] = m_run;
-            a.part_ml[out_item * 2 + 1] = l_tot;
+        for (int w = 1; w < kDecWaves; ++w) m = fmaxf(m, s_ml[w][0][g]);
+        float L = 0.0f;
+        f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int w = 0; w < kDecWaves; ++w) {
+            const float wgt = fast_exp2(s_ml[w][0][g] - m);
+            L += wgt * s_ml[w][1][g];
+            o += wgt * *(const f32x4*)((const float*)(smem + w * 2 * TILE) + g * OROW + d);
+        }
+        const int64_t head = (int64_t)b * a.Hq + hkv * a.G + g;
+        if (only) {
+            const float inv = 1.0f / L;
+            *(u32x2*)(a.O + head * D + d) = u32x2{pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv)};
+            if (d == 0 && a.LSE) a.LSE[head] = (m + fast_log2(L)) * kLn2;
+        } else {
+            const int64_t item = head * a.max_splits + split;
+            *(f32x4*)(a.part_O + item * D + d) = o;
+            if (d == 0) *(float2*)(a.part_ml + item * 2) = make_float2(m, L);
         }
     }
 }
 
-// One wave per (sequence, query head): O = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max m).
+// One workgroup per (sequence, query head): O = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max m).
+// The rows of the splits are read side by side by 256 threads (8 rows at a time for D = 128), the first of
+// them before the maximum is known: what bounds this kernel is the latency of its loads, of which a wave
+// that walks the splits one after the other pays one per split.
 template <int D>
-__global__ __launch_bounds__(64) void decode_combine_kernel(const DecodeArgs a) {
-    const int lane = threadIdx.x;
+__global__ __launch_bounds__(kDecWaves * 64) void decode_combine_kernel(const DecodeArgs a) {
+    constexpr int LPR = D / 4, ROWS = kDecWaves * 64 / LPR, PRE = 4;   // lanes per row, rows side by side
+    __shared__ float s_o[ROWS][D + 4];
+    __shared__ float s_l[ROWS];
+    const int tid = threadIdx.x, lane = tid & 63, r0 = tid / LPR, d = (tid % LPR) * 4;
     const int b = blockIdx.x / a.Hq, hq = blockIdx.x % a.Hq;
-    const int ctx = min(max(a.ctx_lens[b], 0), a.max_ctx);                          // as in the split kernel
+    const int ctx = min(max(ldc(a.ctx_lens + b), 0), a.max_ctx);                    // as in the split kernel
     const int ns = (ctx + a.split_len - 1) / a.split_len;                           // <= max_splits
     const int s0 = a.window >= 0 ? max(ctx - 1 - a.window, 0) / a.split_len : 0;    // splits below the window are empty
-    const int64_t base = ((int64_t)b * a.Hq + hq) * a.max_splits;
-    bf16* o = a.O + ((int64_t)b * a.Hq + hq) * D;
-    constexpr int PER = D / 64;
-    if (ns == 0) {
+    if (ns - s0 <= 1) return;                                                       // written by the split kernel
+    const int64_t head = (int64_t)b * a.Hq + hq, base = head * a.max_splits;
+    f32x4 pre[PRE];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) o[lane * PER + i] = (bf16)0.0f;
-        if (lane == 0 && a.LSE) a.LSE[(int64_t)b * a.Hq + hq] = -INFINITY;
-        return;
+    for (int i = 0; i < PRE; ++i) {
+        const int s = s0 + r0 + i * ROWS;
+        pre[i] = *(const f32x4*)(a.part_O + (base + min(s, ns - 1)) * D + d);
     }
     float m = -INFINITY;
-    for (int s = s0; s < ns; ++s) m = fmaxf(m, a.part_ml[(base + s) * 2]);
-    float L = 0.0f, acc[PER];
+    for (int s = s0 + lane; s < ns; s += 64) m = fmaxf(m, a.part_ml[(base + s) * 2]);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) acc[i] = 0.0f;
-    for (int s = s0; s < ns; ++s) {
-        const float wgt = fast_exp2(a.part_ml[(base + s) * 2] - m);
-        L += wgt * a.part_ml[(base + s) * 2 + 1];
-        const float* po = a.part_O + (base + s) * D + lane * PER;
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    float L = 0.0f;
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto add = [&](int s, const f32x4& row) {
+        const float2 ml = *(const float2*)(a.part_ml + (base + s) * 2);
+        const float wgt = fast_exp2(ml.x - m);
+        L += wgt * ml.y;
+        acc += wgt * row;
+    };
 #pragma unroll
-        for (int i = 0; i < PER; ++i) acc[i] += wgt * po[i];
+    for (int i = 0; i < PRE; ++i)
+        if (s0 + r0 + i * ROWS < ns) add(s0 + r0 + i * ROWS, pre[i]);
+#pragma unroll 4
+    for (int s = s0 + r0 + PRE * ROWS; s < ns; s += ROWS) add(s, *(const f32x4*)(a.part_O + (base + s) * D + d));
+    *(f32x4*)&s_o[r0][d] = acc;
+    if (d == 0) s_l[r0] = L;
+    __syncthreads();
+    if (tid < D / 2) {
+        float o0 = 0.0f, o1 = 0.0f, lt = 0.0f;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            o0 += s_o[r][2 * tid];
+            o1 += s_o[r][2 * tid + 1];
+            lt += s_l[r];
+        }
+        const float inv = 1.0f / lt;
+        *(uint32_t*)(a.O + head * D + 2 * tid) = pack_bf16(o0 * inv, o1 * inv);
+        if (tid == 0 && a.LSE) a.LSE[head] = (m + fast_log2(lt)) * kLn2;
     }
-    const float inv = 1.0f / L;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) o[lane * PER + i] = (bf16)(acc[i] * inv);
-    if (lane == 0 && a.LSE) a.LSE[(int64_t)b * a.Hq + hq] = (m + fast_log2(L)) * kLn2;
 }
 
-// Keys per split.  One wave works on one (sequence, KV head, split), so a launch offers
-// nseq * Hkv * ceil(ctx / split_len) waves; the host cannot see the context lengths and sizes the
-// split for the longest context the page table addresses: the largest power of two in
-// [kDecSplitMin, kDecSplitMax] that still gives every SIMD of the chip a wave, so that a small batch
-// of long sequences is cut finer than a large one (measured: aiming at two waves per SIMD instead
-// makes one sequence of 32k tokens 1.5x slower -- each wave's start-up outweighs its 128 keys).
-static int split_len_of(const flexattn_decode_dims* d) {
-    const long long max_tokens = (long long)d->max_pages * d->page_size;
-    const long long per_wave = max_tokens * d->nseq * d->Hkv / kDecTargetWaves;
+// Keys per split: the largest power of two in [kDecSplitMin, longest] that still cuts the longest context
+// the page table addresses (the host cannot see the context lengths) into `want` pieces over all
+// (sequence, KV head) units.
+static int cut(const flexattn_decode_dims* d, long long want, int longest) {
+    const long long per_piece = (long long)d->max_pages * d->page_size * d->nseq * d->Hkv / want;
     int len = kDecSplitMin;
-    while (len < kDecSplitMax && 2 * len <= per_wave) len *= 2;
+    while (len < longest && 2 * len <= per_piece) len *= 2;
     return len;
 }
+// A workgroup works on one (sequence, KV head, split).  512 workgroups are two per CU, all that run at
+// once: a small batch is cut until it offers them (measured, D = 128, 8 KV heads, us at 256 / 512 / 1024 /
+// 2048 keys per split: one sequence of 32k tokens 29.3 / 27.1 / 29.2 / 41.1, four of 8k 27.9 / 26.4 / 28.8 /
+// 41.0, one of 128k 102 / 92 / 88 / 86).  A large batch takes the longest splits, which pay a workgroup's
+// start and its partial result least often (64 sequences of 1k to 32k: 908 / 797 / 753 / 719, and 715
+// at 4096, where a batch whose contexts stay far below the table's reach would no longer fill the chip).
+static int split_len_of(const flexattn_decode_dims* d) { return cut(d, 512, kDecSplitMax); }
 
-static int max_splits_of(const flexattn_decode_dims* d) {
-    const long long max_tokens = (long long)d->max_pages * d->page_size;
-    const int len = split_len_of(d);
-    return (int)((max_tokens + len - 1) / len);
+static int splits(const flexattn_decode_dims* d, int len) {
+    return (int)(((long long)d->max_pages * d->page_size + len - 1) / len);
 }
+// Room in the workspace: for the splits of 128 to 1024 keys of 1024 pieces, never fewer than are made.
+static int max_splits_of(const flexattn_decode_dims* d) { return splits(d, cut(d, 1024, 1024)); }
 
 template <int D>
 static int launch_decode(const DecodeArgs& a, uint32_t score_id, hipStream_t st) {
-    const int spw = a.max_splits >= 4 ? 4 : (a.max_splits >= 2 ? 2 : 1), upw = kDecWaves / spw;
-    const dim3 grid((unsigned)((a.nseq * a.Hkv + upw - 1) / upw), (unsigned)((a.max_splits + spw - 1) / spw));
+    constexpr int kGridY = 32768;      // (the y dimension of a grid ends at 65535)
+    const dim3 grid((unsigned)(a.nseq * a.Hkv), (unsigned)(a.max_splits < kGridY ? a.max_splits : kGridY),
+                    (unsigned)((a.max_splits + kGridY - 1) / kGridY));
     switch (score_id) {
 #define CASE(S)                                                                                           \
     case S:                                                                                               \
@@ -303,7 +400,8 @@ static int launch_decode(const DecodeArgs& a, uint32_t score_id, hipStream_t st)
 #undef CASE
         default: return FLEXATTN_ERR_UNSUPPORTED;
     }
-    hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)(a.nseq * a.Hq)), dim3(64), 0, st, a);
+    if (a.max_splits > 1)
+        hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)(a.nseq * a.Hq)), dim3(kDecWaves * 64), 0, st, a);
     return FLEXATTN_OK;
 }
 
@@ -395,8 +493,8 @@ extern "C" int flexattn_paged_decode(const flexattn_decode_dims* d, const void* 
     a.nseq = d->nseq; a.Hq = d->Hq; a.Hkv = d->Hkv; a.G = d->Hq / d->Hkv;
     a.page_size = d->page_size;
     a.page_shift = __builtin_ctz((unsigned)d->page_size);
-    a.max_splits = max_splits_of(d);
     a.split_len = split_len_of(d);
+    a.max_splits = splits(d, a.split_len);
     a.max_ctx = d->max_pages * d->page_size;
     a.n_pool_pages = d->n_pool_pages;
     a.window = mask_id == kCtxWindow ? p.window : -1;

@@ -103,6 +103,23 @@ def test_small_batches_are_cut_into_short_splits(nseq, Hkv, ctx_max):
     compare(inp, O, LSE, fo.Identity())
 
 
+@pytest.mark.parametrize("D,G,ctx", [
+    (128, 16, [0, 1, 31, 32, 33, 127, 128]),                 # one split each (some waves without a tile), none
+    (64, 16, [129, 128, 255, 256, 257, 0, 2048]),            # one to a few splits beside each other
+    (128, 2, [4096, 32 * 128, 32 * 128 + 1, 33 * 128, 8192]),  # combine: 32 splits, one more, 64
+    (64, 1, [64 * 128, 64 * 128 + 1, 80 * 128, 12000]),      # D = 64 combines 64 splits in its first round
+])
+def test_split_merge_edges(D, G, ctx):
+    """The merge of the four waves of a split, the split that is a sequence's only one (written without the
+    combine kernel), and the combine kernel at the number of splits it reads in its first round; tolerance
+    as everywhere in this file.  One KV head: the splits are cut to 128 ... 256 keys."""
+    wl = wlm.CFG5.scaled(B=len(ctx), Hq=G, Hkv=1, D=D, max_pages=(max(ctx) + 15) // 16)
+    inp = wlm.make_decode_inputs(wl, ctx_lens=ctx, slack_pages=2)
+    print(f"[case] merge D={D} G={G} ctx={ctx}", flush=True)
+    O, LSE = run_decode(inp)
+    compare(inp, O, LSE, fo.Identity())
+
+
 def test_wrong_tables_never_leave_the_buffers():
     """Device-side values are not trusted: page ids outside the pool and context lengths beyond what the
     page table addresses (or negative) are clamped, so the call returns normally with finite numbers --
