@@ -145,6 +145,8 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
     __shared__ int s_steps[kListMax + 2];          // the walk of the current head, see below
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];   // relative-bias row of the current head
+    using Mask = PartialMask<MASK>;
+    __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? TQ : 4];   // [slot] tags of a PARTIAL step's queries
 
     // workgroup -> (b, hkv, 64-key tile); all tiles of one (b, hkv) on one XCD.  The columns of
     // blocks are taken in the BlockMask's work order (longest first; that of the group's first query
@@ -210,6 +212,25 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
     const uint32_t row_lds = lds_addr(&s_row[0][0][0]) + (32 * x + 4 * half) * 4;
     const uint32_t xchg_mine = lds_addr(&s_xchg[w][0][lane]), xchg_theirs = lds_addr(&s_xchg[w ^ 2][0][lane]);
     const int q_off = q_offset_of(a.p, b);
+    const Mask mask(a.p, b, a.kv_len);
+    uint32_t k_tag = 0;
+    i32x4 doc_rsrc = {};
+    if constexpr (Mask::kDoc) {
+        const int32_t* docs = a.p.doc_ids + (int64_t)b * a.p.doc_stride_b;
+        k_tag = (uint32_t)docs[min(kv_lane, a.kv_len - 1)];
+        doc_rsrc = make_rsrc(docs, (uint32_t)(q_off + a.q_len) * 4u);
+    }
+    if constexpr (Mask::kCanvas) k_tag = mask.key_pixel(min(kv_lane, a.kv_len - 1));
+    // Tags of the 64 queries of the step whose first row is q0, into s_tag[slot] (visible after the
+    // barrier that makes the step's tiles visible)
+    auto make_tags = [&](int slot, int q0) __attribute__((always_inline)) {
+        if constexpr (Mask::kDoc) {
+            if (w == 0) dma_dword(doc_rsrc, lds_addr(&s_tag[slot][0]), lane * 4, (q_off + q0) * 4);
+        }
+        if constexpr (Mask::kCanvas) {
+            if (w == 2 * slot) s_tag[slot][lane] = mask.query_pixel(q_off + min(q0 + lane, a.q_len - 1));
+        }
+    };
     const int ds_lane = w * 1024 + lane * 8;     // this lane's place inside a step of dS in memory (bf16 elements)
 
     for (int g = 0; g < a.G; ++g) {
@@ -297,6 +318,7 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
             };
 
             load_step(std::integral_constant<int, 0>{});
+            if (part_of[0]) make_tags(0, q0_of[0]);
             wait_vmem();
             __syncthreads();
 
@@ -308,8 +330,11 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                 // wave waits on every load instruction until the memory pipe has taken it
                 constexpr std::integral_constant<int, SLOT ^ 1> ld_slot{};
                 load_begin(ld_slot);
-                const bool partial = part_of[SLOT];
+                if (part_of[SLOT ^ 1]) make_tags(SLOT ^ 1, q0_of[SLOT ^ 1]);
                 const int q_first = q0_of[SLOT] + 32 * x;
+                // (wave-uniform) does the mask touch this wave's 32 x 32 block at all?
+                const bool partial = part_of[SLOT] && !mask.full(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb,
+                                                                 kv0 + 32 * kb + 31);
 
                 // scores
                 f32x4 nd[4], rcv4[4];
@@ -342,6 +367,8 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                 float rel_uni;
                 const bool rel_is_uni = smod.rel_uniform(q_off + q_first - (kv0 + 32 * kb + 31),
                                                          q_off + q_first + 31 - (kv0 + 32 * kb), rel_uni);
+                typename Mask::Bits bits = {};
+                if (partial) bits = mask.key_bits(kv_lane, q_off + q_first + 4 * half);
                 u32x4 pk[2], dsk[2];
 #pragma unroll
                 for (int c4 = 0; c4 < 4; ++c4) {
@@ -363,20 +390,18 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                     }
                     if (rel_is_uni) smod.template p_with_grad4<true>(sv, dqk, rcv, gr, pe, rel_uni);
                     else smod.template p_with_grad4<false>(sv, dqk, rcv, gr, pe);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];
                     if (partial) {
                         asm volatile("" ::: "memory");   // keep this a (scalar, rarely taken) branch
+                        // (a masked P makes dS vanish with it.  Rows past q_len hold zeros in Q and dO: whatever
+                        // the mask says there adds nothing)
+                        u32x4 tags = {};
+                        if constexpr (Mask::kTags) tags = *(const u32x4*)&s_tag[SLOT][32 * x + 8 * c4 + 4 * half];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            // (rows past q_len hold zeros in Q and dO: whatever the mask says there adds nothing)
-                            const MaskRow<MASK> mrow(a.p, b, hq, q_off + min(q_first + crow(4 * c4 + i, half), a.q_len - 1),
-                                                     a.kv_len);
-                            const bool keep = mrow(kv_lane);
-                            pe[i] = keep ? pe[i] : 0.0f;
-                            ds[i] = keep ? ds[i] : 0.0f;
-                        }
+                        for (int i = 0; i < 4; ++i)
+                            pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i, mask.tags_match(k_tag, tags[i])), pe[i]);
                     }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
                         const int e = 2 * c4 + i;
@@ -474,6 +499,8 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
     constexpr int kTabAlibi = 1024;                                  // the table has at most 1024 entries
     __shared__ float s_tab[CAPTURED ? kTabAlibi + 1 : 1];            // relative-bias entries, then the ALiBi sum
     __shared__ float s_rel[ScoreMod<SCORE>::kRel ? kRelTableMax : 1]; // relative-bias row of the head (values)
+    using Mask = PartialMask<MASK>;
+    __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? 64 : 4];   // tags of a PARTIAL tile's keys (even, odd)
 
     const int units = a.B * a.Hkv;
     const int id = blockIdx.x, xcd = id & 7, kk = id >> 3;
@@ -532,7 +559,23 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
     const ScoreMod<SCORE, true> smod(a.p, hq, a.scale, lds_addr(s_rel));
     smod.fill_table(tid, NW * 64);                  // visible after the prologue's barrier
     const int q_pos = q_ld + q_offset_of(a.p, b);   // as the mods see it
-    const MaskRow<MASK> mrow(a.p, b, hq, q_pos, a.kv_len);
+    const Mask mask(a.p, b, a.kv_len);
+    uint32_t q_tag = 0;
+    i32x4 doc_rsrc = {};
+    if constexpr (Mask::kDoc) {
+        const int32_t* docs = a.p.doc_ids + (int64_t)b * a.p.doc_stride_b;
+        q_tag = (uint32_t)docs[q_pos];
+        doc_rsrc = make_rsrc(docs, (uint32_t)a.kv_len * 4u);
+    }
+    if constexpr (Mask::kCanvas) q_tag = mask.query_pixel(q_pos);
+    auto make_tags = [&](int buf, int kv0, int turn) __attribute__((always_inline)) {   // as in the forward
+        if constexpr (Mask::kDoc) {
+            if (w == 0) dma_dword(doc_rsrc, lds_addr(&s_tag[buf][0]), lane * 4, kv0 * 4);
+        }
+        if constexpr (Mask::kCanvas) {
+            if (w == (turn & (NW - 1))) s_tag[buf][lane] = mask.key_pixel(min(kv0 + lane, a.kv_len - 1));
+        }
+    };
 
     TileWalk<> walk(a.full_kv_idx + line * a.NC, a.kv_idx + line * a.NC, n_full, n_part, sub, a.Bk);
     const WaveTileLoader<D, NW> k_loader(a.k_ss, w, lane), v_loader(a.v_ss, w, lane);
@@ -556,6 +599,7 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
     bool part_next = false;
     int kv0 = walk.next(part_next);
     load_tiles(0, kv0);
+    if (part_next) make_tags(0, kv0, 0);
     wait_vmem();
     __syncthreads();
 
@@ -564,15 +608,14 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
         constexpr int BUF = decltype(buf_tag)::value;
         const int kv0_cur = kv0;
         const bool partial = part_next;
-        int tile_docs = 0;          // document ids of this tile's keys: one coalesced read, used after the MFMAs
-        if constexpr (MaskRow<MASK>::kUsesDoc) {
-            if (partial) tile_docs = MaskRow<MASK>::tile_docs(a.p, b, kv0_cur, a.kv_len - 1, lane);
-        }
         // K(t+1), V(t+1) go to buffer BUF ^ 1, last read in step t-1.  Their loads are issued piece by
         // piece between the first MFMAs below: a wave waits on every load instruction until the
         // memory pipe has taken it.
         const bool ld = t + 1 < T;
-        if (ld) kv0 = walk.next(part_next);
+        if (ld) {
+            kv0 = walk.next(part_next);
+            if (part_next) make_tags(BUF ^ 1, kv0, t + 1);
+        }
         constexpr uint32_t kt = BUF * (TILE * 2), vt = (2 + BUF) * (TILE * 2);
         using L = WaveTileLoader<D, NW>;
         constexpr int NKS = D / 16, NDB = D / 32, PF = 4;
@@ -639,16 +682,17 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
                     dpacc[r] = pe * gr * dpacc[r];
                 }
             }
-            if (partial) {
+            if (partial && !mask.full(q_wave_min, q_wave_min + 31, kvs_blk, kvs_blk + 31)) {
                 asm volatile("" ::: "memory");   // keep this a branch
+                const typename Mask::Bits bits = mask.row_bits(q_pos, kvs_blk + 4 * half);
+                u32x4 tags[4] = {};
+                if constexpr (Mask::kTags) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int off = kvb * 32 + crow(r, half);
-                    bool keep;
-                    if constexpr (MaskRow<MASK>::kUsesDoc) keep = mrow.eval(kv0_cur + off, MaskRow<MASK>::doc_at(tile_docs, off));
-                    else keep = mrow(kv0_cur + off);
-                    dpacc[r] = keep ? dpacc[r] : 0.0f;
+                    for (int rg = 0; rg < 4; ++rg) tags[rg] = *(const u32x4*)&s_tag[BUF][kvb * 32 + 8 * rg + 4 * half];
                 }
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    dpacc[r] = keep_or_zero(Mask::keep(bits, r, mask.tags_match(tags[r >> 2][r & 3], q_tag)), dpacc[r]);
             }
             if constexpr (CAPTURED) {
                 const int kvs = kv0_cur + kvb * 32;

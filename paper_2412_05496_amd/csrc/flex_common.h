@@ -211,14 +211,6 @@ struct MaskRow {
     MaskTermRow<T0> t0;
     MaskTermRow<T1> t1;
     int kv_last;
-    // Masks that read the document table can take the ids from the caller instead, who fetches
-    // them for a whole tile with one coalesced load (lane j: entry first + j) and hands them from
-    // lane to lane (tile_docs / doc_at), rather than with one table read per score element.
-    static constexpr bool kUsesDoc = (((MASK | (MASK >> 8)) & 0xffu) & FLEXATTN_M_DOCUMENT) != 0;
-    __device__ __forceinline__ static int tile_docs(const flexattn_mod_params& p, int b, int first, int last, int lane) {
-        return (p.doc_ids + (int64_t)b * p.doc_stride_b)[min(first + lane, last)];
-    }
-    __device__ __forceinline__ static int doc_at(int docs, int offset_in_tile) { return __shfl(docs, offset_in_tile, 64); }
     // kv_len: keys at or past it do not exist (last block of a length that is no multiple of the
     // block size): they are masked, and the primitives are evaluated at the last real key instead
     // so that no table is read out of range.  q_idx must be a real row.
@@ -237,12 +229,6 @@ struct MaskRow {
         if constexpr (T1 != 0) f = f || t1.block_full(q_lo, q_hi, kv_lo, kv_hi);
         return f;
     }
-    // with the document id of key kv supplied (any value for keys past the end)
-    __device__ __forceinline__ bool eval(int kv, int doc_kv) const {
-        bool r = t0.eval(kv, doc_kv);
-        if constexpr (T1 != 0) r = r || t1.eval(kv, doc_kv);
-        return r && kv <= kv_last;
-    }
     __device__ __forceinline__ bool operator()(int kv) const {
         const int kc = min(kv, kv_last);
         bool r = t0(kc);
@@ -250,6 +236,160 @@ struct MaskRow {
         return r && kv <= kv_last;
     }
 };
+
+// ---------------------------------------------------------------------------------------
+// mask_mod of a PARTIAL block inside the MFMA kernels.
+//
+// A lane holds 16 elements of a 32 x 32 block that share its query (forward, dQ) or its key (dK/dV) and
+// run along the other index at the compile-time positions crow(r, 0) behind a base.  Everything in the
+// mask that compares indices is an interval of those positions per term, so it is worked out once per
+// block as a bit mask (about ten instructions) and costs an element one bit-field extract and one
+// select by bits, whatever the composition.  What is looked up per token -- the document id, the pixel of
+// the canvas -- becomes a 32-bit tag: the lane's own in a register, the other side's in an LDS table of
+// the tile (one tag per token, read four at a time), compared per element.
+// (Evaluating the mask element by element instead -- the canvas decode of every key, a lane exchange or a
+// table read per document id -- made PARTIAL blocks several times as expensive as FULL ones: neighborhood
+// attention on 128 x 128 pixels, K = 13, D = 64, B = 4, H = 16: forward 0.98 ms, dK/dV 1.60 ms before.)
+// ---------------------------------------------------------------------------------------
+
+// Position of element r of a lane's 16 (without the 4 * half that goes into the base).
+__device__ __forceinline__ constexpr int elem_pos(int r) { return 8 * (r >> 2) + (r & 3); }
+
+// bits p of lo <= p <= hi, for the positions 0 .. 27 that elem_pos() takes
+__device__ __forceinline__ uint32_t interval_bits(int lo, int hi) {
+    const int h = min(max(hi, -1), 27) + 1, l = min(max(lo, 0), 28);
+    return ((1u << h) - 1u) & ~((1u << l) - 1u);
+}
+
+template <uint32_t MASK>
+struct PartialMask {
+    static constexpr uint32_t T0 = MASK & 0xffu, T1 = (MASK >> 8) & 0xffu, PRIMS = T0 | T1;
+    static constexpr uint32_t kTagged = FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD;
+    static constexpr bool kDoc = (PRIMS & FLEXATTN_M_DOCUMENT) != 0, kCanvas = (PRIMS & FLEXATTN_M_NEIGHBORHOOD) != 0;
+    static constexpr bool kTags = kDoc || kCanvas;
+    static_assert(!(kDoc && kCanvas), "one tag per token: documents or pixels");
+
+    int window, prefix_len, ctx, kv_last;
+    // pixels (x, y) as x | y << y_shift with one guard bit above each coordinate (guard): with the tag of
+    // a query the top left corner of its window minus the guard bits, a = key tag - query tag has both
+    // guard bits set iff x >= x0 and y >= y0, and span + 2 guard - a iff x <= x0 + span and y <= y0 + span.
+    uint32_t guard, far;
+    int y_shift;
+    std::conditional_t<kCanvas, CanvasOrder, NoCanvas> canvas;
+    int na_r, na_w, na_h;
+
+    __device__ __forceinline__ PartialMask(const flexattn_mod_params& p, int b, int kv_len) : canvas(p) {
+        window = p.window;
+        prefix_len = p.prefix_len;
+        ctx = (PRIMS & FLEXATTN_M_CTX_LEN) ? ldc(p.ctx_lens + b) : 0;
+        kv_last = kv_len - 1;
+        guard = far = 0;
+        y_shift = na_r = na_w = na_h = 0;
+        if constexpr (kCanvas) {
+            na_w = p.na_width;
+            na_h = p.na_height;
+            na_r = p.na_kernel >> 1;
+            const int xb = 32 - __builtin_clz((unsigned)na_w), yb = 32 - __builtin_clz((unsigned)na_h);   // xb + yb <= 22
+            y_shift = xb + 1;
+            guard = (1u << xb) | (1u << (y_shift + yb));
+            far = (uint32_t)(2 * na_r) * (1u | (1u << y_shift)) + 2u * guard;
+        }
+    }
+    // Tags of a key and of a query (indices as the mods see them, in range).
+    __device__ __forceinline__ uint32_t key_pixel(int kv) const {
+        int x, y;
+        canvas.pixel(kv, x, y);
+        return (uint32_t)x | ((uint32_t)y << y_shift);
+    }
+    __device__ __forceinline__ uint32_t query_pixel(int q) const {
+        int x, y;
+        canvas.pixel(q, x, y);
+        x = min(max(x, na_r), na_w - 1 - na_r) - na_r;
+        y = min(max(y, na_r), na_h - 1 - na_r) - na_r;
+        return ((uint32_t)x | ((uint32_t)y << y_shift)) - guard;
+    }
+    __device__ __forceinline__ bool tags_match(uint32_t key_tag, uint32_t query_tag) const {
+        if constexpr (kDoc) return key_tag == query_tag;
+        const uint32_t a = key_tag - query_tag;
+        return (a & (far - a) & guard) == guard;
+    }
+
+    // Bits of the elements whose index comparisons hold: `plain` for the terms that end there, `tagged` for
+    // those that also want the tags to match.
+    struct Bits {
+        uint32_t plain, tagged;
+        __device__ __forceinline__ void add(uint32_t term, uint32_t b) {
+            if (term & kTagged) tagged |= b;
+            else plain |= b;
+        }
+    };
+    template <uint32_t TERM>
+    __device__ __forceinline__ uint32_t row_term(int q, int kv_base) const {
+        int hi = kv_last;
+        if constexpr (TERM & FLEXATTN_M_CAUSAL) hi = min(hi, q);
+        if constexpr (TERM & FLEXATTN_M_PREFIX) hi = min(hi, prefix_len - 1);
+        if constexpr (TERM & FLEXATTN_M_CTX_LEN) hi = min(hi, ctx - 1);
+        int lo = 0;
+        if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) lo = __builtin_elementwise_sub_sat(q - kv_base, window);
+        return interval_bits(lo, hi - kv_base);
+    }
+    // the lane holds query q and the keys kv_base + elem_pos(r)
+    __device__ __forceinline__ Bits row_bits(int q, int kv_base) const {
+        Bits out = {0u, 0u};
+        out.add(T0, row_term<T0>(q, kv_base));
+        if constexpr (T1 != 0) out.add(T1, row_term<T1>(q, kv_base));
+        return out;
+    }
+    template <uint32_t TERM>
+    __device__ __forceinline__ uint32_t key_term(int kv, int q_base) const {
+        bool there = kv <= kv_last;
+        if constexpr (TERM & FLEXATTN_M_PREFIX) there = there && kv < prefix_len;
+        if constexpr (TERM & FLEXATTN_M_CTX_LEN) there = there && kv < ctx;
+        int lo = 0, hi = 27;
+        if constexpr (TERM & FLEXATTN_M_CAUSAL) lo = kv - q_base;
+        if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) hi = __builtin_elementwise_add_sat(kv - q_base, window);
+        return there ? interval_bits(lo, hi) : 0u;
+    }
+    // the lane holds key kv and the queries q_base + elem_pos(r)
+    __device__ __forceinline__ Bits key_bits(int kv, int q_base) const {
+        Bits out = {0u, 0u};
+        out.add(T0, key_term<T0>(kv, q_base));
+        if constexpr (T1 != 0) out.add(T1, key_term<T1>(kv, q_base));
+        return out;
+    }
+    // All-ones if element r is kept, else 0; `match`: its tags match (ignored by masks without tags).
+    __device__ __forceinline__ static uint32_t keep(const Bits& bits, int r, bool match) {
+        const int sh = 31 - elem_pos(r);
+        uint32_t m = 0;
+        if constexpr (!kTags || (T0 & kTagged) == 0 || (T1 != 0 && (T1 & kTagged) == 0)) m = (uint32_t)((int32_t)(bits.plain << sh) >> 31);
+        if constexpr (kTags) m |= match ? (uint32_t)((int32_t)(bits.tagged << sh) >> 31) : 0u;
+        return m;
+    }
+    // Wave-uniform shortcut: no pair of the rectangle is masked (decided by index comparisons alone).
+    template <uint32_t TERM>
+    __device__ __forceinline__ bool term_full(int q_lo, int q_hi, int kv_lo, int kv_hi) const {
+        if constexpr ((TERM & kTagged) != 0) return false;
+        bool f = true;
+        if constexpr (TERM & FLEXATTN_M_CAUSAL) f = f && q_lo >= kv_hi;
+        if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) f = f && q_hi - kv_lo <= window;
+        if constexpr (TERM & FLEXATTN_M_PREFIX) f = f && kv_hi < prefix_len;
+        if constexpr (TERM & FLEXATTN_M_CTX_LEN) f = f && kv_hi < ctx;
+        return f;
+    }
+    __device__ __forceinline__ bool full(int q_lo, int q_hi, int kv_lo, int kv_hi) const {
+        bool f = term_full<T0>(q_lo, q_hi, kv_lo, kv_hi);
+        if constexpr (T1 != 0) f = f || term_full<T1>(q_lo, q_hi, kv_lo, kv_hi);
+        return f && kv_hi <= kv_last;
+    }
+};
+
+// v where m is all-ones, 0 (or -inf) where it is 0
+__device__ __forceinline__ float keep_or_zero(uint32_t m, float v) {
+    return __builtin_bit_cast(float, m & __builtin_bit_cast(uint32_t, v));
+}
+__device__ __forceinline__ float keep_or_neg_inf(uint32_t m, float v) {
+    return __builtin_bit_cast(float, (m & __builtin_bit_cast(uint32_t, v)) | (~m & 0xff800000u));
+}
 
 // ---------------------------------------------------------------------------------------
 // score_mod in the base-2 domain.  apply(acc, q - kv) returns log2(e) * score_mod(acc * scale),

@@ -66,6 +66,8 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
     __shared__ __attribute__((aligned(1024))) bf16 smem[4 * TILE];   // K(even), K(odd), V(even), V(odd)
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];           // relative-bias row of the head
+    using Mask = PartialMask<MASK>;
+    __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys (even, odd)
 
     // ---- workgroup -> (b, hkv, g, row of blocks).  Consecutive workgroup ids go to the 8 XCDs in
     // turn; all rows and all G query heads of one (b, hkv) are sent to the same XCD so that its K/V
@@ -138,7 +140,22 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
     smod.fill_table(tid, NW * 64);                  // visible after the prologue's barrier
     const int q_pos = q_ld + q_offset_of(a.p, b);   // as the mods see it
     const int q_wave_min = row * Bq + w * 32 + q_offset_of(a.p, b);   // the wave's rows: q_wave_min .. +31
-    const MaskRow<MASK> mrow(a.p, b, hq, q_pos, a.kv_len);
+    const Mask mask(a.p, b, a.kv_len);
+    uint32_t q_tag = 0;
+    if constexpr (Mask::kDoc) q_tag = (uint32_t)(a.p.doc_ids + (int64_t)b * a.p.doc_stride_b)[q_pos];
+    if constexpr (Mask::kCanvas) q_tag = mask.query_pixel(q_pos);
+    // Tags of the keys of the tile at kv0, into s_tag[buf] (visible after the next barrier): document ids
+    // come by LDS-DMA (keys past the end read as 0), pixels are worked out by one of the waves.
+    i32x4 doc_rsrc = {};
+    if constexpr (Mask::kDoc) doc_rsrc = make_rsrc(a.p.doc_ids + (int64_t)b * a.p.doc_stride_b, (uint32_t)a.kv_len * 4u);
+    auto make_tags = [&](int buf, int kv0, int turn) __attribute__((always_inline)) {
+        if constexpr (Mask::kDoc) {
+            if (w == 0) dma_dword(doc_rsrc, lds_addr(&s_tag[buf][0]), lane * 4, kv0 * 4);
+        }
+        if constexpr (Mask::kCanvas) {
+            if (w == (turn & (NW - 1))) s_tag[buf][lane] = mask.key_pixel(min(kv0 + lane, a.kv_len - 1));
+        }
+    };
     const float inv_neg2c = smod.capl2 > 0.0f ? -0.5f / smod.capl2 : 0.0f;   // 1 / (-2 cap log2 e)
 
     // first key and PARTIAL flag of tiles t, t+1, t+2 (the walk is always two tiles ahead)
@@ -195,12 +212,19 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
     // score_mod, mask_mod (partial blocks only) and softmax of one 32-key block whose first key is
     // kvs: s -> P^T as two bf16 fragments.  The mask is a separate, rarely taken pass (kept a real
     // branch) so that the common path is one straight run of VALU work next to the MFMAs around it.
-    int tile_docs = 0, tile_first = 0;   // document ids of the current tile's keys (partial tiles of document masks)
-    auto keep = [&](int kv) __attribute__((always_inline)) {
-        if constexpr (MaskRow<MASK>::kUsesDoc) return mrow.eval(kv, MaskRow<MASK>::doc_at(tile_docs, kv - tile_first));
-        else return mrow(kv);
+    // mask_mod of the 32-key block kvb of the tile in buffer buf: put(all-ones or 0, s) for every element
+    auto masked = [&](f32x16& s, int kvs, int buf, int kvb, auto&& put) __attribute__((always_inline)) {
+        const typename Mask::Bits bits = mask.row_bits(q_pos, kvs + 4 * half);
+        u32x4 tags[4] = {};
+        if constexpr (Mask::kTags) {
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) tags[rg] = *(const u32x4*)&s_tag[buf][kvb * 32 + 8 * rg + 4 * half];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = put(Mask::keep(bits, r, mask.tags_match(tags[r >> 2][r & 3], q_tag)), s[r]);
     };
-    auto softmax = [&](f32x16& s, int kvs, bool partial, bf16x8 (&pf)[2]) {
+    auto softmax = [&](f32x16& s, int kvs, bool tile_partial, int buf, int kvb, bf16x8 (&pf)[2]) {
+        const bool partial = tile_partial && !mask.full(q_wave_min, q_wave_min + 31, kvs, kvs + 31);   // (wave-uniform)
         // q_idx - kv_idx of element r is dq0 - 8 (r >> 2) - (r & 3)
         const int dq0 = q_pos - kvs - 4 * half;
         const float abase = smod.alibi_base(dq0);
@@ -225,8 +249,7 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
             }
             if (partial) {
                 asm volatile("" ::: "memory");   // keep this a branch, not 16 selects on every tile
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[r] = keep(kvs + crow(r, half)) ? s[r] : 0.0f;
+                masked(s, kvs, buf, kvb, keep_or_zero);
             }
         } else {
             // Online softmax.  The running maximum only has to keep exp2(s - m) in range, so it follows
@@ -246,8 +269,7 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
             }
             if (partial) {
                 asm volatile("" ::: "memory");
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[r] = keep(kvs + crow(r, half)) ? s[r] : -INFINITY;
+                masked(s, kvs, buf, kvb, keep_or_neg_inf);
             }
             float mx = s[0];
 #pragma unroll
@@ -301,6 +323,7 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
     kv_t = walk.next(part_t, pg_t, pr_t);
     load_k(0, kv_t, pg_t, pr_t);
     load_v(0, kv_t, pg_t, pr_t);
+    if (part_t) make_tags(0, kv_t, 0);
     if (T > 1) {
         kv_t1 = walk.next(part_t1, pg_t1, pr_t1);
         load_k(1, kv_t1, pg_t1, pr_t1);
@@ -330,11 +353,8 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
         tile_src(v_head, v_rsrc, v_row_bytes, kv_t1, pg_t1, pr_t1, v_src, v_soff);
         const int kv0 = kv_t;
         const bool partial = part_t;
-        if constexpr (MaskRow<MASK>::kUsesDoc) {
-            if (partial) {      // one coalesced read, behind the MFMAs that follow
-                tile_first = kv0;
-                tile_docs = MaskRow<MASK>::tile_docs(a.p, b, kv0, a.kv_len - 1, lane);
-            }
+        if constexpr (HAS_NEXT) {
+            if (part_t1) make_tags(BUF ^ 1, kv_t1, t + 1);
         }
         bf16x8 pf[2];
         if constexpr (HAS_NEXT) {
@@ -353,9 +373,9 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
                 });
             });
         }
-        softmax(s_cur[0], kv0, partial, pf);
+        softmax(s_cur[0], kv0, partial, BUF, 0, pf);
         pv(buf_tag, 0, pf);
-        softmax(s_cur[1], kv0 + 32, partial, pf);
+        softmax(s_cur[1], kv0 + 32, partial, BUF, 1, pf);
         pv(buf_tag, 1, pf);
         if constexpr (HAS_NEXT) {
 #pragma unroll
