@@ -368,7 +368,10 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                 const bool rel_is_uni = smod.rel_uniform(q_off + q_first - (kv0 + 32 * kb + 31),
                                                          q_off + q_first + 31 - (kv0 + 32 * kb), rel_uni);
                 typename Mask::Bits bits = {};
-                if (partial) bits = mask.key_bits(kv_lane, q_off + q_first + 4 * half);
+                if (partial) {
+                    bits = mask.key_bits(kv_lane, q_off + q_first + 4 * half);
+                    if constexpr (Mask::kDoc) Mask::match_documents(bits, s_tag[SLOT][32 * x + l32], k_tag, half);
+                }
                 u32x4 pk[2], dsk[2];
 #pragma unroll
                 for (int c4 = 0; c4 < 4; ++c4) {
@@ -395,10 +398,10 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                         // (a masked P makes dS vanish with it.  Rows past q_len hold zeros in Q and dO: whatever
                         // the mask says there adds nothing)
                         u32x4 tags = {};
-                        if constexpr (Mask::kTags) tags = *(const u32x4*)&s_tag[SLOT][32 * x + 8 * c4 + 4 * half];
+                        if constexpr (Mask::kCanvas) tags = *(const u32x4*)&s_tag[SLOT][32 * x + 8 * c4 + 4 * half];
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i, mask.tags_match(k_tag, tags[i])), pe[i]);
+                            pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i, mask.pixels_match(k_tag, tags[i])), pe[i]);
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];
@@ -684,15 +687,16 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
             }
             if (partial && !mask.full(q_wave_min, q_wave_min + 31, kvs_blk, kvs_blk + 31)) {
                 asm volatile("" ::: "memory");   // keep this a branch
-                const typename Mask::Bits bits = mask.row_bits(q_pos, kvs_blk + 4 * half);
+                typename Mask::Bits bits = mask.row_bits(q_pos, kvs_blk + 4 * half);
+                if constexpr (Mask::kDoc) Mask::match_documents(bits, s_tag[BUF][kvb * 32 + l32], q_tag, half);
                 u32x4 tags[4] = {};
-                if constexpr (Mask::kTags) {
+                if constexpr (Mask::kCanvas) {
 #pragma unroll
                     for (int rg = 0; rg < 4; ++rg) tags[rg] = *(const u32x4*)&s_tag[BUF][kvb * 32 + 8 * rg + 4 * half];
                 }
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    dpacc[r] = keep_or_zero(Mask::keep(bits, r, mask.tags_match(tags[r >> 2][r & 3], q_tag)), dpacc[r]);
+                    dpacc[r] = keep_or_zero(Mask::keep(bits, r, mask.pixels_match(tags[r >> 2][r & 3], q_tag)), dpacc[r]);
             }
             if constexpr (CAPTURED) {
                 const int kvs = kv0_cur + kvb * 32;

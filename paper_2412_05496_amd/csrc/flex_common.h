@@ -245,11 +245,13 @@ struct MaskRow {
 // mask that compares indices is an interval of those positions per term, so it is worked out once per
 // block as a bit mask (about ten instructions) and costs an element one bit-field extract and one
 // select by bits, whatever the composition.  What is looked up per token -- the document id, the pixel of
-// the canvas -- becomes a 32-bit tag: the lane's own in a register, the other side's in an LDS table of
-// the tile (one tag per token, read four at a time), compared per element.
+// the canvas -- is a 32-bit tag, the other side's in an LDS table of the tile.  Equal document ids become
+// bits as well, by one ballot per distinct id of the 32 tokens (one or two in packed documents); pixels are
+// compared per element, the tags read four at a time.
 // (Evaluating the mask element by element instead -- the canvas decode of every key, a lane exchange or a
 // table read per document id -- made PARTIAL blocks several times as expensive as FULL ones: neighborhood
-// attention on 128 x 128 pixels, K = 13, D = 64, B = 4, H = 16: forward 0.98 ms, dK/dV 1.60 ms before.)
+// attention on 128 x 128 pixels, K = 13, D = 64, B = 4, H = 16: forward 0.98 ms, dK/dV 1.60 ms before, 0.42
+// and 0.67 since.)
 // ---------------------------------------------------------------------------------------
 
 // Position of element r of a lane's 16 (without the 4 * half that goes into the base).
@@ -259,6 +261,12 @@ __device__ __forceinline__ constexpr int elem_pos(int r) { return 8 * (r >> 2) +
 __device__ __forceinline__ uint32_t interval_bits(int lo, int hi) {
     const int h = min(max(hi, -1), 27) + 1, l = min(max(lo, 0), 28);
     return ((1u << h) - 1u) & ~((1u << l) - 1u);
+}
+
+// All-ones if bit `pos` of `bits` is set, else 0 (the intrinsic, because the compiler turns the shifts it
+// stands for, and the `and` that follows, into a test and a select: three instructions for two)
+__device__ __forceinline__ uint32_t bit_mask(uint32_t bits, int pos) {
+    return (uint32_t)__builtin_amdgcn_sbfe((int)bits, (uint32_t)pos, 1u);
 }
 
 template <uint32_t MASK>
@@ -308,10 +316,22 @@ struct PartialMask {
         y = min(max(y, na_r), na_h - 1 - na_r) - na_r;
         return ((uint32_t)x | ((uint32_t)y << y_shift)) - guard;
     }
-    __device__ __forceinline__ bool tags_match(uint32_t key_tag, uint32_t query_tag) const {
-        if constexpr (kDoc) return key_tag == query_tag;
+    __device__ __forceinline__ bool pixels_match(uint32_t key_tag, uint32_t query_tag) const {
         const uint32_t a = key_tag - query_tag;
         return (a & (far - a) & guard) == guard;
+    }
+
+    // Bits of the lanes l < 32 whose `theirs` equals this lane's `mine` (lanes l and l + 32 hold the same
+    // `theirs`; all lanes of the wave take part).
+    __device__ __forceinline__ static uint32_t equal_bits(uint32_t theirs, uint32_t mine) {
+        uint32_t out = 0, left = 0xffffffffu;
+        while (left != 0) {
+            const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)theirs, __builtin_ctz(left));
+            const uint32_t same = (uint32_t)__ballot(theirs == id);
+            left &= ~same;
+            out |= mine == id ? same : 0u;
+        }
+        return out;
     }
 
     // Bits of the elements whose index comparisons hold: `plain` for the terms that end there, `tagged` for
@@ -357,12 +377,16 @@ struct PartialMask {
         if constexpr (T1 != 0) out.add(T1, key_term<T1>(kv, q_base));
         return out;
     }
-    // All-ones if element r is kept, else 0; `match`: its tags match (ignored by masks without tags).
+    // Document masks: `theirs` holds the ids of the block's 32 tokens of the other index, lane l the one of
+    // token l % 32.
+    __device__ __forceinline__ static void match_documents(Bits& bits, uint32_t theirs, uint32_t mine, int half) {
+        bits.plain |= bits.tagged & (equal_bits(theirs, mine) >> (4 * half));
+    }
+    // All-ones if element r is kept, else 0; `match`: its pixels match (canvas masks only).
     __device__ __forceinline__ static uint32_t keep(const Bits& bits, int r, bool match) {
-        const int sh = 31 - elem_pos(r);
         uint32_t m = 0;
-        if constexpr (!kTags || (T0 & kTagged) == 0 || (T1 != 0 && (T1 & kTagged) == 0)) m = (uint32_t)((int32_t)(bits.plain << sh) >> 31);
-        if constexpr (kTags) m |= match ? (uint32_t)((int32_t)(bits.tagged << sh) >> 31) : 0u;
+        if constexpr (!kCanvas || (T0 & kTagged) == 0 || (T1 != 0 && (T1 & kTagged) == 0)) m = bit_mask(bits.plain, elem_pos(r));
+        if constexpr (kCanvas) m |= match ? bit_mask(bits.tagged, elem_pos(r)) : 0u;
         return m;
     }
     // Wave-uniform shortcut: no pair of the rectangle is masked (decided by index comparisons alone).

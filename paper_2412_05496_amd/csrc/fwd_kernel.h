@@ -69,6 +69,8 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
     using Mask = PartialMask<MASK>;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys (even, odd)
 
+    __shared__ uint32_t s_qtag[Mask::kTags ? NW * 64 : 1];            // each lane's own tag (its query's)
+
     // ---- workgroup -> (b, hkv, g, row of blocks).  Consecutive workgroup ids go to the 8 XCDs in
     // turn; all rows and all G query heads of one (b, hkv) are sent to the same XCD so that its K/V
     // stay in that XCD's L2.  Rows are taken longest first (the BlockMask's work order), or
@@ -141,16 +143,17 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
     const int q_pos = q_ld + q_offset_of(a.p, b);   // as the mods see it
     const int q_wave_min = row * Bq + w * 32 + q_offset_of(a.p, b);   // the wave's rows: q_wave_min .. +31
     const Mask mask(a.p, b, a.kv_len);
-    uint32_t q_tag = 0;
-    if constexpr (Mask::kDoc) q_tag = (uint32_t)(a.p.doc_ids + (int64_t)b * a.p.doc_stride_b)[q_pos];
-    if constexpr (Mask::kCanvas) q_tag = mask.query_pixel(q_pos);
+    // the lane's own tag waits in LDS as well: a register held for it over the whole kernel ends in spills
+    // whose reloads wait for the tile loads
+    if constexpr (Mask::kDoc) s_qtag[tid] = (uint32_t)(a.p.doc_ids + (int64_t)b * a.p.doc_stride_b)[q_pos];
+    if constexpr (Mask::kCanvas) s_qtag[tid] = mask.query_pixel(q_pos);
     // Tags of the keys of the tile at kv0, into s_tag[buf] (visible after the next barrier): document ids
     // come by LDS-DMA (keys past the end read as 0), pixels are worked out by one of the waves.
-    i32x4 doc_rsrc = {};
-    if constexpr (Mask::kDoc) doc_rsrc = make_rsrc(a.p.doc_ids + (int64_t)b * a.p.doc_stride_b, (uint32_t)a.kv_len * 4u);
     auto make_tags = [&](int buf, int kv0, int turn) __attribute__((always_inline)) {
         if constexpr (Mask::kDoc) {
-            if (w == 0) dma_dword(doc_rsrc, lds_addr(&s_tag[buf][0]), lane * 4, kv0 * 4);
+            if (w == 0)
+                dma_global_dword(lds_addr(&s_tag[buf][0]), a.p.doc_ids + (int64_t)b * a.p.doc_stride_b,
+                                 min(kv0 + lane, a.kv_len - 1) * 4);
         }
         if constexpr (Mask::kCanvas) {
             if (w == (turn & (NW - 1))) s_tag[buf][lane] = mask.key_pixel(min(kv0 + lane, a.kv_len - 1));
@@ -214,14 +217,19 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
     // branch) so that the common path is one straight run of VALU work next to the MFMAs around it.
     // mask_mod of the 32-key block kvb of the tile in buffer buf: put(all-ones or 0, s) for every element
     auto masked = [&](f32x16& s, int kvs, int buf, int kvb, auto&& put) __attribute__((always_inline)) {
-        const typename Mask::Bits bits = mask.row_bits(q_pos, kvs + 4 * half);
-        u32x4 tags[4] = {};
-        if constexpr (Mask::kTags) {
+        typename Mask::Bits bits = mask.row_bits(q_pos, kvs + 4 * half);
+        const uint32_t q_tag = Mask::kTags ? s_qtag[tid] : 0u;
+        if constexpr (Mask::kDoc) Mask::match_documents(bits, s_tag[buf][kvb * 32 + l32], q_tag, half);
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) tags[rg] = *(const u32x4*)&s_tag[buf][kvb * 32 + 8 * rg + 4 * half];
+        for (int rg = 0; rg < 4; ++rg) {
+            u32x4 tags = {};
+            if constexpr (Mask::kCanvas) {
+                tags = *(const u32x4*)&s_tag[buf][kvb * 32 + 8 * rg + 4 * half];
+                asm volatile("" ::: "memory");   // (one read at a time: there are no registers for four)
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[4 * rg + i] = put(Mask::keep(bits, 4 * rg + i, mask.pixels_match(tags[i], q_tag)), s[4 * rg + i]);
         }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = put(Mask::keep(bits, r, mask.tags_match(tags[r >> 2][r & 3], q_tag)), s[r]);
     };
     auto softmax = [&](f32x16& s, int kvs, bool tile_partial, int buf, int kvb, bf16x8 (&pf)[2]) {
         const bool partial = tile_partial && !mask.full(q_wave_min, q_wave_min + 31, kvs, kvs + 31);   // (wave-uniform)

@@ -92,6 +92,15 @@ __device__ __forceinline__ void dma_x2(i32x4 rsrc, uint32_t lds, int v0, int v1,
                  :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(v0), "v"(v1), "s"(scalar_rsrc(rsrc)), "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory");
 }
 
+// 64 lanes x 4 bytes from `base` (wave-uniform) + `voff` (per lane, bytes) to `lds` .. +256.
+__device__ __forceinline__ void dma_global_dword(uint32_t lds, const void* base, int voff) {
+    const uint64_t p = (uint64_t)base;
+    const uint64_t sp = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32) |
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2"
+                 :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(sp) : "memory");
+}
+
 // 64 lanes x 16 bytes from per-lane global addresses to `lds` .. +1024, with the non-temporal hint:
 // for data that is read exactly once (the K / V pages of a decode step), which then stream past the
 // caches instead of displacing each other there.
