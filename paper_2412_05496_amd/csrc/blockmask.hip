@@ -1,145 +1,306 @@
 // BlockMask construction (paper section 4.2) and the paged BlockMask conversion (section 5.1).
 //
-// classify: one wave per block evaluates mask_mod on all Bq x Bk scalars and counts the unmasked
-// ones (0 -> skipped, Bq*Bk -> full, else partial).  compact: one wave per row (or column) of
-// blocks turns the per-block kinds into ascending index lists with a zero tail.
+// One workgroup makes the lists of one line: of a row of blocks, or of a column of blocks (both
+// orientations in one launch; a column classifies its blocks again instead of waiting for the rows).  A
+// thread classifies a block from the index ranges and, for documents and canvas pixels, from the range of
+// ids or coordinates its tokens take: that settles the blocks that are hidden or visible as a whole.  The
+// others are counted exactly by one wave each, a lane per query row: the keys that row sees are a 64-bit
+// mask per term (an interval, and the keys whose document id equals the row's, one ballot per distinct id),
+// whose population is the count.
+// What bounds it is latency, not arithmetic: three short kernels.  (A wave per block that evaluated
+// mask_mod scalar by scalar, 8192 to a block, and then one wave per line to compact: 0.18 ms on packed
+// documents of 16384 tokens, 0.11 ms for four causal chunks of 2048 queries on 16384 keys, 0.49 ms for
+// 128 x 128 pixels.)
 #include "flex_common.h"
 
 namespace flexattn {
 
-constexpr int kClassifyWaves = 4;
+constexpr int kLineThreads = 256, kLineWaves = kLineThreads / 64;
+
+// What the tokens of one side of a block have in common.  Documents: ids in [a0, a1].  Canvas: keys with
+// x in [a0, a1] and y in [b0, b1]; queries whose windows start at x0 in [a0, a1], y0 in [b0, b1].
+struct TokenRange {
+    int a0, a1, b0, b1;
+};
+constexpr TokenRange kNoTokens = {INT32_MAX, INT32_MIN, INT32_MAX, INT32_MIN};
+constexpr TokenRange kAnyTokens = {INT32_MIN / 2, INT32_MAX / 2, INT32_MIN / 2, INT32_MAX / 2};
+
+// The mask on whole blocks and, exactly, on the scalars of a block.
+template <uint32_t MASK>
+struct BlockEval {
+    using Partial = PartialMask<MASK>;
+    static constexpr uint32_t T0 = MASK & 0xffu, T1 = (MASK >> 8) & 0xffu;
+    Partial mask;
+    const int32_t* docs;
+    int q_off, q_len, kv_len, Bq, Bk;
+    __device__ __forceinline__ BlockEval(const flexattn_mod_params& p, int b, int q_len_, int kv_len_, int Bq_, int Bk_)
+        : mask(p, b, kv_len_), docs(Partial::kDoc ? p.doc_ids + (int64_t)b * p.doc_stride_b : nullptr),
+          q_off(q_offset_of(p, b)), q_len(q_len_), kv_len(kv_len_), Bq(Bq_), Bk(Bk_) {}
+
+    // one token more of the key (query) side of a block
+    __device__ __forceinline__ void take_key(TokenRange& r, int kv) const {
+        if constexpr (Partial::kDoc) take(r.a0, r.a1, docs[kv]);
+        if constexpr (Partial::kCanvas) {
+            int x, y;
+            mask.canvas.pixel(kv, x, y);
+            take(r.a0, r.a1, x);
+            take(r.b0, r.b1, y);
+        }
+    }
+    __device__ __forceinline__ void take_query(TokenRange& r, int q) const {
+        if constexpr (Partial::kDoc) take(r.a0, r.a1, docs[q_off + q]);
+        if constexpr (Partial::kCanvas) {
+            int x, y;
+            mask.window_corner(q_off + q, x, y);
+            take(r.a0, r.a1, x);
+            take(r.b0, r.b1, y);
+        }
+    }
+    __device__ __forceinline__ static void take(int& lo, int& hi, int v) {
+        lo = min(lo, v);
+        hi = max(hi, v);
+    }
+    // Rows and keys of block (i, j) that exist.
+    __device__ __forceinline__ int rows_of(int i) const { return min(Bq, q_len - i * Bq); }
+    __device__ __forceinline__ int keys_of(int j) const { return min(Bk, kv_len - j * Bk); }
+
+    // 0: every pair of the rectangle is hidden, 2: none is, 1: undecided.
+    template <uint32_t TERM>
+    __device__ __forceinline__ int term_kind(int q_lo, int q_hi, int kv_lo, int kv_hi, const TokenRange& rq,
+                                             const TokenRange& rk) const {
+        bool e = false, f = true;
+        if constexpr (TERM & FLEXATTN_M_CAUSAL) e = e || q_hi < kv_lo, f = f && q_lo >= kv_hi;
+        if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) e = e || q_lo - kv_hi > mask.window, f = f && q_hi - kv_lo <= mask.window;
+        if constexpr (TERM & FLEXATTN_M_PREFIX) e = e || kv_lo >= mask.prefix_len, f = f && kv_hi < mask.prefix_len;
+        if constexpr (TERM & FLEXATTN_M_CTX_LEN) e = e || kv_lo >= mask.ctx, f = f && kv_hi < mask.ctx;
+        if constexpr (TERM & FLEXATTN_M_DOCUMENT) {
+            e = e || rq.a1 < rk.a0 || rk.a1 < rq.a0;
+            f = f && rq.a0 == rq.a1 && rk.a0 == rk.a1 && rq.a0 == rk.a0;
+        }
+        if constexpr (TERM & FLEXATTN_M_NEIGHBORHOOD) {
+            const int span = 2 * mask.na_r;
+            e = e || rk.a1 < rq.a0 || rk.a0 > rq.a1 + span || rk.b1 < rq.b0 || rk.b0 > rq.b1 + span;
+            f = f && rk.a0 >= rq.a1 && rk.a1 <= rq.a0 + span && rk.b0 >= rq.b1 && rk.b1 <= rq.b0 + span;
+        }
+        return e ? 0 : (f ? 2 : 1);
+    }
+    __device__ __forceinline__ int kind(int i, int j, const TokenRange& rq, const TokenRange& rk) const {
+        const int q_lo = q_off + i * Bq, q_hi = q_lo + rows_of(i) - 1, kv_lo = j * Bk, kv_hi = kv_lo + keys_of(j) - 1;
+        int k = term_kind<T0>(q_lo, q_hi, kv_lo, kv_hi, rq, rk);
+        if constexpr (T1 != 0) {
+            const int k1 = term_kind<T1>(q_lo, q_hi, kv_lo, kv_hi, rq, rk);
+            k = k == 2 || k1 == 2 ? 2 : max(k, k1);
+        }
+        // what lies outside the score matrix counts as masked: a block that is cut short is never FULL
+        return k == 2 && (rows_of(i) < Bq || keys_of(j) < Bk) ? 1 : k;
+    }
+
+    // bits of [lo, hi] among the keys kv0 .. kv0 + 63
+    __device__ __forceinline__ static uint64_t span_bits(int lo, int hi, int kv0) {
+        const int h = min(max(hi - kv0, -1), 63) + 1, l = min(max(lo - kv0, 0), 64);
+        const uint64_t below_h = h == 0 ? 0ull : ~0ull >> (64 - h), below_l = l == 0 ? 0ull : ~0ull >> (64 - l);
+        return below_h & ~below_l;
+    }
+    template <uint32_t TERM>
+    __device__ __forceinline__ uint64_t term_bits(int q, int kv0, uint64_t match) const {
+        int hi = kv_len - 1, lo = 0;
+        if constexpr (TERM & FLEXATTN_M_CAUSAL) hi = min(hi, q);
+        if constexpr (TERM & FLEXATTN_M_PREFIX) hi = min(hi, mask.prefix_len - 1);
+        if constexpr (TERM & FLEXATTN_M_CTX_LEN) hi = min(hi, mask.ctx - 1);
+        if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) lo = max(__builtin_elementwise_sub_sat(q, mask.window), 0);
+        return span_bits(lo, hi, kv0) & ((TERM & Partial::kTagged) ? match : ~0ull);
+    }
+    // Unmasked scalars of block (i, j), counted by the whole wave.
+    __device__ __forceinline__ int count(int i, int j, int lane) const {
+        int cnt = 0;
+        const int rows = rows_of(i), keys = keys_of(j);
+        for (int r0 = 0; r0 < rows; r0 += 64) {
+            const int q = q_off + i * Bq + min(r0 + lane, rows - 1);
+            uint32_t q_tag = 0;
+            if constexpr (Partial::kDoc) q_tag = (uint32_t)docs[q];
+            if constexpr (Partial::kCanvas) q_tag = mask.query_pixel(q);
+            int mine = 0;
+            for (int k0 = 0; k0 < keys; k0 += 64) {
+                const int kv0 = j * Bk + k0, n = min(64, keys - k0);
+                uint64_t match = ~0ull;
+                if constexpr (Partial::kTags) {
+                    const int kv = min(kv0 + lane, kv_len - 1);
+                    uint32_t k_tag = 0;
+                    if constexpr (Partial::kDoc) k_tag = (uint32_t)docs[kv];
+                    if constexpr (Partial::kCanvas) k_tag = mask.key_pixel(kv);
+                    match = 0;
+                    for (uint64_t left = ~0ull >> (64 - n); left != 0;) {
+                        const int at = __builtin_ctzll(left);
+                        const uint32_t tag = (uint32_t)__builtin_amdgcn_readlane((int)k_tag, at);
+                        const uint64_t same = __ballot(k_tag == tag);
+                        left &= ~same;
+                        if constexpr (Partial::kDoc) match |= tag == q_tag ? same : 0ull;
+                        if constexpr (Partial::kCanvas) match |= mask.pixels_match(tag, q_tag) ? same : 0ull;
+                    }
+                }
+                uint64_t bits = term_bits<T0>(q, kv0, match);
+                if constexpr (T1 != 0) bits |= term_bits<T1>(q, kv0, match);
+                mine += __popcll(bits & (~0ull >> (64 - n)));
+            }
+            cnt += r0 + lane < rows ? mine : 0;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
+        return cnt;
+    }
+};
+
+struct LineArgs {
+    flexattn_mod_params p;
+    int Bm, Hm, NR, NC, Bq, Bk, q_len, kv_len;
+    int32_t *kv_num, *kv_idx, *full_kv_num, *full_kv_idx, *q_num, *q_idx, *full_q_num, *full_q_idx;
+    unsigned long long* stats;   // nullable
+};
 
 template <uint32_t MASK>
-__global__ __launch_bounds__(kClassifyWaves * 64) void classify_blocks_kernel(
-    flexattn_mod_params p, int Bm, int Hm, int NR, int NC, int Bq, int Bk, int q_len, int kv_len,
-    uint8_t* __restrict__ kinds, unsigned long long* __restrict__ stats) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long long nblocks = (long long)Bm * Hm * NR * NC;
-    const long long blk = (long long)blockIdx.x * kClassifyWaves + wave;
-    __shared__ unsigned long long s_acc[3];
-    if (threadIdx.x < 3) s_acc[threadIdx.x] = 0;
-    __syncthreads();
-    if (blk < nblocks) {
-        const int j = (int)(blk % NC);
-        const int i = (int)((blk / NC) % NR);
-        const int h = (int)((blk / ((long long)NC * NR)) % Hm);
-        const int b = (int)(blk / ((long long)NC * NR * Hm));
-        const int n = Bq * Bk;
-        const int q_off = q_offset_of(p, b);
-        int cnt = 0;
-        // Blocks that lie wholly inside the score matrix and that the index comparisons of the mask
-        // settle as a whole are not enumerated; everything else is evaluated scalar by scalar.
-        bool settled = false;
-        if ((i + 1) * Bq <= q_len && (j + 1) * Bk <= kv_len) {
-            const MaskRow<MASK> corner(p, b, h, q_off + i * Bq, kv_len);
-            const int q_lo = q_off + i * Bq, q_hi = q_lo + Bq - 1, kv_lo = j * Bk, kv_hi = kv_lo + Bk - 1;
-            if (corner.block_empty(q_lo, q_hi, kv_lo, kv_hi)) {
-                settled = true;
-            } else if (corner.block_full(q_lo, q_hi, kv_lo, kv_hi)) {
-                settled = true;
-                cnt = lane == 0 ? n : 0;
+__global__ __launch_bounds__(kLineThreads) void build_lines_kernel(const LineArgs a) {
+    using Eval = BlockEval<MASK>;
+    constexpr bool kTags = Eval::Partial::kTags;
+    __shared__ TokenRange s_fixed;                 // the tokens of the line itself
+    __shared__ uint8_t s_kind[kLineThreads];
+    __shared__ uint16_t s_todo[kLineThreads];
+    __shared__ int s_ntodo, s_part[kLineWaves], s_full[kLineWaves];
+    __shared__ unsigned long long s_scalars;       // unmasked scalars of the line's PARTIAL blocks
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const long long planes = (long long)a.Bm * a.Hm, row_lines = planes * a.NR, lines = row_lines + planes * a.NC;
+
+    for (long long id = blockIdx.x; id < lines; id += gridDim.x) {
+        const bool is_row = id < row_lines;
+        const long long line = is_row ? id : id - row_lines;
+        const int n_lines = is_row ? a.NR : a.NC, len = is_row ? a.NC : a.NR;
+        const int self = (int)(line % n_lines);
+        const int b = (int)(line / n_lines / a.Hm);
+        const Eval ev(a.p, b, a.q_len, a.kv_len, a.Bq, a.Bk);
+        int32_t* out_p = (is_row ? a.kv_idx : a.q_idx) + line * len;
+        int32_t* out_f = (is_row ? a.full_kv_idx : a.full_q_idx) + line * len;
+
+        if (tid == 0) s_scalars = 0;
+        if constexpr (kTags) {
+            if (tid == 0) s_fixed = kNoTokens;
+            __syncthreads();
+            TokenRange r = kNoTokens;
+            if (is_row) for (int t = tid; t < ev.rows_of(self); t += kLineThreads) ev.take_query(r, self * a.Bq + t);
+            else for (int t = tid; t < ev.keys_of(self); t += kLineThreads) ev.take_key(r, self * a.Bk + t);
+            atomicMin(&s_fixed.a0, r.a0);
+            atomicMax(&s_fixed.a1, r.a1);
+            if constexpr (Eval::Partial::kCanvas) {
+                atomicMin(&s_fixed.b0, r.b0);
+                atomicMax(&s_fixed.b1, r.b1);
             }
         }
-        for (int e = lane; e < (settled ? 0 : n); e += 64) {
-            // rows and keys past the end of the score matrix count as masked
-            const int q = i * Bq + e / Bk, kv = j * Bk + e % Bk;
-            MaskRow<MASK> row(p, b, h, q_off + min(q, q_len - 1), kv_len);
-            cnt += (q < q_len && row(kv)) ? 1 : 0;
-        }
-        for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
-        if (lane == 0) {
-            const uint8_t kind = cnt == 0 ? 0 : (cnt == n ? 2 : 1);
-            kinds[blk] = kind;
-            if (stats) {
-                if (kind == 1) atomicAdd(&s_acc[0], 1ull);
-                if (kind == 2) atomicAdd(&s_acc[1], 1ull);
-                atomicAdd(&s_acc[2], (unsigned long long)cnt);
-            }
-        }
-    }
-    __syncthreads();
-    if (stats && threadIdx.x == 0) {
-        if (s_acc[0]) atomicAdd(&stats[0], s_acc[0]);
-        if (s_acc[1]) atomicAdd(&stats[1], s_acc[1]);
-        if (s_acc[2]) atomicAdd(&stats[3], s_acc[2]);
-        if (blockIdx.x == 0) atomicAdd(&stats[2], (unsigned long long)nblocks);
-    }
-}
-
-// One wave per line.  Line `ln` of the plane `pl` reads kinds[pl * plane + ln * line_stride + k * elem_stride],
-// k = 0 .. len-1, and writes the partial (kind 1) and full (kind 2) lists of that line.
-__global__ __launch_bounds__(64) void compact_lines_kernel(
-    const uint8_t* __restrict__ kinds, int nlines, int len, long long plane, long long line_stride,
-    long long elem_stride, int32_t* __restrict__ num_partial, int32_t* __restrict__ idx_partial,
-    int32_t* __restrict__ num_full, int32_t* __restrict__ idx_full) {
-    const int lane = threadIdx.x;
-    const long long line = blockIdx.x;                  // global line = pl * nlines + ln
-    const long long pl = line / nlines, ln = line % nlines;
-    const uint8_t* src = kinds + pl * plane + ln * line_stride;
-    int32_t* out_p = idx_partial + line * len;
-    int32_t* out_f = idx_full + line * len;
-    int np = 0, nf = 0;
-    for (int k0 = 0; k0 < len; k0 += 64) {
-        const int k = k0 + lane;
-        const int kind = k < len ? src[(long long)k * elem_stride] : 0;
-        const unsigned long long mp = __ballot(kind == 1), mf = __ballot(kind == 2);
-        const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-        if (kind == 1) out_p[np + __popcll(mp & below)] = k;
-        if (kind == 2) out_f[nf + __popcll(mf & below)] = k;
-        np += __popcll(mp);
-        nf += __popcll(mf);
-    }
-    for (int k = lane; k < len; k += 64) {
-        if (k >= np) out_p[k] = 0;
-        if (k >= nf) out_f[k] = 0;
-    }
-    if (lane == 0) {
-        num_partial[line] = np;
-        num_full[line] = nf;
-    }
-}
-
-// Work order of one orientation: per plane, the lines sorted by descending num_a + num_b (ties by
-// ascending index) with a bitonic sort of (kOrderCountMax - count, index) keys in LDS; more than
-// kOrderMax lines are left in the fixed order (descending index if `reversed`, else ascending).
-constexpr int kOrderMax = 8192, kOrderIdxBits = 13, kOrderCountMax = (1 << 18) - 1;
-__global__ __launch_bounds__(256) void order_lines_kernel(const int32_t* __restrict__ num_a,
-                                                          const int32_t* __restrict__ num_b, int n, int reversed,
-                                                          int32_t* __restrict__ order) {
-    __shared__ uint32_t keys[kOrderMax];
-    const int64_t base = (int64_t)blockIdx.x * n;
-    if (n > kOrderMax) {
-        for (int i = threadIdx.x; i < n; i += 256) order[base + i] = reversed ? n - 1 - i : i;
-        return;
-    }
-    int n_pad = 1;
-    while (n_pad < n) n_pad <<= 1;
-    for (int i = threadIdx.x; i < n_pad; i += 256) {
-        uint32_t key = 0xffffffffu;
-        if (i < n) {
-            const int cnt = min(num_a[base + i] + num_b[base + i], kOrderCountMax);
-            key = ((uint32_t)(kOrderCountMax - cnt) << kOrderIdxBits) | (uint32_t)i;
-        }
-        keys[i] = key;
-    }
-    __syncthreads();
-    for (int k = 2; k <= n_pad; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < n_pad; i += 256) {
-                const int partner = i ^ j;
-                if (partner > i) {
-                    const uint32_t x = keys[i], y = keys[partner];
-                    const bool ascending = (i & k) == 0;
-                    if ((x > y) == ascending) {
-                        keys[i] = y;
-                        keys[partner] = x;
+        int np = 0, nf = 0;
+        for (int c0 = 0; c0 < len; c0 += kLineThreads) {
+            if (tid == 0) s_ntodo = 0;
+            __syncthreads();
+            const int k = c0 + tid;
+            int kind = 0;
+            if (k < len) {
+                const int i = is_row ? self : k, j = is_row ? k : self;
+                kind = ev.kind(i, j, kAnyTokens, kAnyTokens);       // what the index comparisons alone decide
+                if constexpr (kTags) {
+                    if (kind == 1) {
+                        TokenRange r = kNoTokens;
+                        if (is_row) for (int t = 0; t < ev.keys_of(k); ++t) ev.take_key(r, k * a.Bk + t);
+                        else for (int t = 0; t < ev.rows_of(k); ++t) ev.take_query(r, k * a.Bq + t);
+                        kind = is_row ? ev.kind(i, j, s_fixed, r) : ev.kind(i, j, r, s_fixed);
                     }
+                }
+                if (kind == 1) s_todo[atomicAdd(&s_ntodo, 1)] = (uint16_t)tid;
+            }
+            s_kind[tid] = (uint8_t)kind;
+            __syncthreads();
+            for (int t = wave; t < s_ntodo; t += kLineWaves) {
+                const int kk = s_todo[t];
+                const int cnt = is_row ? ev.count(self, c0 + kk, lane) : ev.count(c0 + kk, self, lane);
+                if (lane == 0) {
+                    const int full = cnt == a.Bq * a.Bk;
+                    s_kind[kk] = (uint8_t)(cnt == 0 ? 0 : (full ? 2 : 1));
+                    if (!full) atomicAdd(&s_scalars, (unsigned long long)cnt);
                 }
             }
             __syncthreads();
+            kind = s_kind[tid];
+            const unsigned long long mp = __ballot(kind == 1), mf = __ballot(kind == 2);
+            if (lane == 0) {
+                s_part[wave] = __popcll(mp);
+                s_full[wave] = __popcll(mf);
+            }
+            __syncthreads();
+            int p0 = np, f0 = nf;
+#pragma unroll
+            for (int w = 0; w < kLineWaves; ++w) {
+                p0 += w < wave ? s_part[w] : 0;
+                f0 += w < wave ? s_full[w] : 0;
+                np += s_part[w];
+                nf += s_full[w];
+            }
+            const unsigned long long below = (1ull << lane) - 1;
+            if (kind == 1) out_p[p0 + __popcll(mp & below)] = k;
+            if (kind == 2) out_f[f0 + __popcll(mf & below)] = k;
         }
+        for (int k = np + tid; k < len; k += kLineThreads) out_p[k] = 0;
+        for (int k = nf + tid; k < len; k += kLineThreads) out_f[k] = 0;
+        if (tid == 0) {
+            (is_row ? a.kv_num : a.q_num)[line] = np;
+            (is_row ? a.full_kv_num : a.full_q_num)[line] = nf;
+            if (is_row && a.stats) {
+                if (np) atomicAdd(&a.stats[0], (unsigned long long)np);
+                if (nf) atomicAdd(&a.stats[1], (unsigned long long)nf);
+                const unsigned long long scalars = s_scalars + (unsigned long long)nf * (unsigned)(a.Bq * a.Bk);
+                if (scalars) atomicAdd(&a.stats[3], scalars);
+                if (id == 0) atomicAdd(&a.stats[2], (unsigned long long)(row_lines * a.NC));
+            }
+        }
+        __syncthreads();
     }
-    for (int i = threadIdx.x; i < n; i += 256) order[base + i] = (int32_t)(keys[i] & ((1u << kOrderIdxBits) - 1));
+}
+
+// Work order of both orientations: per plane, the lines sorted by descending num + full_num (ties by
+// ascending index).  A line's place is the number of keys (kOrderCountMax - count, index) below its own,
+// counted by one thread over a copy of all keys in LDS: no passes and no barriers in between, which is
+// what a sort of a few hundred lines consists of otherwise (bitonic: 7.6 us for 256 lines).  More than
+// kOrderMax lines are left in the fixed order: descending index for rows, ascending for columns.
+constexpr int kOrderMax = 8192, kOrderIdxBits = 13, kOrderCountMax = (1 << 18) - 1;
+__global__ __launch_bounds__(256) void order_lines_kernel(const LineArgs a, int32_t* __restrict__ kv_order,
+                                                          int32_t* __restrict__ q_order) {
+    __shared__ __attribute__((aligned(16))) uint32_t keys[kOrderMax];
+    const bool rows = blockIdx.y == 0;
+    int32_t* order = rows ? kv_order : q_order;
+    const int n = rows ? a.NR : a.NC;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (!order || (int)(blockIdx.x * 256) >= n) return;
+    for (int plane = blockIdx.z; plane < a.Bm * a.Hm; plane += gridDim.z) {
+        const int64_t base = (int64_t)plane * n;
+        if (n > kOrderMax) {
+            if (i < n) order[base + i] = rows ? n - 1 - i : i;
+            continue;
+        }
+        const int32_t* num = (rows ? a.kv_num : a.q_num) + base;
+        const int32_t* full = (rows ? a.full_kv_num : a.full_q_num) + base;
+        const int n4 = (n + 3) & ~3;
+        for (int t = threadIdx.x; t < n4; t += 256)
+            keys[t] = t < n ? ((uint32_t)(kOrderCountMax - min(num[t] + full[t], kOrderCountMax)) << kOrderIdxBits) | (uint32_t)t
+                            : 0xffffffffu;
+        __syncthreads();
+        if (i < n) {
+            typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+            const uint32_t own = keys[i];
+            int place = 0;
+#pragma unroll 4
+            for (int t = 0; t < n4; t += 4) {
+                const u32x4_t v = *(const u32x4_t*)&keys[t];
+                place += (v[0] < own) + (v[1] < own) + (v[2] < own) + (v[3] < own);
+            }
+            order[base + place] = i;
+        }
+        __syncthreads();
+    }
 }
 
 __global__ void zero_stats_kernel(unsigned long long* stats) {
@@ -165,14 +326,10 @@ __global__ __launch_bounds__(256) void paged_convert_kernel(
 }
 
 template <uint32_t MASK>
-static int launch_classify(const flexattn_mod_params& p, const flexattn_blockmask* bm, uint8_t* kinds,
-                           unsigned long long* stats, hipStream_t st) {
-    const int NR = (bm->q_len + bm->Bq - 1) / bm->Bq, NC = (bm->kv_len + bm->Bk - 1) / bm->Bk;
-    const long long nblocks = (long long)bm->Bm * bm->Hm * NR * NC;
-    const long long grid = (nblocks + kClassifyWaves - 1) / kClassifyWaves;
-    hipLaunchKernelGGL(classify_blocks_kernel<MASK>, dim3((unsigned)grid), dim3(kClassifyWaves * 64), 0, st, p,
-                       bm->Bm, bm->Hm, NR, NC, bm->Bq, bm->Bk, bm->q_len, bm->kv_len, kinds, stats);
-    return FLEXATTN_OK;
+static void launch_lines(const LineArgs& a, hipStream_t st) {
+    const long long lines = (long long)a.Bm * a.Hm * (a.NR + a.NC);
+    const unsigned grid = (unsigned)(lines < (1 << 20) ? lines : (1 << 20));    // (the kernel strides over the rest)
+    hipLaunchKernelGGL(build_lines_kernel<MASK>, dim3(grid), dim3(kLineThreads), 0, st, a);
 }
 
 }  // namespace flexattn
@@ -222,16 +379,21 @@ extern "C" int flexattn_blockmask_build(uint32_t mask_id, const flexattn_mod_par
     if (ws_bytes < flexattn_blockmask_workspace_bytes(bm->Bm, bm->Hm, bm->q_len, bm->kv_len, bm->Bq, bm->Bk))
         return FLEXATTN_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    flexattn_mod_params p = {};
-    if (params) p = *params;
-    uint8_t* kinds = (uint8_t*)ws;
-    unsigned long long* st_dev = (unsigned long long*)stats;
-    if (st_dev) hipLaunchKernelGGL(zero_stats_kernel, dim3(1), dim3(64), 0, st, st_dev);
+    LineArgs a = {};
+    if (params) a.p = *params;
+    a.Bm = bm->Bm; a.Hm = bm->Hm; a.NR = NR; a.NC = NC; a.Bq = bm->Bq; a.Bk = bm->Bk;
+    a.q_len = bm->q_len; a.kv_len = bm->kv_len;
+    a.kv_num = bm->kv_num_blocks; a.kv_idx = bm->kv_indices;
+    a.full_kv_num = bm->full_kv_num_blocks; a.full_kv_idx = bm->full_kv_indices;
+    a.q_num = bm->q_num_blocks; a.q_idx = bm->q_indices;
+    a.full_q_num = bm->full_q_num_blocks; a.full_q_idx = bm->full_q_indices;
+    a.stats = (unsigned long long*)stats;
+    if (a.stats) hipLaunchKernelGGL(zero_stats_kernel, dim3(1), dim3(64), 0, st, a.stats);
 
-    // The block classifier is instantiated for every mask the two-term encoding can express with
+    // The builder is instantiated for every mask the two-term encoding can express with
     // the primitives below; unknown combinations are rejected rather than approximated.
     switch (mask_id) {
-#define CASE(M) case M: launch_classify<M>(p, bm, kinds, st_dev, st); break;
+#define CASE(M) case M: launch_lines<M>(a, st); break;
         CASE(FLEXATTN_MASK_NONE)
         CASE(FLEXATTN_MASK_CAUSAL)
         CASE(FLEXATTN_MASK_SLIDING_WINDOW)
@@ -248,23 +410,12 @@ extern "C" int flexattn_blockmask_build(uint32_t mask_id, const flexattn_mod_par
         default: return FLEXATTN_ERR_UNSUPPORTED;
     }
     FLEXATTN_HIP_TRY(hipGetLastError());
-
-    const long long planes = (long long)bm->Bm * bm->Hm;
-    // rows of blocks: line = row i, elements = columns j
-    hipLaunchKernelGGL(compact_lines_kernel, dim3((unsigned)(planes * NR)), dim3(64), 0, st, kinds, NR, NC,
-                       (long long)NR * NC, (long long)NC, 1ll, bm->kv_num_blocks, bm->kv_indices,
-                       bm->full_kv_num_blocks, bm->full_kv_indices);
-    // columns of blocks: line = column j, elements = rows i
-    hipLaunchKernelGGL(compact_lines_kernel, dim3((unsigned)(planes * NC)), dim3(64), 0, st, kinds, NC, NR,
-                       (long long)NR * NC, 1ll, (long long)NC, bm->q_num_blocks, bm->q_indices,
-                       bm->full_q_num_blocks, bm->full_q_indices);
-    if (bm->kv_order)
-        hipLaunchKernelGGL(order_lines_kernel, dim3((unsigned)planes), dim3(256), 0, st, bm->kv_num_blocks,
-                           bm->full_kv_num_blocks, NR, 1, bm->kv_order);
-    if (bm->q_order)
-        hipLaunchKernelGGL(order_lines_kernel, dim3((unsigned)planes), dim3(256), 0, st, bm->q_num_blocks,
-                           bm->full_q_num_blocks, NC, 0, bm->q_order);
-    FLEXATTN_HIP_TRY(hipGetLastError());
+    if (bm->kv_order || bm->q_order) {
+        const int planes = bm->Bm * bm->Hm, longest = NR > NC ? NR : NC;
+        hipLaunchKernelGGL(order_lines_kernel, dim3((unsigned)((longest + 255) / 256), 2, (unsigned)(planes < 4096 ? planes : 4096)),
+                           dim3(256), 0, st, a, bm->kv_order, bm->q_order);
+        FLEXATTN_HIP_TRY(hipGetLastError());
+    }
     return FLEXATTN_OK;
 }
 

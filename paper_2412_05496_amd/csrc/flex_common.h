@@ -73,7 +73,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 
 // ---------------------------------------------------------------------------------------
 // mask_mod: OR of up to two AND-terms over the primitive predicates.
-// A MaskRow caches what depends only on (b, h, q_idx); operator() takes kv_idx.
 // ---------------------------------------------------------------------------------------
 // Token index -> pixel of the canvas, for the neighborhood mask (appendix, Neighborhood Attention).
 struct CanvasOrder {
@@ -126,116 +125,11 @@ struct NoCanvas {
     __device__ __forceinline__ void pixel(int, int&, int&) const {}
 };
 
-template <uint32_t TERM>
-struct MaskTermRow {
-    int q, window, prefix_len, doc_q, ctx;
-    const int32_t* doc_row;
-    // NEIGHBORHOOD: the window of the query pixel, [x0, x0 + span] x [y0, y0 + span]
-    std::conditional_t<(TERM & FLEXATTN_M_NEIGHBORHOOD) != 0, CanvasOrder, NoCanvas> canvas;
-    int x0, y0, span;
-    // doc_q_known >= 0: the caller already holds doc_ids[b, q_idx] (no table read here)
-    __device__ __forceinline__ MaskTermRow(const flexattn_mod_params& p, int b, int /*h*/, int q_idx, int doc_q_known = -1)
-        : canvas(p) {
-        q = q_idx;
-        window = p.window;
-        prefix_len = p.prefix_len;
-        doc_row = nullptr;
-        doc_q = 0;
-        ctx = 0;
-        x0 = y0 = span = 0;
-        if constexpr (TERM & FLEXATTN_M_NEIGHBORHOOD) {
-            const int r = p.na_kernel >> 1;
-            int qx, qy;
-            canvas.pixel(q_idx, qx, qy);
-            x0 = min(max(qx, r), p.na_width - 1 - r) - r;
-            y0 = min(max(qy, r), p.na_height - 1 - r) - r;
-            span = 2 * r;
-        }
-        if constexpr (TERM & FLEXATTN_M_DOCUMENT) {
-            doc_row = p.doc_ids + (int64_t)b * p.doc_stride_b;
-            doc_q = doc_q_known >= 0 ? doc_q_known : doc_row[q_idx];
-        }
-        if constexpr (TERM & FLEXATTN_M_CTX_LEN) ctx = p.ctx_lens[b];
-    }
-    __device__ __forceinline__ bool operator()(int kv) const {
-        int doc_kv = 0;
-        if constexpr (TERM & FLEXATTN_M_DOCUMENT) doc_kv = doc_row[kv];
-        return eval(kv, doc_kv);
-    }
-    // Rectangle tests on q_lo <= q <= q_hi, kv_lo <= kv <= kv_hi, decided from the primitives that are
-    // plain index comparisons: block_empty is true only if NO pair can pass this term, block_full only
-    // if EVERY pair does (a term with a table lookup or the canvas decode is never declared full).
-    __device__ __forceinline__ bool block_empty(int q_lo, int q_hi, int kv_lo, int kv_hi) const {
-        bool e = false;
-        if constexpr (TERM & FLEXATTN_M_CAUSAL) e = e || (q_hi < kv_lo);
-        if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) e = e || (q_lo - kv_hi > window);
-        if constexpr (TERM & FLEXATTN_M_PREFIX) e = e || (kv_lo >= prefix_len);
-        if constexpr (TERM & FLEXATTN_M_CTX_LEN) e = e || (kv_lo >= ctx);
-        return e;
-    }
-    __device__ __forceinline__ bool block_full(int q_lo, int q_hi, int kv_lo, int kv_hi) const {
-        if constexpr ((TERM & (FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD)) != 0) return false;
-        bool f = true;
-        if constexpr (TERM & FLEXATTN_M_CAUSAL) f = f && (q_lo >= kv_hi);
-        if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) f = f && (q_hi - kv_lo <= window);
-        if constexpr (TERM & FLEXATTN_M_PREFIX) f = f && (kv_hi < prefix_len);
-        if constexpr (TERM & FLEXATTN_M_CTX_LEN) f = f && (kv_hi < ctx);
-        return f;
-    }
-    // the same with doc_ids[b, kv] supplied by the caller
-    __device__ __forceinline__ bool eval(int kv, int doc_kv) const {
-        bool r = true;
-        if constexpr (TERM & FLEXATTN_M_CAUSAL) r = r && (q >= kv);
-        if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) r = r && (q - kv <= window);
-        if constexpr (TERM & FLEXATTN_M_DOCUMENT) r = r && (doc_kv == doc_q);
-        if constexpr (TERM & FLEXATTN_M_PREFIX) r = r && (kv < prefix_len);
-        if constexpr (TERM & FLEXATTN_M_CTX_LEN) r = r && (kv < ctx);
-        if constexpr (TERM & FLEXATTN_M_NEIGHBORHOOD) {
-            int kx, ky;
-            canvas.pixel(kv, kx, ky);
-            r = r && ((unsigned)(kx - x0) <= (unsigned)span) && ((unsigned)(ky - y0) <= (unsigned)span);
-        }
-        return r;
-    }
-};
-
 // Offset conversion for inference (section 5.2): the position the mods see for query row 0 of
 // batch entry b.
 __device__ __forceinline__ int q_offset_of(const flexattn_mod_params& p, int b) {
     return p.q_offsets ? ldc(p.q_offsets + b) : 0;
 }
-
-template <uint32_t MASK>
-struct MaskRow {
-    static constexpr uint32_t T0 = MASK & 0xffu, T1 = (MASK >> 8) & 0xffu;
-    MaskTermRow<T0> t0;
-    MaskTermRow<T1> t1;
-    int kv_last;
-    // kv_len: keys at or past it do not exist (last block of a length that is no multiple of the
-    // block size): they are masked, and the primitives are evaluated at the last real key instead
-    // so that no table is read out of range.  q_idx must be a real row.
-    __device__ __forceinline__ MaskRow(const flexattn_mod_params& p, int b, int h, int q_idx, int kv_len,
-                                       int doc_q_known = -1)
-        : t0(p, b, h, q_idx, doc_q_known), t1(p, b, h, q_idx, doc_q_known), kv_last(kv_len - 1) {}
-    // Whole-rectangle shortcuts (exact implications of the index comparisons, never a guess): the
-    // mask hides every pair / no pair of the rectangle.  The rectangle must lie inside the score matrix.
-    __device__ __forceinline__ bool block_empty(int q_lo, int q_hi, int kv_lo, int kv_hi) const {
-        bool e = T0 != 0 && t0.block_empty(q_lo, q_hi, kv_lo, kv_hi);
-        if constexpr (T1 != 0) e = e && t1.block_empty(q_lo, q_hi, kv_lo, kv_hi);
-        return e;
-    }
-    __device__ __forceinline__ bool block_full(int q_lo, int q_hi, int kv_lo, int kv_hi) const {
-        bool f = T0 == 0 || t0.block_full(q_lo, q_hi, kv_lo, kv_hi);
-        if constexpr (T1 != 0) f = f || t1.block_full(q_lo, q_hi, kv_lo, kv_hi);
-        return f;
-    }
-    __device__ __forceinline__ bool operator()(int kv) const {
-        const int kc = min(kv, kv_last);
-        bool r = t0(kc);
-        if constexpr (T1 != 0) r = r || t1(kc);
-        return r && kv <= kv_last;
-    }
-};
 
 // ---------------------------------------------------------------------------------------
 // mask_mod of a PARTIAL block inside the MFMA kernels.
@@ -309,11 +203,15 @@ struct PartialMask {
         canvas.pixel(kv, x, y);
         return (uint32_t)x | ((uint32_t)y << y_shift);
     }
-    __device__ __forceinline__ uint32_t query_pixel(int q) const {
-        int x, y;
+    // top left corner of the window of a query: centred on its pixel, moved inside the canvas
+    __device__ __forceinline__ void window_corner(int q, int& x, int& y) const {
         canvas.pixel(q, x, y);
         x = min(max(x, na_r), na_w - 1 - na_r) - na_r;
         y = min(max(y, na_r), na_h - 1 - na_r) - na_r;
+    }
+    __device__ __forceinline__ uint32_t query_pixel(int q) const {
+        int x, y;
+        window_corner(q, x, y);
         return ((uint32_t)x | ((uint32_t)y << y_shift)) - guard;
     }
     __device__ __forceinline__ bool pixels_match(uint32_t key_tag, uint32_t query_tag) const {

@@ -1,0 +1,94 @@
+"""GPU parity where the per-lane bit masks and token tags of PARTIAL blocks can go wrong: document ids that
+are not packed (many distinct ids in 32 tokens, negative and large ones), canvases of one row or one
+column, windows as large as the canvas, and BlockMask lines longer than a workgroup takes at once.
+BlockMasks bit for bit; O, LSE and gradients at the tolerances of tests/helpers.py."""
+import pytest
+import torch
+
+import flex_workloads as wlm
+from oracle import flex_oracle as fo
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def scattered_ids(B, S, n_ids, seed):
+    g = torch.Generator().manual_seed(seed)
+    names = torch.tensor([-5, 0, 2 ** 31 - 1, -2 ** 31, 7] + list(range(100, 200)), dtype=torch.int64)[:n_ids]
+    return names[torch.randint(0, n_ids, (B, S), generator=g)].to(torch.int32).contiguous()
+
+
+@pytest.mark.parametrize("D,score,Bq,Bk,S,n_ids", [
+    (64, "identity", 128, 64, 320, 40),      # up to 32 distinct ids in 32 tokens
+    (64, "alibi", 64, 128, 257, 3),
+    (128, "rel_bias_softcap", 128, 64, 200, 5),
+    (128, "alibi", 128, 128, 129, 1),        # one document: the tags never hide anything
+])
+def test_scattered_documents(D, score, Bq, Bk, S, n_ids):
+    dev = torch.device(DEV)
+    wl = wlm.CFG3.scaled(name="scattered", B=2, Hq=2, Hkv=1, S=S, D=D, Bq=Bq, Bk=Bk, score=score, softcap=20.0, rel_len=40,
+                         doc_len_min=50, doc_len_max=90, seed=4100 + S)
+    inp = wlm.make_train_inputs(wl, with_dO=True)
+    inp.doc_ids = scattered_ids(2, S, n_ids, seed=S)
+    score_mod, mask_mod = hp.oracle_mods(wl, inp)
+    print(f"[case] scattered documents D={D} {score} S={S} ids={n_ids}", flush=True)
+    O, LSE, bm, ids = hp.run_forward(wl, inp, dev)
+    hp.assert_blockmask_equal(bm, fo.create_block_mask(mask_mod, 2, 1, S, S, Bq, Bk))
+    hp.check_output(O, LSE, *fo.flex_attention(inp.Q, inp.K, inp.V, score_mod, mask_mod, inp.scale))
+    ref = fo.flex_attention_backward(inp.Q, inp.K, inp.V, inp.dO, score_mod, mask_mod, inp.scale)
+    for stored in (False, True):
+        for name, got, r in zip(("dQ", "dK", "dV"), hp.run_backward(wl, inp, dev, O, LSE, bm, ids, stored=stored), ref):
+            hp.check_grad(name, got, r)
+
+
+@pytest.mark.parametrize("w,h,k,layout,tile", [(200, 1, 1, "row_major", 0), (1, 130, 1, "row_major", 0),
+                                               (15, 15, 15, "row_major", 0), (17, 9, 9, "row_major", 0),
+                                               (24, 8, 7, "tiled", 4), (16, 16, 3, "morton", 0)])
+def test_canvas_edges(w, h, k, layout, tile):
+    import paper_2412_05496_amd as fa
+    S, dev = w * h, torch.device(DEV)
+    wl = wlm.CFG1.scaled(name="canvas", B=1, Hq=2, Hkv=2, S=S, D=64, Bq=128, Bk=64, seed=4200 + S)
+    inp = wlm.make_train_inputs(wl, with_dO=True)
+    mask_mod, score_mod = fo.neighborhood_mask(w, h, k, layout, tile), fo.Identity()
+    params = fa.ModParams(na_width=w, na_height=h, na_kernel=k, na_tile=tile,
+                          na_layout={"row_major": fa.NA_ROW_MAJOR, "tiled": fa.NA_TILED, "morton": fa.NA_MORTON}[layout])
+    print(f"[case] canvas {w}x{h} K={k} {layout}", flush=True)
+    bm = fa.alloc_blockmask(1, 1, S, S, wl.Bq, wl.Bk, device=dev)
+    fa.flexattn_blockmask_build(fa.MASK_NEIGHBORHOOD, params, bm)
+    torch.cuda.synchronize()
+    hp.assert_blockmask_equal(bm, fo.create_block_mask(mask_mod, 1, 1, S, S, wl.Bq, wl.Bk))
+    Q, K, V = (t.to(dev) for t in (inp.Q, inp.K, inp.V))
+    O, LSE = torch.full_like(Q, float("nan")), torch.full(Q.shape[:3], float("nan"), device=dev)
+    fa.flexattn_forward(Q, K, V, fa.SCORE_IDENTITY, fa.MASK_NEIGHBORHOOD, params, bm, inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    hp.check_output(O, LSE, *fo.flex_attention(inp.Q, inp.K, inp.V, score_mod, mask_mod, inp.scale))
+    ref = fo.flex_attention_backward(inp.Q, inp.K, inp.V, inp.dO, score_mod, mask_mod, inp.scale)
+    ids = (fa.MASK_NEIGHBORHOOD, fa.SCORE_IDENTITY, params, Q, K, V)
+    for stored in (False, True):
+        for name, got, r in zip(("dQ", "dK", "dV"), hp.run_backward(wl, inp, dev, O, LSE, bm, ids, stored=stored), ref):
+            hp.check_grad(name, got, r)
+
+
+@pytest.mark.parametrize("q_len,kv_len,Bq,Bk", [(48, 4800, 8, 16), (2049, 70, 8, 16), (100, 257 * 5, 33, 5), (130, 200, 130, 200)])
+def test_long_lines_and_odd_blocks(q_len, kv_len, Bq, Bk):
+    """More than 256 blocks in a line (both orientations), block sizes above 64 that are no power of two,
+    query offsets, and more than 256 lines to order."""
+    import paper_2412_05496_amd as fa
+    n = max(q_len, kv_len) + 40
+    docs = scattered_ids(1, n, 3, seed=q_len)
+    packed = wlm.document_ids([60, 37, 300] + [n - 397] if n > 397 else [n // 3, n - n // 3])[None, :].contiguous()
+    off = torch.tensor([40], dtype=torch.int32)
+    p = dict(q_offsets=off.to(DEV))
+    cases = [(fa.MASK_DOCUMENT_CAUSAL, fa.ModParams(doc_ids=docs.to(DEV), **p), fo.and_mask(fo.document_mask(docs), fo.causal_mask)),
+             (fa.MASK_DOCUMENT, fa.ModParams(doc_ids=packed.to(DEV), **p), fo.document_mask(packed)),
+             (fa.MASK_SWA_CAUSAL_OR_PREFIX, fa.ModParams(window=30, prefix_len=19, **p),
+              fo.or_mask(fo.and_mask(fo.causal_mask, fo.sliding_window_mask(30)), fo.prefix_mask(19)))]
+    for mask_id, params, mod in cases:
+        print(f"[case] mask {mask_id:#x} {q_len}x{kv_len} blocks {Bq}x{Bk}", flush=True)
+        bm = fa.alloc_blockmask(1, 1, q_len, kv_len, Bq, Bk, device=DEV)
+        for name in ("kv_indices", "full_kv_indices", "q_indices", "full_q_indices"):
+            getattr(bm, name).fill_(-7)
+        fa.flexattn_blockmask_build(mask_id, params, bm)
+        torch.cuda.synchronize()
+        hp.assert_blockmask_equal(bm, fo.create_block_mask(fo.with_q_offset(mod, off), 1, 1, q_len, kv_len, Bq, Bk))
