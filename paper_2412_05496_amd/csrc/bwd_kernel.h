@@ -129,17 +129,37 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const BwdArgs a) {
 // Q / dO tiles and the per-row scalars are double buffered in LDS; the loads of step v+1 are
 // issued at the top of step v.  Two barriers per step: after the exchange writes, and at the end
 // (exchange buffer and ring slot free again, next tiles landed).
+//
+// kOwn (D = 64): there both accumulators fit a wave, so every wave keeps dV^T and dK^T of its own 32 rows x
+// 32 keys per step: no exchange, no selects between P and dS, one barrier a step, and the two waves of the
+// same keys add their halves up once at the end.  V waits in LDS instead of registers (16 of them), which
+// is what keeps three workgroups on a CU: with V in registers the kernel spills, and two workgroups are 20 %
+// slower.  Blocks of a PARTIAL step that the mask hides from all 32 rows skip everything but S and dP.
+// Step by step it is bound by the sum of its MFMAs and its vector work, short columns by the turnover of
+// workgroups.  us, exchange -> own rows (one MI355X): causal, 64 x 16 heads, S = 1024: 491 -> 472; window of
+// 1024, S = 5000, Hq 16, Hkv 2, B = 4: 222 -> 210; packed documents with ALiBi, S = 16384, 16 heads: 262 -> 252;
+// soft-cap, S = 4096, 64 heads: 532 -> 502; relative bias, window 1024, S = 8192: 598 -> 548.
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
+// Which form: own rows at D = 64.  A soft-cap on top of a bias, and the pixel compares of a canvas, leave too
+// few registers at three waves per SIMD (6 to 24 spills: 431 -> 447 us with ALiBi, 350 -> 370 with documents
+// and a relative bias; canvas 684 -> 763) and keep the exchange, as does D = 128, whose two accumulators
+// are 128 registers.
+template <int D, uint32_t MASK, uint32_t SCORE>
+constexpr bool dkdv_own_rows() {
+    constexpr bool biased_cap = (SCORE & FLEXATTN_SCORE_SOFTCAP) && (SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS));
+    return D == 64 && !PartialMask<MASK>::kCanvas && !biased_cap;
+}
 template <int D, uint32_t MASK, uint32_t SCORE>
 __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv_kernel(const BwdArgs a) {
     constexpr int TQ = 64;                         // query rows per step
     constexpr int TILE = TQ * D;                   // elements per LDS tile
     constexpr int NKS = D / 16, NDB = D / 32;
+    constexpr bool kOwn = dkdv_own_rows<D, MASK, SCORE>();
     using Loader = WaveTileLoader<D, 4>;
-    __shared__ __attribute__((aligned(1024))) bf16 smem[2 * 2 * TILE];        // 2 x (Q tile, dO tile)
-    __shared__ __attribute__((aligned(1024))) u32x4 s_xchg[4][2][64];         // [wave][16-row slice][lane]
+    __shared__ __attribute__((aligned(1024))) bf16 smem[(kOwn ? 5 : 4) * TILE];   // 2 x (Q tile, dO tile); kOwn: V tile
+    __shared__ __attribute__((aligned(1024))) u32x4 s_xchg[kOwn ? 1 : 4][2][64];   // [wave][16-row slice][lane]
     __shared__ __attribute__((aligned(256))) float s_row[2][2][TQ];           // [slot][rc | -delta][row]
     constexpr int kListMax = 512;
     __shared__ int s_steps[kListMax + 2];          // the walk of the current head, see below
@@ -175,7 +195,7 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
     const int kv_lane = kv0 + 32 * kb + l32;
 
     // K, V fragments of this wave's 32 keys: B operands (column = key, k-slots = dims)
-    bf16x8 kf[NKS], vf[NKS];
+    bf16x8 kf[NKS], vf[kOwn ? 1 : NKS];
     {
         // keys past kv_len (last tile of a length that is no multiple of 64) take a copy of the last
         // real key; the mask hides them and they are never stored
@@ -185,15 +205,19 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
             kf[ks] = *(const bf16x8*)(kp + ks * 16);
-            vf[ks] = *(const bf16x8*)(vp + ks * 16);
+            if constexpr (!kOwn) vf[ks] = *(const bf16x8*)(vp + ks * 16);
         }
     }
 
-    f32x16 acc[NDB];                    // x = 0: dV^T, x = 1: dK^T (row = dim, column = key)
+    // x = 0: dV^T, x = 1: dK^T (row = dim, column = key); kOwn: dV^T here, dK^T in acc_k
+    f32x16 acc[NDB], acc_k[kOwn ? NDB : 1];
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[db][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) {
+            acc[db][r] = 0.0f;
+            if constexpr (kOwn) acc_k[db][r] = 0.0f;
+        }
 
     const int sub = a.Bq / TQ;          // steps per BlockMask row block (1 or 2)
     const int sub_shift = sub >> 1;
@@ -205,12 +229,20 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
     const int q_row_bytes = (int)a.q_ss * 2, do_row_bytes = (int)a.do_ss * 2;
     // scores: this wave's 32 rows of the Q tile (the dO tile is one tile further)
     const RowReader<D> row_reader(l32, half, ring + x * 32 * D * 2);
+    // kOwn: V's 64 rows wait in LDS (rows past kv_len as zeros), this wave's keys at v_lds beside row_reader's offsets
+    const uint32_t v_lds = (uint32_t)(4 * TILE + (kb - x) * 32 * D) * 2u;
+    if constexpr (kOwn) {
+        const Loader v_loader(a.v_ss, w, lane);
+        v_loader.start(make_rsrc(a.V + b * a.v_sb + hkv * a.v_sh, (uint32_t)((a.kv_len - 1) * a.v_ss + D) * 2u),
+                       ring + 4 * TILE * 2, kv0 * (int)a.v_ss * 2);     // (awaited with the first step's tiles)
+    }
     // outputs: the tile this wave contracts with (x = 0: dO, x = 1: Q), its own rows first, then
     // its partner's
-    const uint32_t out_tile = ring + (x ? 0 : TILE * 2);
+    // (kOwn: its own rows of both tiles, dO one tile behind Q)
+    const uint32_t out_tile = ring + (x || kOwn ? 0 : TILE * 2);
     const TrReader<D> tr_own(lane, out_tile + x * 32 * D * 2), tr_other(lane, out_tile + (1 - x) * 32 * D * 2);
     const uint32_t row_lds = lds_addr(&s_row[0][0][0]) + (32 * x + 4 * half) * 4;
-    const uint32_t xchg_mine = lds_addr(&s_xchg[w][0][lane]), xchg_theirs = lds_addr(&s_xchg[w ^ 2][0][lane]);
+    const uint32_t xchg_mine = lds_addr(&s_xchg[kOwn ? 0 : w][0][lane]), xchg_theirs = lds_addr(&s_xchg[kOwn ? 0 : w ^ 2][0][lane]);
     const int q_off = q_offset_of(a.p, b);
     const Mask mask(a.p, b, a.kv_len);
     uint32_t k_tag = 0;
@@ -231,7 +263,7 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
             if (w == 2 * slot) s_tag[slot][lane] = mask.query_pixel(q_off + min(q0 + lane, a.q_len - 1));
         }
     };
-    const int ds_lane = w * 1024 + lane * 8;     // this lane's place inside a step of dS in memory (bf16 elements)
+    const uint32_t ds_lane = (uint32_t)(w * 1024 + lane * 8);     // this lane's place inside a step of dS in memory (bf16 elements)
 
     for (int g = 0; g < a.G; ++g) {
         const int hq = hkv * a.G + g;
@@ -248,7 +280,7 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
         int ds_pos_max = 0;
         if (a.ds_store) {
             const int slot0 = min(max(ldc(a.ds_colbase + line), 0), (int)a.ds_blocks - 1);
-            ds_col = a.ds_store + ds_chunk(a, ds_rep(a, b, hq), slot0, key_tile, 0) * 4096 + ds_lane;
+            ds_col = a.ds_store + ds_chunk(a, ds_rep(a, b, hq), slot0, key_tile, 0) * 4096;
             ds_pos_max = (int)a.ds_blocks - 1 - slot0;
         }
         const i32x4 q_rsrc = make_rsrc(a.Q + b * a.q_sb + hq * a.q_sh, q_bytes);
@@ -310,17 +342,35 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                 static_for<0, kLoads>([&](auto piece_tag) { load_piece(slot_tag, piece_tag); });
             };
             // this lane's 16 row scalars of a step: rows 8 rg + 4 half + {0..3} of the wave's 32
+            auto read_row4 = [&](int slot, int which, int rg) {
+                return *(const __attribute__((address_space(3))) f32x4*)(uintptr_t)(
+                    row_lds + (uint32_t)((slot * 2 + which) * TQ + 8 * rg) * 4);
+            };
             auto read_rows = [&](int slot, int which, f32x4 (&out)[4]) {
 #pragma unroll
-                for (int rg = 0; rg < 4; ++rg)
-                    out[rg] = *(const __attribute__((address_space(3))) f32x4*)(uintptr_t)(
-                        row_lds + (uint32_t)((slot * 2 + which) * TQ + 8 * rg) * 4);
+                for (int rg = 0; rg < 4; ++rg) out[rg] = read_row4(slot, which, rg);
             };
 
             load_step(std::integral_constant<int, 0>{});
             if (part_of[0]) make_tags(0, q0_of[0]);
             wait_vmem();
             __syncthreads();
+
+            // this wave's dS of the step to memory, as it sits in the registers
+            auto store_ds = [&](u32x4 c0, u32x4 c1) {
+                const int u = u_step, pos = u >> sub_shift;
+                bf16* dst = ds_col + (int64_t)(min(pos, ds_pos_max) * (sub_k * sub) + (u - (pos << sub_shift))) * 4096;
+                // (written once, read once by another kernel much later: no reason to keep it in a cache)
+                __builtin_nontemporal_store(c0, (u32x4*)(dst + ds_lane));
+                __builtin_nontemporal_store(c1, (u32x4*)(dst + ds_lane + 512));
+            };
+            // the next step's tiles must have landed; the two dS stores, the youngest vector-memory
+            // operations of the step (the counter retires in issue order), may still be under way
+            auto end_step = [&]() {
+                if (a.ds_store) wait_vmem_but<2>();
+                else wait_vmem();
+                __syncthreads();
+            };
 
             // ---- one step; SLOT = v & 1 is compile-time so that every LDS access is "VGPR + immediate"
             auto step = [&](auto slot_tag) {
@@ -336,6 +386,11 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                 const bool partial = part_of[SLOT] && !mask.full(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb,
                                                                  kv0 + 32 * kb + 31);
 
+                bool hid = false;
+                if constexpr (kOwn) {
+                    // a block that the mask hides from all of its rows adds nothing (zeros in the stored dS)
+                    hid = part_of[SLOT] && mask.hidden(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb, kv0 + 32 * kb + 31);
+                }
                 // scores
                 f32x4 nd[4], rcv4[4];
                 read_rows(SLOT, 1, nd);
@@ -346,15 +401,16 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                     dpacc[r] = nd[r >> 2][r & 3];    // dP - delta comes out of the accumulation
                 }
                 {   // operand fragments are read PF MFMAs ahead of their use
-                    constexpr int NM = 2 * NKS, PF = 4;
+                    constexpr int NM = 2 * NKS, PF = kOwn ? 2 : 4;
                     auto frag = [&](int m) { return row_reader.read((m & 1) ? do_cur : q_cur, 0, m >> 1); };
-                    bf16x8 fr[NM];
+                    bf16x8 fr[NM], vr[NKS];
 #pragma unroll
                     for (int m = 0; m < PF; ++m) fr[m] = frag(m);
                     static_for<0, NM>([&](auto m_tag) {
                         constexpr int m = decltype(m_tag)::value;
                         if constexpr (m + PF < NM) fr[m + PF] = frag(m + PF);
-                        if (m & 1) dpacc = mfma32(fr[m], vf[m >> 1], dpacc);
+                        if constexpr (kOwn && !(m & 1)) vr[m >> 1] = row_reader.read(v_lds, 0, m >> 1);
+                        if (m & 1) dpacc = mfma32(fr[m], kOwn ? vr[m >> 1] : vf[kOwn ? 0 : m >> 1], dpacc);
                         else sacc = mfma32(fr[m], kf[m >> 1], sacc);
                         static_for<0, kLoads>([&](auto piece_tag) {
                             if constexpr (decltype(piece_tag)::value * NM / kLoads == m) load_piece(ld_slot, piece_tag);
@@ -362,7 +418,7 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                         __builtin_amdgcn_sched_barrier(0);
                     });
                 }
-                read_rows(SLOT, 0, rcv4);
+                if constexpr (!kOwn) read_rows(SLOT, 0, rcv4);
                 // relative bias: one value for the whole 32 x 32 block unless it lies near the diagonal
                 float rel_uni;
                 const bool rel_is_uni = smod.rel_uniform(q_off + q_first - (kv0 + 32 * kb + 31),
@@ -372,54 +428,75 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                     bits = mask.key_bits(kv_lane, q_off + q_first + 4 * half);
                     if constexpr (Mask::kDoc) Mask::match_documents(bits, s_tag[SLOT][32 * x + l32], k_tag, half);
                 }
-                u32x4 pk[2], dsk[2];
+                u32x4 pk[2] = {}, dsk[2] = {};
+                if (!hid) {
 #pragma unroll
-                for (int c4 = 0; c4 < 4; ++c4) {
-                    float sv[4], rcv[4], gr[4], pe[4], ds[4];
-                    // alibi / rel-bias need q - kv = dq0 + 8 (r >> 2) + (r & 3); the soft-cap and the plain score do not
-                    using RelPos = typename decltype(smod)::RelPos;
-                    constexpr bool kNeedsPos = Score::kAlibi || Score::kRel;
-                    const int dq0 = kNeedsPos ? q_off + q_first + 4 * half - kv_lane : 0;
-                    const float abase = smod.alibi_base(dq0);
-                    auto rel = [&](int r) __attribute__((always_inline)) {
-                        return kNeedsPos ? RelPos(dq0, abase, 8 * (r >> 2) + (r & 3)) : RelPos(0);
-                    };
-                    const RelPos dqk[4] = {rel(4 * c4), rel(4 * c4 + 1), rel(4 * c4 + 2), rel(4 * c4 + 3)};
+                    for (int c4 = 0; c4 < 4; ++c4) {
+                        float sv[4], rcv[4], gr[4], pe[4], ds[4];
+                        // alibi / rel-bias need q - kv = dq0 + 8 (r >> 2) + (r & 3); the soft-cap and the plain score do not
+                        using RelPos = typename decltype(smod)::RelPos;
+                        constexpr bool kNeedsPos = Score::kAlibi || Score::kRel;
+                        const int dq0 = kNeedsPos ? q_off + q_first + 4 * half - kv_lane : 0;
+                        const float abase = smod.alibi_base(dq0);
+                        auto rel = [&](int r) __attribute__((always_inline)) {
+                            return kNeedsPos ? RelPos(dq0, abase, 8 * (r >> 2) + (r & 3)) : RelPos(0);
+                        };
+                        if constexpr (kOwn) {           // (one quad of row constants at a time: there are no registers for four)
+                            rcv4[c4] = read_row4(SLOT, 0, c4);
+                        }
+                        const RelPos dqk[4] = {rel(4 * c4), rel(4 * c4 + 1), rel(4 * c4 + 2), rel(4 * c4 + 3)};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int r = 4 * c4 + i;
-                        sv[i] = sacc[r];
-                        rcv[i] = rcv4[r >> 2][r & 3];
-                    }
-                    if (rel_is_uni) smod.template p_with_grad4<true>(sv, dqk, rcv, gr, pe, rel_uni);
-                    else smod.template p_with_grad4<false>(sv, dqk, rcv, gr, pe);
-                    if (partial) {
-                        asm volatile("" ::: "memory");   // keep this a (scalar, rarely taken) branch
-                        // (a masked P makes dS vanish with it.  Rows past q_len hold zeros in Q and dO: whatever
-                        // the mask says there adds nothing)
-                        u32x4 tags = {};
-                        if constexpr (Mask::kCanvas) tags = *(const u32x4*)&s_tag[SLOT][32 * x + 8 * c4 + 4 * half];
+                        for (int i = 0; i < 4; ++i) {
+                            const int r = 4 * c4 + i;
+                            sv[i] = sacc[r];
+                            rcv[i] = rcv4[r >> 2][r & 3];
+                        }
+                        if (rel_is_uni) smod.template p_with_grad4<true>(sv, dqk, rcv, gr, pe, rel_uni);
+                        else smod.template p_with_grad4<false>(sv, dqk, rcv, gr, pe);
+                        if (partial) {
+                            asm volatile("" ::: "memory");   // keep this a (scalar, rarely taken) branch
+                            // (a masked P makes dS vanish with it.  Rows past q_len hold zeros in Q and dO: whatever
+                            // the mask says there adds nothing)
+                            u32x4 tags = {};
+                            if constexpr (Mask::kCanvas) tags = *(const u32x4*)&s_tag[SLOT][32 * x + 8 * c4 + 4 * half];
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i, mask.pixels_match(k_tag, tags[i])), pe[i]);
-                    }
+                            for (int i = 0; i < 4; ++i)
+                                pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i, mask.pixels_match(k_tag, tags[i])), pe[i]);
+                        }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];
+                        for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const int e = 2 * c4 + i;
-                        pk[e >> 2][e & 3] = pack_bf16(pe[2 * i], pe[2 * i + 1]);
-                        dsk[e >> 2][e & 3] = pack_bf16(ds[2 * i], ds[2 * i + 1]);
+                        for (int i = 0; i < 2; ++i) {
+                            const int e = 2 * c4 + i;
+                            pk[e >> 2][e & 3] = pack_bf16(pe[2 * i], pe[2 * i + 1]);
+                            dsk[e >> 2][e & 3] = pack_bf16(ds[2 * i], ds[2 * i + 1]);
+                        }
                     }
                 }
-                if (a.ds_store) {       // (wave-uniform) this wave's dS of the step, as it sits in the registers
-                    const int u = u_step, pos = u >> sub_shift;
-                    bf16* dst = ds_col + (int64_t)(min(pos, ds_pos_max) * (sub_k * sub) + (u - (pos << sub_shift))) * 4096;
-                    // (written once, read once by another kernel much later: no reason to keep it in a cache)
-                    __builtin_nontemporal_store(dsk[0], (u32x4*)dst);
-                    __builtin_nontemporal_store(dsk[1], (u32x4*)(dst + 512));
-                }
+                if (a.ds_store) store_ds(dsk[0], dsk[1]);       // (wave-uniform)
                 --u_step;
+                if constexpr (kOwn) {
+                    // outputs: dV^T += dO^T P and dK^T += Q^T dS over this wave's own 32 rows
+                    if (!hid) {
+                        constexpr int NM = 4 * NDB, PF = 2;       // MFMAs: [slice c][block db][dV, dK]
+                        auto frag = [&](int m) {
+                            return tr_own.read((m & 1) ? q_cur : do_cur, 16 * ((m >> 1) / NDB), (m >> 1) % NDB);
+                        };
+                        bf16x8 fr[NM];
+#pragma unroll
+                        for (int m = 0; m < PF; ++m) fr[m] = frag(m);
+#pragma unroll
+                        for (int m = 0; m < NM; ++m) {
+                            if (m + PF < NM) fr[m + PF] = frag(m + PF);
+                            const int c = (m >> 1) / NDB, db = (m >> 1) % NDB;
+                            if (m & 1) acc_k[db] = mfma32(fr[m], __builtin_bit_cast(bf16x8, dsk[c]), acc_k[db]);
+                            else acc[db] = mfma32(fr[m], __builtin_bit_cast(bf16x8, pk[c]), acc[db]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                    end_step();
+                    return;
+                }
                 // exchange: keep what this wave's output needs, hand over the other
                 u32x4 own[2];
 #pragma unroll
@@ -450,11 +527,7 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                 for (int c = 0; c < 2; ++c)
                     theirs[c] = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)(xchg_theirs + c * 1024);
                 out_half(tr_other, theirs);
-                // the next step's tiles must have landed; the two dS stores, the youngest vector-memory
-                // operations of the step (the counter retires in issue order), may still be under way
-                if (a.ds_store) wait_vmem_but<2>();
-                else wait_vmem();
-                __syncthreads();
+                end_step();
             };
 
             int v = 0;
@@ -466,6 +539,31 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
         }
     }
 
+    // ---- kOwn: the two waves of the same keys add up, the x = 0 wave dV^T, the x = 1 wave dK^T (the ring is
+    // free: the last step ended with a barrier)
+    if constexpr (kOwn) {
+        wait_vmem();        // (a column without a step has V's load still under way, and must not end before it)
+        f32x4* give = (f32x4*)smem + w * (NDB * 4 * 64) + lane;
+        const f32x4* take = (const f32x4*)smem + (w ^ 2) * (NDB * 4 * 64) + lane;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                f32x4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = x ? acc[db][4 * rg + i] : acc_k[db][4 * rg + i];
+                give[(db * 4 + rg) * 64] = v;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const f32x4 v = take[(db * 4 + rg) * 64];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[db][4 * rg + i] = (x ? acc_k[db][4 * rg + i] : acc[db][4 * rg + i]) + v[i];
+            }
+    }
     // ---- dV (x = 0) or dK (x = 1, with the scale and the score_mod's gradient factor), bf16
     {
         const float oscale = x ? a.scale * ScoreMod<SCORE>::grad_scale() : 1.0f;

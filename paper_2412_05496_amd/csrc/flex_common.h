@@ -303,6 +303,21 @@ struct PartialMask {
         if constexpr (T1 != 0) f = f || term_full<T1>(q_lo, q_hi, kv_lo, kv_hi);
         return f && kv_hi <= kv_last;
     }
+    // The opposite: every pair of the rectangle is masked (decided by index comparisons alone).
+    template <uint32_t TERM>
+    __device__ __forceinline__ bool term_hidden(int q_lo, int q_hi, int kv_lo, int kv_hi) const {
+        bool h = false;
+        if constexpr (TERM & FLEXATTN_M_CAUSAL) h = h || q_hi < kv_lo;
+        if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) h = h || q_lo - kv_hi > window;
+        if constexpr (TERM & FLEXATTN_M_PREFIX) h = h || kv_lo >= prefix_len;
+        if constexpr (TERM & FLEXATTN_M_CTX_LEN) h = h || kv_lo >= ctx;
+        return h;
+    }
+    __device__ __forceinline__ bool hidden(int q_lo, int q_hi, int kv_lo, int kv_hi) const {
+        bool h = term_hidden<T0>(q_lo, q_hi, kv_lo, kv_hi);
+        if constexpr (T1 != 0) h = h && term_hidden<T1>(q_lo, q_hi, kv_lo, kv_hi);
+        return h || kv_lo > kv_last;
+    }
 };
 
 // v where m is all-ones, 0 (or -inf) where it is 0

@@ -42,6 +42,36 @@ def test_scattered_documents(D, score, Bq, Bk, S, n_ids):
             hp.check_grad(name, got, r)
 
 
+@pytest.mark.parametrize("mask,score,S,Bq,Bk,Hkv", [
+    ("causal", "identity", 65, 128, 64, 2), ("causal", "softcap", 160, 64, 128, 1), ("none", "identity", 33, 128, 64, 2),
+    ("swa_causal", "identity", 330, 128, 128, 1), ("prefix_lm", "identity", 200, 128, 64, 2), ("causal", "alibi", 257, 64, 64, 1),
+    ("swa_causal_or_prefix", "rel_bias", 290, 128, 64, 1), ("causal", "alibi_softcap", 190, 128, 64, 2)])
+@pytest.mark.parametrize("extra_keys", [0, 100])
+def test_blocks_hidden_from_a_wave(mask, score, S, Bq, Bk, Hkv, extra_keys):
+    """D = 64 gradients where 32 x 32 blocks of PARTIAL steps are hidden as a whole (diagonals, window and
+    prefix edges, ragged ends), and with keys no query sees (columns of blocks without a step)."""
+    import paper_2412_05496_amd as fa
+    dev = torch.device(DEV)
+    wl = wlm.CFG1.scaled(name="hidden", B=1, Hq=2, Hkv=Hkv, S=S + extra_keys, D=64, Bq=Bq, Bk=Bk, mask=mask, score=score,
+                         window=40, prefix_len=70, softcap=20.0, rel_len=20, seed=4300 + S)
+    inp = wlm.make_train_inputs(wl, with_dO=True)
+    inp.Q, inp.dO = inp.Q[:, :, :S].contiguous(), inp.dO[:, :, :S].contiguous()
+    score_mod, mask_mod = hp.oracle_mods(wl, inp)
+    mask_id, score_id, params, _ = hp.library_mods(wl, inp, dev)
+    print(f"[case] hidden blocks {mask} {score} S={S}+{extra_keys}", flush=True)
+    bm = fa.alloc_blockmask(1, 1, S, S + extra_keys, Bq, Bk, device=dev)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    Q, K, V = (t.to(dev) for t in (inp.Q, inp.K, inp.V))
+    O, LSE = torch.full_like(Q, float("nan")), torch.full(Q.shape[:3], float("nan"), device=dev)
+    fa.flexattn_forward(Q, K, V, score_id, mask_id, params, bm, inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    ref = fo.flex_attention_backward(inp.Q, inp.K, inp.V, inp.dO, score_mod, mask_mod, inp.scale)
+    for stored in (False, True):
+        grads = hp.run_backward(wl, inp, dev, O, LSE, bm, (mask_id, score_id, params, Q, K, V), stored=stored)
+        for name, got, r in zip(("dQ", "dK", "dV"), grads, ref):
+            hp.check_grad(name, got, r)
+
+
 @pytest.mark.parametrize("w,h,k,layout,tile", [(200, 1, 1, "row_major", 0), (1, 130, 1, "row_major", 0),
                                                (15, 15, 15, "row_major", 0), (17, 9, 9, "row_major", 0),
                                                (24, 8, 7, "tiled", 4), (16, 16, 3, "morton", 0)])
