@@ -45,6 +45,35 @@ def test_captured_gradients_match_oracle(case):
         assert float(ref["rel_bias"].abs().max()) > 0
 
 
+@pytest.mark.parametrize("D,S,Bq,rel_len,score,over", [
+    (64, 65, 64, 1, "rel_bias", dict(window=10, prefix_len=3)),          # first entry == last entry
+    (64, 200, 128, 2, "rel_bias", dict(window=300, prefix_len=150)),     # whole prefix on the first entry
+    (128, 131, 128, 33, "rel_bias", dict(window=64, prefix_len=40)),
+    (64, 300, 128, 1024, "rel_bias", dict(window=200, prefix_len=10)),   # a table longer than the sequence
+    (128, 150, 64, 40, "rel_bias_softcap", dict(mask="doc_causal", doc_len_min=40, doc_len_max=70, softcap=20.0)),
+])
+def test_captured_diagonals(D, S, Bq, rel_len, score, over):
+    """Sums along the diagonals of 32 x 32 blocks: clamped ends, ragged rows, hidden elements."""
+    import paper_2412_05496_amd as fa
+    dev = torch.device("cuda:0")
+    wl = wlm.CFG4.scaled(name="diagonals", B=1, Hq=2, Hkv=1, S=S, D=D, Bq=Bq, rel_len=rel_len, score=score, seed=3700 + S, **over)
+    inp = wlm.make_train_inputs(wl, with_dO=True)
+    score_mod, mask_mod = hp.oracle_mods(wl, inp)
+    ref = fo.flex_attention_backward_captured(inp.Q, inp.K, inp.V, inp.dO, score_mod, mask_mod, inp.scale)
+    O, LSE, bm, (mask_id, score_id, params, Q, K, V) = hp.run_forward(wl, inp, dev)
+    d_rel = torch.full((wl.Hq, rel_len), float("nan"), device=dev)
+    fa.flexattn_backward_captured(Q, K, V, O, inp.dO.to(dev), LSE, score_id, mask_id, params, bm, inp.scale, None, d_rel)
+    torch.cuda.synchronize()
+    if rel_len == 1:
+        # every pair on one entry: the true sum is 0 (P (dP - delta) sums to 0 over a row), what is left is the
+        # rounding of O, and of P inside it, to bf16: errors of up to 2^-9 and of random sign on the terms of
+        # sum(dO * O), so eight times 2^-9 times their root sum of squares bounds it
+        bound = 8 * 2.0 ** -9 * (inp.dO.double() * O.double().cpu()).pow(2).sum(dim=(0, 2, 3)).sqrt()
+        assert (d_rel[:, 0].double().cpu().abs() <= bound).all(), (d_rel, bound)
+        return
+    hp.check_grad("d_rel_bias", d_rel, ref["rel_bias"], mean_tol=1e-2)
+
+
 def test_score_mods_without_captured_tensors_are_refused():
     import paper_2412_05496_amd as fa
     dev = torch.device("cuda:0")
