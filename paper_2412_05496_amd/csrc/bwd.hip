@@ -144,7 +144,8 @@ int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
         }
         if (stages & FLEXATTN_BWD_DQ) {
             const float qscale = scale * ((score_id & FLEXATTN_SCORE_SOFTCAP) ? 4.0f : 1.0f);   // ScoreMod::grad_scale()
-            launch_bwd_stored_dq(a, dims->D, qscale, st);
+            if (mask_uses(mask_id, FLEXATTN_M_NEIGHBORHOOD)) launch_bwd_stored_dq<true>(a, dims->D, qscale, st);
+            else launch_bwd_stored_dq<false>(a, dims->D, qscale, st);
         }
     } else {
         rc = kBwdLaunchers[vi](a, dims->D, stages, st);     // the delta pre-pass depends on the score_mod too

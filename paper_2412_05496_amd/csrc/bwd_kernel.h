@@ -146,23 +146,40 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const BwdArgs a) {
 // few registers at three waves per SIMD (6 to 24 spills: 431 -> 447 us with ALiBi, 350 -> 370 with documents
 // and a relative bias; canvas 684 -> 763) and keep the exchange, as does D = 128, whose two accumulators
 // are 128 registers.
+// Neighborhood masks: bit kb + 2 x set if the mask hides the block of the 32 query rows q0 + 32 x .. and the 32
+// keys kv0 + 32 kb .. .  The dQ kernel that reads dS back takes the same answer for the same block
+// (CanvasBlocks::hidden_bits), so the dS of such a block is neither written nor read.
+__device__ __forceinline__ int canvas_step_bits(const flexattn_mod_params& p, int q0, int kv0) {
+    const CanvasBlocks cb(p);
+    const CanvasBlocks::Box qw[2] = {cb.windows(q0), cb.windows(q0 + 32)};
+    const uint32_t b = cb.hidden_bits(qw, kv0);     // bit 2 x + kb
+    return (int)b;
+}
+
+//
+// kCut, neighborhood masks at D = 128: the walk leaves out the steps that are hidden from all four waves, and a
+// wave the vector work and the outputs of its hidden blocks (128 x 128 pixels, tiles of 8 x 8, K = 13, 64 heads:
+// 1047 -> 907 us; 100 x 90 row-major, K = 9: 802 -> 771).  At D = 64 a workgroup is over too soon to pay for
+// finding them (735 -> 725, 446 -> 481).
 template <int D, uint32_t MASK, uint32_t SCORE>
 constexpr bool dkdv_own_rows() {
     constexpr bool biased_cap = (SCORE & FLEXATTN_SCORE_SOFTCAP) && (SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS));
     return D == 64 && !PartialMask<MASK>::kCanvas && !biased_cap;
 }
 template <int D, uint32_t MASK, uint32_t SCORE>
-__global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv_kernel(const BwdArgs a) {
+__global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(const BwdArgs a) {
     constexpr int TQ = 64;                         // query rows per step
     constexpr int TILE = TQ * D;                   // elements per LDS tile
     constexpr int NKS = D / 16, NDB = D / 32;
     constexpr bool kOwn = dkdv_own_rows<D, MASK, SCORE>();
+    constexpr bool kCut = D == 128 && PartialMask<MASK>::kCanvas;     // leaves hidden steps and blocks out
     using Loader = WaveTileLoader<D, 4>;
     __shared__ __attribute__((aligned(1024))) bf16 smem[(kOwn ? 5 : 4) * TILE];   // 2 x (Q tile, dO tile); kOwn: V tile
     __shared__ __attribute__((aligned(1024))) u32x4 s_xchg[kOwn ? 1 : 4][2][64];   // [wave][16-row slice][lane]
     __shared__ __attribute__((aligned(256))) float s_row[2][2][TQ];           // [slot][rc | -delta][row]
     constexpr int kListMax = 512;
     __shared__ int s_steps[kListMax + 2];          // the walk of the current head, see below
+    __shared__ int s_pos[kCut ? kListMax + 2 : 1], s_count;
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];   // relative-bias row of the current head
     using Mask = PartialMask<MASK>;
@@ -298,10 +315,36 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
         // that run side by side on an XCD ask its L2 for the same Q / dO tiles at about the same
         // time.  The walk is laid out in LDS first, kListMax steps at a time -- one entry per step:
         // first query row | 1 if the block is PARTIAL -- so that the main loop finds the next row
-        // offset with one LDS read issued a step ahead.
+        // offset with one LDS read issued a step ahead.  (kCut: bit 1 + w says that the mask
+        // hides wave w's block, see canvas_step_bits, and s_pos holds the step's position in the column's walk.)
         for (int seg0 = 0; seg0 < H_all; seg0 += kListMax) {
-            const int H = min(kListMax, H_all - seg0);
-            for (int i = tid; i < H; i += 256) {
+            int H = min(kListMax, H_all - seg0);
+            if constexpr (kCut) {
+                // one wave lays the walk out and leaves out the steps that are hidden from all four waves (but
+                // for the very first: no segment is empty)
+                if (w == 0) {
+                    int n = 0;
+                    for (int i0 = 0; i0 < H; i0 += 64) {
+                        const int i = i0 + lane, u = max(H_all - 1 - (seg0 + i), 0), pos = u / sub, sidx = u - pos * sub;
+                        const int blk = pos < n_full ? full_idx[pos] : part_idx[pos - n_full];
+                        const int q0 = blk * a.Bq + sidx * TQ;
+                        const int bits = pos < n_full ? 0 : canvas_step_bits(a.p, q0, kv0);
+                        const bool keep = i < H && (bits != 15 || i == 0);
+                        const uint64_t kept = __ballot(keep);
+                        if (keep) {
+                            const int at = n + __popcll(kept & ((1ull << lane) - 1));
+                            s_steps[at] = q0 | (pos >= n_full ? 1 : 0) | (bits << 1);
+                            s_pos[at] = u;
+                            if (kept >> lane == 1ull) s_steps[at + 1] = s_steps[at];     // (see below; the next 64 overwrite it)
+                        }
+                        n += __popcll(kept);
+                    }
+                    if (lane == 0) s_count = n;
+                }
+                __syncthreads();
+                H = __builtin_amdgcn_readfirstlane(s_count);
+            }
+            for (int i = kCut ? H : tid; i < H; i += 256) {
                 const int u = H_all - 1 - (seg0 + i), pos = u / sub, sidx = u - pos * sub;
                 const int blk = pos < n_full ? full_idx[pos] : part_idx[pos - n_full];
                 s_steps[i] = (blk * a.Bq + sidx * TQ) | (pos >= n_full ? 1 : 0);
@@ -315,15 +358,23 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
             int e_next = s_steps[0];
             int q0_of[2];                           // first query row of the step in each ring slot,
             bool part_of[2];                        // and whether its block is PARTIAL
+            // (kCut) whether the mask hides this wave's 32 x 32 block, and that of the other wave of its keys
+            bool hid_of[2] = {false, false}, hid_other_of[2] = {false, false};
+            int u_of[2] = {0, 0};                   // (kCut) the step's position in the column's walk
 
             int ld_q0 = 0;                          // first row of the step being loaded
             constexpr int kLoads = 2 * Loader::NI + 1;      // load instructions per wave and step
             auto load_begin = [&](auto slot_tag) {
                 constexpr int SLOT = decltype(slot_tag)::value;
                 const int e = __builtin_amdgcn_readfirstlane(e_next);
-                ld_q0 = e & ~1;
+                ld_q0 = e & ~63;
                 q0_of[SLOT] = ld_q0;
                 part_of[SLOT] = e & 1;
+                if constexpr (kCut) {
+                    hid_of[SLOT] = (e >> (1 + w)) & 1;
+                    hid_other_of[SLOT] = (e >> (1 + (w ^ 2))) & 1;
+                    u_of[SLOT] = s_pos[ld_v];
+                }
                 e_next = s_steps[++ld_v];
             };
             // piece P of the loads of a step: NI for the Q tile, NI for the dO tile, one row of scalars
@@ -357,8 +408,8 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
             __syncthreads();
 
             // this wave's dS of the step to memory, as it sits in the registers
-            auto store_ds = [&](u32x4 c0, u32x4 c1) {
-                const int u = u_step, pos = u >> sub_shift;
+            auto store_ds = [&](int u_at, u32x4 c0, u32x4 c1) {
+                const int u = kCut ? __builtin_amdgcn_readfirstlane(u_at) : u_step, pos = u >> sub_shift;
                 bf16* dst = ds_col + (int64_t)(min(pos, ds_pos_max) * (sub_k * sub) + (u - (pos << sub_shift))) * 4096;
                 // (written once, read once by another kernel much later: no reason to keep it in a cache)
                 __builtin_nontemporal_store(c0, (u32x4*)(dst + ds_lane));
@@ -366,8 +417,8 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
             };
             // the next step's tiles must have landed; the two dS stores, the youngest vector-memory
             // operations of the step (the counter retires in issue order), may still be under way
-            auto end_step = [&]() {
-                if (a.ds_store) wait_vmem_but<2>();
+            auto end_step = [&](bool stored) {
+                if (stored) wait_vmem_but<2>();
                 else wait_vmem();
                 __syncthreads();
             };
@@ -386,11 +437,10 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                 const bool partial = part_of[SLOT] && !mask.full(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb,
                                                                  kv0 + 32 * kb + 31);
 
+                // a block that the mask hides from all of its rows adds nothing (zeros in the stored dS)
                 bool hid = false;
-                if constexpr (kOwn) {
-                    // a block that the mask hides from all of its rows adds nothing (zeros in the stored dS)
-                    hid = part_of[SLOT] && mask.hidden(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb, kv0 + 32 * kb + 31);
-                }
+                if constexpr (kCut) hid = hid_of[SLOT];
+                else if constexpr (kOwn) hid = part_of[SLOT] && mask.hidden(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb, kv0 + 32 * kb + 31);
                 // scores
                 f32x4 nd[4], rcv4[4];
                 read_rows(SLOT, 1, nd);
@@ -473,7 +523,9 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                         }
                     }
                 }
-                if (a.ds_store) store_ds(dsk[0], dsk[1]);       // (wave-uniform)
+                // (wave-uniform; the blocks a canvas hides are not read back, see CANVAS in bwd_stored.h)
+                const bool stored = a.ds_store && !(kCut && hid);
+                if (stored) store_ds(u_of[SLOT], dsk[0], dsk[1]);
                 --u_step;
                 if constexpr (kOwn) {
                     // outputs: dV^T += dO^T P and dK^T += Q^T dS over this wave's own 32 rows
@@ -494,7 +546,7 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                             __builtin_amdgcn_sched_barrier(0);
                         }
                     }
-                    end_step();
+                    end_step(stored);
                     return;
                 }
                 // exchange: keep what this wave's output needs, hand over the other
@@ -521,13 +573,15 @@ __global__ __launch_bounds__(256, (bwd_waves_per_simd<D, MASK>())) void bwd_dkdv
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 };
-                out_half(tr_own, own);
+                if (!hid) out_half(tr_own, own);
                 __syncthreads();
+                if (!hid_other_of[SLOT]) {
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
-                    theirs[c] = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)(xchg_theirs + c * 1024);
-                out_half(tr_other, theirs);
-                end_step();
+                    for (int c = 0; c < 2; ++c)
+                        theirs[c] = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)(xchg_theirs + c * 1024);
+                    out_half(tr_other, theirs);
+                }
+                end_step(stored);
             };
 
             int v = 0;
@@ -615,8 +669,16 @@ __device__ __forceinline__ float diagonal_sums(const f32x16& v, int half) {
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
+//
+// Hidden blocks are left out where the loads of the next tile need not be spread over the MFMAs of this one:
+// four waves at D = 64 (window of 1024, S = 5000: 130 -> 124 us; canvas 100 x 90, K = 9, row-major: 349 -> 290),
+// not with two (tiles of 8 x 8, K = 13: 348 -> 374) nor at D = 128.
+template <int D, int NW>
+constexpr bool dq_skips_hidden() {
+    return D == 64 && NW == 4;
+}
 template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool CAPTURED = false>
-__global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_dq_kernel(const BwdArgs a) {
+__global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kernel(const BwdArgs a) {
     constexpr int Bq = NW * 32;
     constexpr int TILE = 64 * D;
     __shared__ __attribute__((aligned(1024))) bf16 smem[4 * TILE];   // K(even), K(odd), V(even), V(odd)
@@ -625,6 +687,7 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
     __shared__ float s_rel[ScoreMod<SCORE>::kRel ? kRelTableMax : 1]; // relative-bias row of the head (values)
     using Mask = PartialMask<MASK>;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? 64 : 4];   // tags of a PARTIAL tile's keys (even, odd)
+    __shared__ uint8_t s_hidden[Mask::kCanvas && dq_skips_hidden<D, NW>() ? kHiddenTiles : 1];           // CanvasBlocks::hidden_bits of the first tiles
 
     const int units = a.B * a.Hkv;
     const int id = blockIdx.x, xcd = id & 7, kk = id >> 3;
@@ -720,6 +783,13 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
 #pragma unroll
         for (int r = 0; r < 16; ++r) dq[db][r] = 0.0f;
 
+    // a wave leaves out the blocks of 32 keys that the mask hides from all of its rows
+    constexpr bool kSkip = dq_skips_hidden<D, NW>();
+    if constexpr (kSkip && Mask::kCanvas) fill_hidden_tiles<NW>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, sub, a.Bk, row * Bq, tid);
+    auto hidden_block = [&](int t, bool partial, int kv, int kvb) __attribute__((always_inline)) {
+        if constexpr (Mask::kCanvas) return t < kHiddenTiles && ((__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (2 * w + kvb)) & 1);
+        else return partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31);
+    };
     bool part_next = false;
     int kv0 = walk.next(part_next);
     load_tiles(0, kv0);
@@ -744,8 +814,14 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
         using L = WaveTileLoader<D, NW>;
         constexpr int NKS = D / 16, NDB = D / 32, PF = 4;
 
+        if constexpr (kSkip) {
+            if (ld) load_tiles(BUF ^ 1, kv0);
+        }
         static_for<0, 2>([&](auto kvb_tag) {
             constexpr int kvb = decltype(kvb_tag)::value;
+            if constexpr (kSkip) {
+                if (hidden_block(t, partial, kv0_cur + 32 * kvb, kvb)) return;
+            }
             // S^T = K Q^T and dP^T = V dO^T for 32 keys; operand fragments read PF MFMAs ahead
             f32x16 sacc, dpacc;
 #pragma unroll
@@ -764,7 +840,7 @@ __global__ __launch_bounds__(NW * 64, (bwd_waves_per_simd<D, MASK>())) void bwd_
                     if constexpr (m + PF < NM) fr[m + PF] = frag(m + PF);
                     if (m & 1) dpacc = mfma32(fr[m], dof[m >> 1], dpacc);
                     else sacc = mfma32(fr[m], qf[m >> 1], sacc);
-                    if constexpr (kvb == 0) {
+                    if constexpr (kvb == 0 && !kSkip) {
                         static_for<0, NP>([&](auto p_tag) {
                             constexpr int p = decltype(p_tag)::value;
                             if constexpr (p * NM / NP == m) {

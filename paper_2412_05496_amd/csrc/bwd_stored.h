@@ -94,7 +94,12 @@ struct SliceTrReader {
 // issues K(t+1) and then dS(t+2); the vector-memory counter retires in issue order, so
 // "all but the last four" at the top of a tile means K(t) and dS(t) have landed while dS(t+1) is
 // still under way: the HBM read of dS runs two tiles ahead of its use, the L2 read of K one.
-template <int D, int NW>
+//
+// CANVAS (neighborhood masks): the blocks of 32 keys that the mask hides from a wave's 32 rows are neither
+// loaded (an empty descriptor fills the slice with zeros) nor multiplied; the dK/dV kernel may not have written
+// them.  (8 x 8 tiles, K = 13, D = 64, 64 heads of 128 x 128 pixels: 336 -> 330 us, Morton order, K = 21: 710 ->
+// 559, where K tiles weigh less against dS.)
+template <int D, int NW, bool CANVAS>
 __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs a, const float qscale) {
     constexpr int Bq = NW * 32;
     constexpr int TILE_K = 64 * D, TILE_S = 64 * Bq, SLICE = 64 * 32;   // bf16 elements
@@ -102,6 +107,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
     __shared__ __attribute__((aligned(1024))) bf16 smem[2 * TILE_K + NW * 2 * SLICE];   // K(even), K(odd); per wave dS(even), dS(odd)
     __shared__ int s_kv0[kList + 2];                                 // first key of a tile, -1: nothing to add
     __shared__ int s_chunk[kList + 2];                               // where its dS starts (ds_chunk without the rep)
+    __shared__ uint8_t s_hid[CANVAS ? kList + 2 : 1];                // CanvasBlocks::hidden_bits of the tile
 
     const int units = a.B * a.Hkv;
     const int id = blockIdx.x, xcd = id & 7, kk = id >> 3;
@@ -168,6 +174,13 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
             const int slot = (int)min(max((int64_t)grid_row[c], (int64_t)0), a.ds_blocks - 1);
             s_kv0[i] = kv0 < a.kv_len ? kv0 : -1;      // the dK/dV kernel has no workgroup for keys past kv_len
             s_chunk[i] = slot * sub_k + st;
+            if constexpr (CANVAS) {
+                const CanvasBlocks cb(a.p);
+                CanvasBlocks::Box qw[NW];
+#pragma unroll
+                for (int v = 0; v < NW; ++v) qw[v] = cb.windows(row * Bq + 32 * v);
+                s_hid[i] = pos < n_full ? 0 : (uint8_t)cb.hidden_bits(qw, kv0);
+            }
         }
         __syncthreads();
 
@@ -176,14 +189,22 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
             const int kv0 = max(__builtin_amdgcn_readfirstlane(s_kv0[i]), 0);
             k_loader.start(k_rsrc, k_lds + BUF * (TILE_K * 2), kv0 * k_row_bytes);
         };
+        auto hidden_of = [&](int i) -> uint32_t {
+            if constexpr (!CANVAS) return 0u;
+            else return ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_hid[i]) >> (2 * w)) & 3u;
+        };
         // a tile with nothing to add is loaded through an empty descriptor, which fills the slice with zeros
         auto load_s = [&](int i, auto buf_tag) {
             constexpr int BUF = decltype(buf_tag)::value;
             const int kv0 = __builtin_amdgcn_readfirstlane(s_kv0[i]);
             const int chunk = __builtin_amdgcn_readfirstlane(s_chunk[i]);
-            const i32x4 rsrc = make_rsrc(ds_head + (int64_t)chunk * TILE_S, kv0 >= 0 ? (uint32_t)SLICE * 2u : 0u);
+            const uint32_t hid = hidden_of(i);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) dma_x1_nt(rsrc, s_lds + BUF * (SLICE * 2) + i * 1024, s_voff[i], 0);
+            for (int j = 0; j < 4; ++j) {       // (j >> 1: which 32 keys)
+                const bool there = kv0 >= 0 && !(hid & (1u << (j >> 1)));
+                const i32x4 rsrc = make_rsrc(ds_head + (int64_t)chunk * TILE_S, there ? (uint32_t)SLICE * 2u : 0u);
+                dma_x1_nt(rsrc, s_lds + BUF * (SLICE * 2) + j * 1024, s_voff[j], 0);
+            }
         };
         const std::integral_constant<int, 0> b0;
         const std::integral_constant<int, 1> b1;
@@ -204,9 +225,21 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
             for (int ks = 0; ks < 4; ++ks) bfr[ks] = tr_s.read(stl, 16 * ks);
             // (the slot is refilled below: the reads above must have left LDS first)
             asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bfr[0]), "+v"(bfr[1]), "+v"(bfr[2]), "+v"(bfr[3]) :: "memory");
+            const uint32_t hid = hidden_of(t);
             if (t + 1 < T) load_k(t + 1, nxt);
             if (t + 2 < T) load_s(t + 2, buf_tag);
             constexpr int NDB = D / 32, NM = 4 * NDB, PF = 4;       // [16-key slice][block db]
+            if constexpr (CANVAS) {
+                static_for<0, 2>([&](auto j_tag) {
+                    constexpr int j = decltype(j_tag)::value;
+                    if (!(hid & (1u << j))) {
+#pragma unroll
+                        for (int m = j * NM / 2; m < (j + 1) * NM / 2; ++m)
+                            dq[m % NDB] = mfma32(tr_k.read(kt, 16 * (m / NDB), m % NDB), bfr[m / NDB], dq[m % NDB]);
+                    }
+                });
+                return;
+            }
             auto frag = [&](int m) { return tr_k.read(kt, 16 * (m / NDB), m % NDB); };
             bf16x8 fr[NM];
 #pragma unroll
@@ -239,13 +272,14 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
         }
 }
 
-inline int launch_bwd_stored_dq(const BwdArgs& a, int D, float qscale, hipStream_t st) {
+template <bool CANVAS>
+int launch_bwd_stored_dq(const BwdArgs& a, int D, float qscale, hipStream_t st) {
     const int units = a.B * a.Hkv;
     const unsigned grid_q = (unsigned)(((units + 7) / 8) * 8 * a.G * a.NR);
-    if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 4>), dim3(grid_q), dim3(256), 0, st, a, qscale);
-    else if (D == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 2>), dim3(grid_q), dim3(128), 0, st, a, qscale);
-    else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<64, 4>), dim3(grid_q), dim3(256), 0, st, a, qscale);
-    else hipLaunchKernelGGL((bwd_dq_stored_kernel<64, 2>), dim3(grid_q), dim3(128), 0, st, a, qscale);
+    if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 4, CANVAS>), dim3(grid_q), dim3(256), 0, st, a, qscale);
+    else if (D == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 2, CANVAS>), dim3(grid_q), dim3(128), 0, st, a, qscale);
+    else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<64, 4, CANVAS>), dim3(grid_q), dim3(256), 0, st, a, qscale);
+    else hipLaunchKernelGGL((bwd_dq_stored_kernel<64, 2, CANVAS>), dim3(grid_q), dim3(128), 0, st, a, qscale);
     return FLEXATTN_OK;
 }
 

@@ -120,6 +120,74 @@ struct CanvasOrder {
     }
 };
 
+// Which 32 x 32 blocks of a neighborhood mask hide every pair, found from boxes around the pixels of 32
+// consecutive tokens.  Of the tiles a BlockMask of 128 x 64 blocks lists, a wave's 32 queries meet only some:
+// 15 of 24 32-key blocks with 8 x 8 tiles and K = 13.
+struct CanvasBlocks {
+    CanvasOrder order;
+    int t, tiles_x, w, h, r;    // tiles of 2^t x 2^t pixels (row-major: of one pixel), tiles_x side by side
+    float inv_tiles_x;
+    bool morton, known;         // known: the queries are the pixels (no offsets)
+    struct Box {
+        int x0, x1, y0, y1;
+    };
+    __device__ __forceinline__ explicit CanvasBlocks(const flexattn_mod_params& p) : order(p) {
+        t = p.na_layout == FLEXATTN_NA_TILED ? order.tile_log2 : 0;
+        w = p.na_width;
+        h = p.na_height;
+        tiles_x = w >> t;
+        inv_tiles_x = fast_rcp((float)tiles_x);
+        r = p.na_kernel >> 1;
+        morton = p.na_layout == FLEXATTN_NA_MORTON;
+        known = p.q_offsets == nullptr;
+    }
+    // around the pixels of the tokens n .. n + 31, n a multiple of 32
+    __device__ __forceinline__ Box tokens(int n) const {
+        if (morton) {               // 8 x 4 pixels
+            const int x = CanvasOrder::even_bits((uint32_t)n), y = CanvasOrder::even_bits((uint32_t)n >> 1);
+            return {x, x + 7, y, y + 3};
+        }
+        int tx, ty;
+        CanvasOrder::divmod(n >> (2 * t), tiles_x, inv_tiles_x, ty, tx);
+        if (2 * t >= 5) {           // inside one tile: whole lines of it, or a part of one
+            const int in = n & ((1 << (2 * t)) - 1), lines = t >= 5 ? 1 : 32 >> t, len = t >= 5 ? 32 : 1 << t;
+            const int x = (tx << t) + (in & ((1 << t) - 1)), y = (ty << t) + (in >> t);
+            return {x, x + len - 1, y, y + lines - 1};
+        }
+        // tiles side by side, which may go on at the start of the next line of tiles
+        const int end = tx + (32 >> (2 * t)) - 1;
+        if (end < tiles_x) return {tx << t, (end << t) + (1 << t) - 1, ty << t, (ty << t) + (1 << t) - 1};
+        int lines, rest;
+        CanvasOrder::divmod(end, tiles_x, inv_tiles_x, lines, rest);
+        return {0, w - 1, ty << t, ((ty + lines) << t) + (1 << t) - 1};
+    }
+    // around the windows of the queries n .. n + 31
+    __device__ __forceinline__ Box windows(int n) const {
+        Box b = tokens(n);
+        b.x0 = min(max(b.x0, r), w - 1 - r) - r;
+        b.x1 = min(max(b.x1, r), w - 1 - r) + r;
+        b.y0 = min(max(b.y0, r), h - 1 - r) - r;
+        b.y1 = min(max(b.y1, r), h - 1 - r) + r;
+        return b;
+    }
+    __device__ __forceinline__ bool hidden(const Box& query_windows, const Box& keys) const {
+        return known && (keys.x1 < query_windows.x0 || keys.x0 > query_windows.x1 || keys.y1 < query_windows.y0 ||
+                         keys.y0 > query_windows.y1);
+    }
+    // bit 2 w + j: the 32 keys from kv0 + 32 j on are hidden from the 32 queries from q0 + 32 w on
+    template <int NW>
+    __device__ __forceinline__ uint32_t hidden_bits(const Box (&query_windows)[NW], int kv0) const {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const Box keys = tokens(kv0 + 32 * j);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) bits |= hidden(query_windows[w], keys) ? 1u << (2 * w + j) : 0u;
+        }
+        return bits;
+    }
+};
+
 struct NoCanvas {
     __device__ __forceinline__ explicit NoCanvas(const flexattn_mod_params&) {}
     __device__ __forceinline__ void pixel(int, int&, int&) const {}
@@ -525,21 +593,11 @@ struct ScoreMod {
     }
 };
 
-// Waves per SIMD the MFMA kernels are compiled for.  At D = 64 the lean variants fit 168 registers,
-// so three workgroups share a CU (more latency hiding, more chances for one wave's MFMAs to run
-// beside another's VALU work); the variants that carry a relative-bias table or the canvas decode
-// would spill there and stay at two, as does everything at D = 128.
-template <int D, uint32_t MASK, uint32_t SCORE>
-constexpr int waves_per_simd() {
-    constexpr uint32_t prims = (MASK | (MASK >> 8)) & 0xffu;
-    constexpr bool lean = !(prims & FLEXATTN_M_NEIGHBORHOOD) && !(SCORE & FLEXATTN_SCORE_REL_BIAS);
-    return (D == 64 && lean) ? 3 : 2;
-}
-
-// The backward kernels need fewer registers: at D = 64 only the canvas decode does not fit three waves.
-template <int D, uint32_t MASK>
+// Waves per SIMD the backward kernels are compiled for: at D = 64 they fit 168 registers, so three workgroups
+// share a CU (more latency hiding, more chances for one wave's MFMAs to run beside another's VALU work).
+template <int D>
 constexpr int bwd_waves_per_simd() {
-    return (D == 64 && !(((MASK | (MASK >> 8)) & 0xffu) & FLEXATTN_M_NEIGHBORHOOD)) ? 3 : 2;
+    return D == 64 ? 3 : 2;
 }
 
 // ---------------------------------------------------------------------------------------

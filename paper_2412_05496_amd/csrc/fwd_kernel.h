@@ -51,6 +51,28 @@ struct FwdArgs {
 
 constexpr int kTileKV = 64;   // keys per kernel tile
 
+// Which form of the tile loop.  The pipelined one keeps the scores of two tiles, which at D = 64 allows three
+// waves per SIMD; the plain one needs 112 to 128 registers: four waves, whose turns hide more than the pipeline
+// does, and hidden blocks of PARTIAL tiles cost nothing.  us, pipelined -> plain (one MI355X, Bq = 128, D = 64):
+// causal, S = 1024, 64 x 16 heads: 277 -> 250; window of 1024, S = 5000: 114 -> 105; relative bias, S = 8192,
+// 64 heads: 158 -> 127; no mask, S = 2048: 89.5 -> 86.5; packed documents with ALiBi: 218 -> 216.
+// The pipelined one stays where it is the better one: a bounded soft-cap, whose softmax needs no running
+// maximum (287 -> 299), and Bq = 64, where LDS admits 2.5 waves per SIMD either way (a single small call: 7.7
+// -> 8.4), and D = 128, two waves per SIMD either way.  Neighborhood masks take the plain one at any size:
+// 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (480 -> 355 at 128 x 128 pixels).
+template <int D, int NW, uint32_t MASK, bool BOUNDED>
+constexpr bool fwd_plain() {
+    return NW == 4 && (PartialMask<MASK>::kCanvas || (D == 64 && !BOUNDED));
+}
+// Waves per SIMD to compile for: what registers (512 per SIMD lane) and LDS admit.  The pipelined variants
+// with a relative-bias table would spill at three.
+template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED>
+constexpr int fwd_waves_per_simd() {
+    if (D != 64) return 2;
+    if (fwd_plain<D, NW, MASK, BOUNDED>()) return NW == 4 ? 4 : 2;
+    return (SCORE & FLEXATTN_SCORE_REL_BIAS) ? 2 : 3;
+}
+
 // BOUNDED: the score_mod ends in a soft-cap small enough that the cap itself serves as the fixed
 // softmax maximum (see ScoreMod::bounded); chosen by the host from the cap value.
 // PAGED: the tiles of K and V are fetched from a paged pool through the converted block lists;
@@ -59,7 +81,7 @@ constexpr int kTileKV = 64;   // keys per kernel tile
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
 template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED = false>
-__global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void fwd_kernel(const FwdArgs a) {
+__global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BOUNDED>())) void fwd_kernel(const FwdArgs a) {
     constexpr int Bq = NW * 32;
     constexpr int TILE = kTileKV * D;              // elements per LDS tile
 
@@ -70,6 +92,7 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys (even, odd)
 
     __shared__ uint32_t s_qtag[Mask::kTags ? NW * 64 : 1];            // each lane's own tag (its query's)
+    __shared__ uint8_t s_hidden[Mask::kCanvas && NW == 4 ? kHiddenTiles : 1];    // CanvasBlocks::hidden_bits of the first tiles
 
     // ---- workgroup -> (b, hkv, g, row of blocks).  Consecutive workgroup ids go to the 8 XCDs in
     // turn; all rows and all G query heads of one (b, hkv) are sent to the same XCD so that its K/V
@@ -158,6 +181,12 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
         if constexpr (Mask::kCanvas) {
             if (w == (turn & (NW - 1))) s_tag[buf][lane] = mask.key_pixel(min(kv0 + lane, a.kv_len - 1));
         }
+    };
+    if constexpr (Mask::kCanvas && NW == 4) fill_hidden_tiles<NW>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, a.sub, a.Bk, row * Bq, tid);
+    // 32-key blocks of tile t that are hidden from this wave (bit 0, bit 1); visible after the prologue's barrier
+    auto hidden_of = [&](int t) __attribute__((always_inline)) -> uint32_t {
+        if constexpr (!(Mask::kCanvas && NW == 4)) return 0u;
+        else return t < min(T, kHiddenTiles) ? ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (2 * w)) & 3u : 0u;
     };
     const float inv_neg2c = smod.capl2 > 0.0f ? -0.5f / smod.capl2 : 0.0f;   // 1 / (-2 cap log2 e)
 
@@ -332,80 +361,123 @@ __global__ __launch_bounds__(NW * 64, (waves_per_simd<D, MASK, SCORE>())) void f
     load_k(0, kv_t, pg_t, pr_t);
     load_v(0, kv_t, pg_t, pr_t);
     if (part_t) make_tags(0, kv_t, 0);
-    if (T > 1) {
-        kv_t1 = walk.next(part_t1, pg_t1, pr_t1);
-        load_k(1, kv_t1, pg_t1, pr_t1);
-    }
-    wait_vmem();
-    __syncthreads();
-    f32x16 s_cur[2], s_next[2];
-    qk(std::integral_constant<int, 0>{}, s_cur, [](auto) {});
-
-    // One tile (t & 1 == BUF).  S^T of tile t+1 (MFMA) is issued next to the softmax of tile t (VALU),
-    // P V of the first 32 keys next to the softmax of the second 32.
-    auto tile_step = [&](int t, auto buf_tag, auto has_next_tag) {
-        constexpr int BUF = decltype(buf_tag)::value;
-        constexpr bool HAS_NEXT = decltype(has_next_tag)::value;
-        // Everything this wave asked for has landed; after the barrier so has everyone else's, and
-        // nobody still reads K(t) [buffer BUF] or V(t-1) [buffer BUF ^ 1], which are refilled next.
+    if constexpr (fwd_plain<D, NW, MASK, BOUNDED>()) {
+        // One block of 32 keys after the other, K and V one tile ahead.  A wave leaves out the blocks that
+        // the mask hides from all of its rows.
+        auto hidden_block = [&](uint32_t bits, bool partial, int kv, int kvb) __attribute__((always_inline)) {
+            if constexpr (Mask::kCanvas) return (bits & (1u << kvb)) != 0;
+            else return partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31);
+        };
+        auto plain_step = [&](int t, auto buf_tag) {
+            constexpr int BUF = decltype(buf_tag)::value;
+            wait_vmem();
+            __syncthreads();        // tile t has landed, and nobody still reads tile t - 1
+            const uint32_t hid = hidden_of(t);
+            const int kv0 = kv_t;
+            const bool partial = part_t;
+            if (t + 1 < T) {
+                kv_t = walk.next(part_t, pg_t, pr_t);
+                load_k(BUF ^ 1, kv_t, pg_t, pr_t);
+                load_v(BUF ^ 1, kv_t, pg_t, pr_t);
+                if (part_t) make_tags(BUF ^ 1, kv_t, t + 1);
+            }
+            static_for<0, 2>([&](auto kvb_tag) {
+                constexpr int kvb = decltype(kvb_tag)::value;
+                if (!hidden_block(hid, partial, kv0 + 32 * kvb, kvb)) {
+                    f32x16 s;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+#pragma unroll
+                    for (int ks = 0; ks < D / 16; ++ks)
+                        s = mfma32(k_reader.read(smem_bytes + BUF * (TILE * 2), kvb * 32, ks), qf[ks], s);
+                    bf16x8 pf[2];
+                    softmax(s, kv0 + 32 * kvb, partial, BUF, kvb, pf);
+                    pv(buf_tag, kvb, pf);
+                }
+            });
+        };
+        int t = 0;
+        for (; t + 1 < T; t += 2) {
+            plain_step(t, std::integral_constant<int, 0>{});
+            plain_step(t + 1, std::integral_constant<int, 1>{});
+        }
+        if (t < T) plain_step(t, std::integral_constant<int, 0>{});
+    } else {
+        if (T > 1) {
+            kv_t1 = walk.next(part_t1, pg_t1, pr_t1);
+            load_k(1, kv_t1, pg_t1, pr_t1);
+        }
         wait_vmem();
         __syncthreads();
-        // K(t+2) and V(t+1) are loaded piece by piece between the MFMAs of S^T(t+1): a wave waits on
-        // every load instruction until the memory pipe has taken it, and a burst of them from all
-        // waves at once keeps everybody waiting
-        const bool ld_k = t + 2 < T;
-        if (ld_k) kv_t2 = walk.next(part_t2, pg_t2, pr_t2);
-        i32x4 k_src, v_src;
-        int k_soff, v_soff;
-        tile_src(k_head, k_rsrc, k_row_bytes, kv_t2, pg_t2, pr_t2, k_src, k_soff);
-        tile_src(v_head, v_rsrc, v_row_bytes, kv_t1, pg_t1, pr_t1, v_src, v_soff);
-        const int kv0 = kv_t;
-        const bool partial = part_t;
-        if constexpr (HAS_NEXT) {
-            if (part_t1) make_tags(BUF ^ 1, kv_t1, t + 1);
-        }
-        bf16x8 pf[2];
-        if constexpr (HAS_NEXT) {
-            using L = WaveTileLoader<D, NW>;
-            constexpr int NP = 2 * L::NI, NMQ = 2 * (D / 16);
-            qk(std::integral_constant<int, BUF ^ 1>{}, s_next, [&](auto m_tag) {
-                static_for<0, NP>([&](auto p_tag) {
-                    constexpr int p = decltype(p_tag)::value;
-                    if constexpr (p * NMQ / NP == decltype(m_tag)::value) {
-                        if constexpr (p < L::NI) {
-                            if (ld_k) k_loader.template start_one<p>(k_src, smem_bytes + BUF * (TILE * 2), k_soff);
-                        } else {
-                            v_loader.template start_one<p - L::NI>(v_src, smem_bytes + (2 + (BUF ^ 1)) * (TILE * 2), v_soff);
+        f32x16 s_cur[2], s_next[2];
+        qk(std::integral_constant<int, 0>{}, s_cur, [](auto) {});
+
+        // One tile (t & 1 == BUF).  S^T of tile t+1 (MFMA) is issued next to the softmax of tile t (VALU),
+        // P V of the first 32 keys next to the softmax of the second 32.
+        auto tile_step = [&](int t, auto buf_tag, auto has_next_tag) {
+            constexpr int BUF = decltype(buf_tag)::value;
+            constexpr bool HAS_NEXT = decltype(has_next_tag)::value;
+            // Everything this wave asked for has landed; after the barrier so has everyone else's, and
+            // nobody still reads K(t) [buffer BUF] or V(t-1) [buffer BUF ^ 1], which are refilled next.
+            wait_vmem();
+            __syncthreads();
+            // K(t+2) and V(t+1) are loaded piece by piece between the MFMAs of S^T(t+1): a wave waits on
+            // every load instruction until the memory pipe has taken it, and a burst of them from all
+            // waves at once keeps everybody waiting
+            const bool ld_k = t + 2 < T;
+            if (ld_k) kv_t2 = walk.next(part_t2, pg_t2, pr_t2);
+            i32x4 k_src, v_src;
+            int k_soff, v_soff;
+            tile_src(k_head, k_rsrc, k_row_bytes, kv_t2, pg_t2, pr_t2, k_src, k_soff);
+            tile_src(v_head, v_rsrc, v_row_bytes, kv_t1, pg_t1, pr_t1, v_src, v_soff);
+            const int kv0 = kv_t;
+            const bool partial = part_t;
+            if constexpr (HAS_NEXT) {
+                if (part_t1) make_tags(BUF ^ 1, kv_t1, t + 1);
+            }
+            bf16x8 pf[2];
+            if constexpr (HAS_NEXT) {
+                using L = WaveTileLoader<D, NW>;
+                constexpr int NP = 2 * L::NI, NMQ = 2 * (D / 16);
+                qk(std::integral_constant<int, BUF ^ 1>{}, s_next, [&](auto m_tag) {
+                    static_for<0, NP>([&](auto p_tag) {
+                        constexpr int p = decltype(p_tag)::value;
+                        if constexpr (p * NMQ / NP == decltype(m_tag)::value) {
+                            if constexpr (p < L::NI) {
+                                if (ld_k) k_loader.template start_one<p>(k_src, smem_bytes + BUF * (TILE * 2), k_soff);
+                            } else {
+                                v_loader.template start_one<p - L::NI>(v_src, smem_bytes + (2 + (BUF ^ 1)) * (TILE * 2), v_soff);
+                            }
                         }
-                    }
+                    });
                 });
-            });
-        }
-        softmax(s_cur[0], kv0, partial, BUF, 0, pf);
-        pv(buf_tag, 0, pf);
-        softmax(s_cur[1], kv0 + 32, partial, BUF, 1, pf);
-        pv(buf_tag, 1, pf);
-        if constexpr (HAS_NEXT) {
+            }
+            softmax(s_cur[0], kv0, partial, BUF, 0, pf);
+            pv(buf_tag, 0, pf);
+            softmax(s_cur[1], kv0 + 32, partial, BUF, 1, pf);
+            pv(buf_tag, 1, pf);
+            if constexpr (HAS_NEXT) {
 #pragma unroll
-            for (int kvb = 0; kvb < 2; ++kvb) s_cur[kvb] = s_next[kvb];
-        }
-        kv_t = kv_t1, part_t = part_t1;
-        kv_t1 = kv_t2, part_t1 = part_t2;
-        if constexpr (PAGED) pg_t1 = pg_t2, pr_t1 = pr_t2;
-    };
-    {
-        const std::integral_constant<int, 0> b0;
-        const std::integral_constant<int, 1> b1;
-        int t = 0;
-        for (; t + 2 < T; t += 2) {
-            tile_step(t, b0, std::true_type{});
-            tile_step(t + 1, b1, std::true_type{});
-        }
-        if (T - t == 2) {
-            tile_step(t, b0, std::true_type{});
-            tile_step(t + 1, b1, std::false_type{});
-        } else {
-            tile_step(t, b0, std::false_type{});
+                for (int kvb = 0; kvb < 2; ++kvb) s_cur[kvb] = s_next[kvb];
+            }
+            kv_t = kv_t1, part_t = part_t1;
+            kv_t1 = kv_t2, part_t1 = part_t2;
+            if constexpr (PAGED) pg_t1 = pg_t2, pr_t1 = pr_t2;
+        };
+        {
+            const std::integral_constant<int, 0> b0;
+            const std::integral_constant<int, 1> b1;
+            int t = 0;
+            for (; t + 2 < T; t += 2) {
+                tile_step(t, b0, std::true_type{});
+                tile_step(t + 1, b1, std::true_type{});
+            }
+            if (T - t == 2) {
+                tile_step(t, b0, std::true_type{});
+                tile_step(t + 1, b1, std::false_type{});
+            } else {
+                tile_step(t, b0, std::false_type{});
+            }
         }
     }
 

@@ -100,6 +100,36 @@ def test_canvas_edges(w, h, k, layout, tile):
             hp.check_grad(name, got, r)
 
 
+@pytest.mark.parametrize("w,h,k,layout,tile,Bq,Bk", [
+    (33, 40, 5, "row_major", 0, 128, 64), (100, 9, 3, "row_major", 4, 64, 64), (40, 24, 7, "tiled", 8, 128, 64),
+    (20, 44, 3, "tiled", 2, 128, 128), (24, 36, 5, "tiled", 4, 128, 64), (40, 24, 5, "tiled", 1, 128, 64),
+    (48, 32, 5, "tiled", 16, 64, 128), (64, 32, 5, "tiled", 32, 128, 64), (32, 32, 9, "morton", 0, 128, 128)])
+@pytest.mark.parametrize("D", [64, 128])
+def test_canvas_blocks_left_out(w, h, k, layout, tile, Bq, Bk, D):
+    """Canvases of several row blocks in every token order and tile size: the 32 x 32 blocks, tiles and steps
+    that are left out because the windows cannot reach them."""
+    import paper_2412_05496_amd as fa
+    S, dev = w * h, torch.device(DEV)
+    wl = wlm.CFG1.scaled(name="canvas_cut", B=1, Hq=2, Hkv=1, S=S, D=D, Bq=Bq, Bk=Bk, seed=4400 + S)
+    inp = wlm.make_train_inputs(wl, with_dO=True)
+    mask_mod, score_mod = fo.neighborhood_mask(w, h, k, layout, tile), fo.Identity()
+    params = fa.ModParams(na_width=w, na_height=h, na_kernel=k, na_tile=tile,
+                          na_layout={"row_major": fa.NA_ROW_MAJOR, "tiled": fa.NA_TILED, "morton": fa.NA_MORTON}[layout])
+    print(f"[case] canvas blocks {w}x{h} K={k} {layout} T={tile} D={D}", flush=True)
+    bm = fa.alloc_blockmask(1, 1, S, S, Bq, Bk, device=dev)
+    fa.flexattn_blockmask_build(fa.MASK_NEIGHBORHOOD, params, bm)
+    Q, K, V = (t.to(dev) for t in (inp.Q, inp.K, inp.V))
+    O, LSE = torch.full_like(Q, float("nan")), torch.full(Q.shape[:3], float("nan"), device=dev)
+    fa.flexattn_forward(Q, K, V, fa.SCORE_IDENTITY, fa.MASK_NEIGHBORHOOD, params, bm, inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    hp.check_output(O, LSE, *fo.flex_attention(inp.Q, inp.K, inp.V, score_mod, mask_mod, inp.scale))
+    ref = fo.flex_attention_backward(inp.Q, inp.K, inp.V, inp.dO, score_mod, mask_mod, inp.scale)
+    ids = (fa.MASK_NEIGHBORHOOD, fa.SCORE_IDENTITY, params, Q, K, V)
+    for stored in (False, True):
+        for name, got, r in zip(("dQ", "dK", "dV"), hp.run_backward(wl, inp, dev, O, LSE, bm, ids, stored=stored), ref):
+            hp.check_grad(name, got, r)
+
+
 @pytest.mark.parametrize("q_len,kv_len,Bq,Bk", [(48, 4800, 8, 16), (2049, 70, 8, 16), (100, 257 * 5, 33, 5), (130, 200, 130, 200)])
 def test_long_lines_and_odd_blocks(q_len, kv_len, Bq, Bk):
     """More than 256 blocks in a line (both orientations), block sizes above 64 that are no power of two,
