@@ -58,38 +58,60 @@ constexpr int kTileKV = 64;   // keys per kernel tile
 // 64 heads: 158 -> 127; no mask, S = 2048: 89.5 -> 86.5; packed documents with ALiBi: 218 -> 216.
 // The pipelined one stays where it is the better one: a bounded soft-cap, whose softmax needs no running
 // maximum (287 -> 299), and Bq = 64, where LDS admits 2.5 waves per SIMD either way (a single small call: 7.7
-// -> 8.4), and D = 128, two waves per SIMD either way.  Neighborhood masks take the plain one at any size:
-// 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (480 -> 355 at 128 x 128 pixels).
-template <int D, int NW, uint32_t MASK, bool BOUNDED>
+// -> 8.4).  Neighborhood masks gain most: 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (490 ->
+// 340 at 128 x 128 pixels).
+template <int D, int NW, bool BOUNDED>
 constexpr bool fwd_plain() {
-    return NW == 4 && (PartialMask<MASK>::kCanvas || (D == 64 && !BOUNDED));
+    return D == 64 && NW == 4 && !BOUNDED;
+}
+
+// The same at D = 128, where 64-key tiles of K and V leave LDS for two workgroups: units of 32 keys in a ring of
+// three take 48 KiB, three workgroups of 168 registers.  The chip's power limit eats most of the gain on long
+// dense rows, so the rule is by what was measured (us, pipelined -> units; D = 128, Bq = 128):
+//   rows of few or PARTIAL tiles, and biases: window of 1024, S = 5000 209 -> 191, with a soft-cap 232 -> 200;
+//   documents, S = 2048 358 -> 335; ALiBi, S = 3000 572 -> 544, S = 8192 778 -> 768; relative bias, S = 32768
+//   5210 -> 5020; neighborhood, 128 x 128, K = 13 582 -> 531;
+//   otherwise by length: causal S = 1024 558 -> 516, S = 1536 331 -> 321, no mask S = 1536 454 -> 451, S = 2048
+//   571 -> 584, causal S = 8192 592 -> 626;
+//   never with a relative bias under a soft-cap: its table no longer lets three in (325 -> 345).
+enum class FwdUnits { kNever, kAlways, kShort };
+constexpr int kUnitsMaxKeys = 1536;
+template <int D, int NW, uint32_t MASK, uint32_t SCORE>
+constexpr FwdUnits fwd_units() {
+    constexpr uint32_t prims = (MASK | (MASK >> 8)) & 0xffu;
+    constexpr bool cap = SCORE & FLEXATTN_SCORE_SOFTCAP, bias = SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS);
+    if (D != 128 || NW != 4 || (cap && (SCORE & FLEXATTN_SCORE_REL_BIAS))) return FwdUnits::kNever;
+    if ((prims & (FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD)) || (bias && !cap)) return FwdUnits::kAlways;
+    return FwdUnits::kShort;
 }
 // Waves per SIMD to compile for: what registers (512 per SIMD lane) and LDS admit.  The pipelined variants
 // with a relative-bias table would spill at three.
-template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED>
+template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool UNITS>
 constexpr int fwd_waves_per_simd() {
-    if (D != 64) return 2;
-    if (fwd_plain<D, NW, MASK, BOUNDED>()) return NW == 4 ? 4 : 2;
+    if (D != 64) return UNITS ? 3 : 2;
+    if (fwd_plain<D, NW, BOUNDED>()) return NW == 4 ? 4 : 2;
     return (SCORE & FLEXATTN_SCORE_REL_BIAS) ? 2 : 3;
 }
 
 // BOUNDED: the score_mod ends in a soft-cap small enough that the cap itself serves as the fixed
 // softmax maximum (see ScoreMod::bounded); chosen by the host from the cap value.
+// UNITS: 32-key units in a ring of three (fwd_units).
 // PAGED: the tiles of K and V are fetched from a paged pool through the converted block lists;
 // the mods keep seeing the logical key index.
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
-template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED = false>
-__global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BOUNDED>())) void fwd_kernel(const FwdArgs a) {
+template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED, bool UNITS = false>
+__global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BOUNDED, UNITS>())) void fwd_kernel(const FwdArgs a) {
     constexpr int Bq = NW * 32;
     constexpr int TILE = kTileKV * D;              // elements per LDS tile
 
-    __shared__ __attribute__((aligned(1024))) bf16 smem[4 * TILE];   // K(even), K(odd), V(even), V(odd)
+    // K(even), K(odd), V(even), V(odd); UNITS: three slots of 32 keys, K then V
+    __shared__ __attribute__((aligned(1024))) bf16 smem[(UNITS ? 3 : 4) * TILE];
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];           // relative-bias row of the head
     using Mask = PartialMask<MASK>;
-    __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys (even, odd)
+    __shared__ __attribute__((aligned(256))) uint32_t s_tag[UNITS ? 3 : 2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys, per buffer
 
     __shared__ uint32_t s_qtag[Mask::kTags ? NW * 64 : 1];            // each lane's own tag (its query's)
     __shared__ uint8_t s_hidden[Mask::kCanvas && NW == 4 ? kHiddenTiles : 1];    // CanvasBlocks::hidden_bits of the first tiles
@@ -153,7 +175,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
                         int& soff) __attribute__((always_inline)) {
         if constexpr (PAGED) {
             const int pg = min(max(page, 0), a.n_pool_pages - 1);
-            rsrc = make_rsrc(head + (int64_t)pg * a.page_stride + row * D, (uint32_t)(kTileKV * D * 2));
+            rsrc = make_rsrc(head + (int64_t)pg * a.page_stride + row * D, (uint32_t)((UNITS ? 32 : kTileKV) * D * 2));
             soff = 0;
         } else {
             rsrc = whole;
@@ -356,18 +378,80 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
                 oacc[db] = mfma32(v_reader.read(smem_bytes + (2 + BUF) * (TILE * 2), kvb * 32 + 16 * c, db), pf[c], oacc[db]);
     };
 
-    // ---- prologue: K(0), V(0), K(1) in flight; S^T(0)
-    kv_t = walk.next(part_t, pg_t, pr_t);
-    load_k(0, kv_t, pg_t, pr_t);
-    load_v(0, kv_t, pg_t, pr_t);
-    if (part_t) make_tags(0, kv_t, 0);
-    if constexpr (fwd_plain<D, NW, MASK, BOUNDED>()) {
+    // ---- prologue: K(0), V(0) (and K(1), S^T(0) below) in flight
+    auto first_tile = [&]() {
+        kv_t = walk.next(part_t, pg_t, pr_t);
+        load_k(0, kv_t, pg_t, pr_t);
+        load_v(0, kv_t, pg_t, pr_t);
+        if (part_t) make_tags(0, kv_t, 0);
+    };
+    auto hidden_block = [&](uint32_t bits, bool partial, int kv, int kvb) __attribute__((always_inline)) {
+        if constexpr (Mask::kCanvas) return (bits & (1u << kvb)) != 0;
+        else return partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31);
+    };
+    if constexpr (UNITS) {
+        // 32 keys at a time through a ring of three slots, two units ahead: unit u + 2 is asked for when every
+        // wave is done with u - 1, whose slot it takes.
+        constexpr uint32_t UT = 32 * D * 2;
+        using UnitLoader = WaveTileLoader<D, NW, 32>;
+        const UnitLoader ku_loader(a.k_ss, w, lane), vu_loader(a.v_ss, w, lane);
+        TileWalk<PAGED, 32> uwalk(a.full_idx + line * a.NC, a.kv_idx + line * a.NC, n_full, n_part, 2 * a.sub, a.Bk,
+                                  PAGED ? a.phys_full_idx + line * a.NC : nullptr, PAGED ? a.phys_kv_idx + line * a.NC : nullptr);
+        const int TU = 2 * T;
+        int kv_of[3];
+        bool part_of[3];
+        auto fetch = [&](int u, auto slot_tag) {
+            constexpr int SLOT = decltype(slot_tag)::value;
+            int pg = 0, pr = 0, soff;
+            i32x4 rsrc;
+            const int kv = uwalk.next(part_of[SLOT], pg, pr);
+            kv_of[SLOT] = kv;
+            if (part_of[SLOT]) make_tags(SLOT, kv, u);
+            tile_src(k_head, k_rsrc, k_row_bytes, kv, pg, pr, rsrc, soff);
+            ku_loader.start(rsrc, smem_bytes + SLOT * 2 * UT, soff);
+            tile_src(v_head, v_rsrc, v_row_bytes, kv, pg, pr, rsrc, soff);
+            vu_loader.start(rsrc, smem_bytes + SLOT * 2 * UT + UT, soff);
+        };
+        auto unit_step = [&](int u, auto slot_tag) {
+            constexpr int SLOT = decltype(slot_tag)::value;
+            if (u + 1 < TU) wait_vmem_but<2 * UnitLoader::NI>();     // (unit u + 1 may still be under way)
+            else wait_vmem();
+            __syncthreads();
+            const int kv = kv_of[SLOT];
+            const bool partial = part_of[SLOT];
+            if (u + 2 < TU) fetch(u + 2, std::integral_constant<int, (SLOT + 2) % 3>{});
+            if (!hidden_block(hidden_of(u >> 1) >> (u & 1), partial, kv, 0)) {
+                f32x16 s;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+#pragma unroll
+                for (int ks = 0; ks < D / 16; ++ks) s = mfma32(k_reader.read(smem_bytes + SLOT * 2 * UT, 0, ks), qf[ks], s);
+                bf16x8 pf[2];
+                softmax(s, kv, partial, SLOT, 0, pf);
+#pragma unroll
+                for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        oacc[db] = mfma32(v_reader.read(smem_bytes + SLOT * 2 * UT + UT, 16 * c, db), pf[c], oacc[db]);
+            }
+        };
+        const std::integral_constant<int, 0> s0;
+        const std::integral_constant<int, 1> s1;
+        const std::integral_constant<int, 2> s2;
+        fetch(0, s0);
+        fetch(1, s1);
+        int u = 0;
+        for (; u + 2 < TU; u += 3) {
+            unit_step(u, s0);
+            unit_step(u + 1, s1);
+            unit_step(u + 2, s2);
+        }
+        if (u < TU) unit_step(u, s0);
+        if (u + 1 < TU) unit_step(u + 1, s1);
+    } else if constexpr (fwd_plain<D, NW, BOUNDED>()) {
         // One block of 32 keys after the other, K and V one tile ahead.  A wave leaves out the blocks that
         // the mask hides from all of its rows.
-        auto hidden_block = [&](uint32_t bits, bool partial, int kv, int kvb) __attribute__((always_inline)) {
-            if constexpr (Mask::kCanvas) return (bits & (1u << kvb)) != 0;
-            else return partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31);
-        };
+        first_tile();
         auto plain_step = [&](int t, auto buf_tag) {
             constexpr int BUF = decltype(buf_tag)::value;
             wait_vmem();
@@ -403,6 +487,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
         }
         if (t < T) plain_step(t, std::integral_constant<int, 0>{});
     } else {
+        first_tile();
         if (T > 1) {
             kv_t1 = walk.next(part_t1, pg_t1, pr_t1);
             load_k(1, kv_t1, pg_t1, pr_t1);
@@ -504,7 +589,16 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
 #define FLEXATTN_LAUNCH(DD, NW)                                                                            \
     hipLaunchKernelGGL((fwd_kernel<DD, NW, MASK, SCORE, BOUNDED, PAGED>), dim3(grid), dim3(NW * 64), 0, st, a); \
     return FLEXATTN_OK;
-    if (D == 128 && Bq == 128) { FLEXATTN_LAUNCH(128, 4) }
+    if (D == 128 && Bq == 128) {
+        constexpr FwdUnits units_rule = fwd_units<128, 4, MASK, SCORE>();
+        if constexpr (units_rule != FwdUnits::kNever) {
+            if (units_rule == FwdUnits::kAlways || a.kv_len <= kUnitsMaxKeys) {
+                hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, true>), dim3(grid), dim3(256), 0, st, a);
+                return FLEXATTN_OK;
+            }
+        }
+        if constexpr (units_rule != FwdUnits::kAlways) { FLEXATTN_LAUNCH(128, 4) }
+    }
     if (D == 128 && Bq == 64) { FLEXATTN_LAUNCH(128, 2) }
     if (D == 64 && Bq == 128) { FLEXATTN_LAUNCH(64, 4) }
     if (D == 64 && Bq == 64) { FLEXATTN_LAUNCH(64, 2) }

@@ -120,14 +120,14 @@ __device__ __forceinline__ void dma_x1_nt(i32x4 rsrc, uint32_t lds, int v0, int 
                  :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(v0), "s"(scalar_rsrc(rsrc)), "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory");
 }
 
-// The tile copy with buffer loads, for a workgroup of NW waves: the row of the tile is selected by
+// The tile copy (ROWS rows) with buffer loads, for a workgroup of NW waves: the row of the tile is selected by
 // a scalar byte offset, so starting a tile costs an M0 write per four loads and no vector
 // arithmetic.  Wave w fills the contiguous LDS bytes [w * 1024 * NI, (w + 1) * 1024 * NI) of the
 // tile.  The per-lane offsets stay non-negative as long as the row stride is >= D.
 // Completion: s_waitcnt vmcnt by every wave, then a barrier.
-template <int D, int NW>
+template <int D, int NW, int ROWS = 64>
 struct WaveTileLoader {
-    static constexpr int DC = D / 8, RPI = 64 / DC, NI = DC / NW;   // NI loads per wave
+    static constexpr int DC = D / 8, RPI = 64 / DC, NI = DC / NW * ROWS / 64;   // NI loads per wave
     static_assert(NI == 2 || NI == 4 || NI == 8, "D is 64 or 128, 2 or 4 waves");
     int32_t voff[NI];                           // per-lane byte offsets
     uint32_t wave_off;                          // of this wave's part inside a tile
@@ -206,11 +206,11 @@ struct TrReader {
     }
 };
 
-// Walk over the 64-wide tiles of the blocks a BlockMask lists for one row (or column) of blocks:
+// Walk over the 64-wide (STEP-wide) tiles of the blocks a BlockMask lists for one row (or column) of blocks:
 // FULL blocks first, then PARTIAL ones, each block cut into `sub` tiles.  Written without
 // branches, and the index of the following block is fetched (scalar cache) on every call and only
 // consumed by the call after it, so that the fetch has a tile's worth of work to hide behind.
-template <bool PAGED = false>
+template <bool PAGED = false, int STEP = 64>
 struct TileWalk {
     const int32_t* full_idx;
     const int32_t* part_idx;
@@ -239,11 +239,11 @@ struct TileWalk {
     // in the pool (the page is the physical block); otherwise they are not touched.
     __device__ __forceinline__ int next(bool& partial, int& page, int& row_in_page) {
         blk = entered ? fetched : blk;
-        const int x0 = blk * block_len + s * 64;
+        const int x0 = blk * block_len + s * STEP;
         if constexpr (PAGED) {
             pblk = entered ? pfetched : pblk;
             page = pblk;
-            row_in_page = s * 64;
+            row_in_page = s * STEP;
             pfetched = phys_at(min(pos + 1, n_blocks - 1));
         }
         partial = pos >= n_full;

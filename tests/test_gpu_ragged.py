@@ -20,6 +20,14 @@ CASES = [
 ]
 
 
+# D = 128 forward: 32-key units in a ring of three up to 1536 keys, 64-key tiles above (rows of 1, 2, 3 tiles; both
+# sides of the line)
+CASES += [(f"{mask}_{score}_d128_s{S}", wlm.CFG2, dict(B=1, Hq=1, Hkv=1, S=S, mask=mask, score=score), q_len)
+          for mask, score, S, q_len in [("none", "identity", 33, None), ("none", "identity", 100, 70), ("none", "identity", 190, 20),
+                                        ("causal", "identity", 1536, None), ("causal", "identity", 1537, None),
+                                        ("none", "identity", 1601, 200), ("causal", "softcap", 1540, 130)]]
+
+
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_ragged_lengths(case):
     import paper_2412_05496_amd as fa
