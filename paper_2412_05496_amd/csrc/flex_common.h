@@ -64,6 +64,16 @@ __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_lo
 // Exchange a value with the lane 32 away (the other half of the wave).
 __device__ __forceinline__ float swap_halves(float v) { return __shfl_xor(v, 32, 64); }
 
+// The larger of this lane's value and that of the lane 32 away: one exchange in the vector unit (a shuffle goes
+// through LDS, and takes six instructions to address).
+__device__ __forceinline__ float max_halves(float v) {
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    float m;        // (not fmaxf, which first puts both through a max of their own to quieten NaNs)
+    asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"((unsigned)r[0]), "v"((unsigned)r[1]));
+    return m;
+}
+
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     bf16x2 v;
     v[0] = (bf16)lo;

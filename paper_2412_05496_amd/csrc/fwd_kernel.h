@@ -333,7 +333,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
             float mx = s[0];
 #pragma unroll
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-            mx = fmaxf(mx, swap_halves(mx));
+            mx = max_halves(mx);
             if (__any(mx > m_thr)) {                 // some row of the wave moves its maximum (by mx)
                 const float up = mx > m_thr ? mx : 0.0f;
                 // (a row's first keys: nothing to rescale yet, and 2^-mx could overflow)
