@@ -223,7 +223,7 @@ __device__ __forceinline__ int q_offset_of(const flexattn_mod_params& p, int b) 
 // (Evaluating the mask element by element instead -- the canvas decode of every key, a lane exchange or a
 // table read per document id -- made PARTIAL blocks several times as expensive as FULL ones: neighborhood
 // attention on 128 x 128 pixels, K = 13, D = 64, B = 4, H = 16: forward 0.98 ms, dK/dV 1.60 ms before, 0.42
-// and 0.67 since.)
+// and 0.67 since; the forward 0.34 where it also leaves out the blocks CanvasBlocks finds hidden.)
 // ---------------------------------------------------------------------------------------
 
 // Position of element r of a lane's 16 (without the 4 * half that goes into the base).
