@@ -628,7 +628,7 @@ inline bool mask_id_valid(uint32_t m) {
     return (m & ~0x3f3fu) == 0 && !((m & 0xffu) == 0 && (m >> 8) != 0);
 }
 inline bool score_id_valid(uint32_t s) { return (s & ~7u) == 0; }
-inline bool mask_uses(uint32_t m, uint32_t prim) { return ((m | (m >> 8)) & prim) != 0; }
+constexpr bool mask_uses(uint32_t m, uint32_t prim) { return ((m | (m >> 8)) & prim) != 0; }
 
 // Pointers the selected mods will dereference must be present.
 inline int check_mod_params(uint32_t mask_id, uint32_t score_id, const flexattn_mod_params* p) {

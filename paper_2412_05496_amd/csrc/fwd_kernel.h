@@ -73,9 +73,12 @@ constexpr bool fwd_plain() {
 //   5210 -> 5020; neighborhood, 128 x 128, K = 13 582 -> 531;
 //   otherwise by length: causal S = 1024 558 -> 516, S = 1536 331 -> 321, no mask S = 1536 454 -> 451, S = 2048
 //   571 -> 584, causal S = 8192 592 -> 626;
-//   never with a relative bias under a soft-cap: its table no longer lets three in (325 -> 345).
+//   never with a relative bias under a soft-cap: its table no longer lets three in (325 -> 345);
+//   and only where the workgroups are three rounds of the chip (a round, for the even rows of a window): with
+//   fewer there is nothing to put beside a workgroup, and each is slower by itself (one sequence, S = 4096,
+//   ALiBi, 4 heads 108 -> 127, 24 heads 172 -> 215; window of 1024, 16 heads 48.5 -> 49.3, 24 heads 79 -> 65).
 enum class FwdUnits { kNever, kAlways, kShort };
-constexpr int kUnitsMaxKeys = 1536;
+constexpr int kUnitsMaxKeys = 1536, kUnitsMinGroups = 9 * 256, kUnitsMinGroupsWindow = 3 * 256;
 template <int D, int NW, uint32_t MASK, uint32_t SCORE>
 constexpr FwdUnits fwd_units() {
     constexpr uint32_t prims = (MASK | (MASK >> 8)) & 0xffu;
@@ -113,8 +116,9 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
     using Mask = PartialMask<MASK>;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[UNITS ? 3 : 2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys, per buffer
 
+    constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || fwd_plain<D, NW, BOUNDED>());
     __shared__ uint32_t s_qtag[Mask::kTags ? NW * 64 : 1];            // each lane's own tag (its query's)
-    __shared__ uint8_t s_hidden[Mask::kCanvas && NW == 4 ? kHiddenTiles : 1];    // CanvasBlocks::hidden_bits of the first tiles
+    __shared__ uint8_t s_hidden[kHiddenTable ? kHiddenTiles : 1];    // CanvasBlocks::hidden_bits of the first tiles
 
     // ---- workgroup -> (b, hkv, g, row of blocks).  Consecutive workgroup ids go to the 8 XCDs in
     // turn; all rows and all G query heads of one (b, hkv) are sent to the same XCD so that its K/V
@@ -204,10 +208,10 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
             if (w == (turn & (NW - 1))) s_tag[buf][lane] = mask.key_pixel(min(kv0 + lane, a.kv_len - 1));
         }
     };
-    if constexpr (Mask::kCanvas && NW == 4) fill_hidden_tiles<NW>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, a.sub, a.Bk, row * Bq, tid);
+    if constexpr (kHiddenTable) fill_hidden_tiles<NW>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, a.sub, a.Bk, row * Bq, tid);
     // 32-key blocks of tile t that are hidden from this wave (bit 0, bit 1); visible after the prologue's barrier
     auto hidden_of = [&](int t) __attribute__((always_inline)) -> uint32_t {
-        if constexpr (!(Mask::kCanvas && NW == 4)) return 0u;
+        if constexpr (!kHiddenTable) return 0u;
         else return t < min(T, kHiddenTiles) ? ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (2 * w)) & 3u : 0u;
     };
     const float inv_neg2c = smod.capl2 > 0.0f ? -0.5f / smod.capl2 : 0.0f;   // 1 / (-2 cap log2 e)
@@ -592,12 +596,14 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
     if (D == 128 && Bq == 128) {
         constexpr FwdUnits units_rule = fwd_units<128, 4, MASK, SCORE>();
         if constexpr (units_rule != FwdUnits::kNever) {
-            if (units_rule == FwdUnits::kAlways || a.kv_len <= kUnitsMaxKeys) {
+            const int64_t groups = (int64_t)a.B * a.Hq * a.NR;
+            if ((units_rule == FwdUnits::kAlways || a.kv_len <= kUnitsMaxKeys) &&
+                groups >= (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) ? kUnitsMinGroupsWindow : kUnitsMinGroups)) {
                 hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, true>), dim3(grid), dim3(256), 0, st, a);
                 return FLEXATTN_OK;
             }
         }
-        if constexpr (units_rule != FwdUnits::kAlways) { FLEXATTN_LAUNCH(128, 4) }
+        FLEXATTN_LAUNCH(128, 4)
     }
     if (D == 128 && Bq == 64) { FLEXATTN_LAUNCH(128, 2) }
     if (D == 64 && Bq == 128) { FLEXATTN_LAUNCH(64, 4) }

@@ -20,8 +20,7 @@ CASES = [
 ]
 
 
-# D = 128 forward: 32-key units in a ring of three up to 1536 keys, 64-key tiles above (rows of 1, 2, 3 tiles; both
-# sides of the line)
+# D = 128 forward, few workgroups: 64-key tiles (rows of 1, 2, 3 tiles, short and long)
 CASES += [(f"{mask}_{score}_d128_s{S}", wlm.CFG2, dict(B=1, Hq=1, Hkv=1, S=S, mask=mask, score=score), q_len)
           for mask, score, S, q_len in [("none", "identity", 33, None), ("none", "identity", 100, 70), ("none", "identity", 190, 20),
                                         ("causal", "identity", 1536, None), ("causal", "identity", 1537, None),
@@ -66,3 +65,52 @@ def test_ragged_lengths(case):
     hp.check_grad("dV", dV, dV_ref)
     for buf, rows in ((O_buf, Lq), (dQ_buf, Lq), (dK_buf, wl.S), (dV_buf, wl.S)):
         assert (buf[:, :, rows:] == 7.0).all()
+
+
+@pytest.mark.parametrize("mask,score,S,q_len", [
+    ("none", "identity", 33, None), ("none", "identity", 100, 70), ("none", "identity", 190, 20), ("causal", "identity", 257, None),
+    ("causal", "softcap", 130, None), ("swa_causal", "identity", 300, None), ("swa_causal", "softcap", 200, None),
+    ("causal", "alibi", 190, None), ("swa_causal_or_prefix", "rel_bias", 260, None), ("doc_causal", "alibi", 200, None)])
+def test_forward_d128_many_workgroups(mask, score, S, q_len):
+    """D = 128 forward with enough workgroups for 32-key units: rows of 1, 2, 3 ... units, every mask kind.  All
+    sequences are the same (batch stride 0), so one is compared with the oracle and the others with it."""
+    import paper_2412_05496_amd as fa
+    dev, Lq = torch.device("cuda:0"), q_len or S
+    wl = wlm.CFG2.scaled(name="units", B=1, Hq=2, Hkv=1, S=S, mask=mask, score=score, window=50, prefix_len=40, rel_len=30,
+                         doc_len_min=30, doc_len_max=90, seed=3900 + S)
+    inp = wlm.make_train_inputs(wl)
+    score_mod, mask_mod = hp.oracle_mods(wl, inp)
+    O_ref, LSE_ref = fo.flex_attention(inp.Q[:, :, :Lq], inp.K, inp.V, score_mod, mask_mod, inp.scale)
+    mask_id, score_id, params, _ = hp.library_mods(wl, inp, dev)
+    if params.doc_ids is not None:
+        params.doc_ids = params.doc_ids[0].contiguous()
+    bm = fa.alloc_blockmask(1, 1, Lq, S, wl.Bq, wl.Bk, device=dev)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    B = 2304 // (2 * ((Lq + wl.Bq - 1) // wl.Bq)) + 1
+    Q, K, V = (t.to(dev).expand(B, -1, -1, -1) for t in (inp.Q[:, :, :Lq].contiguous(), inp.K, inp.V))
+    O = torch.full((B, 2, Lq, wl.D), float("nan"), dtype=torch.bfloat16, device=dev)
+    LSE = torch.full((B, 2, Lq), float("nan"), device=dev)
+    fa.flexattn_forward(Q, K, V, score_id, mask_id, params, bm, inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    hp.check_output(O[:1], LSE[:1], O_ref, LSE_ref)
+    assert torch.equal(O, O[:1].expand_as(O)) and torch.equal(LSE, LSE[:1].expand_as(LSE))
+
+
+@pytest.mark.parametrize("w,h,k,layout,tile", [(40, 24, 7, "tiled", 8), (33, 20, 5, "row_major", 0), (32, 32, 9, "morton", 0)])
+def test_forward_d128_canvas_many_workgroups(w, h, k, layout, tile):
+    import paper_2412_05496_amd as fa
+    dev, S = torch.device("cuda:0"), w * h
+    wl = wlm.CFG2.scaled(name="units_canvas", B=1, Hq=2, Hkv=2, S=S, mask="none", score="identity", seed=3950 + S)
+    inp = wlm.make_train_inputs(wl)
+    params = fa.ModParams(na_width=w, na_height=h, na_kernel=k, na_tile=tile,
+                          na_layout={"row_major": fa.NA_ROW_MAJOR, "tiled": fa.NA_TILED, "morton": fa.NA_MORTON}[layout])
+    bm = fa.alloc_blockmask(1, 1, S, S, wl.Bq, wl.Bk, device=dev)
+    fa.flexattn_blockmask_build(fa.MASK_NEIGHBORHOOD, params, bm)
+    B = 2304 // (2 * ((S + wl.Bq - 1) // wl.Bq)) + 1
+    Q, K, V = (t.to(dev).expand(B, -1, -1, -1) for t in (inp.Q, inp.K, inp.V))
+    O = torch.full((B, 2, S, wl.D), float("nan"), dtype=torch.bfloat16, device=dev)
+    LSE = torch.full((B, 2, S), float("nan"), device=dev)
+    fa.flexattn_forward(Q, K, V, fa.SCORE_IDENTITY, fa.MASK_NEIGHBORHOOD, params, bm, inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    hp.check_output(O[:1], LSE[:1], *fo.flex_attention(inp.Q, inp.K, inp.V, fo.Identity(), fo.neighborhood_mask(w, h, k, layout, tile), inp.scale))
+    assert torch.equal(O, O[:1].expand_as(O)) and torch.equal(LSE, LSE[:1].expand_as(LSE))
