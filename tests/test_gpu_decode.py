@@ -91,6 +91,23 @@ def test_relative_bias_in_decode():
     compare(inp, O, LSE, fo.RelBias(table.double()))
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("masked", [float("-inf"), torch.finfo(torch.float32).min])
+@pytest.mark.parametrize("lo,hi", [(32, 64), (0, 32), (100, 420), (128, 1024), (0, 1024)])
+def test_bias_that_masks_keys(D, masked, lo, hi):
+    """A relative bias of -inf (or the lowest float, which the base-2 domain takes to -inf) on the distances
+    lo .. hi - 1: all keys of a tile, of a wave, of a split or of the row.  Rows without a key left: O = 0, LSE = -inf."""
+    import paper_2412_05496_amd as fa
+    ctx = [33, 64, 96, 128, 160, 700, 1025, 3000]
+    wl = wlm.CFG5.scaled(B=len(ctx), Hq=4, Hkv=1, D=D, max_pages=192)
+    inp = wlm.make_decode_inputs(wl, ctx_lens=ctx)
+    table = torch.randn(4, 1024, generator=torch.Generator().manual_seed(10)) * 0.5
+    table[:3, lo:hi] = masked                      # (one head keeps all its keys)
+    print(f"[case] masking bias D={D} {masked} on {lo}..{hi}", flush=True)
+    O, LSE = run_decode(inp, fa.SCORE_REL_BIAS, fa.ModParams(rel_bias=table.to(DEV)))
+    compare(inp, O, LSE, fo.RelBias(torch.where(table < -1e30, torch.tensor(float("-inf")), table).double()))
+
+
 @pytest.mark.parametrize("nseq,Hkv,ctx_max", [(1, 8, 8192), (2, 1, 20000), (3, 2, 700)])
 def test_small_batches_are_cut_into_short_splits(nseq, Hkv, ctx_max):
     """The split length follows nseq * Hkv * (longest addressable context), so a small batch is cut into
