@@ -372,7 +372,8 @@ int flexattn_paged_forward(const flexattn_dims* dims, const flexattn_tensor* Q,
  *              page_table[b, j]; only the first ceil(ctx_lens[b] / page_size) entries are read
  *   ctx_lens   [nseq] int32: visible keys are kv_idx < ctx_lens[b] (0 is legal: O = 0,
  *              LSE = -inf).  score_mods see q_idx = ctx_lens[b] - 1 and the LOGICAL kv_idx.
- *   O [nseq, Hq, D] bf16 dense; LSE nullable [nseq, Hq] fp32.
+ *   O [nseq, Hq, D] bf16 dense, at any element address (16-byte aligned it is written in wide stores);
+ *   LSE nullable [nseq, Hq] fp32.  Q, the pools and the workspace are 16-byte aligned.
  * page_size must be a power of two from 16 to 1024; Hq / Hkv <= 16; max_pages * page_size <= 2^30.
  * Device-side values are not trusted: a context length outside [0, max_pages * page_size] is clamped to
  * that range and a page id outside [0, n_pool_pages) to the nearest valid page, so that wrong tables

@@ -53,8 +53,28 @@ struct DecodeArgs {
     float* part_O;    // [nseq, Hq, max_splits, D]
     float* part_ml;   // [nseq, Hq, max_splits, 2]  (running max in base 2, sum)
     bf16* O;
+    bool o_wide;      // O is 16-byte aligned; otherwise it is written element by element
     float* LSE;
 };
+
+// 2 N consecutive elements of O in one store where O is aligned for it (wide); O itself needs no more than the
+// alignment of its elements.
+template <int N>
+__device__ __forceinline__ void store_o(bf16* p, const uint32_t (&v)[N], bool wide) {
+    typedef uint32_t vec __attribute__((ext_vector_type(N)));
+    if (wide) {
+        vec x;
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = v[i];
+        *(vec*)p = x;
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            ((uint16_t*)p)[2 * i] = (uint16_t)v[i];
+            ((uint16_t*)p)[2 * i + 1] = (uint16_t)(v[i] >> 16);
+        }
+    }
+}
 
 // The values of the two lanes l, l ^ 16 (SWAP16) or l, l ^ 32 in one order or the other, so that a
 // commutative operation on the pair is a reduction over it.  (Inline assembly: the compiler at hand
@@ -125,7 +145,7 @@ __global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_spli
     if (tok_begin >= ctx || tok_begin + a.split_len <= kv_lo) {         // (uniform over the workgroup)
         if (ctx == 0 && split == 0) {
             for (int i = tid; i < a.G * D / 8; i += kDecWaves * 64)
-                *(u32x4*)(a.O + ((int64_t)b * a.Hq + hkv * a.G) * D + i * 8) = u32x4{0, 0, 0, 0};
+                store_o<4>(a.O + ((int64_t)b * a.Hq + hkv * a.G) * D + i * 8, {0u, 0u, 0u, 0u}, a.o_wide);
             if (a.LSE && tid < a.G) a.LSE[(int64_t)b * a.Hq + hkv * a.G + tid] = -INFINITY;
         }
         return;
@@ -300,7 +320,7 @@ __global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_spli
         const int64_t head = (int64_t)b * a.Hq + hkv * a.G + g;
         if (only) {
             const float inv = L > 0.0f ? 1.0f / L : 0.0f;
-            *(u32x2*)(a.O + head * D + d) = u32x2{pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv)};
+            store_o<2>(a.O + head * D + d, {pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv)}, a.o_wide);
             if (d == 0 && a.LSE) a.LSE[head] = (m + fast_log2(L)) * kLn2;
         } else {
             const int64_t item = head * a.max_splits + split;
@@ -362,7 +382,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_combine_kernel(const De
             lt += s_l[r];
         }
         const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
-        *(uint32_t*)(a.O + head * D + 2 * tid) = pack_bf16(o0 * inv, o1 * inv);
+        store_o<1>(a.O + head * D + 2 * tid, {pack_bf16(o0 * inv, o1 * inv)}, a.o_wide);
         if (tid == 0 && a.LSE) a.LSE[head] = (m + fast_log2(lt)) * kLn2;
     }
 }
@@ -510,6 +530,7 @@ extern "C" int flexattn_paged_decode(const flexattn_decode_dims* d, const void* 
     a.part_O = (float*)ws;
     a.part_ml = (float*)ws + items * d->D;
     a.O = (bf16*)O; a.LSE = LSE;
+    a.o_wide = ((uintptr_t)O & 15) == 0;
     rc = d->D == 128 ? launch_decode<128>(a, score_id, (hipStream_t)stream)
                      : launch_decode<64>(a, score_id, (hipStream_t)stream);
     if (rc != FLEXATTN_OK) return rc;

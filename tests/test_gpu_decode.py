@@ -137,6 +137,28 @@ def test_split_merge_edges(D, G, ctx):
     compare(inp, O, LSE, fo.Identity())
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("offset", [1, 2, 4])
+def test_output_at_any_element_address(D, offset):
+    """O needs no more than the alignment of its elements: empty, single-split and combined sequences give the
+    same values 2, 4 and 8 bytes off a 16-byte boundary, and nothing around O is touched."""
+    import paper_2412_05496_amd as fa
+    ctx = [0, 40, 3000]
+    wl = wlm.CFG5.scaled(B=len(ctx), Hq=6, Hkv=2, D=D, max_pages=192)
+    inp = wlm.make_decode_inputs(wl, ctx_lens=ctx)
+    O_ref, LSE_ref = run_decode(inp)
+    n = O_ref.numel()
+    buf = torch.full((n + 32,), 7.0, dtype=torch.bfloat16, device=DEV)
+    O = buf[16 + offset:16 + offset + n].view(O_ref.shape)
+    LSE = torch.full_like(LSE_ref, float("nan"))
+    print(f"[case] O at element {offset} D={D}", flush=True)
+    fa.flexattn_paged_decode(inp.Q.to(DEV), inp.K_pool.to(DEV), inp.V_pool.to(DEV), inp.page_table.to(DEV),
+                             inp.ctx_lens.to(DEV), 0, fa.MASK_CTX_LEN, fa.ModParams(), inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    assert torch.equal(O, O_ref) and torch.equal(LSE, LSE_ref)
+    assert (buf[:16 + offset] == 7.0).all() and (buf[16 + offset + n:] == 7.0).all()
+
+
 def test_wrong_tables_never_leave_the_buffers():
     """Device-side values are not trusted: page ids outside the pool and context lengths beyond what the
     page table addresses (or negative) are clamped, so the call returns normally with finite numbers --
