@@ -102,10 +102,9 @@ __device__ __forceinline__ float column_sum(float v) {
     return q.a + q.b;
 }
 
-// What the exponentials of a row subtract whose largest score so far is m: m, or 0 while every score was -inf
-// (a bias that masks keys).  A wave sees every fourth tile only, a split a part of the keys: both may hold
-// nothing but such keys where the row does not.
-__device__ __forceinline__ float max_to_subtract(float m) { return m == -INFINITY ? 0.0f : m; }
+// Where a running maximum starts.  Not at -inf, which would turn a row into NaN whose scores are all -inf in some
+// tile, wave or split (keys that a bias masks; a wave sees every fourth tile only).
+constexpr float kNoScore = -3.4028234663852886e38f;
 
 // D[16x16] += A[16x32] * B[32x16]: lane l supplies A[row = l % 16][k-slots of group l / 16] and
 // B[k-slots of group l / 16][col = l % 16]; register i of lane l holds D[row = 4 * (l / 16) + i][col = l % 16].
@@ -220,7 +219,7 @@ __global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_spli
     f32x4 oacc[NDB];                                    // O^T: dims 16 db + 4 grp + i of query l16
 #pragma unroll
     for (int db = 0; db < NDB; ++db) oacc[db] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float m_run = -INFINITY, l_run = 0.0f;
+    float m_run = kNoScore, l_run = 0.0f;
 
     for (int tok0 = tok_first; tok0 < tok_end; tok0 += kStep) {
         // ---- tile tok0 has landed; take every operand fragment out of LDS, then start the gather of
@@ -262,14 +261,14 @@ __global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_spli
             mx = fmaxf(mx, x[e]);
         }
         mx = column_max(mx);
-        const float m_old = m_run;
-        m_run = fmaxf(m_run, mx);
-        const float m_sub = max_to_subtract(m_run), alpha = fast_exp2(m_old - m_sub);
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = fast_exp2(m_run - m_new);
+        m_run = m_new;
         float psum = 0.0f;
         u32x4 pk;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
-            const float p0 = fast_exp2(x[2 * jj] - m_sub), p1 = fast_exp2(x[2 * jj + 1] - m_sub);
+            const float p0 = fast_exp2(x[2 * jj] - m_new), p1 = fast_exp2(x[2 * jj + 1] - m_new);
             psum += p0 + p1;
             pk[jj] = pack_bf16(p0, p1);
         }
@@ -308,12 +307,11 @@ __global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_spli
         float m = s_ml[0][0][g];
 #pragma unroll
         for (int w = 1; w < kDecWaves; ++w) m = fmaxf(m, s_ml[w][0][g]);
-        const float m_sub = max_to_subtract(m);
         float L = 0.0f;
         f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int w = 0; w < kDecWaves; ++w) {
-            const float wgt = fast_exp2(s_ml[w][0][g] - m_sub);
+            const float wgt = fast_exp2(s_ml[w][0][g] - m);
             L += wgt * s_ml[w][1][g];
             o += wgt * *(const f32x4*)((const float*)(smem + w * 2 * TILE) + g * OROW + d);
         }
@@ -356,12 +354,11 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_combine_kernel(const De
     for (int s = s0 + lane; s < ns; s += 64) m = fmaxf(m, a.part_ml[(base + s) * 2]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    const float m_sub = max_to_subtract(m);
     float L = 0.0f;
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     auto add = [&](int s, const f32x4& row) {
         const float2 ml = *(const float2*)(a.part_ml + (base + s) * 2);
-        const float wgt = fast_exp2(ml.x - m_sub);
+        const float wgt = fast_exp2(ml.x - m);
         L += wgt * ml.y;
         acc += wgt * row;
     };
