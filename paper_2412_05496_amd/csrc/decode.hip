@@ -118,7 +118,7 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
 template <int D, uint32_t SCORE>
-__global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_split_kernel(const DecodeArgs a) {
+__device__ __forceinline__ void decode_split(const DecodeArgs& a, int tid, int unit, int split) {
     constexpr int DC = D / 8;                  // 16-byte chunks per row
     constexpr int RPI = 64 / DC;               // rows per wave instruction
     constexpr int NI = kDecTile / RPI;         // instructions per tile and tensor
@@ -129,9 +129,8 @@ __global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_spli
     __shared__ float s_ml[kDecWaves][2][16];   // per wave: running max, sum of the 16 query columns
     static_assert(16 * OROW * 4 <= 2 * TILE * 2, "a wave's O must fit its own K and V tiles");
 
-    const int tid = threadIdx.x, lane = tid & 63, grp = lane >> 4, l16 = lane & 15;
+    const int lane = tid & 63, grp = lane >> 4, l16 = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int unit = blockIdx.x, split = blockIdx.y + gridDim.y * blockIdx.z;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     // A context length beyond what the page table addresses (or a negative one) is clamped, and so is
     // every page id below: wrong device-side tables give wrong rows, never an access outside the
@@ -328,6 +327,22 @@ __global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_spli
     }
 }
 
+// One workgroup per (sequence, KV head) and split; MANY: per (sequence, KV head) and gridDim.y-th splits.
+template <int D, uint32_t SCORE, bool MANY>
+__global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_split_kernel(const DecodeArgs a) {
+    if constexpr (!MANY) {
+        decode_split<D, SCORE>(a, threadIdx.x, blockIdx.x, blockIdx.y);
+    } else {
+        for (int split = blockIdx.y; split < a.max_splits; split += gridDim.y) {
+            int tid = threadIdx.x, unit = blockIdx.x;
+            asm volatile("" : "+v"(tid), "+s"(unit));       // (or all that depends on them is worked out ahead of the first split's end)
+            decode_split<D, SCORE>(a, tid, unit, split);
+            if ((split + (int)gridDim.y) * (int64_t)a.split_len >= ldc(a.ctx_lens + unit / a.Hkv)) break;
+            __syncthreads();                                // the merge has read LDS
+        }
+    }
+}
+
 // One workgroup per (sequence, query head): O = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max m).
 // The rows of the splits are read side by side by 256 threads (8 rows at a time for D = 128), the first of
 // them before the maximum is known: what bounds this kernel is the latency of its loads, of which a wave
@@ -409,13 +424,19 @@ static int max_splits_of(const flexattn_decode_dims* d) { return splits(d, cut(d
 
 template <int D>
 static int launch_decode(const DecodeArgs& a, uint32_t score_id, hipStream_t st) {
-    constexpr int kGridY = 32768;      // (the y dimension of a grid ends at 65535)
-    const dim3 grid((unsigned)(a.nseq * a.Hkv), (unsigned)(a.max_splits < kGridY ? a.max_splits : kGridY),
-                    (unsigned)((a.max_splits + kGridY - 1) / kGridY));
+    // The host sees how far the page table reaches, not how long the contexts are: a workgroup beyond their end
+    // returns at once, but holds its LDS until then.  More than kMaxGroups (32 rounds of the chip) are not launched; a
+    // workgroup then takes several splits, if the context has them (us without -> with, a table of 1M tokens: 64
+    // sequences of 512 tokens, 8 KV heads, D = 64 / 128: 95.9 / 143.8 -> 17.6 / 37.5).
+    constexpr int kMaxGroups = 16384;
+    const int units = a.nseq * a.Hkv, room = (kMaxGroups + units - 1) / units;
+    const bool many = a.max_splits > room;
+    const dim3 grid((unsigned)units, (unsigned)(many ? room : a.max_splits));
     switch (score_id) {
 #define CASE(S)                                                                                           \
     case S:                                                                                               \
-        hipLaunchKernelGGL((decode_split_kernel<D, S>), grid, dim3(kDecWaves * 64), 0, st, a);            \
+        if (many) hipLaunchKernelGGL((decode_split_kernel<D, S, true>), grid, dim3(kDecWaves * 64), 0, st, a);  \
+        else hipLaunchKernelGGL((decode_split_kernel<D, S, false>), grid, dim3(kDecWaves * 64), 0, st, a);      \
         break;
         CASE(FLEXATTN_SCORE_IDENTITY)
         CASE(FLEXATTN_SCORE_ALIBI)

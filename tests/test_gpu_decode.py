@@ -159,6 +159,25 @@ def test_output_at_any_element_address(D, offset):
     assert (buf[:16 + offset] == 7.0).all() and (buf[16 + offset + n:] == 7.0).all()
 
 
+@pytest.mark.parametrize("D,window", [(64, None), (128, None), (64, 3000)])
+def test_table_far_beyond_the_contexts(D, window):
+    """256 sequences x 16 KV heads whose page table reaches 32k tokens, 16 splits of 2048 keys: more workgroups than
+    are launched, so one takes every fourth split up to the end of its context."""
+    import paper_2412_05496_amd as fa
+    ctx = [(7 * i) % 40 for i in range(256)]
+    for at, n in ((3, 2048), (40, 2049), (80, 8192), (81, 8193), (120, 16385), (200, 32768), (255, 10000)):
+        ctx[at] = n
+    wl = wlm.CFG5.scaled(B=len(ctx), Hq=16, Hkv=16, D=D, max_pages=2048)
+    inp = wlm.make_decode_inputs(wl, ctx_lens=ctx)
+    print(f"[case] long table D={D} window={window}", flush=True)
+    if window is None:
+        O, LSE = run_decode(inp)
+        compare(inp, O, LSE, fo.Identity())
+    else:
+        O, LSE = run_decode(inp, 0, fa.ModParams(window=window), fa.MASK_CTX_LEN_WINDOW)
+        compare(inp, O, LSE, fo.Identity(), fo.and_mask(fo.ctx_len_mask(inp.ctx_lens), fo.sliding_window_mask(window)))
+
+
 def test_wrong_tables_never_leave_the_buffers():
     """Device-side values are not trusted: page ids outside the pool and context lengths beyond what the
     page table addresses (or negative) are clamped, so the call returns normally with finite numbers --
