@@ -76,20 +76,6 @@ __device__ __forceinline__ void store_o(bf16* p, const uint32_t (&v)[N], bool wi
     }
 }
 
-// The values of the two lanes l, l ^ 16 (SWAP16) or l, l ^ 32 in one order or the other, so that a
-// commutative operation on the pair is a reduction over it.  (Inline assembly: the compiler at hand
-// hands the first result of the swap builtins out for both.  The s_nop covers the wait states between
-// the vector instruction that wrote v and the swap.)
-struct LanePair {
-    float a, b;
-};
-template <bool SWAP16>
-__device__ __forceinline__ LanePair lane_pair(float v) {
-    LanePair p = {v, v};
-    if constexpr (SWAP16) asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(p.a), "+v"(p.b));
-    else asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(p.a), "+v"(p.b));
-    return p;
-}
 // reductions over the four lanes that hold the same query column (lanes l, l ^ 16, l ^ 32, l ^ 48)
 __device__ __forceinline__ float column_max(float v) {
     const LanePair p = lane_pair<true>(v);

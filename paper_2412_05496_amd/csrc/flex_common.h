@@ -64,13 +64,28 @@ __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_lo
 // Exchange a value with the lane 32 away (the other half of the wave).
 __device__ __forceinline__ float swap_halves(float v) { return __shfl_xor(v, 32, 64); }
 
-// The larger of this lane's value and that of the lane 32 away: one exchange in the vector unit (a shuffle goes
-// through LDS, and takes six instructions to address).
-__device__ __forceinline__ float max_halves(float v) {
+// The values of the two lanes l, l ^ 16 (SWAP16) or l, l ^ 32 in one order or the other, so that a commutative
+// operation on the pair is a reduction over it: one exchange in the vector unit (a shuffle goes through LDS, and
+// takes six instructions to address).
+struct LanePair {
+    float a, b;
+};
+template <bool SWAP16>
+__device__ __forceinline__ LanePair lane_pair(float v) {
     const unsigned u = __builtin_bit_cast(unsigned, v);
-    const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    if constexpr (SWAP16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return {__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])};
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return {__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])};
+    }
+}
+// The larger of this lane's value and that of the lane 32 away.
+__device__ __forceinline__ float max_halves(float v) {
+    const LanePair p = lane_pair<false>(v);
     float m;        // (not fmaxf, which first puts both through a max of their own to quieten NaNs)
-    asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"((unsigned)r[0]), "v"((unsigned)r[1]));
+    asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(p.a), "v"(p.b));
     return m;
 }
 
