@@ -53,16 +53,16 @@ struct DecodeArgs {
     float* part_O;    // [nseq, Hq, max_splits, D]
     float* part_ml;   // [nseq, Hq, max_splits, 2]  (running max in base 2, sum)
     bf16* O;
-    bool o_wide;      // O is 16-byte aligned; otherwise it is written element by element
     float* LSE;
 };
 
-// 2 N consecutive elements of O in one store where O is aligned for it (wide); O itself needs no more than the
-// alignment of its elements.
-template <int N>
-__device__ __forceinline__ void store_o(bf16* p, const uint32_t (&v)[N], bool wide) {
+// 2 N consecutive elements of O.  O needs no more than the alignment of its elements (ANY); it is written in one store
+// where it is aligned for it.
+template <bool ANY, int N>
+__device__ __forceinline__ void store_o(const DecodeArgs& a, int64_t at, const uint32_t (&v)[N]) {
     typedef uint32_t vec __attribute__((ext_vector_type(N)));
-    if (wide) {
+    bf16* p = a.O + at;
+    if (!ANY || ((uintptr_t)a.O & 15) == 0) {
         vec x;
 #pragma unroll
         for (int i = 0; i < N; ++i) x[i] = v[i];
@@ -103,7 +103,7 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
-template <int D, uint32_t SCORE>
+template <int D, uint32_t SCORE, bool ANY_O>
 __device__ __forceinline__ void decode_split(const DecodeArgs& a, int tid, int unit, int split) {
     constexpr int DC = D / 8;                  // 16-byte chunks per row
     constexpr int RPI = 64 / DC;               // rows per wave instruction
@@ -129,7 +129,7 @@ __device__ __forceinline__ void decode_split(const DecodeArgs& a, int tid, int u
     if (tok_begin >= ctx || tok_begin + a.split_len <= kv_lo) {         // (uniform over the workgroup)
         if (ctx == 0 && split == 0) {
             for (int i = tid; i < a.G * D / 8; i += kDecWaves * 64)
-                store_o<4>(a.O + ((int64_t)b * a.Hq + hkv * a.G) * D + i * 8, {0u, 0u, 0u, 0u}, a.o_wide);
+                store_o<ANY_O, 4>(a, ((int64_t)b * a.Hq + hkv * a.G) * D + i * 8, {0u, 0u, 0u, 0u});
             if (a.LSE && tid < a.G) a.LSE[(int64_t)b * a.Hq + hkv * a.G + tid] = -INFINITY;
         }
         return;
@@ -303,7 +303,7 @@ __device__ __forceinline__ void decode_split(const DecodeArgs& a, int tid, int u
         const int64_t head = (int64_t)b * a.Hq + hkv * a.G + g;
         if (only) {
             const float inv = L > 0.0f ? 1.0f / L : 0.0f;
-            store_o<2>(a.O + head * D + d, {pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv)}, a.o_wide);
+            store_o<ANY_O, 2>(a, head * D + d, {pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv)});
             if (d == 0 && a.LSE) a.LSE[head] = (m + fast_log2(L)) * kLn2;
         } else {
             const int64_t item = head * a.max_splits + split;
@@ -313,16 +313,17 @@ __device__ __forceinline__ void decode_split(const DecodeArgs& a, int tid, int u
     }
 }
 
-// One workgroup per (sequence, KV head) and split; MANY: per (sequence, KV head) and gridDim.y-th splits.
-template <int D, uint32_t SCORE, bool MANY>
+// One workgroup per (sequence, KV head) and split.  GENERAL: per (sequence, KV head) and every gridDim.y-th split, and O
+// at any element address (a kernel of its own because either costs a small call one to ten percent).
+template <int D, uint32_t SCORE, bool GENERAL>
 __global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_split_kernel(const DecodeArgs a) {
-    if constexpr (!MANY) {
-        decode_split<D, SCORE>(a, threadIdx.x, blockIdx.x, blockIdx.y);
+    if constexpr (!GENERAL) {
+        decode_split<D, SCORE, false>(a, threadIdx.x, blockIdx.x, blockIdx.y);
     } else {
         for (int split = blockIdx.y; split < a.max_splits; split += gridDim.y) {
             int tid = threadIdx.x, unit = blockIdx.x;
             asm volatile("" : "+v"(tid), "+s"(unit));       // (or all that depends on them is worked out ahead of the first split's end)
-            decode_split<D, SCORE>(a, tid, unit, split);
+            decode_split<D, SCORE, true>(a, tid, unit, split);
             if ((split + (int)gridDim.y) * (int64_t)a.split_len >= ldc(a.ctx_lens + unit / a.Hkv)) break;
             __syncthreads();                                // the merge has read LDS
         }
@@ -333,7 +334,7 @@ __global__ __launch_bounds__(kDecWaves * 64, (D == 64 ? 4 : 2)) void decode_spli
 // The rows of the splits are read side by side by 256 threads (8 rows at a time for D = 128), the first of
 // them before the maximum is known: what bounds this kernel is the latency of its loads, of which a wave
 // that walks the splits one after the other pays one per split.
-template <int D>
+template <int D, bool ANY_O>
 __global__ __launch_bounds__(kDecWaves * 64) void decode_combine_kernel(const DecodeArgs a) {
     constexpr int LPR = D / 4, ROWS = kDecWaves * 64 / LPR, PRE = 4;   // lanes per row, rows side by side
     __shared__ float s_o[ROWS][D + 4];
@@ -380,7 +381,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_combine_kernel(const De
             lt += s_l[r];
         }
         const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
-        store_o<1>(a.O + head * D + 2 * tid, {pack_bf16(o0 * inv, o1 * inv)}, a.o_wide);
+        store_o<ANY_O, 1>(a, head * D + 2 * tid, {pack_bf16(o0 * inv, o1 * inv)});
         if (tid == 0 && a.LSE) a.LSE[head] = (m + fast_log2(lt)) * kLn2;
     }
 }
@@ -416,12 +417,12 @@ static int launch_decode(const DecodeArgs& a, uint32_t score_id, hipStream_t st)
     // sequences of 512 tokens, 8 KV heads, D = 64 / 128: 95.9 / 143.8 -> 17.6 / 37.5).
     constexpr int kMaxGroups = 16384;
     const int units = a.nseq * a.Hkv, room = (kMaxGroups + units - 1) / units;
-    const bool many = a.max_splits > room;
-    const dim3 grid((unsigned)units, (unsigned)(many ? room : a.max_splits));
+    const bool aligned = ((uintptr_t)a.O & 15) == 0, general = a.max_splits > room || !aligned;
+    const dim3 grid((unsigned)units, (unsigned)(a.max_splits < room ? a.max_splits : room));
     switch (score_id) {
 #define CASE(S)                                                                                           \
     case S:                                                                                               \
-        if (many) hipLaunchKernelGGL((decode_split_kernel<D, S, true>), grid, dim3(kDecWaves * 64), 0, st, a);  \
+        if (general) hipLaunchKernelGGL((decode_split_kernel<D, S, true>), grid, dim3(kDecWaves * 64), 0, st, a);  \
         else hipLaunchKernelGGL((decode_split_kernel<D, S, false>), grid, dim3(kDecWaves * 64), 0, st, a);      \
         break;
         CASE(FLEXATTN_SCORE_IDENTITY)
@@ -431,8 +432,9 @@ static int launch_decode(const DecodeArgs& a, uint32_t score_id, hipStream_t st)
 #undef CASE
         default: return FLEXATTN_ERR_UNSUPPORTED;
     }
-    if (a.max_splits > 1)
-        hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)(a.nseq * a.Hq)), dim3(kDecWaves * 64), 0, st, a);
+    const dim3 heads((unsigned)(a.nseq * a.Hq));
+    if (a.max_splits > 1 && aligned) hipLaunchKernelGGL((decode_combine_kernel<D, false>), heads, dim3(kDecWaves * 64), 0, st, a);
+    else if (a.max_splits > 1) hipLaunchKernelGGL((decode_combine_kernel<D, true>), heads, dim3(kDecWaves * 64), 0, st, a);
     return FLEXATTN_OK;
 }
 
@@ -534,7 +536,6 @@ extern "C" int flexattn_paged_decode(const flexattn_decode_dims* d, const void* 
     a.part_O = (float*)ws;
     a.part_ml = (float*)ws + items * d->D;
     a.O = (bf16*)O; a.LSE = LSE;
-    a.o_wide = ((uintptr_t)O & 15) == 0;
     rc = d->D == 128 ? launch_decode<128>(a, score_id, (hipStream_t)stream)
                      : launch_decode<64>(a, score_id, (hipStream_t)stream);
     if (rc != FLEXATTN_OK) return rc;
