@@ -68,24 +68,40 @@ constexpr bool fwd_plain() {
 // The same at D = 128, where 64-key tiles of K and V leave LDS for two workgroups: units of 32 keys in a ring of
 // three take 48 KiB, three workgroups of 168 registers.  The chip's power limit eats most of the gain on long
 // dense rows, so the rule is by what was measured (us, pipelined -> units; D = 128, Bq = 128):
-//   rows of few or PARTIAL tiles, and biases: window of 1024, S = 5000 209 -> 191, with a soft-cap 232 -> 200;
-//   documents, S = 2048 358 -> 335; ALiBi, S = 3000 572 -> 544, S = 8192 778 -> 768; relative bias, S = 32768
-//   5210 -> 5020; neighborhood, 128 x 128, K = 13 582 -> 531;
-//   otherwise by length: causal S = 1024 558 -> 516, S = 1536 331 -> 321, no mask S = 1536 454 -> 451, S = 2048
-//   571 -> 584, causal S = 8192 592 -> 626;
+//   documents, canvases and biases always: documents, S = 2048 200 -> 184, one of S = 8192 1092 -> 1063; ALiBi,
+//   S = 1000 254 -> 246, S = 8192 1325 -> 1313; relative bias, S = 32768 5166 -> 4876; neighborhood, 128 x 128, K = 13
+//   582 -> 502, 64 x 64, K = 63 1360 -> 1349;
+//   otherwise by length: causal S = 1024 233 -> 224, no mask 317 -> 319, S = 1536 331 -> 329, S = 2048 561 -> 570, causal
+//   S = 8192 592 -> 626 (four sequences of 16 heads: 1099 -> 1105);
 //   never with a relative bias under a soft-cap: its table no longer lets three in (325 -> 345);
-//   and only where the workgroups are three rounds of the chip (a round, for the even rows of a window): with
-//   fewer there is nothing to put beside a workgroup, and each is slower by itself (one sequence, S = 4096,
-//   ALiBi, 4 heads 108 -> 127, 24 heads 172 -> 215; window of 1024, 16 heads 48.5 -> 49.3, 24 heads 79 -> 65).
-enum class FwdUnits { kNever, kAlways, kShort };
-constexpr int kUnitsMaxKeys = 1536, kUnitsMinGroups = 9 * 256, kUnitsMinGroupsWindow = 3 * 256;
+//   and only where the workgroups are three rounds of the chip: with fewer there is nothing to put beside a
+//   workgroup, and each is slower by itself (one sequence, S = 4096, ALiBi, 4 heads 108 -> 127, 24 heads 172 -> 215).
+// Windows of at most half the keys have rows of one length, and the workgroups (with the idle ones of XCDs that have
+// a KV head fewer) go in rounds, of 768 with units and of 512 without: units where that is one round less, or where
+// there are many rounds (S = 4096, window of 1024; heads 16: 43.9 -> 45.3, 24: 71.1 -> 62.8, 32: 82.5 -> 95.2, 40: 105 -> 102,
+// 64: 154.4 -> 153.6; the same with a relative bias and a prefix, window of 512: 41.2 -> 45.9, 67.3 -> 57.4, 76.6 -> 90.3,
+// 100 -> 97, 147 -> 147; S = 5000, four sequences of 16 / 2 heads: 186 -> 171).  Longer windows go by length (window = S = 4096,
+// heads 24: 133 -> 159, 40: 203 -> 210; S = 8192, 40 heads: 710 -> 731).
+enum class FwdUnits { kNever, kAlways, kShort, kWindow };
+constexpr int kUnitsMaxKeys = 1536, kUnitsMinGroups = 9 * 256;
 template <int D, int NW, uint32_t MASK, uint32_t SCORE>
 constexpr FwdUnits fwd_units() {
-    constexpr uint32_t prims = (MASK | (MASK >> 8)) & 0xffu;
     constexpr bool cap = SCORE & FLEXATTN_SCORE_SOFTCAP, bias = SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS);
     if (D != 128 || NW != 4 || (cap && (SCORE & FLEXATTN_SCORE_REL_BIAS))) return FwdUnits::kNever;
-    if ((prims & (FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD)) || (bias && !cap)) return FwdUnits::kAlways;
+    if (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW)) return FwdUnits::kWindow;
+    if (mask_uses(MASK, FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD) || (bias && !cap)) return FwdUnits::kAlways;
     return FwdUnits::kShort;
+}
+// grid: the workgroups that are launched
+template <uint32_t MASK, uint32_t SCORE>
+bool units_pay(const FwdArgs& a, int64_t grid) {
+    constexpr FwdUnits rule = fwd_units<128, 4, MASK, SCORE>();
+    if constexpr (rule == FwdUnits::kNever) return false;
+    if constexpr (rule == FwdUnits::kWindow) {
+        const int64_t reach = (int64_t)a.p.window + (mask_uses(MASK, FLEXATTN_M_PREFIX) ? a.p.prefix_len : 0);
+        if (2 * reach <= a.kv_len) return (grid > 2 * 256 && grid <= 3 * 256) || grid >= 5 * 256;
+    }
+    return (rule == FwdUnits::kAlways || a.kv_len <= kUnitsMaxKeys) && (int64_t)a.B * a.Hq * a.NR >= kUnitsMinGroups;
 }
 // Waves per SIMD to compile for: what registers (512 per SIMD lane) and LDS admit.  The pipelined variants
 // with a relative-bias table would spill at three.
@@ -598,11 +614,8 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
     hipLaunchKernelGGL((fwd_kernel<DD, NW, MASK, SCORE, BOUNDED, PAGED>), dim3(grid), dim3(NW * 64), 0, st, a); \
     return FLEXATTN_OK;
     if (D == 128 && Bq == 128) {
-        constexpr FwdUnits units_rule = fwd_units<128, 4, MASK, SCORE>();
-        if constexpr (units_rule != FwdUnits::kNever) {
-            const int64_t groups = (int64_t)a.B * a.Hq * a.NR;
-            if ((units_rule == FwdUnits::kAlways || a.kv_len <= kUnitsMaxKeys) &&
-                groups >= (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) ? kUnitsMinGroupsWindow : kUnitsMinGroups)) {
+        if constexpr (fwd_units<128, 4, MASK, SCORE>() != FwdUnits::kNever) {
+            if (units_pay<MASK, SCORE>(a, grid)) {
                 hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, true>), dim3(grid), dim3(256), 0, st, a);
                 return FLEXATTN_OK;
             }

@@ -74,6 +74,39 @@ def test_paged_chunk_matches_oracle(case):
     hp.check_output(O, LSE, O_ref, LSE_ref)
 
 
+@pytest.mark.parametrize("mask,score", [("swa_causal", "identity"), ("causal", "alibi"), ("swa_causal", "softcap")])
+@pytest.mark.parametrize("page", [64, 128])
+def test_paged_chunk_with_many_workgroups(mask, score, page):
+    """D = 128 with enough workgroups for 32-key units: their tiles start inside a page.  97 copies of three sequences
+    (on the same pages), of which three are compared with the oracle and the others with them."""
+    import paper_2412_05496_amd as fa
+    dev, q_len, n = torch.device("cuda:0"), 250, 97
+    kv_lens = [700, 250, 431]
+    max_pages = (max(kv_lens) + page - 1) // page
+    wl = wlm.CFG5.scaled(name="prefill_units", B=3, Hq=4, Hkv=2, D=128, page_size=page, max_pages=max_pages, mask=mask, score=score,
+                         S=q_len, Bq=128, Bk=page, window=90, softcap=30.0, seed=3160)
+    inp = wlm.make_prefill_inputs(wl, kv_lens, q_len, slack_pages=3)
+
+    class Side:
+        doc_ids = rel_bias = None
+        slopes = wlm.alibi_slopes(4) if score == "alibi" else None
+    score_mod, mask_mod = hp.oracle_mods(wl, Side)
+    O_ref, LSE_ref = fo.paged_attention(inp.Q, inp.K_pool, inp.V_pool, inp.page_table, inp.kv_lens, inp.q_offsets,
+                                        score_mod, mask_mod, inp.scale)
+    mask_id, score_id, params, _ = hp.library_mods(wl, Side, dev)
+    params.q_offsets = inp.q_offsets.repeat(n).to(dev)
+    bm, phys_kv, phys_full, _ = build_and_convert(fa, dev, mask_id, params, 3 * n, q_len, max_pages * page, 128, page,
+                                                  inp.page_table.repeat(n, 1).to(dev), inp.K_pool.shape[0])
+    Q = inp.Q.repeat(n, 1, 1, 1).to(dev)
+    O = torch.full_like(Q, float("nan"))
+    LSE = torch.full(Q.shape[:3], float("nan"), dtype=torch.float32, device=dev)
+    fa.flexattn_paged_forward(Q, inp.K_pool.to(dev), inp.V_pool.to(dev), score_id, mask_id, params, bm, phys_kv,
+                              phys_full, inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    hp.check_output(O[:3], LSE[:3], O_ref, LSE_ref)
+    assert torch.equal(O, O[:3].repeat(n, 1, 1, 1)) and torch.equal(LSE, LSE[:3].repeat(n, 1, 1))
+
+
 def test_offset_conversion_in_the_contiguous_forward_and_backward():
     """q_offsets without paging: rows [off, off + Lq) of a longer causal problem, forward and backward."""
     import paper_2412_05496_amd as fa

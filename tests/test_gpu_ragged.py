@@ -114,3 +114,58 @@ def test_forward_d128_canvas_many_workgroups(w, h, k, layout, tile):
     torch.cuda.synchronize()
     hp.check_output(O[:1], LSE[:1], *fo.flex_attention(inp.Q, inp.K, inp.V, fo.Identity(), fo.neighborhood_mask(w, h, k, layout, tile), inp.scale))
     assert torch.equal(O, O[:1].expand_as(O)) and torch.equal(LSE, LSE[:1].expand_as(LSE))
+
+
+@pytest.mark.parametrize("groups", [512, 544, 768, 800, 1248, 1280])
+@pytest.mark.parametrize("mask,score,window", [("swa_causal", "identity", 100), ("swa_causal", "softcap", 200),
+                                               ("swa_causal_or_prefix", "rel_bias", 90)])
+def test_forward_d128_window_rounds(mask, score, window, groups):
+    """Both sides of the numbers of workgroups, and windows up to and above half of the keys, between which the window
+    masks change form at D = 128.  All sequences are the same (batch stride 0)."""
+    import paper_2412_05496_amd as fa
+    dev, S = torch.device("cuda:0"), 256
+    wl = wlm.CFG2.scaled(name="rounds", B=1, Hq=2, Hkv=1, S=S, mask=mask, score=score, window=window, prefix_len=38, rel_len=30, seed=3970)
+    inp = wlm.make_train_inputs(wl)
+    score_mod, mask_mod = hp.oracle_mods(wl, inp)
+    mask_id, score_id, params, _ = hp.library_mods(wl, inp, dev)
+    bm = fa.alloc_blockmask(1, 1, S, S, wl.Bq, wl.Bk, device=dev)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    B = groups // 4                 # (two heads of two row blocks each)
+    Q, K, V = (t.to(dev).expand(B, -1, -1, -1) for t in (inp.Q, inp.K, inp.V))
+    O = torch.full((B, 2, S, wl.D), float("nan"), dtype=torch.bfloat16, device=dev)
+    LSE = torch.full((B, 2, S), float("nan"), device=dev)
+    fa.flexattn_forward(Q, K, V, score_id, mask_id, params, bm, inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    hp.check_output(O[:1], LSE[:1], *fo.flex_attention(inp.Q, inp.K, inp.V, score_mod, mask_mod, inp.scale))
+    assert torch.equal(O, O[:1].expand_as(O)) and torch.equal(LSE, LSE[:1].expand_as(LSE))
+
+
+def many(t, n):
+    return t.repeat(n, *[1] * (t.dim() - 1))
+
+
+@pytest.mark.parametrize("mask,score", [("swa_causal", "identity"), ("causal", "alibi"), ("doc_causal", "identity"), ("swa_causal", "softcap")])
+@pytest.mark.parametrize("Bk", [64, 128])
+def test_forward_d128_many_workgroups_planes_and_offsets(mask, score, Bk):
+    """32-key units with a BlockMask plane per sequence, query offsets and two or four units to a block."""
+    import paper_2412_05496_amd as fa
+    dev, S, Lq, n = torch.device("cuda:0"), 500, 200, 97
+    wl = wlm.CFG2.scaled(name="units_planes", B=3, Hq=4, Hkv=2, S=S, Bk=Bk, mask=mask, score=score, window=70, doc_len_min=30,
+                         doc_len_max=200, seed=3980)
+    inp = wlm.make_train_inputs(wl)
+    off = torch.tensor([300, 111, 0], dtype=torch.int32)
+    score_mod, mask_mod = hp.oracle_mods(wl, inp)
+    score_mod, mask_mod = fo.QOffset(score_mod, off), fo.with_q_offset(mask_mod, off)
+    mask_id, score_id, params, _ = hp.library_mods(wl, inp, dev)
+    params.q_offsets = many(off, n).to(dev)
+    if params.doc_ids is not None:
+        params.doc_ids = many(params.doc_ids, n).contiguous()
+    bm = fa.alloc_blockmask(3 * n, 1, Lq, S, wl.Bq, Bk, device=dev)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    Q, K, V = (many(t, n).to(dev) for t in (inp.Q[:, :, :Lq].contiguous(), inp.K, inp.V))
+    O = torch.full_like(Q, float("nan"))
+    LSE = torch.full(Q.shape[:3], float("nan"), device=dev)
+    fa.flexattn_forward(Q, K, V, score_id, mask_id, params, bm, inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    hp.check_output(O[:3], LSE[:3], *fo.flex_attention(inp.Q[:, :, :Lq], inp.K, inp.V, score_mod, mask_mod, inp.scale))
+    assert torch.equal(O, many(O[:3], n)) and torch.equal(LSE, many(LSE[:3], n))
