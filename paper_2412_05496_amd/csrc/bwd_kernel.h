@@ -670,14 +670,14 @@ __device__ __forceinline__ float diagonal_sums(const f32x16& v, int half) {
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
 //
-// Hidden blocks are left out where the loads of the next tile need not be spread over the MFMAs of this one:
-// four waves at D = 64 (window of 1024, S = 5000: 130 -> 124 us; canvas 100 x 90, K = 9, row-major: 349 -> 290),
+// SKIP: hidden blocks are left out, which means not to spread the loads of the next tile over the MFMAs of this one.
+// Four waves at D = 64 (window of 1024, S = 5000: 130 -> 124 us; canvas 100 x 90, K = 9, row-major: 349 -> 290),
 // not with two (tiles of 8 x 8, K = 13: 348 -> 374) nor at D = 128.
 template <int D, int NW>
 constexpr bool dq_skips_hidden() {
     return D == 64 && NW == 4;
 }
-template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool CAPTURED = false>
+template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool CAPTURED = false, bool SKIP = dq_skips_hidden<D, NW>()>
 __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kernel(const BwdArgs a) {
     constexpr int Bq = NW * 32;
     constexpr int TILE = 64 * D;
@@ -687,7 +687,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     __shared__ float s_rel[ScoreMod<SCORE>::kRel ? kRelTableMax : 1]; // relative-bias row of the head (values)
     using Mask = PartialMask<MASK>;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? 64 : 4];   // tags of a PARTIAL tile's keys (even, odd)
-    __shared__ uint8_t s_hidden[Mask::kCanvas && dq_skips_hidden<D, NW>() ? kHiddenTiles : 1];           // CanvasBlocks::hidden_bits of the first tiles
+    __shared__ uint8_t s_hidden[Mask::kCanvas && SKIP ? kHiddenTiles : 1];           // CanvasBlocks::hidden_bits of the first tiles
 
     const int units = a.B * a.Hkv;
     const int id = blockIdx.x, xcd = id & 7, kk = id >> 3;
@@ -784,8 +784,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         for (int r = 0; r < 16; ++r) dq[db][r] = 0.0f;
 
     // a wave leaves out the blocks of 32 keys that the mask hides from all of its rows
-    constexpr bool kSkip = dq_skips_hidden<D, NW>();
-    if constexpr (kSkip && Mask::kCanvas) fill_hidden_tiles<NW>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, sub, a.Bk, row * Bq, tid);
+    if constexpr (SKIP && Mask::kCanvas) fill_hidden_tiles<NW>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, sub, a.Bk, row * Bq, tid);
     auto hidden_block = [&](int t, bool partial, int kv, int kvb) __attribute__((always_inline)) {
         if constexpr (Mask::kCanvas) return t < kHiddenTiles && ((__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (2 * w + kvb)) & 1);
         else return partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31);
@@ -814,12 +813,12 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         using L = WaveTileLoader<D, NW>;
         constexpr int NKS = D / 16, NDB = D / 32, PF = 4;
 
-        if constexpr (kSkip) {
+        if constexpr (SKIP) {
             if (ld) load_tiles(BUF ^ 1, kv0);
         }
         static_for<0, 2>([&](auto kvb_tag) {
             constexpr int kvb = decltype(kvb_tag)::value;
-            if constexpr (kSkip) {
+            if constexpr (SKIP) {
                 if (hidden_block(t, partial, kv0_cur + 32 * kvb, kvb)) return;
             }
             // S^T = K Q^T and dP^T = V dO^T for 32 keys; operand fragments read PF MFMAs ahead
@@ -840,7 +839,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
                     if constexpr (m + PF < NM) fr[m + PF] = frag(m + PF);
                     if (m & 1) dpacc = mfma32(fr[m], dof[m >> 1], dpacc);
                     else sacc = mfma32(fr[m], qf[m >> 1], sacc);
-                    if constexpr (kvb == 0 && !kSkip) {
+                    if constexpr (kvb == 0 && !SKIP) {
                         static_for<0, NP>([&](auto p_tag) {
                             constexpr int p = decltype(p_tag)::value;
                             if constexpr (p * NM / NP == m) {
@@ -984,6 +983,23 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         }
 }
 
+// dQ at D = 64 with four waves: whether leaving hidden blocks out pays.  The test between the two blocks of a tile
+// keeps their work apart, which shows where at most two workgroups share a CU: masks that hide little more than a
+// diagonal are left out only beyond that (us, computed whole -> left out, causal: one sequence, S = 4096, 8 heads 58.8 ->
+// 64.1; S = 8192, 8 heads 131 -> 136; S = 2048, 2 x 16 heads 47.1 -> 47.2, 4 x 16 75.6 -> 75.9; S = 4096, 64 heads
+// 227.8 -> 222.9; S = 1024, 64 x 16 heads 298.6 -> 285.8).
+template <uint32_t MASK, uint32_t SCORE>
+void launch_dq64(const BwdArgs& a, unsigned grid, hipStream_t st) {
+    constexpr bool often = mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
+    if constexpr (!often) {
+        if (grid <= 2 * 256) {
+            hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, false>), dim3(grid), dim3(256), 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
+}
+
 constexpr uint32_t kBwdStageCaptured = 8u;   // internal: the captured-tensor sums instead of dQ
 
 template <uint32_t MASK, uint32_t SCORE>
@@ -1003,7 +1019,7 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
         if (q && a.Bq == 64) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, a);
     } else {
         if (kv) hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, a);
-        if (q && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, a);
+        if (q && a.Bq == 128) launch_dq64<MASK, SCORE>(a, grid_q, st);
         if (q && a.Bq == 64) hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, a);
     }
     if (stages & kBwdStageCaptured) {

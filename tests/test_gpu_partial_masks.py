@@ -72,6 +72,34 @@ def test_blocks_hidden_from_a_wave(mask, score, S, Bq, Bk, Hkv, extra_keys):
             hp.check_grad(name, got, r)
 
 
+@pytest.mark.parametrize("heads", [512, 520])
+@pytest.mark.parametrize("mask,score", [("causal", "identity"), ("prefix_lm", "identity"), ("causal", "alibi_softcap"), ("none", "identity")])
+def test_dq_with_and_without_hidden_blocks(mask, score, heads):
+    """D = 64 dQ on both sides of the number of workgroups from which hidden blocks are left out.  The heads are the
+    same (stride 0): one is compared with the oracle and the others with it."""
+    import paper_2412_05496_amd as fa
+    dev, S = torch.device(DEV), 100
+    wl = wlm.CFG1.scaled(name="dq_sides", B=1, Hq=1, Hkv=1, S=S, D=64, Bq=128, Bk=64, mask=mask, score=score, prefix_len=70,
+                         softcap=20.0, seed=4350)
+    inp = wlm.make_train_inputs(wl, with_dO=True)
+    score_mod, mask_mod = hp.oracle_mods(wl, inp)
+    mask_id, score_id, params, _ = hp.library_mods(wl, inp, dev)
+    if params.alibi_bias is not None:
+        params.alibi_bias = params.alibi_bias.repeat(heads)
+    bm = fa.alloc_blockmask(1, 1, S, S, 128, 64, device=dev)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    Q, K, V, dO = (t.to(dev).expand(1, heads, S, 64) for t in (inp.Q, inp.K, inp.V, inp.dO))
+    O, LSE = torch.empty(Q.shape, dtype=torch.bfloat16, device=dev), torch.empty(Q.shape[:3], device=dev)
+    fa.flexattn_forward(Q, K, V, score_id, mask_id, params, bm, inp.scale, O, LSE)
+    dQ, dK, dV = (torch.full(Q.shape, float("nan"), dtype=torch.bfloat16, device=dev) for _ in range(3))
+    fa.flexattn_backward(Q, K, V, O, dO, LSE, score_id, mask_id, params, bm, inp.scale, dQ, dK, dV)
+    torch.cuda.synchronize()
+    ref = fo.flex_attention_backward(inp.Q, inp.K, inp.V, inp.dO, score_mod, mask_mod, inp.scale)
+    for name, got, r in zip(("dQ", "dK", "dV"), (dQ, dK, dV), ref):
+        hp.check_grad(name, got[:, :1], r)
+        assert torch.equal(got, got[:, :1].expand_as(got)), name
+
+
 @pytest.mark.parametrize("w,h,k,layout,tile", [(200, 1, 1, "row_major", 0), (1, 130, 1, "row_major", 0),
                                                (15, 15, 15, "row_major", 0), (17, 9, 9, "row_major", 0),
                                                (24, 8, 7, "tiled", 4), (16, 16, 3, "morton", 0)])
