@@ -130,7 +130,7 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const BwdArgs a) {
 // issued at the top of step v.  Two barriers per step: after the exchange writes, and at the end
 // (exchange buffer and ring slot free again, next tiles landed).
 //
-// kOwn (D = 64): there both accumulators fit a wave, so every wave keeps dV^T and dK^T of its own 32 rows x
+// OWN (D = 64): there both accumulators fit a wave, so every wave keeps dV^T and dK^T of its own 32 rows x
 // 32 keys per step: no exchange, no selects between P and dS, one barrier a step, and the two waves of the
 // same keys add their halves up once at the end.  V waits in LDS instead of registers (16 of them), which
 // is what keeps three workgroups on a CU: with V in registers the kernel spills, and two workgroups are 20 %
@@ -166,16 +166,15 @@ constexpr bool dkdv_own_rows() {
     constexpr bool biased_cap = (SCORE & FLEXATTN_SCORE_SOFTCAP) && (SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS));
     return D == 64 && !PartialMask<MASK>::kCanvas && !biased_cap;
 }
-template <int D, uint32_t MASK, uint32_t SCORE>
+template <int D, uint32_t MASK, uint32_t SCORE, bool OWN = dkdv_own_rows<D, MASK, SCORE>()>
 __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(const BwdArgs a) {
     constexpr int TQ = 64;                         // query rows per step
     constexpr int TILE = TQ * D;                   // elements per LDS tile
     constexpr int NKS = D / 16, NDB = D / 32;
-    constexpr bool kOwn = dkdv_own_rows<D, MASK, SCORE>();
     constexpr bool kCut = D == 128 && PartialMask<MASK>::kCanvas;     // leaves hidden steps and blocks out
     using Loader = WaveTileLoader<D, 4>;
-    __shared__ __attribute__((aligned(1024))) bf16 smem[(kOwn ? 5 : 4) * TILE];   // 2 x (Q tile, dO tile); kOwn: V tile
-    __shared__ __attribute__((aligned(1024))) u32x4 s_xchg[kOwn ? 1 : 4][2][64];   // [wave][16-row slice][lane]
+    __shared__ __attribute__((aligned(1024))) bf16 smem[(OWN ? 5 : 4) * TILE];   // 2 x (Q tile, dO tile); OWN: V tile
+    __shared__ __attribute__((aligned(1024))) u32x4 s_xchg[OWN ? 1 : 4][2][64];   // [wave][16-row slice][lane]
     __shared__ __attribute__((aligned(256))) float s_row[2][2][TQ];           // [slot][rc | -delta][row]
     constexpr int kListMax = 512;
     __shared__ int s_steps[kListMax + 2];          // the walk of the current head, see below
@@ -212,7 +211,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     const int kv_lane = kv0 + 32 * kb + l32;
 
     // K, V fragments of this wave's 32 keys: B operands (column = key, k-slots = dims)
-    bf16x8 kf[NKS], vf[kOwn ? 1 : NKS];
+    bf16x8 kf[NKS], vf[OWN ? 1 : NKS];
     {
         // keys past kv_len (last tile of a length that is no multiple of 64) take a copy of the last
         // real key; the mask hides them and they are never stored
@@ -222,18 +221,18 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
             kf[ks] = *(const bf16x8*)(kp + ks * 16);
-            if constexpr (!kOwn) vf[ks] = *(const bf16x8*)(vp + ks * 16);
+            if constexpr (!OWN) vf[ks] = *(const bf16x8*)(vp + ks * 16);
         }
     }
 
-    // x = 0: dV^T, x = 1: dK^T (row = dim, column = key); kOwn: dV^T here, dK^T in acc_k
-    f32x16 acc[NDB], acc_k[kOwn ? NDB : 1];
+    // x = 0: dV^T, x = 1: dK^T (row = dim, column = key); OWN: dV^T here, dK^T in acc_k
+    f32x16 acc[NDB], acc_k[OWN ? NDB : 1];
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             acc[db][r] = 0.0f;
-            if constexpr (kOwn) acc_k[db][r] = 0.0f;
+            if constexpr (OWN) acc_k[db][r] = 0.0f;
         }
 
     const int sub = a.Bq / TQ;          // steps per BlockMask row block (1 or 2)
@@ -246,20 +245,20 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     const int q_row_bytes = (int)a.q_ss * 2, do_row_bytes = (int)a.do_ss * 2;
     // scores: this wave's 32 rows of the Q tile (the dO tile is one tile further)
     const RowReader<D> row_reader(l32, half, ring + x * 32 * D * 2);
-    // kOwn: V's 64 rows wait in LDS (rows past kv_len as zeros), this wave's keys at v_lds beside row_reader's offsets
+    // OWN: V's 64 rows wait in LDS (rows past kv_len as zeros), this wave's keys at v_lds beside row_reader's offsets
     const uint32_t v_lds = (uint32_t)(4 * TILE + (kb - x) * 32 * D) * 2u;
-    if constexpr (kOwn) {
+    if constexpr (OWN) {
         const Loader v_loader(a.v_ss, w, lane);
         v_loader.start(make_rsrc(a.V + b * a.v_sb + hkv * a.v_sh, (uint32_t)((a.kv_len - 1) * a.v_ss + D) * 2u),
                        ring + 4 * TILE * 2, kv0 * (int)a.v_ss * 2);     // (awaited with the first step's tiles)
     }
     // outputs: the tile this wave contracts with (x = 0: dO, x = 1: Q), its own rows first, then
     // its partner's
-    // (kOwn: its own rows of both tiles, dO one tile behind Q)
-    const uint32_t out_tile = ring + (x || kOwn ? 0 : TILE * 2);
+    // (OWN: its own rows of both tiles, dO one tile behind Q)
+    const uint32_t out_tile = ring + (x || OWN ? 0 : TILE * 2);
     const TrReader<D> tr_own(lane, out_tile + x * 32 * D * 2), tr_other(lane, out_tile + (1 - x) * 32 * D * 2);
     const uint32_t row_lds = lds_addr(&s_row[0][0][0]) + (32 * x + 4 * half) * 4;
-    const uint32_t xchg_mine = lds_addr(&s_xchg[kOwn ? 0 : w][0][lane]), xchg_theirs = lds_addr(&s_xchg[kOwn ? 0 : w ^ 2][0][lane]);
+    const uint32_t xchg_mine = lds_addr(&s_xchg[OWN ? 0 : w][0][lane]), xchg_theirs = lds_addr(&s_xchg[OWN ? 0 : w ^ 2][0][lane]);
     const int q_off = q_offset_of(a.p, b);
     const Mask mask(a.p, b, a.kv_len);
     uint32_t k_tag = 0;
@@ -440,7 +439,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 // a block that the mask hides from all of its rows adds nothing (zeros in the stored dS)
                 bool hid = false;
                 if constexpr (kCut) hid = hid_of[SLOT];
-                else if constexpr (kOwn) hid = part_of[SLOT] && mask.hidden(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb, kv0 + 32 * kb + 31);
+                else if constexpr (OWN) hid = part_of[SLOT] && mask.hidden(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb, kv0 + 32 * kb + 31);
                 // scores
                 f32x4 nd[4], rcv4[4];
                 read_rows(SLOT, 1, nd);
@@ -451,7 +450,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                     dpacc[r] = nd[r >> 2][r & 3];    // dP - delta comes out of the accumulation
                 }
                 {   // operand fragments are read PF MFMAs ahead of their use
-                    constexpr int NM = 2 * NKS, PF = kOwn ? 2 : 4;
+                    constexpr int NM = 2 * NKS, PF = OWN ? 2 : 4;
                     auto frag = [&](int m) { return row_reader.read((m & 1) ? do_cur : q_cur, 0, m >> 1); };
                     bf16x8 fr[NM], vr[NKS];
 #pragma unroll
@@ -459,8 +458,8 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                     static_for<0, NM>([&](auto m_tag) {
                         constexpr int m = decltype(m_tag)::value;
                         if constexpr (m + PF < NM) fr[m + PF] = frag(m + PF);
-                        if constexpr (kOwn && !(m & 1)) vr[m >> 1] = row_reader.read(v_lds, 0, m >> 1);
-                        if (m & 1) dpacc = mfma32(fr[m], kOwn ? vr[m >> 1] : vf[kOwn ? 0 : m >> 1], dpacc);
+                        if constexpr (OWN && !(m & 1)) vr[m >> 1] = row_reader.read(v_lds, 0, m >> 1);
+                        if (m & 1) dpacc = mfma32(fr[m], OWN ? vr[m >> 1] : vf[OWN ? 0 : m >> 1], dpacc);
                         else sacc = mfma32(fr[m], kf[m >> 1], sacc);
                         static_for<0, kLoads>([&](auto piece_tag) {
                             if constexpr (decltype(piece_tag)::value * NM / kLoads == m) load_piece(ld_slot, piece_tag);
@@ -468,7 +467,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                         __builtin_amdgcn_sched_barrier(0);
                     });
                 }
-                if constexpr (!kOwn) read_rows(SLOT, 0, rcv4);
+                if constexpr (!OWN) read_rows(SLOT, 0, rcv4);
                 // relative bias: one value for the whole 32 x 32 block unless it lies near the diagonal
                 float rel_uni;
                 const bool rel_is_uni = smod.rel_uniform(q_off + q_first - (kv0 + 32 * kb + 31),
@@ -491,7 +490,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                         auto rel = [&](int r) __attribute__((always_inline)) {
                             return kNeedsPos ? RelPos(dq0, abase, 8 * (r >> 2) + (r & 3)) : RelPos(0);
                         };
-                        if constexpr (kOwn) {           // (one quad of row constants at a time: there are no registers for four)
+                        if constexpr (OWN) {           // (one quad of row constants at a time: there are no registers for four)
                             rcv4[c4] = read_row4(SLOT, 0, c4);
                         }
                         const RelPos dqk[4] = {rel(4 * c4), rel(4 * c4 + 1), rel(4 * c4 + 2), rel(4 * c4 + 3)};
@@ -527,7 +526,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 const bool stored = a.ds_store && !(kCut && hid);
                 if (stored) store_ds(u_of[SLOT], dsk[0], dsk[1]);
                 --u_step;
-                if constexpr (kOwn) {
+                if constexpr (OWN) {
                     // outputs: dV^T += dO^T P and dK^T += Q^T dS over this wave's own 32 rows
                     if (!hid) {
                         constexpr int NM = 4 * NDB, PF = 2;       // MFMAs: [slice c][block db][dV, dK]
@@ -593,9 +592,9 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
         }
     }
 
-    // ---- kOwn: the two waves of the same keys add up, the x = 0 wave dV^T, the x = 1 wave dK^T (the ring is
+    // ---- OWN: the two waves of the same keys add up, the x = 0 wave dV^T, the x = 1 wave dK^T (the ring is
     // free: the last step ended with a barrier)
-    if constexpr (kOwn) {
+    if constexpr (OWN) {
         wait_vmem();        // (a column without a step has V's load still under way, and must not end before it)
         f32x4* give = (f32x4*)smem + w * (NDB * 4 * 64) + lane;
         const f32x4* take = (const f32x4*)smem + (w ^ 2) * (NDB * 4 * 64) + lane;
@@ -988,6 +987,36 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
 // diagonal are left out only beyond that (us, computed whole -> left out, causal: one sequence, S = 4096, 8 heads 58.8 ->
 // 64.1; S = 8192, 8 heads 131 -> 136; S = 2048, 2 x 16 heads 47.1 -> 47.2, 4 x 16 75.6 -> 75.9; S = 4096, 64 heads
 // 227.8 -> 222.9; S = 1024, 64 x 16 heads 298.6 -> 285.8).
+// dK/dV at D = 64: own rows, but for launches that are as long as their longest column of blocks, where a workgroup is
+// alone on its CU most of the time: there the exchange is faster, whose operands are read further ahead.  They are
+// told by what the columns' steps make of 768 workgroups (three per CU) beside the longest column: a third of it (270 of
+// 768 for a mask whose columns are as long as the longest).  Windows and documents have columns of about one length and
+// hidden blocks to leave out, a soft-cap more vector work than the operands' reads take.
+// us, exchange -> own rows: causal, S = 1024, 8 heads 16.8 -> 18.7; S = 4096, 4 heads 59.0 -> 61.6, 8 heads 57.7 -> 59.8, 32 / 4
+// heads 433 -> 457; S = 2048, 16 heads 38.7 -> 38.1, 32 heads 56.5 -> 54.3; no mask, S = 1024, 8 heads 16.9 -> 17.9, S = 4096, 8 heads
+// 78.2 -> 76.7; window 512 or prefix 128, S = 8192, 16 heads 163 -> 170, S = 2048, 32 heads 55.5 -> 53.8; causal with a soft-cap,
+// S = 4096, 4 heads 74.5 -> 70.2.
+template <uint32_t MASK>
+bool own_rows_pay(const BwdArgs& a, unsigned grid) {
+    const float longest = a.q_len / 64.0f;          // steps
+    float mean = MASK == FLEXATTN_MASK_NONE ? longest : 0.5f * longest;
+    if (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW))
+        mean = fminf(longest, a.p.window / 64.0f + 2.0f + longest * a.p.prefix_len / a.kv_len);
+    return grid * mean > 270.0f * longest;
+}
+template <uint32_t MASK, uint32_t SCORE>
+void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
+    constexpr bool even = mask_uses(MASK, FLEXATTN_M_DOCUMENT) ||
+                          (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) && !mask_uses(MASK, FLEXATTN_M_PREFIX));
+    if constexpr (dkdv_own_rows<64, MASK, SCORE>() && !even && !(SCORE & FLEXATTN_SCORE_SOFTCAP)) {
+        if (!own_rows_pay<MASK>(a, grid)) {
+            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false>), dim3(grid), dim3(256), 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
+}
+
 template <uint32_t MASK, uint32_t SCORE>
 void launch_dq64(const BwdArgs& a, unsigned grid, hipStream_t st) {
     constexpr bool often = mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
@@ -1018,7 +1047,7 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
         if (q && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, a);
         if (q && a.Bq == 64) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, a);
     } else {
-        if (kv) hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, a);
+        if (kv) launch_dkdv64<MASK, SCORE>(a, grid_kv, st);
         if (q && a.Bq == 128) launch_dq64<MASK, SCORE>(a, grid_q, st);
         if (q && a.Bq == 64) hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, a);
     }

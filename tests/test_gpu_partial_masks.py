@@ -70,22 +70,39 @@ def test_blocks_hidden_from_a_wave(mask, score, S, Bq, Bk, Hkv, extra_keys):
         grads = hp.run_backward(wl, inp, dev, O, LSE, bm, (mask_id, score_id, params, Q, K, V), stored=stored)
         for name, got, r in zip(("dQ", "dK", "dV"), grads, ref):
             hp.check_grad(name, got, r)
+        # 300 copies (batch stride 0): the forms for many workgroups
+        n, hq = 300, Q.shape[1]
+        Qn, Kn, Vn, On, dOn = (t.to(dev).expand(n, -1, -1, -1) for t in (Q, K, V, O, inp.dO))
+        outs = [torch.full(t.shape, float("nan"), dtype=torch.bfloat16, device=dev) for t in (Qn, Kn, Vn)]
+        args = (Qn, Kn, Vn, On, dOn, LSE.expand(n, hq, -1).contiguous(), score_id, mask_id, params, bm, inp.scale, *outs)
+        if stored:
+            fa.flexattn_backward_stored(*args, hp.nonempty_blocks(bm))
+        else:
+            fa.flexattn_backward(*args)
+        torch.cuda.synchronize()
+        for name, got, r in zip(("dQ", "dK", "dV"), outs, ref):
+            hp.check_grad(name, got[:1], r)
+            assert torch.equal(got, got[:1].expand_as(got)), name
 
 
 @pytest.mark.parametrize("heads", [512, 520])
-@pytest.mark.parametrize("mask,score", [("causal", "identity"), ("prefix_lm", "identity"), ("causal", "alibi_softcap"), ("none", "identity")])
-def test_dq_with_and_without_hidden_blocks(mask, score, heads):
-    """D = 64 dQ on both sides of the number of workgroups from which hidden blocks are left out.  The heads are the
-    same (stride 0): one is compared with the oracle and the others with it."""
+@pytest.mark.parametrize("mask,score", [("causal", "identity"), ("prefix_lm", "identity"), ("causal", "alibi_softcap"), ("none", "identity"),
+                                        ("swa_causal_or_prefix", "rel_bias")])
+def test_backward_d64_few_and_many_workgroups(mask, score, heads):
+    """D = 64 gradients on both sides of the number of workgroups from which dQ leaves hidden blocks out (the one-head tests
+    above take the forms of dK/dV and dQ for few workgroups).  The heads are the same (stride 0): one is compared with the
+    oracle and the others with it."""
     import paper_2412_05496_amd as fa
     dev, S = torch.device(DEV), 100
     wl = wlm.CFG1.scaled(name="dq_sides", B=1, Hq=1, Hkv=1, S=S, D=64, Bq=128, Bk=64, mask=mask, score=score, prefix_len=70,
-                         softcap=20.0, seed=4350)
+                         window=40, softcap=20.0, rel_len=20, seed=4350)
     inp = wlm.make_train_inputs(wl, with_dO=True)
     score_mod, mask_mod = hp.oracle_mods(wl, inp)
     mask_id, score_id, params, _ = hp.library_mods(wl, inp, dev)
     if params.alibi_bias is not None:
         params.alibi_bias = params.alibi_bias.repeat(heads)
+    if params.rel_bias is not None:
+        params.rel_bias = params.rel_bias.repeat(heads, 1)
     bm = fa.alloc_blockmask(1, 1, S, S, 128, 64, device=dev)
     fa.flexattn_blockmask_build(mask_id, params, bm)
     Q, K, V, dO = (t.to(dev).expand(1, heads, S, 64) for t in (inp.Q, inp.K, inp.V, inp.dO))
