@@ -475,7 +475,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 typename Mask::Bits bits = {};
                 if (partial) {
                     bits = mask.key_bits(kv_lane, q_off + q_first + 4 * half);
-                    if constexpr (Mask::kDoc) Mask::match_documents(bits, s_tag[SLOT][32 * x + l32], k_tag, half);
+                    if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[SLOT][32 * x], k_tag, l32, half, false);
                 }
                 u32x4 pk[2] = {}, dsk[2] = {};
                 if (!hid) {
@@ -747,6 +747,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     const int q_pos = q_ld + q_offset_of(a.p, b);   // as the mods see it
     const Mask mask(a.p, b, a.kv_len);
     uint32_t q_tag = 0;
+    bool scattered = false;
     i32x4 doc_rsrc = {};
     if constexpr (Mask::kDoc) {
         const int32_t* docs = a.p.doc_ids + (int64_t)b * a.p.doc_stride_b;
@@ -794,6 +795,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     if (part_next) make_tags(0, kv0, 0);
     wait_vmem();
     __syncthreads();
+    if constexpr (Mask::kDoc) scattered = Mask::scattered_ids(q_tag);               // (not earlier: q_tag would be waited for)
 
     // One tile on buffer BUF (compile-time, so that every LDS read is "VGPR + immediate").
     auto step = [&](int t, auto buf_tag) {
@@ -883,7 +885,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
             if (partial && !mask.full(q_wave_min, q_wave_min + 31, kvs_blk, kvs_blk + 31)) {
                 asm volatile("" ::: "memory");   // keep this a branch
                 typename Mask::Bits bits = mask.row_bits(q_pos, kvs_blk + 4 * half);
-                if constexpr (Mask::kDoc) Mask::match_documents(bits, s_tag[BUF][kvb * 32 + l32], q_tag, half);
+                if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[BUF][kvb * 32], q_tag, l32, half, scattered);
                 u32x4 tags[4] = {};
                 if constexpr (Mask::kCanvas) {
 #pragma unroll

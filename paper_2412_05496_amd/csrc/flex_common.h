@@ -262,6 +262,7 @@ struct PartialMask {
     static constexpr uint32_t kTagged = FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD;
     static constexpr bool kDoc = (PRIMS & FLEXATTN_M_DOCUMENT) != 0, kCanvas = (PRIMS & FLEXATTN_M_NEIGHBORHOOD) != 0;
     static constexpr bool kTags = kDoc || kCanvas;
+    static constexpr int kMaxIds = 9;
     static_assert(!(kDoc && kCanvas), "one tag per token: documents or pixels");
 
     int window, prefix_len, ctx, kv_last;
@@ -312,19 +313,6 @@ struct PartialMask {
         return (a & (far - a) & guard) == guard;
     }
 
-    // Bits of the lanes l < 32 whose `theirs` equals this lane's `mine` (lanes l and l + 32 hold the same
-    // `theirs`; all lanes of the wave take part).
-    __device__ __forceinline__ static uint32_t equal_bits(uint32_t theirs, uint32_t mine) {
-        uint32_t out = 0, left = 0xffffffffu;
-        while (left != 0) {
-            const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)theirs, __builtin_ctz(left));
-            const uint32_t same = (uint32_t)__ballot(theirs == id);
-            left &= ~same;
-            out |= mine == id ? same : 0u;
-        }
-        return out;
-    }
-
     // Bits of the elements whose index comparisons hold: `plain` for the terms that end there, `tagged` for
     // those that also want the tags to match.
     struct Bits {
@@ -368,10 +356,40 @@ struct PartialMask {
         if constexpr (T1 != 0) out.add(T1, key_term<T1>(kv, q_base));
         return out;
     }
-    // Document masks: `theirs` holds the ids of the block's 32 tokens of the other index, lane l the one of
-    // token l % 32.
-    __device__ __forceinline__ static void match_documents(Bits& bits, uint32_t theirs, uint32_t mine, int half) {
-        bits.plain |= bits.tagged & (equal_bits(theirs, mine) >> (4 * half));
+    // Document masks: whether the 32 tokens of a wave (the id of token l % 32 in lane l; all lanes take part) belong to
+    // more documents than packed ones do.
+    __device__ __forceinline__ static bool scattered_ids(uint32_t id) {
+        uint32_t left = 0xffffffffu;
+#pragma unroll 1
+        for (int n = 0; n < kMaxIds && left != 0; ++n)
+            left &= ~(uint32_t)__ballot(id == (uint32_t)__builtin_amdgcn_readlane((int)id, __builtin_ctz(left)));
+        return left != 0;
+    }
+    // `tags` (in LDS) holds the ids of the block's 32 tokens of the other index, `mine` is this lane's.  Packed documents
+    // are matched by one ballot per id (all lanes of the wave take part); a wave whose own ids are scattered compares its
+    // lanes' 16 elements one by one, which takes the time of about seven ids.  (64 ids at random, S = 4096, 32 heads, us, a
+    // ballot per id throughout -> this: forward 349 -> 210 at D = 64, 386 -> 225 at D = 128, dQ 296 -> 175, 425 -> 277.  dK/dV
+    // stays with the ballots: 272 -> 182, but packed documents 1 to 3 % slower.)
+    __device__ __forceinline__ static void match_documents(Bits& bits, const uint32_t* tags, uint32_t mine, int l32, int half, bool scattered) {
+        uint32_t same = 0;
+        if (scattered) {
+#pragma unroll 1
+            for (int rg = 0; rg < 4; ++rg) {
+                const u32x4 t = *(const u32x4*)&tags[8 * rg + 4 * half];
+                const uint32_t four = (t[0] == mine ? 1u : 0u) | (t[1] == mine ? 2u : 0u) | (t[2] == mine ? 4u : 0u) | (t[3] == mine ? 8u : 0u);
+                same |= four << (8 * rg);
+            }
+        } else {
+            const uint32_t theirs = tags[l32];
+            for (uint32_t left = 0xffffffffu; left != 0;) {
+                const uint32_t id = (uint32_t)__builtin_amdgcn_readlane((int)theirs, __builtin_ctz(left));
+                const uint32_t equal = (uint32_t)__ballot(theirs == id);
+                left &= ~equal;
+                same |= mine == id ? equal : 0u;
+            }
+            same >>= 4 * half;
+        }
+        bits.plain |= bits.tagged & same;
     }
     // All-ones if element r is kept, else 0; `match`: its pixels match (canvas masks only).
     __device__ __forceinline__ static uint32_t keep(const Bits& bits, int r, bool match) {

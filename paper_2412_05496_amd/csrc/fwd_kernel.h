@@ -210,7 +210,12 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
     const Mask mask(a.p, b, a.kv_len);
     // the lane's own tag waits in LDS as well: a register held for it over the whole kernel ends in spills
     // whose reloads wait for the tile loads
-    if constexpr (Mask::kDoc) s_qtag[tid] = (uint32_t)(a.p.doc_ids + (int64_t)b * a.p.doc_stride_b)[q_pos];
+    bool scattered = false;
+    if constexpr (Mask::kDoc) {
+        const uint32_t id = (uint32_t)(a.p.doc_ids + (int64_t)b * a.p.doc_stride_b)[q_pos];
+        s_qtag[tid] = id;
+        scattered = Mask::scattered_ids(id);
+    }
     if constexpr (Mask::kCanvas) s_qtag[tid] = mask.query_pixel(q_pos);
     // Tags of the keys of the tile at kv0, into s_tag[buf] (visible after the next barrier): document ids
     // come by LDS-DMA (keys past the end read as 0), pixels are worked out by one of the waves.
@@ -290,7 +295,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
     auto masked = [&](f32x16& s, int kvs, int buf, int kvb, auto&& put) __attribute__((always_inline)) {
         typename Mask::Bits bits = mask.row_bits(q_pos, kvs + 4 * half);
         const uint32_t q_tag = Mask::kTags ? s_qtag[tid] : 0u;
-        if constexpr (Mask::kDoc) Mask::match_documents(bits, s_tag[buf][kvb * 32 + l32], q_tag, half);
+        if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[buf][kvb * 32], q_tag, l32, half, scattered);
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
             u32x4 tags = {};
@@ -351,7 +356,8 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
                 for (int r = 0; r < 16; ++r) s[r] = smod.template apply_shifted<false>(s[r], rel(r), 0.0f, shift);
             }
             if (partial) {
-                asm volatile("" ::: "memory");
+                if constexpr (Mask::kDoc) asm volatile("" : "+v"(s));
+                else asm volatile("" ::: "memory");
                 masked(s, kvs, buf, kvb, keep_or_neg_inf);
             }
             float mx = s[0];

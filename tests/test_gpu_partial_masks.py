@@ -24,6 +24,9 @@ def scattered_ids(B, S, n_ids, seed):
     (64, "alibi", 64, 128, 257, 3),
     (128, "rel_bias_softcap", 128, 64, 200, 5),
     (128, "alibi", 128, 128, 129, 1),        # one document: the tags never hide anything
+    (64, "identity", 128, 64, 300, 9),       # about as many ids as are matched by a ballot each
+    (128, "identity", 128, 64, 333, 10),
+    (128, "rel_bias_softcap", 64, 64, 200, 60),
 ])
 def test_scattered_documents(D, score, Bq, Bk, S, n_ids):
     dev = torch.device(DEV)
