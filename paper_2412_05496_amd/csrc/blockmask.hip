@@ -5,8 +5,10 @@
 // thread classifies a block from the index ranges and, for documents and canvas pixels, from the range of
 // ids or coordinates its tokens take: that settles the blocks that are hidden or visible as a whole.  The
 // others are counted exactly by one wave each, a lane per query row: the keys that row sees are a 64-bit
-// mask per term (an interval, and the keys whose document id equals the row's, one ballot per distinct id),
-// whose population is the count.
+// mask per term (an interval, and the keys whose document id equals the row's, by one ballot for each of the first
+// ids, or whose pixels match), whose population is the count.  Pixels are all different, and ids in any order may be:
+// those keys are compared one by one (a ballot for each, us -> this: 64 x 64 pixels, K = 41 102 -> 51, row-major 107 -> 51,
+// 128 x 128, K = 101 268 -> 136; 64 ids at random, S = 4096 89 -> 57).
 // What bounds it is latency, not arithmetic: three short kernels.  (A wave per block that evaluated
 // mask_mod scalar by scalar, 8192 to a block, and then one wave per line to compact: 0.18 ms on packed
 // documents of 16384 tokens, 0.11 ms for four causal chunks of 2048 queries on 16384 keys, 0.49 ms for
@@ -110,6 +112,7 @@ struct BlockEval {
         if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) lo = max(__builtin_elementwise_sub_sat(q, mask.window), 0);
         return span_bits(lo, hi, kv0) & ((TERM & Partial::kTagged) ? match : ~0ull);
     }
+    static constexpr int kBallots = 6;
     // Unmasked scalars of block (i, j), counted by the whole wave.
     __device__ __forceinline__ int count(int i, int j, int lane) const {
         int cnt = 0;
@@ -129,13 +132,24 @@ struct BlockEval {
                     if constexpr (Partial::kDoc) k_tag = (uint32_t)docs[kv];
                     if constexpr (Partial::kCanvas) k_tag = mask.key_pixel(kv);
                     match = 0;
-                    for (uint64_t left = ~0ull >> (64 - n); left != 0;) {
-                        const int at = __builtin_ctzll(left);
-                        const uint32_t tag = (uint32_t)__builtin_amdgcn_readlane((int)k_tag, at);
-                        const uint64_t same = __ballot(k_tag == tag);
-                        left &= ~same;
-                        if constexpr (Partial::kDoc) match |= tag == q_tag ? same : 0ull;
-                        if constexpr (Partial::kCanvas) match |= mask.pixels_match(tag, q_tag) ? same : 0ull;
+                    uint64_t left = ~0ull >> (64 - n);
+                    if constexpr (Partial::kDoc) {      // the first ids by one ballot each
+                        for (int i = 0; i < kBallots && left != 0; ++i) {
+                            const uint32_t tag = (uint32_t)__builtin_amdgcn_readlane((int)k_tag, __builtin_ctzll(left));
+                            const uint64_t same = __ballot(k_tag == tag);
+                            left &= ~same;
+                            match |= tag == q_tag ? same : 0ull;
+                        }
+                    }
+                    if (left != 0) {                    // key by key
+                        uint32_t part[2] = {0u, 0u};
+#pragma unroll
+                        for (int at = 0; at < 64; ++at) {
+                            const uint32_t tag = (uint32_t)__builtin_amdgcn_readlane((int)k_tag, at);
+                            const bool same = Partial::kDoc ? tag == q_tag : mask.pixels_match(tag, q_tag);
+                            part[at >> 5] |= same ? 1u << (at & 31) : 0u;
+                        }
+                        match |= (uint64_t)part[1] << 32 | part[0];
                     }
                 }
                 uint64_t bits = term_bits<T0>(q, kv0, match);
