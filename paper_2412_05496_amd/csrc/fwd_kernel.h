@@ -58,11 +58,20 @@ constexpr int kTileKV = 64;   // keys per kernel tile
 // 64 heads: 158 -> 127; no mask, S = 2048: 89.5 -> 86.5; packed documents with ALiBi: 218 -> 216.
 // The pipelined one stays where it is the better one: a bounded soft-cap, whose softmax needs no running
 // maximum (287 -> 299), and Bq = 64, where LDS admits 2.5 waves per SIMD either way (a single small call: 7.7
-// -> 8.4).  Neighborhood masks gain most: 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (490 ->
+// -> 8.4); and, where neither a window, documents nor a canvas ends rows early, long rows on a chip that is not full and
+// soft-caps whose maximum has to be tracked (plain_pays; causal, S = 4096, 32 heads 132 <- 110, S = 8192, 16 heads 208 <- 196,
+// S = 4096, 64 heads 190 <- 200; cap of 100, S = 2048, 32 heads 64.6 <- 60.6, S = 8192, 64 heads 924 <- 904, S = 1024, 256 heads
+// 92.3 <- 94.7: plain <- pipelined).  Neighborhood masks gain most: 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (490 ->
 // 340 at 128 x 128 pixels).
 template <int D, int NW, bool BOUNDED>
 constexpr bool fwd_plain() {
     return D == 64 && NW == 4 && !BOUNDED;
+}
+
+template <uint32_t SCORE>
+bool plain_pays(int kv_len, unsigned grid) {
+    if (SCORE & FLEXATTN_SCORE_SOFTCAP) return kv_len < 2048;
+    return kv_len < 4096 || grid >= 6 * 256;
 }
 
 // The same at D = 128, where 64-key tiles of K and V leave LDS for two workgroups: units of 32 keys in a ring of
@@ -105,23 +114,24 @@ bool units_pay(const FwdArgs& a, int64_t grid) {
 }
 // Waves per SIMD to compile for: what registers (512 per SIMD lane) and LDS admit.  The pipelined variants
 // with a relative-bias table would spill at three.
-template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool UNITS>
+template <int D, uint32_t SCORE, bool UNITS, bool PLAIN>
 constexpr int fwd_waves_per_simd() {
     if (D != 64) return UNITS ? 3 : 2;
-    if (fwd_plain<D, NW, BOUNDED>()) return NW == 4 ? 4 : 2;
+    if (PLAIN) return 4;
     return (SCORE & FLEXATTN_SCORE_REL_BIAS) ? 2 : 3;
 }
 
 // BOUNDED: the score_mod ends in a soft-cap small enough that the cap itself serves as the fixed
 // softmax maximum (see ScoreMod::bounded); chosen by the host from the cap value.
-// UNITS: 32-key units in a ring of three (fwd_units).
+// UNITS: 32-key units in a ring of three (fwd_units).  PLAIN: no tile pipeline (fwd_plain).
 // PAGED: the tiles of K and V are fetched from a paged pool through the converted block lists;
 // the mods keep seeing the logical key index.
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
-template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED, bool UNITS = false>
-__global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BOUNDED, UNITS>())) void fwd_kernel(const FwdArgs a) {
+template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED, bool UNITS = false,
+          bool PLAIN = fwd_plain<D, NW, BOUNDED>()>
+__global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN>())) void fwd_kernel(const FwdArgs a) {
     constexpr int Bq = NW * 32;
     constexpr int TILE = kTileKV * D;              // elements per LDS tile
 
@@ -132,7 +142,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
     using Mask = PartialMask<MASK>;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[UNITS ? 3 : 2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys, per buffer
 
-    constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || fwd_plain<D, NW, BOUNDED>());
+    constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || PLAIN);
     __shared__ uint32_t s_qtag[Mask::kTags ? NW * 64 : 1];            // each lane's own tag (its query's)
     __shared__ uint8_t s_hidden[kHiddenTable ? kHiddenTiles : 1];    // CanvasBlocks::hidden_bits of the first tiles
 
@@ -478,7 +488,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, NW, MASK, SCORE, BO
         }
         if (u < TU) unit_step(u, s0);
         if (u + 1 < TU) unit_step(u + 1, s1);
-    } else if constexpr (fwd_plain<D, NW, BOUNDED>()) {
+    } else if constexpr (PLAIN) {
         // One block of 32 keys after the other, K and V one tile ahead.  A wave leaves out the blocks that
         // the mask hides from all of its rows.
         first_tile();
@@ -629,7 +639,16 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
         FLEXATTN_LAUNCH(128, 4)
     }
     if (D == 128 && Bq == 64) { FLEXATTN_LAUNCH(128, 2) }
-    if (D == 64 && Bq == 128) { FLEXATTN_LAUNCH(64, 4) }
+    if (D == 64 && Bq == 128) {
+        constexpr bool dense = !mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
+        if constexpr (fwd_plain<64, 4, BOUNDED>() && dense) {
+            if (!plain_pays<SCORE>(a.kv_len, grid)) {
+                hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false>), dim3(grid), dim3(256), 0, st, a);
+                return FLEXATTN_OK;
+            }
+        }
+        FLEXATTN_LAUNCH(64, 4)
+    }
     if (D == 64 && Bq == 64) { FLEXATTN_LAUNCH(64, 2) }
 #undef FLEXATTN_LAUNCH
     return FLEXATTN_ERR_UNSUPPORTED;

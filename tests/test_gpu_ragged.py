@@ -169,3 +169,31 @@ def test_forward_d128_many_workgroups_planes_and_offsets(mask, score, Bk):
     torch.cuda.synchronize()
     hp.check_output(O[:3], LSE[:3], *fo.flex_attention(inp.Q[:, :, :Lq], inp.K, inp.V, score_mod, mask_mod, inp.scale))
     assert torch.equal(O, many(O[:3], n)) and torch.equal(LSE, many(LSE[:3], n))
+
+
+@pytest.mark.parametrize("mask,score,S,q_len,B", [
+    ("causal", "identity", 4095, 160, 1), ("causal", "identity", 4096, 160, 1), ("none", "identity", 4100, 90, 1),
+    ("prefix_lm", "identity", 4200, 130, 1), ("causal", "alibi", 4097, 33, 1), ("causal", "alibi", 4097, 130, 700),
+    ("causal", "softcap", 2047, 130, 1), ("causal", "softcap", 2050, 130, 1), ("causal", "alibi_softcap", 2048, 200, 1)])
+def test_forward_d64_long_rows(mask, score, S, q_len, B):
+    """D = 64 without windows: both sides of the lengths and of the number of workgroups at which the forward keeps its
+    tile pipeline (soft-caps: too large to serve as the maximum).  The queries are the last of the sequence."""
+    import paper_2412_05496_amd as fa
+    dev = torch.device("cuda:0")
+    wl = wlm.CFG1.scaled(name="long_rows", B=1, Hq=2, Hkv=1, S=S, D=64, Bq=128, Bk=64, mask=mask, score=score, prefix_len=100, softcap=60.0,
+                         seed=3990 + S)
+    inp = wlm.make_train_inputs(wl)
+    score_mod, mask_mod = hp.oracle_mods(wl, inp)
+    off = torch.tensor([S - q_len], dtype=torch.int32)
+    score_mod, mask_mod = fo.QOffset(score_mod, off), fo.with_q_offset(mask_mod, off)
+    mask_id, score_id, params, _ = hp.library_mods(wl, inp, dev)
+    params.q_offsets = off.repeat(B).to(dev)
+    bm = fa.alloc_blockmask(1, 1, q_len, S, 128, 64, device=dev)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    Q, K, V = (t.to(dev).expand(B, -1, -1, -1) for t in (inp.Q[:, :, -q_len:].contiguous(), inp.K, inp.V))
+    O = torch.full(Q.shape, float("nan"), dtype=torch.bfloat16, device=dev)
+    LSE = torch.full(Q.shape[:3], float("nan"), device=dev)
+    fa.flexattn_forward(Q, K, V, score_id, mask_id, params, bm, inp.scale, O, LSE)
+    torch.cuda.synchronize()
+    hp.check_output(O[:1], LSE[:1], *fo.flex_attention(inp.Q[:, :, -q_len:], inp.K, inp.V, score_mod, mask_mod, inp.scale))
+    assert torch.equal(O, O[:1].expand_as(O)) and torch.equal(LSE, LSE[:1].expand_as(LSE))
