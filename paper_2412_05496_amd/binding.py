@@ -176,9 +176,18 @@ def library_path() -> str:
 
 
 def _stream() -> int:
-    """torch's current stream on the current device (without the Stream object torch.cuda.current_stream()
-    makes, 2 us of a call)."""
+    """torch's current stream on the current device."""
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _raw_stream() -> int:
+    """The same without the Stream object torch.cuda.current_stream() makes (2 us of a call), where torch has the two
+    functions that its own generated code calls for it."""
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    _stream = _raw_stream
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

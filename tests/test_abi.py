@@ -3,6 +3,7 @@ arguments on the host before anything touches a GPU (CPU only; no compute calls)
 import ctypes as C
 import os
 import re
+import sys
 
 import pytest
 
@@ -163,3 +164,20 @@ def test_stored_backward_workspace_is_host_arithmetic():
     assert lib.flexattn_backward_stored_workspace_bytes(None, C.byref(bm), 1) == 0
     assert lib.flexattn_backward_stored(C.byref(d), None, None, None, None, None, None, 0, 0, None, C.byref(bm), 1.0,
                                         None, None, None, -1, None, 0, None, 7) == fa.ERR_INVALID_ARG
+
+
+def test_stream_without_torchs_own_shortcuts(monkeypatch):
+    """The stream comes from the public call where torch lacks the two functions the shortcut uses."""
+    import importlib.util
+    import torch
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    spec = importlib.util.spec_from_file_location("binding_without_shortcuts", binding.__file__)
+    other = importlib.util.module_from_spec(spec)
+    monkeypatch.setitem(sys.modules, spec.name, other)
+    spec.loader.exec_module(other)
+
+    class Stream:
+        cuda_stream = 1234
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert other._stream() == 1234

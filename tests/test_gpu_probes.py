@@ -48,3 +48,11 @@ def test_stream_read_probe_and_bad_arguments():
         fa.flexattn_probe_mfma(0, sink)
     with pytest.raises(fa.FlexAttnError):
         fa.flexattn_probe_mfma(10, sink, valu_mix=3)
+
+
+def test_calls_go_to_torchs_current_stream():
+    from paper_2412_05496_amd import binding
+    assert binding._stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert binding._stream() == side.cuda_stream != torch.cuda.default_stream().cuda_stream
