@@ -198,8 +198,9 @@ extern "C" int flexattn_backward_stored(const flexattn_dims* dims, const flexatt
 namespace {
 // Sum of the per-workgroup partials over batch and rows of blocks, in a fixed order, times `factor`:
 // out[hq, i] = factor * sum_{b, row} part[((b * Hq + hq) * NR + row) * width + i].
-// 32 entries side by side, the partials of an entry dealt to 32 threads whose sums are added in order: bound by
-// the latency of one thread's loads, so a thread has as few as that leaves.  (One thread per entry walked all
+// 32 entries side by side, the rows of blocks of an entry dealt to 32 threads whose sums are added in order; a thread
+// takes its rows of every batch entry, so with fewer than 32 rows some have none.  Bound by the latency of one thread's
+// loads.  (One thread per entry walked all
 // partials: 196 us for 8192 entries of 512 partials, a fifth of the kernel that makes them on short
 // sequences; 10 us since.)
 __global__ __launch_bounds__(1024) void captured_reduce_kernel(const float* __restrict__ part, int B, int Hq, int NR,

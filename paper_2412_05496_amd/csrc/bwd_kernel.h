@@ -113,6 +113,16 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const BwdArgs a) {
     }
 }
 
+// Neighborhood masks: bit kb + 2 x is set if the mask hides the block of the 32 query rows q0 + 32 x .. and the 32
+// keys kv0 + 32 kb .. .  The dQ kernel that reads dS back takes the same answer for the same block
+// (CanvasBlocks::hidden_bits), so the dS of such a block is neither written nor read.
+__device__ __forceinline__ int canvas_step_bits(const flexattn_mod_params& p, int q0, int kv0) {
+    const CanvasBlocks cb(p);
+    const CanvasBlocks::Box qw[2] = {cb.windows(q0), cb.windows(q0 + 32)};
+    const uint32_t b = cb.hidden_bits(qw, kv0);     // bit 2 x + kb
+    return (int)b;
+}
+
 // ------------------------------------------------------------------------------------------
 // dK, dV.  256 threads = 4 waves, one workgroup per 64 keys of one (b, hkv), two workgroups per CU
 // (two waves per SIMD, from different workgroups, so that one wave's exp / dS arithmetic runs
@@ -139,23 +149,11 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const BwdArgs a) {
 // workgroups.  us, exchange -> own rows (one MI355X): causal, 64 x 16 heads, S = 1024: 491 -> 472; window of
 // 1024, S = 5000, Hq 16, Hkv 2, B = 4: 222 -> 210; packed documents with ALiBi, S = 16384, 16 heads: 262 -> 252;
 // soft-cap, S = 4096, 64 heads: 532 -> 502; relative bias, window 1024, S = 8192: 598 -> 548.
-// M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
-// compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
-// s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
-// Which form: own rows at D = 64.  A soft-cap on top of a bias, and the pixel compares of a canvas, leave too
+//
+// Which form: own rows at D = 64, but for launches that are too uneven for it (own_rows_pay).  A soft-cap on top of a bias, and the pixel compares of a canvas, leave too
 // few registers at three waves per SIMD (6 to 24 spills: 431 -> 447 us with ALiBi, 350 -> 370 with documents
 // and a relative bias; canvas 684 -> 763) and keep the exchange, as does D = 128, whose two accumulators
 // are 128 registers.
-// Neighborhood masks: bit kb + 2 x set if the mask hides the block of the 32 query rows q0 + 32 x .. and the 32
-// keys kv0 + 32 kb .. .  The dQ kernel that reads dS back takes the same answer for the same block
-// (CanvasBlocks::hidden_bits), so the dS of such a block is neither written nor read.
-__device__ __forceinline__ int canvas_step_bits(const flexattn_mod_params& p, int q0, int kv0) {
-    const CanvasBlocks cb(p);
-    const CanvasBlocks::Box qw[2] = {cb.windows(q0), cb.windows(q0 + 32)};
-    const uint32_t b = cb.hidden_bits(qw, kv0);     // bit 2 x + kb
-    return (int)b;
-}
-
 //
 // kCut, neighborhood masks at D = 128: the walk leaves out the steps that are hidden from all four waves, and a
 // wave the vector work and the outputs of its hidden blocks (128 x 128 pixels, tiles of 8 x 8, K = 13, 64 heads:
@@ -166,6 +164,9 @@ constexpr bool dkdv_own_rows() {
     constexpr bool biased_cap = (SCORE & FLEXATTN_SCORE_SOFTCAP) && (SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS));
     return D == 64 && !PartialMask<MASK>::kCanvas && !biased_cap;
 }
+// M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
+// compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
+// s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
 template <int D, uint32_t MASK, uint32_t SCORE, bool OWN = dkdv_own_rows<D, MASK, SCORE>()>
 __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(const BwdArgs a) {
     constexpr int TQ = 64;                         // query rows per step

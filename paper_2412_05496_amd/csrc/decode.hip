@@ -16,7 +16,8 @@
 // with log-sum-exp weights, and is not needed where a sequence has a single split.
 // Measured on MI355X, 32 query / 8 KV heads, D = 128, 16-token pages (before: one wave per split, 32-column
 // MFMAs, one wave per head walking the splits in the combine): one sequence of 8k tokens 33 -> 14 us, of 32k
-// 69 -> 27, four of 8k 40 -> 26, sixteen of 8k 102 -> 86 (6.2 TB/s), 64 of 1k to 32k 783 -> 718 (6.8 TB/s).
+// 69 -> 27, four of 8k 40 -> 26, sixteen of 8k 102 -> 86 (6.2 TB/s), 64 of 1k to 32k 783 -> 718 (at the rate of a plain
+// streaming read).
 #include <mutex>
 
 #include "flex_common.h"
@@ -400,7 +401,10 @@ static int cut(const flexattn_decode_dims* d, long long want, int longest) {
 // 2048 keys per split: one sequence of 32k tokens 29.3 / 27.1 / 29.2 / 41.1, four of 8k 27.9 / 26.4 / 28.8 /
 // 41.0, one of 128k 102 / 92 / 88 / 86).  A large batch takes the longest splits, which pay a workgroup's
 // start and its partial result least often (64 sequences of 1k to 32k: 908 / 797 / 753 / 719, and 715
-// at 4096, where a batch whose contexts stay far below the table's reach would no longer fill the chip).
+// at 4096, where a batch whose contexts stay far below the table's reach would no longer fill the chip).  At D = 64 four
+// workgroups fit a CU, but the same aim is the better one where contexts come near the table's reach (us at 512 / 1024
+// workgroups, 8 KV heads: one of 32k 13.6 / 14.6, 64 of 1k 20.5 / 25.3, 16 of 4k 23.5 / 23.9; 16 of 2k in a table of 4k, 4 KV
+// heads 10.7 / 9.0).
 static int split_len_of(const flexattn_decode_dims* d) { return cut(d, 512, kDecSplitMax); }
 
 static int splits(const flexattn_decode_dims* d, int len) {

@@ -12,8 +12,13 @@
 // the A operand of K Q^T as they are, V^T fragments come out of the row-major V tile through the
 // transposing LDS read.  Q lives in registers for the whole kernel.
 //
-// Software pipeline, one barrier per tile: while the VALU works on the softmax of tile t, the
-// MFMA unit computes S^T of tile t+1; K(t+2) and V(t+1) are in flight from HBM/L2 meanwhile.
+// Three forms of the loop over the tiles, one barrier per tile in each:
+//   pipelined  while the VALU works on the softmax of tile t, the MFMA unit computes S^T of tile t + 1; K(t + 2) and
+//              V(t + 1) are in flight from HBM / L2 meanwhile;
+//   PLAIN      (D = 64) a 32-key block after the other, K and V one 64-key tile ahead: four waves per SIMD instead of
+//              three (fwd_plain, plain_pays);
+//   UNITS      (D = 128) the same with 32-key tiles in a ring of three, two tiles ahead: three instead of two
+//              (fwd_units, units_pay).
 #pragma once
 
 #include <type_traits>
