@@ -185,17 +185,13 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     using Mask = PartialMask<MASK>;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? TQ : 4];   // [slot] tags of a PARTIAL step's queries
 
-    // workgroup -> (b, hkv, 64-key tile); all tiles of one (b, hkv) on one XCD.  The columns of
+    // workgroup -> (b, hkv, 64-key tile).  The columns of
     // blocks are taken in the BlockMask's work order (longest first; that of the group's first query
     // head where the mask has a plane per head), the 64-key tiles of a column side by side.
-    const int units = a.B * a.Hkv;
     const int sub_k = a.Bk / 64;                   // tiles per column of blocks
-    const int slots = a.NC * sub_k;                // >= tiles: the last column may be cut short
-    const int id = blockIdx.x, xcd = id & 7, kk = id >> 3;
-    const int unit = (kk / slots) * 8 + xcd;
-    if (unit >= units) return;
+    int unit, slot;                                // NC * sub_k slots >= tiles: the last column may be cut short
+    if (!unit_of_workgroup(a.B * a.Hkv, a.NC * sub_k, unit, slot)) return;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
-    const int slot = kk % slots;
     int col = slot / sub_k;
     if (a.q_order) {
         const int64_t plane0 = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hkv * a.G : 0);
@@ -689,12 +685,8 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? 64 : 4];   // tags of a PARTIAL tile's keys (even, odd)
     __shared__ uint8_t s_hidden[Mask::kCanvas && SKIP ? kHiddenTiles : 1];           // CanvasBlocks::hidden_bits of the first tiles
 
-    const int units = a.B * a.Hkv;
-    const int id = blockIdx.x, xcd = id & 7, kk = id >> 3;
-    const int per_unit = a.G * a.NR;
-    const int unit = (kk / per_unit) * 8 + xcd;
-    if (unit >= units) return;
-    const int rem = kk % per_unit;
+    int unit, rem;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR, unit, rem)) return;
     const int g = rem % a.G;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv, hq = hkv * a.G + g;
     const int64_t plane = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0);
@@ -995,10 +987,8 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
 // told by what the columns' steps make of 768 workgroups (three per CU) beside the longest column: a third of it (270 of
 // 768 for a mask whose columns are as long as the longest).  Windows and documents have columns of about one length and
 // hidden blocks to leave out, a soft-cap more vector work than the operands' reads take.
-// us, exchange -> own rows: causal, S = 1024, 8 heads 16.8 -> 18.7; S = 4096, 4 heads 59.0 -> 61.6, 8 heads 57.7 -> 59.8, 32 / 4
-// heads 433 -> 457; S = 2048, 16 heads 38.7 -> 38.1, 32 heads 56.5 -> 54.3; no mask, S = 1024, 8 heads 16.9 -> 17.9, S = 4096, 8 heads
-// 78.2 -> 76.7; window 512 or prefix 128, S = 8192, 16 heads 163 -> 170, S = 2048, 32 heads 55.5 -> 53.8; causal with a soft-cap,
-// S = 4096, 4 heads 74.5 -> 70.2.
+// us, exchange -> own rows: causal, S = 1024, 8 heads 16.8 -> 18.7; S = 4096, 8 heads 57.7 -> 59.8; S = 2048, 16 heads 38.7 -> 38.1, 32 heads 56.5 -> 54.3; no mask, S = 1024, 8 heads 16.9 -> 17.9, S = 4096, 8 heads
+// 78.2 -> 76.7; window 512 or prefix 128, S = 8192, 16 heads 163 -> 170, S = 2048, 32 heads 55.5 -> 53.8.
 template <uint32_t MASK>
 bool own_rows_pay(const BwdArgs& a, unsigned grid) {
     const float longest = a.q_len / 64.0f;          // steps
@@ -1036,9 +1026,8 @@ constexpr uint32_t kBwdStageCaptured = 8u;   // internal: the captured-tensor su
 
 template <uint32_t MASK, uint32_t SCORE>
 int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st) {
-    const int units = a.B * a.Hkv;
-    const unsigned grid_kv = (unsigned)(((units + 7) / 8) * 8 * (a.NC * (a.Bk / 64)));
-    const unsigned grid_q = (unsigned)(((units + 7) / 8) * 8 * a.G * a.NR);
+    const unsigned grid_kv = unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 64));
+    const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
     if (stages & FLEXATTN_BWD_DELTA) {
         const size_t rows = (size_t)a.B * a.Hq * a.q_len;

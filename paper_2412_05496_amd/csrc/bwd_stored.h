@@ -109,12 +109,8 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
     __shared__ int s_chunk[kList + 2];                               // where its dS starts (ds_chunk without the rep)
     __shared__ uint8_t s_hid[CANVAS ? kList + 2 : 1];                // CanvasBlocks::hidden_bits of the tile
 
-    const int units = a.B * a.Hkv;
-    const int id = blockIdx.x, xcd = id & 7, kk = id >> 3;
-    const int per_unit = a.G * a.NR;
-    const int unit = (kk / per_unit) * 8 + xcd;
-    if (unit >= units) return;
-    const int rem = kk % per_unit;
+    int unit, rem;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR, unit, rem)) return;
     const int g = rem % a.G;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv, hq = hkv * a.G + g;
     const int64_t plane = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0);
@@ -274,8 +270,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
 
 template <bool CANVAS>
 int launch_bwd_stored_dq(const BwdArgs& a, int D, float qscale, hipStream_t st) {
-    const int units = a.B * a.Hkv;
-    const unsigned grid_q = (unsigned)(((units + 7) / 8) * 8 * a.G * a.NR);
+    const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 4, CANVAS>), dim3(grid_q), dim3(256), 0, st, a, qscale);
     else if (D == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 2, CANVAS>), dim3(grid_q), dim3(128), 0, st, a, qscale);
     else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<64, 4, CANVAS>), dim3(grid_q), dim3(256), 0, st, a, qscale);

@@ -218,6 +218,32 @@ struct NoCanvas {
     __device__ __forceinline__ void pixel(int, int&, int&) const {}
 };
 
+// Workgroup -> (unit, rank): which KV head of which batch entry, and which of its per_unit pieces (longest first).
+// Workgroup ids go to the 8 XCDs in turn.  Eight units at a time, a unit's pieces all go to one XCD, so that its K and V
+// stay in that XCD's L2.  The 1 .. 7 units that are left are cut into eighths, every eighth piece each, and an XCD
+// takes as many eighths, one after the other, as there are units left: all XCDs end together, with the pieces of at most
+// two units in an L2.  False: nothing to do (the last round of eighths).  (A whole unit on one XCD leaves the others idle:
+// us, that -> this, causal: S = 16384, D = 128, 1 head, forward 472 -> 289, dK/dV 832 -> 269, dQ 574 -> 326; 3 heads, D = 64,
+// 309 -> 213, 537 -> 262, 371 -> 238; S = 8192, D = 128, 16 query and 2 KV heads 874 -> 285, 1855 -> 1074, 1064 -> 369; S = 4096, 9
+// heads, D = 64, 76 -> 75, 83 -> 79, 83 -> 82; 8 and 16 heads the same.)
+__device__ __forceinline__ bool unit_of_workgroup(int units, int per_unit, int& unit, int& rank) {
+    const int xcd = blockIdx.x & 7, rest = units & 7, whole = (units >> 3) * per_unit;
+    const int k = blockIdx.x >> 3;
+    if (k < whole) {
+        const int u = k / per_unit;
+        unit = u * 8 + xcd;
+        rank = k - u * per_unit;
+        return true;
+    }
+    const int round = (k - whole) / rest, eighth = xcd * rest + (k - whole) - round * rest;
+    unit = (units & ~7) + (eighth >> 3);
+    rank = 8 * round + (eighth & 7);
+    return rank < per_unit;
+}
+inline unsigned unit_grid(int units, int per_unit) {
+    return 8u * ((unsigned)(units >> 3) * (unsigned)per_unit + (unsigned)(units & 7) * (unsigned)((per_unit + 7) / 8));
+}
+
 // Offset conversion for inference (section 5.2): the position the mods see for query row 0 of
 // batch entry b.
 __device__ __forceinline__ int q_offset_of(const flexattn_mod_params& p, int b) {

@@ -89,9 +89,8 @@ bool plain_pays(int kv_len, unsigned grid) {
 //   S = 8192 592 -> 626 (four sequences of 16 heads: 1099 -> 1105);
 //   never with a relative bias under a soft-cap: its table no longer lets three in (325 -> 345);
 //   and only where the workgroups are three rounds of the chip: with fewer there is nothing to put beside a
-//   workgroup, and each is slower by itself (one sequence, S = 4096, ALiBi, 4 heads 108 -> 127, 24 heads 172 -> 215).
-// Windows of at most half the keys have rows of one length, and the workgroups (with the idle ones of XCDs that have
-// a KV head fewer) go in rounds, of 768 with units and of 512 without: units where that is one round less, or where
+//   workgroup, and each is slower by itself (one sequence, S = 4096, ALiBi, 24 heads 172 -> 215).
+// Windows of at most half the keys have rows of one length, and the workgroups go in rounds, of 768 with units and of 512 without: units where that is one round less, or where
 // there are many rounds (S = 4096, window of 1024; heads 16: 43.9 -> 45.3, 24: 71.1 -> 62.8, 32: 82.5 -> 95.2, 40: 105 -> 102,
 // 64: 154.4 -> 153.6; the same with a relative bias and a prefix, window of 512: 41.2 -> 45.9, 67.3 -> 57.4, 76.6 -> 90.3,
 // 100 -> 97, 147 -> 147; S = 5000, four sequences of 16 / 2 heads: 186 -> 171).  Longer windows go by length (window = S = 4096,
@@ -151,17 +150,10 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     __shared__ uint32_t s_qtag[Mask::kTags ? NW * 64 : 1];            // each lane's own tag (its query's)
     __shared__ uint8_t s_hidden[kHiddenTable ? kHiddenTiles : 1];    // CanvasBlocks::hidden_bits of the first tiles
 
-    // ---- workgroup -> (b, hkv, g, row of blocks).  Consecutive workgroup ids go to the 8 XCDs in
-    // turn; all rows and all G query heads of one (b, hkv) are sent to the same XCD so that its K/V
-    // stay in that XCD's L2.  Rows are taken longest first (the BlockMask's work order), or
+    // ---- workgroup -> (b, hkv, g, row of blocks).  Rows are taken longest first (the BlockMask's work order), or
     // last-first without one (causal-like masks: longest first).
-    const int units = a.B * a.Hkv;
-    const int id = blockIdx.x;
-    const int xcd = id & 7, k = id >> 3;
-    const int per_unit = a.G * a.NR;
-    const int unit = (k / per_unit) * 8 + xcd;
-    if (unit >= units) return;
-    const int rem = k % per_unit;
+    int unit, rem;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR, unit, rem)) return;
     const int g = rem % a.G;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv, hq = hkv * a.G + g;
     const int64_t plane = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0);
@@ -629,8 +621,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 
 template <uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED>
 int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
-    const int units = a.B * a.Hkv;
-    const unsigned grid = (unsigned)(((units + 7) / 8) * 8 * a.G * a.NR);
+    const unsigned grid = unit_grid(a.B * a.Hkv, a.G * a.NR);
 #define FLEXATTN_LAUNCH(DD, NW)                                                                            \
     hipLaunchKernelGGL((fwd_kernel<DD, NW, MASK, SCORE, BOUNDED, PAGED>), dim3(grid), dim3(NW * 64), 0, st, a); \
     return FLEXATTN_OK;
