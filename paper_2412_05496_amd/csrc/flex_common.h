@@ -81,12 +81,16 @@ __device__ __forceinline__ LanePair lane_pair(float v) {
         return {__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1])};
     }
 }
+// max(a, b) as one instruction (fmaxf first puts both through a max of their own to quieten NaNs)
+__device__ __forceinline__ float raw_max(float a, float b) {
+    float m;
+    asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+    return m;
+}
 // The larger of this lane's value and that of the lane 32 away.
 __device__ __forceinline__ float max_halves(float v) {
     const LanePair p = lane_pair<false>(v);
-    float m;        // (not fmaxf, which first puts both through a max of their own to quieten NaNs)
-    asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(p.a), "v"(p.b));
-    return m;
+    return raw_max(p.a, p.b);
 }
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
@@ -220,22 +224,23 @@ struct NoCanvas {
 
 // Workgroup -> (unit, rank): which KV head of which batch entry, and which of its per_unit pieces (longest first).
 // Workgroup ids go to the 8 XCDs in turn.  Eight units at a time, a unit's pieces all go to one XCD, so that its K and V
-// stay in that XCD's L2.  The 1 .. 7 units that are left are cut into eighths, every eighth piece each, and an XCD
-// takes as many eighths, one after the other, as there are units left: all XCDs end together, with the pieces of at most
-// two units in an L2.  False: nothing to do (the last round of eighths).  (A whole unit on one XCD leaves the others idle:
+// stay in that XCD's L2.  The 1 .. 7 units beyond a multiple of eight come first and are cut into eighths, every eighth
+// piece each; an XCD takes as many eighths side by side as there are such units: all XCDs have the same work, with
+// the pieces of at most two units in an L2.  (First, because what comes last ends the launch, and the long pieces of a whole
+// unit then start earlier.)  False: nothing to do (the last round of eighths).  (A whole unit on one XCD leaves others idle:
 // us, that -> this, causal: S = 16384, D = 128, 1 head, forward 472 -> 289, dK/dV 832 -> 269, dQ 574 -> 326; 3 heads, D = 64,
 // 309 -> 213, 537 -> 262, 371 -> 238; S = 8192, D = 128, 16 query and 2 KV heads 874 -> 285, 1855 -> 1074, 1064 -> 369; S = 4096, 9
-// heads, D = 64, 76 -> 75, 83 -> 79, 83 -> 82; 8 and 16 heads the same.)
+// heads, D = 64, 76 -> 54, 82 -> 61, 83 -> 61, D = 128, 105 -> 80, 130 -> 93, 130 -> 92; 8 and 16 heads the same within 2 %.)
 __device__ __forceinline__ bool unit_of_workgroup(int units, int per_unit, int& unit, int& rank) {
-    const int xcd = blockIdx.x & 7, rest = units & 7, whole = (units >> 3) * per_unit;
+    const int xcd = blockIdx.x & 7, rest = units & 7, rest_pieces = rest * ((per_unit + 7) >> 3);
     const int k = blockIdx.x >> 3;
-    if (k < whole) {
-        const int u = k / per_unit;
+    if (k >= rest_pieces) {
+        const int u = (k - rest_pieces) / per_unit;
         unit = u * 8 + xcd;
-        rank = k - u * per_unit;
+        rank = k - rest_pieces - u * per_unit;
         return true;
     }
-    const int round = (k - whole) / rest, eighth = xcd * rest + (k - whole) - round * rest;
+    const int round = k / rest, eighth = xcd * rest + k - round * rest;
     unit = (units & ~7) + (eighth >> 3);
     rank = 8 * round + (eighth & 7);
     return rank < per_unit;
