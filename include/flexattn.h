@@ -369,7 +369,8 @@ int flexattn_paged_forward(const flexattn_dims* dims, const flexattn_tensor* Q,
  *   Q       [nseq, Hq, D] bf16 (stride_q_seq elements between sequences, heads contiguous)
  *   K_pool, V_pool  [n_pool_pages, Hkv, page_size, D] bf16, dense
  *   page_table [nseq, pt_stride] int32: logical page j of sequence b lives in pool page
- *              page_table[b, j]; only the first ceil(ctx_lens[b] / page_size) entries are read
+ *              page_table[b, j]; the entries from ceil(ctx_lens[b] / page_size) to max_pages may
+ *              hold anything (they may be read, and name no key)
  *   ctx_lens   [nseq] int32: visible keys are kv_idx < ctx_lens[b] (0 is legal: O = 0,
  *              LSE = -inf).  score_mods see q_idx = ctx_lens[b] - 1 and the LOGICAL kv_idx.
  *   O [nseq, Hq, D] bf16 dense, at any element address (16-byte aligned it is written in wide stores);
@@ -378,9 +379,9 @@ int flexattn_paged_forward(const flexattn_dims* dims, const flexattn_tensor* Q,
  * Device-side values are not trusted: a context length outside [0, max_pages * page_size] is clamped to
  * that range and a page id outside [0, n_pool_pages) to the nearest valid page, so that wrong tables
  * give wrong rows and never an access outside the table, the pools or the workspace.
- * The KV range is cut into splits of 128 ... 2048 keys, one workgroup each; the split length is chosen
- * from nseq * Hkv * max_pages * page_size so that the launch still fills the chip when the batch is
- * small (flexattn_paged_decode_workspace_bytes covers it).  mask_id: FLEXATTN_MASK_CTX_LEN (which, with the query at
+ * The KV range is cut into splits of 128 ... 2048 keys, one workgroup each (a table of at most 512 keys mostly into
+ * one); the split length is chosen from nseq * Hkv * max_pages * page_size so that the launch still fills the chip when
+ * the batch is small (flexattn_paged_decode_workspace_bytes covers it).  mask_id: FLEXATTN_MASK_CTX_LEN (which, with the query at
  * q_idx = ctx_len - 1, is also the causal mask of a decode step: the offset conversion of section 5.2) or
  * FLEXATTN_MASK_CTX_LEN_WINDOW (additionally q_idx - kv_idx <= params->window; splits wholly below the
  * window are skipped).

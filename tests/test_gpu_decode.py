@@ -232,3 +232,28 @@ def test_pool_permutation_invariance_bit_exact():
                             inv[inp.page_table.long()].to(torch.int32).contiguous(), inp.ctx_lens, inp.scale)
     O2, L2 = run_decode(inp2)
     assert torch.equal(O1, O2) and torch.equal(L1, L2)
+
+
+@pytest.mark.parametrize("nseq,Hkv,D,reach", [(1, 1, 64, 144), (3, 4, 64, 256), (128, 4, 64, 512), (129, 4, 64, 272), (1, 4, 128, 512),
+                                              (4, 2, 128, 512), (64, 4, 128, 256), (65, 4, 128, 256), (16, 4, 64, 4096), (3, 2, 64, 528)])
+@pytest.mark.parametrize("window", [-1, 70])
+def test_short_tables_and_eight_waves(nseq, Hkv, D, reach, window):
+    """Tables that are not cut into splits and workgroups of eight waves, on both sides of the rules (units, D, reach), with
+    contexts around the tiles of 32 keys, of 32 keys times four and eight waves, and page ids past the contexts that name
+    no page."""
+    import paper_2412_05496_amd as fa
+    edges = [1, 31, 32, 33, 63, 127, 128, 129, 160, 225, 255, 256, 257, 300, 480, 511, 512, 520, 700, 1030, 2049, 3000, 4095, 4096]
+    edges = [e for e in edges if e <= reach]
+    ctx = [edges[(5 * i + 3) % len(edges)] for i in range(nseq)]
+    wl = wlm.CFG5.scaled(B=nseq, Hq=2 * Hkv, Hkv=Hkv, D=D, page_size=16, max_pages=reach // 16)
+    inp = wlm.make_decode_inputs(wl, ctx_lens=ctx, slack_pages=2)
+    for b, n in enumerate(ctx):
+        inp.page_table[b, (n + 15) // 16:] = -5 if b % 2 else 1 << 30
+    mask_id, mask = None, None
+    if window >= 0:
+        mask_id, mask = fa.MASK_CTX_LEN_WINDOW, fo.and_mask(fo.ctx_len_mask(inp.ctx_lens), fo.sliding_window_mask(window))
+    print(f"[case] nseq={nseq} Hkv={Hkv} D={D} reach={reach} window={window} ctx={ctx[:12]}", flush=True)
+    O, LSE = run_decode(inp, fa.SCORE_IDENTITY, fa.ModParams(window=max(window, 0)), mask_id)
+    # (the oracle un-pages whole rows of the table)
+    inp.page_table.clamp_(0, inp.K_pool.shape[0] - 1)
+    compare(inp, O, LSE, fo.Identity(), mask)
