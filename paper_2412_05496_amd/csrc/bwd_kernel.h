@@ -4,7 +4,8 @@
 //     dV = P^T dO,  dP = dO V^T,  dS' = P * (dP - delta),  delta = rowsum(dO * O),
 //     dS = dS' * d score_mod / d s,  dQ = scale * dS K,  dK = scale * dS^T Q.
 // Three kernels, no floating-point atomics (results are deterministic):
-//   bwd_delta_kernel   -delta and the row constant of P = exp2(f(score) + rc) per query row.
+//   bwd_delta_kernel   -delta and the row constant of P = exp2(f(score) + rc) per query row (where the dQ kernel, which
+//                      can make them, does not run first).
 //   bwd_dkdv_kernel    one workgroup per 64 keys of one (b, hkv); walks the q-blocks listed for
 //                      that column of blocks (transposed BlockMask) for every query head of the
 //                      group; score tile in S = Q K^T orientation so that P and dS are the B
@@ -63,6 +64,7 @@ struct BwdArgs {
     int64_t ds_blocks;         // slots per head (capacity)
     float scale;
     flexattn_mod_params p;
+    bool make_delta;           // the dQ kernel works the row scalars out itself (and writes them)
 };
 
 // dS in memory.  The non-empty blocks of all BlockMask planes are numbered column by column of blocks,
@@ -102,7 +104,7 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const BwdArgs a) {
     const bf16x8 g = *(const bf16x8*)(a.dO + b * a.do_sb + h * a.do_sh + (int64_t)q * a.do_ss + c * 8);
     float s = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s += (float)o[i] * (float)g[i];
+    for (int i = 0; i < 8; ++i) s = __builtin_fmaf((float)o[i], (float)g[i], s);
 #pragma unroll
     for (int off = LPR / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
     if (c == 0) {
@@ -706,6 +708,34 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     const bool real_row = q_row < a.q_len;
     const int q_ld = min(q_row, a.q_len - 1);
     const int64_t cap_slot = ((int64_t)b * a.Hq + hq) * a.NR + row;
+    // -delta and the row constant of this lane's row from its dO (in the layout of an MFMA operand), as bwd_delta_kernel
+    // makes them, to the bit: dO is in registers here anyway, and the pass over O and dO is spared.  (us of the whole backward,
+    // with the pass -> this: causal, S = 1024, 64 x 16 heads 774 -> 741 at D = 64, 1501 -> 1442 at D = 128; window of 1024, S = 5000,
+    // 4 x 16 / 2 heads 340 -> 328, 685 -> 666; packed documents with ALiBi, S = 16384 410 -> 399; of the captured sums of a
+    // relative bias, S = 8192, window of 1024, D = 128 240 -> 224.)
+    auto row_scalars = [&](int64_t rowi, const bf16x8 (&g)[D / 16], float& rc, float& neg_delta) __attribute__((always_inline)) {
+        const bf16* op = a.O + b * a.o_sb + hq * a.o_sh + (int64_t)q_ld * a.o_ss + half * 8;
+        float s[D / 16];
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {
+            const bf16x8 o = *(const bf16x8*)(op + ks * 16);
+            s[ks] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s[ks] = __builtin_fmaf((float)o[i], (float)g[ks][i], s[ks]);
+        }
+        // (added up in the order of bwd_delta_kernel: the same bits)
+#pragma unroll
+        for (int n = D / 32; n > 0; n >>= 1)
+#pragma unroll
+            for (int i = 0; i < n; ++i) s[i] += s[i + n];
+        neg_delta = -(s[0] + swap_halves(s[0]));
+        const float l = a.LSE[rowi];
+        rc = ScoreMod<SCORE>(a.p, hq, a.scale).row_const(l == -INFINITY ? INFINITY : l * kLog2e);
+        if (!CAPTURED && real_row && half == 0) {
+            a.delta[rowi] = neg_delta;
+            a.lse2[rowi] = rc;
+        }
+    };
     if (T == 0) {
         if constexpr (CAPTURED) {
             if constexpr (ScoreMod<SCORE>::kRel)
@@ -714,6 +744,11 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
                 if (tid == 0) a.cap_alibi[cap_slot] = 0.0f;
         } else if (real_row) {
             for (int d0 = half * 8; d0 < D; d0 += 16) *(u32x4*)(dq_ptr + d0) = u32x4{0, 0, 0, 0};
+            if (a.make_delta && half == 0) {            // (no column of blocks lists these rows)
+                const int64_t rowi = ((int64_t)b * a.Hq + hq) * a.q_len + q_row;
+                a.delta[rowi] = 0.0f;
+                a.lse2[rowi] = -INFINITY;
+            }
         }
         return;
     }
@@ -731,7 +766,13 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         }
     }
     const int64_t rowi = ((int64_t)b * a.Hq + hq) * a.q_len + q_ld;
-    const float lse2 = a.lse2[rowi], neg_delta = a.delta[rowi];
+    float lse2, neg_delta;
+    if (CAPTURED || a.make_delta) {
+        row_scalars(rowi, dof, lse2, neg_delta);
+    } else {
+        lse2 = a.lse2[rowi];
+        neg_delta = a.delta[rowi];
+    }
     const i32x4 k_rsrc = make_rsrc(a.K + b * a.k_sb + hkv * a.k_sh, (uint32_t)((a.kv_len - 1) * a.k_ss + D) * 2u);
     const i32x4 v_rsrc = make_rsrc(a.V + b * a.v_sb + hkv * a.v_sh, (uint32_t)((a.kv_len - 1) * a.v_ss + D) * 2u);
     const int k_row_bytes = (int)a.k_ss * 2, v_row_bytes = (int)a.v_ss * 2;
@@ -1029,19 +1070,23 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
     const unsigned grid_kv = unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 64));
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
-    if (stages & FLEXATTN_BWD_DELTA) {
+    // dQ first where it makes the row scalars that dK/dV reads
+    if ((stages & FLEXATTN_BWD_DELTA) && !q && !(stages & kBwdStageCaptured)) {
         const size_t rows = (size_t)a.B * a.Hq * a.q_len;
         if (D == 128) hipLaunchKernelGGL((bwd_delta_kernel<128, SCORE>), dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, a);
         else hipLaunchKernelGGL((bwd_delta_kernel<64, SCORE>), dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, st, a);
     }
-    if (D == 128) {
-        if (kv) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, a);
-        if (q && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, a);
-        if (q && a.Bq == 64) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, a);
-    } else {
-        if (kv) launch_dkdv64<MASK, SCORE>(a, grid_kv, st);
-        if (q && a.Bq == 128) launch_dq64<MASK, SCORE>(a, grid_q, st);
-        if (q && a.Bq == 64) hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, a);
+    if (q) {
+        BwdArgs aq = a;
+        aq.make_delta = stages & FLEXATTN_BWD_DELTA;
+        if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
+        else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
+        else if (a.Bq == 128) launch_dq64<MASK, SCORE>(aq, grid_q, st);
+        else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
+    }
+    if (kv) {
+        if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, a);
+        else launch_dkdv64<MASK, SCORE>(a, grid_kv, st);
     }
     if (stages & kBwdStageCaptured) {
         if constexpr ((SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS)) != 0) {
