@@ -94,7 +94,7 @@ extern "C" int flexattn_forward(const flexattn_dims* dims, const flexattn_tensor
     a.q_len = dims->q_len; a.kv_len = dims->kv_len;
     a.NR = (dims->q_len + bm->Bq - 1) / bm->Bq; a.NC = (dims->kv_len + bm->Bk - 1) / bm->Bk;
     a.Bk = bm->Bk; a.sub = bm->Bk / kTileKV;
-    a.bm_Bm = bm->Bm; a.bm_Hm = bm->Hm;
+    a.bm_Bm = bm->Bm; a.bm_Hm = bm->Hm; a.Bq = bm->Bq;
     a.kv_num = bm->kv_num_blocks; a.kv_idx = bm->kv_indices;
     a.full_num = bm->full_kv_num_blocks; a.full_idx = bm->full_kv_indices;
     a.kv_order = bm->kv_order;
@@ -136,7 +136,7 @@ extern "C" int flexattn_paged_forward(const flexattn_dims* dims, const flexattn_
     a.q_len = dims->q_len; a.kv_len = dims->kv_len;
     a.NR = (dims->q_len + bm->Bq - 1) / bm->Bq; a.NC = (dims->kv_len + bm->Bk - 1) / bm->Bk;
     a.Bk = bm->Bk; a.sub = bm->Bk / kTileKV;
-    a.bm_Bm = bm->Bm; a.bm_Hm = bm->Hm;
+    a.bm_Bm = bm->Bm; a.bm_Hm = bm->Hm; a.Bq = bm->Bq;
     a.kv_num = bm->kv_num_blocks; a.kv_idx = bm->kv_indices;
     a.full_num = bm->full_kv_num_blocks; a.full_idx = bm->full_kv_indices;
     a.kv_order = bm->kv_order;

@@ -12,13 +12,15 @@
 // the A operand of K Q^T as they are, V^T fragments come out of the row-major V tile through the
 // transposing LDS read.  Q lives in registers for the whole kernel.
 //
-// Three forms of the loop over the tiles, one barrier per tile in each:
+// Four forms of the loop over the tiles, the first three with one barrier per tile:
 //   pipelined  while the VALU works on the softmax of tile t, the MFMA unit computes S^T of tile t + 1; K(t + 2) and
 //              V(t + 1) are in flight from HBM / L2 meanwhile;
 //   PLAIN      (D = 64) a 32-key block after the other, K and V one 64-key tile ahead: four waves per SIMD instead of
 //              three (fwd_plain, plain_pays);
 //   UNITS      (D = 128) the same with 32-key tiles in a ring of three, two tiles ahead: three instead of two
-//              (fwd_units, units_pay).
+//              (fwd_units, units_pay);
+//   SPLIT      for launches that leave the chip idle: the waves of a workgroup share 32 rows and take their keys in turn,
+//              each through LDS of its own, and merge (m, l, O) at the end (split_waves).
 #pragma once
 
 #include <type_traits>
@@ -52,6 +54,7 @@ struct FwdArgs {
     const int32_t* phys_full_idx;
     int64_t page_stride;
     int n_pool_pages;
+    int Bq;                // rows of a BlockMask block
 };
 
 constexpr int kTileKV = 64;   // keys per kernel tile
@@ -116,10 +119,43 @@ bool units_pay(const FwdArgs& a, int64_t grid) {
     }
     return (rule == FwdUnits::kAlways || a.kv_len <= kUnitsMaxKeys) && (int64_t)a.B * a.Hq * a.NR >= kUnitsMinGroups;
 }
+// The split form: a workgroup takes 32 rows instead of a row of blocks, and its waves the 32-key units of those rows in
+// turn.  A small launch ends with its longest chain of tiles on a wave, which this makes 4 or 8 times shorter, on up to four
+// times as many CUs; it costs each wave its own loads of K and V and a merge of the waves' results, which a full chip has no
+// room for.  us, a row of blocks -> 4 waves / 8 waves: causal, S = 4096, D = 64, 1 head 54 -> 23.5 / 15.8, 4 heads 55 -> 24.8 / 20.1, 8 54 ->
+// 33.5 / 34.0, 16 77 -> 59 / 64, 24 105 -> 90 / 96, 32 113 -> 117; D = 128, 1 head 78 -> 33.6 / 22.8, 4 78 -> 38.6 / 32.3, 8 77 -> 55.6 /
+// 62.4, 16 114 -> 109 / 124, 24 138 -> 162; S = 16384, 1 head 271 -> 105 / 69, D = 128 465 -> 146 / 105, 4 heads 362 -> 385; S = 1000, D = 64,
+// 8 / 32 / 64 heads 17.9 -> 8.8 / 7.3, 18.3 -> 15.5, 23.6 -> 24.4, D = 128, 8 / 16 / 32 heads 22.8 -> 11.9 / 10.5, 23.1 -> 15.1, 23.8 -> 24.5;
+// S = 300, D = 64, 8 / 64 / 128 heads 7.5 -> 5.4 / 5.2, 7.8 -> 7.1, 9.5 -> 11.9, D = 128, 8 / 32 / 64 heads 9.7 -> 7.0, 10.0 -> 9.0, 10.3 ->
+// 13.8; no mask, S = 2048, D = 64, 4 / 16 / 24 heads 32.6 -> 13.7 / 10.3, 32.7 -> 30.1, 43.6 -> 44.4, D = 128, 4 / 8 / 16 heads 41.3 -> 19.7
+// / 16.4, 40.6 -> 28.2, 44.5 -> 55.1; window of 512, S = 4096, D = 64, 8 / 16 heads 13.1 -> 12.2, 17.9 -> 22.0, D = 128, 4 / 8 heads 19.4 ->
+// 12.0 / 16.5, 19.2 -> 22.4; chunks of 518 on 9000 cached keys, 2 heads 126 -> 56 / 35, D = 128 178 -> 86 / 51; of 500, 64 heads, 130 -> 129,
+// D = 128 203 -> 256.
+// So: while the slices of 32 rows are no more than 4 per CU (D = 64) or 2 (D = 128, where a wave's loads weigh more), and
+// longer rows of uneven length, whose longest a full row of blocks leaves alone at the end, up to 12 and 4.
+// Returns the waves, 0: a workgroup per row of blocks.
+template <uint32_t MASK>
+int split_waves(const FwdArgs& a, int D) {
+    const int64_t slices = (int64_t)a.B * a.Hq * ((a.q_len + 31) / 32);
+    int64_t keys = a.kv_len;        // of the longest rows, as far as the host can tell
+    bool uneven = mask_uses(MASK, FLEXATTN_M_DOCUMENT) || (mask_uses(MASK, FLEXATTN_M_CAUSAL) && 2 * (int64_t)a.q_len > a.kv_len);
+    if (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW)) {
+        const int64_t reach = (int64_t)a.p.window + 1 + (mask_uses(MASK, FLEXATTN_M_PREFIX) ? a.p.prefix_len : 0);
+        uneven = uneven && 2 * reach > a.kv_len;
+        if (reach < keys) keys = reach;
+    }
+    int64_t most = D == 64 ? 4 * 256 : 2 * 256;
+    if (D == 64 && uneven && keys >= 2048) most = keys >= 4096 ? 12 * 256 : 8 * 256;
+    if (D == 128 && keys >= 1024) most = uneven && keys >= 2048 ? 4 * 256 : 3 * 256;
+    if (slices > most) return 0;
+    const bool eight = slices <= 256 ? keys > (D == 64 ? 256 : 512) : slices <= 512 && (D == 64 ? keys >= 2048 : uneven && keys >= 4096);
+    return eight ? 8 : 4;
+}
 // Waves per SIMD to compile for: what registers (512 per SIMD lane) and LDS admit.  The pipelined variants
 // with a relative-bias table would spill at three.
-template <int D, uint32_t SCORE, bool UNITS, bool PLAIN>
+template <int D, uint32_t SCORE, bool UNITS, bool PLAIN, bool SPLIT>
 constexpr int fwd_waves_per_simd() {
+    if (SPLIT) return 2;
     if (D != 64) return UNITS ? 3 : 2;
     if (PLAIN) return 4;
     return (SCORE & FLEXATTN_SCORE_REL_BIAS) ? 2 : 3;
@@ -127,33 +163,38 @@ constexpr int fwd_waves_per_simd() {
 
 // BOUNDED: the score_mod ends in a soft-cap small enough that the cap itself serves as the fixed
 // softmax maximum (see ScoreMod::bounded); chosen by the host from the cap value.
-// UNITS: 32-key units in a ring of three (fwd_units).  PLAIN: no tile pipeline (fwd_plain).
+// UNITS: 32-key units in a ring of three (fwd_units).  PLAIN: no tile pipeline (fwd_plain).  SPLIT: the NW waves share 32
+// rows and take the keys in turn (split_waves).
 // PAGED: the tiles of K and V are fetched from a paged pool through the converted block lists;
 // the mods keep seeing the logical key index.
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
 template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED, bool UNITS = false,
-          bool PLAIN = fwd_plain<D, NW, BOUNDED>()>
-__global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN>())) void fwd_kernel(const FwdArgs a) {
-    constexpr int Bq = NW * 32;
+          bool PLAIN = fwd_plain<D, NW, BOUNDED>(), bool SPLIT = false>
+__global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN, SPLIT>())) void fwd_kernel(const FwdArgs a) {
+    const int Bq = SPLIT ? a.Bq : NW * 32;
     constexpr int TILE = kTileKV * D;              // elements per LDS tile
 
-    // K(even), K(odd), V(even), V(odd); UNITS: three slots of 32 keys, K then V
-    __shared__ __attribute__((aligned(1024))) bf16 smem[(UNITS ? 3 : 4) * TILE];
+    // K(even), K(odd), V(even), V(odd); UNITS: three slots of 32 keys, K then V; SPLIT: 32 keys of K, then V, for each wave
+    __shared__ __attribute__((aligned(1024))) bf16 smem[(SPLIT ? NW : UNITS ? 3 : 4) * TILE];
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];           // relative-bias row of the head
     using Mask = PartialMask<MASK>;
-    __shared__ __attribute__((aligned(256))) uint32_t s_tag[UNITS ? 3 : 2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys, per buffer
+    __shared__ __attribute__((aligned(256))) uint32_t s_tag[SPLIT ? NW : UNITS ? 3 : 2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys, per buffer (SPLIT: wave)
 
-    constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || PLAIN);
+    constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || PLAIN || SPLIT);
     __shared__ uint32_t s_qtag[Mask::kTags ? NW * 64 : 1];            // each lane's own tag (its query's)
     __shared__ uint8_t s_hidden[kHiddenTable ? kHiddenTiles : 1];    // CanvasBlocks::hidden_bits of the first tiles
 
     // ---- workgroup -> (b, hkv, g, row of blocks).  Rows are taken longest first (the BlockMask's work order), or
     // last-first without one (causal-like masks: longest first).
-    int unit, rem;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR, unit, rem)) return;
+    int unit, rem, slice = 0;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (SPLIT ? Bq / 32 : 1), unit, rem)) return;
+    if constexpr (SPLIT) {
+        slice = rem & (Bq / 32 - 1);                // which 32 rows of the block
+        rem >>= Bq == 128 ? 2 : 1;
+    }
     const int g = rem % a.G;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv, hq = hkv * a.G + g;
     const int64_t plane = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0);
@@ -162,7 +203,9 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int q_row = row * Bq + w * 32 + l32;
+    const int wave_rows = row * Bq + (SPLIT ? slice : w) * 32;     // first of the wave's 32 rows
+    const int q_row = wave_rows + l32;
+    if (SPLIT && wave_rows >= a.q_len) return;
 
     const int64_t line = plane * a.NR + row;
     const int n_full = ldc(a.full_num + line), n_part = ldc(a.kv_num + line);
@@ -202,7 +245,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
                         int& soff) __attribute__((always_inline)) {
         if constexpr (PAGED) {
             const int pg = min(max(page, 0), a.n_pool_pages - 1);
-            rsrc = make_rsrc(head + (int64_t)pg * a.page_stride + row * D, (uint32_t)((UNITS ? 32 : kTileKV) * D * 2));
+            rsrc = make_rsrc(head + (int64_t)pg * a.page_stride + row * D, (uint32_t)((UNITS || SPLIT ? 32 : kTileKV) * D * 2));
             soff = 0;
         } else {
             rsrc = whole;
@@ -213,7 +256,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     const Score smod(a.p, hq, a.scale, lds_addr(s_rel));
     smod.fill_table(tid, NW * 64);                  // visible after the prologue's barrier
     const int q_pos = q_ld + q_offset_of(a.p, b);   // as the mods see it
-    const int q_wave_min = row * Bq + w * 32 + q_offset_of(a.p, b);   // the wave's rows: q_wave_min .. +31
+    const int q_wave_min = wave_rows + q_offset_of(a.p, b);   // the wave's rows: q_wave_min .. +31
     const Mask mask(a.p, b, a.kv_len);
     // the lane's own tag waits in LDS as well: a register held for it over the whole kernel ends in spills
     // whose reloads wait for the tile loads
@@ -228,19 +271,19 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     // come by LDS-DMA (keys past the end read as 0), pixels are worked out by one of the waves.
     auto make_tags = [&](int buf, int kv0, int turn) __attribute__((always_inline)) {
         if constexpr (Mask::kDoc) {
-            if (w == 0)
+            if (SPLIT || w == 0)
                 dma_global_dword(lds_addr(&s_tag[buf][0]), a.p.doc_ids + (int64_t)b * a.p.doc_stride_b,
                                  min(kv0 + lane, a.kv_len - 1) * 4);
         }
         if constexpr (Mask::kCanvas) {
-            if (w == (turn & (NW - 1))) s_tag[buf][lane] = mask.key_pixel(min(kv0 + lane, a.kv_len - 1));
+            if (SPLIT || w == (turn & (NW - 1))) s_tag[buf][lane] = mask.key_pixel(min(kv0 + lane, a.kv_len - 1));
         }
     };
-    if constexpr (kHiddenTable) fill_hidden_tiles<NW>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, a.sub, a.Bk, row * Bq, tid);
+    if constexpr (kHiddenTable) fill_hidden_tiles<SPLIT ? 1 : NW, NW * 64>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, a.sub, a.Bk, SPLIT ? wave_rows : row * Bq, tid);
     // 32-key blocks of tile t that are hidden from this wave (bit 0, bit 1); visible after the prologue's barrier
     auto hidden_of = [&](int t) __attribute__((always_inline)) -> uint32_t {
         if constexpr (!kHiddenTable) return 0u;
-        else return t < min(T, kHiddenTiles) ? ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (2 * w)) & 3u : 0u;
+        else return t < min(T, kHiddenTiles) ? ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (SPLIT ? 0 : 2 * w)) & 3u : 0u;
     };
     const float inv_neg2c = smod.capl2 > 0.0f ? -0.5f / smod.capl2 : 0.0f;   // 1 / (-2 cap log2 e)
 
@@ -251,7 +294,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     bool part_t = false, part_t1 = false, part_t2 = false;
     int pg_t = 0, pg_t1 = 0, pg_t2 = 0, pr_t = 0, pr_t1 = 0, pr_t2 = 0;   // PAGED: page, row in page
     const uint32_t smem_bytes = lds_addr(smem);
-    const WaveTileLoader<D, NW> k_loader(a.k_ss, w, lane), v_loader(a.v_ss, w, lane);
+    const WaveTileLoader<D, SPLIT ? 4 : NW> k_loader(a.k_ss, w, lane), v_loader(a.v_ss, w, lane);   // (SPLIT has its own)
     // buf = tile index & 1
     auto load_k = [&](int buf, int kv0, int page, int row) {
         i32x4 rsrc;
@@ -426,7 +469,118 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         if constexpr (Mask::kCanvas) return (bits & (1u << kvb)) != 0;
         else return partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31);
     };
-    if constexpr (UNITS) {
+    if constexpr (SPLIT) {
+        // Wave w takes the 32-key units w, w + NW, ... that are not hidden from its rows, through LDS of its own and
+        // without a barrier.  K(next) is asked for when S^T has been computed, V(next) after P V: each has the other half of the
+        // turn to arrive.
+        constexpr uint32_t UT = 32 * D * 2;
+        using L = WaveTileLoader<D, 1, 32>;
+        const L k_load(a.k_ss, 0, lane), v_load(a.v_ss, 0, lane);
+        const uint32_t k_lds = smem_bytes + (uint32_t)w * 2 * UT, v_lds = k_lds + UT;
+        const int TU = 2 * T, per_block = 2 * a.sub, shift = a.sub == 1 ? 1 : 2, n_blocks = n_full + n_part;
+        auto at = [&](const int32_t* full, const int32_t* part, int u) __attribute__((always_inline)) {
+            const int p = min(u >> shift, n_blocks - 1);
+            return ldc(p < n_full ? full + line * a.NC + p : part + line * a.NC + (p - n_full));
+        };
+        int u_next = w, blk_next = at(a.full_idx, a.kv_idx, w), pg_next = PAGED ? at(a.phys_full_idx, a.phys_kv_idx, w) : 0;
+        int kv = 0, page = 0, prow = 0;                 // the unit that is loaded next
+        bool partial = false;
+        auto advance = [&]() __attribute__((always_inline)) {
+            while (u_next < TU) {
+                const int u = u_next, s0 = (u & (per_block - 1)) * 32;
+                kv = blk_next * a.Bk + s0;
+                page = pg_next;
+                prow = s0;
+                partial = (u >> shift) >= n_full;
+                u_next += NW;
+                blk_next = at(a.full_idx, a.kv_idx, u_next);
+                if constexpr (PAGED) pg_next = at(a.phys_full_idx, a.phys_kv_idx, u_next);
+                if (!hidden_block(hidden_of(u >> 1) >> (u & 1), partial, kv, 0)) return true;
+            }
+            return false;
+        };
+        auto load = [&](const L& loader, const bf16* head, i32x4 whole, int row_bytes, uint32_t lds) __attribute__((always_inline)) {
+            i32x4 rsrc;
+            int soff;
+            tile_src(head, whole, row_bytes, kv, page, prow, rsrc, soff);
+            loader.start(rsrc, lds, soff);
+        };
+        if constexpr (kHiddenTable || Score::kRel) __syncthreads();
+        bool more = advance();
+        if (more) {
+            if (partial) make_tags(w, kv, 0);
+            load(k_load, k_head, k_rsrc, k_row_bytes, k_lds);
+            load(v_load, v_head, v_rsrc, v_row_bytes, v_lds);
+        }
+        while (more) {
+            wait_vmem_but<L::NI>();                     // K and the tags are here
+            asm volatile("" ::: "memory");
+            const int kv_now = kv;
+            const bool partial_now = partial;
+            f32x16 s;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < D / 16; ++ks) s = mfma32(k_reader.read(k_lds, 0, ks), qf[ks], s);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");              // (K has left LDS)
+            more = advance();
+            if (more) load(k_load, k_head, k_rsrc, k_row_bytes, k_lds);
+            bf16x8 pf[2];
+            softmax(s, kv_now, partial_now, w, 0, pf);
+            if (more && partial) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // (the tags have been read)
+                make_tags(w, kv, 0);
+            }
+            // V is here; K(next) and its tags may be under way
+            if (!more) wait_vmem();
+            else if (Mask::kDoc && partial) wait_vmem_but<L::NI + 1>();
+            else wait_vmem_but<L::NI>();
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) oacc[db] = mfma32(v_reader.read(v_lds, 16 * c, db), pf[c], oacc[db]);
+            if (more) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // (V has left LDS)
+                load(v_load, v_head, v_rsrc, v_row_bytes, v_lds);
+            }
+        }
+        // ---- the waves' (m, l, O) become one: every wave leaves its O in its own tiles, quad by quad, and adds up every
+        // NW-th quad of all waves
+        __shared__ float s_ml[NW][2][32];
+        const float l_wave = l_run + swap_halves(l_run);
+        if (half == 0) {
+            s_ml[w][0][l32] = m_run;
+            s_ml[w][1][l32] = l_wave;
+        }
+        f32x4* mine = (f32x4*)(smem + w * TILE) + lane;
+#pragma unroll
+        for (int q = 0; q < D / 8; ++q)
+            mine[q * 64] = f32x4{oacc[q >> 2][4 * (q & 3)], oacc[q >> 2][4 * (q & 3) + 1], oacc[q >> 2][4 * (q & 3) + 2], oacc[q >> 2][4 * (q & 3) + 3]};
+        __syncthreads();
+        float m = -INFINITY, l = 0.0f, wgt[NW];
+#pragma unroll
+        for (int v = 0; v < NW; ++v) m = fmaxf(m, s_ml[v][0][l32]);
+        const float m_from = m == -INFINITY ? 0.0f : m;     // (no key at all: every weight 0)
+#pragma unroll
+        for (int v = 0; v < NW; ++v) {
+            wgt[v] = fast_exp2(s_ml[v][0][l32] - m_from);
+            l += wgt[v] * s_ml[v][1][l32];
+        }
+        if (!real_row) return;
+        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+        for (int q = w; q < D / 8; q += NW) {
+            f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int v = 0; v < NW; ++v) o += wgt[v] * *((const f32x4*)(smem + v * TILE) + q * 64 + lane);
+            u32x2 pk;
+            pk[0] = pack_bf16(o[0] * inv, o[1] * inv);
+            pk[1] = pack_bf16(o[2] * inv, o[3] * inv);
+            *(u32x2*)(o_ptr + 8 * q + 4 * half) = pk;
+        }
+        if (w == 0 && half == 0) *lse_ptr = l > 0.0f ? (m + fast_log2(l)) * kLn2 : -INFINITY;
+        return;
+    } else if constexpr (UNITS) {
         // 32 keys at a time through a ring of three slots, two units ahead: unit u + 2 is asked for when every
         // wave is done with u - 1, whose slot it takes.
         constexpr uint32_t UT = 32 * D * 2;
@@ -559,7 +713,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
             }
             bf16x8 pf[2];
             if constexpr (HAS_NEXT) {
-                using L = WaveTileLoader<D, NW>;
+                using L = decltype(k_loader);
                 constexpr int NP = 2 * L::NI, NMQ = 2 * (D / 16);
                 qk(std::integral_constant<int, BUF ^ 1>{}, s_next, [&](auto m_tag) {
                     static_for<0, NP>([&](auto p_tag) {
@@ -622,6 +776,14 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 template <uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED>
 int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
     const unsigned grid = unit_grid(a.B * a.Hkv, a.G * a.NR);
+    if (const int waves = split_waves<MASK>(a, D)) {
+        const dim3 slices(unit_grid(a.B * a.Hkv, a.G * a.NR * (Bq / 32)));
+        if (D == 128 && waves == 8) hipLaunchKernelGGL((fwd_kernel<128, 8, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(512), 0, st, a);
+        else if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(256), 0, st, a);
+        else if (waves == 8) hipLaunchKernelGGL((fwd_kernel<64, 8, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(512), 0, st, a);
+        else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(256), 0, st, a);
+        return FLEXATTN_OK;
+    }
 #define FLEXATTN_LAUNCH(DD, NW)                                                                            \
     hipLaunchKernelGGL((fwd_kernel<DD, NW, MASK, SCORE, BOUNDED, PAGED>), dim3(grid), dim3(NW * 64), 0, st, a); \
     return FLEXATTN_OK;

@@ -264,14 +264,14 @@ struct TileWalk {
 // nothing).  Rows of more tiles are longer than any canvas of up to 256 x 256 pixels makes them; their other
 // tiles are computed whole.
 constexpr int kHiddenTiles = 1024;
-template <int NW>
+template <int NW, int THREADS = NW * 64>
 __device__ __forceinline__ void fill_hidden_tiles(uint8_t* out, const flexattn_mod_params& p,
                                                   const int32_t* part_idx, int n_full, int T, int sub, int Bk, int q0, int tid) {
     const CanvasBlocks cb(p);
     CanvasBlocks::Box qw[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) qw[w] = cb.windows(q0 + 32 * w);
-    for (int i = tid; i < min(T, kHiddenTiles); i += NW * 64) {
+    for (int i = tid; i < min(T, kHiddenTiles); i += THREADS) {
         const int pos = i / sub, kv0 = (i - pos * sub) * 64;
         out[i] = pos < n_full ? 0 : (uint8_t)cb.hidden_bits(qw, part_idx[pos - n_full] * Bk + kv0);
     }
