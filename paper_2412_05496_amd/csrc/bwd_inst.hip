@@ -1,5 +1,5 @@
 // One backward-kernel variant per translation unit: compile with -DFLEXATTN_VARIANT=<index into kVariants>.
-#include "bwd_kernel.h"
+#include "bwd_split.h"
 #include "variants.h"
 
 #ifndef FLEXATTN_VARIANT

@@ -67,6 +67,8 @@ struct BwdArgs {
     bool make_delta;           // the dQ kernel works the row scalars out itself (and writes them)
 };
 
+constexpr uint32_t kBwdStageCaptured = 8u;   // internal: the captured-tensor sums instead of dQ
+
 // dS in memory.  The non-empty blocks of all BlockMask planes are numbered column by column of blocks,
 // in the order of the merged (FULL, then PARTIAL) column lists: that number is the block's slot.
 // Heads that share a plane share the numbering and differ in `rep`.  A block is cut into Bk / 64 tiles
@@ -113,6 +115,32 @@ __global__ __launch_bounds__(256) void bwd_delta_kernel(const BwdArgs a) {
         const ScoreMod<SCORE> smod(a.p, h, a.scale);
         a.lse2[row] = smod.row_const((l == -INFINITY) ? INFINITY : l * kLog2e);
     }
+}
+
+// -delta and the row constant of a lane's row from its dO (in the layout of an MFMA operand), as bwd_delta_kernel
+// makes them, to the bit: dO is in the dQ kernels' registers anyway, and the pass over O and dO is spared.  (us of the
+// whole backward, with the pass -> this: causal, S = 1024, 64 x 16 heads 774 -> 741 at D = 64, 1501 -> 1442 at D = 128; window of
+// 1024, S = 5000, 4 x 16 / 2 heads 340 -> 328, 685 -> 666; packed documents with ALiBi, S = 16384 410 -> 399; of the captured
+// sums of a relative bias, S = 8192, window of 1024, D = 128 240 -> 224.)
+template <int D, uint32_t SCORE>
+__device__ __forceinline__ void row_scalars(const BwdArgs& a, int b, int hq, int q, int half, const bf16x8 (&g)[D / 16], float& rc, float& neg_delta) {
+    const bf16* op = a.O + b * a.o_sb + hq * a.o_sh + (int64_t)q * a.o_ss + half * 8;
+    float s[D / 16];
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) {
+        const bf16x8 o = *(const bf16x8*)(op + ks * 16);
+        s[ks] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s[ks] = __builtin_fmaf((float)o[i], (float)g[ks][i], s[ks]);
+    }
+    // (added up in the order of bwd_delta_kernel: the same bits)
+#pragma unroll
+    for (int n = D / 32; n > 0; n >>= 1)
+#pragma unroll
+        for (int i = 0; i < n; ++i) s[i] += s[i + n];
+    neg_delta = -(s[0] + swap_halves(s[0]));
+    const float l = a.LSE[((int64_t)b * a.Hq + hq) * a.q_len + q];
+    rc = ScoreMod<SCORE>(a.p, hq, a.scale).row_const(l == -INFINITY ? INFINITY : l * kLog2e);
 }
 
 // Neighborhood masks: bit kb + 2 x is set if the mask hides the block of the 32 query rows q0 + 32 x .. and the 32
@@ -708,34 +736,6 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     const bool real_row = q_row < a.q_len;
     const int q_ld = min(q_row, a.q_len - 1);
     const int64_t cap_slot = ((int64_t)b * a.Hq + hq) * a.NR + row;
-    // -delta and the row constant of this lane's row from its dO (in the layout of an MFMA operand), as bwd_delta_kernel
-    // makes them, to the bit: dO is in registers here anyway, and the pass over O and dO is spared.  (us of the whole backward,
-    // with the pass -> this: causal, S = 1024, 64 x 16 heads 774 -> 741 at D = 64, 1501 -> 1442 at D = 128; window of 1024, S = 5000,
-    // 4 x 16 / 2 heads 340 -> 328, 685 -> 666; packed documents with ALiBi, S = 16384 410 -> 399; of the captured sums of a
-    // relative bias, S = 8192, window of 1024, D = 128 240 -> 224.)
-    auto row_scalars = [&](int64_t rowi, const bf16x8 (&g)[D / 16], float& rc, float& neg_delta) __attribute__((always_inline)) {
-        const bf16* op = a.O + b * a.o_sb + hq * a.o_sh + (int64_t)q_ld * a.o_ss + half * 8;
-        float s[D / 16];
-#pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) {
-            const bf16x8 o = *(const bf16x8*)(op + ks * 16);
-            s[ks] = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) s[ks] = __builtin_fmaf((float)o[i], (float)g[ks][i], s[ks]);
-        }
-        // (added up in the order of bwd_delta_kernel: the same bits)
-#pragma unroll
-        for (int n = D / 32; n > 0; n >>= 1)
-#pragma unroll
-            for (int i = 0; i < n; ++i) s[i] += s[i + n];
-        neg_delta = -(s[0] + swap_halves(s[0]));
-        const float l = a.LSE[rowi];
-        rc = ScoreMod<SCORE>(a.p, hq, a.scale).row_const(l == -INFINITY ? INFINITY : l * kLog2e);
-        if (!CAPTURED && real_row && half == 0) {
-            a.delta[rowi] = neg_delta;
-            a.lse2[rowi] = rc;
-        }
-    };
     if (T == 0) {
         if constexpr (CAPTURED) {
             if constexpr (ScoreMod<SCORE>::kRel)
@@ -768,7 +768,11 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     const int64_t rowi = ((int64_t)b * a.Hq + hq) * a.q_len + q_ld;
     float lse2, neg_delta;
     if (CAPTURED || a.make_delta) {
-        row_scalars(rowi, dof, lse2, neg_delta);
+        row_scalars<D, SCORE>(a, b, hq, q_ld, half, dof, lse2, neg_delta);
+        if (!CAPTURED && real_row && half == 0) {
+            a.delta[rowi] = neg_delta;
+            a.lse2[rowi] = lse2;
+        }
     } else {
         lse2 = a.lse2[rowi];
         neg_delta = a.delta[rowi];
@@ -1016,89 +1020,6 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
             pk[1] = pack_bf16(dq[db][4 * rg + 2] * qscale, dq[db][4 * rg + 3] * qscale);
             *(u32x2*)(dq_ptr + db * 32 + 8 * rg + 4 * half) = pk;
         }
-}
-
-// dQ at D = 64 with four waves: whether leaving hidden blocks out pays.  The test between the two blocks of a tile
-// keeps their work apart, which shows where at most two workgroups share a CU: masks that hide little more than a
-// diagonal are left out only beyond that (us, computed whole -> left out, causal: one sequence, S = 4096, 8 heads 58.8 ->
-// 64.1; S = 8192, 8 heads 131 -> 136; S = 2048, 2 x 16 heads 47.1 -> 47.2, 4 x 16 75.6 -> 75.9; S = 4096, 64 heads
-// 227.8 -> 222.9; S = 1024, 64 x 16 heads 298.6 -> 285.8).
-// dK/dV at D = 64: own rows, but for launches that are as long as their longest column of blocks, where a workgroup is
-// alone on its CU most of the time: there the exchange is faster, whose operands are read further ahead.  They are
-// told by what the columns' steps make of 768 workgroups (three per CU) beside the longest column: a third of it (270 of
-// 768 for a mask whose columns are as long as the longest).  Windows and documents have columns of about one length and
-// hidden blocks to leave out, a soft-cap more vector work than the operands' reads take.
-// us, exchange -> own rows: causal, S = 1024, 8 heads 16.8 -> 18.7; S = 4096, 8 heads 57.7 -> 59.8; S = 2048, 16 heads 38.7 -> 38.1, 32 heads 56.5 -> 54.3; no mask, S = 1024, 8 heads 16.9 -> 17.9, S = 4096, 8 heads
-// 78.2 -> 76.7; window 512 or prefix 128, S = 8192, 16 heads 163 -> 170, S = 2048, 32 heads 55.5 -> 53.8.
-template <uint32_t MASK>
-bool own_rows_pay(const BwdArgs& a, unsigned grid) {
-    const float longest = a.q_len / 64.0f;          // steps
-    float mean = MASK == FLEXATTN_MASK_NONE ? longest : 0.5f * longest;
-    if (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW))
-        mean = fminf(longest, a.p.window / 64.0f + 2.0f + longest * a.p.prefix_len / a.kv_len);
-    return grid * mean > 270.0f * longest;
-}
-template <uint32_t MASK, uint32_t SCORE>
-void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
-    constexpr bool even = mask_uses(MASK, FLEXATTN_M_DOCUMENT) ||
-                          (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) && !mask_uses(MASK, FLEXATTN_M_PREFIX));
-    if constexpr (dkdv_own_rows<64, MASK, SCORE>() && !even && !(SCORE & FLEXATTN_SCORE_SOFTCAP)) {
-        if (!own_rows_pay<MASK>(a, grid)) {
-            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false>), dim3(grid), dim3(256), 0, st, a);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
-}
-
-template <uint32_t MASK, uint32_t SCORE>
-void launch_dq64(const BwdArgs& a, unsigned grid, hipStream_t st) {
-    constexpr bool often = mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
-    if constexpr (!often) {
-        if (grid <= 2 * 256) {
-            hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, false>), dim3(grid), dim3(256), 0, st, a);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
-}
-
-constexpr uint32_t kBwdStageCaptured = 8u;   // internal: the captured-tensor sums instead of dQ
-
-template <uint32_t MASK, uint32_t SCORE>
-int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st) {
-    const unsigned grid_kv = unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 64));
-    const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
-    const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
-    // dQ first where it makes the row scalars that dK/dV reads
-    if ((stages & FLEXATTN_BWD_DELTA) && !q && !(stages & kBwdStageCaptured)) {
-        const size_t rows = (size_t)a.B * a.Hq * a.q_len;
-        if (D == 128) hipLaunchKernelGGL((bwd_delta_kernel<128, SCORE>), dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((bwd_delta_kernel<64, SCORE>), dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, st, a);
-    }
-    if (q) {
-        BwdArgs aq = a;
-        aq.make_delta = stages & FLEXATTN_BWD_DELTA;
-        if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
-        else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
-        else if (a.Bq == 128) launch_dq64<MASK, SCORE>(aq, grid_q, st);
-        else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
-    }
-    if (kv) {
-        if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, a);
-        else launch_dkdv64<MASK, SCORE>(a, grid_kv, st);
-    }
-    if (stages & kBwdStageCaptured) {
-        if constexpr ((SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS)) != 0) {
-            if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);
-            else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE, true>), dim3(grid_q), dim3(128), 0, st, a);
-            else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);
-            else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE, true>), dim3(grid_q), dim3(128), 0, st, a);
-        } else {
-            return FLEXATTN_ERR_UNSUPPORTED;     // this score_mod captures no tensor
-        }
-    }
-    return FLEXATTN_OK;
 }
 
 }  // namespace flexattn

@@ -1,0 +1,625 @@
+// dQ and dK/dV for launches that leave the chip idle: the waves of a workgroup share 32 query rows (dQ) or 32 keys (dK/dV)
+// and take the 32-wide units of the other index in turn, each through LDS of its own and without a barrier; their sums
+// are added up at the end.  What ends a small launch is a wave's chain of units, which this makes as many times shorter as
+// there are waves, on two to four times as many CUs.  The arithmetic is that of bwd_dq_kernel and bwd_dkdv_kernel
+// (bwd_kernel.h), in the same precision.
+#pragma once
+
+#include "bwd_kernel.h"
+
+namespace flexattn {
+
+// Adds up what NW waves hold in QUADS register quads each: a wave leaves its quads in `mine` (QUADS KiB of LDS, 64 lanes x 16
+// bytes a quad), and after the barrier takes every NW-th quad of all waves (`all`: the regions side by side).
+template <int NW, int QUADS, typename F>
+__device__ __forceinline__ void add_quads(f32x4* all, int w, int lane, const f32x4 (&quads)[QUADS], F&& out) {
+    f32x4* mine = all + w * (QUADS * 64) + lane;
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) mine[q * 64] = quads[q];
+    __syncthreads();
+    for (int q = w; q < QUADS; q += NW) {
+        f32x4 o = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int v = 0; v < NW; ++v) o += all[v * (QUADS * 64) + q * 64 + lane];
+        out(q, o);
+    }
+}
+
+// M0 RULE: these kernels fill LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the compiler's back.  Keep
+// every register array in them indexed by compile-time constants (no movrel / s_set_gpr_idx code, which would also use M0)
+// and add no other LDS-DMA or M0-based construct.
+//
+// dQ.  A unit's K and V are asked for when the one before has left LDS: K's rows for S^T, K^T's fragments for dQ (kept in
+// registers meanwhile) and V's rows for dP^T.
+template <int D, int NW, uint32_t MASK, uint32_t SCORE>
+__global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(const BwdArgs a) {
+    constexpr uint32_t UT = 32 * D * 2;
+    using Score = ScoreMod<SCORE, true>;
+    using Mask = PartialMask<MASK>;
+    using L = WaveTileLoader<D, 1, 32>;
+    __shared__ __attribute__((aligned(1024))) bf16 smem[NW * 64 * D];       // per wave: K, V
+    __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];
+    __shared__ __attribute__((aligned(256))) uint32_t s_tag[NW][Mask::kTags ? 64 : 4];
+    __shared__ uint8_t s_hidden[Mask::kCanvas ? kHiddenTiles : 1];
+
+    int unit, rem;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (a.Bq / 32), unit, rem)) return;
+    const int slice = rem & (a.Bq / 32 - 1);
+    rem >>= a.Bq == 128 ? 2 : 1;
+    const int g = rem % a.G;
+    const int b = unit / a.Hkv, hkv = unit % a.Hkv, hq = hkv * a.G + g;
+    const int64_t plane = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0);
+    const int row = a.kv_order ? min(max(ldc(a.kv_order + plane * a.NR + rem / a.G), 0), a.NR - 1) : a.NR - 1 - rem / a.G;
+    const int q0 = row * a.Bq + slice * 32;
+    if (q0 >= a.q_len) return;
+
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q_row = q0 + l32;
+    const bool real_row = q_row < a.q_len;
+    const int q_ld = min(q_row, a.q_len - 1);
+    const int64_t line = plane * a.NR + row;
+    const int n_full = ldc(a.full_kv_num + line), n_part = ldc(a.kv_num + line);
+    const int sub = a.Bk / 64, T = (n_full + n_part) * sub;
+    bf16* dq_ptr = a.dQ + b * a.dq_sb + hq * a.dq_sh + (int64_t)q_row * a.dq_ss;
+    const int64_t rowi = ((int64_t)b * a.Hq + hq) * a.q_len + q_ld;
+    if (T == 0) {
+        if (real_row && w == 0) {
+            for (int d0 = half * 8; d0 < D; d0 += 16) *(u32x4*)(dq_ptr + d0) = u32x4{0, 0, 0, 0};
+            if (a.make_delta && half == 0) {
+                a.delta[rowi] = 0.0f;
+                a.lse2[rowi] = -INFINITY;
+            }
+        }
+        return;
+    }
+
+    bf16x8 qf[D / 16], dof[D / 16];
+    {
+        const bf16* qp = a.Q + b * a.q_sb + hq * a.q_sh + (int64_t)q_ld * a.q_ss + half * 8;
+        const bf16* dp = a.dO + b * a.do_sb + hq * a.do_sh + (int64_t)q_ld * a.do_ss + half * 8;
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) {
+            qf[ks] = *(const bf16x8*)(qp + ks * 16);
+            dof[ks] = *(const bf16x8*)(dp + ks * 16);
+        }
+    }
+    float rc, neg_delta;
+    if (a.make_delta) {
+        row_scalars<D, SCORE>(a, b, hq, q_ld, half, dof, rc, neg_delta);
+        if (w == 0 && real_row && half == 0) {
+            a.delta[rowi] = neg_delta;
+            a.lse2[rowi] = rc;
+        }
+    } else {
+        rc = a.lse2[rowi];
+        neg_delta = a.delta[rowi];
+    }
+    const i32x4 k_rsrc = make_rsrc(a.K + b * a.k_sb + hkv * a.k_sh, (uint32_t)((a.kv_len - 1) * a.k_ss + D) * 2u);
+    const i32x4 v_rsrc = make_rsrc(a.V + b * a.v_sb + hkv * a.v_sh, (uint32_t)((a.kv_len - 1) * a.v_ss + D) * 2u);
+    const Score smod(a.p, hq, a.scale, lds_addr(s_rel));
+    smod.fill_table(tid, NW * 64);
+    const int q_off = q_offset_of(a.p, b), q_pos = q_ld + q_off, q_wave_min = q0 + q_off;
+    const Mask mask(a.p, b, a.kv_len);
+    uint32_t q_tag = 0;
+    bool scattered = false;
+    if constexpr (Mask::kDoc) {
+        q_tag = (uint32_t)(a.p.doc_ids + (int64_t)b * a.p.doc_stride_b)[q_pos];
+        scattered = Mask::scattered_ids(q_tag);
+    }
+    if constexpr (Mask::kCanvas) {
+        q_tag = mask.query_pixel(q_pos);
+        fill_hidden_tiles<1, NW * 64>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, sub, a.Bk, q0, tid);
+    }
+    auto make_tags = [&](int kv0) __attribute__((always_inline)) {
+        if constexpr (Mask::kDoc)
+            dma_global_dword(lds_addr(&s_tag[w][0]), a.p.doc_ids + (int64_t)b * a.p.doc_stride_b, min(kv0 + lane, a.kv_len - 1) * 4);
+        if constexpr (Mask::kCanvas) s_tag[w][lane] = mask.key_pixel(min(kv0 + lane, a.kv_len - 1));
+    };
+
+    const L k_load(a.k_ss, 0, lane), v_load(a.v_ss, 0, lane);
+    const uint32_t k_lds = lds_addr(smem) + (uint32_t)w * 2 * UT, v_lds = k_lds + UT;
+    const RowReader<D> rows(l32, half);
+    const TrReader<D> cols(lane);
+    const int TU = 2 * T, per_block = 2 * sub, shift = sub == 1 ? 1 : 2, n_blocks = n_full + n_part;
+    auto block_at = [&](int u) __attribute__((always_inline)) {
+        const int p = min(u >> shift, n_blocks - 1);
+        return ldc(p < n_full ? a.full_kv_idx + line * a.NC + p : a.kv_idx + line * a.NC + (p - n_full));
+    };
+    int u_next = w, blk_next = block_at(w), kv = 0;
+    bool partial = false;
+    auto advance = [&]() __attribute__((always_inline)) {       // the wave's next unit that is not hidden from all rows
+        while (u_next < TU) {
+            const int u = u_next;
+            kv = blk_next * a.Bk + (u & (per_block - 1)) * 32;
+            partial = (u >> shift) >= n_full;
+            u_next += NW;
+            blk_next = block_at(u_next);
+            bool hid = false;
+            if constexpr (Mask::kCanvas) hid = (u >> 1) < kHiddenTiles && ((__builtin_amdgcn_readfirstlane((int)s_hidden[u >> 1]) >> (u & 1)) & 1);
+            else hid = partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31);
+            if (!hid) return true;
+        }
+        return false;
+    };
+    auto load = [&]() __attribute__((always_inline)) {
+        k_load.start(k_rsrc, k_lds, kv * (int)a.k_ss * 2);
+        v_load.start(v_rsrc, v_lds, kv * (int)a.v_ss * 2);
+    };
+
+    f32x16 dq[D / 32];
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dq[db][r] = 0.0f;
+    if constexpr (Mask::kCanvas || Score::kRel) __syncthreads();
+    bool more = advance();
+    if (more) {
+        if (partial) make_tags(kv);
+        load();
+    }
+    while (more) {
+        wait_vmem();
+        asm volatile("" ::: "memory");
+        const int kv_now = kv;
+        const bool masked = partial && !mask.full(q_wave_min, q_wave_min + 31, kv, kv + 31);
+        f32x16 sacc, dpacc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            sacc[r] = 0.0f;
+            dpacc[r] = neg_delta;                   // dP - delta comes out of the accumulation
+        }
+        if constexpr (D == 64) {
+            read_ahead<D / 8>([&](auto m) { return rows.read((decltype(m)::value & 1) ? v_lds : k_lds, 0, decltype(m)::value >> 1); },
+                              [&](auto m, bf16x8 f) {
+                                  constexpr int ks = decltype(m)::value >> 1;
+                                  if constexpr (decltype(m)::value & 1) dpacc = mfma32(f, dof[ks], dpacc);
+                                  else sacc = mfma32(f, qf[ks], sacc);
+                              });
+        } else {            // (there the compiler's order is 3 % the better one)
+#pragma unroll
+            for (int ks = 0; ks < D / 16; ++ks) {
+                sacc = mfma32(rows.read(k_lds, 0, ks), qf[ks], sacc);
+                dpacc = mfma32(rows.read(v_lds, 0, ks), dof[ks], dpacc);
+            }
+        }
+        bf16x8 kt[2][D / 32];
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db) kt[c][db] = cols.read(k_lds, 16 * c, db);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (K and V have left LDS)
+        more = advance();
+        if (more) load();
+
+        const int dq0 = q_pos - (kv_now + 4 * half);            // q_idx - kv_idx of element r is dq0 - elem_pos(r)
+        const float abase = smod.alibi_base(dq0);
+        float rel_uni;
+        const bool rel_is_uni = smod.rel_uniform(q_wave_min - (kv_now + 31), q_wave_min + 31 - kv_now, rel_uni);
+        auto rel = [&](int r) __attribute__((always_inline)) { return typename Score::RelPos(dq0, abase, -elem_pos(r)); };
+        if (rel_is_uni) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                float gr;
+                const float pe = smod.template p_with_grad<true>(sacc[r], rel(r), rc, gr, rel_uni);
+                dpacc[r] = pe * gr * dpacc[r];
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                float gr;
+                const float pe = smod.template p_with_grad<false>(sacc[r], rel(r), rc, gr);
+                dpacc[r] = pe * gr * dpacc[r];
+            }
+        }
+        if (masked) {
+            asm volatile("" ::: "memory");          // keep this a branch
+            typename Mask::Bits bits = mask.row_bits(q_pos, kv_now + 4 * half);
+            if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[w][0], q_tag, l32, half, scattered);
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                u32x4 tags = {};
+                if constexpr (Mask::kCanvas) tags = *(const u32x4*)&s_tag[w][8 * rg + 4 * half];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    dpacc[4 * rg + i] = keep_or_zero(Mask::keep(bits, 4 * rg + i, mask.pixels_match(tags[i], q_tag)), dpacc[4 * rg + i]);
+            }
+        }
+        if (more && partial) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (the tags have been read)
+            make_tags(kv);
+        }
+        // dQ^T += K^T dS^T
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            u32x4 ds;
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) ds[jj] = pack_bf16(dpacc[8 * c + 2 * jj], dpacc[8 * c + 2 * jj + 1]);
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db) dq[db] = mfma32(kt[c][db], __builtin_bit_cast(bf16x8, ds), dq[db]);
+        }
+    }
+    f32x4 quads[D / 8];
+#pragma unroll
+    for (int q = 0; q < D / 8; ++q)
+        quads[q] = f32x4{dq[q >> 2][4 * (q & 3)], dq[q >> 2][4 * (q & 3) + 1], dq[q >> 2][4 * (q & 3) + 2], dq[q >> 2][4 * (q & 3) + 3]};
+    const float qscale = a.scale * Score::grad_scale();
+    add_quads<NW, D / 8>((f32x4*)smem, w, lane, quads, [&](int q, const f32x4& o) __attribute__((always_inline)) {
+        u32x2 pk;
+        pk[0] = pack_bf16(o[0] * qscale, o[1] * qscale);
+        pk[1] = pack_bf16(o[2] * qscale, o[3] * qscale);
+        if (real_row) *(u32x2*)(dq_ptr + 8 * q + 4 * half) = pk;
+    });
+}
+
+// dK, dV.  Q and dO of 32 rows in two slots a wave, one unit ahead; K and V of the 32 keys in registers, dV^T and dK^T of the
+// wave's rows as well.  With dS kept in memory (ds_store) a unit writes its part of a step: that of wave (kb, x) in
+// bwd_dkdv_kernel; hidden units of index masks write zeros, those of a canvas are not read back.
+template <int D, int NW, uint32_t MASK, uint32_t SCORE>
+__global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kernel(const BwdArgs a) {
+    constexpr uint32_t UT = 32 * D * 2;
+    constexpr int NKS = D / 16, NDB = D / 32;
+    using Score = ScoreMod<SCORE, true>;
+    using Mask = PartialMask<MASK>;
+    using L = WaveTileLoader<D, 1, 32>;
+    __shared__ __attribute__((aligned(1024))) bf16 smem[NW * 128 * D];      // per wave: two slots of Q, dO
+    __shared__ __attribute__((aligned(256))) float s_row[NW][2][2][64];     // [wave][slot][rc | -delta][row, 32 of 64]
+    __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];
+    __shared__ __attribute__((aligned(256))) uint32_t s_tag[NW][2][Mask::kTags ? 64 : 4];
+
+    const int parts = a.Bk / 32;
+    int unit, slot_rank;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.NC * parts, unit, slot_rank)) return;
+    const int b = unit / a.Hkv, hkv = unit % a.Hkv;
+    int col = slot_rank / parts;
+    if (a.q_order) {
+        const int64_t plane0 = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hkv * a.G : 0);
+        col = min(max(ldc(a.q_order + plane0 * a.NC + col), 0), a.NC - 1);
+    }
+    const int part = slot_rank & (parts - 1), kv0 = col * a.Bk + part * 32;
+    // (the dQ kernel reads dS in tiles of 64 keys whose first key exists)
+    if ((a.ds_store ? kv0 & ~63 : kv0) >= a.kv_len) return;
+
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kv_lane = kv0 + l32, kv_ld = min(kv_lane, a.kv_len - 1);
+    bf16x8 kf[NKS], vf[NKS];
+    {
+        const bf16* kp = a.K + b * a.k_sb + hkv * a.k_sh + (int64_t)kv_ld * a.k_ss + half * 8;
+        const bf16* vp = a.V + b * a.v_sb + hkv * a.v_sh + (int64_t)kv_ld * a.v_ss + half * 8;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            kf[ks] = *(const bf16x8*)(kp + ks * 16);
+            vf[ks] = *(const bf16x8*)(vp + ks * 16);
+        }
+    }
+    f32x16 dv[NDB], dk[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dv[db][r] = dk[db][r] = 0.0f;
+
+    const int q_off = q_offset_of(a.p, b);
+    const Mask mask(a.p, b, a.kv_len);
+    const int32_t* docs = Mask::kDoc ? a.p.doc_ids + (int64_t)b * a.p.doc_stride_b : nullptr;
+    uint32_t k_tag = 0;
+    if constexpr (Mask::kDoc) k_tag = (uint32_t)docs[kv_ld];
+    if constexpr (Mask::kCanvas) k_tag = mask.key_pixel(kv_ld);
+    const L q_load(a.q_ss, 0, lane), do_load(a.do_ss, 0, lane);
+    const uint32_t base = lds_addr(smem) + (uint32_t)w * 4 * UT;
+    const RowReader<D> rows(l32, half, base);
+    const TrReader<D> cols(lane, base);
+    const uint32_t q_bytes = (uint32_t)((a.q_len - 1) * a.q_ss + D) * 2u, do_bytes = (uint32_t)((a.q_len - 1) * a.do_ss + D) * 2u;
+    const int per_block = a.Bq / 32, shift = a.Bq == 128 ? 2 : 1;
+    int first = w;                                  // the wave's first unit of the next head's walk
+
+    for (int g = 0; g < a.G; ++g) {
+        const int hq = hkv * a.G + g;
+        const int64_t line = ((int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0)) * a.NC + col;
+        const int n_full = ldc(a.full_q_num + line), n_part = ldc(a.q_num + line), H = (n_full + n_part) * per_block;
+        const i32x4 q_rsrc = make_rsrc(a.Q + b * a.q_sb + hq * a.q_sh, q_bytes);
+        const i32x4 do_rsrc = make_rsrc(a.dO + b * a.do_sb + hq * a.do_sh, do_bytes);
+        const int64_t row0 = ((int64_t)b * a.Hq + hq) * a.q_len;
+        const i32x4 rc_rsrc = make_rsrc(a.lse2 + row0, (uint32_t)a.q_len * 4u), nd_rsrc = make_rsrc(a.delta + row0, (uint32_t)a.q_len * 4u);
+        const Score smod(a.p, hq, a.scale, lds_addr(s_rel));
+        if constexpr (Score::kRel) {
+            __syncthreads();                        // (everybody is done with the previous head's row)
+            smod.fill_table(tid, NW * 64);
+            __syncthreads();
+        }
+        int ds_slot0 = 0;
+        int64_t ds_of_rep = 0;
+        if (a.ds_store) {
+            ds_slot0 = ldc(a.ds_colbase + line);
+            ds_of_rep = ds_rep(a, b, hq);
+        }
+        // this wave's part of the dS of walk position (pos, sidx)
+        auto store_ds = [&](int pos, int sidx, u32x4 c0, u32x4 c1) __attribute__((always_inline)) {
+            bf16* dst = a.ds_store + ds_chunk(a, ds_of_rep, ds_slot0 + pos, part >> 1, sidx >> 1) * 4096 +
+                        ((part & 1) + 2 * (sidx & 1)) * 1024 + lane * 8;
+            __builtin_nontemporal_store(c0, (u32x4*)dst);
+            __builtin_nontemporal_store(c1, (u32x4*)(dst + 512));
+        };
+        // The walk, from its end as in bwd_dkdv_kernel: unit u of the wave is row slice H - 1 - u of the column's merged list.
+        auto block_at = [&](int u) __attribute__((always_inline)) {
+            const int p = max(H - 1 - u, 0) >> shift;
+            return H == 0 ? 0 : ldc(p < n_full ? a.full_q_idx + line * a.NR + p : a.q_idx + line * a.NR + (p - n_full));
+        };
+        int u_next = first, blk_next = block_at(first);
+        int q0 = 0, pos = 0, sidx = 0;              // the unit that is loaded next
+        bool partial = false;
+        auto advance = [&]() __attribute__((always_inline)) {
+            while (u_next < H) {
+                const int u = H - 1 - u_next;
+                pos = u >> shift;
+                sidx = u & (per_block - 1);
+                q0 = blk_next * a.Bq + sidx * 32;
+                partial = pos >= n_full;
+                u_next += NW;
+                blk_next = block_at(u_next);
+                if (q0 >= a.q_len) continue;        // (rows that do not exist)
+                bool hid = false;
+                if constexpr (Mask::kCanvas) {
+                    if (partial) {
+                        const CanvasBlocks cb(a.p);
+                        hid = __builtin_amdgcn_readfirstlane(cb.hidden(cb.windows(q0), cb.tokens(kv0)) ? 1 : 0);
+                    }
+                } else {
+                    hid = partial && mask.hidden(q_off + q0, q_off + q0 + 31, kv0, kv0 + 31);
+                    if (hid && a.ds_store) store_ds(pos, sidx, u32x4{0, 0, 0, 0}, u32x4{0, 0, 0, 0});
+                }
+                if (!hid) return true;
+            }
+            return false;
+        };
+        constexpr int kLoads = 2 * L::NI + 2;
+        // (a dword load brings 64 rows of scalars; the second 32 are those of the next unit and not used)
+        auto load = [&](auto slot_tag) __attribute__((always_inline)) {
+            constexpr int SLOT = decltype(slot_tag)::value;
+            if (partial) {
+                if constexpr (Mask::kDoc) dma_global_dword(lds_addr(&s_tag[w][SLOT][0]), docs, (q_off + min(q0 + lane, a.q_len - 1)) * 4);
+                if constexpr (Mask::kCanvas) s_tag[w][SLOT][lane] = mask.query_pixel(q_off + min(q0 + lane, a.q_len - 1));
+            }
+            q_load.start(q_rsrc, base + SLOT * 2 * UT, q0 * (int)a.q_ss * 2);
+            do_load.start(do_rsrc, base + SLOT * 2 * UT + UT, q0 * (int)a.do_ss * 2);
+            dma_dword(rc_rsrc, lds_addr(&s_row[w][SLOT][0][0]), lane * 4, q0 * 4);
+            dma_dword(nd_rsrc, lds_addr(&s_row[w][SLOT][1][0]), lane * 4, q0 * 4);
+        };
+        bool more = advance();
+        if (more) load(std::integral_constant<int, 0>{});
+        // one unit; false after the last
+        auto step = [&](auto slot_tag) __attribute__((always_inline)) {
+            constexpr int SLOT = decltype(slot_tag)::value;
+            const int q_now = q_off + q0, pos_now = pos, sidx_now = sidx;
+            const bool partial_now = partial;
+            more = advance();
+            if (more) load(std::integral_constant<int, SLOT ^ 1>{});
+            if (!more) wait_vmem();
+            else if (Mask::kDoc && partial) wait_vmem_but<kLoads + 1>();
+            else wait_vmem_but<kLoads>();
+            asm volatile("" ::: "memory");
+            constexpr uint32_t q_t = SLOT * 2 * UT, do_t = q_t + UT;
+            f32x16 sacc, dpacc;
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const f32x4 nd = *(const f32x4*)&s_row[w][SLOT][1][8 * rg + 4 * half];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sacc[4 * rg + i] = 0.0f;
+                    dpacc[4 * rg + i] = nd[i];
+                }
+            }
+            read_ahead<2 * NKS>([&](auto m) { return rows.read((decltype(m)::value & 1) ? do_t : q_t, 0, decltype(m)::value >> 1); },
+                                   [&](auto m, bf16x8 f) {
+                                       constexpr int ks = decltype(m)::value >> 1;
+                                       if constexpr (decltype(m)::value & 1) dpacc = mfma32(f, vf[ks], dpacc);
+                                       else sacc = mfma32(f, kf[ks], sacc);
+                                   });
+            float rel_uni;
+            const bool rel_is_uni = smod.rel_uniform(q_now - (kv0 + 31), q_now + 31 - kv0, rel_uni);
+            const bool masked = partial_now && !mask.full(q_now, q_now + 31, kv0, kv0 + 31);
+            typename Mask::Bits bits = {};
+            if (masked) {
+                bits = mask.key_bits(kv_lane, q_now + 4 * half);
+                if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[w][SLOT][0], k_tag, l32, half, false);
+            }
+            u32x4 pk[2], dsk[2];
+#pragma unroll
+            for (int c4 = 0; c4 < 4; ++c4) {
+                float sv[4], rcv[4], gr[4], pe[4], ds[4];
+                using RelPos = typename Score::RelPos;
+                constexpr bool kNeedsPos = Score::kAlibi || Score::kRel;
+                const int dq0 = kNeedsPos ? q_now + 4 * half - kv_lane : 0;
+                const float abase = smod.alibi_base(dq0);
+                auto rel = [&](int r) __attribute__((always_inline)) { return kNeedsPos ? RelPos(dq0, abase, elem_pos(r)) : RelPos(0); };
+                const RelPos dqk[4] = {rel(4 * c4), rel(4 * c4 + 1), rel(4 * c4 + 2), rel(4 * c4 + 3)};
+                const f32x4 rc4 = *(const f32x4*)&s_row[w][SLOT][0][8 * c4 + 4 * half];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sv[i] = sacc[4 * c4 + i];
+                    rcv[i] = rc4[i];
+                }
+                if (rel_is_uni) smod.template p_with_grad4<true>(sv, dqk, rcv, gr, pe, rel_uni);
+                else smod.template p_with_grad4<false>(sv, dqk, rcv, gr, pe);
+                if (masked) {
+                    asm volatile("" ::: "memory");   // keep this a branch
+                    u32x4 tags = {};
+                    if constexpr (Mask::kCanvas) tags = *(const u32x4*)&s_tag[w][SLOT][8 * c4 + 4 * half];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i, mask.pixels_match(k_tag, tags[i])), pe[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    pk[c4 >> 1][2 * (c4 & 1) + i] = pack_bf16(pe[2 * i], pe[2 * i + 1]);
+                    dsk[c4 >> 1][2 * (c4 & 1) + i] = pack_bf16(ds[2 * i], ds[2 * i + 1]);
+                }
+            }
+            if (a.ds_store) store_ds(pos_now, sidx_now, dsk[0], dsk[1]);
+            // dV^T += dO^T P, dK^T += Q^T dS
+            // (MFMAs: [slice c][block db][dV, dK])
+            read_ahead<4 * NDB>([&](auto m) {
+                                       constexpr int i = decltype(m)::value >> 1;
+                                       return cols.read((decltype(m)::value & 1) ? q_t : do_t, 16 * (i / NDB), i % NDB);
+                                   },
+                                   [&](auto m, bf16x8 f) {
+                                       constexpr int c = (decltype(m)::value >> 1) / NDB, db = (decltype(m)::value >> 1) % NDB;
+                                       if constexpr (decltype(m)::value & 1) dk[db] = mfma32(f, __builtin_bit_cast(bf16x8, dsk[c]), dk[db]);
+                                       else dv[db] = mfma32(f, __builtin_bit_cast(bf16x8, pk[c]), dv[db]);
+                                   });
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // (the slot has been read)
+            return more;
+        };
+        if (more)
+            while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{})) {
+            }
+        first = u_next - H;                         // (the heads' walks are dealt to the waves as one)
+    }
+
+    f32x4 quads[D / 4];
+#pragma unroll
+    for (int q = 0; q < D / 4; ++q) {
+        const f32x16& acc = q < D / 8 ? dv[(q % (D / 8)) >> 2] : dk[(q % (D / 8)) >> 2];
+        quads[q] = f32x4{acc[4 * (q & 3)], acc[4 * (q & 3) + 1], acc[4 * (q & 3) + 2], acc[4 * (q & 3) + 3]};
+    }
+    const float kscale = a.scale * Score::grad_scale();
+    add_quads<NW, D / 4>((f32x4*)smem, w, lane, quads, [&](int q, const f32x4& o) __attribute__((always_inline)) {
+        const bool is_k = q >= D / 8;
+        const float s = is_k ? kscale : 1.0f;
+        bf16* out = is_k ? a.dK + b * a.dk_sb + hkv * a.dk_sh + (int64_t)kv_lane * a.dk_ss
+                         : a.dV + b * a.dv_sb + hkv * a.dv_sh + (int64_t)kv_lane * a.dv_ss;
+        u32x2 pk;
+        pk[0] = pack_bf16(o[0] * s, o[1] * s);
+        pk[1] = pack_bf16(o[2] * s, o[3] * s);
+        if (kv_lane < a.kv_len) *(u32x2*)(out + 8 * (q % (D / 8)) + 4 * half) = pk;
+    });
+}
+
+// Where the split kernels take over (waves, 0: they do not), by the slices of 32 rows or keys of the launch and their length.
+// us, bwd_dq_kernel -> 4 waves / 8 waves: causal, S = 4096, D = 64, 1 head 58 -> 23 / 16, 4 59 -> 25 / 22, 8 59 -> 36 / 41, 16 86 -> 70 / 82, 32
+// 127 -> 136; D = 128 (4 waves), 1 head 86 -> 36, 4 87 -> 44, 8 88 -> 85, 16 139 -> 168; S = 1000, D = 64, 8 / 32 / 64 heads 18.8 -> 8.8 / 7.8, 19.3
+// -> 17.3, 27 -> 32, D = 128, 8 / 16 / 32 heads 27 -> 14, 27 -> 19, 29 -> 38; S = 300, D = 64, 32 / 64 heads 8.2 -> 7.0, 8.4 -> 11.0, D = 128, 8 / 32
+// heads 11.6 -> 8.2, 11.8 -> 13.4; no mask, S = 2048, D = 64, 4 / 8 / 16 heads 32 -> 14 / 11, 33 -> 18 / 21, 33 -> 34, D = 128, 4 / 8 / 16
+// heads 46 -> 22, 46 -> 42, 52 -> 83; window of 512, S = 4096, D = 64, 4 / 8 heads 14.8 -> 8.9 / 12.3, 15.1 -> 16.6, D = 128, 4 heads 20.5 -> 21.6.
+template <uint32_t MASK>
+int dq_split_waves(const BwdArgs& a, int D) {
+    const int64_t slices = (int64_t)a.B * a.Hq * ((a.q_len + 31) / 32);
+    const LineShape rows = line_shape<MASK>(a.p, a.q_len, a.kv_len);
+    if (D == 128) return slices <= (rows.longest < 768 ? 256 : rows.uneven && rows.longest >= 4096 ? 1024 : 512) ? 4 : 0;
+    if (slices > (rows.longest < 512 ? 512 : !rows.uneven ? 768 : rows.longest >= 4096 ? 2048 : 1024)) return 0;
+    return (slices <= 256 ? rows.longest >= 512 : slices <= 512 && rows.uneven && rows.longest >= 2048) ? 8 : 4;
+}
+// us, bwd_dkdv_kernel -> 4 waves / 8 waves: causal, S = 4096, D = 64, 1 head 51 -> 39 / 21, 4 52 -> 41 / 29, 8 58 -> 50 / 54, 16 92 -> 98; D = 128 (4
+// waves), 1 head 72 -> 45, 4 74 -> 58, 8 90 -> 111; 8 query and 1 KV heads, S = 2048 199 -> 145 / 74, D = 128 280 -> 166; 32 / 8, S = 2048 101 -> 77 /
+// 53; S = 1000, D = 64, 8 / 16 / 32 heads 16.8 -> 13.7 / 10.1, 17.1 -> 15.9 / 15.3, 23.2 -> 25.1, D = 128, 8 / 16 heads 23.8 -> 16.8, 24.2 -> 23.9; S =
+// 300, D = 64, 32 / 64 heads 9.4 -> 8.8, 12.0 -> 14.1, D = 128, 8 / 32 heads 12.9 -> 10.3, 13.4 -> 16.3; no mask, S = 2048, D = 64, 4 / 8 / 16 heads 29
+// -> 22 / 15, 29 -> 26 / 28, 41 -> 48, D = 128, 4 / 8 heads 40 -> 26, 42 -> 51; window of 512 or prefix of 256, S = 8192, D = 64, 2 x 16 / 4 heads,
+// whose first columns are as long as the sequence times the group 557 -> 324 / 311.
+template <uint32_t MASK>
+int dkdv_split_waves(const BwdArgs& a, int D) {
+    const int64_t slices = (int64_t)a.B * a.Hkv * ((a.kv_len + 31) / 32);
+    // (the columns of a mask that is its own transpose's mirror image are shaped like its rows; a prefix is seen by all rows)
+    LineShape cols = line_shape<MASK>(a.p, a.q_len, a.kv_len);
+    const bool few_long = mask_uses(MASK, FLEXATTN_M_PREFIX) && !cols.uneven;
+    if (mask_uses(MASK, FLEXATTN_M_PREFIX)) cols = {a.q_len, true};
+    if (cols.longest > a.q_len) cols.longest = a.q_len;
+    if (D == 128) return slices <= (few_long ? 2048 : cols.uneven && cols.longest >= 1000 ? 512 : 256) ? 4 : 0;
+    if (slices > (few_long ? 2048 : cols.uneven && cols.longest >= 2048 ? 1024 : 512)) return 0;
+    return few_long || slices <= 256 || (slices <= 512 && cols.uneven && cols.longest >= 2048) ? 8 : 4;
+}
+
+// dQ at D = 64 with four waves: whether leaving hidden blocks out pays.  The test between the two blocks of a tile
+// keeps their work apart, which shows where at most two workgroups share a CU: masks that hide little more than a
+// diagonal are left out only beyond that (us, computed whole -> left out, causal: one sequence, S = 4096, 8 heads 58.8 ->
+// 64.1; S = 8192, 8 heads 131 -> 136; S = 2048, 2 x 16 heads 47.1 -> 47.2, 4 x 16 75.6 -> 75.9; S = 4096, 64 heads
+// 227.8 -> 222.9; S = 1024, 64 x 16 heads 298.6 -> 285.8).
+// dK/dV at D = 64: own rows, but for launches that are as long as their longest column of blocks, where a workgroup is
+// alone on its CU most of the time: there the exchange is faster, whose operands are read further ahead.  They are
+// told by what the columns' steps make of 768 workgroups (three per CU) beside the longest column: a third of it (270 of
+// 768 for a mask whose columns are as long as the longest).  Windows and documents have columns of about one length and
+// hidden blocks to leave out, a soft-cap more vector work than the operands' reads take.
+// us, exchange -> own rows: causal, S = 1024, 8 heads 16.8 -> 18.7; S = 4096, 8 heads 57.7 -> 59.8; S = 2048, 16 heads 38.7 -> 38.1, 32 heads 56.5 -> 54.3; no mask, S = 1024, 8 heads 16.9 -> 17.9, S = 4096, 8 heads
+// 78.2 -> 76.7; window 512 or prefix 128, S = 8192, 16 heads 163 -> 170, S = 2048, 32 heads 55.5 -> 53.8.
+template <uint32_t MASK>
+bool own_rows_pay(const BwdArgs& a, unsigned grid) {
+    const float longest = a.q_len / 64.0f;          // steps
+    float mean = MASK == FLEXATTN_MASK_NONE ? longest : 0.5f * longest;
+    if (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW))
+        mean = fminf(longest, a.p.window / 64.0f + 2.0f + longest * a.p.prefix_len / a.kv_len);
+    return grid * mean > 270.0f * longest;
+}
+template <uint32_t MASK, uint32_t SCORE>
+void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
+    constexpr bool even = mask_uses(MASK, FLEXATTN_M_DOCUMENT) ||
+                          (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) && !mask_uses(MASK, FLEXATTN_M_PREFIX));
+    if constexpr (dkdv_own_rows<64, MASK, SCORE>() && !even && !(SCORE & FLEXATTN_SCORE_SOFTCAP)) {
+        if (!own_rows_pay<MASK>(a, grid)) {
+            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false>), dim3(grid), dim3(256), 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
+}
+
+template <uint32_t MASK, uint32_t SCORE>
+void launch_dq64(const BwdArgs& a, unsigned grid, hipStream_t st) {
+    constexpr bool often = mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
+    if constexpr (!often) {
+        if (grid <= 2 * 256) {
+            hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, false>), dim3(grid), dim3(256), 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
+}
+
+template <uint32_t MASK, uint32_t SCORE>
+int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st) {
+    const unsigned grid_kv = unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 64));
+    const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
+    const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
+    // dQ first where it makes the row scalars that dK/dV reads
+    if ((stages & FLEXATTN_BWD_DELTA) && !q && !(stages & kBwdStageCaptured)) {
+        const size_t rows = (size_t)a.B * a.Hq * a.q_len;
+        if (D == 128) hipLaunchKernelGGL((bwd_delta_kernel<128, SCORE>), dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((bwd_delta_kernel<64, SCORE>), dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, st, a);
+    }
+    if (q) {
+        BwdArgs aq = a;
+        aq.make_delta = stages & FLEXATTN_BWD_DELTA;
+        const int waves = dq_split_waves<MASK>(a, D);
+        if (waves) {
+            const dim3 slices(unit_grid(a.B * a.Hkv, a.G * a.NR * (a.Bq / 32)));
+            if (D == 128) hipLaunchKernelGGL((bwd_dq_split_kernel<128, 4, MASK, SCORE>), slices, dim3(256), 0, st, aq);
+            else if (waves == 8) hipLaunchKernelGGL((bwd_dq_split_kernel<64, 8, MASK, SCORE>), slices, dim3(512), 0, st, aq);
+            else hipLaunchKernelGGL((bwd_dq_split_kernel<64, 4, MASK, SCORE>), slices, dim3(256), 0, st, aq);
+        } else if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
+        else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
+        else if (a.Bq == 128) launch_dq64<MASK, SCORE>(aq, grid_q, st);
+        else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
+    }
+    if (kv) {
+        const int waves = dkdv_split_waves<MASK>(a, D);
+        if (waves) {
+            const dim3 slices(unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 32)));
+            if (D == 128) hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 4, MASK, SCORE>), slices, dim3(256), 0, st, a);
+            else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 8, MASK, SCORE>), slices, dim3(512), 0, st, a);
+            else hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 4, MASK, SCORE>), slices, dim3(256), 0, st, a);
+        } else if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, a);
+        else launch_dkdv64<MASK, SCORE>(a, grid_kv, st);
+    }
+    if (stages & kBwdStageCaptured) {
+        if constexpr ((SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS)) != 0) {
+            if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);
+            else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE, true>), dim3(grid_q), dim3(128), 0, st, a);
+            else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);
+            else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE, true>), dim3(grid_q), dim3(128), 0, st, a);
+        } else {
+            return FLEXATTN_ERR_UNSUPPORTED;     // this score_mod captures no tensor
+        }
+    }
+    return FLEXATTN_OK;
+}
+
+}  // namespace flexattn

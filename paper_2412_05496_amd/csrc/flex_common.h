@@ -691,6 +691,23 @@ void set_last_hip_error(int e);
 inline bool mask_id_valid(uint32_t m) {
     return (m & ~0x3f3fu) == 0 && !((m & 0xffu) == 0 && (m >> 8) != 0);
 }
+// What the host can tell of the rows of a mask: how many keys the longest see, and whether others see far fewer (so that
+// a launch of few rows ends with the longest alone).
+struct LineShape {
+    int64_t longest;
+    bool uneven;
+};
+template <uint32_t MASK>
+LineShape line_shape(const flexattn_mod_params& p, int q_len, int kv_len) {
+    constexpr uint32_t prims = MASK | (MASK >> 8);
+    LineShape s = {kv_len, (prims & FLEXATTN_M_DOCUMENT) || ((prims & FLEXATTN_M_CAUSAL) && 2 * (int64_t)q_len > kv_len)};
+    if (prims & FLEXATTN_M_SLIDING_WINDOW) {
+        const int64_t reach = (int64_t)p.window + 1 + ((prims & FLEXATTN_M_PREFIX) ? p.prefix_len : 0);
+        s.uneven = s.uneven && 2 * reach > kv_len;
+        if (reach < s.longest) s.longest = reach;
+    }
+    return s;
+}
 inline bool score_id_valid(uint32_t s) { return (s & ~7u) == 0; }
 constexpr bool mask_uses(uint32_t m, uint32_t prim) { return ((m | (m >> 8)) & prim) != 0; }
 

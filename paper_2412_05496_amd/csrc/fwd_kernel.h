@@ -137,13 +137,9 @@ bool units_pay(const FwdArgs& a, int64_t grid) {
 template <uint32_t MASK>
 int split_waves(const FwdArgs& a, int D) {
     const int64_t slices = (int64_t)a.B * a.Hq * ((a.q_len + 31) / 32);
-    int64_t keys = a.kv_len;        // of the longest rows, as far as the host can tell
-    bool uneven = mask_uses(MASK, FLEXATTN_M_DOCUMENT) || (mask_uses(MASK, FLEXATTN_M_CAUSAL) && 2 * (int64_t)a.q_len > a.kv_len);
-    if (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW)) {
-        const int64_t reach = (int64_t)a.p.window + 1 + (mask_uses(MASK, FLEXATTN_M_PREFIX) ? a.p.prefix_len : 0);
-        uneven = uneven && 2 * reach > a.kv_len;
-        if (reach < keys) keys = reach;
-    }
+    const LineShape rows = line_shape<MASK>(a.p, a.q_len, a.kv_len);
+    const int64_t keys = rows.longest;
+    const bool uneven = rows.uneven;
     int64_t most = D == 64 ? 4 * 256 : 2 * 256;
     if (D == 64 && uneven && keys >= 2048) most = keys >= 4096 ? 12 * 256 : 8 * 256;
     if (D == 128 && keys >= 1024) most = uneven && keys >= 2048 ? 4 * 256 : 3 * 256;
@@ -520,8 +516,8 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
             f32x16 s;
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[r] = 0.0f;
-#pragma unroll
-            for (int ks = 0; ks < D / 16; ++ks) s = mfma32(k_reader.read(k_lds, 0, ks), qf[ks], s);
+            read_ahead<D / 16>([&](auto m) { return k_reader.read(k_lds, 0, decltype(m)::value); },
+                                    [&](auto m, bf16x8 f) { s = mfma32(f, qf[decltype(m)::value], s); });
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");              // (K has left LDS)
             more = advance();
             if (more) load(k_load, k_head, k_rsrc, k_row_bytes, k_lds);
@@ -536,10 +532,12 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
             else if (Mask::kDoc && partial) wait_vmem_but<L::NI + 1>();
             else wait_vmem_but<L::NI>();
             asm volatile("" ::: "memory");
-#pragma unroll
-            for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-                for (int c = 0; c < 2; ++c) oacc[db] = mfma32(v_reader.read(v_lds, 16 * c, db), pf[c], oacc[db]);
+            constexpr int NDB = D / 32;
+            read_ahead<2 * NDB>([&](auto m) { return v_reader.read(v_lds, 16 * (decltype(m)::value / NDB), decltype(m)::value % NDB); },
+                                     [&](auto m, bf16x8 f) {
+                                         constexpr int db = decltype(m)::value % NDB, c = decltype(m)::value / NDB;
+                                         oacc[db] = mfma32(f, pf[c], oacc[db]);
+                                     });
             if (more) {
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // (V has left LDS)
                 load(v_load, v_head, v_rsrc, v_row_bytes, v_lds);
