@@ -1,8 +1,8 @@
 """ctypes binding of libflexattn.so: argument marshalling only.
 
-A small call is bound by what runs here (the GPU needs 7 us for a forward over 256 tokens), so structures are
-built in one go, passed without byref (the argtypes make the reference) and the stream is asked for as a
-number: 14.2 -> 9.3 us of host time per forward, 13.4 -> 9.9 per decode.
+A small call is bound by what runs here (the GPU needs 5 us for a forward over 256 tokens), so the calls of a step
+with plain arguments are marshalled in C++ (csrc/marshal.cpp); everything else, and everything that is to be refused,
+takes the ctypes path below, which is the same call 3 to 4.5 us of host time later.
 
 Every function here has the name of the C entry point it wraps (see include/flexattn.h), takes
 torch CUDA tensors for device memory, launches on torch's current stream and raises
@@ -94,6 +94,33 @@ class _DecodeDims(C.Structure):
 
 
 _handle = None
+
+
+class _NoMarshal:
+    """Stands for the C++ marshalling where it has not been built: every call takes the ctypes path."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+_marshal = None
+
+
+def _fast():
+    """The C++ marshalling (None from one of its functions: not a plain call, nothing has been launched)."""
+    global _marshal
+    if _marshal is None:
+        lib = _lib()
+        try:
+            from paper_2412_05496_amd import _marshal as m
+        except ImportError:
+            m = _NoMarshal()
+        else:
+            m.setup(ModParams, BlockMask, *(C.cast(getattr(lib, "flexattn_" + n), C.c_void_p).value for n in (
+                "forward", "paged_forward", "backward", "backward_stored", "blockmask_build", "paged_convert_blockmask",
+                "paged_decode")))
+        _marshal = m
+    return _marshal
 
 
 def _lib():
@@ -327,6 +354,10 @@ def flexattn_blockmask_build(mask_id: int, params: ModParams, bm: BlockMask, ws:
     if ws is None:
         n = flexattn_blockmask_workspace_bytes(bm.Bm, bm.Hm, bm.q_len, bm.kv_len, bm.Bq, bm.Bk)
         ws = torch.empty(max(n, 1), dtype=torch.uint8, device=bm.kv_indices.device)
+    status = (_marshal or _fast()).blockmask_build(mask_id, params, bm, ws, _stream)
+    if status is not None:
+        _check(status, "flexattn_blockmask_build")
+        return bm
     p, c = params._c(), bm._c()
     _check(_lib().flexattn_blockmask_build(mask_id, p, c, _ptr(bm.stats), ws.data_ptr(),
                                            ws.numel(), _stream()), "flexattn_blockmask_build")
@@ -335,6 +366,10 @@ def flexattn_blockmask_build(mask_id: int, params: ModParams, bm: BlockMask, ws:
 
 def flexattn_forward(Q, K, V, score_id: int, mask_id: int, params: ModParams, bm: BlockMask, scale: float,
                      O: torch.Tensor, LSE: torch.Tensor):
+    status = (_marshal or _fast()).forward(Q, K, V, score_id, mask_id, params, bm, scale, O, LSE, _stream)
+    if status is not None:
+        _check(status, "flexattn_forward")
+        return O, LSE
     assert LSE.dtype == torch.float32 and LSE.is_contiguous() and LSE.shape == Q.shape[:3]
     d, p, c = _dims(Q, K), params._c(), bm._c()
     tq, tk, tv, to = _tensor(Q), _tensor(K), _tensor(V), _tensor(O)
@@ -348,6 +383,11 @@ def flexattn_paged_forward(Q, K_pool, V_pool, score_id: int, mask_id: int, param
                            O: torch.Tensor, LSE: torch.Tensor):
     """Q [nseq, Hq, q_len, D]; pools [n_pages, Hkv, page, D] contiguous; `bm` is the logical BlockMask
     (Bm == nseq, Bk == page), the phys_* tensors its converted kv lists."""
+    status = (_marshal or _fast()).paged_forward(Q, K_pool, V_pool, score_id, mask_id, params, bm, phys_kv_indices,
+                                                 phys_full_kv_indices, scale, O, LSE, _stream)
+    if status is not None:
+        _check(status, "flexattn_paged_forward")
+        return O, LSE
     assert K_pool.is_contiguous() and V_pool.is_contiguous() and K_pool.shape == V_pool.shape
     assert LSE.dtype == torch.float32 and LSE.is_contiguous() and LSE.shape == Q.shape[:3]
     for phys, logical in ((phys_kv_indices, bm.kv_indices), (phys_full_kv_indices, bm.full_kv_indices)):
@@ -372,6 +412,10 @@ def flexattn_backward(Q, K, V, O, dO, LSE, score_id: int, mask_id: int, params: 
                       scale: float, dQ, dK, dV, ws: Optional[torch.Tensor] = None):
     if ws is None:
         ws = torch.empty(max(flexattn_backward_workspace_bytes(Q, K), 1), dtype=torch.uint8, device=Q.device)
+    status = (_marshal or _fast()).backward(Q, K, V, O, dO, LSE, score_id, mask_id, params, bm, scale, dQ, dK, dV, ws, _stream)
+    if status is not None:
+        _check(status, "flexattn_backward")
+        return dQ, dK, dV
     d, p, c = _dims(Q, K), params._c(), bm._c()
     ts = [_tensor(t) for t in (Q, K, V, O, dO, dQ, dK, dV)]
     _check(_lib().flexattn_backward(d, *ts[:5], LSE.data_ptr(), score_id, mask_id, p, c, scale, *ts[5:],
@@ -392,6 +436,11 @@ def flexattn_backward_stored(Q, K, V, O, dO, LSE, score_id: int, mask_id: int, p
     if ws is None:
         n = flexattn_backward_stored_workspace_bytes(Q, K, bm, n_blocks)
         ws = torch.empty(max(n, 1), dtype=torch.uint8, device=Q.device)
+    status = (_marshal or _fast()).backward_stored(Q, K, V, O, dO, LSE, score_id, mask_id, params, bm, scale, dQ, dK, dV, n_blocks,
+                                                   ws, stages, _stream)
+    if status is not None:
+        _check(status, "flexattn_backward_stored")
+        return dQ, dK, dV
     d, p, c = _dims(Q, K), params._c(), bm._c()
     ins = [_tensor(t) for t in (Q, K, V, O, dO)]
     outs = [None if t is None else _tensor(t) for t in (dQ, dK, dV)]
@@ -433,6 +482,10 @@ def flexattn_backward_captured(Q, K, V, O, dO, LSE, score_id: int, mask_id: int,
 
 
 def flexattn_paged_convert_blockmask(num_blocks, indices, page_table, phys_indices, phys2log=None):
+    status = (_marshal or _fast()).convert(num_blocks, indices, page_table, phys_indices, phys2log, _stream)
+    if status is not None:
+        _check(status, "flexattn_paged_convert_blockmask")
+        return phys_indices, phys2log
     Bm, Hm, NR, NC = indices.shape
     n_pool = phys2log.numel() if phys2log is not None else 2 ** 31 - 1
     _check(_lib().flexattn_paged_convert_blockmask(num_blocks.data_ptr(), indices.data_ptr(), Bm, Hm, NR, NC,
@@ -455,6 +508,12 @@ def flexattn_paged_decode_workspace_bytes(Q, K_pool, page_table) -> int:
 def flexattn_paged_decode(Q, K_pool, V_pool, page_table, ctx_lens, score_id: int, mask_id: int, params: ModParams,
                           scale: float, O, LSE=None, ws: Optional[torch.Tensor] = None):
     """Q [nseq, Hq, 1, D] or [nseq, Hq, D]; pools [n_pages, Hkv, page, D] contiguous."""
+    if ws is not None:
+        status = (_marshal or _fast()).paged_decode(Q, K_pool, V_pool, page_table, ctx_lens, score_id, mask_id, params, scale, O, LSE,
+                                                    ws, _stream)
+        if status is not None:
+            _check(status, "flexattn_paged_decode")
+            return O, LSE
     assert K_pool.is_contiguous() and V_pool.is_contiguous() and O.is_contiguous()
     assert Q.stride(-1) == 1 and Q.stride(1) == Q.shape[-1]
     if ws is None:

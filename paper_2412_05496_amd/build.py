@@ -20,6 +20,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libflexattn.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 NUM_VARIANTS = 13         # must equal kNumVariants in csrc/variants.h
 
@@ -62,12 +63,33 @@ def _compile(unit, force: bool) -> str:
     return obj
 
 
+def _build_marshal(force: bool) -> None:
+    """The binding's argument marshalling (csrc/marshal.cpp), a Python extension next to the library."""
+    import sysconfig
+
+    import torch
+    src = os.path.join(CSRC, "marshal.cpp")
+    if (not force and os.path.exists(MARSHAL)
+            and os.path.getmtime(MARSHAL) > max(os.path.getmtime(src), os.path.getmtime(os.path.join(ROOT, "include", "flexattn.h")))):
+        return
+    at = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(at, "include"),
+           "-I" + os.path.join(at, "include", "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"], src, "-o", MARSHAL,
+           "-L" + os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"marshal.cpp failed:\n{' '.join(cmd)}\n{r.stderr}")
+
+
 def build(jobs: int = 0, force: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     jobs = jobs or min(8, os.cpu_count() or 1)
     units = _units()
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(_build_marshal, force)
         objs = list(ex.map(lambda u: _compile(u, force), units))
+        marshal.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

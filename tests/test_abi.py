@@ -181,3 +181,45 @@ def test_stream_without_torchs_own_shortcuts(monkeypatch):
         cuda_stream = 1234
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
     assert other._stream() == 1234
+
+
+def test_cpp_marshalling_leaves_what_is_not_plain_to_the_python_path():
+    """No function of csrc/marshal.cpp decides about arguments: tensors on the CPU, subclasses, wrong counts, types and ranges
+    all come back as None (nothing launched), and the calls raise what the ctypes path raises."""
+    import torch
+    m = binding._fast()
+    assert hasattr(m, "setup"), "csrc/marshal.cpp has not been built"
+    q = torch.zeros(1, 2, 64, 64, dtype=torch.bfloat16)
+    lse = torch.zeros(1, 2, 64)
+    i32 = lambda *s: torch.zeros(*s, dtype=torch.int32)
+    bm = fa.BlockMask(1, 1, 64, 64, 64, 64, i32(1, 1, 1), i32(1, 1, 1, 1), i32(1, 1, 1), i32(1, 1, 1, 1), i32(1, 1, 1), i32(1, 1, 1, 1),
+                      i32(1, 1, 1), i32(1, 1, 1, 1))
+    p, st = fa.ModParams(), lambda: 0
+    assert m.forward(q, q, q, 0, 0, p, bm, 0.1, q, lse, st) is None                    # not on a GPU
+    assert m.forward(q, q, q) is None and m.forward(*[None] * 11) is None
+    assert m.backward(*[q] * 5, lse, 0, 0, p, bm, 0.1, q, q, q, i32(8), st) is None
+    assert m.backward_stored(*[q] * 5, lse, 0, 0, p, bm, 0.1, q, None, q, 1, i32(8), 7, st) is None
+    assert m.paged_forward(q, q, q, 0, 0, p, bm, i32(1, 1, 1, 1), i32(1, 1, 1, 1), 0.1, q, lse, st) is None
+
+    class Sub(torch.Tensor):
+        pass
+
+    class Params(fa.ModParams):
+        pass
+    ws = torch.zeros(256, dtype=torch.uint8)
+    # (the builder looks at no device, so that only what makes a call not plain keeps it from the entry point; mask_id 255 << 14
+    # is none the entry point knows)
+    assert m.blockmask_build(255 << 14, p, bm, ws, st) == fa.ERR_INVALID_ARG
+    assert m.blockmask_build(255 << 14, p, bm, ws.as_subclass(Sub), st) is None
+    assert m.blockmask_build(255 << 14, Params(), bm, ws, st) is None
+    assert m.blockmask_build(-1, p, bm, ws, st) is None and m.blockmask_build(True, p, bm, ws, st) is None
+    assert m.blockmask_build(255 << 14, fa.ModParams(window=1 << 40), bm, ws, st) is None
+    assert m.blockmask_build(255 << 14, fa.ModParams(window=1.5), bm, ws, st) is None
+    assert m.blockmask_build(255 << 14, fa.ModParams(doc_ids=i32(64)), bm, ws, st) is None
+    assert m.blockmask_build(255 << 14, p, bm, torch.empty(256, dtype=torch.uint8, device="meta"), st) in (None, fa.ERR_INVALID_ARG)
+    assert m.blockmask_build(255 << 14, p, bm, ws.to_sparse(), st) is None              # no storage: torch's exception stays inside
+    with pytest.raises(AssertionError):
+        fa.flexattn_forward(q, q, q, 0, 0, p, bm, 0.1, q, lse)
+    def no_stream():
+        raise RuntimeError
+    assert m.blockmask_build(255 << 14, p, bm, ws, no_stream) is None
