@@ -821,11 +821,12 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
 #pragma unroll
         for (int r = 0; r < 16; ++r) dq[db][r] = 0.0f;
 
-    // a wave leaves out the blocks of 32 keys that the mask hides from all of its rows
+    // a wave leaves out the blocks of 32 keys that the mask hides from all of its rows, and all if it has no row
+    const bool no_row = row * Bq + w * 32 >= a.q_len;
     if constexpr (SKIP && Mask::kCanvas) fill_hidden_tiles<NW>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, sub, a.Bk, row * Bq, tid);
     auto hidden_block = [&](int t, bool partial, int kv, int kvb) __attribute__((always_inline)) {
-        if constexpr (Mask::kCanvas) return t < kHiddenTiles && ((__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (2 * w + kvb)) & 1);
-        else return partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31);
+        if constexpr (Mask::kCanvas) return no_row || (t < kHiddenTiles && ((__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (2 * w + kvb)) & 1));
+        else return no_row || (partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31));
     };
     bool part_next = false;
     int kv0 = walk.next(part_next);

@@ -461,9 +461,12 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         load_v(0, kv_t, pg_t, pr_t);
         if (part_t) make_tags(0, kv_t, 0);
     };
+    // (a wave of the last block whose rows lie past q_len hides all: D = 64, 128 heads of 777 rows, no mask 37.2 -> 36.6 us, of 660,
+    // causal 20.8 -> 19.1)
+    const bool no_row = wave_rows >= a.q_len;
     auto hidden_block = [&](uint32_t bits, bool partial, int kv, int kvb) __attribute__((always_inline)) {
-        if constexpr (Mask::kCanvas) return (bits & (1u << kvb)) != 0;
-        else return partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31);
+        if constexpr (Mask::kCanvas) return no_row || (bits & (1u << kvb)) != 0;
+        else return no_row || (partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31));
     };
     if constexpr (SPLIT) {
         // Wave w takes the 32-key units w, w + NW, ... that are not hidden from its rows, through LDS of its own and

@@ -1,5 +1,5 @@
 // The argument marshalling of binding.py for the calls of a training step and a decoding loop, in C++: a small call is bound
-// by its host side, of which building the C structures from Python took 3 to 4.5 us (forward over 256 tokens 9.2 -> 4.9 us
+// by its host side, of which building the C structures from Python took 3 to 5 us (forward over 256 tokens 9.2 -> 4.3 us
 // of host time, a decode with two launches 10.4 -> 7.3, with one 7.4 -> 4.2).
 //
 // Every function returns the status of the C entry point, or None where anything about the arguments is not plain
