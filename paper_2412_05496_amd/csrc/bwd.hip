@@ -51,6 +51,14 @@ bool stored_layout(const flexattn_dims* d, const flexattn_blockmask* bm, int64_t
     return true;
 }
 
+// Whether two tensors of the same heads and rows may share memory (the spans of their rows meet).
+bool may_overlap(const flexattn_tensor& a, const flexattn_tensor& b, int B, int H, int len, int D) {
+    auto end = [&](const flexattn_tensor& t) {
+        return (uintptr_t)t.ptr + 2 * (uintptr_t)((B - 1) * t.stride_b + (H - 1) * t.stride_h + (len - 1) * t.stride_s + D);
+    };
+    return (uintptr_t)a.ptr < end(b) && (uintptr_t)b.ptr < end(a);
+}
+
 // ds_blocks < 0: dQ recomputes S and dP; otherwise dS goes through memory (every stage runs).
 int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
                                         const flexattn_tensor* K, const flexattn_tensor* V, const flexattn_tensor* O,
@@ -128,6 +136,8 @@ int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
     a.kv_order = bm->kv_order; a.q_order = bm->q_order;
     a.scale = scale;
     if (params) a.p = *params;
+    a.dq_last = (stages & FLEXATTN_BWD_DQ) && (may_overlap(*dQ, *Q, dims->B, dims->Hq, dims->q_len, dims->D) ||
+                                               may_overlap(*dQ, *dO, dims->B, dims->Hq, dims->q_len, dims->D));
 
     hipStream_t st = (hipStream_t)stream;
     if (stored) {

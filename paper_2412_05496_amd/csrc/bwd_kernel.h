@@ -65,6 +65,7 @@ struct BwdArgs {
     float scale;
     flexattn_mod_params p;
     bool make_delta;           // the dQ kernel works the row scalars out itself (and writes them)
+    bool dq_last;              // (host) dQ is written over Q or dO: dK/dV runs first
 };
 
 constexpr uint32_t kBwdStageCaptured = 8u;   // internal: the captured-tensor sums instead of dQ

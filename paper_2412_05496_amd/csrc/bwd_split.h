@@ -579,15 +579,16 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
     const unsigned grid_kv = unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 64));
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
-    // dQ first where it makes the row scalars that dK/dV reads
-    if ((stages & FLEXATTN_BWD_DELTA) && !q && !(stages & kBwdStageCaptured)) {
+    // dQ first, where it makes the row scalars that dK/dV reads; last, after a pass that makes them, where it is written over
+    // Q or dO, which dK/dV reads
+    if ((stages & FLEXATTN_BWD_DELTA) && (!q || a.dq_last) && !(stages & kBwdStageCaptured)) {
         const size_t rows = (size_t)a.B * a.Hq * a.q_len;
         if (D == 128) hipLaunchKernelGGL((bwd_delta_kernel<128, SCORE>), dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, a);
         else hipLaunchKernelGGL((bwd_delta_kernel<64, SCORE>), dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, st, a);
     }
-    if (q) {
+    auto run_dq = [&] {
         BwdArgs aq = a;
-        aq.make_delta = stages & FLEXATTN_BWD_DELTA;
+        aq.make_delta = (stages & FLEXATTN_BWD_DELTA) && !a.dq_last;
         const int waves = dq_split_waves<MASK>(a, D);
         if (waves) {
             const dim3 slices(unit_grid(a.B * a.Hkv, a.G * a.NR * (a.Bq / 32)));
@@ -598,7 +599,8 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
         else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
         else if (a.Bq == 128) launch_dq64<MASK, SCORE>(aq, grid_q, st);
         else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
-    }
+    };
+    if (q && !a.dq_last) run_dq();
     if (kv) {
         const int waves = dkdv_split_waves<MASK>(a, D);
         if (waves) {
@@ -609,6 +611,7 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
         } else if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, a);
         else launch_dkdv64<MASK, SCORE>(a, grid_kv, st);
     }
+    if (q && a.dq_last) run_dq();
     if (stages & kBwdStageCaptured) {
         if constexpr ((SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS)) != 0) {
             if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);

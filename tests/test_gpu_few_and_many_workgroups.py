@@ -105,3 +105,28 @@ def test_paged_alone_and_in_a_batch(D, page, copies):
     torch.cuda.synchronize()
     hp.check_output(O[:4], LSE[:4], O_ref, LSE_ref)
     assert torch.equal(O, O[:4].repeat(copies, 1, 1, 1)) and torch.equal(LSE, LSE[:4].repeat(copies, 1, 1))
+
+
+@pytest.mark.parametrize("copies", [1, COPIES])
+@pytest.mark.parametrize("over", ["Q", "dO", "O"])
+def test_dq_written_over_a_tensor_of_its_shape(over, copies):
+    """dQ may take the memory of Q, dO or O: nothing reads a row of theirs after its dQ has been written."""
+    import paper_2412_05496_amd as fa
+    wl = wlm.CFG1.scaled(name="dq_over", B=copies, Hq=2, Hkv=1, S=419, D=64, mask="causal", score="identity", seed=9300)
+    inp = wlm.make_train_inputs(wl, with_dO=True)
+    mask_id, score_id, params, _ = hp.library_mods(wl, inp, DEV)
+    t = [x.to(DEV) for x in (inp.Q, inp.K, inp.V, inp.dO)]
+    bm = fa.alloc_blockmask(1, 1, wl.S, wl.S, wl.Bq, wl.Bk, device=DEV)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    for stored in (False, True):
+        O, LSE, *want = run(mask_id, score_id, params, 1, t, inp.scale, wl.Bq, wl.Bk, stored)
+        Q, K, V, dO = (x.clone() for x in t)
+        dQ, dK, dV = {"Q": Q, "dO": dO, "O": O}[over], torch.empty_like(K), torch.empty_like(V)
+        args = (Q, K, V, O, dO, LSE, score_id, mask_id, params, bm, inp.scale, dQ, dK, dV)
+        if stored:
+            fa.flexattn_backward_stored(*args, hp.nonempty_blocks(bm))
+        else:
+            fa.flexattn_backward(*args)
+        torch.cuda.synchronize()
+        for got, ref in zip((dQ, dK, dV), want):
+            assert torch.equal(got, ref)
