@@ -278,9 +278,11 @@ int flexattn_backward_stages(const flexattn_dims* dims,
  * 4.2's transposed walk) and dQ = scale * dS K is then one block-sparse product over the written
  * blocks: the backward executes the five matrix products of its definition instead of seven.
  * Whether it pays depends on what the recomputation costs against 4 bytes of HBM traffic per
- * unmasked score: measured on MI355X it is 9-15 % faster at D = 128 (soft-cap, relative bias,
- * neighborhood attention), even at D = 64 with a soft-cap, and slower at D = 64 otherwise: 3-7 % for
- * neighborhood attention, 1-10 % for documents with ALiBi, 22 % with a plain causal score.
+ * unmasked score: measured on MI355X it is 2-15 % faster at D = 128 (soft-cap, relative bias,
+ * neighborhood attention), 3 % at D = 64 with a soft-cap, and slower at D = 64 otherwise (4-25 %) and for
+ * small launches, whose dS is small but takes three launches more.  dQ therefore
+ * recomputes dS where that is faster (but never if it is written over V), in a call of one stage
+ * as in a call of all, with the same bits; only the latter then leaves the dS blocks unwritten.
  *   n_blocks  capacity, in blocks of Bq x Bk scores: at least the number of non-empty (PARTIAL +
  *             FULL) blocks of the BlockMask, all planes together -- stats[0] + stats[1] of
  *             flexattn_blockmask_build.  A smaller value gives wrong gradients for the blocks that

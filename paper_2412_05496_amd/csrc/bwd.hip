@@ -51,12 +51,36 @@ bool stored_layout(const flexattn_dims* d, const flexattn_blockmask* bm, int64_t
     return true;
 }
 
-// Whether two tensors of the same heads and rows may share memory (the spans of their rows meet).
-bool may_overlap(const flexattn_tensor& a, const flexattn_tensor& b, int B, int H, int len, int D) {
-    auto end = [&](const flexattn_tensor& t) {
-        return (uintptr_t)t.ptr + 2 * (uintptr_t)((B - 1) * t.stride_b + (H - 1) * t.stride_h + (len - 1) * t.stride_s + D);
-    };
-    return (uintptr_t)a.ptr < end(b) && (uintptr_t)b.ptr < end(a);
+// Whether two tensors may share memory (the spans of their rows meet).
+struct Span {
+    uintptr_t lo, hi;
+    Span(const flexattn_tensor* t, int B, int H, int len, int D)
+        : lo((uintptr_t)t->ptr), hi(lo + 2 * (uintptr_t)((B - 1) * t->stride_b + (H - 1) * t->stride_h + (len - 1) * t->stride_s + D)) {}
+    bool meets(const Span& o) const { return lo < o.hi && o.lo < hi; }
+};
+
+// Whether dS through memory is faster than recomputing it for dQ.  Memory costs 4 bytes a score and three more small launches
+// (about 8 us); recomputing costs two matrix products and the score_mod, which at D = 64 is the less, but for a soft-cap on
+// long rows.  us of the whole backward, dS in memory -> recomputed:
+//   D = 64     causal, S = 1024, 64 x 16 heads 916 -> 736; S = 4096, 64 heads 630 -> 539; S = 256, 2 heads 22.5 -> 14.1; no mask, S = 2048,
+//              8 x 16 593 -> 477; window of 1024, S = 5000, 4 x 16 / 2 388 -> 321; documents with ALiBi, S = 16384 461 -> 394;
+//   soft-cap   8 heads, S = 1024 33.0 -> 22.9, 2048 55.8 -> 44.0; 32 x 16, S = 512 175 -> 160; 4 heads, S = 8192 207 -> 198; but 32, S = 2048 124 ->
+//              142, 32, S = 8192 1244 -> 1281; window of 1024, S = 5000, 4 x 16 / 4 430 -> 414;
+//   canvases   (whose blocks are mostly hidden parts, which dS in memory leaves out at the granularity of a wave's 32 x 32)
+//              64 x 64 pixels, K = 13, 4 / 16 heads 40.7 -> 32.5, 73.4 -> 72.0; 128 x 128, 2 heads 52.2 -> 52.9, row-major 87 -> 101, 8 heads 129
+//              -> 124, row-major 240 -> 255, 64 heads 990 -> 881; 100 x 100, row-major, K = 9, 2 x 16 / 4 386 -> 370;
+//   D = 128    only small launches: causal, 16 heads, S = 512 32.7 -> 25.0, 8 x 16 84.7 -> 77.7; 2 heads, S = 4096 109 -> 90; 8 heads, S = 2048
+//              75.5 -> 66.8; window of 512, 32 heads, S = 2048 99.4 -> 95.8; 4 heads, S = 8192 290 -> 338; soft-cap, 8 heads, S = 1024 43.8 -> 38.1,
+//              32 / 8 heads 87.5 -> 92.6; 32 x 32 pixels, 8 heads 43.3 -> 35.1, 64 x 64, 4 heads 51.9 -> 54.9.
+// The lines go by slices of 32 query rows and by the longest row (line_shape).
+bool stored_pays(const flexattn_dims* d, uint32_t mask_id, uint32_t score_id, const flexattn_mod_params& p) {
+    const int64_t slices = (int64_t)d->B * d->Hq * ((d->q_len + 31) / 32);
+    const LineShape rows = line_shape(mask_id, p, d->q_len, d->kv_len);
+    const bool cap = score_id & FLEXATTN_SCORE_SOFTCAP;
+    if (mask_uses(mask_id, FLEXATTN_M_NEIGHBORHOOD)) return d->D == 64 ? d->q_len > 4096 && slices < 8192 : slices > 256;
+    if (d->D == 64) return cap && slices > 1024 && rows.longest >= (rows.uneven ? 1024 : 1536);
+    if (cap) return slices > 256;
+    return slices > 512 && (rows.longest > 1024 || slices >= 4096);
 }
 
 // ds_blocks < 0: dQ recomputes S and dP; otherwise dS goes through memory (every stage runs).
@@ -90,7 +114,7 @@ int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
     if ((rc = check_canvas(mask_id, params, dims->q_len, dims->kv_len)) != FLEXATTN_OK) return rc;
     const int vi = find_variant(mask_id, score_id);
     if (vi < 0) return FLEXATTN_ERR_UNSUPPORTED;
-    const bool stored = ds_blocks >= 0;
+    bool stored = ds_blocks >= 0;
     StoredLayout lay = {};
     if (stored) {
         if (!stored_layout(dims, bm, ds_blocks, &lay)) return FLEXATTN_ERR_INVALID_ARG;
@@ -106,16 +130,6 @@ int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
     a.dQ = (bf16*)dQ->ptr; a.dK = (bf16*)dK->ptr; a.dV = (bf16*)dV->ptr;
     const size_t rows = (size_t)dims->B * dims->Hq * dims->q_len;
     a.delta = (float*)ws; a.lse2 = (float*)ws + rows;
-    int32_t* colbase = nullptr;
-    int32_t* grid = nullptr;
-    if (stored) {
-        colbase = (int32_t*)((char*)ws + lay.colbase_off);
-        grid = (int32_t*)((char*)ws + lay.grid_off);
-        a.ds_colbase = colbase;
-        a.ds_grid = grid;
-        a.ds_store = (bf16*)((char*)ws + lay.store_off);
-        a.ds_blocks = lay.cap;
-    }
     a.q_sb = Q->stride_b; a.q_sh = Q->stride_h; a.q_ss = Q->stride_s;
     a.k_sb = K->stride_b; a.k_sh = K->stride_h; a.k_ss = K->stride_s;
     a.v_sb = V->stride_b; a.v_sh = V->stride_h; a.v_ss = V->stride_s;
@@ -136,23 +150,39 @@ int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
     a.kv_order = bm->kv_order; a.q_order = bm->q_order;
     a.scale = scale;
     if (params) a.p = *params;
-    a.dq_last = (stages & FLEXATTN_BWD_DQ) && (may_overlap(*dQ, *Q, dims->B, dims->Hq, dims->q_len, dims->D) ||
-                                               may_overlap(*dQ, *dO, dims->B, dims->Hq, dims->q_len, dims->D));
+    bool dq_from_memory = stored;
+    if (stages & FLEXATTN_BWD_DQ) {
+        // outputs written over inputs: dQ over Q or dO waits for dK/dV; with dS in memory it may also take V's place
+        const Span dq(dQ, dims->B, dims->Hq, dims->q_len, dims->D);
+        a.dq_last = dq.meets(Span(Q, dims->B, dims->Hq, dims->q_len, dims->D)) || dq.meets(Span(dO, dims->B, dims->Hq, dims->q_len, dims->D));
+        // (a dK/dV stage by itself always writes dS: it does not know where dQ will go)
+        if (stored && !dq.meets(Span(V, dims->B, dims->Hkv, dims->kv_len, dims->D))) dq_from_memory = stored_pays(dims, mask_id, score_id, a.p);
+        if (stages == FLEXATTN_BWD_ALL) stored = dq_from_memory;
+    }
 
     hipStream_t st = (hipStream_t)stream;
     if (stored) {
+        int32_t* colbase = (int32_t*)((char*)ws + lay.colbase_off);
+        int32_t* grid = (int32_t*)((char*)ws + lay.grid_off);
+        a.ds_colbase = colbase;
+        a.ds_grid = grid;
+        a.ds_store = (bf16*)((char*)ws + lay.store_off);
+        a.ds_blocks = lay.cap;
         if (stages & FLEXATTN_BWD_DELTA) {      // the block numbering belongs to the pre-pass
             hipLaunchKernelGGL(bwd_slots_scan_kernel, dim3(1), dim3(1024), 0, st, a.q_num, a.full_q_num, lay.lines,
                                a.NR, colbase);
             hipLaunchKernelGGL(bwd_slots_fill_kernel, dim3((unsigned)lay.lines), dim3(256), 0, st, a.q_num, a.q_idx,
                                a.full_q_num, a.full_q_idx, a.NR, a.NC, colbase, grid);
         }
-        // delta and dK/dV (which writes dS) from the compiled variant; dQ from what it wrote
+        // delta and dK/dV (which writes dS) from the compiled variant; dQ from what it wrote, or recomputed
         if (stages & (FLEXATTN_BWD_DELTA | FLEXATTN_BWD_DKDV)) {
             rc = kBwdLaunchers[vi](a, dims->D, stages & (FLEXATTN_BWD_DELTA | FLEXATTN_BWD_DKDV), st);
             if (rc != FLEXATTN_OK) return rc;
         }
-        if (stages & FLEXATTN_BWD_DQ) {
+        if ((stages & FLEXATTN_BWD_DQ) && !dq_from_memory) {
+            rc = kBwdLaunchers[vi](a, dims->D, FLEXATTN_BWD_DQ, st);
+            if (rc != FLEXATTN_OK) return rc;
+        } else if (stages & FLEXATTN_BWD_DQ) {
             const float qscale = scale * ((score_id & FLEXATTN_SCORE_SOFTCAP) ? 4.0f : 1.0f);   // ScoreMod::grad_scale()
             if (mask_uses(mask_id, FLEXATTN_M_NEIGHBORHOOD)) launch_bwd_stored_dq<true>(a, dims->D, qscale, st);
             else launch_bwd_stored_dq<false>(a, dims->D, qscale, st);

@@ -697,9 +697,8 @@ struct LineShape {
     int64_t longest;
     bool uneven;
 };
-template <uint32_t MASK>
-LineShape line_shape(const flexattn_mod_params& p, int q_len, int kv_len) {
-    constexpr uint32_t prims = MASK | (MASK >> 8);
+inline LineShape line_shape(uint32_t mask, const flexattn_mod_params& p, int q_len, int kv_len) {
+    const uint32_t prims = mask | (mask >> 8);
     LineShape s = {kv_len, (prims & FLEXATTN_M_DOCUMENT) || ((prims & FLEXATTN_M_CAUSAL) && 2 * (int64_t)q_len > kv_len)};
     if (prims & FLEXATTN_M_SLIDING_WINDOW) {
         const int64_t reach = (int64_t)p.window + 1 + ((prims & FLEXATTN_M_PREFIX) ? p.prefix_len : 0);
@@ -707,6 +706,10 @@ LineShape line_shape(const flexattn_mod_params& p, int q_len, int kv_len) {
         if (reach < s.longest) s.longest = reach;
     }
     return s;
+}
+template <uint32_t MASK>
+LineShape line_shape(const flexattn_mod_params& p, int q_len, int kv_len) {
+    return line_shape(MASK, p, q_len, kv_len);
 }
 inline bool score_id_valid(uint32_t s) { return (s & ~7u) == 0; }
 constexpr bool mask_uses(uint32_t m, uint32_t prim) { return ((m | (m >> 8)) & prim) != 0; }

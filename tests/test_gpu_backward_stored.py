@@ -179,3 +179,61 @@ def test_stored_strided_layout_and_stages_agree():
                                     dVs if stage == fa.BWD_DKDV else None, n_blocks, ws, stage)
     torch.cuda.synchronize()
     assert torch.equal(dQs, dQ) and torch.equal(dKs, dK) and torch.equal(dVs, dV)
+
+
+# (name, base, overrides, q_len, kv_len): both sides of the lines between dS in memory and recomputed dS
+ROUTES = [
+    ("none_d64_q128_kv66560", wlm.CFG1, dict(B=1, Hq=1, Hkv=1, S=66560, D=64, Bq=64, Bk=64, mask="none"), 128, 66560),
+    ("none_d64_q66560_kv128", wlm.CFG1, dict(B=1, Hq=1, Hkv=1, S=66560, D=64, Bq=64, Bk=64, mask="none"), 66560, 128),
+    ("causal_d64_s999", wlm.CFG1, dict(B=2, Hq=4, Hkv=2, S=999, D=64, Bq=64, Bk=128, mask="causal"), 999, 999),
+    ("causal_softcap_d64_1024_slices", wlm.CFG2, dict(B=1, Hq=32, Hkv=8, S=1024, D=64), 1024, 1024),
+    ("causal_softcap_d64_1056_slices", wlm.CFG2, dict(B=1, Hq=32, Hkv=8, S=1030, D=64), 1030, 1030),
+    ("causal_softcap_d128_256_slices", wlm.CFG2, dict(B=1, Hq=8, Hkv=8, S=1020), 1020, 1020),
+    ("causal_softcap_d128_264_slices", wlm.CFG2, dict(B=1, Hq=8, Hkv=8, S=1028), 1028, 1028),
+    ("causal_d128_528_slices_1025_keys", wlm.CFG2, dict(B=1, Hq=16, Hkv=4, S=1025, score="identity"), 1025, 1025),
+    ("causal_d128_528_slices_1024_keys", wlm.CFG2, dict(B=1, Hq=33, Hkv=3, S=512, score="identity"), 512, 512),
+    ("causal_d64_s999_two_heads", wlm.CFG1, dict(B=1, Hq=2, Hkv=2, S=999, D=64, mask="causal"), 999, 999),
+    ("document_alibi_d64_s701", wlm.CFG3, dict(B=1, Hq=3, Hkv=3, S=701, doc_len_min=20, doc_len_max=300), 701, 701),
+    ("document_alibi_d64", wlm.CFG3, dict(B=2, Hq=4, Hkv=2, S=700, doc_len_min=20, doc_len_max=300), 700, 700),
+]
+
+
+@pytest.mark.parametrize("case", ROUTES, ids=[c[0] for c in ROUTES])
+def test_stored_single_stages_and_whole_call(case):
+    """The whole call, the stages one by one and a dQ in V's place, which always goes through memory: against the oracle,
+    the first two bit for bit the same, dK and dV in all, the workspace full of NaN patterns."""
+    import paper_2412_05496_amd as fa
+    name, base, over, Lq, Lk = case
+    wl = base.scaled(name="route_" + name, seed=4700 + len(name), backward=True, **over)
+    inp = wlm.make_train_inputs(wl, with_dO=True)
+    Q, dO = inp.Q[:, :, :Lq].contiguous(), inp.dO[:, :, :Lq].contiguous()
+    K, V = inp.K[:, :, :Lk].contiguous(), inp.V[:, :, :Lk].contiguous()
+    score_mod, mask_mod = oracle_mods(wl, inp)
+    print(f"[case] dS kept in memory, stages and whole call: {name}", flush=True)
+    ref = fo.flex_attention_backward(Q, K, V, dO, score_mod, mask_mod, inp.scale)
+    mask_id, score_id, params, Bm = library_mods(wl, inp, DEV)
+    bm = fa.alloc_blockmask(Bm, 1, Lq, Lk, wl.Bq, wl.Bk, device=DEV)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    Qd, Kd, Vd, dOd = Q.to(DEV), K.to(DEV), V.to(DEV), dO.to(DEV)
+    O = torch.empty_like(Qd)
+    LSE = torch.empty(Qd.shape[:3], dtype=torch.float32, device=DEV)
+    fa.flexattn_forward(Qd, Kd, Vd, score_id, mask_id, params, bm, inp.scale, O, LSE)
+    n_blocks = nonempty_blocks(bm)
+    got = {}
+    for stages in ((fa.BWD_ALL,), (fa.BWD_DELTA, fa.BWD_DKDV, fa.BWD_DQ), "dQ over V"):
+        over_v = stages == "dQ over V"
+        if over_v and Qd.shape != Vd.shape:
+            continue
+        V_in = Vd.clone()
+        g = [V_in if over_v else torch.full_like(Qd, float("nan")), torch.full_like(Kd, float("nan")), torch.full_like(Kd, float("nan"))]
+        ws = torch.full((fa.flexattn_backward_stored_workspace_bytes(Qd, Kd, bm, n_blocks),), 0xFF, dtype=torch.uint8, device=DEV)
+        for stage in (fa.BWD_ALL,) if over_v else stages:
+            fa.flexattn_backward_stored(Qd, Kd, V_in, O, dOd, LSE, score_id, mask_id, params, bm, inp.scale, *g, n_blocks, ws, stage)
+        torch.cuda.synchronize()
+        got[stages] = g
+        for n, x, r in zip(("dQ", "dK", "dV"), g, ref):
+            check_grad(n, x, r)
+    first = got[(fa.BWD_ALL,)]
+    for stages, g in got.items():
+        assert torch.equal(g[1], first[1]) and torch.equal(g[2], first[2])
+        assert stages == "dQ over V" or torch.equal(g[0], first[0])
