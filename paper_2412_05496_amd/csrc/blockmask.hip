@@ -9,15 +9,14 @@
 // ids, or whose pixels match), whose population is the count.  Pixels are all different, and ids in any order may be:
 // those keys are compared one by one (a ballot for each, us -> this: 64 x 64 pixels, K = 41 102 -> 51, row-major 107 -> 51,
 // 128 x 128, K = 101 268 -> 136; 64 ids at random, S = 4096 89 -> 57).
-// What bounds it is latency, not arithmetic: three short kernels.  (A wave per block that evaluated
+// What bounds it is latency, not arithmetic: two short kernels (us on packed documents, S = 16384, before the ids were read 16
+// bytes at a time, the next block's asked for ahead, and the statistics summed without atomics: 38 -> 22; 16 x 4096 46 -> 26).  (A wave per block that evaluated
 // mask_mod scalar by scalar, 8192 to a block, and then one wave per line to compact: 0.18 ms on packed
 // documents of 16384 tokens, 0.11 ms for four causal chunks of 2048 queries on 16384 keys, 0.49 ms for
 // 128 x 128 pixels.)
 #include "flex_common.h"
 
 namespace flexattn {
-
-constexpr int kLineThreads = 256, kLineWaves = kLineThreads / 64;
 
 // What the tokens of one side of a block have in common.  Documents: ids in [a0, a1].  Canvas: keys with
 // x in [a0, a1] and y in [b0, b1]; queries whose windows start at x0 in [a0, a1], y0 in [b0, b1].
@@ -39,24 +38,44 @@ struct BlockEval {
         : mask(p, b, kv_len_), docs(Partial::kDoc ? p.doc_ids + (int64_t)b * p.doc_stride_b : nullptr),
           q_off(q_offset_of(p, b)), q_len(q_len_), kv_len(kv_len_), Bq(Bq_), Bk(Bk_) {}
 
-    // one token more of the key (query) side of a block
-    __device__ __forceinline__ void take_key(TokenRange& r, int kv) const {
-        if constexpr (Partial::kDoc) take(r.a0, r.a1, docs[kv]);
+    // n tokens more of the key (query) side of a block
+    __device__ __forceinline__ void take_keys(TokenRange& r, int kv, int n) const {
+        if constexpr (Partial::kDoc) take_ids(r, docs + kv, n);
         if constexpr (Partial::kCanvas) {
-            int x, y;
-            mask.canvas.pixel(kv, x, y);
-            take(r.a0, r.a1, x);
-            take(r.b0, r.b1, y);
+            for (int t = 0; t < n; ++t) {
+                int x, y;
+                mask.canvas.pixel(kv + t, x, y);
+                take(r.a0, r.a1, x);
+                take(r.b0, r.b1, y);
+            }
         }
     }
-    __device__ __forceinline__ void take_query(TokenRange& r, int q) const {
-        if constexpr (Partial::kDoc) take(r.a0, r.a1, docs[q_off + q]);
+    __device__ __forceinline__ void take_queries(TokenRange& r, int q, int n) const {
+        if constexpr (Partial::kDoc) take_ids(r, docs + q_off + q, n);
         if constexpr (Partial::kCanvas) {
-            int x, y;
-            mask.window_corner(q_off + q, x, y);
-            take(r.a0, r.a1, x);
-            take(r.b0, r.b1, y);
+            for (int t = 0; t < n; ++t) {
+                int x, y;
+                mask.window_corner(q_off + q + t, x, y);
+                take(r.a0, r.a1, x);
+                take(r.b0, r.b1, y);
+            }
         }
+    }
+    // A thread reads the ids of its block 16 bytes at a time (at any element address), eight loads under way: a load per id
+    // touches 64 cache lines a wave as well and is waited for four times as often.
+    __device__ __forceinline__ static void take_ids(TokenRange& r, const int32_t* ids, int n) {
+        typedef int32_t quad __attribute__((ext_vector_type(4), aligned(4)));
+        int t = 0;
+        for (; t + 32 <= n; t += 32) {
+            quad v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = *(const quad*)(ids + t + 4 * i);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) take(r.a0, r.a1, v[i][e]);
+        }
+        for (; t < n; ++t) take(r.a0, r.a1, ids[t]);
     }
     __device__ __forceinline__ static void take(int& lo, int& hi, int v) {
         lo = min(lo, v);
@@ -112,55 +131,76 @@ struct BlockEval {
         if constexpr (TERM & FLEXATTN_M_SLIDING_WINDOW) lo = max(__builtin_elementwise_sub_sat(q, mask.window), 0);
         return span_bits(lo, hi, kv0) & ((TERM & Partial::kTagged) ? match : ~0ull);
     }
-    static constexpr int kBallots = 6;
-    // Unmasked scalars of block (i, j), counted by the whole wave.
-    __device__ __forceinline__ int count(int i, int j, int lane) const {
-        int cnt = 0;
-        const int rows = rows_of(i), keys = keys_of(j);
-        for (int r0 = 0; r0 < rows; r0 += 64) {
-            const int q = q_off + i * Bq + min(r0 + lane, rows - 1);
-            uint32_t q_tag = 0;
-            if constexpr (Partial::kDoc) q_tag = (uint32_t)docs[q];
-            if constexpr (Partial::kCanvas) q_tag = mask.query_pixel(q);
-            int mine = 0;
-            for (int k0 = 0; k0 < keys; k0 += 64) {
-                const int kv0 = j * Bk + k0, n = min(64, keys - k0);
-                uint64_t match = ~0ull;
-                if constexpr (Partial::kTags) {
-                    const int kv = min(kv0 + lane, kv_len - 1);
-                    uint32_t k_tag = 0;
-                    if constexpr (Partial::kDoc) k_tag = (uint32_t)docs[kv];
-                    if constexpr (Partial::kCanvas) k_tag = mask.key_pixel(kv);
-                    match = 0;
-                    uint64_t left = ~0ull >> (64 - n);
-                    if constexpr (Partial::kDoc) {      // the first ids by one ballot each
-                        for (int i = 0; i < kBallots && left != 0; ++i) {
-                            const uint32_t tag = (uint32_t)__builtin_amdgcn_readlane((int)k_tag, __builtin_ctzll(left));
-                            const uint64_t same = __ballot(k_tag == tag);
-                            left &= ~same;
-                            match |= tag == q_tag ? same : 0ull;
-                        }
-                    }
-                    if (left != 0) {                    // key by key
-                        uint32_t part[2] = {0u, 0u};
+    // The document ids of up to 128 rows and 128 keys of a block, two of each to a lane.  (Pixels are worked out where they are used.)
+    struct Tags {
+        uint32_t q[2], k[2];
+    };
+    __device__ __forceinline__ Tags tags(int i, int j, int r0, int k0, int lane) const {
+        Tags t = {};
+        if constexpr (Partial::kDoc) {
 #pragma unroll
-                        for (int at = 0; at < 64; ++at) {
-                            const uint32_t tag = (uint32_t)__builtin_amdgcn_readlane((int)k_tag, at);
-                            const bool same = Partial::kDoc ? tag == q_tag : mask.pixels_match(tag, q_tag);
-                            part[at >> 5] |= same ? 1u << (at & 31) : 0u;
-                        }
-                        match |= (uint64_t)part[1] << 32 | part[0];
-                    }
-                }
-                uint64_t bits = term_bits<T0>(q, kv0, match);
-                if constexpr (T1 != 0) bits |= term_bits<T1>(q, kv0, match);
-                mine += __popcll(bits & (~0ull >> (64 - n)));
+            for (int c = 0; c < 2; ++c) {
+                t.q[c] = (uint32_t)docs[q_off + i * Bq + min(r0 + 64 * c + lane, rows_of(i) - 1)];
+                t.k[c] = (uint32_t)docs[j * Bk + min(k0 + 64 * c + lane, keys_of(j) - 1)];
             }
-            cnt += r0 + lane < rows ? mine : 0;
         }
+        return t;
+    }
+    // Unmasked scalars of block (i, j) in the rows of this lane, by the whole wave.  first: its tags(i, j, 0, 0, lane);
+    // all: whether every pair of a whole block is visible.
+    static constexpr int kBallots = 6, kUnroll = Partial::kCanvas ? 1 : 4;      // (a canvas' keys are long unrolled code as it is)
+    __device__ __forceinline__ int count(int i, int j, int lane, const Tags& first, bool& all) const {
+        const int rows = rows_of(i), keys = keys_of(j);
+        int sum = 0;
+        bool seen = rows == Bq && keys == Bk;
+        for (int r0 = 0; r0 < rows; r0 += 128) {
+            for (int k0 = 0; k0 < keys; k0 += 128) {
+                const Tags t = r0 == 0 && k0 == 0 ? first : tags(i, j, r0, k0, lane);
+#pragma unroll kUnroll
+                for (int c = 0; c < 4; ++c) {
+                    const int rc = r0 + 64 * (c >> 1), kc = k0 + 64 * (c & 1);
+                    if (rc >= rows || kc >= keys) continue;
+                    const int q = q_off + i * Bq + min(rc + lane, rows - 1), kv0 = j * Bk + kc, n = min(64, keys - kc);
+                    uint32_t q_tag = c & 2 ? t.q[1] : t.q[0], k_tag = c & 1 ? t.k[1] : t.k[0];
+                    if constexpr (Partial::kCanvas) {
+                        q_tag = mask.query_pixel(q);
+                        k_tag = mask.key_pixel(min(kv0 + lane, kv_len - 1));
+                    }
+                    const uint64_t match = tag_bits(q_tag, k_tag, ~0ull >> (64 - n));
+                    uint64_t bits = term_bits<T0>(q, kv0, match);
+                    if constexpr (T1 != 0) bits |= term_bits<T1>(q, kv0, match);
+                    const int mine = __popcll(bits & (~0ull >> (64 - n)));
+                    sum += rc + lane < rows ? mine : 0;
+                    seen = seen && mine == n;
+                }
+            }
+        }
+        all = __all(seen);
+        return sum;
+    }
+    // the keys among `there` (a bit per lane) whose tag matches the lane's query
+    __device__ __forceinline__ uint64_t tag_bits(uint32_t q_tag, uint32_t k_tag, uint64_t there) const {
+        if constexpr (!Partial::kTags) return ~0ull;
+        uint64_t match = 0;
+        if constexpr (Partial::kDoc) {      // the first ids by one ballot each
+            for (int i = 0; i < kBallots && there != 0; ++i) {
+                const uint32_t tag = (uint32_t)__builtin_amdgcn_readlane((int)k_tag, __builtin_ctzll(there));
+                const uint64_t same = __ballot(k_tag == tag);
+                there &= ~same;
+                match |= tag == q_tag ? same : 0ull;
+            }
+        }
+        if (there != 0) {                   // key by key
+            uint32_t part[2] = {0u, 0u};
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
-        return cnt;
+            for (int at = 0; at < 64; ++at) {
+                const uint32_t tag = (uint32_t)__builtin_amdgcn_readlane((int)k_tag, at);
+                const bool same = Partial::kDoc ? tag == q_tag : mask.pixels_match(tag, q_tag);
+                part[at >> 5] |= same ? 1u << (at & 31) : 0u;
+            }
+            match |= (uint64_t)part[1] << 32 | part[0];
+        }
+        return match;
     }
 };
 
@@ -168,12 +208,14 @@ struct LineArgs {
     flexattn_mod_params p;
     int Bm, Hm, NR, NC, Bq, Bk, q_len, kv_len;
     int32_t *kv_num, *kv_idx, *full_kv_num, *full_kv_idx, *q_num, *q_idx, *full_q_num, *full_q_idx;
-    unsigned long long* stats;   // nullable
+    unsigned long long* stats;          // nullable
+    unsigned long long* row_scalars;    // unmasked scalars of every row of blocks (null: added to stats by atomics)
 };
 
-template <uint32_t MASK>
+template <uint32_t MASK, int kLineThreads>
 __global__ __launch_bounds__(kLineThreads) void build_lines_kernel(const LineArgs a) {
     using Eval = BlockEval<MASK>;
+    constexpr int kLineWaves = kLineThreads / 64;
     constexpr bool kTags = Eval::Partial::kTags;
     __shared__ TokenRange s_fixed;                 // the tokens of the line itself
     __shared__ uint8_t s_kind[kLineThreads];
@@ -199,8 +241,8 @@ __global__ __launch_bounds__(kLineThreads) void build_lines_kernel(const LineArg
             if (tid == 0) s_fixed = kNoTokens;
             __syncthreads();
             TokenRange r = kNoTokens;
-            if (is_row) for (int t = tid; t < ev.rows_of(self); t += kLineThreads) ev.take_query(r, self * a.Bq + t);
-            else for (int t = tid; t < ev.keys_of(self); t += kLineThreads) ev.take_key(r, self * a.Bk + t);
+            if (is_row) for (int t = tid; t < ev.rows_of(self); t += kLineThreads) ev.take_queries(r, self * a.Bq + t, 1);
+            else for (int t = tid; t < ev.keys_of(self); t += kLineThreads) ev.take_keys(r, self * a.Bk + t, 1);
             atomicMin(&s_fixed.a0, r.a0);
             atomicMax(&s_fixed.a1, r.a1);
             if constexpr (Eval::Partial::kCanvas) {
@@ -220,8 +262,8 @@ __global__ __launch_bounds__(kLineThreads) void build_lines_kernel(const LineArg
                 if constexpr (kTags) {
                     if (kind == 1) {
                         TokenRange r = kNoTokens;
-                        if (is_row) for (int t = 0; t < ev.keys_of(k); ++t) ev.take_key(r, k * a.Bk + t);
-                        else for (int t = 0; t < ev.rows_of(k); ++t) ev.take_query(r, k * a.Bq + t);
+                        if (is_row) ev.take_keys(r, k * a.Bk, ev.keys_of(k));
+                        else ev.take_queries(r, k * a.Bq, ev.rows_of(k));
                         kind = is_row ? ev.kind(i, j, s_fixed, r) : ev.kind(i, j, r, s_fixed);
                     }
                 }
@@ -229,13 +271,29 @@ __global__ __launch_bounds__(kLineThreads) void build_lines_kernel(const LineArg
             }
             s_kind[tid] = (uint8_t)kind;
             __syncthreads();
-            for (int t = wave; t < s_ntodo; t += kLineWaves) {
-                const int kk = s_todo[t];
-                const int cnt = is_row ? ev.count(self, c0 + kk, lane) : ev.count(c0 + kk, self, lane);
-                if (lane == 0) {
-                    const int full = cnt == a.Bq * a.Bk;
-                    s_kind[kk] = (uint8_t)(cnt == 0 ? 0 : (full ? 2 : 1));
-                    if (!full) atomicAdd(&s_scalars, (unsigned long long)cnt);
+            const int n_todo = s_ntodo;
+            // (the tags of the wave's next block are asked for before this one's are used)
+            auto tags_of = [&](int t) __attribute__((always_inline)) {
+                const int kk = __builtin_amdgcn_readfirstlane((int)s_todo[min(t, n_todo - 1)]) + c0;
+                return is_row ? ev.tags(self, kk, 0, 0, lane) : ev.tags(kk, self, 0, 0, lane);
+            };
+            if (wave < n_todo) {
+                unsigned long long scalars = 0;
+                typename Eval::Tags next = tags_of(wave);
+                for (int t = wave; t < n_todo; t += kLineWaves) {
+                    const typename Eval::Tags now = next;
+                    next = tags_of(t + kLineWaves);
+                    const int kk = __builtin_amdgcn_readfirstlane((int)s_todo[t]);
+                    bool full;
+                    const int mine = is_row ? ev.count(self, c0 + kk, lane, now, full) : ev.count(c0 + kk, self, lane, now, full);
+                    const bool any = __any(mine != 0);
+                    if (lane == 0) s_kind[kk] = (uint8_t)(any ? (full ? 2 : 1) : 0);
+                    scalars += full ? 0 : mine;
+                }
+                if (is_row && a.stats) {                // (only the rows' are reported)
+#pragma unroll
+                    for (int off = 32; off > 0; off >>= 1) scalars += __shfl_xor(scalars, off, 64);
+                    if (lane == 0) atomicAdd(&s_scalars, scalars);
                 }
             }
             __syncthreads();
@@ -263,10 +321,12 @@ __global__ __launch_bounds__(kLineThreads) void build_lines_kernel(const LineArg
         if (tid == 0) {
             (is_row ? a.kv_num : a.q_num)[line] = np;
             (is_row ? a.full_kv_num : a.full_q_num)[line] = nf;
-            if (is_row && a.stats) {
+            const unsigned long long scalars = s_scalars + (unsigned long long)nf * (unsigned)(a.Bq * a.Bk);
+            if (is_row && a.row_scalars) {
+                a.row_scalars[line] = scalars;
+            } else if (is_row && a.stats) {
                 if (np) atomicAdd(&a.stats[0], (unsigned long long)np);
                 if (nf) atomicAdd(&a.stats[1], (unsigned long long)nf);
-                const unsigned long long scalars = s_scalars + (unsigned long long)nf * (unsigned)(a.Bq * a.Bk);
                 if (scalars) atomicAdd(&a.stats[3], scalars);
                 if (id == 0) atomicAdd(&a.stats[2], (unsigned long long)(row_lines * a.NC));
             }
@@ -280,10 +340,36 @@ __global__ __launch_bounds__(kLineThreads) void build_lines_kernel(const LineArg
 // counted by one thread over a copy of all keys in LDS: no passes and no barriers in between, which is
 // what a sort of a few hundred lines consists of otherwise (bitonic: 7.6 us for 256 lines).  More than
 // kOrderMax lines are left in the fixed order: descending index for rows, ascending for columns.
+//
+// One workgroup beside them adds up the statistics of the rows.
+__device__ __forceinline__ void sum_stats(const LineArgs& a) {
+    __shared__ unsigned long long s_sum[4][3];
+    const long long rows = (long long)a.Bm * a.Hm * a.NR;
+    unsigned long long sum[3] = {0, 0, 0};
+#pragma unroll 4
+    for (long long r = threadIdx.x; r < rows; r += 256) {
+        sum[0] += (unsigned)a.kv_num[r];
+        sum[1] += (unsigned)a.full_kv_num[r];
+        sum[2] += a.row_scalars[r];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum[i] += __shfl_xor(sum[i], off, 64);
+        if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6][i] = sum[i];
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) a.stats[threadIdx.x < 2 ? threadIdx.x : 3] = s_sum[0][threadIdx.x] + s_sum[1][threadIdx.x] + s_sum[2][threadIdx.x] + s_sum[3][threadIdx.x];
+    if (threadIdx.x == 3) a.stats[2] = (unsigned long long)(rows * a.NC);
+}
 constexpr int kOrderMax = 8192, kOrderIdxBits = 13, kOrderCountMax = (1 << 18) - 1;
 __global__ __launch_bounds__(256) void order_lines_kernel(const LineArgs a, int32_t* __restrict__ kv_order,
                                                           int32_t* __restrict__ q_order) {
     __shared__ __attribute__((aligned(16))) uint32_t keys[kOrderMax];
+    if (blockIdx.y == 2) {
+        if (blockIdx.x == 0 && blockIdx.z == 0) sum_stats(a);
+        return;
+    }
     const bool rows = blockIdx.y == 0;
     int32_t* order = rows ? kv_order : q_order;
     const int n = rows ? a.NR : a.NC;
@@ -343,7 +429,16 @@ template <uint32_t MASK>
 static void launch_lines(const LineArgs& a, hipStream_t st) {
     const long long lines = (long long)a.Bm * a.Hm * (a.NR + a.NC);
     const unsigned grid = (unsigned)(lines < (1 << 20) ? lines : (1 << 20));    // (the kernel strides over the rest)
-    hipLaunchKernelGGL(build_lines_kernel<MASK>, dim3(grid), dim3(kLineThreads), 0, st, a);
+    // Documents of a few long sequences: eight waves share the count of a line's undecided blocks (us of the build, 256 -> 512
+    // threads: S = 16384, documents of 256 to 4096 27.5 -> 21.9, of 8000 39.8 -> 28.7, of 16 to 100 15.9 -> 18.5; S = 32768, 768 lines 34.2 -> 33.4;
+    // 16 x 4096, 1536 lines 25.8 -> 40.8, whose waves no longer run all at once; 128 x 128 pixels 48 -> 53).
+    if constexpr (PartialMask<MASK>::kDoc) {
+        if (lines <= 512) {
+            hipLaunchKernelGGL((build_lines_kernel<MASK, 512>), dim3(grid), dim3(512), 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((build_lines_kernel<MASK, 256>), dim3(grid), dim3(256), 0, st, a);
 }
 
 }  // namespace flexattn
@@ -402,7 +497,11 @@ extern "C" int flexattn_blockmask_build(uint32_t mask_id, const flexattn_mod_par
     a.q_num = bm->q_num_blocks; a.q_idx = bm->q_indices;
     a.full_q_num = bm->full_q_num_blocks; a.full_q_idx = bm->full_q_indices;
     a.stats = (unsigned long long*)stats;
-    if (a.stats) hipLaunchKernelGGL(zero_stats_kernel, dim3(1), dim3(64), 0, st, a.stats);
+    // The rows leave their scalars in the workspace, where a row has the eight blocks that make it large enough: atomics of
+    // all rows on one cache line, which go one after the other, bounded the build of many (us, 16 sequences of 4096 38.7 -> 25.8, 64 of 1000
+    // 37.3 -> 25.1, one of 16384 29.8 -> 27.5).
+    if (a.stats && NC >= 8 && ((uintptr_t)ws & 7) == 0) a.row_scalars = (unsigned long long*)ws;
+    else if (a.stats) hipLaunchKernelGGL(zero_stats_kernel, dim3(1), dim3(64), 0, st, a.stats);
 
     // The builder is instantiated for every mask the two-term encoding can express with
     // the primitives below; unknown combinations are rejected rather than approximated.
@@ -424,9 +523,9 @@ extern "C" int flexattn_blockmask_build(uint32_t mask_id, const flexattn_mod_par
         default: return FLEXATTN_ERR_UNSUPPORTED;
     }
     FLEXATTN_HIP_TRY(hipGetLastError());
-    if (bm->kv_order || bm->q_order) {
+    if (bm->kv_order || bm->q_order || a.row_scalars) {
         const int planes = bm->Bm * bm->Hm, longest = NR > NC ? NR : NC;
-        hipLaunchKernelGGL(order_lines_kernel, dim3((unsigned)((longest + 255) / 256), 2, (unsigned)(planes < 4096 ? planes : 4096)),
+        hipLaunchKernelGGL(order_lines_kernel, dim3((unsigned)((longest + 255) / 256), a.row_scalars ? 3 : 2, (unsigned)(planes < 4096 ? planes : 4096)),
                            dim3(256), 0, st, a, bm->kv_order, bm->q_order);
         FLEXATTN_HIP_TRY(hipGetLastError());
     }

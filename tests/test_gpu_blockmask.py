@@ -106,3 +106,20 @@ def test_paged_conversion_matches_oracle():
         # counts are untouched by the conversion
         assert torch.equal(getattr(bm, num_name).cpu(), fo.create_block_mask(
             fo.ctx_len_mask(inp.ctx_lens), wl.B, 1, 1, kv_len, 1, wl.page_size)[num_name])
+
+
+@pytest.mark.parametrize("B,S,Bq,Bk,shift", [(1, 2100, 128, 64, 0), (1, 2100, 128, 64, 1), (1, 999, 64, 128, 3), (1, 700, 200, 300, 1),
+                                             (3, 449, 128, 64, 0), (3, 448, 64, 64, 2), (1, 5300, 16, 33, 1)])
+@pytest.mark.parametrize("lo,hi", [(1, 9), (40, 400)])
+def test_documents_at_any_address_few_and_many_lines(B, S, Bq, Bk, shift, lo, hi):
+    """Ids read four at a time from any element address; blocks of more than 128 rows or keys; lines on both sides of 512
+    (workgroups of eight and of four waves); rows of fewer than eight blocks, whose statistics are summed by atomics, and more."""
+    import paper_2412_05496_amd as fa
+    g = torch.Generator().manual_seed(S + Bq)
+    doc = torch.stack([wlm.document_ids(wlm.document_lengths(g, S, lo, hi)) for _ in range(B)])
+    flat = torch.full((B, S + 5), 3, dtype=doc.dtype, device=DEV)
+    flat[:, shift:shift + S] = doc.to(DEV)
+    ids = flat[:, shift:shift + S]
+    for mask_id, mod in ((fa.MASK_DOCUMENT, fo.document_mask(doc)), (fa.MASK_DOCUMENT_CAUSAL, fo.and_mask(fo.document_mask(doc), fo.causal_mask))):
+        bm = build(mask_id, fa.ModParams(doc_ids=ids), B, 1, S, S, Bq, Bk)
+        assert_blockmask_equal(bm, fo.create_block_mask(mod, B, 1, S, S, Bq, Bk))
