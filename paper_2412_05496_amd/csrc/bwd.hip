@@ -67,8 +67,9 @@ struct Span {
 //   soft-cap   8 heads, S = 1024 33.0 -> 22.9, 2048 55.8 -> 44.0; 32 x 16, S = 512 175 -> 160; 4 heads, S = 8192 207 -> 198; but 32, S = 2048 124 ->
 //              142, 32, S = 8192 1244 -> 1281; window of 1024, S = 5000, 4 x 16 / 4 430 -> 414;
 //   canvases   (whose blocks are mostly hidden parts, which dS in memory leaves out at the granularity of a wave's 32 x 32)
-//              64 x 64 pixels, K = 13, 4 / 16 heads 40.7 -> 32.5, 73.4 -> 72.0; 128 x 128, 2 heads 52.2 -> 52.9, row-major 87 -> 101, 8 heads 129
-//              -> 124, row-major 240 -> 255, 64 heads 990 -> 881; 100 x 100, row-major, K = 9, 2 x 16 / 4 386 -> 370;
+//              64 x 64 pixels, K = 13, 4 heads 40.7 -> 32.5; 128 x 128, 2 heads 49.7 -> 51.0, row-major 87 -> 102, 8 heads 119 -> 115,
+//              row-major 223 -> 240, 64 heads 990 -> 881 (812 since dK/dV leaves hidden steps out); 100 x 100, row-major, K = 9, 2 x 16 / 4 386
+//              -> 370;
 //   D = 128    only small launches: causal, 16 heads, S = 512 32.7 -> 25.0, 8 x 16 84.7 -> 77.7; 2 heads, S = 4096 109 -> 90; 8 heads, S = 2048
 //              75.5 -> 66.8; window of 512, 32 heads, S = 2048 99.4 -> 95.8; 4 heads, S = 8192 290 -> 338; soft-cap, 8 heads, S = 1024 43.8 -> 38.1,
 //              32 / 8 heads 87.5 -> 92.6; 32 x 32 pixels, 8 heads 43.3 -> 35.1, 64 x 64, 4 heads 51.9 -> 54.9.

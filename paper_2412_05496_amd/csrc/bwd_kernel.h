@@ -186,10 +186,10 @@ __device__ __forceinline__ int canvas_step_bits(const flexattn_mod_params& p, in
 // and a relative bias; canvas 684 -> 763) and keep the exchange, as does D = 128, whose two accumulators
 // are 128 registers.
 //
-// kCut, neighborhood masks at D = 128: the walk leaves out the steps that are hidden from all four waves, and a
-// wave the vector work and the outputs of its hidden blocks (128 x 128 pixels, tiles of 8 x 8, K = 13, 64 heads:
-// 1047 -> 907 us; 100 x 90 row-major, K = 9: 802 -> 771).  At D = 64 a workgroup is over too soon to pay for
-// finding them (735 -> 725, 446 -> 481).
+// kCut, neighborhood masks: the walk leaves out the steps that are hidden from all four waves, and a
+// wave the vector work and the outputs of its hidden blocks (D = 128, 128 x 128 pixels, tiles of 8 x 8, K = 13, 64 heads:
+// 1047 -> 907 us; 100 x 90 row-major, K = 9: 802 -> 771; D = 64, 128 x 128, K = 13 548 -> 481, 64 x 64 in Morton order, K = 21, 243 -> 209, 32 x 32,
+// K = 7, 256 heads 112 -> 99, 100 x 100 row-major, K = 9, 32 heads 225 -> 221, 128 x 128 row-major, K = 27, 8 heads 287 -> 259).
 template <int D, uint32_t MASK, uint32_t SCORE>
 constexpr bool dkdv_own_rows() {
     constexpr bool biased_cap = (SCORE & FLEXATTN_SCORE_SOFTCAP) && (SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS));
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     constexpr int TQ = 64;                         // query rows per step
     constexpr int TILE = TQ * D;                   // elements per LDS tile
     constexpr int NKS = D / 16, NDB = D / 32;
-    constexpr bool kCut = D == 128 && PartialMask<MASK>::kCanvas;     // leaves hidden steps and blocks out
+    constexpr bool kCut = PartialMask<MASK>::kCanvas;     // leaves hidden steps and blocks out
     using Loader = WaveTileLoader<D, 4>;
     __shared__ __attribute__((aligned(1024))) bf16 smem[(OWN ? 5 : 4) * TILE];   // 2 x (Q tile, dO tile); OWN: V tile
     __shared__ __attribute__((aligned(1024))) u32x4 s_xchg[OWN ? 1 : 4][2][64];   // [wave][16-row slice][lane]

@@ -117,3 +117,34 @@ def test_blockmask_on_a_large_canvas_sampled_blocks(layout, tile):
         want = 0 if cnt == 0 else (2 if cnt == Bq * Bk else 1)
         got = 1 if j in idx[i, :int(num[i])].tolist() else (2 if j in fidx[i, :int(fnum[i])].tolist() else 0)
         assert got == want, (i, j, got, want)
+
+
+@pytest.mark.parametrize("B", [1, 24])         # few workgroups and many
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("W,H,K,layout,tile", [(40, 24, 7, "row_major", 0), (40, 24, 7, "tiled", 8), (32, 32, 13, "morton", 0)])
+def test_ds_in_memory_leaves_out_hidden_blocks(B, D, W, H, K, layout, tile):
+    """dS of hidden 32 x 32 blocks is neither written nor read: a dQ in V's place always goes through memory; its workspace is
+    full of NaN patterns, and its gradients are those of the recomputing backward."""
+    import paper_2412_05496_amd as fa
+    dev = torch.device("cuda:0")
+    g = torch.Generator().manual_seed(W * D + K)
+    S = W * H
+    Q, Kt, V, dO = (torch.randn(B, 2, S, D, generator=g).to(torch.bfloat16).to(dev) for _ in range(4))
+    params = na_params(fa, W, H, K, layout, tile)
+    bm = fa.alloc_blockmask(1, 1, S, S, 128, 64, device=dev)
+    fa.flexattn_blockmask_build(fa.MASK_NEIGHBORHOOD, params, bm)
+    O, LSE = torch.empty_like(Q), torch.empty(B, 2, S, dtype=torch.float32, device=dev)
+    head = (fa.SCORE_IDENTITY, fa.MASK_NEIGHBORHOOD, params, bm, D ** -0.5)
+    fa.flexattn_forward(Q, Kt, V, *head, O, LSE)
+    want = [torch.empty_like(Q) for _ in range(3)]
+    fa.flexattn_backward(Q, Kt, V, O, dO, LSE, *head, *want)
+    n = hp.nonempty_blocks(bm)
+    ws = torch.full((fa.flexattn_backward_stored_workspace_bytes(Q, Kt, bm, n),), 0xFF, dtype=torch.uint8, device=dev)
+    V_in = V.clone()
+    got = [V_in, torch.empty_like(Q), torch.empty_like(Q)]
+    fa.flexattn_backward_stored(Q, Kt, V_in, O, dO, LSE, *head, *got, n, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+    # the same bf16 dS summed in another order in fp32: one bf16 rounding of each result, 2^-8 of the larger values
+    err = (got[0].float() - want[0].float()).abs()
+    assert torch.isfinite(got[0].float()).all() and err.max() <= 2 ** -7 * want[0].float().abs().max()
