@@ -562,7 +562,7 @@ extern "C" int flexattn_paged_decode_static(const flexattn_decode_dims* d, const
                                             float* LSE, void* stream) {
     int rc = check_decode_dims(d);
     if (rc != FLEXATTN_OK) return rc;
-    // Every partial the combine kernel reads was written by the split kernel of the same call, so
+    // Every partial that counts in the combine kernel was written by the split kernel of the same call, so
     // nothing in the array has to start at zero.
     if (flexattn_paged_decode_workspace_bytes(d) > kStaticScratchBytes) return FLEXATTN_ERR_WORKSPACE;
     void* ws = nullptr;
