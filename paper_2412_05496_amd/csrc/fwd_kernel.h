@@ -345,6 +345,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     float m_run = BOUNDED ? smod.capl2 : -INFINITY, l_run = 0.0f;
     float m_use = 0.0f;     // the maximum the exponentials subtract: m_run, or 0 while the row has seen no key
     float m_thr = -INFINITY; // what a block's largest shifted score must exceed for the maximum to move
+    bool seeded = false;     // (wave-uniform) every row has seen a key
 
     // score_mod, mask_mod (partial blocks only) and softmax of one 32-key block whose first key is
     // kvs: s -> P^T as two bf16 fragments.  The mask is a separate, rarely taken pass (kept a real
@@ -364,6 +365,22 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 #pragma unroll
             for (int i = 0; i < 4; ++i) s[4 * rg + i] = put(Mask::keep(bits, 4 * rg + i, mask.pixels_match(tags[i], q_tag)), s[4 * rg + i]);
         }
+    };
+    // The probabilities of a block as two bf16 fragments, and this lane's part of the row sum: over the bf16-rounded
+    // probabilities, the values P V is computed from, two at a time (dot product of a packed pair with (1, 1), fp32 accumulation).
+    auto weigh = [&](const f32x16& s, bf16x8 (&pf)[2], auto&& prob) __attribute__((always_inline)) {
+        float psum[2] = {0.0f, 0.0f};
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            u32x4 pk;
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                pk[jj] = pack_bf16(prob(s[8 * c + 2 * jj]), prob(s[8 * c + 2 * jj + 1]));
+                psum[jj & 1] = pair_sum_bf16(pk[jj], psum[jj & 1]);
+            }
+            pf[c] = __builtin_bit_cast(bf16x8, pk);
+        }
+        return psum[0] + psum[1];
     };
     auto softmax = [&](f32x16& s, int kvs, bool tile_partial, int buf, int kvb, bf16x8 (&pf)[2]) {
         const bool partial = tile_partial && !mask.full(q_wave_min, q_wave_min + 31, kvs, kvs + 31);   // (wave-uniform)
@@ -397,14 +414,16 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
                 else asm volatile("" ::: "memory");
                 masked(s, kvs, buf, kvb, keep_or_zero);
             }
+            l_run += weigh(s, pf, [](float x) __attribute__((always_inline)) { return x; });
         } else {
             // Online softmax.  The running maximum only has to keep exp2(s - m) in range, so it follows
-            // the scores lazily: a row keeps its maximum until a block exceeds it by more than kLazyMax
-            // (P then reaches 2^kLazyMax at most, the row sum as much more; O / l and LSE = m + log2 l
-            // come out the same).  The score_mod therefore subtracts the CURRENT maximum on its way (folded
-            // into its multiply-adds), and only when some row of the wave moves its maximum -- rare after a
-            // row's first blocks -- are the scores shifted again and O^T and l rescaled.
-            constexpr float kLazyMax = 8.0f;
+            // the scores lazily: the score_mod subtracts the CURRENT maximum on its way (folded into its
+            // multiply-adds), and the maximum moves only when the block's probabilities under it add up to more
+            // than kLazySum in some lane, or while some row has seen no key (O / l and LSE = m + log2 l come out
+            // the same).  The sum is there anyway, so that a block whose maximum stays costs no maximum at all: 12 of
+            // 66 vector instructions at D = 64 (us, a maximum per block -> this: no mask, S = 777, 128 heads, D = 64 35.8 -> 34.3; chunks
+            // of 2048 on 4096 to 14336 cached keys, 4 sequences of 32 heads, D = 128 1382 -> 1353).
+            constexpr float kLazyMax = 8.0f, kLazySum = 4096.0f;    // 16 of 2^kLazyMax: above the sum, the largest is above the maximum
             const float shift = -m_use;
             if (rel_is_uni) {
 #pragma unroll
@@ -418,42 +437,37 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
                 else asm volatile("" ::: "memory");
                 masked(s, kvs, buf, kvb, keep_or_neg_inf);
             }
-            float mx = s[0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-            mx = max_halves(mx);
-            if (__any(mx > m_thr)) {                 // some row of the wave moves its maximum (by mx)
-                const float up = mx > m_thr ? mx : 0.0f;
-                // (a row's first keys: nothing to rescale yet, and 2^-mx could overflow)
-                const float alpha = m_thr == -INFINITY ? 0.0f : fast_exp2(-up);
-                m_use += up;                         // (0 before the row's first key)
-                m_run = mx > m_thr ? m_use : m_run;
-                m_thr = mx > m_thr ? kLazyMax : m_thr;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[r] -= up;
-                l_run *= alpha;
-#pragma unroll
-                for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+            float sum = 0.0f;
+            bool moves = true;
+            if (seeded) {
+                sum = weigh(s, pf, [](float x) __attribute__((always_inline)) { return fast_exp2(x); });
+                moves = __any(sum > kLazySum);
             }
+            if (moves) {
+                float mx = s[0];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = fast_exp2(s[r]);
-        }
-        // The row sum adds up the bf16-rounded probabilities, the values P V is computed from, two at
-        // a time (dot product of a packed pair with (1, 1), fp32 accumulation).
-        float psum[2] = {0.0f, 0.0f};
+                for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+                mx = max_halves(mx);
+                if (__any(mx > m_thr)) {                 // some row of the wave moves its maximum (by mx)
+                    const float up = mx > m_thr ? mx : 0.0f;
+                    // (a row's first keys: nothing to rescale yet, and 2^-mx could overflow)
+                    const float alpha = m_thr == -INFINITY ? 0.0f : fast_exp2(-up);
+                    m_use += up;                         // (0 before the row's first key)
+                    m_run = mx > m_thr ? m_use : m_run;
+                    m_thr = mx > m_thr ? kLazyMax : m_thr;
+                    seeded = !__any(m_thr == -INFINITY);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            u32x4 pk;
+                    for (int r = 0; r < 16; ++r) s[r] -= up;
+                    l_run *= alpha;
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                pk[jj] = pack_bf16(s[8 * c + 2 * jj], s[8 * c + 2 * jj + 1]);
-                psum[jj & 1] = pair_sum_bf16(pk[jj], psum[jj & 1]);
+                    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+                }
+                sum = weigh(s, pf, [](float x) __attribute__((always_inline)) { return fast_exp2(x); });
             }
-            pf[c] = __builtin_bit_cast(bf16x8, pk);
+            l_run += sum;
         }
-        l_run += psum[0] + psum[1];
     };
 
     // O^T += V^T P^T for the 32-key block kvb (compile-time) of the V tile in buffer BUF

@@ -1,0 +1,62 @@
+"""The forward moves a row's running maximum only when the probabilities of a 32-key block under the old one add up to
+more than a bound, and walks ALiBi rows from the end with the larger biases.  Where that can go wrong: sums at the bound,
+jumps that overflow 2^x, first keys far below zero, rows whose first blocks are hidden, biases of either sign and zero; on
+every form of the tile loop (few workgroups: the split forms; 300 copies: the others).  O and LSE at the tolerances of
+tests/helpers.py."""
+import math
+
+import pytest
+import torch
+
+from oracle import flex_oracle as fo
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+S = 320
+# log2 of the un-normalised weight of each 32-key block
+STEPS = {"bound": [0, 8, 8.0625, 16, 16.125, 7, 40, 3, 48, 0], "overflow": [-3, 0, 5, 140, 2, 700, 701, -90, 1, 0],
+         "low": [-400, -400, -391, -380, -140, -3, 0, 11, 12, 13], "falling": [60, 9, 3, 0, -1, -9, -60, -300, -2, 1]}
+
+
+def check(Q, K, V, score_id, score, mask_id, mask, params, scale, Bq, Bk):
+    import paper_2412_05496_amd as fa
+    O_ref, LSE_ref = fo.flex_attention(Q, K, V, score, mask, scale)
+    bm = fa.alloc_blockmask(1, 1, S, S, Bq, Bk, device=DEV)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    for copies in (1, 300):
+        q, k, v = (t.to(torch.bfloat16).to(DEV).expand(copies, -1, -1, -1) for t in (Q, K, V))
+        O = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
+        LSE = torch.full(q.shape[:3], float("nan"), device=DEV)
+        fa.flexattn_forward(q, k, v, score_id, mask_id, params, bm, scale, O, LSE)
+        torch.cuda.synchronize()
+        assert torch.equal(O, O[:1].expand_as(O)) and torch.equal(LSE, LSE[:1].expand_as(LSE))
+        # (LSE in fp32 is exact to 2^-24 of its size: 5e-5 at 700)
+        hp.check_output(O[:1], LSE[:1], O_ref, LSE_ref)
+
+
+@pytest.mark.parametrize("steps", sorted(STEPS))
+@pytest.mark.parametrize("mask_name,D,Bq,Bk", [("none", 64, 128, 64), ("causal", 64, 64, 64), ("causal", 128, 128, 128),
+                                               ("none", 128, 64, 64), ("swa_causal", 64, 128, 64), ("swa_causal", 128, 128, 64)])
+def test_maxima_that_move(steps, mask_name, D, Bq, Bk):
+    import paper_2412_05496_amd as fa
+    gen = torch.Generator().manual_seed(97)
+    Q, K, V = torch.zeros(1, 2, S, D), torch.zeros(1, 2, S, D), torch.randn(1, 2, S, D, generator=gen).to(torch.bfloat16).float()
+    Q[..., 0] = 1.0
+    Q[:, 1, ::3, 0] = -0.5                  # (head 1: rows of one wave whose maxima move at different blocks)
+    K[..., 0] = torch.tensor(STEPS[steps]).repeat_interleave(32).to(torch.bfloat16).float()
+    mask_id, mask, params = {"none": (fa.MASK_NONE, fo.no_mask, fa.ModParams()), "causal": (fa.MASK_CAUSAL, fo.causal_mask, fa.ModParams()),
+                             "swa_causal": (fa.MASK_SWA_CAUSAL, fo.and_mask(fo.sliding_window_mask(70), fo.causal_mask), fa.ModParams(window=70))}[mask_name]
+    print(f"[case] {steps} {mask_name} D={D} Bq={Bq} Bk={Bk}", flush=True)
+    check(Q, K, V, fa.SCORE_IDENTITY, fo.Identity(), mask_id, mask, params, math.log(2.0), Bq, Bk)
+
+
+@pytest.mark.parametrize("biases", [(-0.7, -0.001), (0.6, 0.0), (-3.0, 2.0)])
+@pytest.mark.parametrize("D,Bq,Bk", [(64, 128, 64), (64, 64, 128), (128, 128, 64), (128, 64, 128)])
+def test_alibi_of_either_sign(biases, D, Bq, Bk):
+    import paper_2412_05496_amd as fa
+    gen = torch.Generator().manual_seed(98 + D)
+    Q, K, V = (torch.randn(1, 2, S, D, generator=gen).to(torch.bfloat16).float() for _ in range(3))
+    bias = torch.tensor(biases, dtype=torch.float32)
+    print(f"[case] ALiBi {biases} D={D} Bq={Bq} Bk={Bk}", flush=True)
+    check(Q, K, V, fa.SCORE_ALIBI, fo.Alibi(bias.double()), fa.MASK_CAUSAL, fo.causal_mask, fa.ModParams(alibi_bias=bias.to(DEV)), D ** -0.5, Bq, Bk)
