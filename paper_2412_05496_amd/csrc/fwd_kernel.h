@@ -295,9 +295,15 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     };
     const float inv_neg2c = smod.capl2 > 0.0f ? -0.5f / smod.capl2 : 0.0f;   // 1 / (-2 cap log2 e)
 
+    // ALiBi: from the end where the largest scores are (the bias falls with the distance: from the diagonal), so that the first
+    // block of a row sets a maximum that stays; the other way round a steep head moves it in every block.
+    // (us, forwards -> this: a step on packed documents, S = 16384, 16 heads, D = 64 658 -> 612; chunks of 1811 on about 2000 cached keys,
+    // four sequences of 8 heads, D = 128, 146 -> 125; of 902 on about 6000, two of 8, D = 64, 72 -> 64)
+    static_assert(!(Mask::kCanvas && Score::kAlibi), "s_hidden goes by the walk's forward order");
+    const bool backwards = Score::kAlibi && smod.k_bias < 0.0f;
     // first key and PARTIAL flag of tiles t, t+1, t+2 (the walk is always two tiles ahead)
     TileWalk<PAGED> walk(a.full_idx + line * a.NC, a.kv_idx + line * a.NC, n_full, n_part, a.sub, a.Bk,
-                         PAGED ? a.phys_full_idx + line * a.NC : nullptr, PAGED ? a.phys_kv_idx + line * a.NC : nullptr);
+                         PAGED ? a.phys_full_idx + line * a.NC : nullptr, PAGED ? a.phys_kv_idx + line * a.NC : nullptr, backwards);
     int kv_t = 0, kv_t1 = 0, kv_t2 = 0;
     bool part_t = false, part_t1 = false, part_t2 = false;
     int pg_t = 0, pg_t1 = 0, pg_t2 = 0, pr_t = 0, pr_t1 = 0, pr_t2 = 0;   // PAGED: page, row in page
@@ -503,8 +509,9 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         const L k_load(a.k_ss, 0, lane), v_load(a.v_ss, 0, lane);
         const uint32_t k_lds = smem_bytes + (uint32_t)w * 2 * UT, v_lds = k_lds + UT;
         const int TU = 2 * T, per_block = 2 * a.sub, shift = a.sub == 1 ? 1 : 2, n_blocks = n_full + n_part;
+        auto place = [&](int p) __attribute__((always_inline)) { return backwards ? n_blocks - 1 - p : p; };
         auto at = [&](const int32_t* full, const int32_t* part, int u) __attribute__((always_inline)) {
-            const int p = min(u >> shift, n_blocks - 1);
+            const int p = place(min(u >> shift, n_blocks - 1));
             return ldc(p < n_full ? full + line * a.NC + p : part + line * a.NC + (p - n_full));
         };
         int u_next = w, blk_next = at(a.full_idx, a.kv_idx, w), pg_next = PAGED ? at(a.phys_full_idx, a.phys_kv_idx, w) : 0;
@@ -512,11 +519,11 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         bool partial = false;
         auto advance = [&]() __attribute__((always_inline)) {
             while (u_next < TU) {
-                const int u = u_next, s0 = (u & (per_block - 1)) * 32;
+                const int u = u_next, in_block = u & (per_block - 1), s0 = (backwards ? per_block - 1 - in_block : in_block) * 32;
                 kv = blk_next * a.Bk + s0;
                 page = pg_next;
                 prow = s0;
-                partial = (u >> shift) >= n_full;
+                partial = place(u >> shift) >= n_full;
                 u_next += NW;
                 blk_next = at(a.full_idx, a.kv_idx, u_next);
                 if constexpr (PAGED) pg_next = at(a.phys_full_idx, a.phys_kv_idx, u_next);
@@ -614,7 +621,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         using UnitLoader = WaveTileLoader<D, NW, 32>;
         const UnitLoader ku_loader(a.k_ss, w, lane), vu_loader(a.v_ss, w, lane);
         TileWalk<PAGED, 32> uwalk(a.full_idx + line * a.NC, a.kv_idx + line * a.NC, n_full, n_part, 2 * a.sub, a.Bk,
-                                  PAGED ? a.phys_full_idx + line * a.NC : nullptr, PAGED ? a.phys_kv_idx + line * a.NC : nullptr);
+                                  PAGED ? a.phys_full_idx + line * a.NC : nullptr, PAGED ? a.phys_kv_idx + line * a.NC : nullptr, backwards);
         const int TU = 2 * T;
         int kv_of[3];
         bool part_of[3];

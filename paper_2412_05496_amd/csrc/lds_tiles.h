@@ -226,6 +226,7 @@ __device__ __forceinline__ void read_ahead(F&& frag, U&& use) {
 // FULL blocks first, then PARTIAL ones, each block cut into `sub` tiles.  Written without
 // branches, and the index of the following block is fetched (scalar cache) on every call and only
 // consumed by the call after it, so that the fetch has a tile's worth of work to hide behind.
+// backwards: from the last tile of the last block to the first.
 template <bool PAGED = false, int STEP = 64>
 struct TileWalk {
     const int32_t* full_idx;
@@ -235,18 +236,22 @@ struct TileWalk {
     int n_full, n_blocks, sub, block_len;
     int pos, s, blk, fetched, pblk, pfetched;
     bool entered;                               // the previous call moved on to the next block
+    bool backwards;
+    __device__ __forceinline__ int place(int p) const { return backwards ? n_blocks - 1 - p : p; }   // in the merged list
     __device__ __forceinline__ int block_at(int p) const {
-        return ldc(p < n_full ? full_idx + p : part_idx + (p - n_full));
+        const int i = place(p);
+        return ldc(i < n_full ? full_idx + i : part_idx + (i - n_full));
     }
     __device__ __forceinline__ int phys_at(int p) const {
-        return ldc(p < n_full ? full_phys + p : part_phys + (p - n_full));
+        const int i = place(p);
+        return ldc(i < n_full ? full_phys + i : part_phys + (i - n_full));
     }
     __device__ __forceinline__ TileWalk(const int32_t* full_idx_, const int32_t* part_idx_, int n_full_, int n_part,
                                         int sub_, int block_len_, const int32_t* full_phys_ = nullptr,
-                                        const int32_t* part_phys_ = nullptr)
+                                        const int32_t* part_phys_ = nullptr, bool backwards_ = false)
         : full_idx(full_idx_), part_idx(part_idx_), full_phys(full_phys_), part_phys(part_phys_), n_full(n_full_),
           n_blocks(n_full_ + n_part), sub(sub_), block_len(block_len_), pos(0), s(0), fetched(0), pblk(0),
-          pfetched(0), entered(false) {
+          pfetched(0), entered(false), backwards(backwards_) {
         blk = n_blocks > 0 ? block_at(0) : 0;
         if constexpr (PAGED) pblk = n_blocks > 0 ? phys_at(0) : 0;
     }
@@ -255,14 +260,15 @@ struct TileWalk {
     // in the pool (the page is the physical block); otherwise they are not touched.
     __device__ __forceinline__ int next(bool& partial, int& page, int& row_in_page) {
         blk = entered ? fetched : blk;
-        const int x0 = blk * block_len + s * STEP;
+        const int first = (backwards ? sub - 1 - s : s) * STEP;
+        const int x0 = blk * block_len + first;
         if constexpr (PAGED) {
             pblk = entered ? pfetched : pblk;
             page = pblk;
-            row_in_page = s * STEP;
+            row_in_page = first;
             pfetched = phys_at(min(pos + 1, n_blocks - 1));
         }
-        partial = pos >= n_full;
+        partial = place(pos) >= n_full;
         fetched = block_at(min(pos + 1, n_blocks - 1));
         entered = s + 1 == sub;
         s = entered ? 0 : s + 1;
