@@ -181,7 +181,7 @@ __device__ __forceinline__ int canvas_step_bits(const flexattn_mod_params& p, in
 // 1024, S = 5000, Hq 16, Hkv 2, B = 4: 222 -> 210; packed documents with ALiBi, S = 16384, 16 heads: 262 -> 252;
 // soft-cap, S = 4096, 64 heads: 532 -> 502; relative bias, window 1024, S = 8192: 598 -> 548.
 //
-// Which form: own rows at D = 64, but for launches that are too uneven for it (own_rows_pay).  A soft-cap on top of a bias, and the pixel compares of a canvas, leave too
+// Which form: own rows at D = 64, but for launches that are too uneven for it (own_rows_pay).  A soft-cap on top of a bias, and the rectangles of a canvas, leave too
 // few registers at three waves per SIMD (6 to 24 spills: 431 -> 447 us with ALiBi, 350 -> 370 with documents
 // and a relative bias; canvas 684 -> 763) and keep the exchange, as does D = 128, whose two accumulators
 // are 128 registers.
@@ -214,6 +214,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];   // relative-bias row of the current head
     using Mask = PartialMask<MASK>;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? TQ : 4];   // [slot] tags of a PARTIAL step's queries
+    __shared__ u32x2 s_corners[Mask::kCanvas ? 64 : 1];               // key_corners() of the keys
 
     // workgroup -> (b, hkv, 64-key tile).  The columns of
     // blocks are taken in the BlockMask's work order (longest first; that of the group's first query
@@ -295,7 +296,9 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
         k_tag = (uint32_t)docs[min(kv_lane, a.kv_len - 1)];
         doc_rsrc = make_rsrc(docs, (uint32_t)(q_off + a.q_len) * 4u);
     }
-    if constexpr (Mask::kCanvas) k_tag = mask.key_pixel(min(kv_lane, a.kv_len - 1));
+    if constexpr (Mask::kCanvas) {
+        if (tid < 64) s_corners[tid] = mask.key_corners(kv0 + tid);     // (visible after the barriers before the first step)
+    }
     // Tags of the 64 queries of the step whose first row is q0, into s_tag[slot] (visible after the
     // barrier that makes the step's tiles visible)
     auto make_tags = [&](int slot, int q0) __attribute__((always_inline)) {
@@ -303,7 +306,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
             if (w == 0) dma_dword(doc_rsrc, lds_addr(&s_tag[slot][0]), lane * 4, (q_off + q0) * 4);
         }
         if constexpr (Mask::kCanvas) {
-            if (w == 2 * slot) s_tag[slot][lane] = mask.query_pixel(q_off + min(q0 + lane, a.q_len - 1));
+            if (w == 2 * slot) s_tag[slot][lane] = mask.query_block_tag(q_off + min(q0 + lane, a.q_len - 1));
         }
     };
     const uint32_t ds_lane = (uint32_t)(w * 1024 + lane * 8);     // this lane's place inside a step of dS in memory (bf16 elements)
@@ -386,7 +389,6 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
             bool part_of[2];                        // and whether its block is PARTIAL
             // (CUT) whether the mask hides this wave's 32 x 32 block, and that of the other wave of its keys
             bool hid_of[2] = {false, false}, hid_other_of[2] = {false, false};
-            int u_of[2] = {0, 0};                   // (CUT) the step's position in the column's walk
 
             int ld_q0 = 0;                          // first row of the step being loaded
             constexpr int kLoads = 2 * Loader::NI + 1;      // load instructions per wave and step
@@ -399,7 +401,6 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 if constexpr (CUT) {
                     hid_of[SLOT] = (e >> (1 + w)) & 1;
                     hid_other_of[SLOT] = (e >> (1 + (w ^ 2))) & 1;
-                    u_of[SLOT] = s_pos[ld_v];
                 }
                 e_next = s_steps[++ld_v];
             };
@@ -467,6 +468,11 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 bool hid = false;
                 if constexpr (CUT) hid = hid_of[SLOT];
                 else if constexpr (OWN) hid = part_of[SLOT] && mask.hidden(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb, kv0 + 32 * kb + 31);
+                // (a canvas' here, while the score accumulators do not take registers yet)
+                typename Mask::Bits bits = {};
+                if constexpr (Mask::kCanvas) {
+                    if (partial && !hid) bits = mask.match_queries(&s_tag[SLOT][32 * x], s_corners[32 * kb + l32], half);
+                }
                 // scores
                 f32x4 nd[4], rcv4[4];
                 read_rows(SLOT, 1, nd);
@@ -499,8 +505,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 float rel_uni;
                 const bool rel_is_uni = smod.rel_uniform(q_off + q_first - (kv0 + 32 * kb + 31),
                                                          q_off + q_first + 31 - (kv0 + 32 * kb), rel_uni);
-                typename Mask::Bits bits = {};
-                if (partial) {
+                if (partial && !Mask::kCanvas) {
                     bits = mask.key_bits(kv_lane, q_off + q_first + 4 * half);
                     if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[SLOT][32 * x], k_tag, l32, half, false);
                 }
@@ -533,11 +538,8 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                             asm volatile("" ::: "memory");   // keep this a (scalar, rarely taken) branch
                             // (a masked P makes dS vanish with it.  Rows past q_len hold zeros in Q and dO: whatever
                             // the mask says there adds nothing)
-                            u32x4 tags = {};
-                            if constexpr (Mask::kCanvas) tags = *(const u32x4*)&s_tag[SLOT][32 * x + 8 * c4 + 4 * half];
 #pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i, mask.pixels_match(k_tag, tags[i])), pe[i]);
+                            for (int i = 0; i < 4; ++i) pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i), pe[i]);
                         }
 #pragma unroll
                         for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];
@@ -551,7 +553,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 }
                 // (wave-uniform; the blocks a canvas hides are not read back, see CANVAS in bwd_stored.h)
                 const bool stored = a.ds_store && !(CUT && hid);
-                if (stored) store_ds(u_of[SLOT], dsk[0], dsk[1]);
+                if (stored) store_ds(CUT ? s_pos[ld_v - 2] : 0, dsk[0], dsk[1]);
                 --u_step;
                 if constexpr (OWN) {
                     // outputs: dV^T += dO^T P and dK^T += Q^T dS over this wave's own 32 rows
@@ -587,8 +589,8 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 constexpr uint32_t slot_off = SLOT * 2 * (TILE * 2);
                 constexpr int NMH = 2 * NDB, PF = 4;          // MFMAs per half: [slice c][block db]
                 u32x4 theirs[2];
-                auto out_half = [&](const TrReader<D>& reader, const u32x4 (&bop)[2]) {
-                    auto frag = [&](int m) { return reader.read(slot_off, 16 * (m / NDB), m % NDB); };
+                auto out_half = [&](const TrReader<D>& reader, uint32_t further, const u32x4 (&bop)[2]) {
+                    auto frag = [&](int m) { return reader.read(slot_off + further, 16 * (m / NDB), m % NDB); };
                     bf16x8 fr[NMH];
 #pragma unroll
                     for (int m = 0; m < PF; ++m) fr[m] = frag(m);
@@ -599,13 +601,19 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 };
-                if (!hid) out_half(tr_own, own);
+                if (!hid) out_half(tr_own, 0u, own);
                 __syncthreads();
                 if (!hid_other_of[SLOT]) {
 #pragma unroll
                     for (int c = 0; c < 2; ++c)
                         theirs[c] = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)(xchg_theirs + c * 1024);
-                    out_half(tr_other, theirs);
+                    // (CUT: tr_other's addresses are made here, it has no registers to keep them)
+                    uint32_t further = 0;
+                    if constexpr (CUT) {
+                        further = (uint32_t)((1 - 2 * x) * 32 * D * 2);
+                        asm volatile("" : "+s"(further));
+                    }
+                    out_half(CUT ? tr_own : tr_other, further, theirs);
                 }
                 end_step(stored);
             };
@@ -925,14 +933,9 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
                 asm volatile("" ::: "memory");   // keep this a branch
                 typename Mask::Bits bits = mask.row_bits(q_pos, kvs_blk + 4 * half);
                 if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[BUF][kvb * 32], q_tag, l32, half, scattered);
-                u32x4 tags[4] = {};
-                if constexpr (Mask::kCanvas) {
+                if constexpr (Mask::kCanvas) mask.match_keys(bits, &s_tag[BUF][kvb * 32], q_tag, half);
 #pragma unroll
-                    for (int rg = 0; rg < 4; ++rg) tags[rg] = *(const u32x4*)&s_tag[BUF][kvb * 32 + 8 * rg + 4 * half];
-                }
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    dpacc[r] = keep_or_zero(Mask::keep(bits, r, mask.pixels_match(tags[r >> 2][r & 3], q_tag)), dpacc[r]);
+                for (int r = 0; r < 16; ++r) dpacc[r] = keep_or_zero(Mask::keep(bits, r), dpacc[r]);
             }
             if constexpr (CAPTURED) {
                 const int kvs = kv0_cur + kvb * 32;

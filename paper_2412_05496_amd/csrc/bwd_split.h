@@ -216,14 +216,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(
             asm volatile("" ::: "memory");          // keep this a branch
             typename Mask::Bits bits = mask.row_bits(q_pos, kv_now + 4 * half);
             if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[w][0], q_tag, l32, half, scattered);
+            if constexpr (Mask::kCanvas) mask.match_keys(bits, &s_tag[w][0], q_tag, half);
 #pragma unroll
-            for (int rg = 0; rg < 4; ++rg) {
-                u32x4 tags = {};
-                if constexpr (Mask::kCanvas) tags = *(const u32x4*)&s_tag[w][8 * rg + 4 * half];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    dpacc[4 * rg + i] = keep_or_zero(Mask::keep(bits, 4 * rg + i, mask.pixels_match(tags[i], q_tag)), dpacc[4 * rg + i]);
-            }
+            for (int r = 0; r < 16; ++r) dpacc[r] = keep_or_zero(Mask::keep(bits, r), dpacc[r]);
         }
         if (more && partial) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (the tags have been read)
@@ -304,7 +299,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
     const int32_t* docs = Mask::kDoc ? a.p.doc_ids + (int64_t)b * a.p.doc_stride_b : nullptr;
     uint32_t k_tag = 0;
     if constexpr (Mask::kDoc) k_tag = (uint32_t)docs[kv_ld];
-    if constexpr (Mask::kCanvas) k_tag = mask.key_pixel(kv_ld);
+    u32x2 corners = {};
+    if constexpr (Mask::kCanvas) corners = mask.key_corners(kv_lane);
     const L q_load(a.q_ss, 0, lane), do_load(a.do_ss, 0, lane);
     const uint32_t base = lds_addr(smem) + (uint32_t)w * 4 * UT;
     const RowReader<D> rows(l32, half, base);
@@ -378,7 +374,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
             constexpr int SLOT = decltype(slot_tag)::value;
             if (partial) {
                 if constexpr (Mask::kDoc) dma_global_dword(lds_addr(&s_tag[w][SLOT][0]), docs, (q_off + min(q0 + lane, a.q_len - 1)) * 4);
-                if constexpr (Mask::kCanvas) s_tag[w][SLOT][lane] = mask.query_pixel(q_off + min(q0 + lane, a.q_len - 1));
+                if constexpr (Mask::kCanvas) s_tag[w][SLOT][lane] = mask.query_block_tag(q_off + min(q0 + lane, a.q_len - 1));
             }
             q_load.start(q_rsrc, base + SLOT * 2 * UT, q0 * (int)a.q_ss * 2);
             do_load.start(do_rsrc, base + SLOT * 2 * UT + UT, q0 * (int)a.do_ss * 2);
@@ -420,8 +416,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
             const bool masked = partial_now && !mask.full(q_now, q_now + 31, kv0, kv0 + 31);
             typename Mask::Bits bits = {};
             if (masked) {
-                bits = mask.key_bits(kv_lane, q_now + 4 * half);
-                if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[w][SLOT][0], k_tag, l32, half, false);
+                if constexpr (Mask::kCanvas) {
+                    bits = mask.match_queries(&s_tag[w][SLOT][0], corners, half);
+                } else {
+                    bits = mask.key_bits(kv_lane, q_now + 4 * half);
+                    if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[w][SLOT][0], k_tag, l32, half, false);
+                }
             }
             u32x4 pk[2], dsk[2];
 #pragma unroll
@@ -443,10 +443,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
                 else smod.template p_with_grad4<false>(sv, dqk, rcv, gr, pe);
                 if (masked) {
                     asm volatile("" ::: "memory");   // keep this a branch
-                    u32x4 tags = {};
-                    if constexpr (Mask::kCanvas) tags = *(const u32x4*)&s_tag[w][SLOT][8 * c4 + 4 * half];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i, mask.pixels_match(k_tag, tags[i])), pe[i]);
+                    for (int i = 0; i < 4; ++i) pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i), pe[i]);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];

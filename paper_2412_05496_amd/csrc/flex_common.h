@@ -264,12 +264,16 @@ __device__ __forceinline__ int q_offset_of(const flexattn_mod_params& p, int b) 
 // block as a bit mask (about ten instructions) and costs an element one bit-field extract and one
 // select by bits, whatever the composition.  What is looked up per token -- the document id, the pixel of
 // the canvas -- is a 32-bit tag, the other side's in an LDS table of the tile.  Equal document ids become
-// bits as well, by one ballot per distinct id of the 32 tokens (one or two in packed documents); pixels are
-// compared per element, the tags read four at a time.
+// bits as well, by one ballot per distinct id of the 32 tokens (one or two in packed documents).  The pixels that
+// match a lane's are a rectangle, of which 32 consecutive tokens hold a piece that is worked out line by line
+// (tokens_inside; the tags of the block's first token say where it lies).
 // (Evaluating the mask element by element instead -- the canvas decode of every key, a lane exchange or a
 // table read per document id -- made PARTIAL blocks several times as expensive as FULL ones: neighborhood
 // attention on 128 x 128 pixels, K = 13, D = 64, B = 4, H = 16: forward 0.98 ms, dK/dV 1.60 ms before, 0.42
-// and 0.67 since; the forward 0.34 where it also leaves out the blocks CanvasBlocks finds hidden.)
+// and 0.67 since; the forward 0.34 where it also leaves out the blocks CanvasBlocks finds hidden.  Pixels as rectangles instead
+// of six instructions a score, B = 4, H = 16, us forward / backward: 128 x 128, K = 13, tiles of 8 x 8 287 -> 272 / 818 -> 814, row-major 546 ->
+// 483 / 1687 -> 1631; 64 x 64, K = 21, Morton order 135 -> 118 / 357 -> 348; 15 x 40, K = 7, row-major 29.1 -> 29.0 / 83.6 -> 84.7; but tiles of 4 x 4,
+// 64 x 64, K = 9 54.3 -> 53.9 / 179 -> 190.)
 // ---------------------------------------------------------------------------------------
 
 // Position of element r of a lane's 16 (without the 4 * half that goes into the base).
@@ -302,6 +306,10 @@ struct PartialMask {
     // guard bits set iff x >= x0 and y >= y0, and span + 2 guard - a iff x <= x0 + span and y <= y0 + span.
     uint32_t guard, far;
     int y_shift;
+    // How 32 consecutive tokens lie on the canvas: each line of it a run of its own (kLines, row-major), lines of 2^line_log2
+    // pixels below each other (kRows, tiles of 4 x 4 and more), 8 x 4 in Z order (kZ); or as their tags say (kTagged32).
+    enum Way { kTagged32, kLines, kRows, kZ };
+    int way, query_way, line_log2;      // of keys (whose blocks start at a multiple of 32); of queries, which offsets may move
     std::conditional_t<kCanvas, CanvasOrder, NoCanvas> canvas;
     int na_r, na_w, na_h;
 
@@ -311,7 +319,8 @@ struct PartialMask {
         ctx = (PRIMS & FLEXATTN_M_CTX_LEN) ? ldc(p.ctx_lens + b) : 0;
         kv_last = kv_len - 1;
         guard = far = 0;
-        y_shift = na_r = na_w = na_h = 0;
+        y_shift = na_r = na_w = na_h = line_log2 = 0;
+        way = query_way = kTagged32;
         if constexpr (kCanvas) {
             na_w = p.na_width;
             na_h = p.na_height;
@@ -320,6 +329,11 @@ struct PartialMask {
             y_shift = xb + 1;
             guard = (1u << xb) | (1u << (y_shift + yb));
             far = (uint32_t)(2 * na_r) * (1u | (1u << y_shift)) + 2u * guard;
+            // (tiles of 2 x 2 cut 32 tokens into too many pieces: a compare a token is cheaper)
+            line_log2 = min(canvas.tile_log2, 5);
+            way = p.na_layout == FLEXATTN_NA_MORTON ? (na_w >= 8 ? kZ : kTagged32)
+                  : p.na_layout == FLEXATTN_NA_TILED && line_log2 > 0 ? (line_log2 >= 2 ? kRows : kTagged32) : kLines;
+            query_way = p.q_offsets ? kTagged32 : way;
         }
     }
     // Tags of a key and of a query (indices as the mods see them, in range).
@@ -339,6 +353,8 @@ struct PartialMask {
         window_corner(q, x, y);
         return ((uint32_t)x | ((uint32_t)y << y_shift)) - guard;
     }
+    // what the table of a step's 32-query blocks holds (match_queries)
+    __device__ __forceinline__ uint32_t query_block_tag(int q) const { return query_way == kTagged32 ? query_pixel(q) : key_pixel(q); }
     __device__ __forceinline__ bool pixels_match(uint32_t key_tag, uint32_t query_tag) const {
         const uint32_t a = key_tag - query_tag;
         return (a & (far - a) & guard) == guard;
@@ -422,13 +438,98 @@ struct PartialMask {
         }
         bits.plain |= bits.tagged & same;
     }
-    // All-ones if element r is kept, else 0; `match`: its pixels match (canvas masks only).
-    __device__ __forceinline__ static uint32_t keep(const Bits& bits, int r, bool match) {
-        uint32_t m = 0;
-        if constexpr (!kCanvas || (T0 & kTagged) == 0 || (T1 != 0 && (T1 & kTagged) == 0)) m = bit_mask(bits.plain, elem_pos(r));
-        if constexpr (kCanvas) m |= match ? bit_mask(bits.tagged, elem_pos(r)) : 0u;
-        return m;
+    // bits lo .. end - 1 of 32
+    __device__ __forceinline__ static uint32_t span(int lo, int end) {
+        const int l = min(max(lo, 0), 32), e = min(max(end, 0), 32);
+        return (uint32_t)((1ull << e) - 1ull) & ~(uint32_t)((1ull << l) - 1ull);
     }
+    // Which of 32 consecutive tokens, whose pixels are in `tags` (LDS; of the first, and with tiles of 4 x 4 of the 17th, is
+    // asked), lie inside a lane's rectangle (corners included).
+    __device__ __forceinline__ uint32_t tokens_inside(int the_way, const uint32_t* tags, int x0, int y0, int x1, int y1) const {
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)tags[0]), xm = (1u << (y_shift - 1)) - 1u;
+        const int fx = (int)(first & xm), fy = (int)(first >> y_shift);
+        if (the_way == kLines) {
+            uint32_t bits = 0;
+            if (na_w < 32) {                // several lines: the line's bits once, moved to each
+                const uint32_t line = span(x0, x1 + 1), tall = (uint32_t)(y1 - y0);
+                for (int y = fy, at = 32 - fx; at < 64; ++y, at += na_w)
+                    bits |= (uint32_t)(y - y0) <= tall ? (uint32_t)(((uint64_t)line << at) >> 32) : 0u;
+            } else {
+                for (int y = fy, at = -fx; at < 32; ++y, at += na_w) bits |= y >= y0 && y <= y1 ? span(at + x0, at + x1 + 1) : 0u;
+            }
+            return bits;
+        }
+        uint32_t xs = span(x0 - fx, x1 + 1 - fx);
+        if (the_way == kRows) {
+            // (the line's bits, again for every line)
+            if (line_log2 == 2) {
+                const uint32_t next = (uint32_t)__builtin_amdgcn_readfirstlane((int)tags[16]);
+                const int nx = (int)(next & xm), ny = (int)(next >> y_shift);
+                const uint32_t a = (xs & 15u) * 0x1111u & span((y0 - fy) << 2, (y1 + 1 - fy) << 2);
+                const uint32_t b = (span(x0 - nx, x1 + 1 - nx) & 15u) * 0x1111u & span((y0 - ny) << 2, (y1 + 1 - ny) << 2);
+                return a | (b << 16);
+            }
+            xs = __builtin_amdgcn_perm(xs, xs, line_log2 == 3 ? 0x00000000u : line_log2 == 4 ? 0x01000100u : 0x03020100u);
+            return xs & span((y0 - fy) << line_log2, (y1 + 1 - fy) << line_log2);
+        }
+        // token 16 x2 + 8 y1 + 4 x1 + 2 y0 + x0 of the pixel (x, y), bit by bit
+        xs = (xs & 0x0fu) | ((xs & 0xf0u) << 12);
+        xs = (xs & 0x00030003u) | ((xs & 0x000c000cu) << 2);
+        xs |= xs << 2;
+        xs |= xs << 8;
+        uint32_t ys = span(y0 - fy, y1 + 1 - fy);
+        ys = (ys & 0x3u) | ((ys & 0xcu) << 6);
+        ys = (ys & 0x101u) | ((ys & 0x202u) << 1);
+        ys |= ys << 1;
+        ys |= ys << 4;
+        ys |= ys << 16;
+        return xs & ys;
+    }
+    // The lane's query has the window at `query_tag`, its elements are the keys whose pixels are in `tags` (LDS).
+    __device__ __forceinline__ void match_keys(Bits& bits, const uint32_t* tags, uint32_t query_tag, int half) const {
+        if (way != kTagged32) {
+            const uint32_t corner = query_tag + guard;
+            const int x0 = (int)(corner & ((1u << (y_shift - 1)) - 1u)), y0 = (int)(corner >> y_shift);
+            bits.plain |= bits.tagged & (tokens_inside(way, tags, x0, y0, x0 + 2 * na_r, y0 + 2 * na_r) >> (4 * half));
+        } else {
+            match_tags(bits, tags, half, [&](uint32_t t) __attribute__((always_inline)) { return pixels_match(t, query_tag); });
+        }
+    }
+    // The queries that see a key are a rectangle too: those around it, and up to the border where the windows there reach
+    // it.  Its corners (the key's own pixel twice where match_queries compares tags); empty past the last key.
+    __device__ __forceinline__ u32x2 key_corners(int kv) const {
+        if (kv > kv_last) return u32x2{(1u << (y_shift - 1)) - 1u, 0u};      // (a column past any query's)
+        const uint32_t tag = key_pixel(kv);
+        if (query_way == kTagged32) return u32x2{tag, tag};
+        const int x = (int)(tag & ((1u << (y_shift - 1)) - 1u)), y = (int)(tag >> y_shift), d = 2 * na_r;
+        const int x0 = x <= d ? 0 : x - na_r, x1 = x >= na_w - 1 - d ? na_w - 1 : x + na_r;
+        const int y0 = y <= d ? 0 : y - na_r, y1 = y >= na_h - 1 - d ? na_h - 1 : y + na_r;
+        return u32x2{(uint32_t)x0 | ((uint32_t)y0 << y_shift), (uint32_t)x1 | ((uint32_t)y1 << y_shift)};
+    }
+    // The lane's key has these key_corners(), its elements are the queries whose query_block_tag() is in `tags`.
+    __device__ __forceinline__ Bits match_queries(const uint32_t* tags, u32x2 corners, int half) const {
+        Bits bits = {0u, ~0u};
+        if (query_way != kTagged32) {
+            const uint32_t xm = (1u << (y_shift - 1)) - 1u;
+            bits.plain = tokens_inside(query_way, tags, (int)(corners[0] & xm), (int)(corners[0] >> y_shift), (int)(corners[1] & xm), (int)(corners[1] >> y_shift)) >> (4 * half);
+        } else {
+            match_tags(bits, tags, half, [&](uint32_t t) __attribute__((always_inline)) { return pixels_match(corners[0], t); });
+        }
+        return bits;
+    }
+    template <typename F>
+    __device__ __forceinline__ static void match_tags(Bits& bits, const uint32_t* tags, int half, F&& match) {
+        uint32_t same = 0;
+#pragma unroll 1
+        for (int rg = 0; rg < 4; ++rg) {
+            const u32x4 t = *(const u32x4*)&tags[8 * rg + 4 * half];
+            const uint32_t four = (match(t[0]) ? 1u : 0u) | (match(t[1]) ? 2u : 0u) | (match(t[2]) ? 4u : 0u) | (match(t[3]) ? 8u : 0u);
+            same |= four << (8 * rg);
+        }
+        bits.plain |= bits.tagged & same;
+    }
+    // All-ones if element r is kept, else 0.
+    __device__ __forceinline__ static uint32_t keep(const Bits& bits, int r) { return bit_mask(bits.plain, elem_pos(r)); }
     // Wave-uniform shortcut: no pair of the rectangle is masked (decided by index comparisons alone).
     template <uint32_t TERM>
     __device__ __forceinline__ bool term_full(int q_lo, int q_hi, int kv_lo, int kv_hi) const {

@@ -361,16 +361,9 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         typename Mask::Bits bits = mask.row_bits(q_pos, kvs + 4 * half);
         const uint32_t q_tag = Mask::kTags ? s_qtag[tid] : 0u;
         if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[buf][kvb * 32], q_tag, l32, half, scattered);
+        if constexpr (Mask::kCanvas) mask.match_keys(bits, &s_tag[buf][kvb * 32], q_tag, half);
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) {
-            u32x4 tags = {};
-            if constexpr (Mask::kCanvas) {
-                tags = *(const u32x4*)&s_tag[buf][kvb * 32 + 8 * rg + 4 * half];
-                asm volatile("" ::: "memory");   // (one read at a time: there are no registers for four)
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[4 * rg + i] = put(Mask::keep(bits, 4 * rg + i, mask.pixels_match(tags[i], q_tag)), s[4 * rg + i]);
-        }
+        for (int r = 0; r < 16; ++r) s[r] = put(Mask::keep(bits, r), s[r]);
     };
     // The probabilities of a block as two bf16 fragments, and this lane's part of the row sum: over the bf16-rounded
     // probabilities, the values P V is computed from, two at a time (dot product of a packed pair with (1, 1), fp32 accumulation).
@@ -439,7 +432,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
                 for (int r = 0; r < 16; ++r) s[r] = smod.template apply_shifted<false>(s[r], rel(r), 0.0f, shift);
             }
             if (partial) {
-                if constexpr (Mask::kDoc) asm volatile("" : "+v"(s));
+                if constexpr (Mask::kTags) asm volatile("" : "+v"(s));
                 else asm volatile("" ::: "memory");
                 masked(s, kvs, buf, kvb, keep_or_neg_inf);
             }

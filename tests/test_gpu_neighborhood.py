@@ -148,3 +148,40 @@ def test_ds_in_memory_leaves_out_hidden_blocks(B, D, W, H, K, layout, tile):
     # the same bf16 dS summed in another order in fp32: one bf16 rounding of each result, 2^-8 of the larger values
     err = (got[0].float() - want[0].float()).abs()
     assert torch.isfinite(got[0].float()).all() and err.max() <= 2 ** -7 * want[0].float().abs().max()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("W,H,K,layout,tile", [
+    (1, 70, 1, "row_major", 0), (3, 50, 3, "row_major", 0), (15, 19, 15, "row_major", 0), (31, 9, 7, "row_major", 0),     # many lines in 32 tokens
+    (33, 12, 9, "row_major", 0), (130, 3, 3, "row_major", 0),                                                             # two, or one
+    (12, 20, 5, "tiled", 4), (10, 14, 3, "tiled", 2), (6, 20, 5, "tiled", 1), (24, 16, 13, "tiled", 8), (48, 16, 15, "tiled", 16),
+    (64, 64, 21, "tiled", 64), (16, 16, 5, "morton", 0), (8, 8, 7, "morton", 0), (4, 4, 3, "morton", 0)])
+def test_ways_32_tokens_lie_on_a_canvas(W, H, K, layout, tile, D):
+    """The matching pixels of 32 tokens as a rectangle, in every shape that 32 tokens take; few workgroups and 300 copies, with
+    offsets (all 0: the queries' positions are then not known to start at multiples of 32) and without."""
+    import paper_2412_05496_amd as fa
+    dev = torch.device("cuda:0")
+    S = W * H
+    g = torch.Generator().manual_seed(S * K)
+    Q, Kt, V, dO = (torch.randn(1, 2, S, D, generator=g).to(torch.bfloat16).float() for _ in range(4))
+    mask = fo.neighborhood_mask(W, H, K, layout, tile)
+    O_ref, LSE_ref = fo.flex_attention(Q, Kt, V, fo.Identity(), mask, D ** -0.5)
+    refs = fo.flex_attention_backward(Q, Kt, V, dO, fo.Identity(), mask, D ** -0.5)
+    bm = fa.alloc_blockmask(1, 1, S, S, 128, 64, device=dev)
+    params = na_params(fa, W, H, K, layout, tile)
+    fa.flexattn_blockmask_build(fa.MASK_NEIGHBORHOOD, params, bm)
+    print(f"[case] {W} x {H} K={K} {layout} {tile} D={D}", flush=True)
+    for copies in (1, 300 if S < 1024 else 40):
+        q, k, v, do = (t.to(torch.bfloat16).to(dev).expand(copies, -1, -1, -1) for t in (Q, Kt, V, dO))
+        for offsets in (None, torch.zeros(copies, dtype=torch.int32, device=dev)):
+            params.q_offsets = offsets
+            O, LSE = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=dev), torch.full(q.shape[:3], float("nan"), device=dev)
+            head = (fa.SCORE_IDENTITY, fa.MASK_NEIGHBORHOOD, params, bm, D ** -0.5)
+            fa.flexattn_forward(q, k, v, *head, O, LSE)
+            grads = [torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=dev) for _ in range(3)]
+            fa.flexattn_backward(q, k, v, O, do, LSE, *head, *grads)
+            torch.cuda.synchronize()
+            hp.check_output(O[:1], LSE[:1], O_ref, LSE_ref)
+            for name, got, ref in zip(("dQ", "dK", "dV"), grads, refs):
+                hp.check_grad(name, got[:1], ref)
+                assert torch.equal(got, got[:1].expand_as(got)), name
