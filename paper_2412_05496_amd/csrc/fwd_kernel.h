@@ -12,13 +12,14 @@
 // the A operand of K Q^T as they are, V^T fragments come out of the row-major V tile through the
 // transposing LDS read.  Q lives in registers for the whole kernel.
 //
-// Four forms of the loop over the tiles, the first three with one barrier per tile:
+// Five forms of the loop over the tiles, the first four with one barrier per tile:
 //   pipelined  while the VALU works on the softmax of tile t, the MFMA unit computes S^T of tile t + 1; K(t + 2) and
 //              V(t + 1) are in flight from HBM / L2 meanwhile;
 //   PLAIN      (D = 64) a 32-key block after the other, K and V one 64-key tile ahead: four waves per SIMD instead of
 //              three (fwd_plain, plain_pays);
 //   UNITS      (D = 128) the same with 32-key tiles in a ring of three, two tiles ahead: three instead of two
 //              (fwd_units, units_pay);
+//   PAIRS      four waves on 64 rows, each with its half of a tile's keys: rows of blocks of 64, and halves of 128 (pairs_pay);
 //   SPLIT      for launches that leave the chip idle: the waves of a workgroup share 32 rows and take their keys in turn,
 //              each through LDS of its own, and merge (m, l, O) at the end (split_waves).
 #pragma once
@@ -65,8 +66,7 @@ constexpr int kTileKV = 64;   // keys per kernel tile
 // causal, S = 1024, 64 x 16 heads: 277 -> 250; window of 1024, S = 5000: 114 -> 105; relative bias, S = 8192,
 // 64 heads: 158 -> 127; no mask, S = 2048: 89.5 -> 86.5; packed documents with ALiBi: 218 -> 216.
 // The pipelined one stays where it is the better one: a bounded soft-cap, whose softmax needs no running
-// maximum (287 -> 299), and Bq = 64, where LDS admits 2.5 waves per SIMD either way (a single small call: 7.7
-// -> 8.4); and, where neither a window, documents nor a canvas ends rows early, long rows on a chip that is not full and
+// maximum (287 -> 299); and, where neither a window, documents nor a canvas ends rows early, long rows on a chip that is not full and
 // soft-caps whose maximum has to be tracked (plain_pays; causal, S = 4096, 32 heads 132 <- 110, S = 8192, 16 heads 208 <- 196,
 // S = 4096, 64 heads 190 <- 200; cap of 100, S = 2048, 32 heads 64.6 <- 60.6, S = 8192, 64 heads 924 <- 904, S = 1024, 256 heads
 // 92.3 <- 94.7: plain <- pipelined).  Neighborhood masks gain most: 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (490 ->
@@ -159,11 +159,32 @@ int split_waves(const FwdArgs& a, int D) {
     const bool eight = groups <= 256 ? rows.longest > (D == 64 ? 256 : 512) : groups <= 512 && (D == 64 ? keys >= 2048 : rows.sure_uneven && keys >= 4096);
     return eight ? 8 : 4;
 }
+// The pairs form: a workgroup takes 64 rows, and its four waves are two slices of 32 rows times the two 32-key halves of every
+// tile; the two waves of the same rows merge (m, l, O) at the end.  Rows of blocks of 64 always: two waves, one per slice, leave
+// LDS for one (D = 128) or 2.5 (D = 64) waves per SIMD, four that share the tiles make it two and four (us, two waves -> pairs, Bq
+// = 64: causal, S = 8192, 16 heads, D = 128 / 64 381 -> 302 / 225 -> 178; S = 1024, 256 heads 153 -> 117 / 72 -> 62; S = 300, 1024 heads 98 -> 91 /
+// 40 -> 39; no mask, S = 2048, 64 heads 192 -> 155 / 105 -> 85; window of 1024, S = 8192, 2 x 16 / 4 heads 225 -> 169 / 108 -> 88; soft-cap, S = 835, 45 x
+// 32 heads 641 -> 529 / 347 -> 296).  Rows of blocks of 128 where their halves end the launch sooner: rows of uneven length on a chip
+// that they do not fill for long, by the workgroups of 128 rows (us, a row of blocks -> pairs, S x heads: causal, D = 64, 8192 x 16
+// 189 -> 170, 4096 x 32 106 -> 98, 2048 x 64 65 -> 58, 16384 x 6 259 -> 257, but 16384 x 16 614 -> 627, 8192 x 64 622 -> 654, 1024 x 256 60 -> 62;
+// D = 128, 8192 x 8 173 -> 153, 4096 x 16 110 -> 83, 2048 x 32 60 -> 58, but 8192 x 16 279 -> 299, 16384 x 6 399 -> 446; documents of 256 to
+// 4096 with ALiBi, D = 64, 8192 x 16 92 -> 63, 16384 x 6 97 -> 63, 16384 x 16 156 -> 148, 8192 x 32 164 -> 143, 2048 x 128 108 -> 103, but 8192 x
+// 64 285 -> 283; D = 128, 4096 x 16 97 -> 65, 8192 x 8 77 -> 55, 16384 x 6 116 -> 95, but 8192 x 16 103 -> 102, 16384 x 16 218 -> 239; soft-cap, D = 64, 4096
+// x 32 142 -> 123, but 8192 x 16 246 -> 252).  Rows of one length lose (no mask, S = 2048, 32 heads 45 -> 46, window of 600 62 -> 68).
+template <uint32_t MASK, bool BOUNDED>
+bool pairs_pay(const FwdArgs& a, int D, unsigned grid) {
+    if (a.Bq == 64) return true;
+    if (!line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven || a.kv_len < 2048) return false;
+    constexpr bool doc = PartialMask<MASK>::kDoc;
+    if (D == 128) return grid <= (doc ? 3 * 256 : 2 * 256);
+    return grid <= (doc ? 8 * 256 : 4 * 256) && !(BOUNDED && !doc && a.kv_len >= 8192);
+}
 // Waves per SIMD to compile for: what registers (512 per SIMD lane) and LDS admit.  The pipelined variants
 // with a relative-bias table would spill at three.
-template <int D, uint32_t SCORE, bool UNITS, bool PLAIN, bool SPLIT>
+template <int D, uint32_t SCORE, bool UNITS, bool PLAIN, bool SPLIT, bool PAIRS>
 constexpr int fwd_waves_per_simd() {
     if (SPLIT) return 2;
+    if (PAIRS) return D == 64 ? 4 : 2;
     if (D != 64) return UNITS ? 3 : 2;
     if (PLAIN) return 4;
     return (SCORE & FLEXATTN_SCORE_REL_BIAS) ? 2 : 3;
@@ -171,7 +192,7 @@ constexpr int fwd_waves_per_simd() {
 
 // BOUNDED: the score_mod ends in a soft-cap small enough that the cap itself serves as the fixed
 // softmax maximum (see ScoreMod::bounded); chosen by the host from the cap value.
-// UNITS: 32-key units in a ring of three (fwd_units).  PLAIN: no tile pipeline (fwd_plain).  SPLIT: the NW waves share 32
+// UNITS: 32-key units in a ring of three (fwd_units).  PLAIN: no tile pipeline (fwd_plain).  PAIRS: see pairs_pay.  SPLIT: the NW waves share 32
 // rows and take the keys in turn (split_waves).
 // PAGED: the tiles of K and V are fetched from a paged pool through the converted block lists;
 // the mods keep seeing the logical key index.
@@ -179,9 +200,11 @@ constexpr int fwd_waves_per_simd() {
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
 template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED, bool UNITS = false,
-          bool PLAIN = fwd_plain<D, NW, BOUNDED>(), bool SPLIT = false>
-__global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN, SPLIT>())) void fwd_kernel(const FwdArgs a) {
-    const int Bq = SPLIT ? a.Bq : NW * 32;
+          bool PLAIN = fwd_plain<D, NW, BOUNDED>(), bool SPLIT = false, bool PAIRS = false>
+__global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN, SPLIT, PAIRS>())) void fwd_kernel(const FwdArgs a) {
+    static_assert(!PAIRS || (NW == 4 && !UNITS && !PLAIN && !SPLIT), "two row slices times two key halves");
+    constexpr int kSlices = PAIRS ? NW / 2 : NW;    // of 32 rows
+    const int Bq = SPLIT || PAIRS ? a.Bq : kSlices * 32;
     constexpr int TILE = kTileKV * D;              // elements per LDS tile
 
     // K(even), K(odd), V(even), V(odd); UNITS: three slots of 32 keys, K then V; SPLIT: 32 keys of K, then V, for each wave
@@ -191,17 +214,21 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     using Mask = PartialMask<MASK>;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[SPLIT ? NW : UNITS ? 3 : 2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys, per buffer (SPLIT: wave)
 
-    constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || PLAIN || SPLIT);
+    constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || PLAIN || SPLIT || PAIRS);
     __shared__ uint32_t s_qtag[Mask::kTags ? NW * 64 : 1];            // each lane's own tag (its query's)
     __shared__ uint8_t s_hidden[kHiddenTable ? kHiddenTiles : 1];    // CanvasBlocks::hidden_bits of the first tiles
 
     // ---- workgroup -> (b, hkv, g, row of blocks).  Rows are taken longest first (the BlockMask's work order), or
     // last-first without one (causal-like masks: longest first).
     int unit, rem, slice = 0;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (SPLIT ? Bq / 32 : 1), unit, rem)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (SPLIT ? Bq / 32 : PAIRS ? Bq / 64 : 1), unit, rem)) return;
     if constexpr (SPLIT) {
         slice = rem & (Bq / 32 - 1);                // which 32 rows of the block
         rem >>= Bq == 128 ? 2 : 1;
+    }
+    if constexpr (PAIRS) {
+        slice = rem & (Bq / 64 - 1);                // which 64 rows of the block
+        rem >>= Bq == 128 ? 1 : 0;
     }
     const int g = rem % a.G;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv, hq = hkv * a.G + g;
@@ -211,9 +238,11 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wave_rows = row * Bq + (SPLIT ? slice : w) * 32;     // first of the wave's 32 rows
+    const int my_slice = PAIRS ? w & 1 : w, my_keys = PAIRS ? w >> 1 : 0;  // PAIRS: which 32 rows, which 32 keys of every tile
+    const int first_row = row * Bq + (SPLIT ? 32 : 64) * slice;            // of the workgroup
+    const int wave_rows = first_row + (SPLIT ? 0 : my_slice) * 32;         // first of the wave's 32 rows
     const int q_row = wave_rows + l32;
-    if (SPLIT && wave_rows >= a.q_len) return;
+    if ((SPLIT || PAIRS) && first_row >= a.q_len) return;
 
     const int64_t line = plane * a.NR + row;
     const int n_full = ldc(a.full_num + line), n_part = ldc(a.kv_num + line);
@@ -287,11 +316,11 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
             if (SPLIT || w == (turn & (NW - 1))) s_tag[buf][lane] = mask.key_pixel(min(kv0 + lane, a.kv_len - 1));
         }
     };
-    if constexpr (kHiddenTable) fill_hidden_tiles<SPLIT ? 1 : NW, NW * 64>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, a.sub, a.Bk, SPLIT ? wave_rows : row * Bq, tid);
+    if constexpr (kHiddenTable) fill_hidden_tiles<SPLIT ? 1 : kSlices, NW * 64>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, a.sub, a.Bk, first_row, tid);
     // 32-key blocks of tile t that are hidden from this wave (bit 0, bit 1); visible after the prologue's barrier
     auto hidden_of = [&](int t) __attribute__((always_inline)) -> uint32_t {
         if constexpr (!kHiddenTable) return 0u;
-        else return t < min(T, kHiddenTiles) ? ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (SPLIT ? 0 : 2 * w)) & 3u : 0u;
+        else return t < min(T, kHiddenTiles) ? ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (SPLIT ? 0 : 2 * my_slice)) & 3u : 0u;
     };
     const float inv_neg2c = smod.capl2 > 0.0f ? -0.5f / smod.capl2 : 0.0f;   // 1 / (-2 cap log2 e)
 
@@ -322,8 +351,8 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         tile_src(v_head, v_rsrc, v_row_bytes, kv0, page, row, rsrc, soff);
         v_loader.start(rsrc, smem_bytes + (2 + buf) * (TILE * 2), soff);
     };
-    const RowReader<D> k_reader(l32, half);
-    const TrReader<D> v_reader(lane);
+    const RowReader<D> k_reader(l32, half, my_keys * 32 * D * 2);
+    const TrReader<D> v_reader(lane, my_keys * 32 * D * 2);
 
     // S^T = K Q^T for the two 32-key blocks of the K tile in buffer BUF (compile-time);
     // between(m) runs after the m-th of the 2 D / 16 MFMAs (used to spread out tile loads)
@@ -666,6 +695,79 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         }
         if (u < TU) unit_step(u, s0);
         if (u + 1 < TU) unit_step(u + 1, s1);
+    } else if constexpr (PAIRS) {
+        // Every wave takes its 32 keys of every tile, K and V one tile ahead.
+        first_tile();
+        auto pair_step = [&](int t, auto buf_tag) {
+            constexpr int BUF = decltype(buf_tag)::value;
+            wait_vmem();
+            __syncthreads();        // tile t has landed, and nobody still reads tile t - 1
+            const uint32_t hid = hidden_of(t) >> my_keys;
+            const int kv = kv_t + 32 * my_keys;
+            const bool partial = part_t;
+            if (t + 1 < T) {
+                kv_t = walk.next(part_t, pg_t, pr_t);
+                load_k(BUF ^ 1, kv_t, pg_t, pr_t);
+                load_v(BUF ^ 1, kv_t, pg_t, pr_t);
+                if (part_t) make_tags(BUF ^ 1, kv_t, t + 1);
+            }
+            if (hidden_block(hid, partial, kv, 0)) return;
+            f32x16 s;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+            read_ahead<D / 16>([&](auto m) { return k_reader.read(smem_bytes + BUF * (TILE * 2), 0, decltype(m)::value); },
+                               [&](auto m, bf16x8 f) { s = mfma32(f, qf[decltype(m)::value], s); });
+            bf16x8 pf[2];
+            softmax(s, kv, partial, BUF, my_keys, pf);
+            constexpr int NDB = D / 32;
+            read_ahead<2 * NDB>([&](auto m) { return v_reader.read(smem_bytes + (2 + BUF) * (TILE * 2), 16 * (decltype(m)::value / NDB), decltype(m)::value % NDB); },
+                                [&](auto m, bf16x8 f) {
+                                    constexpr int db = decltype(m)::value % NDB, c = decltype(m)::value / NDB;
+                                    oacc[db] = mfma32(f, pf[c], oacc[db]);
+                                });
+        };
+        int t = 0;
+        for (; t + 1 < T; t += 2) {
+            pair_step(t, std::integral_constant<int, 0>{});
+            pair_step(t + 1, std::integral_constant<int, 1>{});
+        }
+        if (t < T) pair_step(t, std::integral_constant<int, 0>{});
+        // ---- the two waves of the same rows become one: each finishes half of the dims and hands over the other half
+        __shared__ float s_ml[NW][2][32];
+        const float l_wave = l_run + swap_halves(l_run);
+        if (half == 0) {
+            s_ml[w][0][l32] = m_run;
+            s_ml[w][1][l32] = l_wave;
+        }
+        constexpr int HDB = D / 64;
+        __syncthreads();            // (the last tile has been read)
+        f32x4* give = (f32x4*)smem + w * (HDB * 4 * 64) + lane;
+#pragma unroll
+        for (int q = 0; q < HDB * 4; ++q) {
+            f32x4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = my_keys ? oacc[q >> 2][4 * (q & 3) + i] : oacc[HDB + (q >> 2)][4 * (q & 3) + i];
+            give[q * 64] = v;
+        }
+        __syncthreads();
+        const float m_other = s_ml[w ^ 2][0][l32], m = fmaxf(m_run, m_other), m_from = m == -INFINITY ? 0.0f : m;
+        const float mine = fast_exp2(m_run - m_from), theirs = fast_exp2(m_other - m_from);
+        const float l = mine * l_wave + theirs * s_ml[w ^ 2][1][l32];
+        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+        if (!real_row) return;
+        const f32x4* take = (const f32x4*)smem + (w ^ 2) * (HDB * 4 * 64) + lane;
+#pragma unroll
+        for (int q = 0; q < HDB * 4; ++q) {
+            f32x4 o = theirs * take[q * 64];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(mine, my_keys ? oacc[HDB + (q >> 2)][4 * (q & 3) + i] : oacc[q >> 2][4 * (q & 3) + i], o[i]) * inv;
+            u32x2 pk;
+            pk[0] = pack_bf16(o[0], o[1]);
+            pk[1] = pack_bf16(o[2], o[3]);
+            *(u32x2*)(o_ptr + (my_keys * HDB + (q >> 2)) * 32 + 8 * (q & 3) + 4 * half) = pk;
+        }
+        if (my_keys == 0 && half == 0) *lse_ptr = l > 0.0f ? (m + fast_log2(l)) * kLn2 : -INFINITY;
+        return;
     } else if constexpr (PLAIN) {
         // One block of 32 keys after the other, K and V one tile ahead.  A wave leaves out the blocks that
         // the mask hides from all of its rows.
@@ -811,6 +913,12 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
         else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(256), 0, st, a);
         return FLEXATTN_OK;
     }
+    if (pairs_pay<MASK, BOUNDED>(a, D, grid)) {
+        const dim3 halves(unit_grid(a.B * a.Hkv, a.G * a.NR * (Bq / 64)));
+        if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), halves, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), halves, dim3(256), 0, st, a);
+        return FLEXATTN_OK;
+    }
 #define FLEXATTN_LAUNCH(DD, NW)                                                                            \
     hipLaunchKernelGGL((fwd_kernel<DD, NW, MASK, SCORE, BOUNDED, PAGED>), dim3(grid), dim3(NW * 64), 0, st, a); \
     return FLEXATTN_OK;
@@ -823,7 +931,6 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
         }
         FLEXATTN_LAUNCH(128, 4)
     }
-    if (D == 128 && Bq == 64) { FLEXATTN_LAUNCH(128, 2) }
     if (D == 64 && Bq == 128) {
         constexpr bool dense = !mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
         if constexpr (fwd_plain<64, 4, BOUNDED>() && dense) {
@@ -834,7 +941,6 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
         }
         FLEXATTN_LAUNCH(64, 4)
     }
-    if (D == 64 && Bq == 64) { FLEXATTN_LAUNCH(64, 2) }
 #undef FLEXATTN_LAUNCH
     return FLEXATTN_ERR_UNSUPPORTED;
 }
