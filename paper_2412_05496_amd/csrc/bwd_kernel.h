@@ -711,9 +711,16 @@ template <int D, int NW>
 constexpr bool dq_skips_hidden() {
     return D == 64 && NW == 4;
 }
-template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool CAPTURED = false, bool SKIP = dq_skips_hidden<D, NW>()>
+//
+// PAIRS: a workgroup takes 64 rows; the four waves are two slices of 32 rows times the two key halves of every tile, and the two waves
+// of the same rows add up at the end.  Two waves, one per slice, leave LDS for one (D = 128) or 2.5 (D = 64) waves per SIMD;
+// four that share the tiles make it two and three
+// (dq_pairs_pay has the times, and where the halves of rows of blocks of 128 take this form).
+template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool CAPTURED = false, bool SKIP = dq_skips_hidden<D, NW>(), bool PAIRS = false>
 __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kernel(const BwdArgs a) {
-    constexpr int Bq = NW * 32;
+    static_assert(!PAIRS || (NW == 4 && SKIP), "two row slices times two key halves");
+    constexpr int kSlices = PAIRS ? NW / 2 : NW;
+    const int Bq = PAIRS ? a.Bq : kSlices * 32;
     constexpr int TILE = 64 * D;
     __shared__ __attribute__((aligned(1024))) bf16 smem[4 * TILE];   // K(even), K(odd), V(even), V(odd)
     constexpr int kTabAlibi = 1024;                                  // the table has at most 1024 entries
@@ -724,7 +731,12 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     __shared__ uint8_t s_hidden[Mask::kCanvas && SKIP ? kHiddenTiles : 1];           // CanvasBlocks::hidden_bits of the first tiles
 
     int unit, rem;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR, unit, rem)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (PAIRS ? Bq / 64 : 1), unit, rem)) return;
+    int slice = 0;                                                   // PAIRS: which 64 rows of the block
+    if constexpr (PAIRS) {
+        slice = rem & (Bq / 64 - 1);
+        rem >>= Bq == 128 ? 1 : 0;
+    }
     const int g = rem % a.G;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv, hq = hkv * a.G + g;
     const int64_t plane = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0);
@@ -732,7 +744,10 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int q_row = row * Bq + w * 32 + l32;
+    const int my_slice = PAIRS ? w & 1 : w, my_keys = PAIRS ? w >> 1 : 0;
+    const int first_row = row * Bq + 64 * slice, wave_rows = first_row + my_slice * 32;
+    if (PAIRS && !CAPTURED && first_row >= a.q_len) return;
+    const int q_row = wave_rows + l32;
 
     const int64_t line = ((int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0)) * a.NR + row;
     const int n_full = ldc(a.full_kv_num + line), n_part = ldc(a.kv_num + line);
@@ -777,7 +792,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     float lse2, neg_delta;
     if (CAPTURED || a.make_delta) {
         row_scalars<D, SCORE>(a, b, hq, q_ld, half, dof, lse2, neg_delta);
-        if (!CAPTURED && real_row && half == 0) {
+        if (!CAPTURED && real_row && half == 0 && my_keys == 0) {
             a.delta[rowi] = neg_delta;
             a.lse2[rowi] = lse2;
         }
@@ -816,11 +831,11 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         k_loader.start(k_rsrc, lds_addr(smem) + buf * (TILE * 2), kv0 * k_row_bytes);
         v_loader.start(v_rsrc, lds_addr(smem) + (2 + buf) * (TILE * 2), kv0 * v_row_bytes);
     };
-    const RowReader<D> row_reader(l32, half, lds_addr(smem));
-    const TrReader<D> tr_reader(lane, lds_addr(smem));
+    const RowReader<D> row_reader(l32, half, lds_addr(smem) + my_keys * 32 * D * 2);
+    const TrReader<D> tr_reader(lane, lds_addr(smem) + my_keys * 32 * D * 2);
     // a row past q_len must add nothing to the sums
     const float rc = (CAPTURED && !real_row) ? -INFINITY : lse2;
-    const int q_wave_min = row * Bq + w * 32 + q_offset_of(a.p, b);   // smallest q_idx of this wave's rows
+    const int q_wave_min = wave_rows + q_offset_of(a.p, b);   // smallest q_idx of this wave's rows
     float g_alibi = 0.0f, g_hi = 0.0f, g_lo = 0.0f;
 
     f32x16 dq[D / 32];
@@ -830,10 +845,10 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         for (int r = 0; r < 16; ++r) dq[db][r] = 0.0f;
 
     // a wave leaves out the blocks of 32 keys that the mask hides from all of its rows, and all if it has no row
-    const bool no_row = row * Bq + w * 32 >= a.q_len;
-    if constexpr (SKIP && Mask::kCanvas) fill_hidden_tiles<NW>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, sub, a.Bk, row * Bq, tid);
+    const bool no_row = wave_rows >= a.q_len;
+    if constexpr (SKIP && Mask::kCanvas) fill_hidden_tiles<kSlices, NW * 64>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, sub, a.Bk, first_row, tid);
     auto hidden_block = [&](int t, bool partial, int kv, int kvb) __attribute__((always_inline)) {
-        if constexpr (Mask::kCanvas) return no_row || (t < kHiddenTiles && ((__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (2 * w + kvb)) & 1));
+        if constexpr (Mask::kCanvas) return no_row || (t < kHiddenTiles && ((__builtin_amdgcn_readfirstlane((int)s_hidden[t]) >> (2 * my_slice + kvb)) & 1));
         else return no_row || (partial && mask.hidden(q_wave_min, q_wave_min + 31, kv, kv + 31));
     };
     bool part_next = false;
@@ -864,10 +879,11 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         if constexpr (SKIP) {
             if (ld) load_tiles(BUF ^ 1, kv0);
         }
-        static_for<0, 2>([&](auto kvb_tag) {
+        static_for<0, PAIRS ? 1 : 2>([&](auto kvb_tag) {
             constexpr int kvb = decltype(kvb_tag)::value;
+            const int block = PAIRS ? my_keys : kvb;        // (the readers know my_keys)
             if constexpr (SKIP) {
-                if (hidden_block(t, partial, kv0_cur + 32 * kvb, kvb)) return;
+                if (hidden_block(t, partial, kv0_cur + 32 * block, block)) return;
             }
             // S^T = K Q^T and dP^T = V dO^T for 32 keys; operand fragments read PF MFMAs ahead
             f32x16 sacc, dpacc;
@@ -906,10 +922,10 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
                 });
             }
             // q_idx - kv_idx of element r is dq0 - 8 (r >> 2) - (r & 3)
-            const int dq0 = q_pos - (kv0_cur + kvb * 32 + 4 * half);
+            const int dq0 = q_pos - (kv0_cur + block * 32 + 4 * half);
             const float abase = smod.alibi_base(dq0);
             float rel_uni;
-            const int kvs_blk = kv0_cur + kvb * 32;
+            const int kvs_blk = kv0_cur + block * 32;
             const bool rel_is_uni = smod.rel_uniform(q_wave_min - (kvs_blk + 31), q_wave_min + 31 - kvs_blk, rel_uni);
             auto rel = [&](int r) __attribute__((always_inline)) {
                 return typename decltype(smod)::RelPos(dq0, abase, -(8 * (r >> 2) + (r & 3)));
@@ -932,13 +948,13 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
             if (partial && !mask.full(q_wave_min, q_wave_min + 31, kvs_blk, kvs_blk + 31)) {
                 asm volatile("" ::: "memory");   // keep this a branch
                 typename Mask::Bits bits = mask.row_bits(q_pos, kvs_blk + 4 * half);
-                if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[BUF][kvb * 32], q_tag, l32, half, scattered);
-                if constexpr (Mask::kCanvas) mask.match_keys(bits, &s_tag[BUF][kvb * 32], q_tag, half);
+                if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[BUF][block * 32], q_tag, l32, half, scattered);
+                if constexpr (Mask::kCanvas) mask.match_keys(bits, &s_tag[BUF][block * 32], q_tag, half);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) dpacc[r] = keep_or_zero(Mask::keep(bits, r), dpacc[r]);
             }
             if constexpr (CAPTURED) {
-                const int kvs = kv0_cur + kvb * 32;
+                const int kvs = kvs_blk;
                 if constexpr (ScoreMod<SCORE>::kAlibi) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
@@ -1014,6 +1030,33 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         return;
     }
     const float qscale = a.scale * ScoreMod<SCORE>::grad_scale();
+    if constexpr (PAIRS) {
+        // each of the two waves of the same rows finishes half of the dims and hands over the other half (the last step ended
+        // with a barrier: the tiles are free)
+        constexpr int HDB = D / 64;
+        f32x4* give = (f32x4*)smem + w * (HDB * 4 * 64) + lane;
+        const f32x4* take = (const f32x4*)smem + (w ^ 2) * (HDB * 4 * 64) + lane;
+#pragma unroll
+        for (int q = 0; q < HDB * 4; ++q) {
+            f32x4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = my_keys ? dq[q >> 2][4 * (q & 3) + i] : dq[HDB + (q >> 2)][4 * (q & 3) + i];
+            give[q * 64] = v;
+        }
+        __syncthreads();
+        if (!real_row) return;
+#pragma unroll
+        for (int q = 0; q < HDB * 4; ++q) {
+            f32x4 v = take[q * 64];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = (v[i] + (my_keys ? dq[HDB + (q >> 2)][4 * (q & 3) + i] : dq[q >> 2][4 * (q & 3) + i])) * qscale;
+            u32x2 pk;
+            pk[0] = pack_bf16(v[0], v[1]);
+            pk[1] = pack_bf16(v[2], v[3]);
+            *(u32x2*)(dq_ptr + (my_keys * HDB + (q >> 2)) * 32 + 8 * (q & 3) + 4 * half) = pk;
+        }
+        return;
+    }
     if (!real_row) return;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)

@@ -520,6 +520,20 @@ int dq_split_waves(const BwdArgs& a, int D) {
     if (groups > most) return 0;
     return (groups <= 256 ? rows.longest >= 512 : groups <= 512 && rows.sure_uneven && keys >= 2048) ? 8 : 4;
 }
+// The pairs form of dQ (bwd_dq_kernel), by the length of the longest rows with Bq = 64, and with Bq = 128 by the workgroups of 128
+// uneven rows, whose halves end a launch sooner.  us of the whole backward, without -> with: Bq = 64, D = 128, causal, S = 8192, 16
+// heads 950 -> 892, S = 512, 128 heads 85 -> 81, S = 300, 1024 heads 280 -> 284, window of 1024 546 -> 493, D = 64, S = 8192 527 -> 488, S = 835, 45 x
+// 32 heads 931 -> 885, S = 512 45 -> 48, documents, S = 16384, 16 heads 414 -> 373; Bq = 128, S x heads, D = 64, causal, 8192 x 16 532 -> 506, 2048 x 32
+// 104 -> 99, 16384 x 16 1952 -> 1905, 8192 x 32 1010 -> 1013, but 1024 x 256 188 -> 193, documents, 8192 x 8 131 -> 110, 16384 x 16 403 -> 392, but 8192 x 64 828
+// -> 844, D = 128, causal, 4096 x 16 294 -> 262, but 8192 x 16 909 -> 918, documents, 8192 x 8 184 -> 158, 8192 x 16 304 -> 301, but 16384 x 16 705 -> 736.
+template <uint32_t MASK>
+bool dq_pairs_pay(const BwdArgs& a, int D) {
+    const LineShape rows = line_shape<MASK>(a.p, a.q_len, a.kv_len);
+    if (a.Bq == 64) return rows.longest >= (D == 64 ? 768 : 448);
+    if (!rows.uneven || a.kv_len < 2048) return false;
+    const unsigned grid = unit_grid(a.B * a.Hkv, a.G * a.NR);
+    return grid <= (D == 64 ? 8 * 256 : PartialMask<MASK>::kDoc ? 4 * 256 : 2 * 256);
+}
 // us, bwd_dkdv_kernel -> 4 waves / 8 waves: causal, S = 4096, D = 64, 1 head 51 -> 39 / 21, 4 52 -> 41 / 29, 8 58 -> 50 / 54, 16 92 -> 98; D = 128 (4
 // waves), 1 head 72 -> 45, 4 74 -> 58, 8 90 -> 111; 8 query and 1 KV heads, S = 2048 199 -> 145 / 74, D = 128 280 -> 166; 32 / 8, S = 2048 101 -> 77 /
 // 53; S = 1000, D = 64, 8 / 16 / 32 heads 16.8 -> 13.7 / 10.1, 17.1 -> 15.9 / 15.3, 23.2 -> 25.1, D = 128, 8 / 16 heads 23.8 -> 16.8, 24.2 -> 23.9; S =
@@ -636,6 +650,10 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
             if (D == 128) hipLaunchKernelGGL((bwd_dq_split_kernel<128, 4, MASK, SCORE>), slices, dim3(256), 0, st, aq);
             else if (waves == 8) hipLaunchKernelGGL((bwd_dq_split_kernel<64, 8, MASK, SCORE>), slices, dim3(512), 0, st, aq);
             else hipLaunchKernelGGL((bwd_dq_split_kernel<64, 4, MASK, SCORE>), slices, dim3(256), 0, st, aq);
+        } else if (dq_pairs_pay<MASK>(a, D)) {
+            const dim3 halves(unit_grid(a.B * a.Hkv, a.G * a.NR * (a.Bq / 64)));
+            if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, false, true, true>), halves, dim3(256), 0, st, aq);
+            else hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, true, true>), halves, dim3(256), 0, st, aq);
         } else if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
         else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
         else if (a.Bq == 128) launch_dq64<MASK, SCORE>(aq, grid_q, st);
@@ -656,8 +674,13 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
     if (stages & kBwdStageCaptured) {
         if constexpr ((SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS)) != 0) {
             if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);
-            else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE, true>), dim3(grid_q), dim3(128), 0, st, a);
             else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);
+            // (us, two waves -> pairs, ALiBi, causal: D = 64 / 128, S = 8192, 16 heads 276 -> 237 / 435 -> 321, S = 700, 256 heads 59 -> 52 / 100
+            // -> 85, S = 1000, 4 heads 26 -> 17 / 32 -> 21, but S = 300, 1024 heads 71 -> 76 / 141 -> 143; documents, S = 8192, 16 heads 121 -> 85 / 178 -> 121)
+            else if (const bool pairs = line_shape<MASK>(a.p, a.q_len, a.kv_len).longest >= 448; D == 128) {
+                if (pairs) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, true, true, true>), dim3(grid_q), dim3(256), 0, st, a);
+                else hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE, true>), dim3(grid_q), dim3(128), 0, st, a);
+            } else if (pairs) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, true, true, true>), dim3(grid_q), dim3(256), 0, st, a);
             else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE, true>), dim3(grid_q), dim3(128), 0, st, a);
         } else {
             return FLEXATTN_ERR_UNSUPPORTED;     // this score_mod captures no tensor
