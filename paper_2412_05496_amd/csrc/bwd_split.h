@@ -525,13 +525,15 @@ int dq_split_waves(const BwdArgs& a, int D) {
 // heads 950 -> 892, S = 512, 128 heads 85 -> 81, S = 300, 1024 heads 280 -> 284, window of 1024 546 -> 493, D = 64, S = 8192 527 -> 488, S = 835, 45 x
 // 32 heads 931 -> 885, S = 512 45 -> 48, documents, S = 16384, 16 heads 414 -> 373; Bq = 128, S x heads, D = 64, causal, 8192 x 16 532 -> 506, 2048 x 32
 // 104 -> 99, 16384 x 16 1952 -> 1905, 8192 x 32 1010 -> 1013, but 1024 x 256 188 -> 193, documents, 8192 x 8 131 -> 110, 16384 x 16 403 -> 392, but 8192 x 64 828
-// -> 844, D = 128, causal, 4096 x 16 294 -> 262, but 8192 x 16 909 -> 918, documents, 8192 x 8 184 -> 158, 8192 x 16 304 -> 301, but 16384 x 16 705 -> 736.
+// -> 844, D = 128, causal, 4096 x 16 294 -> 262, but 8192 x 16 909 -> 918, documents, 8192 x 8 184 -> 158, 8192 x 16 304 -> 301, but 16384 x 16 705 -> 736;
+// rows of one length, D = 64, no mask, 1500 x 32 89 -> 84, but 3000 x 32 267 -> 274.
 template <uint32_t MASK>
 bool dq_pairs_pay(const BwdArgs& a, int D) {
     const LineShape rows = line_shape<MASK>(a.p, a.q_len, a.kv_len);
     if (a.Bq == 64) return rows.longest >= (D == 64 ? 768 : 448);
-    if (!rows.uneven || a.kv_len < 2048) return false;
     const unsigned grid = unit_grid(a.B * a.Hkv, a.G * a.NR);
+    if (D == 64 && rows.sure >= 1024 && grid <= 2 * 256) return true;
+    if (!rows.uneven || a.kv_len < 2048) return false;
     return grid <= (D == 64 ? 8 * 256 : PartialMask<MASK>::kDoc ? 4 * 256 : 2 * 256);
 }
 // us, bwd_dkdv_kernel -> 4 waves / 8 waves: causal, S = 4096, D = 64, 1 head 51 -> 39 / 21, 4 52 -> 41 / 29, 8 58 -> 50 / 54, 16 92 -> 98; D = 128 (4

@@ -170,11 +170,15 @@ int split_waves(const FwdArgs& a, int D) {
 // D = 128, 8192 x 8 173 -> 153, 4096 x 16 110 -> 83, 2048 x 32 60 -> 58, but 8192 x 16 279 -> 299, 16384 x 6 399 -> 446; documents of 256 to
 // 4096 with ALiBi, D = 64, 8192 x 16 92 -> 63, 16384 x 6 97 -> 63, 16384 x 16 156 -> 148, 8192 x 32 164 -> 143, 2048 x 128 108 -> 103, but 8192 x
 // 64 285 -> 283; D = 128, 4096 x 16 97 -> 65, 8192 x 8 77 -> 55, 16384 x 6 116 -> 95, but 8192 x 16 103 -> 102, 16384 x 16 218 -> 239; soft-cap, D = 64, 4096
-// x 32 142 -> 123, but 8192 x 16 246 -> 252).  Rows of one length lose (no mask, S = 2048, 32 heads 45 -> 46, window of 600 62 -> 68).
+// x 32 142 -> 123, but 8192 x 16 246 -> 252).  Of one length, long rows at D = 64 while there are at most two workgroups per CU (no mask, S = 1500,
+// 32 heads 33.5 -> 29.4, chunks of 640 on 2000 to 3000 cached keys, 2 x 32 heads 69 -> 58, of 1500 on 8000, 32 heads 189 -> 168; but no mask, S = 3000, 32
+// heads 88 -> 95, window of 500, S = 4096, 32 heads 31 -> 36; D = 128, S = 1500, 32 heads 51 -> 53).
 template <uint32_t MASK, bool BOUNDED>
 bool pairs_pay(const FwdArgs& a, int D, unsigned grid) {
     if (a.Bq == 64) return true;
-    if (!line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven || a.kv_len < 2048) return false;
+    const LineShape rows = line_shape<MASK>(a.p, a.q_len, a.kv_len);
+    if (D == 64 && rows.sure >= 1024 && grid <= 2 * 256) return true;
+    if (!rows.uneven || a.kv_len < 2048) return false;
     constexpr bool doc = PartialMask<MASK>::kDoc;
     if (D == 128) return grid <= (doc ? 3 * 256 : 2 * 256);
     return grid <= (doc ? 8 * 256 : 4 * 256) && !(BOUNDED && !doc && a.kv_len >= 8192);

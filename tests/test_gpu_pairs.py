@@ -79,7 +79,8 @@ def test_rows_of_blocks_of_64(mask, score, S, Bk, heads, copies, D):
 @pytest.mark.parametrize("mask,score,D,S,Bk,copies", [
     ("causal", "identity", 64, 2100, 64, 40), ("causal", "softcap", 64, 2176, 128, 56), ("doc_causal", "alibi", 64, 2111, 64, 110),
     ("prefix_lm", "identity", 64, 2050, 64, 45), ("causal", "identity", 128, 2100, 64, 24), ("doc_causal", "alibi", 128, 2060, 128, 40),
-    ("causal", "alibi", 128, 2048, 64, 30), ("causal", "identity", 64, 2047, 64, 60)])
+    ("causal", "alibi", 128, 2048, 64, 30), ("causal", "identity", 64, 2047, 64, 60),
+    ("none", "identity", 64, 1100, 64, 40), ("none", "identity", 64, 1024, 128, 64), ("causal", "softcap", 64, 1025, 64, 50)])
 def test_halves_of_128_row_blocks(mask, score, D, S, Bk, copies):
     wl = wlm.CFG1.scaled(name="pairs128", B=1, Hq=1, Hkv=1, S=S, D=D, Bq=128, Bk=Bk, mask=mask, score=score, window=700,
                          prefix_len=300, softcap=20.0, doc_len_min=100, doc_len_max=700, seed=5200 + S)
