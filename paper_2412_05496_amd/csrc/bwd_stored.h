@@ -99,25 +99,39 @@ struct SliceTrReader {
 // loaded (an empty descriptor fills the slice with zeros) nor multiplied; the dK/dV kernel may not have written
 // them.  (8 x 8 tiles, K = 13, D = 64, 64 heads of 128 x 128 pixels: 336 -> 330 us, Morton order, K = 21: 710 ->
 // 559, where K tiles weigh less against dS.)
-template <int D, int NW, bool CANVAS>
-__global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs a, const float qscale) {
-    constexpr int Bq = NW * 32;
+//
+// HEADS: a workgroup takes the same row of blocks of HEADS query heads that share a KV head and a BlockMask plane, NW waves each:
+// the K tiles, which come from L2 but cost as many loads as dS, serve all of them (relative bias, S =
+// 32768, 2 x 32 / 8 heads: 4680 -> 4080 us, 5 TB/s of dS).
+// ROWS: the same with ROWS neighbouring rows of blocks of one head, whose lists are merged column by column; a tile that one of the
+// rows does not list is a zero for its waves.
+template <int D, int NW, bool CANVAS, int HEADS = 1, int ROWS = 1>
+__global__ __launch_bounds__(NW * 64 * HEADS * ROWS, 2) void bwd_dq_stored_kernel(const BwdArgs a, const float qscale) {
+    constexpr int Bq = NW * 32, THREADS = NW * 64 * HEADS * ROWS;
+    static_assert(ROWS == 1 || (ROWS == 2 && HEADS == 1 && !CANVAS), "one thing at a time");
     constexpr int TILE_K = 64 * D, TILE_S = 64 * Bq, SLICE = 64 * 32;   // bf16 elements
     constexpr int kList = 512;
-    __shared__ __attribute__((aligned(1024))) bf16 smem[2 * TILE_K + NW * 2 * SLICE];   // K(even), K(odd); per wave dS(even), dS(odd)
+    static_assert(ROWS == 1 || THREADS == kList, "a thread per column");
+    __shared__ __attribute__((aligned(1024))) bf16 smem[2 * TILE_K + HEADS * ROWS * NW * 2 * SLICE];   // K(even), K(odd); per wave dS(even), dS(odd)
     __shared__ int s_kv0[kList + 2];                                 // first key of a tile, -1: nothing to add
     __shared__ int s_chunk[kList + 2];                               // where its dS starts (ds_chunk without the rep)
+    __shared__ int s_slot[ROWS > 1 ? ROWS : 1][ROWS > 1 ? kList : 1], s_listed[ROWS > 1 ? ROWS : 1][ROWS > 1 ? kList : 1], s_count[16];   // ROWS: see below
     __shared__ uint8_t s_hid[CANVAS ? kList + 2 : 1];                // CanvasBlocks::hidden_bits of the tile
 
     int unit, rem;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR, unit, rem)) return;
-    const int g = rem % a.G;
+    const int groups = a.G / HEADS;
+    const int row_sets = (a.NR + ROWS - 1) / ROWS;
+    if (!unit_of_workgroup(a.B * a.Hkv, groups * row_sets, unit, rem)) return;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), w = wave & (NW - 1);
+    const int g = (rem % groups) * HEADS + (ROWS > 1 ? 0 : wave / NW);
     const int b = unit / a.Hkv, hkv = unit % a.Hkv, hq = hkv * a.G + g;
     const int64_t plane = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0);
-    const int row = a.kv_order ? min(max(ldc(a.kv_order + plane * a.NR + rem / a.G), 0), a.NR - 1) : a.NR - 1 - rem / a.G;
+    // (ROWS: the last rows first; the last set may have only one)
+    const int first_row = (row_sets - 1 - rem / groups) * ROWS;
+    const int row = ROWS > 1 ? first_row + wave / NW
+                    : a.kv_order ? min(max(ldc(a.kv_order + plane * a.NR + rem / groups), 0), a.NR - 1) : a.NR - 1 - rem / groups;
 
-    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the dS tile's columns are the block's query rows with bits 2 and 3 of the index exchanged (the
     // order in which the dK/dV kernel's registers hold them): lane l32 of wave w owns this row
     const int q_in_block = 32 * w + (l32 & 19) + ((l32 & 4) << 1) + ((l32 & 8) >> 1);
@@ -125,11 +139,11 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
     const bool real_row = q_row < a.q_len;
     bf16* dq_ptr = a.dQ + b * a.dq_sb + hq * a.dq_sh + (int64_t)q_row * a.dq_ss;
 
-    const int64_t line = plane * a.NR + row;
+    const int64_t line = plane * a.NR + (ROWS > 1 ? min(row, a.NR - 1) : row);
     const int n_full = ldc(a.full_kv_num + line), n_part = ldc(a.kv_num + line);
     const int sub_k = a.Bk / 64;
     const int T_all = (n_full + n_part) * sub_k;
-    if (T_all == 0) {
+    if (ROWS == 1 && T_all == 0) {
         if (real_row)
             for (int d0 = half * 8; d0 < D; d0 += 16) *(u32x4*)(dq_ptr + d0) = u32x4{0, 0, 0, 0};
         return;
@@ -142,7 +156,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
 
     const i32x4 k_rsrc = make_rsrc(a.K + b * a.k_sb + hkv * a.k_sh, (uint32_t)((a.kv_len - 1) * a.k_ss + D) * 2u);
     const int k_row_bytes = (int)a.k_ss * 2;
-    const WaveTileLoader<D, NW> k_loader(a.k_ss, w, lane);
+    const WaveTileLoader<D, NW * HEADS * ROWS> k_loader(a.k_ss, wave, lane);
     // slice position (key, 8 columns) <- where the dK/dV kernel put those 8 values: chunk c = columns
     // 16 c .., lane 32 h + key % 32 of the wave that had keys 32 kb ..
     int32_t s_voff[4];
@@ -151,7 +165,7 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
         const int pos = i * 64 + lane, key = pos >> 2, pc = pos & 3;
         s_voff[i] = (key >> 5) * 2048 + (pc >> 1) * 1024 + (32 * (pc & 1) + (key & 31)) * 16;
     }
-    const uint32_t k_lds = lds_addr(smem), s_lds = k_lds + 2 * TILE_K * 2 + w * (2 * SLICE * 2);
+    const uint32_t k_lds = lds_addr(smem), s_lds = k_lds + 2 * TILE_K * 2 + wave * (2 * SLICE * 2);
     const TrReader<D> tr_k(lane, k_lds);
     const SliceTrReader tr_s(lane, s_lds);
 
@@ -161,9 +175,47 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
 #pragma unroll
         for (int r = 0; r < 16; ++r) dq[db][r] = 0.0f;
 
-    for (int seg0 = 0; seg0 < T_all; seg0 += kList) {
-        const int T = min(kList, T_all - seg0);
-        for (int i = tid; i < T; i += NW * 64) {
+    const int seg_end = ROWS > 1 ? a.NC : T_all;        // ROWS: a segment is kList columns
+    for (int seg0 = 0; seg0 < seg_end; seg0 += kList) {
+        int T = min(kList, T_all - seg0);
+        if constexpr (ROWS > 1) {
+            // every row enters the slots of its blocks under their columns; the columns that any row lists move together
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) s_slot[r][tid] = -1;
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                if (first_row + r >= a.NR) break;
+                const int64_t l = plane * a.NR + first_row + r;
+                const int nf = ldc(a.full_kv_num + l), n = nf + ldc(a.kv_num + l);
+                for (int i = tid; i < n; i += THREADS) {
+                    const int c = min(max(i < nf ? a.full_kv_idx[l * a.NC + i] : a.kv_idx[l * a.NC + i - nf], 0), a.NC - 1);
+                    if ((unsigned)(c - seg0) < (unsigned)kList)
+                        s_slot[r][c - seg0] = (int)min(max((int64_t)a.ds_grid[l * a.NC + c], (int64_t)0), a.ds_blocks - 1);
+                }
+            }
+            __syncthreads();
+            bool listed = false;
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) listed = listed || s_slot[r][tid] >= 0;
+            const uint64_t mine = __ballot(listed);
+            if (lane == 0) s_count[wave] = __popcll(mine);
+            __syncthreads();
+            int at = __popcll(mine & ((1ull << lane) - 1)), total = 0;
+#pragma unroll
+            for (int v = 0; v < THREADS / 64; ++v) {
+                const int n = s_count[v];
+                at += v < wave ? n : 0;
+                total += n;
+            }
+            if (listed) {
+                s_kv0[at] = (seg0 + tid) * a.Bk;
+#pragma unroll
+                for (int r = 0; r < ROWS; ++r) s_listed[r][at] = s_slot[r][tid];
+            }
+            T = __builtin_amdgcn_readfirstlane(total) * sub_k;
+        }
+        for (int i = ROWS > 1 ? T : tid; i < T; i += THREADS) {
             const int t = seg0 + i, pos = t / sub_k, st = t - pos * sub_k;
             const int c = min(max(pos < n_full ? full_idx[pos] : part_idx[pos - n_full], 0), a.NC - 1);
             const int kv0 = c * a.Bk + st * 64;
@@ -180,9 +232,21 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
         }
         __syncthreads();
 
+        if (ROWS > 1 && T == 0) continue;               // (the same for all; the next segment's first barrier is behind s_slot's writes)
+        // first key of tile i, or -1; and where its dS starts, or -1
+        auto kv0_of = [&](int i) __attribute__((always_inline)) {
+            if constexpr (ROWS == 1) return __builtin_amdgcn_readfirstlane(s_kv0[i]);
+            const int st = sub_k == 2 ? i & 1 : 0, kv0 = __builtin_amdgcn_readfirstlane(s_kv0[sub_k == 2 ? i >> 1 : i]) + 64 * st;
+            return kv0 < a.kv_len ? kv0 : -1;
+        };
+        auto chunk_of = [&](int i) __attribute__((always_inline)) {
+            if constexpr (ROWS == 1) return __builtin_amdgcn_readfirstlane(s_chunk[i]);
+            const int slot = __builtin_amdgcn_readfirstlane(s_listed[wave / NW & (ROWS - 1)][sub_k == 2 ? i >> 1 : i]);
+            return slot < 0 ? -1 : slot * sub_k + (sub_k == 2 ? i & 1 : 0);
+        };
         auto load_k = [&](int i, auto buf_tag) {
             constexpr int BUF = decltype(buf_tag)::value;
-            const int kv0 = max(__builtin_amdgcn_readfirstlane(s_kv0[i]), 0);
+            const int kv0 = max(kv0_of(i), 0);
             k_loader.start(k_rsrc, k_lds + BUF * (TILE_K * 2), kv0 * k_row_bytes);
         };
         auto hidden_of = [&](int i) -> uint32_t {
@@ -192,13 +256,12 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
         // a tile with nothing to add is loaded through an empty descriptor, which fills the slice with zeros
         auto load_s = [&](int i, auto buf_tag) {
             constexpr int BUF = decltype(buf_tag)::value;
-            const int kv0 = __builtin_amdgcn_readfirstlane(s_kv0[i]);
-            const int chunk = __builtin_amdgcn_readfirstlane(s_chunk[i]);
+            const int kv0 = kv0_of(i), chunk = chunk_of(i);
             const uint32_t hid = hidden_of(i);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {       // (j >> 1: which 32 keys)
-                const bool there = kv0 >= 0 && !(hid & (1u << (j >> 1)));
-                const i32x4 rsrc = make_rsrc(ds_head + (int64_t)chunk * TILE_S, there ? (uint32_t)SLICE * 2u : 0u);
+                const bool there = kv0 >= 0 && (ROWS == 1 || chunk >= 0) && !(hid & (1u << (j >> 1)));
+                const i32x4 rsrc = make_rsrc(ds_head + (int64_t)(ROWS == 1 ? chunk : max(chunk, 0)) * TILE_S, there ? (uint32_t)SLICE * 2u : 0u);
                 dma_x1_nt(rsrc, s_lds + BUF * (SLICE * 2) + j * 1024, s_voff[j], 0);
             }
         };
@@ -268,9 +331,20 @@ __global__ __launch_bounds__(NW * 64, 2) void bwd_dq_stored_kernel(const BwdArgs
         }
 }
 
+enum class StoredShare { kNone, kHeads, kRows };     // (stored_share; D = 128, Bq = 128)
 template <bool CANVAS>
-int launch_bwd_stored_dq(const BwdArgs& a, int D, float qscale, hipStream_t st) {
+int launch_bwd_stored_dq(const BwdArgs& a, int D, float qscale, StoredShare share, hipStream_t st) {
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
+    if constexpr (!CANVAS) {
+        if (share == StoredShare::kHeads) {         // (an even number of heads to a group, one plane for all)
+            hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 4, false, 2>), dim3(unit_grid(a.B * a.Hkv, a.G / 2 * a.NR)), dim3(512), 0, st, a, qscale);
+            return FLEXATTN_OK;
+        }
+        if (share == StoredShare::kRows) {
+            hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 4, false, 1, 2>), dim3(unit_grid(a.B * a.Hkv, a.G * ((a.NR + 1) / 2))), dim3(512), 0, st, a, qscale);
+            return FLEXATTN_OK;
+        }
+    }
     if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 4, CANVAS>), dim3(grid_q), dim3(256), 0, st, a, qscale);
     else if (D == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 2, CANVAS>), dim3(grid_q), dim3(128), 0, st, a, qscale);
     else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_stored_kernel<64, 4, CANVAS>), dim3(grid_q), dim3(256), 0, st, a, qscale);

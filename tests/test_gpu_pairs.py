@@ -85,3 +85,38 @@ def test_halves_of_128_row_blocks(mask, score, D, S, Bk, copies):
     wl = wlm.CFG1.scaled(name="pairs128", B=1, Hq=1, Hkv=1, S=S, D=D, Bq=128, Bk=Bk, mask=mask, score=score, window=700,
                          prefix_len=300, softcap=20.0, doc_len_min=100, doc_len_max=700, seed=5200 + S)
     check(wl, copies)
+
+
+@pytest.mark.parametrize("mask,score,S,Hq,Hkv,Bk,B", [
+    ("causal", "softcap", 4100, 2, 1, 64, 8), ("swa_causal", "softcap", 4480, 4, 2, 64, 4),    # two heads to a workgroup
+    ("causal", "softcap", 4100, 3, 3, 64, 11), ("none", "identity", 4001, 3, 1, 128, 11),       # two rows of blocks (33, 32 of them)
+    ("prefix_lm", "identity", 4160, 1, 1, 64, 32)])
+def test_stored_dq_that_shares_k_tiles(mask, score, S, Hq, Hkv, Bk, B):
+    """dQ through memory is the recomputed one up to the order of its fp32 sums: one bf16 rounding of each, 2^-8 of the larger
+    values.  The workspace starts as NaN patterns, dS of blocks that a row does not list is not read."""
+    import paper_2412_05496_amd as fa
+    dev = torch.device(DEV)
+    gen = torch.Generator(device=dev).manual_seed(S + Hq)
+    Q, dO = (torch.randn(B, Hq, S, 128, generator=gen, device=dev).to(torch.bfloat16) for _ in range(2))
+    K, V = (torch.randn(B, Hkv, S, 128, generator=gen, device=dev).to(torch.bfloat16) for _ in range(2))
+    params = fa.ModParams(softcap=30.0, window=4200, prefix_len=500)
+    mask_id = {"causal": fa.MASK_CAUSAL, "none": fa.MASK_NONE, "swa_causal": fa.MASK_SWA_CAUSAL, "prefix_lm": fa.MASK_PREFIX_LM}[mask]
+    score_id = fa.SCORE_SOFTCAP if score == "softcap" else fa.SCORE_IDENTITY
+    print(f"[case] {mask} {score} S={S} heads={Hq}/{Hkv} Bk={Bk} B={B}", flush=True)
+    bm = fa.alloc_blockmask(1, 1, S, S, 128, Bk, device=dev)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    O, LSE = torch.empty_like(Q), torch.empty(B, Hq, S, dtype=torch.float32, device=dev)
+    head = (score_id, mask_id, params, bm, 128 ** -0.5)
+    fa.flexattn_forward(Q, K, V, *head, O, LSE)
+    want = [torch.empty_like(t) for t in (Q, K, V)]
+    fa.flexattn_backward(Q, K, V, O, dO, LSE, *head, *want)
+    n = hp.nonempty_blocks(bm)
+    ws = hp.dirty_stored_workspace(Q, K, bm, n)
+    got = [torch.full_like(t, float("nan")) for t in (Q, K, V)]
+    fa.flexattn_backward_stored(Q, K, V, O, dO, LSE, *head, *got, n, ws)
+    torch.cuda.synchronize()
+    assert hp.ds_written(ws, bm, n)
+    assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+    err = (got[0].float() - want[0].float()).abs()
+    assert torch.isfinite(got[0].float()).all() and err.max() <= 2 ** -7 * want[0].float().abs().max()
+    assert err.mean() <= 2 ** -9 * want[0].float().abs().mean()
