@@ -526,7 +526,8 @@ int dq_split_waves(const BwdArgs& a, int D) {
 // 32 heads 931 -> 885, S = 512 45 -> 48, documents, S = 16384, 16 heads 414 -> 373; Bq = 128, S x heads, D = 64, causal, 8192 x 16 532 -> 506, 2048 x 32
 // 104 -> 99, 16384 x 16 1952 -> 1905, 8192 x 32 1010 -> 1013, but 1024 x 256 188 -> 193, documents, 8192 x 8 131 -> 110, 16384 x 16 403 -> 392, but 8192 x 64 828
 // -> 844, D = 128, causal, 4096 x 16 294 -> 262, but 8192 x 16 909 -> 918, documents, 8192 x 8 184 -> 158, 8192 x 16 304 -> 301, but 16384 x 16 705 -> 736;
-// rows of one length, D = 64, no mask, 1500 x 32 89 -> 84, but 3000 x 32 267 -> 274.
+// rows of one length, D = 64, no mask, 1500 x 32 89 -> 84, but 3000 x 32 267 -> 274; documents of 16 to 100, 8192 x 16, which the host cannot tell from
+// longer ones, D = 64 68 -> 72, D = 128 109 -> 119.
 template <uint32_t MASK>
 bool dq_pairs_pay(const BwdArgs& a, int D) {
     const LineShape rows = line_shape<MASK>(a.p, a.q_len, a.kv_len);

@@ -173,6 +173,9 @@ int split_waves(const FwdArgs& a, int D) {
 // x 32 142 -> 123, but 8192 x 16 246 -> 252).  Of one length, long rows at D = 64 while there are at most two workgroups per CU (no mask, S = 1500,
 // 32 heads 33.5 -> 29.4, chunks of 640 on 2000 to 3000 cached keys, 2 x 32 heads 69 -> 58, of 1500 on 8000, 32 heads 189 -> 168; but no mask, S = 3000, 32
 // heads 88 -> 95, window of 500, S = 4096, 32 heads 31 -> 36; D = 128, S = 1500, 32 heads 51 -> 53).
+// Documents of a few tokens, which the host cannot tell from long ones, pay for the halves' starts (Bq = 128, 8192 x 16, of 16 to 100 D = 64
+// 20.0 -> 23.3, D = 128 36.6 -> 37.5, of 100 to 400 25.8 -> 25.0, 41.0 -> 40.9); a workgroup that takes such a row whole while the other
+// half's ends at once is slower yet (27.7: it waits for its place and its counts like any other).
 template <uint32_t MASK, bool BOUNDED>
 bool pairs_pay(const FwdArgs& a, int D, unsigned grid) {
     if (a.Bq == 64) return true;
