@@ -69,7 +69,8 @@ constexpr int kTileKV = 64;   // keys per kernel tile
 // maximum (287 -> 299); and, where neither a window, documents nor a canvas ends rows early, long rows on a chip that is not full and
 // soft-caps whose maximum has to be tracked (plain_pays; causal, S = 4096, 32 heads 132 <- 110, S = 8192, 16 heads 208 <- 196,
 // S = 4096, 64 heads 190 <- 200; cap of 100, S = 2048, 32 heads 64.6 <- 60.6, S = 8192, 64 heads 924 <- 904, S = 1024, 256 heads
-// 92.3 <- 94.7: plain <- pipelined).  Neighborhood masks gain most: 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (490 ->
+// 92.3 <- 94.7: plain <- pipelined), but rows of one length whose workgroups are the four per CU that
+// run at once (no mask, S = 4096, 32 heads 150 <- 154, S = 16384, 8 heads 574 <- 589, but 40 heads 189 <- 187, S = 8192, 10 heads 213 <- 208).  Neighborhood masks gain most: 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (490 ->
 // 340 at 128 x 128 pixels).
 template <int D, int NW, bool BOUNDED>
 constexpr bool fwd_plain() {
@@ -77,9 +78,9 @@ constexpr bool fwd_plain() {
 }
 
 template <uint32_t SCORE>
-bool plain_pays(int kv_len, unsigned grid) {
+bool plain_pays(int kv_len, unsigned grid, bool uneven) {
     if (SCORE & FLEXATTN_SCORE_SOFTCAP) return kv_len < 2048;
-    return kv_len < 4096 || grid >= 6 * 256;
+    return kv_len < 4096 || grid >= 6 * 256 || (!uneven && grid > 3 * 256 && grid <= 4 * 256);
 }
 
 // The same at D = 128, where 64-key tiles of K and V leave LDS for two workgroups: units of 32 keys in a ring of
@@ -941,7 +942,7 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
     if (D == 64 && Bq == 128) {
         constexpr bool dense = !mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
         if constexpr (fwd_plain<64, 4, BOUNDED>() && dense) {
-            if (!plain_pays<SCORE>(a.kv_len, grid)) {
+            if (!plain_pays<SCORE>(a.kv_len, grid, line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven)) {
                 hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false>), dim3(grid), dim3(256), 0, st, a);
                 return FLEXATTN_OK;
             }
