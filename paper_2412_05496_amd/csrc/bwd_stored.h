@@ -104,7 +104,7 @@ struct SliceTrReader {
 // the K tiles, which come from L2 but cost as many loads as dS, serve all of them (relative bias, S =
 // 32768, 2 x 32 / 8 heads: 4680 -> 4080 us, 5 TB/s of dS).
 // ROWS: the same with ROWS neighbouring rows of blocks of one head, whose lists are merged column by column; a tile that one of the
-// rows does not list is a zero for its waves.
+// rows does not list is left out by its waves (a zero times a K that is not finite would be NaN).
 template <int D, int NW, bool CANVAS, int HEADS = 1, int ROWS = 1>
 __global__ __launch_bounds__(NW * 64 * HEADS * ROWS, 2) void bwd_dq_stored_kernel(const BwdArgs a, const float qscale) {
     constexpr int Bq = NW * 32, THREADS = NW * 64 * HEADS * ROWS;
@@ -253,11 +253,13 @@ __global__ __launch_bounds__(NW * 64 * HEADS * ROWS, 2) void bwd_dq_stored_kerne
             if constexpr (!CANVAS) return 0u;
             else return ((uint32_t)__builtin_amdgcn_readfirstlane((int)s_hid[i]) >> (2 * w)) & 3u;
         };
+        bool listed_of[2] = {true, true};       // ROWS: whether this wave's row lists the tile of the slot
         // a tile with nothing to add is loaded through an empty descriptor, which fills the slice with zeros
         auto load_s = [&](int i, auto buf_tag) {
             constexpr int BUF = decltype(buf_tag)::value;
             const int kv0 = kv0_of(i), chunk = chunk_of(i);
             const uint32_t hid = hidden_of(i);
+            if constexpr (ROWS > 1) listed_of[BUF] = chunk >= 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {       // (j >> 1: which 32 keys)
                 const bool there = kv0 >= 0 && (ROWS == 1 || chunk >= 0) && !(hid & (1u << (j >> 1)));
@@ -279,6 +281,11 @@ __global__ __launch_bounds__(NW * 64 * HEADS * ROWS, 2) void bwd_dq_stored_kerne
             else wait_vmem();
             __syncthreads();
             constexpr uint32_t kt = BUF * (TILE_K * 2), stl = BUF * (SLICE * 2);
+            if (ROWS > 1 && !listed_of[BUF]) {          // (wave-uniform; the barriers and the other tiles' loads stay)
+                if (t + 1 < T) load_k(t + 1, nxt);
+                if (t + 2 < T) load_s(t + 2, buf_tag);
+                return;
+            }
             bf16x8 bfr[4];
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) bfr[ks] = tr_s.read(stl, 16 * ks);
