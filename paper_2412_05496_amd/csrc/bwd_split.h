@@ -531,8 +531,8 @@ int dq_split_waves(const BwdArgs& a, int D) {
 template <uint32_t MASK>
 bool dq_pairs_pay(const BwdArgs& a, int D) {
     const LineShape rows = line_shape<MASK>(a.p, a.q_len, a.kv_len);
-    if (a.Bq == 64) return rows.longest >= (D == 64 ? 768 : 448);
     const unsigned grid = unit_grid(a.B * a.Hkv, a.G * a.NR);
+    if (a.Bq == 64) return rows.longest >= (D == 64 ? 768 : 448) && grid <= kMaxLaunch;
     if (D == 64 && rows.sure >= 1024 && grid <= 2 * 256) return true;
     if (!rows.uneven || a.kv_len < 2048) return false;
     return grid <= (D == 64 ? 8 * 256 : PartialMask<MASK>::kDoc ? 4 * 256 : 2 * 256);
@@ -680,7 +680,7 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
             else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);
             // (us, two waves -> pairs, ALiBi, causal: D = 64 / 128, S = 8192, 16 heads 276 -> 237 / 435 -> 321, S = 700, 256 heads 59 -> 52 / 100
             // -> 85, S = 1000, 4 heads 26 -> 17 / 32 -> 21, but S = 300, 1024 heads 71 -> 76 / 141 -> 143; documents, S = 8192, 16 heads 121 -> 85 / 178 -> 121)
-            else if (const bool pairs = line_shape<MASK>(a.p, a.q_len, a.kv_len).longest >= 448; D == 128) {
+            else if (const bool pairs = line_shape<MASK>(a.p, a.q_len, a.kv_len).longest >= 448 && grid_q <= kMaxLaunch; D == 128) {
                 if (pairs) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, true, true, true>), dim3(grid_q), dim3(256), 0, st, a);
                 else hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE, true>), dim3(grid_q), dim3(128), 0, st, a);
             } else if (pairs) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, true, true, true>), dim3(grid_q), dim3(256), 0, st, a);

@@ -231,9 +231,9 @@ struct NoCanvas {
 // us, that -> this, causal: S = 16384, D = 128, 1 head, forward 472 -> 289, dK/dV 832 -> 269, dQ 574 -> 326; 3 heads, D = 64,
 // 309 -> 213, 537 -> 262, 371 -> 238; S = 8192, D = 128, 16 query and 2 KV heads 874 -> 285, 1855 -> 1074, 1064 -> 369; S = 4096, 9
 // heads, D = 64, 76 -> 54, 82 -> 61, 83 -> 61, D = 128, 105 -> 80, 130 -> 93, 130 -> 92; 8 and 16 heads the same within 2 %.)
-__device__ __forceinline__ bool unit_of_workgroup(int units, int per_unit, int& unit, int& rank) {
-    const int xcd = blockIdx.x & 7, rest = units & 7, rest_pieces = rest * ((per_unit + 7) >> 3);
-    const int k = blockIdx.x >> 3;
+__device__ __forceinline__ bool unit_of_workgroup(unsigned id, int units, int per_unit, int& unit, int& rank) {
+    const int xcd = id & 7, rest = units & 7, rest_pieces = rest * ((per_unit + 7) >> 3);
+    const int k = id >> 3;
     if (k >= rest_pieces) {
         const int u = (k - rest_pieces) / per_unit;
         unit = u * 8 + xcd;
@@ -245,9 +245,15 @@ __device__ __forceinline__ bool unit_of_workgroup(int units, int per_unit, int& 
     rank = 8 * round + (eighth & 7);
     return rank < per_unit;
 }
+__device__ __forceinline__ bool unit_of_workgroup(int units, int per_unit, int& unit, int& rank) {
+    return unit_of_workgroup(blockIdx.x, units, per_unit, unit, rank);
+}
 inline unsigned unit_grid(int units, int per_unit) {
     return 8u * ((unsigned)(units >> 3) * (unsigned)per_unit + (unsigned)(units & 7) * (unsigned)((per_unit + 7) / 8));
 }
+// A launch counts its work items in 32 bits: 2^24 workgroups of 256 are too many (some are then left out, without an error).
+// What may need more takes several launches of at most this many.
+constexpr unsigned kMaxLaunch = 1u << 23;
 
 // Offset conversion for inference (section 5.2): the position the mods see for query row 0 of
 // batch entry b.

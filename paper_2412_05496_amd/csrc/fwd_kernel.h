@@ -56,6 +56,7 @@ struct FwdArgs {
     int64_t page_stride;
     int n_pool_pages;
     int Bq;                // rows of a BlockMask block
+    unsigned first_id;     // PAIRS: of the launch's workgroups, where there are several launches (kMaxLaunch)
 };
 
 constexpr int kTileKV = 64;   // keys per kernel tile
@@ -229,7 +230,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     // ---- workgroup -> (b, hkv, g, row of blocks).  Rows are taken longest first (the BlockMask's work order), or
     // last-first without one (causal-like masks: longest first).
     int unit, rem, slice = 0;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (SPLIT ? Bq / 32 : PAIRS ? Bq / 64 : 1), unit, rem)) return;
+    if (!unit_of_workgroup(blockIdx.x + (PAIRS ? a.first_id : 0u), a.B * a.Hkv, a.G * a.NR * (SPLIT ? Bq / 32 : PAIRS ? Bq / 64 : 1), unit, rem)) return;
     if constexpr (SPLIT) {
         slice = rem & (Bq / 32 - 1);                // which 32 rows of the block
         rem >>= Bq == 128 ? 2 : 1;
@@ -922,9 +923,13 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
         return FLEXATTN_OK;
     }
     if (pairs_pay<MASK, BOUNDED>(a, D, grid)) {
-        const dim3 halves(unit_grid(a.B * a.Hkv, a.G * a.NR * (Bq / 64)));
-        if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), halves, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), halves, dim3(256), 0, st, a);
+        const unsigned halves = unit_grid(a.B * a.Hkv, a.G * a.NR * (Bq / 64));
+        FwdArgs part = a;
+        for (part.first_id = 0; part.first_id < halves; part.first_id += kMaxLaunch) {
+            const dim3 ids(min(halves - part.first_id, kMaxLaunch));
+            if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, part);
+            else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, part);
+        }
         return FLEXATTN_OK;
     }
 #define FLEXATTN_LAUNCH(DD, NW)                                                                            \
