@@ -514,6 +514,7 @@ struct PartialMask {
     }
     // The lane's key has these key_corners(), its elements are the queries whose query_block_tag() is in `tags`.
     __device__ __forceinline__ Bits match_queries(const uint32_t* tags, u32x2 corners, int half) const {
+        static_assert(T0 == FLEXATTN_M_NEIGHBORHOOD && T1 == 0, "a canvas with another predicate: dK/dV asks the pixels alone");
         Bits bits = {0u, ~0u};
         if (query_way != kTagged32) {
             const uint32_t xm = (1u << (y_shift - 1)) - 1u;
@@ -869,7 +870,8 @@ inline int check_canvas(uint32_t mask_id, const flexattn_mod_params* p, int q_le
 // and benchmark variants, and three compositions of them (sliding window with a soft-cap; nested
 // score_mods: ALiBi then soft-cap, relative bias then soft-cap under a document mask).  The functors
 // compose freely -- another pair is one more line here (and in the launcher lists that
-// FLEXATTN_VARIANT_INDICES drives), nothing else.
+// FLEXATTN_VARIANT_INDICES drives), nothing else -- but for a canvas with another predicate, for which dK/dV would have to
+// ask key_bits again (PartialMask::match_queries does not compile for it).
 // X(mask_id, score_id)
 #define FLEXATTN_FOR_EACH_VARIANT(X)                                                    \
     X(FLEXATTN_MASK_NONE, FLEXATTN_SCORE_IDENTITY)                                      \

@@ -1,0 +1,31 @@
+"""What dK/dV leaves out of a mask must not be asked for by it: for a canvas it works out which pixels match and nothing else, so that
+a composition of a canvas with another predicate has to be refused by the compiler.  (Front end only, no code is made.)"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2412_05496_amd import build
+
+SOURCE = """
+#include "flex_common.h"
+using namespace flexattn;
+__global__ void kernel(const flexattn_mod_params p, const uint32_t* tags, uint32_t* out) {
+    const PartialMask<TESTED_MASK> mask(p, 0, 64);
+    out[0] = mask.match_queries(tags, mask.key_corners(0), 0).plain;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which(build.HIPCC) is None, reason="no hipcc")
+@pytest.mark.parametrize("mask,accepted", [
+    ("FLEXATTN_M_NEIGHBORHOOD", True), ("FLEXATTN_M_NEIGHBORHOOD | FLEXATTN_M_CAUSAL", False),
+    ("FLEXATTN_M_NEIGHBORHOOD | (FLEXATTN_M_PREFIX << 8)", False)])
+def test_canvas_with_another_predicate(mask, accepted, tmp_path):
+    src = os.path.join(tmp_path, "mask.hip")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    r = subprocess.run([build.HIPCC, *build.FLAGS, f"-DTESTED_MASK=({mask})", "--cuda-device-only", "-fsyntax-only", src], capture_output=True, text=True, timeout=300)
+    assert (r.returncode == 0) == accepted, r.stderr
+    assert accepted or "a canvas with another predicate" in r.stderr
