@@ -533,7 +533,7 @@ bool dq_pairs_pay(const BwdArgs& a, int D) {
     const LineShape rows = line_shape<MASK>(a.p, a.q_len, a.kv_len);
     const unsigned grid = unit_grid(a.B * a.Hkv, a.G * a.NR);
     if (a.Bq == 64) return rows.longest >= (D == 64 ? 768 : 448) && grid <= kMaxLaunch;
-    if (D == 64 && rows.sure >= 1024 && grid <= 2 * 256) return true;
+    if (D == 64 && rows.sure >= 1024 && 2 * grid <= (rows.uneven ? 4 : 3) * 256) return true;
     if (!rows.uneven || a.kv_len < 2048) return false;
     return grid <= (D == 64 ? 8 * 256 : PartialMask<MASK>::kDoc ? 4 * 256 : 2 * 256);
 }
