@@ -545,8 +545,12 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                             asm volatile("" ::: "memory");   // keep this a (scalar, rarely taken) branch
                             // (a masked P makes dS vanish with it.  Rows past q_len hold zeros in Q and dO: whatever
                             // the mask says there adds nothing)
+                            if constexpr (Mask::kCanvas) {
+                                mask.keep_queries(bits, &s_tag[SLOT][32 * x], c4, half, pe);
+                            } else {
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i), pe[i]);
+                                for (int i = 0; i < 4; ++i) pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i), pe[i]);
+                            }
                         }
 #pragma unroll
                         for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];
@@ -956,9 +960,12 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
                 asm volatile("" ::: "memory");   // keep this a branch
                 typename Mask::Bits bits = mask.row_bits(q_pos, kvs_blk + 4 * half);
                 if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[BUF][block * 32], q_tag, l32, half, scattered);
-                if constexpr (Mask::kCanvas) mask.match_keys(bits, &s_tag[BUF][block * 32], q_tag, half);
+                if constexpr (Mask::kCanvas) {
+                    mask.template mask_keys<false>(bits, &s_tag[BUF][block * 32], q_tag, half, [&](int r, uint32_t m) __attribute__((always_inline)) { dpacc[r] = keep_or_zero(m, dpacc[r]); });
+                } else {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) dpacc[r] = keep_or_zero(Mask::keep(bits, r), dpacc[r]);
+                    for (int r = 0; r < 16; ++r) dpacc[r] = keep_or_zero(Mask::keep(bits, r), dpacc[r]);
+                }
             }
             if constexpr (CAPTURED) {
                 const int kvs = kvs_blk;

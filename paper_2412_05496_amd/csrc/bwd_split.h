@@ -216,9 +216,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(
             asm volatile("" ::: "memory");          // keep this a branch
             typename Mask::Bits bits = mask.row_bits(q_pos, kv_now + 4 * half);
             if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[w][0], q_tag, l32, half, scattered);
-            if constexpr (Mask::kCanvas) mask.match_keys(bits, &s_tag[w][0], q_tag, half);
+            if constexpr (Mask::kCanvas) {
+                mask.template mask_keys<false>(bits, &s_tag[w][0], q_tag, half, [&](int r, uint32_t m) __attribute__((always_inline)) { dpacc[r] = keep_or_zero(m, dpacc[r]); });
+            } else {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) dpacc[r] = keep_or_zero(Mask::keep(bits, r), dpacc[r]);
+                for (int r = 0; r < 16; ++r) dpacc[r] = keep_or_zero(Mask::keep(bits, r), dpacc[r]);
+            }
         }
         if (more && partial) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (the tags have been read)
@@ -443,8 +446,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
                 else smod.template p_with_grad4<false>(sv, dqk, rcv, gr, pe);
                 if (masked) {
                     asm volatile("" ::: "memory");   // keep this a branch
+                    if constexpr (Mask::kCanvas) {
+                        mask.keep_queries(bits, &s_tag[w][SLOT][0], c4, half, pe);
+                    } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i), pe[i]);
+                        for (int i = 0; i < 4; ++i) pe[i] = keep_or_zero(Mask::keep(bits, 4 * c4 + i), pe[i]);
+                    }
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) ds[i] = pe[i] * gr[i] * dpacc[4 * c4 + i];

@@ -272,14 +272,14 @@ __device__ __forceinline__ int q_offset_of(const flexattn_mod_params& p, int b) 
 // the canvas -- is a 32-bit tag, the other side's in an LDS table of the tile.  Equal document ids become
 // bits as well, by one ballot per distinct id of the 32 tokens (one or two in packed documents).  The pixels that
 // match a lane's are a rectangle, of which 32 consecutive tokens hold a piece that is worked out line by line
-// (tokens_inside; the tags of the block's first token say where it lies).
+// (tokens_inside; the tags of the block's first token say where it lies), or, in kernels of their own for canvases that cut 32
+// tokens into many pieces (canvas_by_tags), compared per element.
 // (Evaluating the mask element by element instead -- the canvas decode of every key, a lane exchange or a
 // table read per document id -- made PARTIAL blocks several times as expensive as FULL ones: neighborhood
 // attention on 128 x 128 pixels, K = 13, D = 64, B = 4, H = 16: forward 0.98 ms, dK/dV 1.60 ms before, 0.42
 // and 0.67 since; the forward 0.34 where it also leaves out the blocks CanvasBlocks finds hidden.  Pixels as rectangles instead
-// of six instructions a score, B = 4, H = 16, us forward / backward: 128 x 128, K = 13, tiles of 8 x 8 287 -> 272 / 818 -> 814, row-major 546 ->
-// 483 / 1687 -> 1631; 64 x 64, K = 21, Morton order 135 -> 118 / 357 -> 348; 15 x 40, K = 7, row-major 29.1 -> 29.0 / 83.6 -> 84.7; but tiles of 4 x 4,
-// 64 x 64, K = 9 54.3 -> 53.9 / 179 -> 190.)
+// of six instructions a score, B = 4, H = 16, us forward / backward: 128 x 128, K = 13, tiles of 8 x 8 282 -> 252 / 841 -> 807, row-major, 64 x 64,
+// K = 9 78 -> 68 / 223 -> 215; 64 x 64, K = 9, Morton order 57 -> 53 / 181 -> 175, tiles of 16 x 16 72 -> 63 / 200 -> 189.)
 // ---------------------------------------------------------------------------------------
 
 // Position of element r of a lane's 16 (without the 4 * half that goes into the base).
@@ -297,12 +297,23 @@ __device__ __forceinline__ uint32_t bit_mask(uint32_t bits, int pos) {
     return (uint32_t)__builtin_amdgcn_sbfe((int)bits, (uint32_t)pos, 1u);
 }
 
+// v where m is all-ones, 0 (or -inf) where it is 0
+__device__ __forceinline__ float keep_or_zero(uint32_t m, float v) {
+    return __builtin_bit_cast(float, m & __builtin_bit_cast(uint32_t, v));
+}
+__device__ __forceinline__ float keep_or_neg_inf(uint32_t m, float v) {
+    return __builtin_bit_cast(float, (m & __builtin_bit_cast(uint32_t, v)) | (~m & 0xff800000u));
+}
+
+// A canvas whose matching pixels are compared token by token (canvas_by_tags); not accepted from callers.
+constexpr uint32_t kCanvasByTags = 0x40u;
+
 template <uint32_t MASK>
 struct PartialMask {
     static constexpr uint32_t T0 = MASK & 0xffu, T1 = (MASK >> 8) & 0xffu, PRIMS = T0 | T1;
     static constexpr uint32_t kTagged = FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD;
     static constexpr bool kDoc = (PRIMS & FLEXATTN_M_DOCUMENT) != 0, kCanvas = (PRIMS & FLEXATTN_M_NEIGHBORHOOD) != 0;
-    static constexpr bool kTags = kDoc || kCanvas;
+    static constexpr bool kTags = kDoc || kCanvas, kByTags = kCanvas && (PRIMS & kCanvasByTags) != 0;
     static constexpr int kMaxIds = 9;
     static_assert(!(kDoc && kCanvas), "one tag per token: documents or pixels");
 
@@ -312,10 +323,10 @@ struct PartialMask {
     // guard bits set iff x >= x0 and y >= y0, and span + 2 guard - a iff x <= x0 + span and y <= y0 + span.
     uint32_t guard, far;
     int y_shift;
-    // How 32 consecutive tokens lie on the canvas: each line of it a run of its own (kLines, row-major), lines of 2^line_log2
-    // pixels below each other (kRows, tiles of 4 x 4 and more), 8 x 4 in Z order (kZ); or as their tags say (kTagged32).
-    enum Way { kTagged32, kLines, kRows, kZ };
-    int way, query_way, line_log2;      // of keys (whose blocks start at a multiple of 32); of queries, which offsets may move
+    // How 32 consecutive tokens, the first at a multiple of 32, lie on the canvas: each line of it a run of its own (kLines, row-major),
+    // lines of 2^line_log2 pixels below each other (kRows, tiles of 8 x 8 and more), or 8 x 4 in Z order (kZ).
+    enum Way { kLines, kRows, kZ };
+    int way, line_log2;
     std::conditional_t<kCanvas, CanvasOrder, NoCanvas> canvas;
     int na_r, na_w, na_h;
 
@@ -326,7 +337,7 @@ struct PartialMask {
         kv_last = kv_len - 1;
         guard = far = 0;
         y_shift = na_r = na_w = na_h = line_log2 = 0;
-        way = query_way = kTagged32;
+        way = kLines;
         if constexpr (kCanvas) {
             na_w = p.na_width;
             na_h = p.na_height;
@@ -335,11 +346,8 @@ struct PartialMask {
             y_shift = xb + 1;
             guard = (1u << xb) | (1u << (y_shift + yb));
             far = (uint32_t)(2 * na_r) * (1u | (1u << y_shift)) + 2u * guard;
-            // (tiles of 2 x 2 cut 32 tokens into too many pieces: a compare a token is cheaper)
             line_log2 = min(canvas.tile_log2, 5);
-            way = p.na_layout == FLEXATTN_NA_MORTON ? (na_w >= 8 ? kZ : kTagged32)
-                  : p.na_layout == FLEXATTN_NA_TILED && line_log2 > 0 ? (line_log2 >= 2 ? kRows : kTagged32) : kLines;
-            query_way = p.q_offsets ? kTagged32 : way;
+            way = p.na_layout == FLEXATTN_NA_MORTON ? kZ : p.na_layout == FLEXATTN_NA_TILED && line_log2 > 0 ? kRows : kLines;
         }
     }
     // Tags of a key and of a query (indices as the mods see them, in range).
@@ -359,8 +367,8 @@ struct PartialMask {
         window_corner(q, x, y);
         return ((uint32_t)x | ((uint32_t)y << y_shift)) - guard;
     }
-    // what the table of a step's 32-query blocks holds (match_queries)
-    __device__ __forceinline__ uint32_t query_block_tag(int q) const { return query_way == kTagged32 ? query_pixel(q) : key_pixel(q); }
+    // what the table of a step's 32-query blocks holds (match_queries, keep_queries)
+    __device__ __forceinline__ uint32_t query_block_tag(int q) const { return kByTags ? query_pixel(q) : key_pixel(q); }
     __device__ __forceinline__ bool pixels_match(uint32_t key_tag, uint32_t query_tag) const {
         const uint32_t a = key_tag - query_tag;
         return (a & (far - a) & guard) == guard;
@@ -449,12 +457,12 @@ struct PartialMask {
         const int l = min(max(lo, 0), 32), e = min(max(end, 0), 32);
         return (uint32_t)((1ull << e) - 1ull) & ~(uint32_t)((1ull << l) - 1ull);
     }
-    // Which of 32 consecutive tokens, whose pixels are in `tags` (LDS; of the first, and with tiles of 4 x 4 of the 17th, is
-    // asked), lie inside a lane's rectangle (corners included).
-    __device__ __forceinline__ uint32_t tokens_inside(int the_way, const uint32_t* tags, int x0, int y0, int x1, int y1) const {
+    // Which of 32 consecutive tokens, whose pixels are in `tags` (LDS; the first is asked), lie inside a lane's rectangle (corners
+    // included).
+    __device__ __forceinline__ uint32_t tokens_inside(const uint32_t* tags, int x0, int y0, int x1, int y1) const {
         const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)tags[0]), xm = (1u << (y_shift - 1)) - 1u;
         const int fx = (int)(first & xm), fy = (int)(first >> y_shift);
-        if (the_way == kLines) {
+        if (way == kLines) {
             uint32_t bits = 0;
             if (na_w < 32) {                // several lines: the line's bits once, moved to each
                 const uint32_t line = span(x0, x1 + 1), tall = (uint32_t)(y1 - y0);
@@ -466,15 +474,8 @@ struct PartialMask {
             return bits;
         }
         uint32_t xs = span(x0 - fx, x1 + 1 - fx);
-        if (the_way == kRows) {
+        if (way == kRows) {
             // (the line's bits, again for every line)
-            if (line_log2 == 2) {
-                const uint32_t next = (uint32_t)__builtin_amdgcn_readfirstlane((int)tags[16]);
-                const int nx = (int)(next & xm), ny = (int)(next >> y_shift);
-                const uint32_t a = (xs & 15u) * 0x1111u & span((y0 - fy) << 2, (y1 + 1 - fy) << 2);
-                const uint32_t b = (span(x0 - nx, x1 + 1 - nx) & 15u) * 0x1111u & span((y0 - ny) << 2, (y1 + 1 - ny) << 2);
-                return a | (b << 16);
-            }
             xs = __builtin_amdgcn_perm(xs, xs, line_log2 == 3 ? 0x00000000u : line_log2 == 4 ? 0x01000100u : 0x03020100u);
             return xs & span((y0 - fy) << line_log2, (y1 + 1 - fy) << line_log2);
         }
@@ -491,49 +492,54 @@ struct PartialMask {
         ys |= ys << 16;
         return xs & ys;
     }
-    // The lane's query has the window at `query_tag`, its elements are the keys whose pixels are in `tags` (LDS).
-    __device__ __forceinline__ void match_keys(Bits& bits, const uint32_t* tags, uint32_t query_tag, int half) const {
-        if (way != kTagged32) {
+    // put(r, all-ones or 0) for each of a lane's elements: its query has the window at `query_tag`, they are the keys whose pixels
+    // are in `tags` (LDS).  ONE_READ: there are no registers for four reads of them at a time.
+    template <bool ONE_READ, typename F>
+    __device__ __forceinline__ void mask_keys(Bits bits, const uint32_t* tags, uint32_t query_tag, int half, F&& put) const {
+        if constexpr (kByTags) {
+#pragma unroll
+            for (int rg = 0; rg < 4; ++rg) {
+                const u32x4 t = *(const u32x4*)&tags[8 * rg + 4 * half];
+                if constexpr (ONE_READ) asm volatile("" ::: "memory");
+#pragma unroll
+                for (int i = 0; i < 4; ++i) put(4 * rg + i, keep(bits, 4 * rg + i) | (pixels_match(t[i], query_tag) ? bit_mask(bits.tagged, elem_pos(4 * rg + i)) : 0u));
+            }
+        } else {
             const uint32_t corner = query_tag + guard;
             const int x0 = (int)(corner & ((1u << (y_shift - 1)) - 1u)), y0 = (int)(corner >> y_shift);
-            bits.plain |= bits.tagged & (tokens_inside(way, tags, x0, y0, x0 + 2 * na_r, y0 + 2 * na_r) >> (4 * half));
-        } else {
-            match_tags(bits, tags, half, [&](uint32_t t) __attribute__((always_inline)) { return pixels_match(t, query_tag); });
+            bits.plain |= bits.tagged & (tokens_inside(tags, x0, y0, x0 + 2 * na_r, y0 + 2 * na_r) >> (4 * half));
+#pragma unroll
+            for (int r = 0; r < 16; ++r) put(r, keep(bits, r));
         }
     }
     // The queries that see a key are a rectangle too: those around it, and up to the border where the windows there reach
-    // it.  Its corners (the key's own pixel twice where match_queries compares tags); empty past the last key.
+    // it.  Its corners (the key's own pixel twice where keep_queries compares tags); empty past the last key.
     __device__ __forceinline__ u32x2 key_corners(int kv) const {
         if (kv > kv_last) return u32x2{(1u << (y_shift - 1)) - 1u, 0u};      // (a column past any query's)
         const uint32_t tag = key_pixel(kv);
-        if (query_way == kTagged32) return u32x2{tag, tag};
+        if constexpr (kByTags) return u32x2{tag, tag};
         const int x = (int)(tag & ((1u << (y_shift - 1)) - 1u)), y = (int)(tag >> y_shift), d = 2 * na_r;
         const int x0 = x <= d ? 0 : x - na_r, x1 = x >= na_w - 1 - d ? na_w - 1 : x + na_r;
         const int y0 = y <= d ? 0 : y - na_r, y1 = y >= na_h - 1 - d ? na_h - 1 : y + na_r;
         return u32x2{(uint32_t)x0 | ((uint32_t)y0 << y_shift), (uint32_t)x1 | ((uint32_t)y1 << y_shift)};
     }
-    // The lane's key has these key_corners(), its elements are the queries whose query_block_tag() is in `tags`.
+    // The lane's key has these key_corners(), its elements are the queries whose query_block_tag() is in `tags`: what keep_queries
+    // wants to know of them (their bits, or the key's pixel).
     __device__ __forceinline__ Bits match_queries(const uint32_t* tags, u32x2 corners, int half) const {
-        static_assert(T0 == FLEXATTN_M_NEIGHBORHOOD && T1 == 0, "a canvas with another predicate: dK/dV asks the pixels alone");
-        Bits bits = {0u, ~0u};
-        if (query_way != kTagged32) {
-            const uint32_t xm = (1u << (y_shift - 1)) - 1u;
-            bits.plain = tokens_inside(query_way, tags, (int)(corners[0] & xm), (int)(corners[0] >> y_shift), (int)(corners[1] & xm), (int)(corners[1] >> y_shift)) >> (4 * half);
-        } else {
-            match_tags(bits, tags, half, [&](uint32_t t) __attribute__((always_inline)) { return pixels_match(corners[0], t); });
-        }
-        return bits;
+        static_assert((T0 & ~kCanvasByTags) == FLEXATTN_M_NEIGHBORHOOD && T1 == 0, "a canvas with another predicate: dK/dV asks the pixels alone");
+        if constexpr (kByTags) return Bits{corners[0], 0u};
+        const uint32_t xm = (1u << (y_shift - 1)) - 1u;
+        return Bits{tokens_inside(tags, (int)(corners[0] & xm), (int)(corners[0] >> y_shift), (int)(corners[1] & xm), (int)(corners[1] >> y_shift)) >> (4 * half), 0u};
     }
-    template <typename F>
-    __device__ __forceinline__ static void match_tags(Bits& bits, const uint32_t* tags, int half, F&& match) {
-        uint32_t same = 0;
-#pragma unroll 1
-        for (int rg = 0; rg < 4; ++rg) {
-            const u32x4 t = *(const u32x4*)&tags[8 * rg + 4 * half];
-            const uint32_t four = (match(t[0]) ? 1u : 0u) | (match(t[1]) ? 2u : 0u) | (match(t[2]) ? 4u : 0u) | (match(t[3]) ? 8u : 0u);
-            same |= four << (8 * rg);
+    // Elements 4 c4 .. of the lane, kept or 0.
+    __device__ __forceinline__ void keep_queries(const Bits& bits, const uint32_t* tags, int c4, int half, float (&pe)[4]) const {
+        u32x4 t = {};
+        if constexpr (kByTags) t = *(const u32x4*)&tags[8 * c4 + 4 * half];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (kByTags) pe[i] = keep_or_zero(pixels_match(bits.plain, t[i]) ? ~0u : 0u, pe[i]);
+            else pe[i] = keep_or_zero(keep(bits, 4 * c4 + i), pe[i]);
         }
-        bits.plain |= bits.tagged & same;
     }
     // All-ones if element r is kept, else 0.
     __device__ __forceinline__ static uint32_t keep(const Bits& bits, int r) { return bit_mask(bits.plain, elem_pos(r)); }
@@ -569,14 +575,6 @@ struct PartialMask {
         return h || kv_lo > kv_last;
     }
 };
-
-// v where m is all-ones, 0 (or -inf) where it is 0
-__device__ __forceinline__ float keep_or_zero(uint32_t m, float v) {
-    return __builtin_bit_cast(float, m & __builtin_bit_cast(uint32_t, v));
-}
-__device__ __forceinline__ float keep_or_neg_inf(uint32_t m, float v) {
-    return __builtin_bit_cast(float, (m & __builtin_bit_cast(uint32_t, v)) | (~m & 0xff800000u));
-}
 
 // ---------------------------------------------------------------------------------------
 // score_mod in the base-2 domain.  apply(acc, q - kv) returns log2(e) * score_mod(acc * scale),
@@ -866,6 +864,19 @@ inline int check_canvas(uint32_t mask_id, const flexattn_mod_params* p, int q_le
     return (q_len == n && kv_len == n) ? FLEXATTN_OK : FLEXATTN_ERR_INVALID_ARG;
 }
 
+// Whether the kernels compare the pixels of a canvas token by token, and not as the rectangle that a lane's window is: where 32
+// tokens are many short pieces, or (queries, in dK/dV) do not start at a known multiple of 32.
+// (us, compared -> as a rectangle, 64 heads, K = 9 at 64 x 64, K = 7 and 3 for the narrow ones, forward / dK/dV / dQ: tiles of 2 x 2 68 -> 74 / 127 -> 139 /
+// 87 -> 105, of 4 x 4 62 -> 61 / 110 -> 114 / 74 -> 77, row-major 4 x 1024 38 -> 40 / 75 -> 79 / 51 -> 55, 8 x 512 38 -> 39 / 75 -> 76 / 51 -> 53, but 16 x 256 42 ->
+// 40 / 75 -> 73 / 56 -> 55, 31 x 132 50 -> 46 / 92 -> 88 / 66 -> 64.  Both in one kernel cost the rectangles' side up to 15 % of dQ: spills, and code that
+// leaves the instruction cache.)
+inline bool canvas_by_tags(const flexattn_mod_params& p, bool backward) {
+    if (backward && p.q_offsets) return true;
+    if (p.na_layout == FLEXATTN_NA_MORTON) return p.na_width < 8;
+    if (p.na_layout == FLEXATTN_NA_TILED && p.na_tile > 1) return p.na_tile < 8;
+    return p.na_width < 16;
+}
+
 // The (mask, score) pairs that forward/backward kernels are instantiated for: the paper's examples
 // and benchmark variants, and three compositions of them (sliding window with a soft-cap; nested
 // score_mods: ALiBi then soft-cap, relative bias then soft-cap under a document mask).  The functors
@@ -886,9 +897,10 @@ inline int check_canvas(uint32_t mask_id, const flexattn_mod_params* p, int q_le
     X(FLEXATTN_MASK_NEIGHBORHOOD, FLEXATTN_SCORE_IDENTITY)                              \
     X(FLEXATTN_MASK_SWA_CAUSAL, FLEXATTN_SCORE_SOFTCAP)                                 \
     X(FLEXATTN_MASK_CAUSAL, (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_SOFTCAP))            \
-    X(FLEXATTN_MASK_DOCUMENT_CAUSAL, (FLEXATTN_SCORE_REL_BIAS | FLEXATTN_SCORE_SOFTCAP))
+    X(FLEXATTN_MASK_DOCUMENT_CAUSAL, (FLEXATTN_SCORE_REL_BIAS | FLEXATTN_SCORE_SOFTCAP))  \
+    X((FLEXATTN_MASK_NEIGHBORHOOD | kCanvasByTags), FLEXATTN_SCORE_IDENTITY)
 
 // One entry per line of FLEXATTN_FOR_EACH_VARIANT: X(index)
-#define FLEXATTN_VARIANT_INDICES(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12)
+#define FLEXATTN_VARIANT_INDICES(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13)
 
 }  // namespace flexattn

@@ -66,7 +66,7 @@ extern "C" const char* flexattn_strerror(int status) {
 extern "C" int flexattn_last_hip_error(void) { return g_last_hip_error; }
 extern "C" int flexattn_version(void) { return 120; }   // 120: flexattn_backward_stored (110: work-order arrays, probes, static decode)
 extern "C" int flexattn_is_supported(uint32_t mask_id, uint32_t score_id, int32_t D) {
-    return (D == 64 || D == 128) && find_variant(mask_id, score_id) >= 0;
+    return (D == 64 || D == 128) && mask_id_valid(mask_id) && find_variant(mask_id, score_id) >= 0;
 }
 
 extern "C" int flexattn_forward(const flexattn_dims* dims, const flexattn_tensor* Q, const flexattn_tensor* K,
@@ -80,7 +80,7 @@ extern "C" int flexattn_forward(const flexattn_dims* dims, const flexattn_tensor
     if (!LSE || !(scale > 0.0f)) return FLEXATTN_ERR_INVALID_ARG;
     if ((rc = check_mod_params(mask_id, score_id, params)) != FLEXATTN_OK) return rc;
     if ((rc = check_canvas(mask_id, params, dims->q_len, dims->kv_len)) != FLEXATTN_OK) return rc;
-    const int vi = find_variant(mask_id, score_id);
+    const int vi = variant_of(mask_id, score_id, params, false);
     if (vi < 0) return FLEXATTN_ERR_UNSUPPORTED;
 
     FwdArgs a = {};
@@ -122,7 +122,7 @@ extern "C" int flexattn_paged_forward(const flexattn_dims* dims, const flexattn_
     if (bm->Bm != dims->B) return FLEXATTN_ERR_INVALID_ARG;        // every sequence has its own pages
     if ((rc = check_mod_params(mask_id, score_id, params)) != FLEXATTN_OK) return rc;
     if ((rc = check_canvas(mask_id, params, dims->q_len, dims->kv_len)) != FLEXATTN_OK) return rc;
-    const int vi = find_variant(mask_id, score_id);
+    const int vi = variant_of(mask_id, score_id, params, false);
     if (vi < 0) return FLEXATTN_ERR_UNSUPPORTED;
 
     FwdArgs a = {};

@@ -399,9 +399,12 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         typename Mask::Bits bits = mask.row_bits(q_pos, kvs + 4 * half);
         const uint32_t q_tag = Mask::kTags ? s_qtag[tid] : 0u;
         if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[buf][kvb * 32], q_tag, l32, half, scattered);
-        if constexpr (Mask::kCanvas) mask.match_keys(bits, &s_tag[buf][kvb * 32], q_tag, half);
+        if constexpr (Mask::kCanvas) {
+            mask.template mask_keys<true>(bits, &s_tag[buf][kvb * 32], q_tag, half, [&](int r, uint32_t m) __attribute__((always_inline)) { s[r] = put(m, s[r]); });
+        } else {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = put(Mask::keep(bits, r), s[r]);
+            for (int r = 0; r < 16; ++r) s[r] = put(Mask::keep(bits, r), s[r]);
+        }
     };
     // The probabilities of a block as two bf16 fragments, and this lane's part of the row sum: over the bf16-rounded
     // probabilities, the values P V is computed from, two at a time (dot product of a packed pair with (1, 1), fp32 accumulation).

@@ -26,6 +26,11 @@ inline int find_variant(uint32_t mask, uint32_t score) {
     return -1;
 }
 
+// the variant of a call (of a valid mask)
+inline int variant_of(uint32_t mask, uint32_t score, const flexattn_mod_params* p, bool backward) {
+    return find_variant(mask_uses(mask, FLEXATTN_M_NEIGHBORHOOD) && canvas_by_tags(*p, backward) ? mask | kCanvasByTags : mask, score);
+}
+
 #define FLEXATTN_CAT_(a, b) a##b
 #define FLEXATTN_CAT(a, b) FLEXATTN_CAT_(a, b)
 

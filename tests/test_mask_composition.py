@@ -29,3 +29,10 @@ def test_canvas_with_another_predicate(mask, accepted, tmp_path):
     r = subprocess.run([build.HIPCC, *build.FLAGS, f"-DTESTED_MASK=({mask})", "--cuda-device-only", "-fsyntax-only", src], capture_output=True, text=True, timeout=300)
     assert (r.returncode == 0) == accepted, r.stderr
     assert accepted or "a canvas with another predicate" in r.stderr
+
+
+@pytest.mark.parametrize("mask", [0x60, 0x6020, 0x40, 0x61])
+def test_the_internal_canvas_flag_is_not_accepted(mask):
+    """Bit 6 selects, inside the library, the kernels that compare pixels token by token: no mask of a caller has it."""
+    import paper_2412_05496_amd as fa
+    assert not fa.flexattn_is_supported(mask, 0, 64) and fa.flexattn_is_supported(fa.MASK_NEIGHBORHOOD, 0, 64)
