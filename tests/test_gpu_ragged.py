@@ -176,8 +176,9 @@ def test_forward_d128_many_workgroups_planes_and_offsets(mask, score, Bk):
     ("prefix_lm", "identity", 4200, 130, 1), ("causal", "alibi", 4097, 33, 1), ("causal", "alibi", 4097, 130, 700),
     ("causal", "softcap", 2047, 130, 1), ("causal", "softcap", 2050, 130, 1), ("causal", "alibi_softcap", 2048, 200, 1)])
 def test_forward_d64_long_rows(mask, score, S, q_len, B):
-    """D = 64 without windows: both sides of the lengths and of the number of workgroups at which the forward keeps its
-    tile pipeline (soft-caps: too large to serve as the maximum).  The queries are the last of the sequence."""
+    """D = 64 without windows: lengths on both sides of those at which the forward keeps its tile pipeline (soft-caps: too large
+    to serve as the maximum), in launches so small that they are split, and one large one, plain by its number of workgroups
+    (tests/test_gpu_forward_pipelined.py has the pipeline).  The queries are the last of the sequence."""
     import paper_2412_05496_amd as fa
     dev = torch.device("cuda:0")
     wl = wlm.CFG1.scaled(name="long_rows", B=1, Hq=2, Hkv=1, S=S, D=64, Bq=128, Bk=64, mask=mask, score=score, prefix_len=100, softcap=60.0,

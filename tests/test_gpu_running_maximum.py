@@ -1,8 +1,8 @@
 """The forward moves a row's running maximum only when the probabilities of a 32-key block under the old one add up to
 more than a bound, and walks ALiBi rows from the end with the larger biases.  Where that can go wrong: sums at the bound,
 jumps that overflow 2^x, first keys far below zero, rows whose first blocks are hidden, biases of either sign and zero; on
-every form of the tile loop (few workgroups: the split forms; 300 copies: the others).  O and LSE at the tolerances of
-tests/helpers.py."""
+the split form (few workgroups), and in 300 copies on the plain and the pairs form, and at D = 128 on 32-key units and the pipeline
+(tests/test_gpu_forward_pipelined.py has the pipeline at D = 64).  O and LSE at the tolerances of tests/helpers.py."""
 import math
 
 import pytest
