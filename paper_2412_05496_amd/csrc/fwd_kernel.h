@@ -479,7 +479,9 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
             }
             float sum = 0.0f;
             bool moves = true;
-            if (seeded) {
+            // SPLIT: a maximum per block, since a wave's few blocks are mostly a row's first (us, the sum -> this: causal, S = 256, 2 heads 5.29 ->
+            // 5.26, S = 4096, 4 heads 21.5 -> 21.3, documents, S = 4096, 4 heads 23.4 -> 23.0, chunks of 518 on 9000 cached keys, 2 heads 63.7 -> 62.6).
+            if (!SPLIT && seeded) {
                 sum = weigh(s, pf, [](float x) __attribute__((always_inline)) { return fast_exp2(x); });
                 moves = __any(sum > kLazySum);
             }
