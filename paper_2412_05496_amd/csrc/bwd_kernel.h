@@ -511,7 +511,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 }
                 u32x4 pk[2] = {}, dsk[2] = {};
                 if (!hid) {
-                    constexpr int kAhead = Score::kRel ? 0 : 2;
+                    constexpr int kAhead = Score::kRel || Score::kCap ? 0 : 2;
                     if constexpr (OWN) {
 #pragma unroll
                         for (int c4 = 0; c4 < kAhead; ++c4) rcv4[c4] = read_row4(SLOT, 0, c4);
@@ -527,8 +527,10 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                         auto rel = [&](int r) __attribute__((always_inline)) {
                             return kNeedsPos ? RelPos(dq0, abase, 8 * (r >> 2) + (r & 3)) : RelPos(0);
                         };
-                        // (OWN: a quad of row constants, two ahead of its use, for four there are no registers, nor with a relative bias for
-                        // any: soft-cap, S = 4096, 64 heads 728 -> 702 us of the backward, causal, S = 1024, 1024 heads 747 -> 747)
+                        // (OWN: a quad of row constants, two ahead of its use; for four there are no registers, nor with a relative bias or a
+                        // soft-cap for any.  us, dK/dV, where they are used -> two ahead: no mask, S = 1600, 36 heads 67 -> 65, causal, S = 2000,
+                        // 30 heads 52 -> 51, ALiBi, S = 2048, 128 heads 180 -> 177 (2 spills); soft-cap, 5 and 6 spills, causal, S = 600, 256 heads 59 ->
+                        // 61, S = 8192, 32 heads 683 -> 678, window of 300, S = 4096, 32 heads 52 -> 54)
                         if constexpr (OWN) {
                             if (c4 + kAhead < 4) rcv4[c4 + kAhead] = read_row4(SLOT, 0, c4 + kAhead);
                         }
