@@ -57,6 +57,7 @@ struct FwdArgs {
     int n_pool_pages;
     int Bq;                // rows of a BlockMask block
     unsigned first_id;     // PAIRS: of the launch's workgroups, where there are several launches (kMaxLaunch)
+    int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
 };
 
 constexpr int kTileKV = 64;   // keys per kernel tile
@@ -188,6 +189,21 @@ bool pairs_pay(const FwdArgs& a, int D, unsigned grid) {
     if (D == 128) return grid <= (doc ? 3 * 256 : 2 * 256);
     return grid <= (doc ? 8 * 256 : 4 * 256) && !(BOUNDED && !doc && a.kv_len >= 8192);
 }
+// Documents with Bq = 128: a third of the rows of blocks, the longest, goes in halves, and of a batch whose longest row is short (tiles of 64
+// keys) none; the host cannot tell.  A workgroup of the same kernel takes a row as a whole, two passes over every tile's halves.
+// (us, D = 64, a workgroup per row of blocks / all in halves / this: documents of 16 to 100, 8192 x 16 19.8 / 23.2 / 20.4, ALiBi, 16384 x 16 34.7 / 39.0 /
+// 36.9, of 100 to 400, 4096 x 16 20.2 / 17.0 / 16.1, of 256 to 4096, 4096 x 16 74 / 51 / 45, 8192 x 16 88 / 60 / 59, ALiBi, 16384 x 16 178 / 127 / 129; D = 128, of
+// 16 to 100, 8192 x 8 20.5 / 22.3 / 18.7, of 100 to 400, 16384 x 6 35.7 / 37.4 / 33.0, of 256 to 4096, 2048 x 48 58 / 59 / 51, ALiBi, 4096 x 16 111 / 62 / 63,
+// 8192 x 12 115 / 77 / 80.  A quarter or a half in halves: 1 to 8 % less on one side each.  Empty workgroups between full ones
+// instead of whole rows: 28 for the first.)  A relative bias under a soft-cap whose maximum is tracked keeps all in halves at D = 64: the whole rows
+// cost it 18 spills (of 16 to 100, 8192 x 16 30.3 -> 33.9).
+template <int D, uint32_t MASK, uint32_t SCORE, bool BOUNDED>
+constexpr bool mixed_pays() {
+    return PartialMask<MASK>::kDoc && !(D == 64 && (SCORE & FLEXATTN_SCORE_REL_BIAS) && (SCORE & FLEXATTN_SCORE_SOFTCAP) && !BOUNDED);
+}
+constexpr int halved_rows(int NR) { return (NR + 2) / 3; }
+template <int D>
+constexpr int kShortTiles = D == 64 ? 6 : 10;
 // Waves per SIMD to compile for: what registers (512 per SIMD lane) and LDS admit.  The pipelined variants
 // with a relative-bias table would spill at three.
 template <int D, uint32_t SCORE, bool UNITS, bool PLAIN, bool SPLIT, bool PAIRS>
@@ -201,19 +217,20 @@ constexpr int fwd_waves_per_simd() {
 
 // BOUNDED: the score_mod ends in a soft-cap small enough that the cap itself serves as the fixed
 // softmax maximum (see ScoreMod::bounded); chosen by the host from the cap value.
-// UNITS: 32-key units in a ring of three (fwd_units).  PLAIN: no tile pipeline (fwd_plain).  PAIRS: see pairs_pay.  SPLIT: the NW waves share 32
-// rows and take the keys in turn (split_waves).
+// UNITS: 32-key units in a ring of three (fwd_units).  PLAIN: no tile pipeline (fwd_plain).  PAIRS: see pairs_pay.  MIXED: PAIRS with Bq = 128
+// where only some rows of blocks go in halves (halved_rows).  SPLIT: the NW waves share 32 rows and take the keys in turn (split_waves).
 // PAGED: the tiles of K and V are fetched from a paged pool through the converted block lists;
 // the mods keep seeing the logical key index.
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
 template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED, bool UNITS = false,
-          bool PLAIN = fwd_plain<D, NW, BOUNDED>(), bool SPLIT = false, bool PAIRS = false>
+          bool PLAIN = fwd_plain<D, NW, BOUNDED>(), bool SPLIT = false, bool PAIRS = false, bool MIXED = false>
 __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN, SPLIT, PAIRS>())) void fwd_kernel(const FwdArgs a) {
     static_assert(!PAIRS || (NW == 4 && !UNITS && !PLAIN && !SPLIT), "two row slices times two key halves");
+    static_assert(!MIXED || PAIRS, "halves and whole rows");
     constexpr int kSlices = PAIRS ? NW / 2 : NW;    // of 32 rows
-    const int Bq = SPLIT || PAIRS ? a.Bq : kSlices * 32;
+    const int Bq = MIXED ? 128 : SPLIT || PAIRS ? a.Bq : kSlices * 32;
     constexpr int TILE = kTileKV * D;              // elements per LDS tile
 
     // K(even), K(odd), V(even), V(odd); UNITS: three slots of 32 keys, K then V; SPLIT: 32 keys of K, then V, for each wave
@@ -230,12 +247,24 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     // ---- workgroup -> (b, hkv, g, row of blocks).  Rows are taken longest first (the BlockMask's work order), or
     // last-first without one (causal-like masks: longest first).
     int unit, rem, slice = 0;
-    if (!unit_of_workgroup(blockIdx.x + (PAIRS ? a.first_id : 0u), a.B * a.Hkv, a.G * a.NR * (SPLIT ? Bq / 32 : PAIRS ? Bq / 64 : 1), unit, rem)) return;
+    const int per_unit = a.G * (MIXED ? a.NR + a.halved : a.NR * (SPLIT ? Bq / 32 : PAIRS ? Bq / 64 : 1));
+    if (!unit_of_workgroup(blockIdx.x + (PAIRS ? a.first_id : 0u), a.B * a.Hkv, per_unit, unit, rem)) return;
     if constexpr (SPLIT) {
         slice = rem & (Bq / 32 - 1);                // which 32 rows of the block
         rem >>= Bq == 128 ? 2 : 1;
     }
-    if constexpr (PAIRS) {
+    bool whole = false;                             // MIXED: 32 rows and all keys to a wave
+    if constexpr (MIXED) {
+        // (where the longest row is short, by the first plane of the unit, none: the ids that are left over are the last and end at once)
+        const int64_t rows = ((int64_t)(a.bm_Bm > 1 ? unit / a.Hkv : 0) * a.bm_Hm + (a.bm_Hm > 1 ? unit % a.Hkv * a.G : 0)) * a.NR;
+        const int64_t longest = rows + (a.kv_order ? min(max(ldc(a.kv_order + rows), 0), a.NR - 1) : a.NR - 1);
+        const bool halve = (ldc(a.full_num + longest) + ldc(a.kv_num + longest)) * a.sub > kShortTiles<D>;
+        const int halves = halve ? 2 * a.halved * a.G : 0;
+        if (rem - (halves >> 1) >= a.NR * a.G) return;
+        whole = rem >= halves;
+        slice = rem < halves ? rem & 1 : 0;
+        rem = rem < halves ? rem >> 1 : rem - (halves >> 1);
+    } else if constexpr (PAIRS) {
         slice = rem & (Bq / 64 - 1);                // which 64 rows of the block
         rem >>= Bq == 128 ? 1 : 0;
     }
@@ -247,7 +276,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int my_slice = PAIRS ? w & 1 : w, my_keys = PAIRS ? w >> 1 : 0;  // PAIRS: which 32 rows, which 32 keys of every tile
+    const int my_slice = PAIRS && !whole ? w & 1 : w, my_keys = PAIRS && !whole ? w >> 1 : 0;  // PAIRS: which 32 rows, which 32 keys of every tile
     const int first_row = row * Bq + (SPLIT ? 32 : 64) * slice;            // of the workgroup
     const int wave_rows = first_row + (SPLIT ? 0 : my_slice) * 32;         // first of the wave's 32 rows
     const int q_row = wave_rows + l32;
@@ -360,8 +389,8 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         tile_src(v_head, v_rsrc, v_row_bytes, kv0, page, row, rsrc, soff);
         v_loader.start(rsrc, smem_bytes + (2 + buf) * (TILE * 2), soff);
     };
-    const RowReader<D> k_reader(l32, half, my_keys * 32 * D * 2);
-    const TrReader<D> v_reader(lane, my_keys * 32 * D * 2);
+    RowReader<D> k_reader(l32, half, my_keys * 32 * D * 2);
+    TrReader<D> v_reader(lane, my_keys * 32 * D * 2);
 
     // S^T = K Q^T for the two 32-key blocks of the K tile in buffer BUF (compile-time);
     // between(m) runs after the m-th of the 2 D / 16 MFMAs (used to spread out tile loads)
@@ -710,14 +739,14 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         if (u < TU) unit_step(u, s0);
         if (u + 1 < TU) unit_step(u + 1, s1);
     } else if constexpr (PAIRS) {
-        // Every wave takes its 32 keys of every tile, K and V one tile ahead.
+        // Every wave takes its 32 keys of every tile (whole: all 64, one half after the other), K and V one tile ahead.
         first_tile();
         auto pair_step = [&](int t, auto buf_tag) {
             constexpr int BUF = decltype(buf_tag)::value;
             wait_vmem();
             __syncthreads();        // tile t has landed, and nobody still reads tile t - 1
             const uint32_t hid = hidden_of(t) >> my_keys;
-            const int kv = kv_t + 32 * my_keys;
+            const int kv0 = kv_t;
             const bool partial = part_t;
             if (t + 1 < T) {
                 kv_t = walk.next(part_t, pg_t, pr_t);
@@ -725,20 +754,29 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
                 load_v(BUF ^ 1, kv_t, pg_t, pr_t);
                 if (part_t) make_tags(BUF ^ 1, kv_t, t + 1);
             }
-            if (hidden_block(hid, partial, kv, 0)) return;
-            f32x16 s;
+            int keys = my_keys;
+            do {
+                const int kv = kv0 + 32 * keys;
+                if (!hidden_block(hid, partial, kv, 0)) {
+                    f32x16 s;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) s[r] = 0.0f;
-            read_ahead<D / 16>([&](auto m) { return k_reader.read(smem_bytes + BUF * (TILE * 2), 0, decltype(m)::value); },
-                               [&](auto m, bf16x8 f) { s = mfma32(f, qf[decltype(m)::value], s); });
-            bf16x8 pf[2];
-            softmax(s, kv, partial, BUF, my_keys, pf);
-            constexpr int NDB = D / 32;
-            read_ahead<2 * NDB>([&](auto m) { return v_reader.read(smem_bytes + (2 + BUF) * (TILE * 2), 16 * (decltype(m)::value / NDB), decltype(m)::value % NDB); },
-                                [&](auto m, bf16x8 f) {
-                                    constexpr int db = decltype(m)::value % NDB, c = decltype(m)::value / NDB;
-                                    oacc[db] = mfma32(f, pf[c], oacc[db]);
-                                });
+                    for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+                    read_ahead<D / 16>([&](auto m) { return k_reader.read(smem_bytes + BUF * (TILE * 2), 0, decltype(m)::value); },
+                                       [&](auto m, bf16x8 f) { s = mfma32(f, qf[decltype(m)::value], s); });
+                    bf16x8 pf[2];
+                    softmax(s, kv, partial, BUF, keys, pf);
+                    constexpr int NDB = D / 32;
+                    read_ahead<2 * NDB>([&](auto m) { return v_reader.read(smem_bytes + (2 + BUF) * (TILE * 2), 16 * (decltype(m)::value / NDB), decltype(m)::value % NDB); },
+                                        [&](auto m, bf16x8 f) {
+                                            constexpr int db = decltype(m)::value % NDB, c = decltype(m)::value / NDB;
+                                            oacc[db] = mfma32(f, pf[c], oacc[db]);
+                                        });
+                }
+                if (!MIXED || !whole) break;
+                keys ^= 1;
+                k_reader.flip();
+                v_reader.flip();
+            } while (keys);
         };
         int t = 0;
         for (; t + 1 < T; t += 2) {
@@ -746,42 +784,44 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
             pair_step(t + 1, std::integral_constant<int, 1>{});
         }
         if (t < T) pair_step(t, std::integral_constant<int, 0>{});
-        // ---- the two waves of the same rows become one: each finishes half of the dims and hands over the other half
-        __shared__ float s_ml[NW][2][32];
-        const float l_wave = l_run + swap_halves(l_run);
-        if (half == 0) {
-            s_ml[w][0][l32] = m_run;
-            s_ml[w][1][l32] = l_wave;
+        if (!MIXED || !whole) {
+            // ---- the two waves of the same rows become one: each finishes half of the dims and hands over the other half
+            __shared__ float s_ml[NW][2][32];
+            const float l_wave = l_run + swap_halves(l_run);
+            if (half == 0) {
+                s_ml[w][0][l32] = m_run;
+                s_ml[w][1][l32] = l_wave;
+            }
+            constexpr int HDB = D / 64;
+            __syncthreads();            // (the last tile has been read)
+            f32x4* give = (f32x4*)smem + w * (HDB * 4 * 64) + lane;
+#pragma unroll
+            for (int q = 0; q < HDB * 4; ++q) {
+                f32x4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = my_keys ? oacc[q >> 2][4 * (q & 3) + i] : oacc[HDB + (q >> 2)][4 * (q & 3) + i];
+                give[q * 64] = v;
+            }
+            __syncthreads();
+            const float m_other = s_ml[w ^ 2][0][l32], m = fmaxf(m_run, m_other), m_from = m == -INFINITY ? 0.0f : m;
+            const float mine = fast_exp2(m_run - m_from), theirs = fast_exp2(m_other - m_from);
+            const float l = mine * l_wave + theirs * s_ml[w ^ 2][1][l32];
+            const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+            if (!real_row) return;
+            const f32x4* take = (const f32x4*)smem + (w ^ 2) * (HDB * 4 * 64) + lane;
+#pragma unroll
+            for (int q = 0; q < HDB * 4; ++q) {
+                f32x4 o = theirs * take[q * 64];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(mine, my_keys ? oacc[HDB + (q >> 2)][4 * (q & 3) + i] : oacc[q >> 2][4 * (q & 3) + i], o[i]) * inv;
+                u32x2 pk;
+                pk[0] = pack_bf16(o[0], o[1]);
+                pk[1] = pack_bf16(o[2], o[3]);
+                *(u32x2*)(o_ptr + (my_keys * HDB + (q >> 2)) * 32 + 8 * (q & 3) + 4 * half) = pk;
+            }
+            if (my_keys == 0 && half == 0) *lse_ptr = l > 0.0f ? (m + fast_log2(l)) * kLn2 : -INFINITY;
+            return;
         }
-        constexpr int HDB = D / 64;
-        __syncthreads();            // (the last tile has been read)
-        f32x4* give = (f32x4*)smem + w * (HDB * 4 * 64) + lane;
-#pragma unroll
-        for (int q = 0; q < HDB * 4; ++q) {
-            f32x4 v;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = my_keys ? oacc[q >> 2][4 * (q & 3) + i] : oacc[HDB + (q >> 2)][4 * (q & 3) + i];
-            give[q * 64] = v;
-        }
-        __syncthreads();
-        const float m_other = s_ml[w ^ 2][0][l32], m = fmaxf(m_run, m_other), m_from = m == -INFINITY ? 0.0f : m;
-        const float mine = fast_exp2(m_run - m_from), theirs = fast_exp2(m_other - m_from);
-        const float l = mine * l_wave + theirs * s_ml[w ^ 2][1][l32];
-        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
-        if (!real_row) return;
-        const f32x4* take = (const f32x4*)smem + (w ^ 2) * (HDB * 4 * 64) + lane;
-#pragma unroll
-        for (int q = 0; q < HDB * 4; ++q) {
-            f32x4 o = theirs * take[q * 64];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(mine, my_keys ? oacc[HDB + (q >> 2)][4 * (q & 3) + i] : oacc[q >> 2][4 * (q & 3) + i], o[i]) * inv;
-            u32x2 pk;
-            pk[0] = pack_bf16(o[0], o[1]);
-            pk[1] = pack_bf16(o[2], o[3]);
-            *(u32x2*)(o_ptr + (my_keys * HDB + (q >> 2)) * 32 + 8 * (q & 3) + 4 * half) = pk;
-        }
-        if (my_keys == 0 && half == 0) *lse_ptr = l > 0.0f ? (m + fast_log2(l)) * kLn2 : -INFINITY;
-        return;
     } else if constexpr (PLAIN) {
         // One block of 32 keys after the other, K and V one tile ahead.  A wave leaves out the blocks that
         // the mask hides from all of its rows.
@@ -928,11 +968,16 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
         return FLEXATTN_OK;
     }
     if (pairs_pay<MASK, BOUNDED>(a, D, grid)) {
-        const unsigned halves = unit_grid(a.B * a.Hkv, a.G * a.NR * (Bq / 64));
+        constexpr bool mixed64 = mixed_pays<64, MASK, SCORE, BOUNDED>(), mixed128 = mixed_pays<128, MASK, SCORE, BOUNDED>();
+        const bool mixed = Bq == 128 && (D == 64 ? mixed64 : mixed128);
         FwdArgs part = a;
-        for (part.first_id = 0; part.first_id < halves; part.first_id += kMaxLaunch) {
-            const dim3 ids(min(halves - part.first_id, kMaxLaunch));
-            if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, part);
+        part.halved = Bq == 64 ? 0 : mixed ? halved_rows(a.NR) : a.NR;
+        const unsigned pieces = unit_grid(a.B * a.Hkv, a.G * (a.NR + part.halved));
+        for (part.first_id = 0; part.first_id < pieces; part.first_id += kMaxLaunch) {
+            const dim3 ids(min(pieces - part.first_id, kMaxLaunch));
+            if (D == 128 && mixed) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true, mixed128>), ids, dim3(256), 0, st, part);
+            else if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, part);
+            else if (mixed) hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true, mixed64>), ids, dim3(256), 0, st, part);
             else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, part);
         }
         return FLEXATTN_OK;

@@ -167,6 +167,11 @@ struct RowReader {
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks) off[ks] = base + 2u * (uint32_t)tile_off<D>(l32, 2 * ks + half);
     }
+    // from the first 32 rows of the tile (for all reads) to the other 32, and back
+    __device__ __forceinline__ void flip() {
+#pragma unroll
+        for (int ks = 0; ks < D / 16; ++ks) off[ks] ^= 64u * D;
+    }
     // `tile_bytes`: LDS byte address of the tile (wave-uniform); row0 and ks are compile-time
     __device__ __forceinline__ bf16x8 read(uint32_t tile_bytes, int row0, int ks) const {
         return *(const __attribute__((address_space(3))) bf16x8*)(uintptr_t)(tile_bytes + off[ks] + 2u * row0 * D);
@@ -195,6 +200,13 @@ struct TrReader {
             const int col = cb * 32 + 16 * (grp & 1) + 4 * (j & 3);
             off[cb][0] = base + 2u * (uint32_t)(tile_off<D>(row, col >> 3) + (col & 7));
             off[cb][1] = base + 2u * (uint32_t)(tile_off<D>(row + 8, col >> 3) + (col & 7));
+        }
+    }
+    __device__ __forceinline__ void flip() {        // as RowReader's
+#pragma unroll
+        for (int cb = 0; cb < D / 32; ++cb) {
+            off[cb][0] ^= 64u * D;
+            off[cb][1] ^= 64u * D;
         }
     }
     // r0 (multiple of 16) and cb are compile-time: swz depends on r0 only through (r0 >> 2) & 3 == 0
