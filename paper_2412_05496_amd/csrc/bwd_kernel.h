@@ -66,6 +66,7 @@ struct BwdArgs {
     flexattn_mod_params p;
     bool make_delta;           // the dQ kernel works the row scalars out itself (and writes them)
     bool dq_last;              // (host) dQ is written over what dK/dV or the row scalars are made of: it runs last, after a pass for the latter
+    int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
 };
 
 constexpr uint32_t kBwdStageCaptured = 8u;   // internal: the captured-tensor sums instead of dQ
@@ -728,12 +729,14 @@ constexpr bool dq_skips_hidden() {
 // PAIRS: a workgroup takes 64 rows; the four waves are two slices of 32 rows times the two key halves of every tile, and the two waves
 // of the same rows add up at the end.  Two waves, one per slice, leave LDS for one (D = 128) or 2.5 (D = 64) waves per SIMD;
 // four that share the tiles make it two and three
-// (dq_pairs_pay has the times, and where the halves of rows of blocks of 128 take this form).
-template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool CAPTURED = false, bool SKIP = dq_skips_hidden<D, NW>(), bool PAIRS = false>
+// (dq_pairs_pay has the times, and where the halves of rows of blocks of 128 take this form).  MIXED: some rows of blocks whole (dq_halved_rows).
+template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool CAPTURED = false, bool SKIP = dq_skips_hidden<D, NW>(), bool PAIRS = false, bool MIXED = false>
 __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kernel(const BwdArgs a) {
     static_assert(!PAIRS || (NW == 4 && SKIP), "two row slices times two key halves");
+    static_assert(!MIXED || (PAIRS && !CAPTURED), "halves and whole rows");
+    constexpr int kShortTiles = 10;                                  // MIXED: longest rows of no more stay whole
     constexpr int kSlices = PAIRS ? NW / 2 : NW;
-    const int Bq = PAIRS ? a.Bq : kSlices * 32;
+    const int Bq = MIXED ? 128 : PAIRS ? a.Bq : kSlices * 32;
     constexpr int TILE = 64 * D;
     __shared__ __attribute__((aligned(1024))) bf16 smem[4 * TILE];   // K(even), K(odd), V(even), V(odd)
     constexpr int kTabAlibi = 1024;                                  // the table has at most 1024 entries
@@ -744,9 +747,13 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     __shared__ uint8_t s_hidden[Mask::kCanvas && SKIP ? kHiddenTiles : 1];           // CanvasBlocks::hidden_bits of the first tiles
 
     int unit, rem;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (PAIRS ? Bq / 64 : 1), unit, rem)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * (MIXED ? a.NR + a.halved : a.NR * (PAIRS ? Bq / 64 : 1)), unit, rem)) return;
     int slice = 0;                                                   // PAIRS: which 64 rows of the block
-    if constexpr (PAIRS) {
+    bool whole = false;                                              // MIXED: 32 rows and all keys to a wave
+    if constexpr (MIXED) {
+        const int64_t rows = ((int64_t)(a.bm_Bm > 1 ? unit / a.Hkv : 0) * a.bm_Hm + (a.bm_Hm > 1 ? unit % a.Hkv * a.G : 0)) * a.NR;
+        if (!half_or_row(a.kv_order, a.full_kv_num, a.kv_num, rows, a.NR, a.G, a.Bk / 64, a.halved, kShortTiles, rem, slice, whole)) return;
+    } else if constexpr (PAIRS) {
         slice = rem & (Bq / 64 - 1);
         rem >>= Bq == 128 ? 1 : 0;
     }
@@ -757,7 +764,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int my_slice = PAIRS ? w & 1 : w, my_keys = PAIRS ? w >> 1 : 0;
+    const int my_slice = PAIRS && !whole ? w & 1 : w, my_keys = PAIRS && !whole ? w >> 1 : 0;
     const int first_row = row * Bq + 64 * slice, wave_rows = first_row + my_slice * 32;
     if (PAIRS && !CAPTURED && first_row >= a.q_len) return;
     const int q_row = wave_rows + l32;
@@ -872,8 +879,8 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     __syncthreads();
     if constexpr (Mask::kDoc) scattered = Mask::scattered_ids(q_tag);               // (not earlier: q_tag would be waited for)
 
-    // One tile on buffer BUF (compile-time, so that every LDS read is "VGPR + immediate").
-    auto step = [&](int t, auto buf_tag) {
+    // One tile on buffer BUF (compile-time, so that every LDS read is "VGPR + immediate"); half_tag: the wave's half of it alone.
+    auto step = [&](int t, auto buf_tag, auto half_tag) __attribute__((always_inline)) {
         constexpr int BUF = decltype(buf_tag)::value;
         const int kv0_cur = kv0;
         const bool partial = part_next;
@@ -887,14 +894,15 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         }
         constexpr uint32_t kt = BUF * (TILE * 2), vt = (2 + BUF) * (TILE * 2);
         using L = WaveTileLoader<D, NW>;
-        constexpr int NKS = D / 16, NDB = D / 32, PF = 4;
+        // (MIXED at D = 64: with four read ahead 7 registers spill, ALiBi, S = 16384, 16 heads 158 -> 176 us)
+        constexpr int NKS = D / 16, NDB = D / 32, PF = MIXED && D == 64 ? 3 : 4;
 
         if constexpr (SKIP) {
             if (ld) load_tiles(BUF ^ 1, kv0);
         }
-        static_for<0, PAIRS ? 1 : 2>([&](auto kvb_tag) {
+        static_for<0, decltype(half_tag)::value ? 1 : 2>([&](auto kvb_tag) __attribute__((always_inline)) {
             constexpr int kvb = decltype(kvb_tag)::value;
-            const int block = PAIRS ? my_keys : kvb;        // (the readers know my_keys)
+            const int block = decltype(half_tag)::value ? my_keys : kvb;        // (the readers know my_keys)
             if constexpr (SKIP) {
                 if (hidden_block(t, partial, kv0_cur + 32 * block, block)) return;
             }
@@ -1013,13 +1021,20 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         wait_vmem();
         __syncthreads();
     };
-    {
+    auto all_tiles = [&](auto half_tag) __attribute__((always_inline)) {
         int t = 0;
         for (; t + 1 < T; t += 2) {
-            step(t, std::integral_constant<int, 0>{});
-            step(t + 1, std::integral_constant<int, 1>{});
+            step(t, std::integral_constant<int, 0>{}, half_tag);
+            step(t + 1, std::integral_constant<int, 1>{}, half_tag);
         }
-        if (t < T) step(t, std::integral_constant<int, 0>{});
+        if (t < T) step(t, std::integral_constant<int, 0>{}, half_tag);
+    };
+    // (two loops: in one for both, which moves the readers, long rows took 3 to 9 % more)
+    if constexpr (MIXED) {
+        if (whole) all_tiles(std::false_type{});
+        else all_tiles(std::true_type{});
+    } else {
+        all_tiles(std::bool_constant<PAIRS>{});
     }
 
     if constexpr (CAPTURED) {
@@ -1046,7 +1061,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         return;
     }
     const float qscale = a.scale * ScoreMod<SCORE>::grad_scale();
-    if constexpr (PAIRS) {
+    if (PAIRS && !whole) {
         // each of the two waves of the same rows finishes half of the dims and hands over the other half (the last step ended
         // with a barrier: the tiles are free)
         constexpr int HDB = D / 64;

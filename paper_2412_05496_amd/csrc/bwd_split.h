@@ -544,6 +544,18 @@ bool dq_pairs_pay(const BwdArgs& a, int D) {
     if (!rows.uneven || a.kv_len < 2048) return false;
     return grid <= (D == 64 ? 8 * 256 : PartialMask<MASK>::kDoc ? 4 * 256 : 2 * 256);
 }
+// Documents with Bq = 128 in the pairs form: how many of the rows of blocks, the longest, go in halves while the others stay whole, unless even the
+// longest is short (half_or_row).  us of dQ, a workgroup per row of blocks / all in halves / this: D = 64, documents of 16 to 100, 8192 x 16 28.7 / 33.8 / 28.7,
+// ALiBi, 16384 x 16 46.4 / 56.7 / 46.8, of 100 to 400, 8192 x 16 31.7 / 38.2 / 32.0, 4096 x 16 25.2 / 23.1 / 25.0, of 256 to 4096, 8192 x 16 98 / 74 / 76, ALiBi,
+// 16384 x 16 175 / 166 / 158; D = 128, of 16 to 100, 8192 x 8 26.1 / 30.4 / 25.5, 2048 x 48 39.4 / 44.1 / 38.2, of 100 to 400, 8192 x 12 43.8 / 50.4 / 44.9, of 256 to
+// 4096, 8192 x 8 94 / 70 / 70, ALiBi, 4096 x 16 118 / 79 / 76, 2048 x 48 74 / 75 / 66, 16384 x 6 145 / 121 / 124.  All of them at D = 64 while the whole rows are
+// about a round (a quarter of long ones, with a loop that is slower: 8192 x 16 79 and 77), a quarter then (a third, ALiBi, 16384 x 16 167 and 164).
+// A relative bias under a soft-cap keeps all in halves: 12 and 19 spills.
+template <uint32_t MASK, uint32_t SCORE>
+constexpr bool dq_can_mix() {
+    return PartialMask<MASK>::kDoc && !((SCORE & FLEXATTN_SCORE_REL_BIAS) && (SCORE & FLEXATTN_SCORE_SOFTCAP));
+}
+inline int dq_halved_rows(int D, int NR, unsigned grid) { return D == 128 ? halved_rows(NR) : grid <= 4 * 256 ? NR : (NR + 3) / 4; }
 // us, bwd_dkdv_kernel -> 4 waves / 8 waves: causal, S = 4096, D = 64, 1 head 51 -> 39 / 21, 4 52 -> 41 / 29, 8 58 -> 50 / 54, 16 92 -> 98; D = 128 (4
 // waves), 1 head 72 -> 45, 4 74 -> 58, 8 90 -> 111; 8 query and 1 KV heads, S = 2048 199 -> 145 / 74, D = 128 280 -> 166; 32 / 8, S = 2048 101 -> 77 /
 // 53; S = 1000, D = 64, 8 / 16 / 32 heads 16.8 -> 13.7 / 10.1, 17.1 -> 15.9 / 15.3, 23.2 -> 25.1, D = 128, 8 / 16 heads 23.8 -> 16.8, 24.2 -> 23.9; S =
@@ -661,9 +673,15 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
             else if (waves == 8) hipLaunchKernelGGL((bwd_dq_split_kernel<64, 8, MASK, SCORE>), slices, dim3(512), 0, st, aq);
             else hipLaunchKernelGGL((bwd_dq_split_kernel<64, 4, MASK, SCORE>), slices, dim3(256), 0, st, aq);
         } else if (dq_pairs_pay<MASK>(a, D)) {
-            const dim3 halves(unit_grid(a.B * a.Hkv, a.G * a.NR * (a.Bq / 64)));
-            if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, false, true, true>), halves, dim3(256), 0, st, aq);
-            else hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, true, true>), halves, dim3(256), 0, st, aq);
+            constexpr bool can_mix = dq_can_mix<MASK, SCORE>();
+            const bool mixed = can_mix && a.Bq == 128;
+            BwdArgs part = aq;
+            part.halved = a.Bq == 64 ? 0 : mixed ? dq_halved_rows(D, a.NR, grid_q) : a.NR;
+            const dim3 pieces(unit_grid(a.B * a.Hkv, a.G * (a.NR + part.halved)));
+            if (D == 128 && mixed) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, false, true, true, can_mix>), pieces, dim3(256), 0, st, part);
+            else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, false, true, true>), pieces, dim3(256), 0, st, part);
+            else if (mixed) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, true, true, can_mix>), pieces, dim3(256), 0, st, part);
+            else hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, true, true>), pieces, dim3(256), 0, st, part);
         } else if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
         else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
         else if (a.Bq == 128) launch_dq64<MASK, SCORE>(aq, grid_q, st);

@@ -255,6 +255,21 @@ inline unsigned unit_grid(int units, int per_unit) {
 // What may need more takes several launches of at most this many.
 constexpr unsigned kMaxLaunch = 1u << 23;
 
+// Workgroups that take either a row of blocks of 128 rows as a whole or one of its halves (MIXED in the forward and dQ): the first `halved` ranks in
+// halves, but where the longest row of the unit's first plane (the first in work order) is short, none; the ids that are left over then are the
+// last.  rem: the piece of a unit (G query heads) of G * (NR + halved) -> the piece of G * NR rows.  False: nothing to do.
+__device__ __forceinline__ bool half_or_row(const int32_t* order, const int32_t* full_num, const int32_t* part_num, int64_t plane_rows, int NR, int G,
+                                            int sub, int halved, int short_tiles, int& rem, int& slice, bool& whole) {
+    const int64_t longest = plane_rows + (order ? min(max(ldc(order + plane_rows), 0), NR - 1) : NR - 1);
+    const int halves = (ldc(full_num + longest) + ldc(part_num + longest)) * sub > short_tiles ? 2 * halved * G : 0;
+    if (rem - (halves >> 1) >= NR * G) return false;
+    whole = rem >= halves;
+    slice = whole ? 0 : rem & 1;
+    rem = whole ? rem - (halves >> 1) : rem >> 1;
+    return true;
+}
+constexpr int halved_rows(int NR) { return (NR + 2) / 3; }
+
 // Offset conversion for inference (section 5.2): the position the mods see for query row 0 of
 // batch entry b.
 __device__ __forceinline__ int q_offset_of(const flexattn_mod_params& p, int b) {

@@ -201,7 +201,6 @@ template <int D, uint32_t MASK, uint32_t SCORE, bool BOUNDED>
 constexpr bool mixed_pays() {
     return PartialMask<MASK>::kDoc && !(D == 64 && (SCORE & FLEXATTN_SCORE_REL_BIAS) && (SCORE & FLEXATTN_SCORE_SOFTCAP) && !BOUNDED);
 }
-constexpr int halved_rows(int NR) { return (NR + 2) / 3; }
 template <int D>
 constexpr int kShortTiles = D == 64 ? 6 : 10;
 // Waves per SIMD to compile for: what registers (512 per SIMD lane) and LDS admit.  The pipelined variants
@@ -255,15 +254,8 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     }
     bool whole = false;                             // MIXED: 32 rows and all keys to a wave
     if constexpr (MIXED) {
-        // (where the longest row is short, by the first plane of the unit, none: the ids that are left over are the last and end at once)
         const int64_t rows = ((int64_t)(a.bm_Bm > 1 ? unit / a.Hkv : 0) * a.bm_Hm + (a.bm_Hm > 1 ? unit % a.Hkv * a.G : 0)) * a.NR;
-        const int64_t longest = rows + (a.kv_order ? min(max(ldc(a.kv_order + rows), 0), a.NR - 1) : a.NR - 1);
-        const bool halve = (ldc(a.full_num + longest) + ldc(a.kv_num + longest)) * a.sub > kShortTiles<D>;
-        const int halves = halve ? 2 * a.halved * a.G : 0;
-        if (rem - (halves >> 1) >= a.NR * a.G) return;
-        whole = rem >= halves;
-        slice = rem < halves ? rem & 1 : 0;
-        rem = rem < halves ? rem >> 1 : rem - (halves >> 1);
+        if (!half_or_row(a.kv_order, a.full_num, a.kv_num, rows, a.NR, a.G, a.sub, a.halved, kShortTiles<D>, rem, slice, whole)) return;
     } else if constexpr (PAIRS) {
         slice = rem & (Bq / 64 - 1);                // which 64 rows of the block
         rem >>= Bq == 128 ? 1 : 0;
@@ -774,8 +766,8 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
                 }
                 if (!MIXED || !whole) break;
                 keys ^= 1;
-                k_reader.flip();
-                v_reader.flip();
+                k_reader.move(keys ? 64 * D : -64 * D);
+                v_reader.move(keys ? 64 * D : -64 * D);
             } while (keys);
         };
         int t = 0;

@@ -167,10 +167,10 @@ struct RowReader {
 #pragma unroll
         for (int ks = 0; ks < D / 16; ++ks) off[ks] = base + 2u * (uint32_t)tile_off<D>(l32, 2 * ks + half);
     }
-    // from the first 32 rows of the tile (for all reads) to the other 32, and back
-    __device__ __forceinline__ void flip() {
+    // all reads `bytes` further (wave-uniform)
+    __device__ __forceinline__ void move(int bytes) {
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) off[ks] ^= 64u * D;
+        for (int ks = 0; ks < D / 16; ++ks) off[ks] += (uint32_t)bytes;
     }
     // `tile_bytes`: LDS byte address of the tile (wave-uniform); row0 and ks are compile-time
     __device__ __forceinline__ bf16x8 read(uint32_t tile_bytes, int row0, int ks) const {
@@ -202,11 +202,11 @@ struct TrReader {
             off[cb][1] = base + 2u * (uint32_t)(tile_off<D>(row + 8, col >> 3) + (col & 7));
         }
     }
-    __device__ __forceinline__ void flip() {        // as RowReader's
+    __device__ __forceinline__ void move(int bytes) {
 #pragma unroll
         for (int cb = 0; cb < D / 32; ++cb) {
-            off[cb][0] ^= 64u * D;
-            off[cb][1] ^= 64u * D;
+            off[cb][0] += (uint32_t)bytes;
+            off[cb][1] += (uint32_t)bytes;
         }
     }
     // r0 (multiple of 16) and cb are compile-time: swz depends on r0 only through (r0 >> 2) & 3 == 0
