@@ -498,15 +498,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
                 else asm volatile("" ::: "memory");
                 masked(s, kvs, buf, kvb, keep_or_neg_inf);
             }
-            float sum = 0.0f;
-            bool moves = true;
-            // SPLIT: a maximum per block, since a wave's few blocks are mostly a row's first (us, the sum -> this: causal, S = 256, 2 heads 5.29 ->
-            // 5.26, S = 4096, 4 heads 21.5 -> 21.3, documents, S = 4096, 4 heads 23.4 -> 23.0, chunks of 518 on 9000 cached keys, 2 heads 63.7 -> 62.6).
-            if (!SPLIT && seeded) {
-                sum = weigh(s, pf, [](float x) __attribute__((always_inline)) { return fast_exp2(x); });
-                moves = __any(sum > kLazySum);
-            }
-            if (moves) {
+            auto track = [&]() __attribute__((always_inline)) {
                 float mx = s[0];
 #pragma unroll
                 for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
@@ -527,7 +519,33 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 #pragma unroll
                         for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
                 }
-                sum = weigh(s, pf, [](float x) __attribute__((always_inline)) { return fast_exp2(x); });
+            };
+            auto weighed = [&]() __attribute__((always_inline)) { return weigh(s, pf, [](float x) __attribute__((always_inline)) { return fast_exp2(x); }); };
+            float sum = 0.0f;
+            constexpr bool kOnePlace = D == 128 ? !SPLIT && (Score::kAlibi || Mask::kTags) : PLAIN && Score::kAlibi;
+            if constexpr (kOnePlace) {
+                // (the weights in one place: in two, registers spill, which short rows pay for most; us, two -> one: D = 64, causal with ALiBi, S = 100,
+                // 2048 heads 27.8 -> 24.2, S = 300, 1024 heads 44.1 -> 39.6, S = 1500, 256 heads 123 -> 118; D = 128, documents of 16 to 100 with ALiBi,
+                // S = 16384, 16 heads 70 -> 66.  Elsewhere within 1 to 2 % either way.)
+                bool moves = !seeded;
+                for (;;) {
+                    if (moves) track();
+                    sum = weighed();
+                    if (moves || !__any(sum > kLazySum)) break;
+                    moves = true;
+                }
+            } else {
+                // SPLIT: a maximum per block, since a wave's few blocks are mostly a row's first (us, the sum -> this: causal, S = 256, 2 heads 5.29 ->
+                // 5.26, S = 4096, 4 heads 21.5 -> 21.3, documents, S = 4096, 4 heads 23.4 -> 23.0, chunks of 518 on 9000 cached keys, 2 heads 63.7 -> 62.6).
+                bool moves = true;
+                if (!SPLIT && seeded) {
+                    sum = weighed();
+                    moves = __any(sum > kLazySum);
+                }
+                if (moves) {
+                    track();
+                    sum = weighed();
+                }
             }
             l_run += sum;
         }
