@@ -64,6 +64,19 @@ bool same_rows(const flexattn_tensor* a, const flexattn_tensor* b) {
     return a->ptr == b->ptr && a->stride_b == b->stride_b && a->stride_h == b->stride_h && a->stride_s == b->stride_s;
 }
 
+// How the dQ kernel that reads dS back shares its K tiles (bwd_stored.h), D = 128, Bq = 128: among two heads of a group, else among two rows
+// of blocks; on long rows, with enough workgroups left.  us of the whole backward, a head's row of blocks by itself -> shared: two heads, S x
+// query / KV heads, causal with soft-cap, 8192 x 64 / 32 3572 -> 3502, 8192 x 16 / 8 919 -> 897, no mask, 16384 x 4 / 2 1565 -> 1518, but 2048 x 32 / 8
+// 185 -> 195, 1000 x 16 / 4 83 -> 93; two rows, causal with soft-cap, 8192 x 64 3685 -> 3602, 4096 x 32 527 -> 518, prefix, 4000 x 32 491 -> 484, but 2048
+// x 128 608 -> 619, no mask, 1500 x 96 412 -> 415, causal, 8192 x 8 466 -> 479, window of 1024, 8192 x 32 550 -> 561.
+StoredShare stored_share(const flexattn_dims* d, const flexattn_blockmask* bm, uint32_t mask_id, const flexattn_mod_params& p) {
+    if (d->D != 128 || bm->Bq != 128 || mask_uses(mask_id, FLEXATTN_M_NEIGHBORHOOD)) return StoredShare::kNone;
+    if (line_shape(mask_id, p, d->q_len, d->kv_len).sure < 4000) return StoredShare::kNone;
+    const int64_t sets = (int64_t)d->B * d->Hq * ((d->q_len + 127) / 128) / 2;
+    if (d->Hq / d->Hkv % 2 == 0 && bm->Hm == 1) return sets >= 256 ? StoredShare::kHeads : StoredShare::kNone;
+    return sets >= 512 && !mask_uses(mask_id, FLEXATTN_M_SLIDING_WINDOW) ? StoredShare::kRows : StoredShare::kNone;
+}
+
 // Whether dS through memory is faster than recomputing it for dQ.  Memory costs 4 bytes a score and three more small launches
 // (about 8 us); recomputing costs two matrix products and the score_mod, which at D = 64 is the less, but for a soft-cap on
 // long rows.  us of the whole backward, dS in memory -> recomputed:
@@ -82,18 +95,6 @@ bool same_rows(const flexattn_tensor* a, const flexattn_tensor* b) {
 // 16 heads 39.3 -> 48.5, 64 x 64 pixels, K = 27, 16 heads 129 -> 148 (4 heads 86 -> 75); D = 128, documents, S = 1100, 8 heads 36.0 -> 39.5, no mask 54.6 -> 58.1
 // (4 heads 46 -> 37), a window of 300 or prefix of 100 with a relative bias, S = 1100, 8 heads 44 -> 50, 64 heads 118 -> 123.
 // The lines go by slices of 32 query rows and by the longest row (line_shape).
-// How the dQ kernel that reads dS back shares its K tiles (bwd_stored.h), D = 128, Bq = 128: among two heads of a group, else among two rows
-// of blocks; on long rows, with enough workgroups left.  us of the whole backward, a head's row of blocks by itself -> shared: two heads, S x
-// query / KV heads, causal with soft-cap, 8192 x 64 / 32 3572 -> 3502, 8192 x 16 / 8 919 -> 897, no mask, 16384 x 4 / 2 1565 -> 1518, but 2048 x 32 / 8
-// 185 -> 195, 1000 x 16 / 4 83 -> 93; two rows, causal with soft-cap, 8192 x 64 3685 -> 3602, 4096 x 32 527 -> 518, prefix, 4000 x 32 491 -> 484, but 2048
-// x 128 608 -> 619, no mask, 1500 x 96 412 -> 415, causal, 8192 x 8 466 -> 479, window of 1024, 8192 x 32 550 -> 561.
-StoredShare stored_share(const flexattn_dims* d, const flexattn_blockmask* bm, uint32_t mask_id, const flexattn_mod_params& p) {
-    if (d->D != 128 || bm->Bq != 128 || mask_uses(mask_id, FLEXATTN_M_NEIGHBORHOOD)) return StoredShare::kNone;
-    if (line_shape(mask_id, p, d->q_len, d->kv_len).sure < 4000) return StoredShare::kNone;
-    const int64_t sets = (int64_t)d->B * d->Hq * ((d->q_len + 127) / 128) / 2;
-    if (d->Hq / d->Hkv % 2 == 0 && bm->Hm == 1) return sets >= 256 ? StoredShare::kHeads : StoredShare::kNone;
-    return sets >= 512 && !mask_uses(mask_id, FLEXATTN_M_SLIDING_WINDOW) ? StoredShare::kRows : StoredShare::kNone;
-}
 bool stored_pays(const flexattn_dims* d, uint32_t mask_id, uint32_t score_id, const flexattn_mod_params& p) {
     const int64_t slices = (int64_t)d->B * d->Hq * ((d->q_len + 31) / 32);
     const LineShape rows = line_shape(mask_id, p, d->q_len, d->kv_len);
