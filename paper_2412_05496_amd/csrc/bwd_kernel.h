@@ -719,17 +719,16 @@ __device__ __forceinline__ float diagonal_sums(const f32x16& v, int half) {
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
 //
 // SKIP: hidden blocks are left out, which means not to spread the loads of the next tile over the MFMAs of this one.
-// Four waves at D = 64 (window of 1024, S = 5000: 130 -> 124 us; canvas 100 x 90, K = 9, row-major: 349 -> 290),
-// not with two (tiles of 8 x 8, K = 13: 348 -> 374) nor at D = 128.
+// Four waves at D = 64 (window of 1024, S = 5000: 130 -> 124 us; canvas 100 x 90, K = 9, row-major: 349 -> 290; masks that hide a diagonal or nothing
+// too: causal, S = 520, 96 heads 18.1 -> 16.9, no mask, S = 100, 256 heads 12.2 -> 11.2, S = 1300, 42 heads 38.8 -> 37.2, but with a soft-cap, S = 1000,
+// 48 heads 41.2 -> 42.1), not with two (tiles of 8 x 8, K = 13: 348 -> 374) nor at D = 128.
 template <int D, int NW>
 constexpr bool dq_skips_hidden() {
     return D == 64 && NW == 4;
 }
-//
 // PAIRS: a workgroup takes 64 rows; the four waves are two slices of 32 rows times the two key halves of every tile, and the two waves
 // of the same rows add up at the end.  Two waves, one per slice, leave LDS for one (D = 128) or 2.5 (D = 64) waves per SIMD;
-// four that share the tiles make it two and three
-// (dq_pairs_pay has the times, and where the halves of rows of blocks of 128 take this form).  MIXED: some rows of blocks whole (dq_halved_rows).
+// four that share the tiles make it two and three (dq_pairs_pay has the times, and where the halves of rows of blocks of 128 take this form).  MIXED: some rows of blocks whole (dq_halved_rows).
 template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool CAPTURED = false, bool SKIP = dq_skips_hidden<D, NW>(), bool PAIRS = false, bool MIXED = false>
 __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kernel(const BwdArgs a) {
     static_assert(!PAIRS || (NW == 4 && SKIP), "two row slices times two key halves");

@@ -531,10 +531,13 @@ int dq_split_waves(const BwdArgs& a, int D) {
 // uneven rows, whose halves end a launch sooner.  us of the whole backward, without -> with: Bq = 64, D = 128, causal, S = 8192, 16
 // heads 950 -> 892, S = 512, 128 heads 85 -> 81, S = 300, 1024 heads 280 -> 284, window of 1024 546 -> 493, D = 64, S = 8192 527 -> 488, S = 835, 45 x
 // 32 heads 931 -> 885, S = 512 45 -> 48, documents, S = 16384, 16 heads 414 -> 373; Bq = 128, S x heads, D = 64, causal, 8192 x 16 532 -> 506, 2048 x 32
-// 104 -> 99, 16384 x 16 1952 -> 1905, 8192 x 32 1010 -> 1013, but 1024 x 256 188 -> 193, documents, 8192 x 8 131 -> 110, 16384 x 16 403 -> 392, but 8192 x 64 828
-// -> 844, D = 128, causal, 4096 x 16 294 -> 262, but 8192 x 16 909 -> 918, documents, 8192 x 8 184 -> 158, 8192 x 16 304 -> 301, but 16384 x 16 705 -> 736;
-// rows of one length, D = 64, no mask, 1500 x 32 89 -> 84, but 3000 x 32 267 -> 274; documents of 16 to 100, 8192 x 16, which the host cannot tell from
-// longer ones, D = 64 68 -> 72, D = 128 109 -> 119.
+// 104 -> 99, 16384 x 16 1952 -> 1905, 8192 x 32 1010 -> 1013, but 1024 x 256 188 -> 193, D = 128, causal, 4096 x 16 294 -> 262, but 8192 x 16 909 -> 918.
+// us of dQ, Bq = 128: documents of 256 to 4096, their longest rows in halves, 8192 x 16 99 -> 76, ALiBi, 16384 x 6 110 -> 74, 16384 x 16 180 -> 162, 2048 x 128
+// 132 -> 128, but 8192 x 64 345 -> 348, 16384 x 32 337 -> 348, D = 128, 4096 x 16 119 -> 78, 8192 x 12 127 -> 99, 16384 x 6 150 -> 121, but 16384 x 9 162 -> 168,
+// 16384 x 16 286 -> 304; of 16 to 100, which the host cannot tell from longer ones, 16384 x 6 21.9 -> 23.0, 2048 x 128 46.1 -> 47.2, D = 128, 8192 x 8 26.3 ->
+// 25.8; shorter or even rows at D = 64, causal, 1050 x 52 27.8 -> 26.9, 1600 x 36 39 -> 34, no mask, 1500 x 32 41 -> 38, 2000 x 20 49 -> 43, canvases, 64 x 64,
+// K = 21, 12 heads 50 -> 43, 32 x 32, K = 21, 48 heads 34 -> 29, but no mask, 1300 x 40 38 -> 45, 4000 x 14 97 -> 111,
+// row-major, K = 27, 16 heads 68 -> 80 (in tiles of 8 x 8 70 -> 60).
 template <uint32_t MASK>
 bool dq_pairs_pay(const BwdArgs& a, int D) {
     const LineShape rows = line_shape<MASK>(a.p, a.q_len, a.kv_len);
@@ -634,23 +637,6 @@ void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
     hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
 }
 
-// dQ at D = 64 with four waves: whether leaving hidden blocks out pays.  The test between the two blocks of a tile
-// keeps their work apart, which shows where at most two workgroups share a CU: masks that hide little more than a
-// diagonal are left out only beyond that (us, computed whole -> left out, causal: one sequence, S = 4096, 8 heads 58.8 ->
-// 64.1; S = 8192, 8 heads 131 -> 136; S = 2048, 2 x 16 heads 47.1 -> 47.2, 4 x 16 75.6 -> 75.9; S = 4096, 64 heads
-// 227.8 -> 222.9; S = 1024, 64 x 16 heads 298.6 -> 285.8).
-template <uint32_t MASK, uint32_t SCORE>
-void launch_dq64(const BwdArgs& a, unsigned grid, hipStream_t st) {
-    constexpr bool often = mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
-    if constexpr (!often) {
-        if (grid <= 2 * 256) {
-            hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, false>), dim3(grid), dim3(256), 0, st, a);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
-}
-
 template <uint32_t MASK, uint32_t SCORE>
 int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st) {
     const unsigned grid_kv = unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 64));
@@ -684,7 +670,7 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
             else hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, true, true>), pieces, dim3(256), 0, st, part);
         } else if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
         else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
-        else if (a.Bq == 128) launch_dq64<MASK, SCORE>(aq, grid_q, st);
+        else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
         else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
     };
     if (q && !a.dq_last) run_dq();
