@@ -69,10 +69,10 @@ constexpr int kTileKV = 64;   // keys per kernel tile
 // 64 heads: 158 -> 127; no mask, S = 2048: 89.5 -> 86.5; packed documents with ALiBi: 218 -> 216.
 // The pipelined one stays where it is the better one: a bounded soft-cap, whose softmax needs no running
 // maximum (287 -> 299); and, where neither a window, documents nor a canvas ends rows early, long rows on a chip that is not full and
-// soft-caps whose maximum has to be tracked (plain_pays; causal, S = 4096, 32 heads 132 <- 110, S = 8192, 16 heads 208 <- 196,
-// S = 4096, 64 heads 190 <- 200; cap of 100, S = 2048, 32 heads 64.6 <- 60.6, S = 8192, 64 heads 924 <- 904, S = 1024, 256 heads
-// 92.3 <- 94.7: plain <- pipelined), but rows of one length whose workgroups are the four per CU that
-// run at once (no mask, S = 4096, 32 heads 150 <- 154, S = 16384, 8 heads 574 <- 589, but 40 heads 189 <- 187, S = 8192, 10 heads 213 <- 208).  Neighborhood masks gain most: 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (490 ->
+// soft-caps whose maximum has to be tracked (plain_pays; plain / pipelined, S x heads: causal, 4096 x 36 126 / 120, 4096 x 48 136 / 151, 8192 x 20 238 /
+// 211, 16384 x 10 408 / 390, 4096 x 64 178 / 192, ALiBi, 4096 x 40 145 / 127; cap of 100, 2048 x 72 104 / 92, 8192 x 32 485 / 461, 1024 x 256 89.5 / 91.9), but
+// rows of one length whose workgroups are the four per CU that run at once (no mask, 4096 x 32 152 / 155, 16384 x 8 585 / 597, but 4096 x 40 193 / 190, 8192 x
+// 10 215 / 210).  Neighborhood masks gain most: 37 % of the 32 x 32 blocks of 8 x 8 tiles with K = 13 are hidden (490 ->
 // 340 at 128 x 128 pixels).
 template <int D, int NW, bool BOUNDED>
 constexpr bool fwd_plain() {
@@ -170,15 +170,17 @@ int split_waves(const FwdArgs& a, int D) {
 // 32 heads 641 -> 529 / 347 -> 296).  Rows of blocks of 128 where their halves end the launch sooner: rows of uneven length on a chip
 // that they do not fill for long, by the workgroups of 128 rows (us, a row of blocks -> pairs, S x heads: causal, D = 64, 8192 x 16
 // 189 -> 170, 4096 x 32 106 -> 98, 2048 x 64 65 -> 58, 16384 x 6 259 -> 257, but 16384 x 16 614 -> 627, 8192 x 64 622 -> 654, 1024 x 256 60 -> 62;
-// D = 128, 8192 x 8 173 -> 153, 4096 x 16 110 -> 83, 2048 x 32 60 -> 58, but 8192 x 16 279 -> 299, 16384 x 6 399 -> 446; documents of 256 to
-// 4096 with ALiBi, D = 64, 8192 x 16 92 -> 63, 16384 x 6 97 -> 63, 16384 x 16 156 -> 148, 8192 x 32 164 -> 143, 2048 x 128 108 -> 103, but 8192 x
-// 64 285 -> 283; D = 128, 4096 x 16 97 -> 65, 8192 x 8 77 -> 55, 16384 x 6 116 -> 95, but 8192 x 16 103 -> 102, 16384 x 16 218 -> 239; soft-cap, D = 64, 4096
-// x 32 142 -> 123, but 8192 x 16 246 -> 252).  Of one length, long rows at D = 64 while there are at most two workgroups per CU (no mask, S = 1500,
-// 32 heads 33.5 -> 29.4, chunks of 640 on 2000 to 3000 cached keys, 2 x 32 heads 69 -> 58, of 1500 on 8000, 32 heads 189 -> 168; but no mask, S = 3000, 32
-// heads 88 -> 95, window of 500, S = 4096, 32 heads 31 -> 36; D = 128, S = 1500, 32 heads 51 -> 53).
-// Documents of a few tokens, which the host cannot tell from long ones, pay for the halves' starts (Bq = 128, 8192 x 16, of 16 to 100 D = 64
-// 20.0 -> 23.3, D = 128 36.6 -> 37.5, of 100 to 400 25.8 -> 25.0, 41.0 -> 40.9); a workgroup that takes such a row whole while the other
-// half's ends at once is slower yet (27.7: it waits for its place and its counts like any other).
+// D = 128, 8192 x 8 173 -> 153, 4096 x 16 110 -> 83, 2048 x 32 60 -> 58, but 8192 x 16 279 -> 299, 16384 x 6 399 -> 446; soft-cap, D = 64, 4096
+// x 32 142 -> 123, but 8192 x 16 246 -> 252; documents of 256 to 4096 with ALiBi, their longest rows in halves (halved_rows), D = 64, 8192 x 16 92 -> 63, 16384 x
+// 6 96 -> 67, 16384 x 16 146 -> 132, 8192 x 32 165 -> 141, 2048 x 128 111 -> 103, but 8192 x 64 279 -> 272 and of 100 to 400 77 -> 81; D = 128, 4096 x 16
+// 95 -> 64, 8192 x 8 75 -> 58, 16384 x 6 117 -> 97, but 8192 x 16 100 -> 102, 16384 x 9 126 -> 135, without ALiBi 16384 x 16 214 -> 228).
+// Rows of one length, or shorter than 2048: long ones at D = 64 while there are at most two workgroups per CU
+// (no mask, 1500 x 32 33 -> 29, 4000 x 12 75 -> 63, even from one and a half on, 1500 x 36 35.6 -> 34.1, 1500 x 40 33.6 -> 34.8, but 3000 x 32 88 -> 95; chunks of 640 on 2000 to 3000 cached
+// keys, 2 x 32 heads 69 -> 58, 2 x 48 78 -> 75, of 1500 on 8000, 32 heads 189 -> 168; windows, 2048 x 28, of 1024 25.8 -> 24.3, 4096 x 16, of 2048 45 -> 45, but
+// 4096 x 32, of 500 31 -> 36; window of 1500 or prefix of 200 with a relative bias, 4096 x 16 50 -> 43; canvases, 32 x 32, K = 21, 48 heads 28.7 -> 23.6, 64 x 64,
+// K = 27, 13 heads 50 -> 36, Morton order, K = 21, 16 heads 51 -> 40; causal, 1050 x 52 20.6 -> 20.4, 1600 x 36 29 -> 26, ALiBi, 2000 x 30 45 -> 37, soft-cap, 1600
+// x 36 40 -> 32; D = 128, no mask, 1500 x 32 51 -> 53).
+// Documents of a few tokens, which the host cannot tell from long ones, pay a little (8192 x 16, of 16 to 100 19.7 -> 20.8).
 template <uint32_t MASK, bool BOUNDED>
 bool pairs_pay(const FwdArgs& a, int D, unsigned grid) {
     if (a.Bq == 64) return true;
