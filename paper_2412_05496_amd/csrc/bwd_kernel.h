@@ -728,7 +728,8 @@ constexpr bool dq_skips_hidden() {
 }
 // PAIRS: a workgroup takes 64 rows; the four waves are two slices of 32 rows times the two key halves of every tile, and the two waves
 // of the same rows add up at the end.  Two waves, one per slice, leave LDS for one (D = 128) or 2.5 (D = 64) waves per SIMD;
-// four that share the tiles make it two and three (dq_pairs_pay has the times, and where the halves of rows of blocks of 128 take this form).  MIXED: some rows of blocks whole (dq_halved_rows).
+// four that share the tiles make it two and three (dq_pairs_pay has the times, and where the halves of rows of blocks of 128 take this form).
+// MIXED: some rows of blocks whole (dq_halved_rows).
 template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool CAPTURED = false, bool SKIP = dq_skips_hidden<D, NW>(), bool PAIRS = false, bool MIXED = false>
 __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kernel(const BwdArgs a) {
     static_assert(!PAIRS || (NW == 4 && SKIP), "two row slices times two key halves");

@@ -174,12 +174,12 @@ int split_waves(const FwdArgs& a, int D) {
 // x 32 142 -> 123, but 8192 x 16 246 -> 252; documents of 256 to 4096 with ALiBi, their longest rows in halves (halved_rows), D = 64, 8192 x 16 92 -> 63, 16384 x
 // 6 96 -> 67, 16384 x 16 146 -> 132, 8192 x 32 165 -> 141, 2048 x 128 111 -> 103, but 8192 x 64 279 -> 272 and of 100 to 400 77 -> 81; D = 128, 4096 x 16
 // 95 -> 64, 8192 x 8 75 -> 58, 16384 x 6 117 -> 97, but 8192 x 16 100 -> 102, 16384 x 9 126 -> 135, without ALiBi 16384 x 16 214 -> 228).
-// Rows of one length, or shorter than 2048: long ones at D = 64 while there are at most two workgroups per CU
-// (no mask, 1500 x 32 33 -> 29, 4000 x 12 75 -> 63, even from one and a half on, 1500 x 36 35.6 -> 34.1, 1500 x 40 33.6 -> 34.8, but 3000 x 32 88 -> 95; chunks of 640 on 2000 to 3000 cached
-// keys, 2 x 32 heads 69 -> 58, 2 x 48 78 -> 75, of 1500 on 8000, 32 heads 189 -> 168; windows, 2048 x 28, of 1024 25.8 -> 24.3, 4096 x 16, of 2048 45 -> 45, but
-// 4096 x 32, of 500 31 -> 36; window of 1500 or prefix of 200 with a relative bias, 4096 x 16 50 -> 43; canvases, 32 x 32, K = 21, 48 heads 28.7 -> 23.6, 64 x 64,
-// K = 27, 13 heads 50 -> 36, Morton order, K = 21, 16 heads 51 -> 40; causal, 1050 x 52 20.6 -> 20.4, 1600 x 36 29 -> 26, ALiBi, 2000 x 30 45 -> 37, soft-cap, 1600
-// x 36 40 -> 32; D = 128, no mask, 1500 x 32 51 -> 53).
+// Rows of one length, or shorter than 2048: long ones at D = 64 while there are at most two workgroups per CU (no mask, 1500 x 32 33 -> 29, 4000 x 12 75 -> 63,
+// even from one and a half on, 1500 x 36 35.6 -> 34.1, 1500 x 40 33.6 -> 34.8, but 3000 x 32 88 -> 95; chunks of 640 on 2000 to 3000 cached keys, 2 x 32 heads
+// 69 -> 58, 2 x 48 78 -> 75, of 1500 on 8000, 32 heads 189 -> 168; windows, 2048 x 28, of 1024 25.8 -> 24.3, 4096 x 16, of 2048 45 -> 45, but 4096 x 32, of 500
+// 31 -> 36; window of 1500 or prefix of 200 with a relative bias, 4096 x 16 50 -> 43; canvases, 32 x 32, K = 21, 48 heads 28.7 -> 23.6, 64 x 64, K = 27, 13 heads
+// 50 -> 36, Morton order, K = 21, 16 heads 51 -> 40; causal, 1050 x 52 20.6 -> 20.4, 1600 x 36 29 -> 26, ALiBi, 2000 x 30 45 -> 37, soft-cap, 1600 x 36 40 -> 32;
+// D = 128, no mask, 1500 x 32 51 -> 53).
 // Documents of a few tokens, which the host cannot tell from long ones, pay a little (8192 x 16, of 16 to 100 19.7 -> 20.8).
 template <uint32_t MASK, bool BOUNDED>
 bool pairs_pay(const FwdArgs& a, int D, unsigned grid) {
