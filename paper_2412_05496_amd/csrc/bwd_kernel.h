@@ -67,6 +67,7 @@ struct BwdArgs {
     bool make_delta;           // the dQ kernel works the row scalars out itself (and writes them)
     bool dq_last;              // (host) dQ is written over what dK/dV or the row scalars are made of: it runs last, after a pass for the latter
     int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
+    UnitSets abreast;      // of the launch (unit_of_workgroup)
 };
 
 constexpr uint32_t kBwdStageCaptured = 8u;   // internal: the captured-tensor sums instead of dQ
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     // head where the mask has a plane per head), the 64-key tiles of a column side by side.
     const int sub_k = a.Bk / 64;                   // tiles per column of blocks
     int unit, slot;                                // NC * sub_k slots >= tiles: the last column may be cut short
-    if (!unit_of_workgroup(a.B * a.Hkv, a.NC * sub_k, unit, slot)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.NC * sub_k, a.abreast, unit, slot)) return;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     int col = slot / sub_k;
     if (a.q_order) {
@@ -747,7 +748,9 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     __shared__ uint8_t s_hidden[Mask::kCanvas && SKIP ? kHiddenTiles : 1];           // CanvasBlocks::hidden_bits of the first tiles
 
     int unit, rem;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.G * (MIXED ? a.NR + a.halved : a.NR * (PAIRS ? Bq / 64 : 1)), unit, rem)) return;
+    UnitSets abreast = a.abreast;
+    if constexpr (Mask::kDoc) abreast = abreast_if_long(abreast, a.B * a.Hkv, longest_row(a.kv_order, a.full_kv_num, a.kv_num, 0, a.NR, a.Bk / 64));
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * (MIXED ? a.NR + a.halved : a.NR * (PAIRS ? Bq / 64 : 1)), abreast, unit, rem)) return;
     int slice = 0;                                                   // PAIRS: which 64 rows of the block
     bool whole = false;                                              // MIXED: 32 rows and all keys to a wave
     if constexpr (MIXED) {

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(
     __shared__ uint8_t s_hidden[Mask::kCanvas ? kHiddenTiles : 1];
 
     int unit, rem;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (a.Bq / 32), unit, rem)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (a.Bq / 32), a.abreast, unit, rem)) return;
     const int slice = rem & (a.Bq / 32 - 1);
     rem >>= a.Bq == 128 ? 2 : 1;
     const int g = rem % a.G;
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
 
     const int parts = a.Bk / 32;
     int unit, slot_rank;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.NC * parts, unit, slot_rank)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.NC * parts, a.abreast, unit, slot_rank)) return;
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     int col = slot_rank / parts;
     if (a.q_order) {
@@ -638,7 +638,12 @@ void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
 }
 
 template <uint32_t MASK, uint32_t SCORE>
-int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st) {
+int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t st) {
+    BwdArgs a = args;
+    const int units = a.B * a.Hkv;
+    const bool uneven = line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven;
+    auto rows_by = [&](int rows) { return units_abreast(units, a.G * rows, bwd_waves_per_simd_of(D), rows_abreast<MASK>(uneven, D)); };
+    a.abreast = one_by_one(units);
     const unsigned grid_kv = unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 64));
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
@@ -663,15 +668,19 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
             const bool mixed = can_mix && a.Bq == 128;
             BwdArgs part = aq;
             part.halved = a.Bq == 64 ? 0 : mixed ? dq_halved_rows(D, a.NR, grid_q) : a.NR;
+            part.abreast = rows_by(a.NR + part.halved);
             const dim3 pieces(unit_grid(a.B * a.Hkv, a.G * (a.NR + part.halved)));
             if (D == 128 && mixed) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, false, true, true, can_mix>), pieces, dim3(256), 0, st, part);
             else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, false, true, true>), pieces, dim3(256), 0, st, part);
             else if (mixed) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, true, true, can_mix>), pieces, dim3(256), 0, st, part);
             else hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, false, true, true>), pieces, dim3(256), 0, st, part);
-        } else if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
-        else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
-        else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
-        else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
+        } else {
+            aq.abreast = rows_by(a.NR);
+            if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
+            else if (D == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
+            else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE>), dim3(grid_q), dim3(256), 0, st, aq);
+            else hipLaunchKernelGGL((bwd_dq_kernel<64, 2, MASK, SCORE>), dim3(grid_q), dim3(128), 0, st, aq);
+        }
     };
     if (q && !a.dq_last) run_dq();
     if (kv) {
@@ -681,11 +690,16 @@ int launch_bwd_variant(const BwdArgs& a, int D, uint32_t stages, hipStream_t st)
             if (D == 128) hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 4, MASK, SCORE>), slices, dim3(256), 0, st, a);
             else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 8, MASK, SCORE>), slices, dim3(512), 0, st, a);
             else hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 4, MASK, SCORE>), slices, dim3(256), 0, st, a);
-        } else if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, a);
-        else launch_dkdv64<MASK, SCORE>(a, grid_kv, st);
+        } else {
+            BwdArgs akv = a;
+            akv.abreast = units_abreast(units, a.NC * (a.Bk / 64), bwd_waves_per_simd_of(D), uneven && !mask_uses(MASK, FLEXATTN_M_DOCUMENT) ? kColumnsAbreast : 1);
+            if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, akv);
+            else launch_dkdv64<MASK, SCORE>(akv, grid_kv, st);
+        }
     }
     if (q && a.dq_last) run_dq();
     if (stages & kBwdStageCaptured) {
+        a.abreast = rows_by(a.NR);
         if constexpr ((SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS)) != 0) {
             if (D == 128 && a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<128, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);
             else if (a.Bq == 128) hipLaunchKernelGGL((bwd_dq_kernel<64, 4, MASK, SCORE, true>), dim3(grid_q), dim3(256), 0, st, a);

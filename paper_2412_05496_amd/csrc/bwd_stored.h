@@ -121,7 +121,7 @@ __global__ __launch_bounds__(NW * 64 * HEADS * ROWS, 2) void bwd_dq_stored_kerne
     int unit, rem;
     const int groups = a.G / HEADS;
     const int row_sets = (a.NR + ROWS - 1) / ROWS;
-    if (!unit_of_workgroup(a.B * a.Hkv, groups * row_sets, unit, rem)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv, groups * row_sets, a.abreast, unit, rem)) return;
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), w = wave & (NW - 1);
     const int g = (rem % groups) * HEADS + (ROWS > 1 ? 0 : wave / NW);
@@ -340,8 +340,10 @@ __global__ __launch_bounds__(NW * 64 * HEADS * ROWS, 2) void bwd_dq_stored_kerne
 
 enum class StoredShare { kNone, kHeads, kRows };     // (stored_share; D = 128, Bq = 128)
 template <bool CANVAS>
-int launch_bwd_stored_dq(const BwdArgs& a, int D, float qscale, StoredShare share, hipStream_t st) {
+int launch_bwd_stored_dq(const BwdArgs& args, int D, float qscale, StoredShare share, bool uneven, hipStream_t st) {
+    BwdArgs a = args;
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
+    a.abreast = units_abreast(a.B * a.Hkv, share == StoredShare::kNone ? a.G * a.NR : a.G * ((a.NR + 1) / 2), share != StoredShare::kNone ? 1 : bwd_waves_per_simd_of(D), uneven ? kRowsAbreast : 1);
     if constexpr (!CANVAS) {
         if (share == StoredShare::kHeads) {         // (an even number of heads to a group, one plane for all)
             hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 4, false, 2>), dim3(unit_grid(a.B * a.Hkv, a.G / 2 * a.NR)), dim3(512), 0, st, a, qscale);

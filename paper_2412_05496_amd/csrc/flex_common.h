@@ -222,6 +222,11 @@ struct NoCanvas {
     __device__ __forceinline__ void pixel(int, int&, int&) const {}
 };
 
+// Of the eighth of a launch's units that an XCD takes (whole ones): `sets` sets, one after the other, of 2^side units whose
+// pieces take turns (the last set: and what is left over).
+struct UnitSets {
+    int side, sets;
+};
 // Workgroup -> (unit, rank): which KV head of which batch entry, and which of its per_unit pieces (longest first).
 // Workgroup ids go to the 8 XCDs in turn.  Eight units at a time, a unit's pieces all go to one XCD, so that its K and V
 // stay in that XCD's L2.  The 1 .. 7 units beyond a multiple of eight come first and are cut into eighths, every eighth
@@ -231,13 +236,20 @@ struct NoCanvas {
 // us, that -> this, causal: S = 16384, D = 128, 1 head, forward 472 -> 289, dK/dV 832 -> 269, dQ 574 -> 326; 3 heads, D = 64,
 // 309 -> 213, 537 -> 262, 371 -> 238; S = 8192, D = 128, 16 query and 2 KV heads 874 -> 285, 1855 -> 1074, 1064 -> 369; S = 4096, 9
 // heads, D = 64, 76 -> 54, 82 -> 61, 83 -> 61, D = 128, 105 -> 80, 130 -> 93, 130 -> 92; 8 and 16 heads the same within 2 %.)
-__device__ __forceinline__ bool unit_of_workgroup(unsigned id, int units, int per_unit, int& unit, int& rank) {
+// The units of a set take turns piece by piece, so that the long pieces of all start before the short ones (units_abreast).
+__device__ __forceinline__ bool unit_of_workgroup(unsigned id, int units, int per_unit, UnitSets abreast, int& unit, int& rank) {
     const int xcd = id & 7, rest = units & 7, rest_pieces = rest * ((per_unit + 7) >> 3);
     const int k = id >> 3;
     if (k >= rest_pieces) {
-        const int u = (k - rest_pieces) / per_unit;
-        unit = u * 8 + xcd;
-        rank = k - rest_pieces - u * per_unit;
+        const int p = k - rest_pieces, set = min(p / per_unit >> abreast.side, abreast.sets - 1);
+        const int first = set << abreast.side, in = p - first * per_unit;
+        int of = in >> abreast.side, turn = in & ((1 << abreast.side) - 1);
+        if (const int last = (units >> 3) - first; set + 1 == abreast.sets && last != 1 << abreast.side) {
+            of = in / last;
+            turn = in - of * last;
+        }
+        unit = (first + turn) * 8 + xcd;
+        rank = of;
         return true;
     }
     const int round = k / rest, eighth = xcd * rest + k - round * rest;
@@ -245,8 +257,28 @@ __device__ __forceinline__ bool unit_of_workgroup(unsigned id, int units, int pe
     rank = 8 * round + (eighth & 7);
     return rank < per_unit;
 }
-__device__ __forceinline__ bool unit_of_workgroup(int units, int per_unit, int& unit, int& rank) {
-    return unit_of_workgroup(blockIdx.x, units, per_unit, unit, rank);
+__device__ __forceinline__ bool unit_of_workgroup(int units, int per_unit, UnitSets abreast, int& unit, int& rank) {
+    return unit_of_workgroup(blockIdx.x, units, per_unit, abreast, unit, rank);
+}
+__host__ __device__ inline UnitSets one_by_one(int units) { return {0, units >= 8 ? units >> 3 : 1}; }
+// How many units take turns.  Pieces of uneven length end a launch sooner if the short ones of many units come last, and units that
+// a set's workgroups hold at once share the XCD's L2 all the same.  So: as many as make two rounds of the XCD's workgroups (per_cu of them on each of 32 CUs),
+// at most 8 (rows), 4 (columns: dK/dV, S = 1024, 1024 heads, 436 one by one, 417 four, 429 eight, 468 all): with more, a unit's K and V
+// have left L2 before its next piece.  Rows of one length gain nothing, and a unit that fills the XCD by itself loses the lockstep in which its
+// workgroups stream K and V (chunks of 2048 on 4096 .. 14336 cached keys, 4 x 32 / 8 heads, 1277 -> 1571 with four): one by one.
+// us, one by one -> so (one MI355X), causal: forward / dQ / dK/dV, D = 64, S = 1024 x 1024 heads 219 -> 202 / 284 -> 263 / 436 -> 417, 1024 x 256 60 -> 51 / 78 -> 64 /
+// 109 -> 102, 2048 x 256 178 -> 165 / 238 -> 217 / 344 -> 336, 4096 x 64 181 -> 153 / 231 -> 219 / 317 -> 298, 8192 x 64 635 -> 577 / 821 -> 764 / 1145 -> 1122, 1500 x 40
+// 27 -> 22 / 32 -> 27 / 42 -> 35, 200 x 2048 43 -> 43 / 57 -> 54 / 128 -> 112, soft-cap, 1024 x 256 86 -> 68 / 113 -> 89 / 125 -> 117, 16 / 4 heads, 2048 x 128
+// 92 -> 83 / 122 -> 121 / 189 -> 156; D = 128, 1024 x 256 113 -> 98 / 150 -> 135 / 224 -> 215, 2048 x 128 174 -> 157 / 230 -> 210 / 337 -> 328, 8192 x 32 552 -> 532 /
+// 741 -> 710 / 1069 -> 1081; the captured sums of ALiBi, D = 64, 2048 x 64 82 -> 60; documents of 256 to 4096, D = 64, 8192 x 64 244 -> 218 / 302 -> 273 (columns gain
+// nothing: 407), D = 128, 4096 x 64 224 -> 189 / 286 -> 252; windows of 512, D = 64, 4096 x 64 54 -> 53 / 69 -> 67.
+constexpr int kRowsAbreast = 8, kColumnsAbreast = 4;
+inline UnitSets units_abreast(int units, int per_unit, int per_cu, int most) {
+    const int mine = units >> 3, round = 32 * per_cu;
+    const int limit = per_unit < 4 && most > 4 ? 4 : most;      // (24 workgroups to a set: 32 CUs are dealt them unevenly, dQ, 300 x 512 26 -> 27)
+    int side = 0;
+    while (2 << side <= limit && 2 << side <= mine && (int64_t)per_unit << side < 2 * round) ++side;
+    return {side, mine > 0 ? mine >> side : 1};
 }
 inline unsigned unit_grid(int units, int per_unit) {
     return 8u * ((unsigned)(units >> 3) * (unsigned)per_unit + (unsigned)(units & 7) * (unsigned)((per_unit + 7) / 8));
@@ -255,13 +287,24 @@ inline unsigned unit_grid(int units, int per_unit) {
 // What may need more takes several launches of at most this many.
 constexpr unsigned kMaxLaunch = 1u << 23;
 
+// Tiles of the longest row of blocks (the first in work order) of a plane whose rows start at plane_rows.
+__device__ __forceinline__ int longest_row(const int32_t* order, const int32_t* full_num, const int32_t* part_num, int64_t plane_rows, int NR, int sub) {
+    const int64_t longest = plane_rows + (order ? min(max(ldc(order + plane_rows), 0), NR - 1) : NR - 1);
+    return (ldc(full_num + longest) + ldc(part_num + longest)) * sub;
+}
+// Documents of a few hundred tokens, which the host cannot tell from longer ones, head by head: their rows are bound by K and V, which then stay
+// in L2 (D = 64, 8192 x 64, us, head by head / abreast: of 30 to 300 tokens, forward 61 / 67, dQ 85 / 91, of 100 to 1000 95 / 95, 130 / 133, of 256 to 4096
+// 249 / 223, 304 / 278).  By the longest row of the launch's first plane, which all workgroups ask alike.
+constexpr int kAbreastTiles = 24;
+__device__ __forceinline__ UnitSets abreast_if_long(UnitSets abreast, int units, int longest) {
+    return longest > kAbreastTiles ? abreast : one_by_one(units);
+}
 // Workgroups that take either a row of blocks of 128 rows as a whole or one of its halves (MIXED in the forward and dQ): the first `halved` ranks in
 // halves, but where the longest row of the unit's first plane (the first in work order) is short, none; the ids that are left over then are the
 // last.  rem: the piece of a unit (G query heads) of G * (NR + halved) -> the piece of G * NR rows.  False: nothing to do.
 __device__ __forceinline__ bool half_or_row(const int32_t* order, const int32_t* full_num, const int32_t* part_num, int64_t plane_rows, int NR, int G,
                                             int sub, int halved, int short_tiles, int& rem, int& slice, bool& whole) {
-    const int64_t longest = plane_rows + (order ? min(max(ldc(order + plane_rows), 0), NR - 1) : NR - 1);
-    const int halves = (ldc(full_num + longest) + ldc(part_num + longest)) * sub > short_tiles ? 2 * halved * G : 0;
+    const int halves = longest_row(order, full_num, part_num, plane_rows, NR, sub) > short_tiles ? 2 * halved * G : 0;
     if (rem - (halves >> 1) >= NR * G) return false;
     whole = rem >= halves;
     slice = whole ? 0 : rem & 1;
@@ -790,9 +833,10 @@ struct ScoreMod {
 
 // Waves per SIMD the backward kernels are compiled for: at D = 64 they fit 168 registers, so three workgroups
 // share a CU (more latency hiding, more chances for one wave's MFMAs to run beside another's VALU work).
+constexpr int bwd_waves_per_simd_of(int D) { return D == 64 ? 3 : 2; }
 template <int D>
 constexpr int bwd_waves_per_simd() {
-    return D == 64 ? 3 : 2;
+    return bwd_waves_per_simd_of(D);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -812,6 +856,7 @@ void set_last_hip_error(int e);
 inline bool mask_id_valid(uint32_t m) {
     return (m & ~0x3f3fu) == 0 && !((m & 0xffu) == 0 && (m >> 8) != 0);
 }
+constexpr bool mask_uses(uint32_t m, uint32_t prim) { return ((m | (m >> 8)) & prim) != 0; }
 // What the host can tell of the rows of a mask: how many keys the longest see, and whether others see far fewer (so that
 // a launch of few rows ends with the longest alone); and how many they see at least, for rules that must not make short rows slower.
 // A row of packed documents may see a tile or two whatever the batch's length, a row of a canvas about the pixels around 64.
@@ -842,8 +887,13 @@ template <uint32_t MASK>
 LineShape line_shape(const flexattn_mod_params& p, int q_len, int kv_len) {
     return line_shape(MASK, p, q_len, kv_len);
 }
+// units_abreast's limit for the rows of a mask: of uneven length, or, at D = 64, windows, whose first rows are shorter than the others (at D = 128
+// window of 512, 4096 x 64: dQ 141 -> 146)
+template <uint32_t MASK>
+int rows_abreast(bool uneven, int D) {
+    return uneven || (D == 64 && mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) && !mask_uses(MASK, FLEXATTN_M_PREFIX)) ? kRowsAbreast : 1;
+}
 inline bool score_id_valid(uint32_t s) { return (s & ~7u) == 0; }
-constexpr bool mask_uses(uint32_t m, uint32_t prim) { return ((m | (m >> 8)) & prim) != 0; }
 
 // Pointers the selected mods will dereference must be present.
 inline int check_mod_params(uint32_t mask_id, uint32_t score_id, const flexattn_mod_params* p) {

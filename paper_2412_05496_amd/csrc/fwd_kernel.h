@@ -58,6 +58,7 @@ struct FwdArgs {
     int Bq;                // rows of a BlockMask block
     unsigned first_id;     // PAIRS: of the launch's workgroups, where there are several launches (kMaxLaunch)
     int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
+    UnitSets abreast;      // of the launch (unit_of_workgroup)
 };
 
 constexpr int kTileKV = 64;   // keys per kernel tile
@@ -249,7 +250,9 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     // last-first without one (causal-like masks: longest first).
     int unit, rem, slice = 0;
     const int per_unit = a.G * (MIXED ? a.NR + a.halved : a.NR * (SPLIT ? Bq / 32 : PAIRS ? Bq / 64 : 1));
-    if (!unit_of_workgroup(blockIdx.x + (PAIRS ? a.first_id : 0u), a.B * a.Hkv, per_unit, unit, rem)) return;
+    UnitSets abreast = a.abreast;
+    if constexpr (Mask::kDoc && !SPLIT) abreast = abreast_if_long(abreast, a.B * a.Hkv, longest_row(a.kv_order, a.full_num, a.kv_num, 0, a.NR, a.sub));
+    if (!unit_of_workgroup(blockIdx.x + (PAIRS ? a.first_id : 0u), a.B * a.Hkv, per_unit, abreast, unit, rem)) return;
     if constexpr (SPLIT) {
         slice = rem & (Bq / 32 - 1);                // which 32 rows of the block
         rem >>= Bq == 128 ? 2 : 1;
@@ -969,8 +972,12 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 }
 
 template <uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED>
-int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
+int launch_fwd_shape(const FwdArgs& args, int D, int Bq, hipStream_t st) {
+    FwdArgs a = args;
     const unsigned grid = unit_grid(a.B * a.Hkv, a.G * a.NR);
+    const bool uneven = line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven;
+    auto order_units = [&](int rows, int per_cu) { a.abreast = units_abreast(a.B * a.Hkv, a.G * rows, per_cu, rows_abreast<MASK>(uneven, D)); };
+    a.abreast = one_by_one(a.B * a.Hkv);
     if (const int waves = split_waves<MASK, SCORE>(a, D)) {
         const dim3 slices(unit_grid(a.B * a.Hkv, a.G * a.NR * (Bq / 32)));
         if (D == 128 && waves == 8) hipLaunchKernelGGL((fwd_kernel<128, 8, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(512), 0, st, a);
@@ -982,15 +989,15 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
     if (pairs_pay<MASK, BOUNDED>(a, D, grid)) {
         constexpr bool mixed64 = mixed_pays<64, MASK, SCORE, BOUNDED>(), mixed128 = mixed_pays<128, MASK, SCORE, BOUNDED>();
         const bool mixed = Bq == 128 && (D == 64 ? mixed64 : mixed128);
-        FwdArgs part = a;
-        part.halved = Bq == 64 ? 0 : mixed ? halved_rows(a.NR) : a.NR;
-        const unsigned pieces = unit_grid(a.B * a.Hkv, a.G * (a.NR + part.halved));
-        for (part.first_id = 0; part.first_id < pieces; part.first_id += kMaxLaunch) {
-            const dim3 ids(min(pieces - part.first_id, kMaxLaunch));
-            if (D == 128 && mixed) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true, mixed128>), ids, dim3(256), 0, st, part);
-            else if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, part);
-            else if (mixed) hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true, mixed64>), ids, dim3(256), 0, st, part);
-            else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, part);
+        a.halved = Bq == 64 ? 0 : mixed ? halved_rows(a.NR) : a.NR;
+        order_units(a.NR + a.halved, D == 64 ? 4 : 2);
+        const unsigned pieces = unit_grid(a.B * a.Hkv, a.G * (a.NR + a.halved));
+        for (a.first_id = 0; a.first_id < pieces; a.first_id += kMaxLaunch) {
+            const dim3 ids(min(pieces - a.first_id, kMaxLaunch));
+            if (D == 128 && mixed) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true, mixed128>), ids, dim3(256), 0, st, a);
+            else if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, a);
+            else if (mixed) hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true, mixed64>), ids, dim3(256), 0, st, a);
+            else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, a);
         }
         return FLEXATTN_OK;
     }
@@ -1000,20 +1007,24 @@ int launch_fwd_shape(const FwdArgs& a, int D, int Bq, hipStream_t st) {
     if (D == 128 && Bq == 128) {
         if constexpr (fwd_units<128, 4, MASK, SCORE>() != FwdUnits::kNever) {
             if (units_pay<MASK, SCORE>(a, grid)) {
+                order_units(a.NR, 3);
                 hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, true>), dim3(grid), dim3(256), 0, st, a);
                 return FLEXATTN_OK;
             }
         }
+        order_units(a.NR, 2);
         FLEXATTN_LAUNCH(128, 4)
     }
     if (D == 64 && Bq == 128) {
         constexpr bool dense = !mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
         if constexpr (fwd_plain<64, 4, BOUNDED>() && dense) {
-            if (!plain_pays<SCORE>(a.kv_len, grid, line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven)) {
+            if (!plain_pays<SCORE>(a.kv_len, grid, uneven)) {
+                order_units(a.NR, 3);
                 hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false>), dim3(grid), dim3(256), 0, st, a);
                 return FLEXATTN_OK;
             }
         }
+        order_units(a.NR, 4);
         FLEXATTN_LAUNCH(64, 4)
     }
 #undef FLEXATTN_LAUNCH
