@@ -983,9 +983,11 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
             if constexpr (CAPTURED) {
                 const int kvs = kvs_blk;
                 if constexpr (ScoreMod<SCORE>::kAlibi) {
+                    // (integers below 2^24: the differences are exact, in one instruction instead of a subtraction and a conversion.  us: causal,
+                    // S = 4096, 32 heads, D = 64 / 128 104 -> 99 / 167 -> 158, packed documents, S = 16384, D = 64 177 -> 168)
+                    const float first = (float)dq0;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        g_alibi = __builtin_fmaf(dpacc[r], (float)(q_pos - (kvs + crow(r, half))), g_alibi);
+                    for (int r = 0; r < 16; ++r) g_alibi = __builtin_fmaf(dpacc[r], first - (float)elem_pos(r), g_alibi);
                 }
                 if constexpr (ScoreMod<SCORE>::kRel) {
                     if (q_wave_min - (kvs + 31) >= smod.rel_max) {          // every pair on the last entry
