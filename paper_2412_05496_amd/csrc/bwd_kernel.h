@@ -68,6 +68,41 @@ struct BwdArgs {
     bool dq_last;              // (host) dQ is written over what dK/dV or the row scalars are made of: it runs last, after a pass for the latter
     int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
     UnitSets abreast;      // of the launch (unit_of_workgroup)
+    int head_parts;        // dK/dV: workgroups among which the query heads of a group are divided (kv_head_parts)
+    float* kv_part;        //        more than one: their sums, [head_parts][dV, dK][B, Hkv, kv_len, D] (host: where there is room for them, or null)
+};
+
+// Among how many workgroups the query heads of a group are divided.  One that takes them all walks G times the steps of a column: few KV heads
+// leave most of the chip idle, and end with the longest column alone.  A part costs its sums in fp32, 128 bytes a key and D / 16 each way, and all a launch that
+// adds them up (3 us).  So: up to 768 workgroups (D = 64: all that run at once), of parts that have 48 steps of 64 rows or more in the longest column (D = 128: 32, whose steps are longer),
+// or 12 (4) while they are no more than half of the CUs.  us, dK/dV, whole groups -> this, S x query / KV heads, causal: D = 64, 4096 x 8 / 1 136 -> 54, 1500 x 16 / 2
+// 59 -> 34, 3000 x 32 / 4 114 -> 106, 12000 x 16 / 2 811 -> 702, 700 x 8 / 1 35 -> 17; D = 128, 1500 x 8 / 1 126 -> 42, 3000 x 16 / 2 241 -> 99, 700 x 64 / 8 70 -> 67,
+// 3000 x 4 / 1 125 -> 44, 6000 x 8 / 4 221 -> 166; documents, 6000 x 16 / 2, D = 64 227 -> 122, D = 128 477 -> 190; no mask, D = 128, 6000 x 16 / 2 863 -> 602; window of
+// 1000, D = 64, 6000 x 32 / 4 162 -> 129.  More parts: 1500 x 32 x 8 / 1, D = 128, two 375, whole 342; window of 1024, 4 x 5000 x 16 / 2, D = 64, two 208, whole 198, no mask, 12653 x 8 / 2, two 843, whole 797;
+// shorter ones: 300 x 2 / 1, D = 64 14.4, whole 11.2.  Over 444 launches (masks as above, groups of 2, 4, 8, up to 64 KV heads, S = 300 to 12000) three are slower than
+// whole, by 2 to 7 %; all together they are 1.14 (D = 64) and 1.27 times as fast.
+inline int kv_head_parts(int64_t units, int G, int kv_len, int D, int64_t longest_column) {
+    const int64_t tiles = units * ((kv_len + 63) / 64), steps = (longest_column + 63) / 64 * G;
+    int parts = 1;
+    for (int p = 2; p <= G && p <= 8 && tiles * p <= 768; p *= 2)
+        if (steps >= (int64_t)p * (tiles * p <= 128 ? (D == 64 ? 12 : 4) : (D == 64 ? 48 : 32))) parts = p;
+    return parts;
+}
+// The query heads of a group that a dK/dV workgroup takes, and where their sums go.
+struct KvHeads {
+    int part, first, end;
+    // unit: (b, hkv, part) -> (b, hkv)
+    __device__ __forceinline__ KvHeads(const BwdArgs& a, int& unit) : part(0), first(0), end(a.G) {
+        if (a.head_parts > 1) {
+            part = unit % a.head_parts;
+            unit /= a.head_parts;
+            first = part * a.G / a.head_parts;
+            end = (part + 1) * a.G / a.head_parts;
+        }
+    }
+    __device__ __forceinline__ float* sums(const BwdArgs& a, int unit, int is_k, int D) const {
+        return a.kv_part + (((int64_t)(2 * part + is_k) * a.B * a.Hkv + unit) * a.kv_len) * D;
+    }
 };
 
 constexpr uint32_t kBwdStageCaptured = 8u;   // internal: the captured-tensor sums instead of dQ
@@ -223,7 +258,8 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     // head where the mask has a plane per head), the 64-key tiles of a column side by side.
     const int sub_k = a.Bk / 64;                   // tiles per column of blocks
     int unit, slot;                                // NC * sub_k slots >= tiles: the last column may be cut short
-    if (!unit_of_workgroup(a.B * a.Hkv, a.NC * sub_k, a.abreast, unit, slot)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv * a.head_parts, a.NC * sub_k, a.abreast, unit, slot)) return;
+    const KvHeads heads(a, unit);
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     int col = slot / sub_k;
     if (a.q_order) {
@@ -313,7 +349,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     };
     const uint32_t ds_lane = (uint32_t)(w * 1024 + lane * 8);     // this lane's place inside a step of dS in memory (bf16 elements)
 
-    for (int g = 0; g < a.G; ++g) {
+    for (int g = heads.first; g < heads.end; ++g) {
         const int hq = hkv * a.G + g;
         const int64_t line = ((int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0)) * a.NC + col;
         const int n_full = a.full_q_num[line], n_part = a.q_num[line];
@@ -669,10 +705,19 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     }
     // ---- dV (x = 0) or dK (x = 1, with the scale and the score_mod's gradient factor), bf16
     {
+        if (kv_lane >= a.kv_len) return;
+        if (a.kv_part) {                // (kv_parts_sum_kernel scales)
+            float* out = heads.sums(a, unit, x, D) + (int64_t)kv_lane * D;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int rg = 0; rg < 4; ++rg)
+                    *(f32x4*)(out + db * 32 + 8 * rg + 4 * half) = f32x4{acc[db][4 * rg], acc[db][4 * rg + 1], acc[db][4 * rg + 2], acc[db][4 * rg + 3]};
+            return;
+        }
         const float oscale = x ? a.scale * ScoreMod<SCORE>::grad_scale() : 1.0f;
         bf16* op = x ? a.dK + b * a.dk_sb + hkv * a.dk_sh + (int64_t)kv_lane * a.dk_ss
                      : a.dV + b * a.dv_sb + hkv * a.dv_sh + (int64_t)kv_lane * a.dv_ss;
-        if (kv_lane >= a.kv_len) return;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll

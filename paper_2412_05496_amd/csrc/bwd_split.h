@@ -267,7 +267,8 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
 
     const int parts = a.Bk / 32;
     int unit, slot_rank;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.NC * parts, a.abreast, unit, slot_rank)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv * a.head_parts, a.NC * parts, a.abreast, unit, slot_rank)) return;
+    const KvHeads heads(a, unit);
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     int col = slot_rank / parts;
     if (a.q_order) {
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
     const int per_block = a.Bq / 32, shift = a.Bq == 128 ? 2 : 1;
     int first = w;                                  // the wave's first unit of the next head's walk
 
-    for (int g = 0; g < a.G; ++g) {
+    for (int g = heads.first; g < heads.end; ++g) {
         const int hq = hkv * a.G + g;
         const int64_t line = ((int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hq : 0)) * a.NC + col;
         const int n_full = ldc(a.full_q_num + line), n_part = ldc(a.q_num + line), H = (n_full + n_part) * per_block;
@@ -491,6 +492,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
     const float kscale = a.scale * Score::grad_scale();
     add_quads<NW, D / 4>((f32x4*)smem, w, lane, quads, [&](int q, const f32x4& o) __attribute__((always_inline)) {
         const bool is_k = q >= D / 8;
+        if (a.kv_part) {
+            if (kv_lane < a.kv_len) *(f32x4*)(heads.sums(a, unit, is_k, D) + (int64_t)kv_lane * D + 8 * (q % (D / 8)) + 4 * half) = o;
+            return;
+        }
         const float s = is_k ? kscale : 1.0f;
         bf16* out = is_k ? a.dK + b * a.dk_sb + hkv * a.dk_sh + (int64_t)kv_lane * a.dk_ss
                          : a.dV + b * a.dv_sb + hkv * a.dv_sh + (int64_t)kv_lane * a.dv_ss;
@@ -573,7 +578,7 @@ inline int dq_halved_rows(int D, int NR, unsigned grid) { return D == 128 ? halv
 // workgroups as the columns have rows, whose chain is what ends the launch.
 template <uint32_t MASK>
 int dkdv_split_waves(const BwdArgs& a, int D) {
-    const int64_t groups = unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 32));
+    const int64_t groups = unit_grid(a.B * a.Hkv * a.head_parts, a.NC * (a.Bk / 32));
     // (the columns of a mask that is its own transpose's mirror image are shaped like its rows; a prefix is seen by all rows)
     LineShape cols = line_shape<MASK>(a.p, a.q_len, a.kv_len);
     const bool few_long = mask_uses(MASK, FLEXATTN_M_PREFIX) && !cols.uneven;
@@ -637,14 +642,45 @@ void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
     hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
 }
 
+// Rows that the longest column of blocks sees (of a canvas: those around its pixels).
+template <uint32_t MASK>
+int64_t longest_column(const BwdArgs& a) {
+    if (mask_uses(MASK, FLEXATTN_M_PREFIX)) return a.q_len;
+    const LineShape cols = line_shape<MASK>(a.p, a.q_len, a.kv_len);
+    const int64_t rows = PartialMask<MASK>::kCanvas ? cols.sure : cols.longest;
+    return rows < a.q_len ? rows : a.q_len;
+}
+// dV (blockIdx.y = 0) and dK from what the parts of every group left: eight dims a thread, in the order of the parts.
+static __global__ __launch_bounds__(256) void kv_parts_sum_kernel(const BwdArgs a, int D, float kscale) {
+    const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x, rows = (int64_t)a.B * a.Hkv * a.kv_len;
+    const int shift = D == 128 ? 4 : 3, d = ((int)at & ((1 << shift) - 1)) * 8;
+    const int64_t row = at >> shift;
+    if (row >= rows) return;
+    const bool is_k = blockIdx.y != 0;
+    const float* src = a.kv_part + ((int64_t)is_k * rows + row) * D + d;
+    f32x4 lo = *(const f32x4*)src, hi = *(const f32x4*)(src + 4);
+    for (int part = 1; part < a.head_parts; ++part) {
+        src += 2 * rows * D;
+        lo += *(const f32x4*)src;
+        hi += *(const f32x4*)(src + 4);
+    }
+    const float s = is_k ? kscale : 1.0f;
+    const int kv = (int)(row % a.kv_len), unit = (int)(row / a.kv_len), b = unit / a.Hkv, hkv = unit - b * a.Hkv;
+    bf16* out = is_k ? a.dK + b * a.dk_sb + hkv * a.dk_sh + (int64_t)kv * a.dk_ss : a.dV + b * a.dv_sb + hkv * a.dv_sh + (int64_t)kv * a.dv_ss;
+    *(u32x4*)(out + d) = u32x4{pack_bf16(lo[0] * s, lo[1] * s), pack_bf16(lo[2] * s, lo[3] * s), pack_bf16(hi[0] * s, hi[1] * s), pack_bf16(hi[2] * s, hi[3] * s)};
+}
+
 template <uint32_t MASK, uint32_t SCORE>
 int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t st) {
     BwdArgs a = args;
     const int units = a.B * a.Hkv;
+    a.head_parts = a.kv_part ? kv_head_parts(units, a.G, a.kv_len, D, longest_column<MASK>(a)) : 1;
+    if (a.head_parts == 1) a.kv_part = nullptr;
     const bool uneven = line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven;
     auto rows_by = [&](int rows) { return units_abreast(units, a.G * rows, bwd_waves_per_simd_of(D), rows_abreast<MASK>(uneven, D)); };
     a.abreast = one_by_one(units);
-    const unsigned grid_kv = unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 64));
+    const int kv_units = units * a.head_parts;
+    const unsigned grid_kv = unit_grid(kv_units, a.NC * (a.Bk / 64));
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
     // dQ first, where it makes the row scalars that dK/dV reads; last, after a pass that makes them, where it is written over
@@ -685,16 +721,23 @@ int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t 
     if (q && !a.dq_last) run_dq();
     if (kv) {
         const int waves = dkdv_split_waves<MASK>(a, D);
+        a.abreast = one_by_one(kv_units);
         if (waves) {
-            const dim3 slices(unit_grid(a.B * a.Hkv, a.NC * (a.Bk / 32)));
+            const dim3 slices(unit_grid(kv_units, a.NC * (a.Bk / 32)));
             if (D == 128) hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 4, MASK, SCORE>), slices, dim3(256), 0, st, a);
             else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 8, MASK, SCORE>), slices, dim3(512), 0, st, a);
             else hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 4, MASK, SCORE>), slices, dim3(256), 0, st, a);
         } else {
             BwdArgs akv = a;
-            akv.abreast = units_abreast(units, a.NC * (a.Bk / 64), bwd_waves_per_simd_of(D), uneven && !mask_uses(MASK, FLEXATTN_M_DOCUMENT) ? kColumnsAbreast : 1);
+            akv.abreast = units_abreast(kv_units, a.NC * (a.Bk / 64), bwd_waves_per_simd_of(D), uneven && !mask_uses(MASK, FLEXATTN_M_DOCUMENT) ? kColumnsAbreast : 1);
             if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, akv);
             else launch_dkdv64<MASK, SCORE>(akv, grid_kv, st);
+        }
+        a.abreast = one_by_one(units);
+        if (a.kv_part) {
+            const float kscale = a.scale * ScoreMod<SCORE>::grad_scale();
+            const int64_t eights = (int64_t)units * a.kv_len * (D / 8);
+            hipLaunchKernelGGL(kv_parts_sum_kernel, dim3((unsigned)((eights + 255) / 256), 2), dim3(256), 0, st, a, D, kscale);
         }
     }
     if (q && a.dq_last) run_dq();

@@ -1,0 +1,96 @@
+"""dK and dV of few KV heads, whose query heads are divided among workgroups: parts of one head and of several, of unlike size, in either kernel,
+against the oracle; and the same launch with a workspace that has no room for the parts' sums."""
+import pytest
+import torch
+
+from oracle import flex_oracle as fo
+from tests import helpers as hp
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# B, Hq, Hkv, S, D, mask, Bq, Bk, per-head BlockMasks, parts
+CASES = [
+    (1, 4, 1, 709, 128, "causal", 128, 64, False, 4),
+    (1, 3, 1, 1100, 128, "causal", 128, 64, False, 2),          # parts of one and two heads
+    (2, 7, 1, 900, 64, "prefix", 128, 128, False, 4),           # of one, two, two and two
+    (1, 8, 1, 2500, 64, "causal", 128, 64, False, 4),
+    (2, 16, 2, 1500, 64, "documents", 128, 64, False, 4),       # 384 workgroups, not by slices of 32 keys
+    (2, 16, 2, 1500, 128, "causal", 128, 64, False, 4),         # the same
+    (1, 16, 4, 850, 128, "documents", 64, 64, False, 2),
+    (1, 6, 2, 1500, 64, "window", 128, 64, True, 2),
+    (1, 8, 1, 1024, 64, "neighborhood", 128, 64, False, 8),
+    (1, 8, 1, 1024, 128, "none", 64, 128, True, 8),
+]
+
+
+def mods(fa, mask, S, B):
+    params = fa.ModParams()
+    if mask == "causal":
+        return params, fa.MASK_CAUSAL, fo.causal_mask
+    if mask == "none":
+        return params, fa.MASK_NONE, fo.no_mask
+    if mask == "prefix":
+        params.prefix_len = 70
+        return params, fa.MASK_PREFIX_LM, fo.or_mask(fo.causal_mask, fo.prefix_mask(70))
+    if mask == "window":
+        params.window = 900
+        return params, fa.MASK_SWA_CAUSAL, fo.and_mask(fo.causal_mask, fo.sliding_window_mask(900))
+    if mask == "documents":
+        ids = (torch.arange(S) >= S // 3).to(torch.int32).expand(B, S).contiguous()
+        params.doc_ids = ids.to(DEV)
+        return params, fa.MASK_DOCUMENT_CAUSAL, fo.and_mask(fo.document_mask(ids), fo.causal_mask)
+    params.na_width, params.na_height, params.na_kernel, params.na_layout, params.na_tile = 32, 32, 21, fa.NA_TILED, 8
+    return params, fa.MASK_NEIGHBORHOOD, fo.neighborhood_mask(32, 32, 21, "tiled", 8)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,mask,Bq,Bk,per_head,parts", CASES)
+def test_divided_groups(B, Hq, Hkv, S, D, mask, Bq, Bk, per_head, parts):
+    import paper_2412_05496_amd as fa
+    print("[case]", B, Hq, Hkv, S, D, mask, Bq, Bk, flush=True)
+    gen = torch.Generator().manual_seed(S + Hq)
+    Q, dO = (torch.randn(B, Hq, S, D, generator=gen).to(torch.bfloat16) for _ in range(2))
+    K, V = (torch.randn(B, Hkv, S, D, generator=gen).to(torch.bfloat16) for _ in range(2))
+    params, mask_id, oracle_mask = mods(fa, mask, S, B)
+    scale = D ** -0.5
+    bm = fa.alloc_blockmask(B if per_head or mask == "documents" else 1, Hq if per_head else 1, S, S, Bq, Bk, device=DEV)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    q, k, v, do = (t.to(DEV) for t in (Q, K, V, dO))
+    O, LSE = torch.empty_like(q), torch.empty(B, Hq, S, device=DEV)
+    head = (fa.SCORE_IDENTITY, mask_id, params, bm, scale)
+    fa.flexattn_forward(q, k, v, *head, O, LSE)
+    scalars = 2 * B * Hq * S * 4
+    at_most = (fa.flexattn_backward_workspace_bytes(q, k) - scalars) // (2 * B * Hkv * S * D * 4)
+    assert at_most >= parts                                     # (whatever the mask)
+    ref = fo.flex_attention_backward(Q, K, V, dO, fo.Identity(), oracle_mask, scale)
+    got = []
+    for room in (fa.flexattn_backward_workspace_bytes(q, k), scalars):
+        ws = torch.full((room + 4096,), 0xFF, dtype=torch.uint8, device=DEV)
+        # rows of every other head's storage, [B, S, H, D]
+        dQ, dK, dV = (torch.full((B, S, t.shape[1], D), float("nan"), dtype=torch.bfloat16, device=DEV).transpose(1, 2) for t in (q, k, k))
+        fa.flexattn_backward(q, k, v, O, do, LSE, *head, dQ, dK, dV, ws[:room])
+        torch.cuda.synchronize()
+        for name, g, r in zip(("dQ", "dK", "dV"), (dQ, dK, dV), ref):
+            hp.check_grad(name, g, r)
+        assert bool((ws[room:] == 0xFF).all())
+        written = int((ws[:room].view(torch.int32) != -1).sum()) * 4 - scalars
+        # the parts of this mask; the sums are hardly ever NaN patterns
+        assert room == scalars or abs(written / (2 * B * Hkv * S * D * 4) - parts) < 0.01, written / (2 * B * Hkv * S * D * 4)
+        got.append((dK, dV))
+    # the same products, added up in another order in fp32: one bf16 rounding of each result
+    for a, b in zip(*got):
+        assert (a.float() - b.float()).abs().max() <= 2 ** -7 * b.float().abs().max()
+    # with dS in memory, bit for bit, by stages and with no more room than whole groups need
+    n = hp.nonempty_blocks(bm)
+    need = fa.flexattn_backward_stored_workspace_bytes(q, k, bm, n)
+    parts_room = (fa.flexattn_backward_workspace_bytes(q, k) + 255) // 256 * 256 - (scalars + 255) // 256 * 256
+    for room, want in ((need, got[0]), (need - parts_room, got[1])):
+        ws = torch.full((room,), 0xFF, dtype=torch.uint8, device=DEV)
+        dQ, dK, dV = (torch.full_like(t, float("nan")) for t in (q, k, k))
+        for stages in (1, 2, 4):
+            fa.flexattn_backward_stored(q, k, v, O, do, LSE, *head, dQ, dK, dV, n, ws, stages)
+        torch.cuda.synchronize()
+        hp.check_grad("dQ*", dQ, ref[0])
+        assert torch.equal(dK, want[0]) and torch.equal(dV, want[1])
+    with pytest.raises(fa.FlexAttnError):
+        fa.flexattn_backward(q, k, v, O, do, LSE, *head, dQ, dK, dV, ws[:scalars - 4])
