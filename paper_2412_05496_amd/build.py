@@ -22,7 +22,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libflexattn.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-NUM_VARIANTS = 14         # must equal kNumVariants in csrc/variants.h
+NUM_VARIANTS = 16         # must equal kNumVariants in csrc/variants.h
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"),
          "-I" + CSRC, "-Wno-unused-result", "-Wno-pass-failed",

@@ -251,7 +251,8 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];   // relative-bias row of the current head
     using Mask = PartialMask<MASK>;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[2][Mask::kTags ? TQ : 4];   // [slot] tags of a PARTIAL step's queries
-    __shared__ u32x2 s_corners[Mask::kCanvas ? 64 : 1];               // key_corners() of the keys
+    __shared__ u32x2 s_corners[Mask::kCanvas && !Mask::kCells ? 64 : 1];        // key_corners() of the keys
+    __shared__ u32x4 s_rect[Mask::kCells ? 64 : 1];                             // cells: the queries that see them
 
     // workgroup -> (b, hkv, 64-key tile).  The columns of
     // blocks are taken in the BlockMask's work order (longest first; that of the group's first query
@@ -334,7 +335,11 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
         k_tag = (uint32_t)docs[min(kv_lane, a.kv_len - 1)];
         doc_rsrc = make_rsrc(docs, (uint32_t)(q_off + a.q_len) * 4u);
     }
-    if constexpr (Mask::kCanvas) {
+    typename Mask::CellBase cell_base = {};
+    if constexpr (Mask::kCells) {
+        cell_base = mask.base_of_keys(a.p, kv0 + 32 * kb);
+        if (x == 0) s_rect[32 * kb + l32] = mask.key_rectangle(kv_lane, cell_base);     // (visible as below)
+    } else if constexpr (Mask::kCanvas) {
         if (tid < 64) s_corners[tid] = mask.key_corners(kv0 + tid);     // (visible after the barriers before the first step)
     }
     // Tags of the 64 queries of the step whose first row is q0, into s_tag[slot] (visible after the
@@ -508,7 +513,8 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 else if constexpr (OWN) hid = part_of[SLOT] && mask.hidden(q_off + q_first, q_off + q_first + 31, kv0 + 32 * kb, kv0 + 32 * kb + 31);
                 // (a canvas' here, while the score accumulators do not take registers yet)
                 typename Mask::Bits bits = {};
-                if constexpr (Mask::kCanvas) {
+                typename Mask::CellMasks cells = {{~0u, ~0u}, ~0u};
+                if constexpr (Mask::kCanvas && !Mask::kCells) {
                     if (partial && !hid) bits = mask.match_queries(&s_tag[SLOT][32 * x], s_corners[32 * kb + l32], half);
                 }
                 // scores
@@ -549,6 +555,11 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 }
                 u32x4 pk[2] = {}, dsk[2] = {};
                 if (!hid) {
+                    if constexpr (Mask::kCells) {
+                        // (the lane's number is asked for again: what is held of it over the loop spills, and a reload waits for the next tiles)
+                        const int again = lane_again();
+                        if (partial) cells = mask.cell_masks(s_rect[32 * kb + (again & 31)], &s_tag[SLOT][32 * x], cell_base, again >> 5, true);
+                    }
                     constexpr int kAhead = Score::kRel || Score::kCap ? 0 : 2;
                     if constexpr (OWN) {
 #pragma unroll
@@ -581,7 +592,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                         }
                         if (rel_is_uni) smod.template p_with_grad4<true>(sv, dqk, rcv, gr, pe, rel_uni);
                         else smod.template p_with_grad4<false>(sv, dqk, rcv, gr, pe);
-                        if (partial) {
+                        if (partial && !Mask::kCells) {
                             asm volatile("" ::: "memory");   // keep this a (scalar, rarely taken) branch
                             // (a masked P makes dS vanish with it.  Rows past q_len hold zeros in Q and dO: whatever
                             // the mask says there adds nothing)
@@ -599,6 +610,10 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                             const int e = 2 * c4 + i;
                             pk[e >> 2][e & 3] = pack_bf16(pe[2 * i], pe[2 * i + 1]);
                             dsk[e >> 2][e & 3] = pack_bf16(ds[2 * i], ds[2 * i + 1]);
+                            if constexpr (Mask::kCells) {
+                                pk[e >> 2][e & 3] = cells.pair(pk[e >> 2][e & 3], e);
+                                dsk[e >> 2][e & 3] = cells.pair(dsk[e >> 2][e & 3], e);
+                            }
                         }
                     }
                 }
@@ -883,7 +898,14 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
         q_tag = (uint32_t)docs[q_pos];
         doc_rsrc = make_rsrc(docs, (uint32_t)a.kv_len * 4u);
     }
-    if constexpr (Mask::kCanvas) q_tag = mask.query_pixel(q_pos);
+    typename Mask::CellBase cell_base = {};
+    u32x4 q_rect = {};
+    if constexpr (Mask::kCells) {
+        cell_base = mask.base_of_queries(a.p, wave_rows);
+        q_rect = mask.query_rectangle(q_pos, cell_base);
+    } else if constexpr (Mask::kCanvas) {
+        q_tag = mask.query_pixel(q_pos);
+    }
     auto make_tags = [&](int buf, int kv0, int turn) __attribute__((always_inline)) {   // as in the forward
         if constexpr (Mask::kDoc) {
             if (w == 0) dma_dword(doc_rsrc, lds_addr(&s_tag[buf][0]), lane * 4, kv0 * 4);
@@ -1014,7 +1036,10 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
                     dpacc[r] = pe * gr * dpacc[r];
                 }
             }
-            if (partial && !mask.full(q_wave_min, q_wave_min + 31, kvs_blk, kvs_blk + 31)) {
+            typename Mask::CellMasks cells = {{~0u, ~0u}, ~0u};
+            if constexpr (Mask::kCells) {
+                if (partial) cells = mask.cell_masks(q_rect, &s_tag[BUF][block * 32], cell_base, half, kvs_blk <= mask.kv_last);
+            } else if (partial && !mask.full(q_wave_min, q_wave_min + 31, kvs_blk, kvs_blk + 31)) {
                 asm volatile("" ::: "memory");   // keep this a branch
                 typename Mask::Bits bits = mask.row_bits(q_pos, kvs_blk + 4 * half);
                 if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[BUF][block * 32], q_tag, l32, half, scattered);
@@ -1053,7 +1078,10 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
 #pragma unroll
             for (int c = 0; c < 2; ++c)
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) dsk[c][jj] = pack_bf16(dpacc[8 * c + 2 * jj], dpacc[8 * c + 2 * jj + 1]);
+                for (int jj = 0; jj < 4; ++jj) {
+                    dsk[c][jj] = pack_bf16(dpacc[8 * c + 2 * jj], dpacc[8 * c + 2 * jj + 1]);
+                    if constexpr (Mask::kCells) dsk[c][jj] = cells.pair(dsk[c][jj], 4 * c + jj);
+                }
             {
                 constexpr int NM = 2 * NDB;              // [slice c][block db]
                 auto frag = [&](int m) { return tr_reader.read(kt, kvb * 32 + 16 * (m / NDB), m % NDB); };

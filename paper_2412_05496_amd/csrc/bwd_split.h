@@ -107,8 +107,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(
         q_tag = (uint32_t)(a.p.doc_ids + (int64_t)b * a.p.doc_stride_b)[q_pos];
         scattered = Mask::scattered_ids(q_tag);
     }
+    typename Mask::CellBase cell_base = {};
+    u32x4 q_rect = {};
+    if constexpr (Mask::kCells) {
+        cell_base = mask.base_of_queries(a.p, q0);
+        q_rect = mask.query_rectangle(q_pos, cell_base);
+    }
     if constexpr (Mask::kCanvas) {
-        q_tag = mask.query_pixel(q_pos);
+        if constexpr (!Mask::kCells) q_tag = mask.query_pixel(q_pos);
         fill_hidden_tiles<1, NW * 64>(s_hidden, a.p, a.kv_idx + line * a.NC, n_full, T, sub, a.Bk, q0, tid);
     }
     auto make_tags = [&](int kv0) __attribute__((always_inline)) {
@@ -212,7 +218,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(
                 dpacc[r] = pe * gr * dpacc[r];
             }
         }
-        if (masked) {
+        typename Mask::CellMasks cells = {{~0u, ~0u}, ~0u};
+        if constexpr (Mask::kCells) {
+            if (masked) cells = mask.cell_masks(q_rect, &s_tag[w][0], cell_base, half, kv_now <= mask.kv_last);
+        } else if (masked) {
             asm volatile("" ::: "memory");          // keep this a branch
             typename Mask::Bits bits = mask.row_bits(q_pos, kv_now + 4 * half);
             if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[w][0], q_tag, l32, half, scattered);
@@ -232,7 +241,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(
         for (int c = 0; c < 2; ++c) {
             u32x4 ds;
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) ds[jj] = pack_bf16(dpacc[8 * c + 2 * jj], dpacc[8 * c + 2 * jj + 1]);
+            for (int jj = 0; jj < 4; ++jj) {
+                ds[jj] = pack_bf16(dpacc[8 * c + 2 * jj], dpacc[8 * c + 2 * jj + 1]);
+                if constexpr (Mask::kCells) ds[jj] = cells.pair(ds[jj], 4 * c + jj);
+            }
 #pragma unroll
             for (int db = 0; db < D / 32; ++db) dq[db] = mfma32(kt[c][db], __builtin_bit_cast(bf16x8, ds), dq[db]);
         }
@@ -304,7 +316,14 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
     uint32_t k_tag = 0;
     if constexpr (Mask::kDoc) k_tag = (uint32_t)docs[kv_ld];
     u32x2 corners = {};
-    if constexpr (Mask::kCanvas) corners = mask.key_corners(kv_lane);
+    typename Mask::CellBase cell_base = {};
+    u32x4 k_rect = {};
+    if constexpr (Mask::kCells) {
+        cell_base = mask.base_of_keys(a.p, kv0);
+        k_rect = mask.key_rectangle(kv_lane, cell_base);
+    } else if constexpr (Mask::kCanvas) {
+        corners = mask.key_corners(kv_lane);
+    }
     const L q_load(a.q_ss, 0, lane), do_load(a.do_ss, 0, lane);
     const uint32_t base = lds_addr(smem) + (uint32_t)w * 4 * UT;
     const RowReader<D> rows(l32, half, base);
@@ -419,8 +438,11 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
             const bool rel_is_uni = smod.rel_uniform(q_now - (kv0 + 31), q_now + 31 - kv0, rel_uni);
             const bool masked = partial_now && !mask.full(q_now, q_now + 31, kv0, kv0 + 31);
             typename Mask::Bits bits = {};
+            typename Mask::CellMasks cells = {{~0u, ~0u}, ~0u};
             if (masked) {
-                if constexpr (Mask::kCanvas) {
+                if constexpr (Mask::kCells) {
+                    cells = mask.cell_masks(k_rect, &s_tag[w][SLOT][0], cell_base, half, true);
+                } else if constexpr (Mask::kCanvas) {
                     bits = mask.match_queries(&s_tag[w][SLOT][0], corners, half);
                 } else {
                     bits = mask.key_bits(kv_lane, q_now + 4 * half);
@@ -445,7 +467,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
                 }
                 if (rel_is_uni) smod.template p_with_grad4<true>(sv, dqk, rcv, gr, pe, rel_uni);
                 else smod.template p_with_grad4<false>(sv, dqk, rcv, gr, pe);
-                if (masked) {
+                if (masked && !Mask::kCells) {
                     asm volatile("" ::: "memory");   // keep this a branch
                     if constexpr (Mask::kCanvas) {
                         mask.keep_queries(bits, &s_tag[w][SLOT][0], c4, half, pe);
@@ -460,6 +482,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
                 for (int i = 0; i < 2; ++i) {
                     pk[c4 >> 1][2 * (c4 & 1) + i] = pack_bf16(pe[2 * i], pe[2 * i + 1]);
                     dsk[c4 >> 1][2 * (c4 & 1) + i] = pack_bf16(ds[2 * i], ds[2 * i + 1]);
+                    if constexpr (Mask::kCells) {
+                        pk[c4 >> 1][2 * (c4 & 1) + i] = cells.pair(pk[c4 >> 1][2 * (c4 & 1) + i], 2 * c4 + i);
+                        dsk[c4 >> 1][2 * (c4 & 1) + i] = cells.pair(dsk[c4 >> 1][2 * (c4 & 1) + i], 2 * c4 + i);
+                    }
                 }
             }
             if (a.ds_store) store_ds(pos_now, sidx_now, dsk[0], dsk[1]);

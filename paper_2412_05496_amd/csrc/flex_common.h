@@ -93,6 +93,13 @@ __device__ __forceinline__ float max_halves(float v) {
     return raw_max(p.a, p.b);
 }
 
+// This lane's number in its wave, worked out here and now.
+__device__ __forceinline__ int lane_again() {
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
+    return lane;
+}
+
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     bf16x2 v;
     v[0] = (bf16)lo;
@@ -331,7 +338,8 @@ __device__ __forceinline__ int q_offset_of(const flexattn_mod_params& p, int b) 
 // bits as well, by one ballot per distinct id of the 32 tokens (one or two in packed documents).  The pixels that
 // match a lane's are a rectangle, of which 32 consecutive tokens hold a piece that is worked out line by line
 // (tokens_inside; the tags of the block's first token say where it lies), or, in kernels of their own for canvases that cut 32
-// tokens into many pieces (canvas_by_tags), compared per element.
+// tokens into many pieces (canvas_by_tags), compared per element, and for those whose 32 tokens are always a cell of 8 x 4 pixels
+// (canvas_in_cells) kept by pairs (CellMasks).
 // (Evaluating the mask element by element instead -- the canvas decode of every key, a lane exchange or a
 // table read per document id -- made PARTIAL blocks several times as expensive as FULL ones: neighborhood
 // attention on 128 x 128 pixels, K = 13, D = 64, B = 4, H = 16: forward 0.98 ms, dK/dV 1.60 ms before, 0.42
@@ -365,13 +373,16 @@ __device__ __forceinline__ float keep_or_neg_inf(uint32_t m, float v) {
 
 // A canvas whose matching pixels are compared token by token (canvas_by_tags); not accepted from callers.
 constexpr uint32_t kCanvasByTags = 0x40u;
+// A canvas whose 32 consecutive tokens are cells of 8 x 4 pixels (canvas_in_cells), line by line, or (both bits) in Z order.
+constexpr uint32_t kCanvasCells = 0x80u, kCanvasCellsZ = 0xc0u;
 
 template <uint32_t MASK>
 struct PartialMask {
     static constexpr uint32_t T0 = MASK & 0xffu, T1 = (MASK >> 8) & 0xffu, PRIMS = T0 | T1;
     static constexpr uint32_t kTagged = FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD;
     static constexpr bool kDoc = (PRIMS & FLEXATTN_M_DOCUMENT) != 0, kCanvas = (PRIMS & FLEXATTN_M_NEIGHBORHOOD) != 0;
-    static constexpr bool kTags = kDoc || kCanvas, kByTags = kCanvas && (PRIMS & kCanvasByTags) != 0;
+    static constexpr bool kTags = kDoc || kCanvas, kCells = kCanvas && (PRIMS & kCanvasCells) != 0,
+                          kCellsZ = kCells && (PRIMS & kCanvasByTags) != 0, kByTags = kCanvas && !kCells && (PRIMS & kCanvasByTags) != 0;
     static constexpr int kMaxIds = 9;
     static_assert(!(kDoc && kCanvas), "one tag per token: documents or pixels");
 
@@ -584,10 +595,74 @@ struct PartialMask {
     // The lane's key has these key_corners(), its elements are the queries whose query_block_tag() is in `tags`: what keep_queries
     // wants to know of them (their bits, or the key's pixel).
     __device__ __forceinline__ Bits match_queries(const uint32_t* tags, u32x2 corners, int half) const {
-        static_assert((T0 & ~kCanvasByTags) == FLEXATTN_M_NEIGHBORHOOD && T1 == 0, "a canvas with another predicate: dK/dV asks the pixels alone");
+        static_assert((T0 & ~(kCanvasByTags | kCanvasCells)) == FLEXATTN_M_NEIGHBORHOOD && T1 == 0, "a canvas with another predicate: dK/dV asks the pixels alone");
         if constexpr (kByTags) return Bits{corners[0], 0u};
         const uint32_t xm = (1u << (y_shift - 1)) - 1u;
         return Bits{tokens_inside(tags, (int)(corners[0] & xm), (int)(corners[0] >> y_shift), (int)(corners[1] & xm), (int)(corners[1] >> y_shift)) >> (4 * half), 0u};
+    }
+    // Cells: what a lane's rectangle of pixels leaves of a cell's elements.  Elements 2 p and 2 p + 1 are two pixels side by side, eight of them on a
+    // line: line by line p = 2 y + x / 2 (for the half's four columns), in Z order the bits of p are y0, y1, x2.  So a pair of packed bf16 is kept by two of six
+    // masks, one operation a pair where a mask per element takes two an element and its place in the block another 20.
+    struct CellMasks {
+        uint32_t x[2], lines;       // (all-ones or 0 for either pixel of a pair; a bit for each of four lines)
+        __device__ __forceinline__ uint32_t of(int p) const { return x[kCellsZ ? p >> 2 : p & 1] & bit_mask(lines, kCellsZ ? p & 3 : p >> 1); }
+        __device__ __forceinline__ uint32_t pair(uint32_t v, int p) const { return v & of(p); }
+        // all-ones or 0
+        __device__ __forceinline__ uint32_t element(int r) const {
+            const int m = (int)of(r >> 1);
+            return (uint32_t)(r & 1 ? m >> 16 : (int)((uint32_t)m << 16) >> 16);
+        }
+    };
+    // The corner that the columns and lines of a wave's rectangles count from: its 32 queries' windows, or the queries around its 32 keys.
+    struct CellBase {
+        int col, line;
+    };
+    __device__ __forceinline__ static CellBase base_at(int x0, int y0) {
+        return {__builtin_amdgcn_readfirstlane(x0 >> 3), __builtin_amdgcn_readfirstlane(y0 & ~3)};
+    }
+    __device__ __forceinline__ CellBase base_of_queries(const flexattn_mod_params& p, int q) const {
+        const CanvasBlocks::Box w = CanvasBlocks(p).windows(q);
+        return base_at(w.x0, w.y0);
+    }
+    __device__ __forceinline__ CellBase base_of_keys(const flexattn_mod_params& p, int kv) const {
+        const CanvasBlocks::Box k = CanvasBlocks(p).tokens(kv);
+        return base_at(k.x0 <= 2 * na_r ? 0 : k.x0 - na_r, k.y0 <= 2 * na_r ? 0 : k.y0 - na_r);
+    }
+    // A lane's rectangle (corners included) as 64 columns and 64 lines.
+    __device__ __forceinline__ static u32x4 rectangle(int x0, int y0, int x1, int y1, CellBase base) {
+        auto bits = [](int lo, int hi) { return (~0ull >> (63 - hi)) & (~0ull << lo); };
+        const uint64_t xs = bits(x0 - 8 * base.col, x1 - 8 * base.col), ys = bits(y0 - base.line, y1 - base.line);
+        return u32x4{(uint32_t)xs, (uint32_t)(xs >> 32), (uint32_t)ys, (uint32_t)(ys >> 32)};
+    }
+    __device__ __forceinline__ u32x4 query_rectangle(int q, CellBase base) const {
+        int x, y;
+        window_corner(q, x, y);
+        return rectangle(x, y, x + 2 * na_r, y + 2 * na_r, base);
+    }
+    __device__ __forceinline__ u32x4 key_rectangle(int kv, CellBase base) const {
+        int x, y;
+        canvas.pixel(min(kv, kv_last), x, y);
+        const int d = 2 * na_r;
+        return rectangle(x <= d ? 0 : x - na_r, y <= d ? 0 : y - na_r, x >= na_w - 1 - d ? na_w - 1 : x + na_r, y >= na_h - 1 - d ? na_h - 1 : y + na_r, base);
+    }
+    // tags: of the cell's tokens (key_pixel, in LDS; the first is asked); there: whether it has any
+    __device__ __forceinline__ CellMasks cell_masks(u32x4 rect, const uint32_t* tags, CellBase base, int half, bool there) const {
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)tags[0]);
+        const int col = (int)((first & ((1u << (y_shift - 1)) - 1u)) >> 3) - base.col, line = (int)(first >> y_shift) - base.line;
+        if (!there || (unsigned)col > 7u || (unsigned)line > 63u) return CellMasks{};
+        typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+        typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+        // the column's bits in bytes 1 and 3 (the half's first pixel first), two of them moved up to the signs of both 16-bit halves
+        const u16x2 t = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(rect[1], rect[0], 0x000c000cu | (uint32_t)col << 8 | (uint32_t)col << 24) >> ((kCellsZ ? 2 : 4) * half));
+        auto mask = [&](int bit) __attribute__((always_inline)) {
+            const u16x2 up = {(uint16_t)(7 - bit), (uint16_t)(6 - bit)};
+            return __builtin_bit_cast(uint32_t, (i16x2)(__builtin_bit_cast(i16x2, (u16x2)(t << up)) >> (int16_t)15));
+        };
+        CellMasks m;
+        m.x[0] = mask(0);
+        m.x[1] = mask(kCellsZ ? 4 : 2);
+        m.lines = (uint32_t)(((uint64_t)rect[3] << 32 | rect[2]) >> line);
+        return m;
     }
     // Elements 4 c4 .. of the lane, kept or 0.
     __device__ __forceinline__ void keep_queries(const Bits& bits, const uint32_t* tags, int c4, int half, float (&pe)[4]) const {
@@ -942,6 +1017,19 @@ inline bool canvas_by_tags(const flexattn_mod_params& p, bool backward) {
     return p.na_width < 16;
 }
 
+// Whether 32 consecutive tokens, the first at a multiple of 32, are cells of 8 x 4 pixels whose rectangles fit the 64 columns and lines of
+// PartialMask::rectangle.  Those of a cell's keys are the widest: 2 r + 8 columns, 3 r + 8 where they reach a border (and up to 7 before
+// the first, a multiple of 8, but for the left border's), so r <= 16; on a canvas both of whose borders they reach, all of its 4 r + 8.
+// (Positions that start elsewhere, other tiles, which cut 32 tokens otherwise, and wider windows are compared as before.)  Cells against
+// that, us, B = 4, H = 16, D = 64, forward / dQ / dK/dV: 128 x 128, K = 13, tiles of 8 241 -> 232 / 296 -> 276 / 450; 64 x 64, K = 27,
+// tiles of 8 128 -> 115 / 158 -> 142 / 224 -> 219, K = 3 51.7 -> 51.4 / 64.1 -> 59.5 / 101.7 -> 100; K = 9, Morton 51.7 -> 49.6 / 65.6 -> 59.7 /
+// 102.3 -> 99.4.  At D = 128 dQ 1.04x to 1.12x, dK/dV 1.00x to 1.03x; the forward compares as before.
+inline bool canvas_in_cells(const flexattn_mod_params& p) {
+    if (p.q_offsets || !(p.na_layout == FLEXATTN_NA_MORTON ? p.na_width >= 8 : p.na_layout == FLEXATTN_NA_TILED && p.na_tile == 8)) return false;
+    const int r = p.na_kernel / 2, side = p.na_width < p.na_height ? p.na_width : p.na_height;
+    return r <= (side > 4 * r + 8 ? 16 : 14);
+}
+
 // The (mask, score) pairs that forward/backward kernels are instantiated for: the paper's examples
 // and benchmark variants, and three compositions of them (sliding window with a soft-cap; nested
 // score_mods: ALiBi then soft-cap, relative bias then soft-cap under a document mask).  The functors
@@ -963,9 +1051,11 @@ inline bool canvas_by_tags(const flexattn_mod_params& p, bool backward) {
     X(FLEXATTN_MASK_SWA_CAUSAL, FLEXATTN_SCORE_SOFTCAP)                                 \
     X(FLEXATTN_MASK_CAUSAL, (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_SOFTCAP))            \
     X(FLEXATTN_MASK_DOCUMENT_CAUSAL, (FLEXATTN_SCORE_REL_BIAS | FLEXATTN_SCORE_SOFTCAP))  \
-    X((FLEXATTN_MASK_NEIGHBORHOOD | kCanvasByTags), FLEXATTN_SCORE_IDENTITY)
+    X((FLEXATTN_MASK_NEIGHBORHOOD | kCanvasByTags), FLEXATTN_SCORE_IDENTITY)            \
+    X((FLEXATTN_MASK_NEIGHBORHOOD | kCanvasCells), FLEXATTN_SCORE_IDENTITY)             \
+    X((FLEXATTN_MASK_NEIGHBORHOOD | kCanvasCellsZ), FLEXATTN_SCORE_IDENTITY)
 
 // One entry per line of FLEXATTN_FOR_EACH_VARIANT: X(index)
-#define FLEXATTN_VARIANT_INDICES(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13)
+#define FLEXATTN_VARIANT_INDICES(X) X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
 
 }  // namespace flexattn

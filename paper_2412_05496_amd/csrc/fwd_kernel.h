@@ -240,10 +240,12 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];           // relative-bias row of the head
     using Mask = PartialMask<MASK>;
+    constexpr bool CELLS = Mask::kCells && D == 64;                   // (D = 128: six masks more spill 16 and 28 registers, 469 -> 682 us)
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[SPLIT ? NW : UNITS ? 3 : 2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys, per buffer (SPLIT: wave)
 
     constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || PLAIN || SPLIT || PAIRS);
-    __shared__ uint32_t s_qtag[Mask::kTags ? NW * 64 : 1];            // each lane's own tag (its query's)
+    __shared__ uint32_t s_qtag[Mask::kTags && !CELLS ? NW * 64 : 1];            // each lane's own tag (its query's)
+    __shared__ u32x4 s_rect[CELLS ? NW * 32 : 1];              // cells: its window, for both halves
     __shared__ uint8_t s_hidden[kHiddenTable ? kHiddenTiles : 1];    // CanvasBlocks::hidden_bits of the first tiles
 
     // ---- workgroup -> (b, hkv, g, row of blocks).  Rows are taken longest first (the BlockMask's work order), or
@@ -338,7 +340,13 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
         s_qtag[tid] = id;
         scattered = Mask::scattered_ids(id);
     }
-    if constexpr (Mask::kCanvas) s_qtag[tid] = mask.query_pixel(q_pos);
+    typename Mask::CellBase cell_base = {};
+    if constexpr (CELLS) {
+        cell_base = mask.base_of_queries(a.p, wave_rows);
+        s_rect[w * 32 + l32] = mask.query_rectangle(q_pos, cell_base);
+    } else if constexpr (Mask::kCanvas) {
+        s_qtag[tid] = mask.query_pixel(q_pos);
+    }
     // Tags of the keys of the tile at kv0, into s_tag[buf] (visible after the next barrier): document ids
     // come by LDS-DMA (keys past the end read as 0), pixels are worked out by one of the waves.
     auto make_tags = [&](int buf, int kv0, int turn) __attribute__((always_inline)) {
@@ -423,9 +431,9 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     // mask_mod of the 32-key block kvb of the tile in buffer buf: put(all-ones or 0, s) for every element
     auto masked = [&](f32x16& s, int kvs, int buf, int kvb, auto&& put) __attribute__((always_inline)) {
         typename Mask::Bits bits = mask.row_bits(q_pos, kvs + 4 * half);
-        const uint32_t q_tag = Mask::kTags ? s_qtag[tid] : 0u;
+        const uint32_t q_tag = Mask::kTags && !CELLS ? s_qtag[tid] : 0u;
         if constexpr (Mask::kDoc) Mask::match_documents(bits, &s_tag[buf][kvb * 32], q_tag, l32, half, scattered);
-        if constexpr (Mask::kCanvas) {
+        if constexpr (Mask::kCanvas && !CELLS) {
             mask.template mask_keys<true>(bits, &s_tag[buf][kvb * 32], q_tag, half, [&](int r, uint32_t m) __attribute__((always_inline)) { s[r] = put(m, s[r]); });
         } else {
 #pragma unroll
@@ -434,6 +442,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     };
     // The probabilities of a block as two bf16 fragments, and this lane's part of the row sum: over the bf16-rounded
     // probabilities, the values P V is computed from, two at a time (dot product of a packed pair with (1, 1), fp32 accumulation).
+    typename Mask::CellMasks cells = {};      // of the block that is worked on
     auto weigh = [&](const f32x16& s, bf16x8 (&pf)[2], auto&& prob) __attribute__((always_inline)) {
         float psum[2] = {0.0f, 0.0f};
 #pragma unroll
@@ -442,6 +451,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 pk[jj] = pack_bf16(prob(s[8 * c + 2 * jj]), prob(s[8 * c + 2 * jj + 1]));
+                if constexpr (CELLS) pk[jj] = cells.pair(pk[jj], 4 * c + jj);
                 psum[jj & 1] = pair_sum_bf16(pk[jj], psum[jj & 1]);
             }
             pf[c] = __builtin_bit_cast(bf16x8, pk);
@@ -498,12 +508,19 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
 #pragma unroll
                 for (int r = 0; r < 16; ++r) s[r] = smod.template apply_shifted<false>(s[r], rel(r), 0.0f, shift);
             }
-            if (partial) {
+            if constexpr (CELLS) {
+                cells = {{~0u, ~0u}, ~0u};
+                if (partial) cells = mask.cell_masks(s_rect[w * 32 + l32], &s_tag[buf][kvb * 32], cell_base, half, kvs <= mask.kv_last);
+            } else if (partial) {
                 if constexpr (Mask::kTags) asm volatile("" : "+v"(s));
                 else asm volatile("" ::: "memory");
                 masked(s, kvs, buf, kvb, keep_or_neg_inf);
             }
             auto track = [&]() __attribute__((always_inline)) {
+                if constexpr (CELLS) {       // (the weights need no more than their pairs' masks)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[r] = keep_or_neg_inf(cells.element(r), s[r]);
+                }
                 float mx = s[0];
 #pragma unroll
                 for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);

@@ -28,7 +28,9 @@ inline int find_variant(uint32_t mask, uint32_t score) {
 
 // the variant of a call (of a valid mask)
 inline int variant_of(uint32_t mask, uint32_t score, const flexattn_mod_params* p, bool backward) {
-    return find_variant(mask_uses(mask, FLEXATTN_M_NEIGHBORHOOD) && canvas_by_tags(*p, backward) ? mask | kCanvasByTags : mask, score);
+    if (!mask_uses(mask, FLEXATTN_M_NEIGHBORHOOD)) return find_variant(mask, score);
+    if (canvas_in_cells(*p)) return find_variant(mask | (p->na_layout == FLEXATTN_NA_MORTON ? kCanvasCellsZ : kCanvasCells), score);
+    return find_variant(canvas_by_tags(*p, backward) ? mask | kCanvasByTags : mask, score);
 }
 
 #define FLEXATTN_CAT_(a, b) a##b
