@@ -227,6 +227,14 @@ __device__ __forceinline__ int canvas_step_bits(const flexattn_mod_params& p, in
 // wave the vector work and the outputs of its hidden blocks (D = 128, 128 x 128 pixels, tiles of 8 x 8, K = 13, 64 heads:
 // 1047 -> 907 us; 100 x 90 row-major, K = 9: 802 -> 771; D = 64 where canvas_cut_pays, 128 x 128, K = 13 548 -> 481, 64 x 64 in Morton order, K = 21,
 // 234 -> 204).
+//
+// LEAVE (D = 128, other masks): the walk leaves out the steps at its front, where the PARTIAL blocks are, that the indices alone hide
+// from all four waves: every other column of 64 keys has one at its diagonal if Bq = 128 or Bk = 128, one at the window's far edge, and all have
+// one behind a q_len in the first half of its block.  us, B x H = 256, D = 128: causal, S = 1024 214 -> 207,
+// S = 300 (512) 79.6 -> 72; window of 512, S = 4096 (64) 218 -> 209; window of 195, soft-cap, Bq = 64, Bk = 128, S = 2427 (512) 673 -> 608;
+// causal, 128 x 128, S = 947, Hkv = 2 (48) 261 -> 237; long causal columns 1.00x to 1.02x.
+// (At D = 64 such a step has no more than S and dP, and short columns lose by the walk's layout what that is: 16 x 16 heads, S = 1024,
+// Bq = 64 99 -> 101, B = 8, S = 500 24.3 -> 25.2.)
 template <int D, uint32_t MASK, uint32_t SCORE>
 constexpr bool dkdv_own_rows() {
     constexpr bool biased_cap = (SCORE & FLEXATTN_SCORE_SOFTCAP) && (SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS));
@@ -247,6 +255,8 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     constexpr int kListMax = 512;
     __shared__ int s_steps[kListMax + 2];          // the walk of the current head, see below
     __shared__ int s_pos[CUT ? kListMax + 2 : 1], s_count;
+    constexpr bool LEAVE = D == 128 && !CUT;
+    __shared__ uint64_t s_left_out;
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];   // relative-bias row of the current head
     using Mask = PartialMask<MASK>;
@@ -416,22 +426,43 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 __syncthreads();
                 H = __builtin_amdgcn_readfirstlane(s_count);
             }
+            // (LEAVE: the steps that are kept of the first 64 move up to the 65th, and the walk starts behind the gap.  Bits 1 .. 5 say by how
+            // many places, for that of their dS in memory.)
             for (int i = CUT ? H : tid; i < H; i += 256) {
                 const int u = H_all - 1 - (seg0 + i), pos = u / sub, sidx = u - pos * sub;
                 const int blk = pos < n_full ? full_idx[pos] : part_idx[pos - n_full];
-                s_steps[i] = (blk * a.Bq + sidx * TQ) | (pos >= n_full ? 1 : 0);
+                const int q0 = blk * a.Bq + sidx * TQ;
+                int up = 0;
+                if constexpr (LEAVE) {
+                    if (i < 64) {
+                        const bool hid = seg0 == 0 && pos >= n_full && (q0 >= a.q_len || mask.hidden(q_off + q0, q_off + q0 + TQ - 1, kv0, kv0 + 63));
+                        uint64_t out = __ballot(hid);
+                        if (__popcll(out) == H) out &= ~1ull;                       // (no segment is empty)
+                        if (a.ds_store && __popcll(out) > 31) out = 0;              // (no room in an entry)
+                        if (i == 0) s_left_out = out;
+                        if ((out >> i) & 1) continue;
+                        up = __popcll(out >> i);
+                    }
+                }
+                const int e = (blk * a.Bq + sidx * TQ) | ((up & 31) << 1) | (pos >= n_full ? 1 : 0);
+                s_steps[i + up] = e;
                 // loads are issued for one step past the end as well (into the free ring slot,
                 // never read): it repeats the last step's rows
-                if (i == H - 1) s_steps[H] = s_steps[i];
+                if (i + up == H - 1) s_steps[H] = e;
             }
             __syncthreads();
-            int ld_v = 0;                           // step whose loads are issued next
-            int u_step = H_all - 1 - seg0;          // position of the current step in the column's walk (counts down)
-            int e_next = s_steps[0];
+            uint64_t left_out = 0;
+            if constexpr (LEAVE)
+                left_out = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(s_left_out >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)s_left_out);
+            const int first = __popcll(left_out);
+            int ld_v = first;                       // step whose loads are issued next
+            int u_step = H_all - 1 - seg0 - first;          // position of the current step in the column's walk (counts down)
+            int e_next = s_steps[first];
             int q0_of[2];                           // first query row of the step in each ring slot,
             bool part_of[2];                        // and whether its block is PARTIAL
             // (CUT) whether the mask hides this wave's 32 x 32 block, and that of the other wave of its keys
             bool hid_of[2] = {false, false}, hid_other_of[2] = {false, false};
+            int up_of[2] = {0, 0};                  // (LEAVE) by how many places it moved
 
             int ld_q0 = 0;                          // first row of the step being loaded
             constexpr int kLoads = 2 * Loader::NI + 1;      // load instructions per wave and step
@@ -445,6 +476,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                     hid_of[SLOT] = (e >> (1 + w)) & 1;
                     hid_other_of[SLOT] = (e >> (1 + (w ^ 2))) & 1;
                 }
+                if constexpr (LEAVE) up_of[SLOT] = (e >> 1) & 31;
                 e_next = s_steps[++ld_v];
             };
             // piece P of the loads of a step: NI for the Q tile, NI for the dO tile, one row of scalars
@@ -472,19 +504,21 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 for (int rg = 0; rg < 4; ++rg) out[rg] = read_row4(slot, which, rg);
             };
 
-            load_step(std::integral_constant<int, 0>{});
-            if (part_of[0]) make_tags(0, q0_of[0]);
-            wait_vmem();
-            __syncthreads();
-
             // this wave's dS of the step to memory, as it sits in the registers
             auto store_ds = [&](int u_at, u32x4 c0, u32x4 c1) {
-                const int u = CUT ? __builtin_amdgcn_readfirstlane(u_at) : u_step, pos = u >> sub_shift;
+                const int u = CUT ? __builtin_amdgcn_readfirstlane(u_at) : u_at, pos = u >> sub_shift;
                 bf16* dst = ds_col + (int64_t)(min(pos, ds_pos_max) * (sub_k * sub) + (u - (pos << sub_shift))) * 4096;
                 // (written once, read once by another kernel much later: no reason to keep it in a cache)
                 __builtin_nontemporal_store(c0, (u32x4*)(dst + ds_lane));
                 __builtin_nontemporal_store(c1, (u32x4*)(dst + ds_lane + 512));
             };
+            if (LEAVE && a.ds_store)                // dS of the steps left out
+                for (uint64_t rest = left_out; rest; rest &= rest - 1) store_ds(H_all - 1 - __builtin_ctzll(rest), u32x4{}, u32x4{});
+            load_step(std::integral_constant<int, 0>{});
+            if (part_of[0]) make_tags(0, q0_of[0]);
+            wait_vmem();
+            __syncthreads();
+
             // the next step's tiles must have landed; the two dS stores, the youngest vector-memory
             // operations of the step (the counter retires in issue order), may still be under way
             auto end_step = [&](bool stored) {
@@ -619,7 +653,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 }
                 // (wave-uniform; the blocks a canvas hides are not read back, see CANVAS in bwd_stored.h)
                 const bool stored = a.ds_store && !(CUT && hid);
-                if (stored) store_ds(CUT ? s_pos[ld_v - 2] : 0, dsk[0], dsk[1]);
+                if (stored) store_ds(CUT ? s_pos[ld_v - 2] : u_step + up_of[SLOT], dsk[0], dsk[1]);
                 --u_step;
                 if constexpr (OWN) {
                     // outputs: dV^T += dO^T P and dK^T += Q^T dS over this wave's own 32 rows
@@ -684,7 +718,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 end_step(stored);
             };
 
-            int v = 0;
+            int v = first;
             for (; v + 1 < H; v += 2) {
                 step(std::integral_constant<int, 0>{});
                 step(std::integral_constant<int, 1>{});
