@@ -270,6 +270,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     const int sub_k = a.Bk / 64;                   // tiles per column of blocks
     int unit, slot;                                // NC * sub_k slots >= tiles: the last column may be cut short
     if (!unit_of_workgroup(a.B * a.Hkv * a.head_parts, a.NC * sub_k, a.abreast, unit, slot)) return;
+    if (a.ds_store) unit = last_unit_first(unit, a.B * a.Hkv * a.head_parts);
     const KvHeads heads(a, unit);
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     int col = slot / sub_k;
@@ -845,6 +846,7 @@ __global__ __launch_bounds__(NW * 64, bwd_waves_per_simd<D>()) void bwd_dq_kerne
     UnitSets abreast = a.abreast;
     if constexpr (Mask::kDoc) abreast = abreast_if_long(abreast, a.B * a.Hkv, longest_row(a.kv_order, a.full_kv_num, a.kv_num, 0, a.NR, a.Bk / 64));
     if (!unit_of_workgroup(a.B * a.Hkv, a.G * (MIXED ? a.NR + a.halved : a.NR * (PAIRS ? Bq / 64 : 1)), abreast, unit, rem)) return;
+    unit = last_unit_first(unit, a.B * a.Hkv);
     int slice = 0;                                                   // PAIRS: which 64 rows of the block
     bool whole = false;                                              // MIXED: 32 rows and all keys to a wave
     if constexpr (MIXED) {

@@ -267,6 +267,17 @@ __device__ __forceinline__ bool unit_of_workgroup(unsigned id, int units, int pe
 __device__ __forceinline__ bool unit_of_workgroup(int units, int per_unit, UnitSets abreast, int& unit, int& rank) {
     return unit_of_workgroup(blockIdx.x, units, per_unit, abreast, unit, rank);
 }
+// The unit in its place where an XCD takes its whole units the other way round.  Kernels that follow one another on the same
+// tensors do so in turn -- forward up, dQ down, dK/dV up; where dS is kept in memory the row scalars up, dK/dV down, dQ up -- so that
+// the second starts on what the first has touched last, of which the memory's cache of 256 MB still holds as much.  (Bound by nothing but what misses
+// that cache: smaller tensors take the same time, and an XCD keeps its units, else those that fit its L2 lose 3 %.)  us, dQ and dK/dV together,
+// both up -> this: causal, D = 64, S = 1024 x 1024 heads 726 -> 703, 512 x 1024 251 -> 241, 2048 x 256 557 -> 545; D = 128, 1024 x 256
+// 362 -> 350, 200 x 1024 182 -> 173; no mask, D = 64, 1000 x 512 527 -> 516; canvas 64 x 64, K = 9, 128 heads 334 -> 324; a step with
+// dS in memory, soft-cap, D = 128, 1024 x 256 489 -> 479, 2048 x 128 762 -> 754.
+__host__ __device__ inline int last_unit_first(int unit, int units) {
+    const int whole = units & ~7;
+    return unit < whole ? whole - 8 - (unit & ~7) + (unit & 7) : unit;
+}
 __host__ __device__ inline UnitSets one_by_one(int units) { return {0, units >= 8 ? units >> 3 : 1}; }
 // How many units take turns.  Pieces of uneven length end a launch sooner if the short ones of many units come last, and units that
 // a set's workgroups hold at once share the XCD's L2 all the same.  So: as many as make two rounds of the XCD's workgroups (per_cu of them on each of 32 CUs),
