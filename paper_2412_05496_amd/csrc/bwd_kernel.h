@@ -228,12 +228,13 @@ __device__ __forceinline__ int canvas_step_bits(const flexattn_mod_params& p, in
 // 1047 -> 907 us; 100 x 90 row-major, K = 9: 802 -> 771; D = 64 where canvas_cut_pays, 128 x 128, K = 13 548 -> 481, 64 x 64 in Morton order, K = 21,
 // 234 -> 204).
 //
-// LEAVE (D = 128, other masks): the walk leaves out the steps at its front, where the PARTIAL blocks are, that the indices alone hide
+// LEAVE (no own rows, other masks): the walk leaves out the steps at its front, where the PARTIAL blocks are, that the indices alone hide
 // from all four waves: every other column of 64 keys has one at its diagonal if Bq = 128 or Bk = 128, one at the window's far edge, and all have
 // one behind a q_len in the first half of its block.  us, B x H = 256, D = 128: causal, S = 1024 214 -> 207,
 // S = 300 (512) 79.6 -> 72; window of 512, S = 4096 (64) 218 -> 209; window of 195, soft-cap, Bq = 64, Bk = 128, S = 2427 (512) 673 -> 608;
-// causal, 128 x 128, S = 947, Hkv = 2 (48) 261 -> 237; long causal columns 1.00x to 1.02x.
-// (At D = 64 such a step has no more than S and dP, and short columns lose by the walk's layout what that is: 16 x 16 heads, S = 1024,
+// causal, 128 x 128, S = 947, Hkv = 2 (48) 261 -> 237; long causal columns 1.00x to 1.02x;
+// D = 64, ALiBi and soft-cap, S = 1000 (256) 124 -> 120, 300 (1024) 92.9 -> 80.9, 128 x 128, S = 947, Hkv = 2 (48) 170 -> 161.
+// (With own rows such a step has no more than S and dP, and short columns lose by the walk's layout what that is: 16 x 16 heads, S = 1024,
 // Bq = 64 99 -> 101, B = 8, S = 500 24.3 -> 25.2.)
 template <int D, uint32_t MASK, uint32_t SCORE>
 constexpr bool dkdv_own_rows() {
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     constexpr int kListMax = 512;
     __shared__ int s_steps[kListMax + 2];          // the walk of the current head, see below
     __shared__ int s_pos[CUT ? kListMax + 2 : 1], s_count;
-    constexpr bool LEAVE = D == 128 && !CUT;
+    constexpr bool LEAVE = !OWN && !PartialMask<MASK>::kCanvas;
     __shared__ uint64_t s_left_out;
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];   // relative-bias row of the current head

@@ -1,4 +1,4 @@
-"""dK/dV at D = 128 of columns of blocks that list steps of 64 queries which the indices alone hide from the 64 keys: at a diagonal, at
+"""dK/dV, in the kernels whose waves exchange P and dS, of columns of blocks that list steps of 64 queries which the indices alone hide from the 64 keys: at a diagonal, at
 a window's far edge, behind the last query, in columns without a visible one, and more of them than one entry of the walk counts.
 Gradients against the oracle, recomputed and with dS in memory (whose hidden steps must read as zeros)."""
 import pytest
@@ -11,14 +11,19 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def gradients(mask_id, mask_mod, S, Bq, Bk, params, everything=False, Hq=2, Hkv=1, B=1, q_len=None):
+def gradients(mask_id, mask_mod, S, Bq, Bk, params, everything=False, Hq=2, Hkv=1, B=1, q_len=None, capped=False):
     """everything: all blocks are listed as PARTIAL, whatever the mask hides of them."""
     import paper_2412_05496_amd as fa
-    D, q_len = 128, q_len or S
+    D, q_len = 64 if capped else 128, q_len or S
+    score_id, score = fa.SCORE_IDENTITY, fo.Identity()
+    if capped:                  # (at D = 64 a bias and a soft-cap take that kernel)
+        bias = torch.tensor([-0.03, 0.01])[:Hq]
+        params.alibi_bias, params.softcap = bias.to(DEV), 30.0
+        score_id, score = fa.SCORE_ALIBI | fa.SCORE_SOFTCAP, fo.Compose(fo.Alibi(bias), fo.Softcap(30.0))
     g = torch.Generator().manual_seed(S + Bq + Bk)
     Q, dO = (torch.randn(B, Hq, q_len, D, generator=g).to(torch.bfloat16) for _ in range(2))
     K, V = (torch.randn(B, Hkv, S, D, generator=g).to(torch.bfloat16) for _ in range(2))
-    refs = fo.flex_attention_backward(*(t[:1].float() for t in (Q, K, V, dO)), fo.Identity(), mask_mod, D ** -0.5)
+    refs = fo.flex_attention_backward(*(t[:1].float() for t in (Q, K, V, dO)), score, mask_mod, D ** -0.5)
     bm = fa.alloc_blockmask(1, 1, q_len, S, Bq, Bk, device=torch.device(DEV))
     fa.flexattn_blockmask_build(mask_id, params, bm)
     if everything:
@@ -30,7 +35,7 @@ def gradients(mask_id, mask_mod, S, Bq, Bk, params, everything=False, Hq=2, Hkv=
         bm.stats[0], bm.stats[1] = NR * NC, 0
     Q, K, V, dO = (t.to(DEV) for t in (Q, K, V, dO))
     O, LSE = torch.empty_like(Q), torch.empty(B, Hq, q_len, device=DEV)
-    head = (fa.SCORE_IDENTITY, mask_id, params, bm, D ** -0.5)
+    head = (score_id, mask_id, params, bm, D ** -0.5)
     fa.flexattn_forward(Q, K, V, *head, O, LSE)
     n = hp.nonempty_blocks(bm)
     for stored in (False, True):
@@ -49,28 +54,29 @@ def gradients(mask_id, mask_mod, S, Bq, Bk, params, everything=False, Hq=2, Hkv=
 
 
 MASKS = {"causal": lambda fa, w: (fa.MASK_CAUSAL, fo.causal_mask, fa.ModParams()),
+         "capped": lambda fa, w: (fa.MASK_CAUSAL, fo.causal_mask, fa.ModParams()),
          "none": lambda fa, w: (fa.MASK_NONE, fo.no_mask, fa.ModParams()),
          "window": lambda fa, w: (fa.MASK_SWA_CAUSAL, fo.and_mask(fo.causal_mask, fo.sliding_window_mask(w)), fa.ModParams(window=w)),
          "prefix": lambda fa, w: (fa.MASK_PREFIX_LM, fo.or_mask(fo.causal_mask, fo.prefix_mask(w)), fa.ModParams(prefix_len=w))}
 
 
 @pytest.mark.parametrize("Bq,Bk", [(128, 64), (64, 128), (128, 128), (64, 64)])
-@pytest.mark.parametrize("mask,S,w", [("causal", 300, 0), ("causal", 1100, 0), ("none", 777, 0), ("window", 1000, 195),
+@pytest.mark.parametrize("mask,S,w", [("capped", 300, 0), ("capped", 1100, 0), ("causal", 300, 0), ("causal", 1100, 0), ("none", 777, 0), ("window", 1000, 195),
                                       ("window", 830, 31), ("prefix", 700, 130)])
 def test_hidden_steps(mask, S, w, Bq, Bk):
     import paper_2412_05496_amd as fa
     mask_id, mask_mod, params = MASKS[mask](fa, w)
     print(f"[case] {mask} S={S} blocks {Bq}x{Bk}", flush=True)
-    gradients(mask_id, mask_mod, S, Bq, Bk, params, B=40)       # (enough workgroups for the kernel of whole columns)
+    gradients(mask_id, mask_mod, S, Bq, Bk, params, B=40, capped=mask == "capped")       # (enough workgroups for the kernel of whole columns)
 
 
-@pytest.mark.parametrize("mask,S,w", [("causal", 2500, 0), ("window", 2500, 100), ("causal", 5000, 0), ("window", 4200, 70)])
+@pytest.mark.parametrize("mask,S,w", [("capped", 2500, 0), ("causal", 2500, 0), ("window", 2500, 100), ("causal", 5000, 0), ("window", 4200, 70)])
 def test_lists_full_of_hidden_blocks(mask, S, w):
-    """Up to 39, 38, 78 and 65 hidden steps in a column's list: fewer than an entry counts and more, fewer than 64 in a row and more."""
+    """Up to 39, 39, 38, 78 and 65 hidden steps in a column's list: fewer than an entry counts and more, fewer than 64 in a row and more."""
     import paper_2412_05496_amd as fa
     mask_id, mask_mod, params = MASKS[mask](fa, w)
     print(f"[case] {mask} S={S}", flush=True)
-    gradients(mask_id, mask_mod, S, 64 if S < 3000 else 128, 64, params, everything=True, Hq=1, B=12)
+    gradients(mask_id, mask_mod, S, 64 if S < 3000 else 128, 64, params, everything=True, Hq=1, B=12, capped=mask == "capped")
 
 
 def test_columns_without_a_visible_step():
