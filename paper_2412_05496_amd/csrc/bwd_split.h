@@ -649,6 +649,11 @@ inline bool canvas_cut_pays(const flexattn_mod_params& p) {
     const int side = p.na_width < p.na_height ? p.na_width : p.na_height;
     return side >= 24 && 5 * p.na_kernel <= 3 * side;
 }
+// Whether dK/dV looks for steps to leave out (LEAVE).  Lists of 64 x 64 blocks have none.  Workgroups that all run at once end with the longest
+// column, which seldom has any, and later by the look: D = 128, 11 x 2 heads, S = 465, prefix, 128 x 128 16.1 -> 16.4 us.
+inline bool leaving_out_pays(const BwdArgs& a, int D, unsigned grid) {
+    return a.Bq + a.Bk > 128 && grid > 256u * (unsigned)bwd_waves_per_simd_of(D);
+}
 template <uint32_t MASK, uint32_t SCORE>
 void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
     constexpr bool even = mask_uses(MASK, FLEXATTN_M_DOCUMENT) ||
@@ -756,6 +761,7 @@ int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t 
         } else {
             BwdArgs akv = a;
             akv.abreast = units_abreast(kv_units, a.NC * (a.Bk / 64), bwd_waves_per_simd_of(D), uneven && !mask_uses(MASK, FLEXATTN_M_DOCUMENT) ? kColumnsAbreast : 1);
+            akv.leave_out = leaving_out_pays(a, D, grid_kv);
             if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, akv);
             else launch_dkdv64<MASK, SCORE>(akv, grid_kv, st);
         }
