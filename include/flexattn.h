@@ -244,7 +244,8 @@ int flexattn_forward(const flexattn_dims* dims,
  * rel_bias) come from flexattn_backward_captured.  dQ [B,Hq,q_len,D], dK, dV [B,Hkv,kv_len,D] bf16.
  *   ws     device workspace of flexattn_backward_workspace_bytes(dims) bytes: two floats per query row, and where few KV heads
  *          are shared by many query heads room for the fp32 sums of parts of a group, which several workgroups then work
- *          out side by side.  Less is an error only below the two floats per row; without room for the sums a workgroup takes a whole group.
+ *          out side by side.  Less is an error only below the two floats per row; without room for the sums a workgroup takes a whole group,
+ *          which may change the last bits of dK and dV (the order of the additions).
  */
 size_t flexattn_backward_workspace_bytes(const flexattn_dims* dims);
 int flexattn_backward(const flexattn_dims* dims,
@@ -290,10 +291,11 @@ int flexattn_backward_stages(const flexattn_dims* dims,
  *             flexattn_blockmask_build.  A smaller value gives wrong gradients for the blocks that
  *             do not fit (slots are clamped; nothing is accessed outside the workspace).
  *   ws        device workspace, 256-byte aligned, of flexattn_backward_stored_workspace_bytes()
- *             bytes: the row scalars (and sums of parts of a group, which may be missing as above), one int32 per block position of the BlockMask grid, and
+ *             bytes: the row scalars, one int32 per block position of the BlockMask grid, and
  *             2 * Bq * Bk bytes per block and per head that does not share the BlockMask plane with
  *             an equal (b, hq) -- B * Hq * n_blocks blocks for a broadcast BlockMask (config 2:
- *             64 heads x 4160 blocks x 16 KiB = 4.4 GB).  Returns 0 for invalid arguments.
+ *             64 heads x 4160 blocks x 16 KiB = 4.4 GB); behind them the sums of parts of a group, which may be missing as
+ *             above: where the rest lies does not change with ws_bytes.  Returns 0 for invalid arguments.
  *   stages    as in flexattn_backward_stages (FLEXATTN_BWD_ALL for the whole backward): DELTA also
  *             numbers the blocks and must have run on the workspace first; DKDV writes dK, dV and
  *             the dS blocks; DQ reads them, so it must follow DKDV on the same workspace.

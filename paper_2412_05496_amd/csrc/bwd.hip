@@ -22,7 +22,7 @@ using namespace flexattn;
 namespace {
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 size_t row_scalar_bytes(const flexattn_dims* d) { return (size_t)2 * d->B * d->Hq * d->q_len * sizeof(float); }
-// Room, behind the row scalars, for the sums of divided groups: as many parts as columns that all rows list would be given.
+// Room, behind what a workspace must hold, for the sums of divided groups: as many parts as columns that all rows list would be given.
 size_t kv_part_bytes(const flexattn_dims* d) {
     if (d->Hkv <= 0 || d->kv_len <= 0 || d->Hq % d->Hkv || (d->D != 64 && d->D != 128)) return 0;
     const size_t parts = (size_t)kv_head_parts((int64_t)d->B * d->Hkv, d->Hq / d->Hkv, d->kv_len, d->D, d->q_len);
@@ -38,14 +38,14 @@ extern "C" size_t flexattn_backward_workspace_bytes(const flexattn_dims* d) {
 
 namespace {
 // Workspace of the backward that keeps dS in memory: the row scalars of the recomputing backward,
-// then the slot numbering (column bases, grid), then the dS blocks.
+// then the slot numbering (column bases, grid), then the dS blocks, which end at `end`.  (What is optional, the sums of divided groups, comes
+// behind them: stages that are called with workspaces of different sizes find one another's blocks.)
 struct StoredLayout {
-    size_t part_off, colbase_off, grid_off, store_off, total;
+    size_t colbase_off, grid_off, store_off, end;
     int64_t cap;        // slots per head
     int lines, planes;
 };
-// parts: with room for the sums of divided groups
-bool stored_layout(const flexattn_dims* d, const flexattn_blockmask* bm, int64_t n_blocks, bool parts, StoredLayout* out) {
+bool stored_layout(const flexattn_dims* d, const flexattn_blockmask* bm, int64_t n_blocks, StoredLayout* out) {
     if (!d || !bm || d->B <= 0 || d->Hq <= 0 || d->q_len <= 0 || d->kv_len <= 0 || n_blocks < 0) return false;
     if (bm->Bq <= 0 || bm->Bk <= 0 || bm->Bm <= 0 || bm->Hm <= 0) return false;
     const int64_t NR = (d->q_len + bm->Bq - 1) / bm->Bq, NC = (d->kv_len + bm->Bk - 1) / bm->Bk;
@@ -56,11 +56,10 @@ bool stored_layout(const flexattn_dims* d, const flexattn_blockmask* bm, int64_t
     out->cap = cap;
     out->lines = (int)lines;
     out->planes = (int)planes;
-    out->part_off = align256(row_scalar_bytes(d));
-    out->colbase_off = out->part_off + (parts ? kv_part_bytes(d) : 0);
+    out->colbase_off = align256(row_scalar_bytes(d));
     out->grid_off = out->colbase_off + align256((size_t)(lines + 1) * sizeof(int32_t));
     out->store_off = out->grid_off + align256((size_t)(planes * NR * NC) * sizeof(int32_t));
-    out->total = out->store_off + (size_t)reps * (size_t)cap * (size_t)bm->Bq * (size_t)bm->Bk * sizeof(bf16);
+    out->end = out->store_off + (size_t)reps * (size_t)cap * (size_t)bm->Bq * (size_t)bm->Bk * sizeof(bf16);
     return true;
 }
 
@@ -154,18 +153,13 @@ int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
     const int vi = variant_of(mask_id, score_id, params, true);
     if (vi < 0) return FLEXATTN_ERR_UNSUPPORTED;
     bool stored = ds_blocks >= 0;
-    bool divided;       // (a workspace without room for the sums of divided groups will do)
     StoredLayout lay = {};
     if (stored) {
-        if (!stored_layout(dims, bm, ds_blocks, true, &lay)) return FLEXATTN_ERR_INVALID_ARG;
+        if (!stored_layout(dims, bm, ds_blocks, &lay)) return FLEXATTN_ERR_INVALID_ARG;
         if (((uintptr_t)ws & 255)) return FLEXATTN_ERR_INVALID_ARG;
-        divided = ws_bytes >= lay.total;
-        if (!divided) stored_layout(dims, bm, ds_blocks, false, &lay);
-        if (ws_bytes < lay.total) return FLEXATTN_ERR_WORKSPACE;
-    } else {
-        if (ws_bytes < row_scalar_bytes(dims)) return FLEXATTN_ERR_WORKSPACE;
-        divided = ws_bytes >= flexattn_backward_workspace_bytes(dims);
     }
+    const size_t needed = stored ? lay.end : row_scalar_bytes(dims), part_off = align256(needed), part_bytes = kv_part_bytes(dims);
+    if (ws_bytes < needed) return FLEXATTN_ERR_WORKSPACE;
 
     BwdArgs a = {};
     a.Q = (const bf16*)Q->ptr; a.K = (const bf16*)K->ptr; a.V = (const bf16*)V->ptr;
@@ -193,7 +187,7 @@ int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
     a.kv_order = bm->kv_order; a.q_order = bm->q_order;
     a.scale = scale;
     if (params) a.p = *params;
-    if (divided && kv_part_bytes(dims)) a.kv_part = (float*)((char*)ws + align256(row_scalar_bytes(dims)));
+    if (part_bytes && ws_bytes >= part_off + part_bytes) a.kv_part = (float*)((char*)ws + part_off);     // (a workspace without room for them will do)
     if (stages & FLEXATTN_BWD_DQ) {
         // outputs written over inputs: dQ over Q or dO waits for dK/dV, over O or LSE for the pass that makes the row scalars of
         // them (but over O row for row: a wave reads its rows of O before it writes them); with dS in memory it may also take V's place
@@ -269,7 +263,9 @@ extern "C" int flexattn_backward(const flexattn_dims* dims, const flexattn_tenso
 extern "C" size_t flexattn_backward_stored_workspace_bytes(const flexattn_dims* dims, const flexattn_blockmask* bm,
                                                            int64_t n_blocks) {
     StoredLayout lay;
-    return stored_layout(dims, bm, n_blocks, true, &lay) ? lay.total : 0;
+    if (!stored_layout(dims, bm, n_blocks, &lay)) return 0;
+    const size_t parts = kv_part_bytes(dims);
+    return parts ? align256(lay.end) + parts : lay.end;
 }
 
 extern "C" int flexattn_backward_stored(const flexattn_dims* dims, const flexattn_tensor* Q, const flexattn_tensor* K,

@@ -83,8 +83,7 @@ def test_divided_groups(B, Hq, Hkv, S, D, mask, Bq, Bk, per_head, parts):
     # with dS in memory, bit for bit, by stages and with no more room than whole groups need
     n = hp.nonempty_blocks(bm)
     need = fa.flexattn_backward_stored_workspace_bytes(q, k, bm, n)
-    parts_room = (fa.flexattn_backward_workspace_bytes(q, k) + 255) // 256 * 256 - (scalars + 255) // 256 * 256
-    for room, want in ((need, got[0]), (need - parts_room, got[1])):
+    for room, want in ((need, got[0]), (need - hp.room_for_parts(q, k), got[1])):
         ws = torch.full((room,), 0xFF, dtype=torch.uint8, device=DEV)
         dQ, dK, dV = (torch.full_like(t, float("nan")) for t in (q, k, k))
         for stages in (1, 2, 4):
@@ -94,3 +93,36 @@ def test_divided_groups(B, Hq, Hkv, S, D, mask, Bq, Bk, per_head, parts):
         assert torch.equal(dK, want[0]) and torch.equal(dV, want[1])
     with pytest.raises(fa.FlexAttnError):
         fa.flexattn_backward(q, k, v, O, do, LSE, *head, dQ, dK, dV, ws[:scalars - 4])
+
+
+def test_stages_with_workspaces_of_different_sizes():
+    """Where the block numbers and dS lie does not depend on whether the workspace has room for the parts' sums: every stage may be
+    told of it or not.  (dQ first: the others' blocks at other places would be read, within the workspace.)"""
+    import paper_2412_05496_amd as fa
+    B, Hq, Hkv, S, D = 1, 4, 1, 709, 128
+    gen = torch.Generator().manual_seed(5)
+    Q, dO = (torch.randn(B, Hq, S, D, generator=gen).to(torch.bfloat16) for _ in range(2))
+    K, V = (torch.randn(B, Hkv, S, D, generator=gen).to(torch.bfloat16) for _ in range(2))
+    bm = fa.alloc_blockmask(1, 1, S, S, 128, 64, device=DEV)
+    params = fa.ModParams()
+    fa.flexattn_blockmask_build(fa.MASK_CAUSAL, params, bm)
+    q, k, v, do = (t.to(DEV) for t in (Q, K, V, dO))
+    O, LSE = torch.empty_like(q), torch.empty(B, Hq, S, device=DEV)
+    head = (fa.SCORE_IDENTITY, fa.MASK_CAUSAL, params, bm, D ** -0.5)
+    fa.flexattn_forward(q, k, v, *head, O, LSE)
+    ref = fo.flex_attention_backward(Q, K, V, dO, fo.Identity(), fo.causal_mask, D ** -0.5)
+    n = hp.nonempty_blocks(bm)
+    need, less = fa.flexattn_backward_stored_workspace_bytes(q, k, bm, n), hp.room_for_parts(q, k)
+    assert less > 0
+    first = None
+    for lacking in (4, 0, 7, 3, 2, 5, 1, 6):                # the stages (a bit each) whose workspace lacks the room
+        print("[case] lacking", lacking, flush=True)
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device=DEV)
+        dQ, dK, dV = (torch.full_like(t, float("nan")) for t in (q, k, k))
+        for stage in (1, 2, 4):
+            fa.flexattn_backward_stored(q, k, v, O, do, LSE, *head, dQ, dK, dV, n, ws[:need - less] if lacking & stage else ws, stage)
+        torch.cuda.synchronize()
+        for name, g, r in zip(("dQ", "dK", "dV"), (dQ, dK, dV), ref):
+            hp.check_grad(name, g, r)
+        first = dQ if first is None else first
+        assert torch.equal(dQ, first)
