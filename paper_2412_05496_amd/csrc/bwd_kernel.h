@@ -89,18 +89,24 @@ inline int kv_head_parts(int64_t units, int G, int kv_len, int D, int64_t longes
         if (steps >= (int64_t)p * (tiles * p <= 128 ? (D == 64 ? 12 : 4) : (D == 64 ? 48 : 32))) parts = p;
     return parts;
 }
-// The query heads of a group that a dK/dV workgroup takes, and where their sums go.
+// The query heads of a group that a dK/dV workgroup takes, and where their sums go.  Kernels of their own: what this keeps over the walk and the second way
+// to write the sums spill up to 6 registers in those that take whole groups, whose launches of one round last up to 4 % longer (one kernel for both -> two, us: D = 64,
+// window of 300 and soft-cap, S = 1000, 32 heads 17.6 -> 17.2, documents with ALiBi, S = 800, 24 heads 18.0 -> 17.6; D = 128, causal, S = 1000, 4 heads 18.5 -> 17.7, no mask,
+// S = 500, 8 heads 13.5 -> 13.0).
+template <bool DIVIDED>
 struct KvHeads {
     int part, first, end;
     // unit: (b, hkv, part) -> (b, hkv)
     __device__ __forceinline__ KvHeads(const BwdArgs& a, int& unit) : part(0), first(0), end(a.G) {
-        if (a.head_parts > 1) {
+        if (DIVIDED && a.head_parts > 1) {      // (it always is, but unless that is asked the parts' addresses are made ahead of the walk and spill 50 scalar
+                                                // registers: relative bias, window of 200 or prefix of 64, S = 8192, 16 / 2 heads, D = 128, 389 -> 405 us, D = 64 159 -> 169)
             part = unit % a.head_parts;
             unit /= a.head_parts;
             first = part * a.G / a.head_parts;
             end = (part + 1) * a.G / a.head_parts;
         }
     }
+    __host__ __device__ __forceinline__ static int units(const BwdArgs& a) { return a.B * a.Hkv * (DIVIDED ? a.head_parts : 1); }
     __device__ __forceinline__ float* sums(const BwdArgs& a, int unit, int is_k, int D) const {
         return a.kv_part + (((int64_t)(2 * part + is_k) * a.B * a.Hkv + unit) * a.kv_len) * D;
     }
@@ -245,7 +251,7 @@ constexpr bool dkdv_own_rows() {
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
-template <int D, uint32_t MASK, uint32_t SCORE, bool OWN = dkdv_own_rows<D, MASK, SCORE>(), bool CUT = PartialMask<MASK>::kCanvas>
+template <int D, uint32_t MASK, uint32_t SCORE, bool OWN = dkdv_own_rows<D, MASK, SCORE>(), bool CUT = PartialMask<MASK>::kCanvas, bool DIVIDED = false>
 __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(const BwdArgs a) {
     constexpr int TQ = 64;                         // query rows per step
     constexpr int TILE = TQ * D;                   // elements per LDS tile
@@ -271,9 +277,10 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     // head where the mask has a plane per head), the 64-key tiles of a column side by side.
     const int sub_k = a.Bk / 64;                   // tiles per column of blocks
     int unit, slot;                                // NC * sub_k slots >= tiles: the last column may be cut short
-    if (!unit_of_workgroup(a.B * a.Hkv * a.head_parts, a.NC * sub_k, a.abreast, unit, slot)) return;
-    if (a.ds_store) unit = last_unit_first(unit, a.B * a.Hkv * a.head_parts);
-    const KvHeads heads(a, unit);
+    using Heads = KvHeads<DIVIDED>;
+    if (!unit_of_workgroup(Heads::units(a), a.NC * sub_k, a.abreast, unit, slot)) return;
+    if (a.ds_store) unit = last_unit_first(unit, Heads::units(a));
+    const Heads heads(a, unit);
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     int col = slot / sub_k;
     if (a.q_order) {
@@ -757,8 +764,8 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     }
     // ---- dV (x = 0) or dK (x = 1, with the scale and the score_mod's gradient factor), bf16
     {
-        if (kv_lane >= a.kv_len) return;
-        if (a.kv_part) {                // (kv_parts_sum_kernel scales)
+        if (DIVIDED && a.kv_part) {     // (always, see KvHeads; kv_parts_sum_kernel scales)
+            if (kv_lane >= a.kv_len) return;
             float* out = heads.sums(a, unit, x, D) + (int64_t)kv_lane * D;
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
@@ -767,9 +774,11 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                     *(f32x4*)(out + db * 32 + 8 * rg + 4 * half) = f32x4{acc[db][4 * rg], acc[db][4 * rg + 1], acc[db][4 * rg + 2], acc[db][4 * rg + 3]};
             return;
         }
+        if (!Score::kRel && kv_lane >= a.kv_len) return;       // (a relative bias asks later: 6 spills instead of 8, the others 0 to 3 instead of 1 to 7)
         const float oscale = x ? a.scale * ScoreMod<SCORE>::grad_scale() : 1.0f;
         bf16* op = x ? a.dK + b * a.dk_sb + hkv * a.dk_sh + (int64_t)kv_lane * a.dk_ss
                      : a.dV + b * a.dv_sb + hkv * a.dv_sh + (int64_t)kv_lane * a.dv_ss;
+        if (Score::kRel && kv_lane >= a.kv_len) return;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll

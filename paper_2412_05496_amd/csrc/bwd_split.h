@@ -265,7 +265,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(
 // dK, dV.  Q and dO of 32 rows in two slots a wave, one unit ahead; K and V of the 32 keys in registers, dV^T and dK^T of the
 // wave's rows as well.  With dS kept in memory (ds_store) a unit writes its part of a step: that of wave (kb, x) in
 // bwd_dkdv_kernel; hidden units of index masks write zeros, those of a canvas are not read back.
-template <int D, int NW, uint32_t MASK, uint32_t SCORE>
+template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool DIVIDED>
 __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kernel(const BwdArgs a) {
     constexpr uint32_t UT = 32 * D * 2;
     constexpr int NKS = D / 16, NDB = D / 32;
@@ -279,8 +279,9 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
 
     const int parts = a.Bk / 32;
     int unit, slot_rank;
-    if (!unit_of_workgroup(a.B * a.Hkv * a.head_parts, a.NC * parts, a.abreast, unit, slot_rank)) return;
-    const KvHeads heads(a, unit);
+    using Heads = KvHeads<DIVIDED>;
+    if (!unit_of_workgroup(Heads::units(a), a.NC * parts, a.abreast, unit, slot_rank)) return;
+    const Heads heads(a, unit);
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     int col = slot_rank / parts;
     if (a.q_order) {
@@ -518,7 +519,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
     const float kscale = a.scale * Score::grad_scale();
     add_quads<NW, D / 4>((f32x4*)smem, w, lane, quads, [&](int q, const f32x4& o) __attribute__((always_inline)) {
         const bool is_k = q >= D / 8;
-        if (a.kv_part) {
+        if (DIVIDED && a.kv_part) {     // (always, see KvHeads)
             if (kv_lane < a.kv_len) *(f32x4*)(heads.sums(a, unit, is_k, D) + (int64_t)kv_lane * D + 8 * (q % (D / 8)) + 4 * half) = o;
             return;
         }
@@ -654,23 +655,45 @@ inline bool canvas_cut_pays(const flexattn_mod_params& p) {
 inline bool leaving_out_pays(const BwdArgs& a, int D, unsigned grid) {
     return a.Bq + a.Bk > 128 && grid > 256u * (unsigned)bwd_waves_per_simd_of(D);
 }
-template <uint32_t MASK, uint32_t SCORE>
+template <uint32_t MASK, uint32_t SCORE, bool DIVIDED>
 void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
+    constexpr bool own = dkdv_own_rows<64, MASK, SCORE>(), canvas = PartialMask<MASK>::kCanvas;
     constexpr bool even = mask_uses(MASK, FLEXATTN_M_DOCUMENT) ||
                           (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) && !mask_uses(MASK, FLEXATTN_M_PREFIX));
-    if constexpr (dkdv_own_rows<64, MASK, SCORE>() && !even && !(SCORE & FLEXATTN_SCORE_SOFTCAP)) {
+    if constexpr (own && !even && !(SCORE & FLEXATTN_SCORE_SOFTCAP)) {
         if (!own_rows_pay<MASK>(a, grid)) {
-            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false>), dim3(grid), dim3(256), 0, st, a);
+            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false, canvas, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
             return;
         }
     }
-    if constexpr (PartialMask<MASK>::kCanvas) {
+    if constexpr (canvas) {
         if (!canvas_cut_pays(a.p)) {
-            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false, false>), dim3(grid), dim3(256), 0, st, a);
+            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false, false, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
             return;
         }
     }
-    hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE>), dim3(grid), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, own, canvas, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
+}
+
+// dK/dV (DIVIDED: or the sums of the parts of a group)
+template <uint32_t MASK, uint32_t SCORE, bool DIVIDED>
+void launch_dkdv(const BwdArgs& args, int D, bool uneven, hipStream_t st) {
+    BwdArgs a = args;
+    const int units = KvHeads<DIVIDED>::units(a);
+    const int waves = dkdv_split_waves<MASK>(a, D);
+    if (waves) {
+        a.abreast = one_by_one(units);
+        const dim3 slices(unit_grid(units, a.NC * (a.Bk / 32)));
+        if (D == 128) hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 4, MASK, SCORE, DIVIDED>), slices, dim3(256), 0, st, a);
+        else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 8, MASK, SCORE, DIVIDED>), slices, dim3(512), 0, st, a);
+        else hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 4, MASK, SCORE, DIVIDED>), slices, dim3(256), 0, st, a);
+        return;
+    }
+    const unsigned grid = unit_grid(units, a.NC * (a.Bk / 64));
+    a.abreast = units_abreast(units, a.NC * (a.Bk / 64), bwd_waves_per_simd_of(D), uneven && !mask_uses(MASK, FLEXATTN_M_DOCUMENT) ? kColumnsAbreast : 1);
+    a.leave_out = leaving_out_pays(a, D, grid);
+    if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE, false, PartialMask<MASK>::kCanvas, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
+    else launch_dkdv64<MASK, SCORE, DIVIDED>(a, grid, st);
 }
 
 // Rows that the longest column of blocks sees (of a canvas: those around its pixels).
@@ -710,8 +733,6 @@ int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t 
     const bool uneven = line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven;
     auto rows_by = [&](int rows) { return units_abreast(units, a.G * rows, bwd_waves_per_simd_of(D), rows_abreast<MASK>(uneven, D)); };
     a.abreast = one_by_one(units);
-    const int kv_units = units * a.head_parts;
-    const unsigned grid_kv = unit_grid(kv_units, a.NC * (a.Bk / 64));
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
     // dQ first, where it makes the row scalars that dK/dV reads; last, after a pass that makes them, where it is written over
@@ -751,21 +772,8 @@ int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t 
     };
     if (q && !a.dq_last) run_dq();
     if (kv) {
-        const int waves = dkdv_split_waves<MASK>(a, D);
-        a.abreast = one_by_one(kv_units);
-        if (waves) {
-            const dim3 slices(unit_grid(kv_units, a.NC * (a.Bk / 32)));
-            if (D == 128) hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 4, MASK, SCORE>), slices, dim3(256), 0, st, a);
-            else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 8, MASK, SCORE>), slices, dim3(512), 0, st, a);
-            else hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 4, MASK, SCORE>), slices, dim3(256), 0, st, a);
-        } else {
-            BwdArgs akv = a;
-            akv.abreast = units_abreast(kv_units, a.NC * (a.Bk / 64), bwd_waves_per_simd_of(D), uneven && !mask_uses(MASK, FLEXATTN_M_DOCUMENT) ? kColumnsAbreast : 1);
-            akv.leave_out = leaving_out_pays(a, D, grid_kv);
-            if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE>), dim3(grid_kv), dim3(256), 0, st, akv);
-            else launch_dkdv64<MASK, SCORE>(akv, grid_kv, st);
-        }
-        a.abreast = one_by_one(units);
+        if (a.kv_part) launch_dkdv<MASK, SCORE, true>(a, D, uneven, st);
+        else launch_dkdv<MASK, SCORE, false>(a, D, uneven, st);
         if (a.kv_part) {
             const float kscale = a.scale * ScoreMod<SCORE>::grad_scale();
             const int64_t eights = (int64_t)units * a.kv_len * (D / 8);
