@@ -66,7 +66,6 @@ struct BwdArgs {
     flexattn_mod_params p;
     bool make_delta;           // the dQ kernel works the row scalars out itself (and writes them)
     bool dq_last;              // (host) dQ is written over what dK/dV or the row scalars are made of: it runs last, after a pass for the latter
-    bool leave_out;        // dK/dV: LEAVE is worth its look at the steps (leaving_out_pays)
     int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
     UnitSets abreast;      // of the launch (unit_of_workgroup)
     int head_parts;        // dK/dV: workgroups among which the query heads of a group are divided (kv_head_parts)
@@ -235,7 +234,7 @@ __device__ __forceinline__ int canvas_step_bits(const flexattn_mod_params& p, in
 // 1047 -> 907 us; 100 x 90 row-major, K = 9: 802 -> 771; D = 64 where canvas_cut_pays, 128 x 128, K = 13 548 -> 481, 64 x 64 in Morton order, K = 21,
 // 234 -> 204).
 //
-// LEAVE (no own rows, other masks; a relative bias with a soft-cap would spill more): the walk leaves out the steps at its front, where the PARTIAL blocks are, that the indices alone hide
+// LEAVE (kernels of their own; no own rows, other masks; a relative bias with a soft-cap would spill more): the walk leaves out the steps at its front, where the PARTIAL blocks are, that the indices alone hide
 // from all four waves: every other column of 64 keys has one at its diagonal if Bq = 128 or Bk = 128, one at the window's far edge, and all have
 // one behind a q_len in the first half of its block.  us, B x H = 256, D = 128: causal, S = 1024 214 -> 207,
 // S = 300 (512) 79.6 -> 72; window of 512, S = 4096 (64) 218 -> 209; window of 195, soft-cap, Bq = 64, Bk = 128, S = 2427 (512) 673 -> 608;
@@ -248,10 +247,15 @@ constexpr bool dkdv_own_rows() {
     constexpr bool biased_cap = (SCORE & FLEXATTN_SCORE_SOFTCAP) && (SCORE & (FLEXATTN_SCORE_ALIBI | FLEXATTN_SCORE_REL_BIAS));
     return D == 64 && !PartialMask<MASK>::kCanvas && !biased_cap;
 }
+// Whether there are kernels that LEAVE (leaving_out_pays: which launches take them).
+template <int D, uint32_t MASK, uint32_t SCORE>
+constexpr bool dkdv_can_leave() {
+    return !dkdv_own_rows<D, MASK, SCORE>() && !PartialMask<MASK>::kCanvas && !((SCORE & FLEXATTN_SCORE_REL_BIAS) && (SCORE & FLEXATTN_SCORE_SOFTCAP));
+}
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
-template <int D, uint32_t MASK, uint32_t SCORE, bool OWN = dkdv_own_rows<D, MASK, SCORE>(), bool CUT = PartialMask<MASK>::kCanvas, bool DIVIDED = false>
+template <int D, uint32_t MASK, uint32_t SCORE, bool OWN = dkdv_own_rows<D, MASK, SCORE>(), bool CUT = PartialMask<MASK>::kCanvas, bool DIVIDED = false, bool LEAVE = false>
 __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(const BwdArgs a) {
     constexpr int TQ = 64;                         // query rows per step
     constexpr int TILE = TQ * D;                   // elements per LDS tile
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     constexpr int kListMax = 512;
     __shared__ int s_steps[kListMax + 2];          // the walk of the current head, see below
     __shared__ int s_pos[CUT ? kListMax + 2 : 1], s_count;
-    constexpr bool LEAVE = !OWN && !PartialMask<MASK>::kCanvas && !((SCORE & FLEXATTN_SCORE_REL_BIAS) && (SCORE & FLEXATTN_SCORE_SOFTCAP));
+    static_assert(!LEAVE || dkdv_can_leave<D, MASK, SCORE>(), "of the waves that exchange P and dS, and of masks that the indices decide");
     __shared__ uint64_t s_left_out;
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];   // relative-bias row of the current head
@@ -444,7 +448,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
                 const int q0 = blk * a.Bq + sidx * TQ;
                 int up = 0;
                 if constexpr (LEAVE) {
-                    if (a.leave_out && i < 64) {
+                    if (i < 64) {
                         const bool hid = seg0 == 0 && pos >= n_full && (q0 >= a.q_len || mask.hidden(q_off + q0, q_off + q0 + TQ - 1, kv0, kv0 + 63));
                         uint64_t out = __ballot(hid);
                         if (__popcll(out) == H) out &= ~1ull;                       // (no segment is empty)
@@ -462,7 +466,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
             }
             __syncthreads();
             uint64_t left_out = 0;
-            if (LEAVE && a.leave_out)
+            if constexpr (LEAVE)
                 left_out = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(s_left_out >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)s_left_out);
             const int first = __popcll(left_out);
             int ld_v = first;                       // step whose loads are issued next

@@ -651,12 +651,17 @@ inline bool canvas_cut_pays(const flexattn_mod_params& p) {
     return side >= 24 && 5 * p.na_kernel <= 3 * side;
 }
 // Whether dK/dV looks for steps to leave out (LEAVE).  Lists of 64 x 64 blocks have none.  Workgroups that all run at once end with the longest
-// column, which seldom has any, and later by the look: D = 128, 11 x 2 heads, S = 465, prefix, 128 x 128 16.1 -> 16.4 us.
-inline bool leaving_out_pays(const BwdArgs& a, int D, unsigned grid) {
+// column, which seldom has any, and later by the look: D = 128, 11 x 2 heads, S = 465, prefix, 128 x 128 16.1 -> 16.4 us.  A relative bias spills 5 registers with
+// the walk's gap, and looks only where most columns have hidden steps, those of 128 keys, or behind a q_len in the first half of its block: us, D = 128, 16 heads, no look -> look,
+// B x S, window of 300 (S = 300: of 100), 16 x 300 49.1 -> 46.3, 128 x 128 50.7 -> 46.9, 16 x 947 / 4 KV heads 177 -> 172, 128 x 128 206 -> 193, but 8 x 1000 109.7 -> 111.3
+// (128 x 128 114.6 -> 111.5), with dS in memory 111.7 -> 115.4.
+template <uint32_t MASK, uint32_t SCORE>
+bool leaving_out_pays(const BwdArgs& a, int D, unsigned grid) {
+    if ((SCORE & FLEXATTN_SCORE_REL_BIAS) && a.Bk == 64 && (a.q_len - 1) % 128 >= 64) return false;
     return a.Bq + a.Bk > 128 && grid > 256u * (unsigned)bwd_waves_per_simd_of(D);
 }
 template <uint32_t MASK, uint32_t SCORE, bool DIVIDED>
-void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
+void launch_dkdv64(const BwdArgs& a, unsigned grid, bool leave_out, hipStream_t st) {
     constexpr bool own = dkdv_own_rows<64, MASK, SCORE>(), canvas = PartialMask<MASK>::kCanvas;
     constexpr bool even = mask_uses(MASK, FLEXATTN_M_DOCUMENT) ||
                           (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) && !mask_uses(MASK, FLEXATTN_M_PREFIX));
@@ -669,6 +674,12 @@ void launch_dkdv64(const BwdArgs& a, unsigned grid, hipStream_t st) {
     if constexpr (canvas) {
         if (!canvas_cut_pays(a.p)) {
             hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false, false, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
+            return;
+        }
+    }
+    if constexpr (dkdv_can_leave<64, MASK, SCORE>() && !DIVIDED) {          // (divided launches are no larger than a round)
+        if (leave_out) {
+            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, own, canvas, false, true>), dim3(grid), dim3(256), 0, st, a);
             return;
         }
     }
@@ -691,9 +702,16 @@ void launch_dkdv(const BwdArgs& args, int D, bool uneven, hipStream_t st) {
     }
     const unsigned grid = unit_grid(units, a.NC * (a.Bk / 64));
     a.abreast = units_abreast(units, a.NC * (a.Bk / 64), bwd_waves_per_simd_of(D), uneven && !mask_uses(MASK, FLEXATTN_M_DOCUMENT) ? kColumnsAbreast : 1);
-    a.leave_out = leaving_out_pays(a, D, grid);
-    if (D == 128) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE, false, PartialMask<MASK>::kCanvas, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
-    else launch_dkdv64<MASK, SCORE, DIVIDED>(a, grid, st);
+    const bool leave_out = leaving_out_pays<MASK, SCORE>(a, D, grid);
+    if (D == 64) return launch_dkdv64<MASK, SCORE, DIVIDED>(a, grid, leave_out, st);
+    constexpr bool canvas = PartialMask<MASK>::kCanvas;
+    if constexpr (dkdv_can_leave<128, MASK, SCORE>()) {
+        if (leave_out) {
+            hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE, false, canvas, DIVIDED, true>), dim3(grid), dim3(256), 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE, false, canvas, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
 }
 
 // Rows that the longest column of blocks sees (of a canvas: those around its pixels).

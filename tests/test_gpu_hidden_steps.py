@@ -21,6 +21,10 @@ def gradients(mask_id, mask_mod, S, Bq, Bk, params, everything=False, Hq=2, q_le
         bias = torch.tensor([-0.03, 0.01])[:Hq]
         params.alibi_bias, params.softcap = bias.to(DEV), 30.0
         score_id, score = fa.SCORE_ALIBI | fa.SCORE_SOFTCAP, fo.Compose(fo.Alibi(bias), fo.Softcap(30.0))
+    if mask_id == fa.MASK_SWA_CAUSAL_OR_PREFIX:         # (compiled with a relative bias)
+        table = 0.3 * torch.randn(Hq, 90, generator=torch.Generator().manual_seed(3))
+        params.rel_bias = table.to(DEV)
+        score_id, score = fa.SCORE_REL_BIAS, fo.RelBias(table.double())
     g = torch.Generator().manual_seed(S + Bq + Bk)
     Q, dO = (torch.randn(B, Hq, q_len, D, generator=g).to(torch.bfloat16) for _ in range(2))
     K, V = (torch.randn(B, Hkv, S, D, generator=g).to(torch.bfloat16) for _ in range(2))
@@ -58,12 +62,15 @@ MASKS = {"causal": lambda fa, w: (fa.MASK_CAUSAL, fo.causal_mask, fa.ModParams()
          "capped": lambda fa, w: (fa.MASK_CAUSAL, fo.causal_mask, fa.ModParams()),
          "none": lambda fa, w: (fa.MASK_NONE, fo.no_mask, fa.ModParams()),
          "window": lambda fa, w: (fa.MASK_SWA_CAUSAL, fo.and_mask(fo.causal_mask, fo.sliding_window_mask(w)), fa.ModParams(window=w)),
+         "biased": lambda fa, w: (fa.MASK_SWA_CAUSAL_OR_PREFIX, fo.or_mask(fo.and_mask(fo.causal_mask, fo.sliding_window_mask(w)), fo.prefix_mask(40)),
+                                  fa.ModParams(window=w, prefix_len=40)),
          "prefix": lambda fa, w: (fa.MASK_PREFIX_LM, fo.or_mask(fo.causal_mask, fo.prefix_mask(w)), fa.ModParams(prefix_len=w))}
 
 
 @pytest.mark.parametrize("Bq,Bk", [(128, 64), (64, 128), (128, 128), (64, 64)])
 @pytest.mark.parametrize("mask,S,w", [("capped", 300, 0), ("capped", 1100, 0), ("causal", 300, 0), ("causal", 1100, 0), ("none", 777, 0), ("window", 1000, 195),
-                                      ("window", 830, 31), ("prefix", 700, 130)])
+                                      ("window", 830, 31), ("prefix", 700, 130), ("biased", 300, 100),
+                                      ("biased", 1000, 195)])
 def test_hidden_steps(mask, S, w, Bq, Bk):
     import paper_2412_05496_amd as fa
     mask_id, mask_mod, params = MASKS[mask](fa, w)
@@ -71,9 +78,9 @@ def test_hidden_steps(mask, S, w, Bq, Bk):
     gradients(mask_id, mask_mod, S, Bq, Bk, params, capped=mask == "capped")
 
 
-@pytest.mark.parametrize("mask,S,w", [("capped", 2500, 0), ("causal", 2500, 0), ("window", 2500, 100), ("causal", 5000, 0), ("window", 4200, 70)])
+@pytest.mark.parametrize("mask,S,w", [("capped", 2500, 0), ("causal", 2500, 0), ("window", 2500, 100), ("causal", 5000, 0), ("window", 4200, 70), ("biased", 2500, 100)])
 def test_lists_full_of_hidden_blocks(mask, S, w):
-    """Up to 39, 39, 38, 78 and 65 hidden steps in a column's list: fewer than an entry counts and more, fewer than 64 in a row and more."""
+    """Up to 39, 39, 38, 78, 65 and 38 hidden steps in a column's list: fewer than an entry counts and more, fewer than 64 in a row and more."""
     import paper_2412_05496_amd as fa
     mask_id, mask_mod, params = MASKS[mask](fa, w)
     print(f"[case] {mask} S={S}", flush=True)
