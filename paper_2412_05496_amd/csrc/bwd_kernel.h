@@ -46,6 +46,9 @@ struct BwdArgs {
     int B, Hq, Hkv, G, q_len, kv_len;
     int NR, NC, Bq, Bk;
     int bm_Bm, bm_Hm;
+    UnitSets abreast;      // of the launch (unit_of_workgroup)
+    int head_parts;        // dK/dV: workgroups among which the query heads of a group are divided (kv_head_parts)
+    int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
     const int32_t* kv_num;
     const int32_t* kv_idx;
     const int32_t* full_kv_num;
@@ -66,10 +69,7 @@ struct BwdArgs {
     flexattn_mod_params p;
     bool make_delta;           // the dQ kernel works the row scalars out itself (and writes them)
     bool dq_last;              // (host) dQ is written over what dK/dV or the row scalars are made of: it runs last, after a pass for the latter
-    int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
-    UnitSets abreast;      // of the launch (unit_of_workgroup)
-    int head_parts;        // dK/dV: workgroups among which the query heads of a group are divided (kv_head_parts)
-    float* kv_part;        //        more than one: their sums, [head_parts][dV, dK][B, Hkv, kv_len, D] (host: where there is room for them, or null)
+    float* kv_part;        // dK/dV, head_parts > 1: their sums, [head_parts][dV, dK][B, Hkv, kv_len, D] (host: where there is room for them, or null)
 };
 
 // Among how many workgroups the query heads of a group are divided.  One that takes them all walks G times the steps of a column: few KV heads

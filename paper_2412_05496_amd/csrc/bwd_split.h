@@ -43,7 +43,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(
     __shared__ uint8_t s_hidden[Mask::kCanvas ? kHiddenTiles : 1];
 
     int unit, rem;
-    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (a.Bq / 32), a.abreast, unit, rem)) return;
+    if (!unit_of_workgroup(a.B * a.Hkv, a.G * a.NR * (a.Bq / 32), one_by_one(a.B * a.Hkv), unit, rem)) return;
     const int slice = rem & (a.Bq / 32 - 1);
     rem >>= a.Bq == 128 ? 2 : 1;
     const int g = rem % a.G;
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
     const int parts = a.Bk / 32;
     int unit, slot_rank;
     using Heads = KvHeads<DIVIDED>;
-    if (!unit_of_workgroup(Heads::units(a), a.NC * parts, a.abreast, unit, slot_rank)) return;
+    if (!unit_of_workgroup(Heads::units(a), a.NC * parts, one_by_one(Heads::units(a)), unit, slot_rank)) return;
     const Heads heads(a, unit);
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     int col = slot_rank / parts;
@@ -693,7 +693,6 @@ void launch_dkdv(const BwdArgs& args, int D, bool uneven, hipStream_t st) {
     const int units = KvHeads<DIVIDED>::units(a);
     const int waves = dkdv_split_waves<MASK>(a, D);
     if (waves) {
-        a.abreast = one_by_one(units);
         const dim3 slices(unit_grid(units, a.NC * (a.Bk / 32)));
         if (D == 128) hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 4, MASK, SCORE, DIVIDED>), slices, dim3(256), 0, st, a);
         else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 8, MASK, SCORE, DIVIDED>), slices, dim3(512), 0, st, a);
@@ -750,7 +749,6 @@ int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t 
     if (a.head_parts == 1) a.kv_part = nullptr;
     const bool uneven = line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven;
     auto rows_by = [&](int rows) { return units_abreast(units, a.G * rows, bwd_waves_per_simd_of(D), rows_abreast<MASK>(uneven, D)); };
-    a.abreast = one_by_one(units);
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
     // dQ first, where it makes the row scalars that dK/dV reads; last, after a pass that makes them, where it is written over

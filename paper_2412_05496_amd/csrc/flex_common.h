@@ -243,12 +243,20 @@ struct UnitSets {
 // us, that -> this, causal: S = 16384, D = 128, 1 head, forward 472 -> 289, dK/dV 832 -> 269, dQ 574 -> 326; 3 heads, D = 64,
 // 309 -> 213, 537 -> 262, 371 -> 238; S = 8192, D = 128, 16 query and 2 KV heads 874 -> 285, 1855 -> 1074, 1064 -> 369; S = 4096, 9
 // heads, D = 64, 76 -> 54, 82 -> 61, 83 -> 61, D = 128, 105 -> 80, 130 -> 93, 130 -> 92; 8 and 16 heads the same within 2 %.)
-// The units of a set take turns piece by piece, so that the long pieces of all start before the short ones (units_abreast).
+// The units of a set take turns piece by piece, so that the long pieces of all start before the short ones (units_abreast).  (A launch that all runs at once
+// lasts as long as its workgroups' way to their first load: kernels whose units always come one by one say so themselves, and the others' arguments lie
+// beside those that are read here anyway, where a line of their own cost 0.5 us: dK/dV, D = 128, causal, S = 1024, 16 heads.)
 __device__ __forceinline__ bool unit_of_workgroup(unsigned id, int units, int per_unit, UnitSets abreast, int& unit, int& rank) {
     const int xcd = id & 7, rest = units & 7, rest_pieces = rest * ((per_unit + 7) >> 3);
     const int k = id >> 3;
     if (k >= rest_pieces) {
-        const int p = k - rest_pieces, set = min(p / per_unit >> abreast.side, abreast.sets - 1);
+        const int p = k - rest_pieces, u = p / per_unit;
+        if (abreast.side == 0) {
+            unit = u * 8 + xcd;
+            rank = p - u * per_unit;
+            return true;
+        }
+        const int set = min(u >> abreast.side, abreast.sets - 1);
         const int first = set << abreast.side, in = p - first * per_unit;
         int of = in >> abreast.side, turn = in & ((1 << abreast.side) - 1);
         if (const int last = (units >> 3) - first; set + 1 == abreast.sets && last != 1 << abreast.side) {

@@ -41,6 +41,7 @@ struct FwdArgs {
     int B, Hq, Hkv, G, q_len, kv_len;
     int NR, NC, Bk, sub;   // BlockMask geometry; sub = Bk / 64 kernel tiles per block
     int bm_Bm, bm_Hm;
+    UnitSets abreast;      // of the launch (unit_of_workgroup)
     const int32_t* kv_num;
     const int32_t* kv_idx;
     const int32_t* full_num;
@@ -58,7 +59,6 @@ struct FwdArgs {
     int Bq;                // rows of a BlockMask block
     unsigned first_id;     // PAIRS: of the launch's workgroups, where there are several launches (kMaxLaunch)
     int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
-    UnitSets abreast;      // of the launch (unit_of_workgroup)
 };
 
 constexpr int kTileKV = 64;   // keys per kernel tile
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     // last-first without one (causal-like masks: longest first).
     int unit, rem, slice = 0;
     const int per_unit = a.G * (MIXED ? a.NR + a.halved : a.NR * (SPLIT ? Bq / 32 : PAIRS ? Bq / 64 : 1));
-    UnitSets abreast = a.abreast;
+    UnitSets abreast = SPLIT ? one_by_one(a.B * a.Hkv) : a.abreast;
     if constexpr (Mask::kDoc && !SPLIT) abreast = abreast_if_long(abreast, a.B * a.Hkv, longest_row(a.kv_order, a.full_num, a.kv_num, 0, a.NR, a.sub));
     if (!unit_of_workgroup(blockIdx.x + (PAIRS ? a.first_id : 0u), a.B * a.Hkv, per_unit, abreast, unit, rem)) return;
     if constexpr (SPLIT) {
