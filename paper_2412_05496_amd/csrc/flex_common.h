@@ -320,7 +320,8 @@ __device__ __forceinline__ int longest_row(const int32_t* order, const int32_t* 
 }
 // Documents of a few hundred tokens, which the host cannot tell from longer ones, head by head: their rows are bound by K and V, which then stay
 // in L2 (D = 64, 8192 x 64, us, head by head / abreast: of 30 to 300 tokens, forward 61 / 67, dQ 85 / 91, of 100 to 1000 95 / 95, 130 / 133, of 256 to 4096
-// 249 / 223, 304 / 278).  By the longest row of the launch's first plane, which all workgroups ask alike.
+// 249 / 223, 304 / 278).  By the longest row of the launch's first plane, which all workgroups ask alike, and also where no head takes turns (dQ, D = 64, 12 heads of
+// 3000, documents of 16 to 100: 13.3, asked only where some do 14.0, D = 128 21.1 and 21.8: the lines are needed next anyway).
 constexpr int kAbreastTiles = 24;
 __device__ __forceinline__ UnitSets abreast_if_long(UnitSets abreast, int units, int longest) {
     return longest > kAbreastTiles ? abreast : one_by_one(units);
