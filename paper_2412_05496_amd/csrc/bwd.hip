@@ -25,7 +25,7 @@ size_t row_scalar_bytes(const flexattn_dims* d) { return (size_t)2 * d->B * d->H
 // Room, behind what a workspace must hold, for the sums of divided groups: as many parts as columns that all rows list would be given.
 size_t kv_part_bytes(const flexattn_dims* d) {
     if (d->Hkv <= 0 || d->kv_len <= 0 || d->Hq % d->Hkv || (d->D != 64 && d->D != 128)) return 0;
-    const size_t parts = (size_t)kv_head_parts((int64_t)d->B * d->Hkv, d->Hq / d->Hkv, d->kv_len, d->D, d->q_len);
+    const size_t parts = (size_t)kv_head_parts((int64_t)d->B * d->Hkv, d->Hq / d->Hkv, d->kv_len, d->D, d->q_len, [](int) { return true; });
     return parts < 2 ? 0 : parts * 2 * d->B * d->Hkv * d->kv_len * d->D * sizeof(float);
 }
 }  // namespace

@@ -721,6 +721,24 @@ int64_t longest_column(const BwdArgs& a) {
     const int64_t rows = PartialMask<MASK>::kCanvas ? cols.sure : cols.longest;
     return rows < a.q_len ? rows : a.q_len;
 }
+// What speaks against parts beside the steps they spare (kv_head_parts).  Whole groups that are split among the waves of their workgroups
+// use the chip already: two parts that would be split among fewer, parts of a single head that would not be split, and small groups of more workgroups than two to a CU lose (us, dK/dV, whole / two / four,
+// S x query / KV heads: D = 64, no mask, 4000 x 4 / 2 45 / 64, 1500 x 20 / 5 37 / 51 / 41, 1000 x 64 / 8 49 / 66, causal, 4000 x 8 / 4 48 / 54, 4000 x 12 / 3 75 / 75 / 82; a window of 200 or a prefix of 64, 4000 x 12 / 6
+// 45 / 60).
+template <uint32_t MASK>
+bool parts_pay(const BwdArgs& a, int D, int parts) {
+    const int64_t groups = a.B * a.Hkv * ((a.kv_len + 63) / 64) * (int64_t)parts;
+    auto waves = [&](int p) {
+        BwdArgs of = a;
+        of.head_parts = p;
+        return dkdv_split_waves<MASK>(of, D);
+    };
+    if (const int whole = waves(1)) {
+        const int then = waves(parts);
+        if ((parts == 2 && then < whole) || (a.G < 4 && groups > 512) || (D == 64 && !then && a.G < 2 * parts)) return false;
+    }
+    return true;
+}
 // dV (blockIdx.y = 0) and dK from what the parts of every group left: eight dims a thread, in the order of the parts.
 static __global__ __launch_bounds__(256) void kv_parts_sum_kernel(const BwdArgs a, int D, float kscale) {
     const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x, rows = (int64_t)a.B * a.Hkv * a.kv_len;
@@ -745,7 +763,7 @@ template <uint32_t MASK, uint32_t SCORE>
 int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t st) {
     BwdArgs a = args;
     const int units = a.B * a.Hkv;
-    a.head_parts = a.kv_part ? kv_head_parts(units, a.G, a.kv_len, D, longest_column<MASK>(a)) : 1;
+    a.head_parts = a.kv_part ? kv_head_parts(units, a.G, a.kv_len, D, longest_column<MASK>(a), [&](int p) { return parts_pay<MASK>(a, D, p); }) : 1;
     if (a.head_parts == 1) a.kv_part = nullptr;
     const bool uneven = line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven;
     auto rows_by = [&](int rows) { return units_abreast(units, a.G * rows, bwd_waves_per_simd_of(D), rows_abreast<MASK>(uneven, D)); };

@@ -126,3 +126,34 @@ def test_stages_with_workspaces_of_different_sizes():
             hp.check_grad(name, g, r)
         first = dQ if first is None else first
         assert torch.equal(dQ, first)
+
+
+# B, Hq, Hkv, S, D, mask: groups that stay whole, though they have heads and steps enough
+WHOLE = [
+    (1, 6, 2, 4000, 64, "none"),            # unlike parts
+    (4, 9, 3, 1000, 128, "causal"),
+    (1, 4, 2, 4000, 64, "none"),            # split among the waves, which two parts would not be
+    (1, 64, 8, 1000, 64, "none"),
+    (1, 12, 3, 1500, 64, "causal"),         # one head each
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,mask", WHOLE)
+def test_groups_that_stay_whole(B, Hq, Hkv, S, D, mask):
+    import paper_2412_05496_amd as fa
+    print("[case]", B, Hq, Hkv, S, D, mask, flush=True)
+    q, k, v, do = (torch.randn(B, h, S, D, device=DEV).to(torch.bfloat16) for h in (Hq, Hkv, Hkv, Hq))
+    params, mask_id, _ = mods(fa, mask, S, B)
+    bm = fa.alloc_blockmask(1, 1, S, S, 128, 64, device=DEV)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    O, LSE = torch.empty_like(q), torch.empty(B, Hq, S, device=DEV)
+    head = (fa.SCORE_IDENTITY, mask_id, params, bm, D ** -0.5)
+    fa.flexattn_forward(q, k, v, *head, O, LSE)
+    scalars, got = 2 * B * Hq * S * 4, []
+    for room in (fa.flexattn_backward_workspace_bytes(q, k), scalars):
+        ws = torch.full((room,), 0xFF, dtype=torch.uint8, device=DEV)
+        dQ, dK, dV = (torch.full_like(t, float("nan")) for t in (q, k, k))
+        fa.flexattn_backward(q, k, v, O, do, LSE, *head, dQ, dK, dV, ws)
+        assert bool((ws[scalars:] == 0xFF).all())
+        got.append((dK, dV))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
