@@ -47,7 +47,8 @@ struct BwdArgs {
     int NR, NC, Bq, Bk;
     int bm_Bm, bm_Hm;
     UnitSets abreast;      // of the launch (unit_of_workgroup)
-    int head_parts;        // dK/dV: workgroups among which the query heads of a group are divided (kv_head_parts)
+    int head_parts;        // dK/dV: workgroups among which the query heads of a group are divided (kv_head_parts),
+    int least_steps;       //        kPartsIfLong: if the longest column has as many steps
     int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
     const int32_t* kv_num;
     const int32_t* kv_idx;
@@ -100,24 +101,39 @@ int kv_head_parts(int64_t units, int G, int kv_len, int D, int64_t longest_colum
 // to write the sums spill up to 6 registers in those that take whole groups, whose launches of one round last up to 4 % longer (one kernel for both -> two, us: D = 64,
 // window of 300 and soft-cap, S = 1000, 32 heads 17.6 -> 17.2, documents with ALiBi, S = 800, 24 heads 18.0 -> 17.6; D = 128, causal, S = 1000, 4 heads 18.5 -> 17.7, no mask,
 // S = 500, 8 heads 13.5 -> 13.0).
-template <bool DIVIDED>
+enum class Groups { kWhole, kParts, kPartsIfLong };
+template <Groups GROUPS>
 struct KvHeads {
     int part, first, end;
-    // unit: (b, hkv, part) -> (b, hkv)
-    __device__ __forceinline__ KvHeads(const BwdArgs& a, int& unit) : part(0), first(0), end(a.G) {
-        if (DIVIDED && a.head_parts > 1) {      // (it always is, but unless that is asked the parts' addresses are made ahead of the walk and spill 50 scalar
-                                                // registers: relative bias, window of 200 or prefix of 64, S = 8192, 16 / 2 heads, D = 128, 389 -> 405 us, D = 64 159 -> 169)
-            part = unit % a.head_parts;
-            unit /= a.head_parts;
-            first = part * a.G / a.head_parts;
-            end = (part + 1) * a.G / a.head_parts;
+    bool apart;         // the sums are those of a part
+    // unit: (b, hkv, part) -> (b, hkv).  (`parts` is asked here and `apart` at the sums even where they are known: else the parts' addresses are made ahead of the walk and
+    // spill 50 scalar registers: relative bias, window of 200 or prefix of 64, S = 8192, 16 / 2 heads, D = 128, 389 -> 405 us, D = 64 159 -> 169)
+    __device__ __forceinline__ KvHeads(const BwdArgs& a, int parts, int& unit) : part(0), first(0), end(a.G), apart(false) {
+        if (GROUPS != Groups::kWhole && parts > 1) {
+            part = unit % parts;
+            unit /= parts;
+            first = part * a.G / parts;
+            end = (part + 1) * a.G / parts;
+            apart = true;
         }
     }
-    __host__ __device__ __forceinline__ static int units(const BwdArgs& a) { return a.B * a.Hkv * (DIVIDED ? a.head_parts : 1); }
     __device__ __forceinline__ float* sums(const BwdArgs& a, int unit, int is_k, int D) const {
         return a.kv_part + (((int64_t)(2 * part + is_k) * a.B * a.Hkv + unit) * a.kv_len) * D;
     }
 };
+// kPartsIfLong: among how many workgroups the heads are divided in the end, by the steps of a head in the longest column of blocks (the first in work order) of the first plane.
+__device__ __forceinline__ int parts_if_long(const BwdArgs& a) {
+    const int col = min(max(ldc(a.q_order), 0), a.NC - 1);
+    return (ldc(a.full_q_num + col) + ldc(a.q_num + col)) * (a.Bq / 64) < a.least_steps ? 1 : a.head_parts;
+}
+// Workgroup -> (b, hkv, part) and its piece of a column's, of a launch for a.head_parts; parts: of how many.  False: nothing to do.
+template <Groups GROUPS>
+__device__ __forceinline__ bool kv_unit_of_workgroup(const BwdArgs& a, int per_unit, UnitSets abreast, int& parts, int& unit, int& rank) {
+    parts = GROUPS == Groups::kWhole ? 1 : GROUPS == Groups::kParts ? a.head_parts : parts_if_long(a);
+    const int units = a.B * a.Hkv * parts;
+    if (GROUPS == Groups::kPartsIfLong && blockIdx.x >= unit_grid(units, per_unit)) return false;
+    return unit_of_workgroup(units, per_unit, abreast, unit, rank);
+}
 
 constexpr uint32_t kBwdStageCaptured = 8u;   // internal: the captured-tensor sums instead of dQ
 
@@ -263,7 +279,8 @@ constexpr bool dkdv_can_leave() {
 // M0 RULE: this kernel fills LDS through the LDS-DMA helpers of lds_tiles.h, which write M0 behind the
 // compiler's back.  Keep every register array in it indexed by compile-time constants (no movrel /
 // s_set_gpr_idx code, which would also use M0) and add no other LDS-DMA or M0-based construct.
-template <int D, uint32_t MASK, uint32_t SCORE, bool OWN = dkdv_own_rows<D, MASK, SCORE>(), bool CUT = PartialMask<MASK>::kCanvas, bool DIVIDED = false, bool LEAVE = false>
+template <int D, uint32_t MASK, uint32_t SCORE, bool OWN = dkdv_own_rows<D, MASK, SCORE>(), bool CUT = PartialMask<MASK>::kCanvas, Groups GROUPS = Groups::kWhole,
+          bool LEAVE = false>
 __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(const BwdArgs a) {
     constexpr int TQ = 64;                         // query rows per step
     constexpr int TILE = TQ * D;                   // elements per LDS tile
@@ -289,10 +306,10 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     // head where the mask has a plane per head), the 64-key tiles of a column side by side.
     const int sub_k = a.Bk / 64;                   // tiles per column of blocks
     int unit, slot;                                // NC * sub_k slots >= tiles: the last column may be cut short
-    using Heads = KvHeads<DIVIDED>;
-    if (!unit_of_workgroup(Heads::units(a), a.NC * sub_k, a.abreast, unit, slot)) return;
-    if (a.ds_store) unit = last_unit_first(unit, Heads::units(a));
-    const Heads heads(a, unit);
+    int parts;
+    if (!kv_unit_of_workgroup<GROUPS>(a, a.NC * sub_k, a.abreast, parts, unit, slot)) return;
+    if (a.ds_store) unit = last_unit_first(unit, a.B * a.Hkv * parts);
+    const KvHeads<GROUPS> heads(a, parts, unit);
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
     int col = slot / sub_k;
     if (a.q_order) {
@@ -776,7 +793,7 @@ __global__ __launch_bounds__(256, bwd_waves_per_simd<D>()) void bwd_dkdv_kernel(
     }
     // ---- dV (x = 0) or dK (x = 1, with the scale and the score_mod's gradient factor), bf16
     {
-        if (DIVIDED && a.kv_part) {     // (always, see KvHeads; kv_parts_sum_kernel scales)
+        if (GROUPS != Groups::kWhole && heads.apart) {      // (kv_parts_sum_kernel scales)
             if (kv_lane >= a.kv_len) return;
             float* out = heads.sums(a, unit, x, D) + (int64_t)kv_lane * D;
 #pragma unroll

@@ -265,7 +265,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dq_split_kernel(
 // dK, dV.  Q and dO of 32 rows in two slots a wave, one unit ahead; K and V of the 32 keys in registers, dV^T and dK^T of the
 // wave's rows as well.  With dS kept in memory (ds_store) a unit writes its part of a step: that of wave (kb, x) in
 // bwd_dkdv_kernel; hidden units of index masks write zeros, those of a canvas are not read back.
-template <int D, int NW, uint32_t MASK, uint32_t SCORE, bool DIVIDED>
+template <int D, int NW, uint32_t MASK, uint32_t SCORE, Groups GROUPS>
 __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kernel(const BwdArgs a) {
     constexpr uint32_t UT = 32 * D * 2;
     constexpr int NKS = D / 16, NDB = D / 32;
@@ -277,18 +277,17 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[NW][2][Mask::kTags ? 64 : 4];
 
-    const int parts = a.Bk / 32;
-    int unit, slot_rank;
-    using Heads = KvHeads<DIVIDED>;
-    if (!unit_of_workgroup(Heads::units(a), a.NC * parts, one_by_one(Heads::units(a)), unit, slot_rank)) return;
-    const Heads heads(a, unit);
+    const int slices = a.Bk / 32;
+    int unit, slot_rank, parts;
+    if (!kv_unit_of_workgroup<GROUPS>(a, a.NC * slices, UnitSets{}, parts, unit, slot_rank)) return;
+    const KvHeads<GROUPS> heads(a, parts, unit);
     const int b = unit / a.Hkv, hkv = unit % a.Hkv;
-    int col = slot_rank / parts;
+    int col = slot_rank / slices;
     if (a.q_order) {
         const int64_t plane0 = (int64_t)(a.bm_Bm > 1 ? b : 0) * a.bm_Hm + (a.bm_Hm > 1 ? hkv * a.G : 0);
         col = min(max(ldc(a.q_order + plane0 * a.NC + col), 0), a.NC - 1);
     }
-    const int part = slot_rank & (parts - 1), kv0 = col * a.Bk + part * 32;
+    const int part = slot_rank & (slices - 1), kv0 = col * a.Bk + part * 32;
     // (the dQ kernel reads dS in tiles of 64 keys whose first key exists)
     if ((a.ds_store ? kv0 & ~63 : kv0) >= a.kv_len) return;
 
@@ -519,7 +518,7 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 2 : 1) void bwd_dkdv_split_kerne
     const float kscale = a.scale * Score::grad_scale();
     add_quads<NW, D / 4>((f32x4*)smem, w, lane, quads, [&](int q, const f32x4& o) __attribute__((always_inline)) {
         const bool is_k = q >= D / 8;
-        if (DIVIDED && a.kv_part) {     // (always, see KvHeads)
+        if (GROUPS != Groups::kWhole && heads.apart) {
             if (kv_lane < a.kv_len) *(f32x4*)(heads.sums(a, unit, is_k, D) + (int64_t)kv_lane * D + 8 * (q % (D / 8)) + 4 * half) = o;
             return;
         }
@@ -660,57 +659,30 @@ bool leaving_out_pays(const BwdArgs& a, int D, unsigned grid) {
     if ((SCORE & FLEXATTN_SCORE_REL_BIAS) && a.Bk == 64 && (a.q_len - 1) % 128 >= 64) return false;
     return a.Bq + a.Bk > 128 && grid > 256u * (unsigned)bwd_waves_per_simd_of(D);
 }
-template <uint32_t MASK, uint32_t SCORE, bool DIVIDED>
+template <uint32_t MASK, uint32_t SCORE, Groups GROUPS>
 void launch_dkdv64(const BwdArgs& a, unsigned grid, bool leave_out, hipStream_t st) {
     constexpr bool own = dkdv_own_rows<64, MASK, SCORE>(), canvas = PartialMask<MASK>::kCanvas;
     constexpr bool even = mask_uses(MASK, FLEXATTN_M_DOCUMENT) ||
                           (mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) && !mask_uses(MASK, FLEXATTN_M_PREFIX));
     if constexpr (own && !even && !(SCORE & FLEXATTN_SCORE_SOFTCAP)) {
         if (!own_rows_pay<MASK>(a, grid)) {
-            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false, canvas, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
+            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false, canvas, GROUPS>), dim3(grid), dim3(256), 0, st, a);
             return;
         }
     }
     if constexpr (canvas) {
         if (!canvas_cut_pays(a.p)) {
-            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false, false, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
+            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, false, false, GROUPS>), dim3(grid), dim3(256), 0, st, a);
             return;
         }
     }
-    if constexpr (dkdv_can_leave<64, MASK, SCORE>() && !DIVIDED) {          // (divided launches are no larger than a round)
+    if constexpr (dkdv_can_leave<64, MASK, SCORE>() && GROUPS == Groups::kWhole) {          // (launches for parts are no larger than a round)
         if (leave_out) {
-            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, own, canvas, false, true>), dim3(grid), dim3(256), 0, st, a);
+            hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, own, canvas, GROUPS, true>), dim3(grid), dim3(256), 0, st, a);
             return;
         }
     }
-    hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, own, canvas, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
-}
-
-// dK/dV (DIVIDED: or the sums of the parts of a group)
-template <uint32_t MASK, uint32_t SCORE, bool DIVIDED>
-void launch_dkdv(const BwdArgs& args, int D, bool uneven, hipStream_t st) {
-    BwdArgs a = args;
-    const int units = KvHeads<DIVIDED>::units(a);
-    const int waves = dkdv_split_waves<MASK>(a, D);
-    if (waves) {
-        const dim3 slices(unit_grid(units, a.NC * (a.Bk / 32)));
-        if (D == 128) hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 4, MASK, SCORE, DIVIDED>), slices, dim3(256), 0, st, a);
-        else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 8, MASK, SCORE, DIVIDED>), slices, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 4, MASK, SCORE, DIVIDED>), slices, dim3(256), 0, st, a);
-        return;
-    }
-    const unsigned grid = unit_grid(units, a.NC * (a.Bk / 64));
-    a.abreast = units_abreast(units, a.NC * (a.Bk / 64), bwd_waves_per_simd_of(D), uneven && !mask_uses(MASK, FLEXATTN_M_DOCUMENT) ? kColumnsAbreast : 1);
-    const bool leave_out = leaving_out_pays<MASK, SCORE>(a, D, grid);
-    if (D == 64) return launch_dkdv64<MASK, SCORE, DIVIDED>(a, grid, leave_out, st);
-    constexpr bool canvas = PartialMask<MASK>::kCanvas;
-    if constexpr (dkdv_can_leave<128, MASK, SCORE>()) {
-        if (leave_out) {
-            hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE, false, canvas, DIVIDED, true>), dim3(grid), dim3(256), 0, st, a);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE, false, canvas, DIVIDED>), dim3(grid), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((bwd_dkdv_kernel<64, MASK, SCORE, own, canvas, GROUPS>), dim3(grid), dim3(256), 0, st, a);
 }
 
 // Rows that the longest column of blocks sees (of a canvas: those around its pixels).
@@ -723,28 +695,34 @@ int64_t longest_column(const BwdArgs& a) {
 }
 // What speaks against parts beside the steps they spare (kv_head_parts).  Whole groups that are split among the waves of their workgroups
 // use the chip already: two parts that would be split among fewer, parts of a single head that would not be split, and small groups of more workgroups than two to a CU lose (us, dK/dV, whole / two / four,
-// S x query / KV heads: D = 64, no mask, 4000 x 4 / 2 45 / 64, 1500 x 20 / 5 37 / 51 / 41, 1000 x 64 / 8 49 / 66, causal, 4000 x 8 / 4 48 / 54, 4000 x 12 / 3 75 / 75 / 82; a window of 200 or a prefix of 64, 4000 x 12 / 6
+// S x query / KV heads: D = 64, no mask, 4000 x 4 / 2 45 / 64, 1500 x 20 / 5 37 / 51 / 41, 1000 x 56 / 8 45 / 65 / 49, causal, 4000 x 8 / 4 48 / 54, 4000 x 12 / 3 75 / 75 / 82; a window of 200 or a prefix of 64, 4000 x 12 / 6
 // 45 / 60).
+// Documents, many of which the host cannot tell to be short, spare a workgroup little and pay the sums of all keys.  So few sums for each head that is spared that documents of 16 to 200 tokens do not lose by
+// more than 3 % (D = 128, 1500 x 4 / 2, of 16 to 100, 8 %: 14.7 / 15.7, of 256 to 4096 40 / 28), or else they ask (kPartsIfLong).  Whole groups that are split do not ask, bwd_dkdv_kernel is no match for them: 3000 x 2 x 8 / 2,
+// D = 64, documents of 16 to 100, split 17, in two 23, whole after the question 27, of 256 to 4096 97 / 86; 9000 x 4 / 1 18 / - / 21 and 122 / - / 63.
+inline bool short_documents_pay(const BwdArgs& a, int D, int parts) {
+    const int64_t sums = a.B * a.Hkv * ((a.kv_len + 63) / 64) * (int64_t)parts * 64 * D, spared = a.G - (a.G + parts - 1) / parts;      // of dK; heads
+    return sums <= (a.G >= 4 ? 1200000 : D == 128 ? 800000 : 0) * spared;
+}
 template <uint32_t MASK>
 bool parts_pay(const BwdArgs& a, int D, int parts) {
-    const int64_t groups = a.B * a.Hkv * ((a.kv_len + 63) / 64) * (int64_t)parts;
     auto waves = [&](int p) {
         BwdArgs of = a;
         of.head_parts = p;
         return dkdv_split_waves<MASK>(of, D);
     };
-    if (const int whole = waves(1)) {
-        const int then = waves(parts);
-        if ((parts == 2 && then < whole) || (a.G < 4 && groups > 512) || (D == 64 && !then && a.G < 2 * parts)) return false;
-    }
-    return true;
+    const int whole = waves(1), then = waves(parts);
+    if (whole && ((parts == 2 && then < whole) || (a.G < 4 && a.B * a.Hkv * ((a.kv_len + 63) / 64) * parts > 512) || (D == 64 && !then && a.G < 2 * parts))) return false;
+    return !PartialMask<MASK>::kDoc || short_documents_pay(a, D, parts) || (!whole && a.q_order);
 }
 // dV (blockIdx.y = 0) and dK from what the parts of every group left: eight dims a thread, in the order of the parts.
-static __global__ __launch_bounds__(256) void kv_parts_sum_kernel(const BwdArgs a, int D, float kscale) {
+template <bool IF_LONG>
+__global__ __launch_bounds__(256) void kv_parts_sum_kernel(const BwdArgs a, int D, float kscale) {
     const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x, rows = (int64_t)a.B * a.Hkv * a.kv_len;
     const int shift = D == 128 ? 4 : 3, d = ((int)at & ((1 << shift) - 1)) * 8;
     const int64_t row = at >> shift;
     if (row >= rows) return;
+    if (IF_LONG && parts_if_long(a) == 1) return;       // (the columns' workgroups have written)
     const bool is_k = blockIdx.y != 0;
     const float* src = a.kv_part + ((int64_t)is_k * rows + row) * D + d;
     f32x4 lo = *(const f32x4*)src, hi = *(const f32x4*)(src + 4);
@@ -757,6 +735,41 @@ static __global__ __launch_bounds__(256) void kv_parts_sum_kernel(const BwdArgs 
     const int kv = (int)(row % a.kv_len), unit = (int)(row / a.kv_len), b = unit / a.Hkv, hkv = unit - b * a.Hkv;
     bf16* out = is_k ? a.dK + b * a.dk_sb + hkv * a.dk_sh + (int64_t)kv * a.dk_ss : a.dV + b * a.dv_sb + hkv * a.dv_sh + (int64_t)kv * a.dv_ss;
     *(u32x4*)(out + d) = u32x4{pack_bf16(lo[0] * s, lo[1] * s), pack_bf16(lo[2] * s, lo[3] * s), pack_bf16(hi[0] * s, hi[1] * s), pack_bf16(hi[2] * s, hi[3] * s)};
+}
+
+// dK/dV, and what adds the parts of groups up.  kPartsIfLong, whose launch has workgroups enough for whole groups as well: us, whole / in parts / this, S x query / KV heads, documents of 16 to 100, 30 to 300
+// and 256 to 4096: D = 64, 6000 x 8 / 4 15.3 / 23.5 / 18.2, 18.9 / 24.9 / 21.7, 75 / 55 / 56, 8000 x 6 / 3 15.8 / 23.9 / 18.5, 19.3 / 25.2 / 21.9, 101 / 69 / 70; D = 128, 6000 x 8 / 4 23.6 / 39.4 / 25.9,
+// 28.7 / 41.7 / 30.3, 108 / 81 / 81, 6000 x 32 / 4 64 / 73 / 67, 83 / 80 / 81, 408 / 267 / 267, 3000 x 2 x 8 / 2 31.7 / 38.2 / 34.0, 40.3 / 40.6 / 41.4, 212 / 97 / 97.  (What is left of short ones' loss is
+// the launch that adds nothing up, and the question, 1 us.)
+template <uint32_t MASK, uint32_t SCORE, Groups GROUPS>
+void launch_dkdv(const BwdArgs& args, int D, bool uneven, hipStream_t st) {
+    BwdArgs a = args;
+    const int units = a.B * a.Hkv * a.head_parts;
+    const int waves = GROUPS == Groups::kPartsIfLong ? 0 : dkdv_split_waves<MASK>(a, D), per_unit = a.NC * (a.Bk / (waves ? 32 : 64));
+    const unsigned grid = std::max(unit_grid(units, per_unit), GROUPS == Groups::kPartsIfLong ? unit_grid(a.B * a.Hkv, per_unit) : 0u);
+    constexpr bool canvas = PartialMask<MASK>::kCanvas;
+    a.least_steps = a.G < 4 ? 12 : 5;
+    if constexpr (GROUPS != Groups::kPartsIfLong) {
+        if (D == 128 && waves) hipLaunchKernelGGL((bwd_dkdv_split_kernel<128, 4, MASK, SCORE, GROUPS>), dim3(grid), dim3(256), 0, st, a);
+        else if (waves == 8) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 8, MASK, SCORE, GROUPS>), dim3(grid), dim3(512), 0, st, a);
+        else if (waves) hipLaunchKernelGGL((bwd_dkdv_split_kernel<64, 4, MASK, SCORE, GROUPS>), dim3(grid), dim3(256), 0, st, a);
+    }
+    if (!waves) {
+        a.abreast = units_abreast(units, per_unit, bwd_waves_per_simd_of(D), uneven && !mask_uses(MASK, FLEXATTN_M_DOCUMENT) ? kColumnsAbreast : 1);
+        const bool leave_out = leaving_out_pays<MASK, SCORE>(a, D, grid);
+        if (D == 64) launch_dkdv64<MASK, SCORE, GROUPS>(a, grid, leave_out, st);
+        else if constexpr (dkdv_can_leave<128, MASK, SCORE>()) {
+            if (leave_out) hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE, false, canvas, GROUPS, true>), dim3(grid), dim3(256), 0, st, a);
+            else hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE, false, canvas, GROUPS>), dim3(grid), dim3(256), 0, st, a);
+        } else {
+            hipLaunchKernelGGL((bwd_dkdv_kernel<128, MASK, SCORE, false, canvas, GROUPS>), dim3(grid), dim3(256), 0, st, a);
+        }
+    }
+    if constexpr (GROUPS != Groups::kWhole) {
+        const float kscale = a.scale * ScoreMod<SCORE>::grad_scale();
+        const int64_t eights = (int64_t)a.B * a.Hkv * a.kv_len * (D / 8);
+        hipLaunchKernelGGL(kv_parts_sum_kernel<GROUPS == Groups::kPartsIfLong>, dim3((unsigned)((eights + 255) / 256), 2), dim3(256), 0, st, a, D, kscale);
+    }
 }
 
 template <uint32_t MASK, uint32_t SCORE>
@@ -806,13 +819,9 @@ int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t 
     };
     if (q && !a.dq_last) run_dq();
     if (kv) {
-        if (a.kv_part) launch_dkdv<MASK, SCORE, true>(a, D, uneven, st);
-        else launch_dkdv<MASK, SCORE, false>(a, D, uneven, st);
-        if (a.kv_part) {
-            const float kscale = a.scale * ScoreMod<SCORE>::grad_scale();
-            const int64_t eights = (int64_t)units * a.kv_len * (D / 8);
-            hipLaunchKernelGGL(kv_parts_sum_kernel, dim3((unsigned)((eights + 255) / 256), 2), dim3(256), 0, st, a, D, kscale);
-        }
+        if (!a.kv_part) launch_dkdv<MASK, SCORE, Groups::kWhole>(a, D, uneven, st);
+        else if (!PartialMask<MASK>::kDoc || short_documents_pay(a, D, a.head_parts)) launch_dkdv<MASK, SCORE, Groups::kParts>(a, D, uneven, st);
+        else if constexpr (PartialMask<MASK>::kDoc) launch_dkdv<MASK, SCORE, Groups::kPartsIfLong>(a, D, uneven, st);
     }
     if (q && a.dq_last) run_dq();
     if (stages & kBwdStageCaptured) {

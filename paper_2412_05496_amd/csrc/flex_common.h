@@ -306,7 +306,7 @@ inline UnitSets units_abreast(int units, int per_unit, int per_cu, int most) {
     while (2 << side <= limit && 2 << side <= mine && (int64_t)per_unit << side < 2 * round) ++side;
     return {side, mine > 0 ? mine >> side : 1};
 }
-inline unsigned unit_grid(int units, int per_unit) {
+__host__ __device__ inline unsigned unit_grid(int units, int per_unit) {
     return 8u * ((unsigned)(units >> 3) * (unsigned)per_unit + (unsigned)(units & 7) * (unsigned)((per_unit + 7) / 8));
 }
 // A launch counts its work items in 32 bits: 2^24 workgroups of 256 are too many (some are then left out, without an error).

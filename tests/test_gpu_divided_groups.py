@@ -128,6 +128,71 @@ def test_stages_with_workspaces_of_different_sizes():
         assert torch.equal(dQ, first)
 
 
+# B, Hq, Hkv, S, D, length of the documents of plane 0 and of the others, the orders of the BlockMask are there, parts of the sums
+DOCUMENTS = [
+    (8, 2, 1, 2048, 128, 40, 40, True, 0),          # asked: the longest column is short, whole groups
+    (8, 2, 1, 2048, 128, 2048, 40, True, 2),        # asked: long
+    (8, 2, 1, 2048, 128, 40, 2048, True, 0),        # (the first plane's columns are asked for all)
+    (8, 2, 1, 2048, 128, 2048, 2048, False, 0),     # nothing says which column is the longest: whole
+    (2, 12, 3, 4000, 128, 30, 60, True, 0),         # asked, of four heads
+    (2, 12, 3, 4000, 128, 700, 300, True, 2),
+    (3, 4, 2, 4096, 64, 90, 90, True, 0),           # asked, 768 workgroups
+    (3, 4, 2, 4096, 64, 900, 90, True, 2),
+    (1, 8, 1, 900, 64, 50, 50, True, 8),            # so few keys that short ones do not lose
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D,first,others,orders,parts", DOCUMENTS)
+def test_documents(B, Hq, Hkv, S, D, first, others, orders, parts):
+    """Launches that divide the groups of long documents and leave those of short ones whole."""
+    import paper_2412_05496_amd as fa
+    print("[case]", B, Hq, Hkv, S, D, first, others, orders, flush=True)
+    gen = torch.Generator().manual_seed(S + Hq)
+    Q, dO = (torch.randn(B, Hq, S, D, generator=gen).to(torch.bfloat16) for _ in range(2))
+    K, V = (torch.randn(B, Hkv, S, D, generator=gen).to(torch.bfloat16) for _ in range(2))
+    ids = torch.stack([torch.arange(S, dtype=torch.int32) // (others if b else first) for b in range(B)])
+    params = fa.ModParams()
+    params.doc_ids = ids.to(DEV)
+    bm = fa.alloc_blockmask(B, 1, S, S, 128, 64, device=DEV)
+    fa.flexattn_blockmask_build(fa.MASK_DOCUMENT_CAUSAL, params, bm)
+    if not orders:
+        bm.kv_order = bm.q_order = None
+    q, k, v, do = (t.to(DEV) for t in (Q, K, V, dO))
+    O, LSE = torch.empty_like(q), torch.empty(B, Hq, S, device=DEV)
+    head = (fa.SCORE_IDENTITY, fa.MASK_DOCUMENT_CAUSAL, params, bm, D ** -0.5)
+    fa.flexattn_forward(q, k, v, *head, O, LSE)
+    room, scalars = fa.flexattn_backward_workspace_bytes(q, k), 2 * B * Hq * S * 4
+    one = 2 * B * Hkv * S * D * 4
+    assert room - scalars >= max(parts, 2) * one
+    n, got = hp.nonempty_blocks(bm), []
+    for stored in (False, True):
+        ws = hp.dirty_stored_workspace(q, k, bm, n) if stored else torch.full((room,), 0xFF, dtype=torch.uint8, device=DEV)
+        dQ, dK, dV = (torch.full_like(t, float("nan")) for t in (q, k, k))
+        for stage in (1, 2, 4):
+            if stored:
+                fa.flexattn_backward_stored(q, k, v, O, do, LSE, *head, dQ, dK, dV, n, ws, stage)
+            else:
+                fa.flexattn_backward_stages(q, k, v, O, do, LSE, *head, dQ, dK, dV, ws, stage)
+        torch.cuda.synchronize()
+        sums = ws[ws.numel() - hp.room_for_parts(q, k):]
+        written = int((sums.view(torch.int32) != -1).sum()) * 4 / one
+        assert abs(written - parts) < 0.01, written
+        got.append((dQ, dK, dV))
+    assert torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][2], got[1][2])
+    for b in sorted({0, B - 1}):            # (an entry at a time, document by document: the oracle's scores are S x S)
+        for lo in range(0, S, others if b else first):
+            hi = min(lo + (others if b else first), S)
+            if lo and hi < S and lo % 3:    # (a third of them, the first and the last)
+                continue
+            cut = [t[b:b + 1, :, lo:hi].float() for t in (Q, K, V, dO)]
+            ref = fo.flex_attention_backward(*cut, fo.Identity(), fo.causal_mask, D ** -0.5)
+            for grads in got:
+                for name, g, r in zip(("dQ", "dK", "dV"), grads, ref):
+                    hp.check_grad(name, g[b:b + 1, :, lo:hi], r)
+    for t in (x for grads in got for x in grads):
+        assert bool(torch.isfinite(t).all())
+
+
 # B, Hq, Hkv, S, D, mask: groups that stay whole, though they have heads and steps enough
 WHOLE = [
     (1, 6, 2, 4000, 64, "none"),            # unlike parts

@@ -49,7 +49,7 @@ def kernels(library):
 def test_the_others_pay_nothing_for_divided_groups_and_steps_left_out():
     seen, leaving = {}, {}
     for name, kernel in kernels(build.LIB).items():
-        m = re.match(r"_ZN8flexattn15bwd_dkdv_kernelILi(\d+)ELj(\d+)ELj(\d+)ELb([01])ELb([01])ELb0ELb([01])EEEv", name)
+        m = re.match(r"_ZN8flexattn15bwd_dkdv_kernelILi(\d+)ELj(\d+)ELj(\d+)ELb([01])ELb([01])ELNS_6GroupsE0ELb([01])EEEv", name)
         if m:
             (leaving if m.group(6) == "1" else seen)[tuple(int(g) for g in m.groups()[:5])] = kernel[".private_segment_fixed_size"]
     assert len(seen) > 30 and set(SCRATCH) <= set(seen)
