@@ -227,8 +227,9 @@ int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
         }
         if (stages & FLEXATTN_BWD_DQ) {
             const float qscale = scale * ((score_id & FLEXATTN_SCORE_SOFTCAP) ? 4.0f : 1.0f);   // ScoreMod::grad_scale()
-            if (mask_uses(mask_id, FLEXATTN_M_NEIGHBORHOOD)) launch_bwd_stored_dq<true>(a, dims->D, qscale, StoredShare::kNone, false, st);
-            else launch_bwd_stored_dq<false>(a, dims->D, qscale, stored_share(dims, bm, mask_id, a.p), line_shape(mask_id, a.p, dims->q_len, dims->kv_len).uneven, st);
+            if (mask_uses(mask_id, FLEXATTN_M_NEIGHBORHOOD)) launch_bwd_stored_dq<true>(a, dims->D, qscale, StoredShare::kNone, false, false, st);
+            else launch_bwd_stored_dq<false>(a, dims->D, qscale, stored_share(dims, bm, mask_id, a.p), line_shape(mask_id, a.p, dims->q_len, dims->kv_len).uneven,
+                                             mask_uses(mask_id, FLEXATTN_M_DOCUMENT), st);
         }
     } else {
         rc = kBwdLaunchers[vi](a, dims->D, stages, st);     // the delta pre-pass depends on the score_mod too

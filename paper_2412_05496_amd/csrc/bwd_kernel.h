@@ -50,6 +50,7 @@ struct BwdArgs {
     int head_parts;        // dK/dV: workgroups among which the query heads of a group are divided (kv_head_parts),
     int least_steps;       //        kPartsIfLong: if the longest column has as many steps
     int halved;            // MIXED: how many of the rows of blocks, in work order, are taken in halves
+    int turns_above;       // dS in memory: heads take turns where the longest row has more tiles (documents; 0: always)
     const int32_t* kv_num;
     const int32_t* kv_idx;
     const int32_t* full_kv_num;

@@ -121,7 +121,9 @@ __global__ __launch_bounds__(NW * 64 * HEADS * ROWS, 2) void bwd_dq_stored_kerne
     int unit, rem;
     const int groups = a.G / HEADS;
     const int row_sets = (a.NR + ROWS - 1) / ROWS;
-    if (!unit_of_workgroup(a.B * a.Hkv, groups * row_sets, a.abreast, unit, rem)) return;
+    UnitSets abreast = a.abreast;
+    if (a.turns_above && abreast.side && longest_row(a.kv_order, a.full_kv_num, a.kv_num, 0, a.NR, a.Bk / 64) <= a.turns_above) abreast = one_by_one(a.B * a.Hkv);
+    if (!unit_of_workgroup(a.B * a.Hkv, groups * row_sets, abreast, unit, rem)) return;
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), w = wave & (NW - 1);
     const int g = (rem % groups) * HEADS + (ROWS > 1 ? 0 : wave / NW);
@@ -340,10 +342,14 @@ __global__ __launch_bounds__(NW * 64 * HEADS * ROWS, 2) void bwd_dq_stored_kerne
 
 enum class StoredShare { kNone, kHeads, kRows };     // (stored_share; D = 128, Bq = 128)
 template <bool CANVAS>
-int launch_bwd_stored_dq(const BwdArgs& args, int D, float qscale, StoredShare share, bool uneven, hipStream_t st) {
+int launch_bwd_stored_dq(const BwdArgs& args, int D, float qscale, StoredShare share, bool uneven, bool documents, hipStream_t st) {
     BwdArgs a = args;
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     a.abreast = units_abreast(a.B * a.Hkv, share == StoredShare::kNone ? a.G * a.NR : a.G * ((a.NR + 1) / 2), share != StoredShare::kNone ? 1 : bwd_waves_per_simd_of(D), uneven ? kRowsAbreast : 1);
+    // Short documents one head after the other, as in abreast_if_long.  us of dQ, B x S x heads, one by one / in turns, documents of 16 to 100, 30 to 300, 100 to 1000 and 256 to 4096: D = 64,
+    // 8192 x 64 61 / 64, 68 / 71, 125 / 124, 329 / 285, 4 x 4096 x 16 35.7 / 37.0, 39.5 / 40.3, 68 / 60, 203 / 161; D = 128, 8 x 2048 x 64 189 / 206, 207 / 234, 314 / 328, 604 / 582, 4 x 4096 x 16 50 / 51,
+    // 53 / 58, 83 / 78, 228 / 198, 16 x 1024 x 32 91 / 94, 104 / 103, 154 / 138, 191 / 168.
+    if (documents) a.turns_above = 8;
     if constexpr (!CANVAS) {
         if (share == StoredShare::kHeads) {         // (an even number of heads to a group, one plane for all)
             hipLaunchKernelGGL((bwd_dq_stored_kernel<128, 4, false, 2>), dim3(unit_grid(a.B * a.Hkv, a.G / 2 * a.NR)), dim3(512), 0, st, a, qscale);

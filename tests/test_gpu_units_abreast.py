@@ -19,6 +19,7 @@ DEV = "cuda:0"
     (40, 1000, 64, 128, 700),       # documents whose longest row is long, in halves and whole rows
     (136, 500, 64, 128, 30),        # and short: head by head
     (67, 400, 128, 128, 350),
+    (44, 700, 128, 128, 60),        # short ones in rows of 128 queries, by heads that would take turns with dS in memory as well
 ])
 def test_every_head_is_the_first(heads, S, D, Bq, doc):
     import paper_2412_05496_amd as fa
