@@ -11,7 +11,7 @@ from paper_2412_05496_amd import build
 msgpack = pytest.importorskip("msgpack")
 # (D, mask_mod, score_mod, waves keep their own rows, canvas walk): bytes a lane; the others have none
 SCRATCH = {
-    (128, 5, 6, 0, 0): 36, (64, 1, 1, 1, 0): 12, (64, 5, 0, 1, 0): 12, (64, 5, 1, 1, 0): 16,
+    (128, 5, 6, 0, 0): 36, (64, 1, 1, 1, 0): 12, (64, 3, 4, 1, 0): 8, (64, 5, 0, 1, 0): 12, (64, 5, 1, 1, 0): 16,
     (64, 5, 6, 0, 0): 48, (64, 2051, 2, 1, 0): 28, (64, 2051, 2, 0, 0): 8,
     (64, 32, 0, 0, 1): 8, (64, 96, 0, 0, 1): 20, (64, 160, 0, 0, 1): 8, (64, 224, 0, 0, 1): 8,
 }
