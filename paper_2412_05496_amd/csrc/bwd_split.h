@@ -778,8 +778,9 @@ int launch_bwd_variant(const BwdArgs& args, int D, uint32_t stages, hipStream_t 
     const int units = a.B * a.Hkv;
     a.head_parts = a.kv_part ? kv_head_parts(units, a.G, a.kv_len, D, longest_column<MASK>(a), [&](int p) { return parts_pay<MASK>(a, D, p); }) : 1;
     if (a.head_parts == 1) a.kv_part = nullptr;
-    const bool uneven = line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven;
-    auto rows_by = [&](int rows) { return units_abreast(units, a.G * rows, bwd_waves_per_simd_of(D), rows_abreast<MASK>(uneven, D)); };
+    const LineShape rows_shape = line_shape<MASK>(a.p, a.q_len, a.kv_len);
+    const bool uneven = rows_shape.uneven;
+    auto rows_by = [&](int rows) { return units_abreast(units, a.G * rows, bwd_waves_per_simd_of(D), rows_abreast<MASK>(rows_shape, a.kv_len, D)); };
     const unsigned grid_q = unit_grid(a.B * a.Hkv, a.G * a.NR);
     const bool kv = stages & FLEXATTN_BWD_DKDV, q = stages & FLEXATTN_BWD_DQ;
     // dQ first, where it makes the row scalars that dK/dV reads; last, after a pass that makes them, where it is written over

@@ -982,11 +982,13 @@ template <uint32_t MASK>
 LineShape line_shape(const flexattn_mod_params& p, int q_len, int kv_len) {
     return line_shape(MASK, p, q_len, kv_len);
 }
-// units_abreast's limit for the rows of a mask: of uneven length, or, at D = 64, windows, whose first rows are shorter than the others (at D = 128
-// window of 512, 4096 x 64: dQ 141 -> 146)
+// units_abreast's limit for the rows of a mask: of uneven length, or, at D = 64, windows of an eighth of the keys or more, whose first rows are shorter than the others (us, forward / dQ, one by one -> in turns,
+// Bq = 128, 4 x 2048 x 16, window of 600 31 -> 29 / 48 -> 41, of 300 23.0 -> 23.1 / 37 -> 33, of 100 18.6 -> 19.0 / 27.2 -> 26.6, 8192 x 64, of 600 110 -> 111 / 162 -> 162, of 100 57 -> 59 / 94 -> 99, 2 x 3000 x 24, of 600
+// 39 -> 34 / 49 -> 46, of 300, 64 x 128 28 -> 30 / 41 -> 44; at D = 128 window of 512, 4096 x 64: dQ 141 -> 146).
 template <uint32_t MASK>
-int rows_abreast(bool uneven, int D) {
-    return uneven || (D == 64 && mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) && !mask_uses(MASK, FLEXATTN_M_PREFIX)) ? kRowsAbreast : 1;
+int rows_abreast(const LineShape& rows, int kv_len, int D) {
+    const bool window = mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW) && !mask_uses(MASK, FLEXATTN_M_PREFIX);
+    return rows.uneven || (D == 64 && window && 8 * rows.longest > kv_len) ? kRowsAbreast : 1;
 }
 inline bool score_id_valid(uint32_t s) { return (s & ~7u) == 0; }
 

@@ -992,8 +992,8 @@ template <uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED>
 int launch_fwd_shape(const FwdArgs& args, int D, int Bq, hipStream_t st) {
     FwdArgs a = args;
     const unsigned grid = unit_grid(a.B * a.Hkv, a.G * a.NR);
-    const bool uneven = line_shape<MASK>(a.p, a.q_len, a.kv_len).uneven;
-    auto order_units = [&](int rows, int per_cu) { a.abreast = units_abreast(a.B * a.Hkv, a.G * rows, per_cu, rows_abreast<MASK>(uneven, D)); };
+    const LineShape rows_shape = line_shape<MASK>(a.p, a.q_len, a.kv_len);
+    auto order_units = [&](int rows, int per_cu) { a.abreast = units_abreast(a.B * a.Hkv, a.G * rows, per_cu, rows_abreast<MASK>(rows_shape, a.kv_len, D)); };
     a.abreast = one_by_one(a.B * a.Hkv);
     if (const int waves = split_waves<MASK, SCORE>(a, D)) {
         const dim3 slices(unit_grid(a.B * a.Hkv, a.G * a.NR * (Bq / 32)));
@@ -1035,7 +1035,7 @@ int launch_fwd_shape(const FwdArgs& args, int D, int Bq, hipStream_t st) {
     if (D == 64 && Bq == 128) {
         constexpr bool dense = !mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
         if constexpr (fwd_plain<64, 4, BOUNDED>() && dense) {
-            if (!plain_pays<SCORE>(a.kv_len, grid, uneven)) {
+            if (!plain_pays<SCORE>(a.kv_len, grid, rows_shape.uneven)) {
                 order_units(a.NR, 3);
                 hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false>), dim3(grid), dim3(256), 0, st, a);
                 return FLEXATTN_OK;
