@@ -30,6 +30,9 @@ def mods(fa, mask, S, B):
         return params, fa.MASK_CAUSAL, fo.causal_mask
     if mask == "none":
         return params, fa.MASK_NONE, fo.no_mask
+    if mask == "window_or_prefix":
+        params.window, params.prefix_len = 300, 50
+        return params, fa.MASK_SWA_CAUSAL_OR_PREFIX, None
     if mask == "prefix":
         params.prefix_len = 70
         return params, fa.MASK_PREFIX_LM, fo.or_mask(fo.causal_mask, fo.prefix_mask(70))
@@ -200,6 +203,7 @@ WHOLE = [
     (1, 4, 2, 4000, 64, "none"),            # split among the waves, which two parts would not be
     (1, 64, 8, 1000, 64, "none"),
     (1, 12, 3, 1500, 64, "causal"),         # one head each
+    (1, 40, 8, 2048, 64, "window_or_prefix"),       # unlike parts, split in either case
 ]
 
 
@@ -212,7 +216,8 @@ def test_groups_that_stay_whole(B, Hq, Hkv, S, D, mask):
     bm = fa.alloc_blockmask(1, 1, S, S, 128, 64, device=DEV)
     fa.flexattn_blockmask_build(mask_id, params, bm)
     O, LSE = torch.empty_like(q), torch.empty(B, Hq, S, device=DEV)
-    head = (fa.SCORE_IDENTITY, mask_id, params, bm, D ** -0.5)
+    head = (fa.SCORE_REL_BIAS if mask == "window_or_prefix" else fa.SCORE_IDENTITY, mask_id, params, bm, D ** -0.5)
+    params.rel_bias = torch.zeros(Hq, 16, device=DEV)
     fa.flexattn_forward(q, k, v, *head, O, LSE)
     scalars, got = 2 * B * Hq * S * 4, []
     for room in (fa.flexattn_backward_workspace_bytes(q, k), scalars):
