@@ -150,7 +150,7 @@ int backward_impl(const flexattn_dims* dims, const flexattn_tensor* Q,
         return FLEXATTN_ERR_INVALID_ARG;
     if ((rc = check_mod_params(mask_id, score_id, params)) != FLEXATTN_OK) return rc;
     if ((rc = check_canvas(mask_id, params, dims->q_len, dims->kv_len)) != FLEXATTN_OK) return rc;
-    const int vi = variant_of(mask_id, score_id, params, true);
+    const int vi = variant_of(mask_id, score_id, params, true, dims->D);
     if (vi < 0) return FLEXATTN_ERR_UNSUPPORTED;
     bool stored = ds_blocks >= 0;
     StoredLayout lay = {};
@@ -343,7 +343,7 @@ extern "C" int flexattn_backward_captured(const flexattn_dims* dims, const flexa
     const bool alibi = score_id & FLEXATTN_SCORE_ALIBI, rel = score_id & FLEXATTN_SCORE_REL_BIAS;
     if (!alibi && !rel) return FLEXATTN_ERR_UNSUPPORTED;               // nothing is captured
     if ((alibi && !d_alibi_bias) || (rel && !d_rel_bias)) return FLEXATTN_ERR_INVALID_ARG;
-    const int vi = variant_of(mask_id, score_id, params, true);
+    const int vi = variant_of(mask_id, score_id, params, true, dims->D);
     if (vi < 0) return FLEXATTN_ERR_UNSUPPORTED;
     if (ws_bytes < flexattn_backward_captured_workspace_bytes(dims, bm, score_id, params)) return FLEXATTN_ERR_WORKSPACE;
 

@@ -80,7 +80,7 @@ extern "C" int flexattn_forward(const flexattn_dims* dims, const flexattn_tensor
     if (!LSE || !(scale > 0.0f)) return FLEXATTN_ERR_INVALID_ARG;
     if ((rc = check_mod_params(mask_id, score_id, params)) != FLEXATTN_OK) return rc;
     if ((rc = check_canvas(mask_id, params, dims->q_len, dims->kv_len)) != FLEXATTN_OK) return rc;
-    const int vi = variant_of(mask_id, score_id, params, false);
+    const int vi = variant_of(mask_id, score_id, params, false, dims->D);
     if (vi < 0) return FLEXATTN_ERR_UNSUPPORTED;
 
     FwdArgs a = {};
@@ -122,7 +122,7 @@ extern "C" int flexattn_paged_forward(const flexattn_dims* dims, const flexattn_
     if (bm->Bm != dims->B) return FLEXATTN_ERR_INVALID_ARG;        // every sequence has its own pages
     if ((rc = check_mod_params(mask_id, score_id, params)) != FLEXATTN_OK) return rc;
     if ((rc = check_canvas(mask_id, params, dims->q_len, dims->kv_len)) != FLEXATTN_OK) return rc;
-    const int vi = variant_of(mask_id, score_id, params, false);
+    const int vi = variant_of(mask_id, score_id, params, false, dims->D);
     if (vi < 0) return FLEXATTN_ERR_UNSUPPORTED;
 
     FwdArgs a = {};

@@ -240,7 +240,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     using Score = ScoreMod<SCORE, true>;
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];           // relative-bias row of the head
     using Mask = PartialMask<MASK>;
-    constexpr bool CELLS = Mask::kCells && D == 64;                   // (D = 128: six masks more spill 16 and 28 registers, 469 -> 682 us)
+    constexpr bool CELLS = Mask::kCells;
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[SPLIT ? NW : UNITS ? 3 : 2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys, per buffer (SPLIT: wave)
 
     constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || PLAIN || SPLIT || PAIRS);
@@ -988,40 +988,33 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     if (half == 0) *lse_ptr = l_tot > 0.0f ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
 }
 
-template <uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED>
-int launch_fwd_shape(const FwdArgs& args, int D, int Bq, hipStream_t st) {
+template <int D, uint32_t MASK, uint32_t SCORE, bool BOUNDED, bool PAGED>
+int launch_fwd_shape(const FwdArgs& args, int Bq, hipStream_t st) {
     FwdArgs a = args;
     const unsigned grid = unit_grid(a.B * a.Hkv, a.G * a.NR);
     const LineShape rows_shape = line_shape<MASK>(a.p, a.q_len, a.kv_len);
     auto order_units = [&](int rows, int per_cu) { a.abreast = units_abreast(a.B * a.Hkv, a.G * rows, per_cu, rows_abreast<MASK>(rows_shape, a.kv_len, D)); };
-    a.abreast = one_by_one(a.B * a.Hkv);
     if (const int waves = split_waves<MASK, SCORE>(a, D)) {
         const dim3 slices(unit_grid(a.B * a.Hkv, a.G * a.NR * (Bq / 32)));
-        if (D == 128 && waves == 8) hipLaunchKernelGGL((fwd_kernel<128, 8, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(512), 0, st, a);
-        else if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(256), 0, st, a);
-        else if (waves == 8) hipLaunchKernelGGL((fwd_kernel<64, 8, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(512), 0, st, a);
-        else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(256), 0, st, a);
+        if (waves == 8) hipLaunchKernelGGL((fwd_kernel<D, 8, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(512), 0, st, a);
+        else hipLaunchKernelGGL((fwd_kernel<D, 4, MASK, SCORE, BOUNDED, PAGED, false, false, true>), slices, dim3(256), 0, st, a);
         return FLEXATTN_OK;
     }
     if (pairs_pay<MASK, BOUNDED>(a, D, grid)) {
-        constexpr bool mixed64 = mixed_pays<64, MASK, SCORE, BOUNDED>(), mixed128 = mixed_pays<128, MASK, SCORE, BOUNDED>();
-        const bool mixed = Bq == 128 && (D == 64 ? mixed64 : mixed128);
+        constexpr bool can_mix = mixed_pays<D, MASK, SCORE, BOUNDED>();
+        const bool mixed = Bq == 128 && can_mix;
         a.halved = Bq == 64 ? 0 : mixed ? halved_rows(a.NR) : a.NR;
         order_units(a.NR + a.halved, D == 64 ? 4 : 2);
         const unsigned pieces = unit_grid(a.B * a.Hkv, a.G * (a.NR + a.halved));
         for (a.first_id = 0; a.first_id < pieces; a.first_id += kMaxLaunch) {
             const dim3 ids(min(pieces - a.first_id, kMaxLaunch));
-            if (D == 128 && mixed) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true, mixed128>), ids, dim3(256), 0, st, a);
-            else if (D == 128) hipLaunchKernelGGL((fwd_kernel<128, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, a);
-            else if (mixed) hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true, mixed64>), ids, dim3(256), 0, st, a);
-            else hipLaunchKernelGGL((fwd_kernel<64, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, a);
+            if (mixed) hipLaunchKernelGGL((fwd_kernel<D, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true, can_mix>), ids, dim3(256), 0, st, a);
+            else hipLaunchKernelGGL((fwd_kernel<D, 4, MASK, SCORE, BOUNDED, PAGED, false, false, false, true>), ids, dim3(256), 0, st, a);
         }
         return FLEXATTN_OK;
     }
-#define FLEXATTN_LAUNCH(DD, NW)                                                                            \
-    hipLaunchKernelGGL((fwd_kernel<DD, NW, MASK, SCORE, BOUNDED, PAGED>), dim3(grid), dim3(NW * 64), 0, st, a); \
-    return FLEXATTN_OK;
-    if (D == 128 && Bq == 128) {
+    if (Bq != 128) return FLEXATTN_ERR_UNSUPPORTED;
+    if constexpr (D == 128) {
         if constexpr (fwd_units<128, 4, MASK, SCORE>() != FwdUnits::kNever) {
             if (units_pay<MASK, SCORE>(a, grid)) {
                 order_units(a.NR, 3);
@@ -1030,9 +1023,7 @@ int launch_fwd_shape(const FwdArgs& args, int D, int Bq, hipStream_t st) {
             }
         }
         order_units(a.NR, 2);
-        FLEXATTN_LAUNCH(128, 4)
-    }
-    if (D == 64 && Bq == 128) {
+    } else {
         constexpr bool dense = !mask_uses(MASK, FLEXATTN_M_SLIDING_WINDOW | FLEXATTN_M_DOCUMENT | FLEXATTN_M_NEIGHBORHOOD);
         if constexpr (fwd_plain<64, 4, BOUNDED>() && dense) {
             if (!plain_pays<SCORE>(a.kv_len, grid, rows_shape.uneven)) {
@@ -1042,18 +1033,23 @@ int launch_fwd_shape(const FwdArgs& args, int D, int Bq, hipStream_t st) {
             }
         }
         order_units(a.NR, 4);
-        FLEXATTN_LAUNCH(64, 4)
     }
-#undef FLEXATTN_LAUNCH
-    return FLEXATTN_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL((fwd_kernel<D, 4, MASK, SCORE, BOUNDED, PAGED>), dim3(grid), dim3(256), 0, st, a);
+    return FLEXATTN_OK;
 }
 
 template <uint32_t MASK, uint32_t SCORE, bool PAGED = false>
 int launch_fwd_variant(const FwdArgs& a, int D, int Bq, hipStream_t st) {
-    if constexpr (SCORE & FLEXATTN_SCORE_SOFTCAP) {
-        if (2.0f * a.p.softcap * kLog2e <= 100.0f) return launch_fwd_shape<MASK, SCORE, true, PAGED>(a, D, Bq, st);
-    }
-    return launch_fwd_shape<MASK, SCORE, false, PAGED>(a, D, Bq, st);
+    auto of = [&](auto head_dim) {
+        constexpr int DD = decltype(head_dim)::value;
+        if constexpr (SCORE & FLEXATTN_SCORE_SOFTCAP) {
+            if (2.0f * a.p.softcap * kLog2e <= 100.0f) return launch_fwd_shape<DD, MASK, SCORE, true, PAGED>(a, Bq, st);
+        }
+        return launch_fwd_shape<DD, MASK, SCORE, false, PAGED>(a, Bq, st);
+    };
+    if (D == 64) return of(std::integral_constant<int, 64>{});
+    if constexpr (PartialMask<MASK>::kCells) return FLEXATTN_ERR_UNSUPPORTED;        // (variant_of: the general kernels)
+    else return of(std::integral_constant<int, 128>{});
 }
 
 }  // namespace flexattn

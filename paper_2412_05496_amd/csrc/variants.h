@@ -26,10 +26,10 @@ inline int find_variant(uint32_t mask, uint32_t score) {
     return -1;
 }
 
-// the variant of a call (of a valid mask)
-inline int variant_of(uint32_t mask, uint32_t score, const flexattn_mod_params* p, bool backward) {
+// the variant of a call (of a valid mask).  (Forward at D = 128: cells' masks spill 16 and 28 registers more there, 469 -> 682 us)
+inline int variant_of(uint32_t mask, uint32_t score, const flexattn_mod_params* p, bool backward, int D) {
     if (!mask_uses(mask, FLEXATTN_M_NEIGHBORHOOD)) return find_variant(mask, score);
-    if (canvas_in_cells(*p)) return find_variant(mask | (p->na_layout == FLEXATTN_NA_MORTON ? kCanvasCellsZ : kCanvasCells), score);
+    if ((backward || D == 64) && canvas_in_cells(*p)) return find_variant(mask | (p->na_layout == FLEXATTN_NA_MORTON ? kCanvasCellsZ : kCanvasCells), score);
     return find_variant(canvas_by_tags(*p, backward) ? mask | kCanvasByTags : mask, score);
 }
 

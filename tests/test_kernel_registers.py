@@ -56,3 +56,12 @@ def test_the_others_pay_nothing_for_divided_groups_and_steps_left_out():
     assert {k: v for k, v in seen.items() if v > SCRATCH.get(k, 0)} == {}
     # a relative bias spills where it leaves steps out, which launches with few hidden steps then do not
     assert {k: v for k, v in leaving.items() if v} == {(128, 2051, 2, 0, 0): 24}
+
+
+@pytest.mark.skipif(not os.path.exists(build.LIB), reason="the library is not built")
+def test_no_forward_is_compiled_twice():
+    """Canvases in cells have forward kernels of their own at D = 64 only: at D = 128 they would be those of any canvas again."""
+    names = list(kernels(build.LIB))
+    cells = [n for n in names if re.match(r"_ZN8flexattn10fwd_kernelILi(64|128)ELi\dELj(160|224)E", n)]
+    assert any("ILi64E" in n for n in cells) and not [n for n in cells if "ILi128E" in n]
+    assert any(re.match(r"_ZN8flexattn10fwd_kernelILi128ELi\dELj32E", n) for n in names)
