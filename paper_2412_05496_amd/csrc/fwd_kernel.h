@@ -241,6 +241,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     __shared__ float s_rel[Score::kRel ? kRelTableMax : 1];           // relative-bias row of the head
     using Mask = PartialMask<MASK>;
     constexpr bool CELLS = Mask::kCells;
+    static_assert(!(CELLS && BOUNDED), "cells: the running maximum's branch sets their masks");
     __shared__ __attribute__((aligned(256))) uint32_t s_tag[SPLIT ? NW : UNITS ? 3 : 2][Mask::kTags ? kTileKV : 4];   // tags of a PARTIAL tile's keys, per buffer (SPLIT: wave)
 
     constexpr bool kHiddenTable = Mask::kCanvas && (UNITS || PLAIN || SPLIT || PAIRS);
@@ -442,7 +443,7 @@ __global__ __launch_bounds__(NW * 64, (fwd_waves_per_simd<D, SCORE, UNITS, PLAIN
     };
     // The probabilities of a block as two bf16 fragments, and this lane's part of the row sum: over the bf16-rounded
     // probabilities, the values P V is computed from, two at a time (dot product of a packed pair with (1, 1), fp32 accumulation).
-    typename Mask::CellMasks cells = {};      // of the block that is worked on
+    typename Mask::CellMasks cells = {{~0u, ~0u}, ~0u};      // of the block that is worked on
     auto weigh = [&](const f32x16& s, bf16x8 (&pf)[2], auto&& prob) __attribute__((always_inline)) {
         float psum[2] = {0.0f, 0.0f};
 #pragma unroll
