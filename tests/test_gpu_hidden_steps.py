@@ -11,11 +11,12 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def gradients(mask_id, mask_mod, S, Bq, Bk, params, everything=False, Hq=2, q_len=None, capped=False):
-    """everything: all blocks are listed as PARTIAL, whatever the mask hides of them."""
+def gradients(mask_id, mask_mod, S, Bq, Bk, params, everything=False, Hq=2, Hkv=1, B=0, q_len=None, capped=False):
+    """everything: all blocks are listed as PARTIAL, whatever the mask hides of them.  The entries of the batch have the same inputs: every one is compared."""
     import paper_2412_05496_amd as fa
-    D, q_len, Hkv = 64 if capped else 128, q_len or S, 1
-    B = 60000 // S + 1          # (more than 768 workgroups: all that run at once look for no steps to leave out)
+    D, q_len = 64 if capped else 128, q_len or S
+    parts = B > 0               # (the groups' heads are divided)
+    B = B or 60000 // S + 1     # (more than 768 workgroups: all that run at once look for no steps to leave out)
     score_id, score = fa.SCORE_IDENTITY, fo.Identity()
     if capped:                  # (at D = 64 a bias and a soft-cap take that kernel)
         bias = torch.tensor([-0.03, 0.01])[:Hq]
@@ -26,9 +27,9 @@ def gradients(mask_id, mask_mod, S, Bq, Bk, params, everything=False, Hq=2, q_le
         params.rel_bias = table.to(DEV)
         score_id, score = fa.SCORE_REL_BIAS, fo.RelBias(table.double())
     g = torch.Generator().manual_seed(S + Bq + Bk)
-    Q, dO = (torch.randn(B, Hq, q_len, D, generator=g).to(torch.bfloat16) for _ in range(2))
-    K, V = (torch.randn(B, Hkv, S, D, generator=g).to(torch.bfloat16) for _ in range(2))
-    refs = fo.flex_attention_backward(*(t[:1].float() for t in (Q, K, V, dO)), score, mask_mod, D ** -0.5)
+    Q, dO = (torch.randn(1, Hq, q_len, D, generator=g).to(torch.bfloat16) for _ in range(2))
+    K, V = (torch.randn(1, Hkv, S, D, generator=g).to(torch.bfloat16) for _ in range(2))
+    refs = fo.flex_attention_backward(*(t.float() for t in (Q, K, V, dO)), score, mask_mod, D ** -0.5)
     bm = fa.alloc_blockmask(1, 1, q_len, S, Bq, Bk, device=torch.device(DEV))
     fa.flexattn_blockmask_build(mask_id, params, bm)
     if everything:
@@ -38,24 +39,29 @@ def gradients(mask_id, mask_mod, S, Bq, Bk, params, everything=False, Hq=2, q_le
             full.zero_()
             idx.copy_(torch.arange(n, dtype=torch.int32).expand(idx.shape))
         bm.stats[0], bm.stats[1] = NR * NC, 0
-    Q, K, V, dO = (t.to(DEV) for t in (Q, K, V, dO))
-    O, LSE = torch.empty_like(Q), torch.empty(B, Hq, q_len, device=DEV)
+    Q, K, V, dO = (t.to(DEV).expand(B, -1, -1, -1) for t in (Q, K, V, dO))
+    unwritten = lambda t: torch.full(t.shape, float("nan"), dtype=t.dtype, device=DEV)
+    O, LSE = unwritten(Q), torch.full((B, Hq, q_len), float("nan"), device=DEV)
     head = (score_id, mask_id, params, bm, D ** -0.5)
     fa.flexattn_forward(Q, K, V, *head, O, LSE)
     n = hp.nonempty_blocks(bm)
     for stored in (False, True):
         dQ, Vs, _ = hp.dq_and_v_in_one_storage(Q, V)
-        got = [dQ, torch.full_like(K, float("nan")), torch.full_like(V, float("nan"))]
+        got = [dQ, unwritten(K), unwritten(V)]
         if stored:
             ws = hp.dirty_stored_workspace(Q, K, bm, n)
             fa.flexattn_backward_stored(Q, K, Vs, O, dO, LSE, *head, *got, n, ws)
             assert hp.ds_written(ws, bm, n)
         else:
-            got[0] = torch.full_like(Q, float("nan"))
-            fa.flexattn_backward(Q, K, V, O, dO, LSE, *head, *got)
+            got[0] = unwritten(Q)
+            ws = torch.full((max(fa.flexattn_backward_workspace_bytes(Q, K), 1),), 0xFF, dtype=torch.uint8, device=DEV)
+            fa.flexattn_backward(Q, K, V, O, dO, LSE, *head, *got, ws)
         torch.cuda.synchronize()
+        room = hp.room_for_parts(Q, K)
+        assert bool((ws[ws.numel() - room:] != 0xFF).any()) == parts
         for name, t, ref in zip(("dQ", "dK", "dV"), got, refs):
             hp.check_grad(name, t[:1], ref)
+            assert torch.equal(t, t[:1].expand_as(t)), name
 
 
 MASKS = {"causal": lambda fa, w: (fa.MASK_CAUSAL, fo.causal_mask, fa.ModParams()),
@@ -91,3 +97,13 @@ def test_columns_without_a_visible_step():
     import paper_2412_05496_amd as fa
     mask_id, mask_mod, params = MASKS["causal"](fa, 0)
     gradients(mask_id, mask_mod, 700, 128, 64, params, everything=True, q_len=200)
+
+
+@pytest.mark.parametrize("mask,S,w,Bq,Bk,Hq,Hkv,B", [
+    ("causal", 1100, 0, 128, 128, 16, 2, 4), ("window", 1600, 1400, 128, 128, 8, 1, 6), ("prefix", 1100, 130, 64, 128, 16, 2, 4), ("causal", 2100, 0, 128, 64, 8, 4, 2)])
+def test_hidden_steps_of_divided_groups(mask, S, w, Bq, Bk, Hq, Hkv, B):
+    """Of 513 to 768 workgroups: the heads of a group are divided, and each part leaves its hidden steps out."""
+    import paper_2412_05496_amd as fa
+    mask_id, mask_mod, params = MASKS[mask](fa, w)
+    print(f"[case] {mask} S={S} blocks {Bq}x{Bk} heads {B} x {Hq} / {Hkv}", flush=True)
+    gradients(mask_id, mask_mod, S, Bq, Bk, params, Hq=Hq, Hkv=Hkv, B=B)
