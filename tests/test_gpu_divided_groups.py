@@ -227,3 +227,35 @@ def test_groups_that_stay_whole(B, Hq, Hkv, S, D, mask):
         assert bool((ws[scalars:] == 0xFF).all())
         got.append((dK, dV))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("D,score", [(64, "softcap"), (128, "softcap"), (64, "alibi"), (128, "alibi"), (64, "alibi_softcap"), (128, "rel_bias"), (64, "rel_bias")])
+def test_divided_groups_with_a_score_mod(D, score):
+    """The factor of a soft-cap's derivative belongs to dK's sums and not to dV's."""
+    import paper_2412_05496_amd as fa
+    print("[case]", D, score, flush=True)
+    B, Hq, Hkv, S = 1, 8, 1, 1100
+    gen = torch.Generator().manual_seed(D)
+    Q, dO = (torch.randn(B, Hq, S, D, generator=gen).to(torch.bfloat16) for _ in range(2))
+    K, V = (torch.randn(B, Hkv, S, D, generator=gen).to(torch.bfloat16) for _ in range(2))
+    bias, table = -2.0 ** -torch.arange(1.0, Hq + 1), 0.3 * torch.randn(Hq, 90, generator=gen)
+    params, mask_id, mask = mods(fa, "causal", S, B)
+    params.softcap, params.alibi_bias, params.rel_bias = 20.0, bias.to(DEV), table.to(DEV)
+    alibi, cap = fo.Alibi(bias.double()), fo.Softcap(20.0)
+    if score == "rel_bias":         # (compiled with a window or a prefix)
+        params.window, params.prefix_len, mask_id = 900, 40, fa.MASK_SWA_CAUSAL_OR_PREFIX
+        mask = fo.or_mask(fo.and_mask(fo.causal_mask, fo.sliding_window_mask(900)), fo.prefix_mask(40))
+    score_id, score_mod = {"softcap": (fa.SCORE_SOFTCAP, cap), "alibi": (fa.SCORE_ALIBI, alibi), "rel_bias": (fa.SCORE_REL_BIAS, fo.RelBias(table.double())),
+                           "alibi_softcap": (fa.SCORE_ALIBI | fa.SCORE_SOFTCAP, fo.Compose(alibi, cap))}[score]
+    bm = fa.alloc_blockmask(1, 1, S, S, 128, 64, device=DEV)
+    fa.flexattn_blockmask_build(mask_id, params, bm)
+    q, k, v, do = (t.to(DEV) for t in (Q, K, V, dO))
+    O, LSE = torch.empty_like(q), torch.empty(B, Hq, S, device=DEV)
+    head = (score_id, mask_id, params, bm, D ** -0.5)
+    fa.flexattn_forward(q, k, v, *head, O, LSE)
+    ws = torch.full((fa.flexattn_backward_workspace_bytes(q, k),), 0xFF, dtype=torch.uint8, device=DEV)
+    grads = [torch.full_like(t, float("nan")) for t in (q, k, k)]
+    fa.flexattn_backward(q, k, v, O, do, LSE, *head, *grads, ws)
+    assert bool((ws[ws.numel() - hp.room_for_parts(q, k):] != 0xFF).any())          # (divided)
+    for name, g, r in zip(("dQ", "dK", "dV"), grads, fo.flex_attention_backward(Q, K, V, dO, score_mod, mask, D ** -0.5)):
+        hp.check_grad(name, g, r)
