@@ -263,7 +263,7 @@ __device__ __forceinline__ int canvas_step_bits(const flexattn_mod_params& p, in
 // from all four waves: every other column of 64 keys has one at its diagonal if Bq = 128 or Bk = 128, one at the window's far edge, and all have
 // one behind a q_len in the first half of its block.  us, B x H = 256, D = 128: causal, S = 1024 214 -> 207,
 // S = 300 (512) 79.6 -> 72; window of 512, S = 4096 (64) 218 -> 209; window of 195, soft-cap, Bq = 64, Bk = 128, S = 2427 (512) 673 -> 608;
-// causal, 128 x 128, S = 947, Hkv = 2 (48) 261 -> 237; long causal columns 1.00x to 1.02x;
+// causal, ALiBi and soft-cap, 128 x 128, S = 947, Hkv = 2 (48) 261 -> 237; long causal columns 1.00x to 1.02x;
 // D = 64, ALiBi and soft-cap, S = 1000 (256) 124 -> 120, 300 (1024) 92.9 -> 80.9, 128 x 128, S = 947, Hkv = 2 (48) 170 -> 161.
 // (With own rows such a step has no more than S and dP, and short columns lose by the walk's layout what that is: 16 x 16 heads, S = 1024,
 // Bq = 64 99 -> 101, B = 8, S = 500 24.3 -> 25.2.)

@@ -296,7 +296,7 @@ __host__ __device__ inline UnitSets one_by_one(int units) { return {0, units >= 
 // 109 -> 102, 2048 x 256 178 -> 165 / 238 -> 217 / 344 -> 336, 4096 x 64 181 -> 153 / 231 -> 219 / 317 -> 298, 8192 x 64 635 -> 577 / 821 -> 764 / 1145 -> 1122, 1500 x 40
 // 27 -> 22 / 32 -> 27 / 42 -> 35, 200 x 2048 43 -> 43 / 57 -> 54 / 128 -> 112, soft-cap, 1024 x 256 86 -> 68 / 113 -> 89 / 125 -> 117, 16 / 4 heads, 2048 x 128
 // 92 -> 83 / 122 -> 121 / 189 -> 156; D = 128, 1024 x 256 113 -> 98 / 150 -> 135 / 224 -> 215, 2048 x 128 174 -> 157 / 230 -> 210 / 337 -> 328, 8192 x 32 552 -> 532 /
-// 741 -> 710 / 1069 -> 1081; the captured sums of ALiBi, D = 64, 2048 x 64 82 -> 60; documents of 256 to 4096, D = 64, 8192 x 64 244 -> 218 / 302 -> 273 (columns gain
+// 741 -> 710 (its columns one by one); the captured sums of ALiBi, D = 64, 2048 x 64 82 -> 60; documents of 256 to 4096, D = 64, 8192 x 64 244 -> 218 / 302 -> 273 (columns gain
 // nothing: 407), D = 128, 4096 x 64 224 -> 189 / 286 -> 252; windows of 512, D = 64, 4096 x 64 54 -> 53 / 69 -> 67.
 constexpr int kRowsAbreast = 8, kColumnsAbreast = 4;
 inline UnitSets units_abreast(int units, int per_unit, int per_cu, int most) {
@@ -1043,7 +1043,7 @@ inline bool canvas_by_tags(const flexattn_mod_params& p, bool backward) {
 // PartialMask::rectangle.  Those of a cell's keys are the widest: 2 r + 8 columns, 3 r + 8 where they reach a border (and up to 7 before
 // the first, a multiple of 8, but for the left border's), so r <= 16; on a canvas both of whose borders they reach, all of its 4 r + 8.
 // (Positions that start elsewhere, other tiles, which cut 32 tokens otherwise, and wider windows are compared as before.)  Cells against
-// that, us, B = 4, H = 16, D = 64, forward / dQ / dK/dV: 128 x 128, K = 13, tiles of 8 241 -> 232 / 296 -> 276 / 450; 64 x 64, K = 27,
+// that, us, B = 4, H = 16, D = 64, forward / dQ / dK/dV: 128 x 128, K = 13, tiles of 8 241 -> 232 / 296 -> 276 / 450 -> 450; 64 x 64, K = 27,
 // tiles of 8 128 -> 115 / 158 -> 142 / 224 -> 219, K = 3 51.7 -> 51.4 / 64.1 -> 59.5 / 101.7 -> 100; K = 9, Morton 51.7 -> 49.6 / 65.6 -> 59.7 /
 // 102.3 -> 99.4.  At D = 128 dQ 1.04x to 1.12x, dK/dV 1.00x to 1.03x; the forward compares as before.
 inline bool canvas_in_cells(const flexattn_mod_params& p) {
