@@ -77,8 +77,7 @@ struct BwdArgs {
 // Among how many workgroups the query heads of a group are divided.  One that takes them all walks G times the steps of a column: few KV heads
 // leave most of the chip idle, and end with the longest column alone.  A part costs its sums in fp32, 128 bytes a key and D / 16 each way, and all a launch that
 // adds them up (3 us).  So: up to 768 workgroups (D = 64: all that run at once), as many parts as spare the longest column's workgroup 48 steps of 64 rows (D = 128: 32, whose steps
-// are longer) or more for each beyond the first, or 12 (6) while they are no more than half of the CUs.  Parts of unlike size, whose larger ones end the launch, only while
-// the CUs are hardly shared, or, of a large group, where sharing them costs less than a head.  worth(parts): what else speaks against it (parts_pay).
+// are longer) or more for each beyond the first, or 12 (6) while they are no more than half of the CUs.  worth(parts): what else speaks against it (parts_pay).
 // us, dK/dV, whole groups -> this, S x query / KV heads, causal: D = 64, 4096 x 8 / 1 136 -> 54, 1500 x 16 / 2
 // 59 -> 34, 3000 x 32 / 4 114 -> 106, 12000 x 16 / 2 811 -> 702, 700 x 8 / 1 35 -> 17; D = 128, 1500 x 8 / 1 126 -> 42, 3000 x 16 / 2 241 -> 99, 700 x 64 / 8 70 -> 67,
 // 3000 x 4 / 1 125 -> 44, 6000 x 8 / 4 221 -> 166; no mask, D = 128, 6000 x 16 / 2 863 -> 602; window of
@@ -93,8 +92,7 @@ int kv_head_parts(int64_t units, int G, int kv_len, int D, int64_t longest_colum
     int parts = 1;
     for (int p = 2; p <= G && p <= 8 && tiles * p <= 768; p *= 2) {
         const int64_t groups = tiles * p, spared = G - (G + p - 1) / p;     // heads
-        const bool unlike = G % p && groups > (D == 64 ? 128 : 256) && !(D == 64 && G > 2 * p) && !(G >= 3 * p && groups <= 512);
-        if (!unlike && steps * spared >= (int64_t)(p - 1) * (groups <= 128 ? (D == 64 ? 12 : 6) : (D == 64 ? 48 : 32)) && worth(p)) parts = p;
+        if (steps * spared >= (int64_t)(p - 1) * (groups <= 128 ? (D == 64 ? 12 : 6) : (D == 64 ? 48 : 32)) && worth(p)) parts = p;
     }
     return parts;
 }
