@@ -259,3 +259,56 @@ def test_divided_groups_with_a_score_mod(D, score):
     assert bool((ws[ws.numel() - hp.room_for_parts(q, k):] != 0xFF).any())          # (divided)
     for name, g, r in zip(("dQ", "dK", "dV"), grads, fo.flex_attention_backward(Q, K, V, dO, score_mod, mask, D ** -0.5)):
         hp.check_grad(name, g, r)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,S,D", [(8, 2, 1, 2048, 128), (3, 4, 2, 4096, 64)])
+def test_documents_that_change_between_replays(B, Hq, Hkv, S, D):
+    """The question is asked on the device, of the lists as they are when a captured step runs: short documents and long ones in turn."""
+    import paper_2412_05496_amd as fa
+    print("[case] replays", B, Hq, Hkv, S, D, flush=True)
+    gen = torch.Generator().manual_seed(S)
+    q, do = (torch.randn(B, Hq, S, D, generator=gen).to(torch.bfloat16).to(DEV) for _ in range(2))
+    k, v = (torch.randn(B, Hkv, S, D, generator=gen).to(torch.bfloat16).to(DEV) for _ in range(2))
+    params = fa.ModParams()
+    params.doc_ids = torch.zeros(B, S, dtype=torch.int32, device=DEV)
+    bm = fa.alloc_blockmask(B, 1, S, S, 128, 64, device=DEV)
+    bm_ws = torch.empty(max(fa.flexattn_blockmask_workspace_bytes(B, 1, S, S, 128, 64), 1), dtype=torch.uint8, device=DEV)
+    O, LSE = torch.empty_like(q), torch.empty(B, Hq, S, device=DEV)
+    grads = [torch.empty_like(t) for t in (q, k, k)]
+    ws = torch.empty(fa.flexattn_backward_workspace_bytes(q, k), dtype=torch.uint8, device=DEV)
+    head = (fa.SCORE_IDENTITY, fa.MASK_DOCUMENT_CAUSAL, params, bm, D ** -0.5)
+
+    def step():
+        fa.flexattn_blockmask_build(fa.MASK_DOCUMENT_CAUSAL, params, bm, bm_ws)
+        fa.flexattn_forward(q, k, v, *head, O, LSE)
+        fa.flexattn_backward(q, k, v, O, do, LSE, *head, *grads, ws)
+
+    def load(length):
+        params.doc_ids.copy_((torch.arange(S, dtype=torch.int32) // length).expand(B, S))
+
+    def parts_written():
+        return bool((ws[ws.numel() - hp.room_for_parts(q, k):] != 0xFF).any())
+
+    lengths, eager = (50, 1500, 90, 700), []
+    for n in lengths:
+        load(n)
+        ws.fill_(0xFF)
+        step()
+        torch.cuda.synchronize()
+        assert parts_written() == (n > 100)
+        eager.append([t.clone() for t in grads])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for _ in range(2):
+        for n, want in zip(lengths, eager):
+            load(n)
+            ws.fill_(0xFF)
+            for t in grads:
+                t.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert parts_written() == (n > 100)
+            for got, ref in zip(grads, want):
+                assert torch.equal(got, ref)
+            (torch.randn(256, 256, device=DEV) @ torch.randn(256, 256, device=DEV)).sum().item()       # eager work between the replays
