@@ -78,14 +78,14 @@ struct BwdArgs {
 // leave most of the chip idle, and end with the longest column alone.  A part costs its sums in fp32, 128 bytes a key and D / 16 each way, and all a launch that
 // adds them up (3 us).  So: up to 768 workgroups (D = 64: all that run at once), as many parts as spare the longest column's workgroup 48 steps of 64 rows (D = 128: 32, whose steps
 // are longer) or more for each beyond the first, or 12 (6) while they are no more than half of the CUs.  worth(parts): what else speaks against it (parts_pay).
-// us, dK/dV, whole groups -> this, S x query / KV heads, causal: D = 64, 4096 x 8 / 1 136 -> 54, 1500 x 16 / 2
-// 59 -> 34, 3000 x 32 / 4 114 -> 106, 12000 x 16 / 2 811 -> 702, 700 x 8 / 1 35 -> 17; D = 128, 1500 x 8 / 1 126 -> 42, 3000 x 16 / 2 241 -> 99, 700 x 64 / 8 70 -> 67,
-// 3000 x 4 / 1 125 -> 44, 6000 x 8 / 4 221 -> 166; no mask, D = 128, 6000 x 16 / 2 863 -> 602; window of
-// 1000, D = 64, 6000 x 32 / 4 162 -> 129.  More parts: 1500 x 32 x 8 / 1, D = 128, two 375, whole 342; window of 1024, 4 x 5000 x 16 / 2, D = 64, two 208, whole 198, no mask, 12653 x 8 / 2, two 843, whole 797;
-// shorter ones: 300 x 2 / 1, D = 64 14.4, whole 11.2.  Parts of unlike size, whole / two / four: 6000 x 5 / 1, no mask, D = 64 137 / - / 195, 4000 x 9 / 3, causal, D = 128 125 / 160, 1500 x 18 / 6 53 / 68, but
-// no mask, 1500 x 7 / 1, D = 64 56 / 38 / 25.
+// us, dK/dV, whole groups -> this, S x query / KV heads, causal: D = 64, 4096 x 8 / 1 137 -> 55, 1500 x 16 / 2
+// 60 -> 33, 3000 x 32 / 4 112 -> 105, 700 x 8 / 1 35 -> 16; D = 128, 1500 x 8 / 1 126 -> 41, 3000 x 16 / 2 242 -> 95,
+// 3000 x 4 / 1 124 -> 42, 6000 x 8 / 4 220 -> 162; no mask, D = 128, 6000 x 16 / 2 825 -> 574; window of
+// 1000, D = 64, 6000 x 32 / 4 151 -> 124.  More parts: 1500 x 32 x 8 / 1, D = 128, two 375, whole 342; window of 1024, 4 x 5000 x 16 / 2, D = 64, two 208, whole 198, no mask, 12653 x 8 / 2, two 843, whole 797;
+// shorter ones: 300 x 2 / 1, D = 64 14.4, whole 11.2.
 // Over 7695 launches (one to sixteen KV heads, groups of 2 to 16, S = 300 to 12000; no mask, causal with and without a soft-cap, a window, a window or a prefix, documents of 16 to 200 and of 256 to
-// 4096, canvases) three are slower than whole, by 3 to 5 %; all together, divided or not, they are 1.21 (D = 64) and 1.38 times as fast.
+// 4096, canvases) three were slower than whole, by 3 to 5 %; all together, divided or not, they were 1.21 (D = 64) and 1.38 times as fast.
+// That sweep was made before parts_pay's lines for parts of unlike size were last moved, and not again since.
 template <class Worth>
 int kv_head_parts(int64_t units, int G, int kv_len, int D, int64_t longest_column, Worth&& worth) {
     const int64_t tiles = units * ((kv_len + 63) / 64), steps = (longest_column + 63) / 64;

@@ -697,7 +697,8 @@ int64_t longest_column(const BwdArgs& a) {
 // use the chip already: two parts that would be split among fewer, parts of a single head that would not be split, small groups of more workgroups than two to a CU and parts of unlike size of more than one lose.  Parts of unlike size, whose larger ones end the launch, only
 // while the CUs are hardly shared, or, of a large group, where sharing them costs less than a head, or where the few long columns of a prefix are what a launch is made of (us, dK/dV, whole / two / four,
 // S x query / KV heads: D = 64, no mask, 4000 x 4 / 2 45 / 64, 1500 x 20 / 5 37 / 51 / 41, 1000 x 56 / 8 45 / 65 / 49, causal, 4000 x 8 / 4 48 / 54, 4000 x 12 / 3 75 / 75 / 82; a window of 200 or a prefix of 64, 4000 x 12 / 6
-// 45 / 60, of 300 or 50, 2048 x 40 / 8 66 / 79, but 7000 x 6 / 3 70 / 53, 12000 x 4 / 2 114 / 67, D = 128 284 / 155).
+// 45 / 60, of 300 or 50, 2048 x 40 / 8 66 / 79, but 7000 x 6 / 3 70 / 53, 12000 x 4 / 2 114 / 67, D = 128 284 / 155; unlike parts: no mask,
+// 6000 x 5 / 1, D = 64 137 / - / 195, causal, 4000 x 9 / 3, D = 128 125 / 160, 1500 x 18 / 6 53 / 68, but no mask, 1500 x 7 / 1, D = 64 56 / 38 / 25, causal with a soft-cap, 3888 x 35 / 5, D = 128 580 / 393).
 // Documents, many of which the host cannot tell to be short, spare a workgroup little and pay the sums of all keys.  So few sums for each head that is spared that documents of 16 to 200 tokens do not lose by
 // more than 3 % (D = 128, 1500 x 4 / 2, of 16 to 100, 8 %: 14.7 / 15.7, of 256 to 4096 40 / 28), or else they ask (kPartsIfLong).  Whole groups that are split do not ask, bwd_dkdv_kernel is no match for them: 3000 x 2 x 8 / 2,
 // D = 64, documents of 16 to 100, split 17, in two 23, whole after the question 27, of 256 to 4096 97 / 86; 9000 x 4 / 1 18 / - / 21 and 122 / - / 63.
